@@ -11,6 +11,8 @@ namespace hm {
 constexpr int kWave = 64;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_align2 __attribute__((aligned(2)));   // the same at the alignment of a bf16 / fp32 element
+typedef u32x4 u32x4_align4 __attribute__((aligned(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }

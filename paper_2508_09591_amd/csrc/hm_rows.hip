@@ -32,6 +32,7 @@
 #include "hm_device.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace hm {
 
@@ -48,7 +49,8 @@ constexpr int kCombineBytesInFlight = 128 * 1024;   // per CU, what the cap on r
 
 struct RowParams {
   int32_t T, K;
-  int32_t nvec;   // 16-byte vectors per row
+  int32_t H;      // elements per row
+  int32_t nvec;   // 16-byte vectors per row (the last one overlaps its neighbour where H is no multiple)
   int32_t nseg;   // segments per row
   int64_t nunits; // T * nseg
   const int32_t *slot_row;
@@ -66,18 +68,50 @@ __device__ __forceinline__ bool unit_of_wave(const RowParams &p, int &t, int &se
   return true;
 }
 
+// How a row's 16-byte vectors are addressed.  Whole: rows are a multiple of 16 bytes and 16-byte
+// aligned.  Ragged: any length of at least one vector, at the alignment of its elements.  Vector v
+// then starts at element min(v * P, H - P), so the last one overlaps the one before it: the values in
+// the overlap are computed twice from the same inputs, to the same bits, and stored twice, which
+// needs neither a tail loop nor a mask.
+template <typename ELEM>
+struct WholeRows {
+  typedef ELEM elem;
+  typedef u32x4 vec;
+  static __device__ __forceinline__ const vec *at(const void *base, const RowParams &p, int64_t row, int v) {
+    return (const vec *)base + (row * p.nvec + v);
+  }
+};
+template <typename ELEM>
+struct RaggedRows {
+  typedef ELEM elem;
+  typedef std::conditional_t<sizeof(ELEM) == 2, u32x4_align2, u32x4_align4> vec;
+  static __device__ __forceinline__ const vec *at(const void *base, const RowParams &p, int64_t row, int v) {
+    constexpr int P = 16 / sizeof(ELEM);
+    return (const vec *)((const ELEM *)base + (row * p.H + min(v * P, p.H - P)));
+  }
+};
+template <typename ACCESS>
+__device__ __forceinline__ u32x4 load_row(const void *base, const RowParams &p, int64_t row, int v) {
+  return __builtin_nontemporal_load(ACCESS::at(base, p, row, v));
+}
+template <typename ACCESS>
+__device__ __forceinline__ void store_row(void *base, const RowParams &p, int64_t row, int v, u32x4 value) {
+  __builtin_nontemporal_store(value, const_cast<typename ACCESS::vec *>(ACCESS::at(base, p, row, v)));
+}
+
 // ---------------------------------------------------------------------------------------------
 // dispatch: packed[slot_row[t,k], :] = x[t, :] for kept slots
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p, const u32x4 *__restrict__ x,
-                                                                     u32x4 *__restrict__ packed, int64_t packed_rows) {
+template <typename ACCESS>
+__global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p, const void *__restrict__ x,
+                                                                     void *__restrict__ packed, int64_t packed_rows) {
   int t, seg;
   if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
   const int lane = lane_id();
   const int v = seg * kWave + lane;
   const bool in_row = v < p.nvec;
   u32x4 r = {0u, 0u, 0u, 0u};
-  if (in_row) r = x[(int64_t)t * p.nvec + v];   // does not wait for the row list below
+  if (in_row) r = *ACCESS::at(x, p, t, v);   // does not wait for the row list below
   int my_row = -1;
   if (lane < p.K) {
     const int64_t s = (int64_t)t * p.K + lane;
@@ -92,7 +126,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p
     const int k = __builtin_ctzll(todo);
     todo &= todo - 1;
     const int row = read_lane(my_row, k);
-    if (in_row) store_stream(packed + (int64_t)row * p.nvec + v, r);
+    if (in_row) store_row<ACCESS>(packed, p, row, v, r);
   }
 }
 
@@ -236,10 +270,10 @@ struct RowF32 {
 // MIX = false: hm_combine.  MIX = true: hm_combine_mix, the sum times the reciprocal of the sum of
 // the merged weights (added in ascending k of each row's first slot); zero for a row without a
 // valid slot.  (A true division per element made the kernel ALU-bound: 8 divisions per 16 bytes.)
-template <bool MIX, int U, int R, typename ROW>
-__global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams p, const u32x4 *__restrict__ y,
+template <bool MIX, int U, int R, typename ROW, typename ACCESS>
+__global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams p, const void *__restrict__ y,
                                                                        int64_t y_rows, const float *__restrict__ topk_weights,
-                                                                       u32x4 *__restrict__ out) {
+                                                                       void *__restrict__ out) {
   int t, seg;
   if (!unit_of_wave<kCombineThreads>(p, t, seg)) return;
   const int lane = lane_id();
@@ -290,10 +324,9 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
         todo &= todo - 1;
         const int row = read_lane(my_row, k);
         a[j] = read_lane(agg, k);
-        const u32x4 *src = y + (int64_t)row * p.nvec;
 #pragma unroll
         for (int i = 0; i < U; ++i)
-          if (v0 + i * kWave < p.nvec) r[j][i] = load_stream(src + v0 + i * kWave);
+          if (v0 + i * kWave < p.nvec) r[j][i] = load_row<ACCESS>(y, p, row, v0 + i * kWave);
       }
     }
 #pragma unroll
@@ -304,7 +337,6 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
       }
     }
   }
-  u32x4 *dst = out + (int64_t)t * p.nvec;
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     if (v0 + i * kWave < p.nvec) {
@@ -312,7 +344,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[i][e] = acc[i][e] * inv_wsum;
       }
-      store_stream(dst + v0 + i * kWave, ROW::pack(acc[i]));
+      store_row<ACCESS>(out, p, t, v0 + i * kWave, ROW::pack(acc[i]));
     }
   }
 }
@@ -321,11 +353,11 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
 // is the first of its row, and row_weight[row] is the fp32 sum, in ascending k, of the weights of
 // the slots that share the row -- the number merge_slots computes.  A wave owns U KiB of the row;
 // the loads of up to R rows are issued before the first fma.
-template <bool MIX, int U, int R, typename ROW>
-__global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowParams p, const u32x4 *__restrict__ y,
+template <bool MIX, int U, int R, typename ROW, typename ACCESS>
+__global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowParams p, const void *__restrict__ y,
                                                                             int64_t y_rows,
                                                                             const float *__restrict__ row_weight,
-                                                                            u32x4 *__restrict__ out) {
+                                                                            void *__restrict__ out) {
   int t, seg;
   if (!unit_of_wave<kCombineThreads>(p, t, seg)) return;
   const int lane = lane_id();
@@ -369,10 +401,9 @@ __global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowP
         todo &= todo - 1;
         const int row = read_lane(my_row, k);
         a[j] = read_lane(agg, k);
-        const u32x4 *src = y + (int64_t)row * p.nvec;
 #pragma unroll
         for (int i = 0; i < U; ++i)
-          if (v0 + i * kWave < p.nvec) r[j][i] = load_stream(src + v0 + i * kWave);
+          if (v0 + i * kWave < p.nvec) r[j][i] = load_row<ACCESS>(y, p, row, v0 + i * kWave);
       }
     }
 #pragma unroll
@@ -383,7 +414,6 @@ __global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowP
       }
     }
   }
-  u32x4 *dst = out + (int64_t)t * p.nvec;
 #pragma unroll
   for (int i = 0; i < U; ++i) {
     if (v0 + i * kWave < p.nvec) {
@@ -391,7 +421,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowP
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[i][e] = acc[i][e] * inv_wsum;
       }
-      store_stream(dst + v0 + i * kWave, ROW::pack(acc[i]));
+      store_row<ACCESS>(out, p, t, v0 + i * kWave, ROW::pack(acc[i]));
     }
   }
 }
@@ -437,10 +467,10 @@ __global__ __launch_bounds__(kElemThreads) void combine_elems_kernel(RowParams p
 // ---------------------------------------------------------------------------------------------
 // transpose: gy[slot_row[t,k], :] = row_weight[row] * gout[t, :] for kept slots (fp32)
 // ---------------------------------------------------------------------------------------------
-template <typename ROW>
-__global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams p, const u32x4 *__restrict__ gout,
+template <typename ROW, typename ACCESS>
+__global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams p, const void *__restrict__ gout,
                                                                       const float *__restrict__ row_weight,
-                                                                      int64_t weight_rows, u32x4 *__restrict__ gy,
+                                                                      int64_t weight_rows, void *__restrict__ gy,
                                                                       int64_t gy_rows) {
   int t, seg;
   if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
@@ -448,7 +478,7 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
   const int v = seg * kWave + lane;
   const bool in_row = v < p.nvec;
   u32x4 r = {0u, 0u, 0u, 0u};
-  if (in_row) r = gout[(int64_t)t * p.nvec + v];
+  if (in_row) r = *ACCESS::at(gout, p, t, v);
   int my_row = -1;
   float my_w = 0.0f;
   if (lane < p.K) {
@@ -469,7 +499,7 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
     todo &= todo - 1;
     const int row = read_lane(my_row, k);
     const float a = read_lane(my_w, k);
-    if (in_row) store_stream(gy + (int64_t)row * p.nvec + v, ROW::scale(a, r));
+    if (in_row) store_row<ACCESS>(gy, p, row, v, ROW::scale(a, r));
   }
 }
 
@@ -494,10 +524,11 @@ __global__ __launch_bounds__(kElemThreads) void transpose_elems_kernel(RowParams
 
 static inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
-// Fills nvec / nseg / nunits for rows of `nvec` 16-byte vectors and sizes the grid.
-static inline bool grid_for_units(RowParams &p, int nvec, int vecs_per_lane, int block, dim3 &grid) {
-  p.nvec = nvec;
-  p.nseg = (nvec + kWave * vecs_per_lane - 1) / (kWave * vecs_per_lane);
+// Fills nvec / nseg / nunits for rows of H elements, `per_vec` to a 16-byte vector, and sizes the grid.
+static inline bool grid_for_units(RowParams &p, int H, int per_vec, int vecs_per_lane, int block, dim3 &grid) {
+  p.H = H;
+  p.nvec = (int)(((int64_t)H + per_vec - 1) / per_vec);
+  p.nseg = (p.nvec + kWave * vecs_per_lane - 1) / (kWave * vecs_per_lane);
   p.nunits = (int64_t)p.T * p.nseg;
   const int waves = block / kWave;
   const int64_t blocks = (p.nunits + waves - 1) / waves;
@@ -507,7 +538,7 @@ static inline bool grid_for_units(RowParams &p, int nvec, int vecs_per_lane, int
 }
 
 static inline bool grid_for_elems(RowParams &p, int64_t n, dim3 &grid) {
-  p.nvec = p.nseg = 0;
+  p.H = p.nvec = p.nseg = 0;
   p.nunits = 0;
   const int64_t blocks = (n + kElemThreads - 1) / kElemThreads;
   if (blocks > 2147483647LL) return false;
@@ -584,6 +615,13 @@ static inline CombineShape combine_shape(const hm_plan_out *plan, int32_t T, boo
   sh.waves_per_cu = waves;
   return sh;
 }
+template <bool MIX, typename ROW, typename ACCESS>
+static inline auto combine_kernel(const CombineShape &sh, bool weights_from_plan) {
+  if (!weights_from_plan) return combine_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW, ACCESS>;
+  if (sh.vecs == 1) return combine_plan_rows_kernel<MIX, 1, kCombineRowsPlan, ROW, ACCESS>;
+  if (sh.rows == kCombineRowsFew) return combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRowsFew, ROW, ACCESS>;
+  return combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW, ACCESS>;
+}
 
 }  // namespace hm
 
@@ -613,10 +651,12 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H % 8 == 0 && aligned16(x_bf16) && aligned16(packed_bf16)) {
-    if (!grid_for_units(p, H / 8, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds_cap_bytes(kCopyWavesPerCu, kCopyThreads),
-                       stream, p, (const u32x4 *)x_bf16, (u32x4 *)packed_bf16, packed_rows);
+  if (H >= 8) {
+    if (!grid_for_units(p, H, 8, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
+    const bool whole = H % 8 == 0 && aligned16(x_bf16) && aligned16(packed_bf16);
+    hipLaunchKernelGGL(whole ? dispatch_rows_kernel<WholeRows<uint16_t>> : dispatch_rows_kernel<RaggedRows<uint16_t>>, grid,
+                       dim3(kCopyThreads), lds_cap_bytes(kCopyWavesPerCu, kCopyThreads), stream, p, x_bf16, packed_bf16,
+                       packed_rows);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL(dispatch_elems_kernel, grid, dim3(kElemThreads), 0, stream, p, H, (const uint16_t *)x_bf16,
@@ -645,27 +685,17 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H % ROW::kPerVec == 0 && aligned16(y) && aligned16(out)) {
-    const int nvec = H / ROW::kPerVec;
+  if (H >= ROW::kPerVec) {
     const CombineShape sh = combine_shape(plan, T, from_plan);
-    if (!grid_for_units(p, nvec, sh.vecs, kCombineThreads, grid)) return HM_ERR_SHAPE;
-    if (from_plan) {
-      // rows the plan's weight array does not cover are treated like rows beyond y
-      const int64_t rows = y_rows < plan->row_capacity ? y_rows : plan->row_capacity;
-      if (sh.vecs == 1)
-        hipLaunchKernelGGL((combine_plan_rows_kernel<MIX, 1, kCombineRowsPlan, ROW>), grid, dim3(kCombineThreads),
-                           lds_cap_bytes(sh.waves_per_cu, kCombineThreads), stream, p, (const u32x4 *)y, rows,
-                           plan->row_weight, (u32x4 *)out);
-      else if (sh.rows == kCombineRowsFew)
-        hipLaunchKernelGGL((combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRowsFew, ROW>), grid, dim3(kCombineThreads), 0,
-                           stream, p, (const u32x4 *)y, rows, plan->row_weight, (u32x4 *)out);
-      else
-        hipLaunchKernelGGL((combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW>), grid, dim3(kCombineThreads), 0,
-                           stream, p, (const u32x4 *)y, rows, plan->row_weight, (u32x4 *)out);
-    } else {
-      hipLaunchKernelGGL((combine_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW>), grid, dim3(kCombineThreads), 0,
-                         stream, p, (const u32x4 *)y, y_rows, topk_weights, (u32x4 *)out);
-    }
+    if (!grid_for_units(p, H, ROW::kPerVec, sh.vecs, kCombineThreads, grid)) return HM_ERR_SHAPE;
+    const bool whole = H % ROW::kPerVec == 0 && aligned16(y) && aligned16(out);
+    // rows the plan's weight array does not cover are treated like rows beyond y
+    const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
+    const float *weights = from_plan ? plan->row_weight : topk_weights;
+    const unsigned lds = sh.vecs == 1 ? lds_cap_bytes(sh.waves_per_cu, kCombineThreads) : 0u;
+    const auto kernel = whole ? combine_kernel<MIX, ROW, WholeRows<elem>>(sh, from_plan)
+                              : combine_kernel<MIX, ROW, RaggedRows<elem>>(sh, from_plan);
+    hipLaunchKernelGGL(kernel, grid, dim3(kCombineThreads), lds, stream, p, y, rows, weights, out);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     // the element-wise kernel finds the first slot of each row itself and takes the row's merged
@@ -727,11 +757,12 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H % ROW::kPerVec == 0 && aligned16(gout) && aligned16(gy)) {
-    if (!grid_for_units(p, H / ROW::kPerVec, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
+  if (H >= ROW::kPerVec) {
+    if (!grid_for_units(p, H, ROW::kPerVec, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
+    const bool whole = H % ROW::kPerVec == 0 && aligned16(gout) && aligned16(gy);
     const unsigned lds = ROW::kPerVec == 4 ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;   // fp32 rows only
-    hipLaunchKernelGGL((transpose_rows_kernel<ROW>), grid, dim3(kCopyThreads), lds, stream, p, (const u32x4 *)gout,
-                       plan->row_weight, plan->row_capacity, (u32x4 *)gy, gy_rows);
+    hipLaunchKernelGGL((whole ? transpose_rows_kernel<ROW, WholeRows<elem>> : transpose_rows_kernel<ROW, RaggedRows<elem>>),
+                       grid, dim3(kCopyThreads), lds, stream, p, gout, plan->row_weight, plan->row_capacity, gy, gy_rows);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((transpose_elems_kernel<ROW>), grid, dim3(kElemThreads), 0, stream, p, H, (const elem *)gout,

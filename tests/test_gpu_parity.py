@@ -368,6 +368,62 @@ def test_vector_and_elementwise_kernels_agree_on_misaligned_views(hw, oracle):
     assert bf16_ulp_distance(hw.bf16_to_host(oa), x).max() == 0
 
 
+@pytest.mark.parametrize("H", [3, 5, 7, 9, 15, 505, 511, 513, 1030, 2049])
+@pytest.mark.parametrize("off", [0, 1])
+def test_rows_that_are_no_multiple_of_a_vector(hw, oracle, H, off):
+    """Every row call on rows of H elements, shorter than a vector, one past it and around the 64-vector
+    segments, at the start of an allocation and one element behind it: against the oracle, with poison
+    on both sides of every output that has to survive."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(H)
+    T, K, E, nodes, rpn = 37, 5, 24, 2, 3
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    ids[4] = -1                                                # a token without a row
+    w = rng.random((T, K), dtype=np.float32) + np.float32(0.05)
+    e2r = rng.integers(0, nodes * rpn, E, dtype=np.int32)
+    x = W.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
+    x32 = rng.standard_normal((T, H)).astype(np.float32)
+
+    def shifted(a, dtype):                                     # a copy of `a`, `off` elements into an allocation
+        store = torch.full((a.size + 16,), 77.0, dtype=dtype, device="cuda")
+        view = store[off:off + a.size].view(a.shape)
+        view.copy_(hw.to_dev_bf16(a) if dtype == torch.bfloat16 else hw.dev(a))
+        return view
+
+    def call(fn, shape, dtype, *args):                         # fn(..., out); the poison around out has to stay
+        n = shape[0] * shape[1]
+        store = torch.full((n + 48,), 77.0, dtype=dtype, device="cuda")
+        out = store[off + 16:off + 16 + n].view(shape)
+        fn(*args, out)
+        assert (store[:off + 16] == 77.0).all() and (store[off + 16 + n:] == 77.0).all(), fn
+        return hw.bf16_to_host(out) if dtype == torch.bfloat16 else out.cpu().numpy()
+
+    for level in (NONE, GPU):
+        ctx = "ragged rows H=%d off=%d level=%s" % (H, off, LEVEL[level])
+        print("case:", ctx, flush=True)
+        ora = oracle.plan(ids, w, e2r, nodes, rpn, level)
+        g = hw.GpuPlan(ids, w, e2r, nodes, rpn, level)
+        n = ora.total_rows
+        assert np.array_equal(call(B.hm_dispatch_pack, (n, H), torch.bfloat16, shifted(x, torch.bfloat16), g.plan),
+                              oracle.dispatch_pack(x, ora.row_token)), ctx
+        y = W.f32_to_bf16_bits((rng.random((n, H)) + 0.5).astype(np.float32))      # same-sign terms
+        y32 = (rng.random((n, H)) + 0.5).astype(np.float32)
+        y_d, y32_d = shifted(y, torch.bfloat16), shifted(y32, torch.float32)
+        for fn, ref in ((B.hm_combine, oracle.combine(y, w, ora.slot_row)), (B.hm_combine_mix, oracle.combine_mix(y, w, ora.slot_row))):
+            got = [call(fn, (T, H), torch.bfloat16, y_d, weights, g.plan) for weights in (g.w_d, None)]
+            assert bf16_ulp_distance(got[0], ref).max() <= 1 and np.array_equal(got[0], got[1]), (ctx, fn)
+        got = [call(B.hm_combine_f32, (T, H), torch.float32, y32_d, weights, g.plan) for weights in (g.w_d, None)]
+        ref = oracle.combine_f32(y32, w, ora.slot_row)
+        # all terms positive: the bound 2K * 2^-24 * sum |w y| is relative to the result
+        assert (np.abs(got[0].astype(np.float64) - ref) <= 2 * K * 2.0 ** -24 * ref).all() and np.array_equal(got[0], got[1]), ctx
+        gy = call(B.hm_combine_transpose, (n, H), torch.float32, shifted(x32, torch.float32), g.plan)
+        assert np.array_equal(gy.view(np.uint32), oracle.combine_transpose(x32, ora.row_token, ora.row_weight).view(np.uint32)), ctx
+        gy = call(B.hm_combine_transpose_bf16, (n, H), torch.bfloat16, shifted(x, torch.bfloat16), g.plan)
+        assert np.array_equal(gy, oracle.combine_transpose_bf16(x, ora.row_token, ora.row_weight)), ctx
+        assert B.hm_plan_status(g.plan)[0] == 0, ctx
+
+
 def test_bad_ids_and_small_buffers_are_flagged_not_faulted(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
