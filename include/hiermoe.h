@@ -180,8 +180,9 @@ hm_status hm_plan_static(const int32_t *topk_ids, const float *topk_weights, con
  * hm_dispatch_pack -- the deduplicated send buffers (Section III-A, Fig.5): for every kept slot,
  * packed[slot_row[t,k], :] = x[t, :], a bit copy of H bf16 values.  x [T,H] bf16 row-major,
  * packed [packed_rows,H] bf16; rows outside [0,packed_rows) are skipped and flagged
- * HM_ERR_CAPACITY.  Uses plan->slot_row, slot_keep, status.  Fast path needs H % 8 == 0 and
- * 16-byte aligned x / packed; any other H or alignment takes a slower element-wise kernel.
+ * HM_ERR_CAPACITY.  Uses plan->slot_row, slot_keep, status.  Any H and any alignment of the elements
+ * is taken (this and the calls below); fastest are rows of whole 128-byte lines in 128-byte aligned
+ * buffers, slowest rows shorter than one 16-byte vector.
  */
 hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, int32_t H, const hm_plan_out *plan,
                            void *packed_bf16, int64_t packed_rows, void *hip_stream);
@@ -205,8 +206,7 @@ hm_status hm_combine(const void *y_bf16, int64_t y_rows, const float *topk_weigh
 
 /*
  * hm_combine_launch_shape -- host only, launches nothing: the shape hm_combine / hm_combine_f32 /
- * hm_combine_mix would launch with for this plan on rows of H % 8 == 0 (H % 4 for fp32) elements:
- * 16-byte vectors per lane, rows whose loads are in flight per wave, resident waves per CU the
+ * hm_combine_mix would launch with for this plan on rows of at least one 16-byte vector: 16-byte vectors per lane, rows whose loads are in flight per wave, resident waves per CU the
  * launch allows (32 = no cap).  weights_from_plan != 0 asks about the topk_weights == NULL form.
  * For tests and tuning: it shows what plan->expected_rows / max_rows_per_token select.
  */
@@ -220,7 +220,7 @@ hm_status hm_combine_launch_shape(int32_t T, int32_t K, int32_t H, const hm_plan
  *     out[t,:] = sum_k topk_weights[t,k] * y[slot_row[t,k], :],  an fp32 fma chain over the token's
  * distinct rows in ascending k of their first slot, merged weights as in hm_combine; the result
  * differs from the exact sum by at most 2K * 2^-24 * sum_k |w y|.  y [y_rows,H] fp32, out [T,H]
- * fp32.  Fast path needs H % 4 == 0 and 16-byte aligned y / out.  Errors as hm_combine.
+ * fp32.  Errors as hm_combine.
  */
 hm_status hm_combine_f32(const float *y, int64_t y_rows, const float *topk_weights, int32_t T, int32_t K,
                          int32_t H, const hm_plan_out *plan, float *out, void *hip_stream);
@@ -241,7 +241,7 @@ hm_status hm_combine_transpose(const float *gout, int32_t T, int32_t K, int32_t 
  * product's own rounding error, recovered with one fma, settles the cases where rounding twice
  * would differ; that error term underflows for |row_weight * gout| below about 2^-102, where an
  * exact tie of the fp32 product may be broken to even instead).  gout [T,H] bf16, gy [gy_rows,H]
- * bf16; fast path needs H % 8 == 0 and 16-byte aligned buffers.  Errors as hm_combine_transpose.
+ * bf16.  Errors as hm_combine_transpose.
  */
 hm_status hm_combine_transpose_bf16(const void *gout_bf16, int32_t T, int32_t K, int32_t H, const hm_plan_out *plan,
                                     void *gy_bf16, int64_t gy_rows, void *hip_stream);

@@ -52,13 +52,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return f32_to_bf16(lo) | (f32_to_bf16(hi) << 16);
 }
 
-// Streaming 16-byte accesses: packed rows are written once and read by a later kernel (or, in a
-// real deployment, by the network), so they should not displace useful lines.
-__device__ __forceinline__ void store_stream(u32x4 *p, u32x4 v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ void store_stream(f32x4 *p, f32x4 v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ u32x4 load_stream(const u32x4 *p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ f32x4 load_stream(const f32x4 *p) { return __builtin_nontemporal_load(p); }
-
 }  // namespace hm
 
 // Host-side argument checks shared by the entry points.

@@ -47,10 +47,14 @@ constexpr int kCombineRowsPlan = 8;   // combine with the plan's weights, two ro
                                       //   up to eight rows in flight
 constexpr int kCombineBytesInFlight = 128 * 1024;   // per CU, what the cap on resident waves aims at
 
+constexpr int kLineBytes = 128;
+constexpr int32_t kMaxVectorH = 1 << 30;   // the vector kernels count elements of a row in 32 bits
+
 struct RowParams {
   int32_t T, K;
   int32_t H;      // elements per row
-  int32_t nvec;   // 16-byte vectors per row (the last one overlaps its neighbour where H is no multiple)
+  int32_t nvec;   // 16-byte vectors per row (whole rows)
+  int32_t shift;  // elements between a 128-byte line and the start of the buffer written (ragged rows)
   int32_t nseg;   // segments per row
   int64_t nunits; // T * nseg
   const int32_t *slot_row;
@@ -68,50 +72,56 @@ __device__ __forceinline__ bool unit_of_wave(const RowParams &p, int &t, int &se
   return true;
 }
 
-// How a row's 16-byte vectors are addressed.  Whole: rows are a multiple of 16 bytes and 16-byte
-// aligned.  Ragged: any length of at least one vector, at the alignment of its elements.  Vector v
-// then starts at element min(v * P, H - P), so the last one overlaps the one before it: the values in
-// the overlap are computed twice from the same inputs, to the same bits, and stored twice, which
-// needs neither a tail loop nor a mask.
+// How a row is cut into 16-byte vectors.
+// WholeRows: the rows of every buffer are whole 128-byte lines; vector v is elements [v P, v P + P).
+// RaggedRows: any length of at least one vector, at the alignment of the elements.  The vectors follow
+// the 16-byte grid of the buffer that is WRITTEN, counted from the 128-byte line that holds the row's
+// first element, so that two waves share no line inside a row: a wave that stores part of a line
+// leaves the rest to a wave behind another die's L2, and each of them then writes a piece of it to
+// memory.  Reads take whatever alignment results.  A vector that reaches over the row's first or last element is moved inside the row
+// instead: its values are computed twice from the same inputs, to the same bits, and stored twice,
+// which needs neither a tail loop nor a mask.
 template <typename ELEM>
 struct WholeRows {
-  typedef ELEM elem;
   typedef u32x4 vec;
-  static __device__ __forceinline__ const vec *at(const void *base, const RowParams &p, int64_t row, int v) {
-    return (const vec *)base + (row * p.nvec + v);
+  static __device__ __forceinline__ bool place(const RowParams &p, int64_t, int v, int &at) {
+    at = v * (int)(16 / sizeof(ELEM));
+    return v < p.nvec;
   }
 };
 template <typename ELEM>
 struct RaggedRows {
-  typedef ELEM elem;
   typedef std::conditional_t<sizeof(ELEM) == 2, u32x4_align2, u32x4_align4> vec;
-  static __device__ __forceinline__ const vec *at(const void *base, const RowParams &p, int64_t row, int v) {
-    constexpr int P = 16 / sizeof(ELEM);
-    return (const vec *)((const ELEM *)base + (row * p.H + min(v * P, p.H - P)));
+  // Vector v of the row as it lies in the buffer written: its first element, false if it is outside the row.
+  static __device__ __forceinline__ bool place(const RowParams &p, int64_t row, int v, int &at) {
+    constexpr int P = 16 / sizeof(ELEM), kLine = kLineBytes / sizeof(ELEM);
+    const int before = (int)((uint32_t)row * (uint32_t)p.H + (uint32_t)p.shift) & (kLine - 1);
+    const int e = v * P - before;
+    at = min(max(e, 0), p.H - P);
+    return e > -P && e < p.H;
   }
 };
-template <typename ACCESS>
-__device__ __forceinline__ u32x4 load_row(const void *base, const RowParams &p, int64_t row, int v) {
-  return __builtin_nontemporal_load(ACCESS::at(base, p, row, v));
+template <typename ACCESS, typename ELEM>
+__device__ __forceinline__ u32x4 load_row(const ELEM *base, const RowParams &p, int64_t row, int at) {
+  return __builtin_nontemporal_load((const typename ACCESS::vec *)(base + (row * p.H + at)));
 }
-template <typename ACCESS>
-__device__ __forceinline__ void store_row(void *base, const RowParams &p, int64_t row, int v, u32x4 value) {
-  __builtin_nontemporal_store(value, const_cast<typename ACCESS::vec *>(ACCESS::at(base, p, row, v)));
+template <typename ACCESS, typename ELEM>
+__device__ __forceinline__ void store_row(ELEM *base, const RowParams &p, int64_t row, int at, u32x4 value) {
+  __builtin_nontemporal_store(value, (typename ACCESS::vec *)(base + (row * p.H + at)));
 }
 
 // ---------------------------------------------------------------------------------------------
 // dispatch: packed[slot_row[t,k], :] = x[t, :] for kept slots
 // ---------------------------------------------------------------------------------------------
-template <typename ACCESS>
-__global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p, const void *__restrict__ x,
-                                                                     void *__restrict__ packed, int64_t packed_rows) {
+__global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p, const uint16_t *__restrict__ x,
+                                                                     uint16_t *__restrict__ packed, int64_t packed_rows) {
   int t, seg;
   if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
   const int lane = lane_id();
-  const int v = seg * kWave + lane;
-  const bool in_row = v < p.nvec;
+  int at;
+  const bool in_row = WholeRows<uint16_t>::place(p, 0, seg * kWave + lane, at);
   u32x4 r = {0u, 0u, 0u, 0u};
-  if (in_row) r = *ACCESS::at(x, p, t, v);   // does not wait for the row list below
+  if (in_row) r = *(const u32x4 *)(x + ((int64_t)t * p.H + at));   // does not wait for the row list below
   int my_row = -1;
   if (lane < p.K) {
     const int64_t s = (int64_t)t * p.K + lane;
@@ -126,7 +136,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p
     const int k = __builtin_ctzll(todo);
     todo &= todo - 1;
     const int row = read_lane(my_row, k);
-    if (in_row) store_row<ACCESS>(packed, p, row, v, r);
+    if (in_row) store_row<WholeRows<uint16_t>>(packed, p, row, at, r);
   }
 }
 
@@ -271,9 +281,9 @@ struct RowF32 {
 // the merged weights (added in ascending k of each row's first slot); zero for a row without a
 // valid slot.  (A true division per element made the kernel ALU-bound: 8 divisions per 16 bytes.)
 template <bool MIX, int U, int R, typename ROW, typename ACCESS>
-__global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams p, const void *__restrict__ y,
+__global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams p, const typename ROW::elem *__restrict__ y,
                                                                        int64_t y_rows, const float *__restrict__ topk_weights,
-                                                                       void *__restrict__ out) {
+                                                                       typename ROW::elem *__restrict__ out) {
   int t, seg;
   if (!unit_of_wave<kCombineThreads>(p, t, seg)) return;
   const int lane = lane_id();
@@ -300,8 +310,11 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
     inv_wsum = wsum != 0.0f ? 1.0f / wsum : 0.0f;
   }
 
-  const int v0 = seg * (kWave * U) + lane;   // this lane's vectors: v0, v0+64, ...
   constexpr int E = ROW::kPerVec;
+  int at[U];   // this lane's vectors: every 64th of the segment
+  bool in_row[U];
+#pragma unroll
+  for (int i = 0; i < U; ++i) in_row[i] = ACCESS::place(p, t, seg * (kWave * U) + i * kWave + lane, at[i]);
   float acc[U][E];
 #pragma unroll
   for (int i = 0; i < U; ++i)
@@ -326,7 +339,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
         a[j] = read_lane(agg, k);
 #pragma unroll
         for (int i = 0; i < U; ++i)
-          if (v0 + i * kWave < p.nvec) r[j][i] = load_row<ACCESS>(y, p, row, v0 + i * kWave);
+          if (in_row[i]) r[j][i] = load_row<ACCESS>(y, p, row, at[i]);
       }
     }
 #pragma unroll
@@ -339,12 +352,12 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
   }
 #pragma unroll
   for (int i = 0; i < U; ++i) {
-    if (v0 + i * kWave < p.nvec) {
+    if (in_row[i]) {
       if (MIX) {
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[i][e] = acc[i][e] * inv_wsum;
       }
-      store_row<ACCESS>(out, p, t, v0 + i * kWave, ROW::pack(acc[i]));
+      store_row<ACCESS>(out, p, t, at[i], ROW::pack(acc[i]));
     }
   }
 }
@@ -354,10 +367,10 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
 // the slots that share the row -- the number merge_slots computes.  A wave owns U KiB of the row;
 // the loads of up to R rows are issued before the first fma.
 template <bool MIX, int U, int R, typename ROW, typename ACCESS>
-__global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowParams p, const void *__restrict__ y,
+__global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowParams p, const typename ROW::elem *__restrict__ y,
                                                                             int64_t y_rows,
                                                                             const float *__restrict__ row_weight,
-                                                                            void *__restrict__ out) {
+                                                                            typename ROW::elem *__restrict__ out) {
   int t, seg;
   if (!unit_of_wave<kCombineThreads>(p, t, seg)) return;
   const int lane = lane_id();
@@ -379,8 +392,11 @@ __global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowP
     for (uint64_t m = todo; m; m &= m - 1) wsum = wsum + read_lane(agg, __builtin_ctzll(m));
     inv_wsum = wsum != 0.0f ? 1.0f / wsum : 0.0f;
   }
-  const int v0 = seg * (kWave * U) + lane;   // this lane's vectors: v0, v0+64, ...
   constexpr int E = ROW::kPerVec;
+  int at[U];   // this lane's vectors: every 64th of the segment
+  bool in_row[U];
+#pragma unroll
+  for (int i = 0; i < U; ++i) in_row[i] = ACCESS::place(p, t, seg * (kWave * U) + i * kWave + lane, at[i]);
   float acc[U][E];
 #pragma unroll
   for (int i = 0; i < U; ++i)
@@ -403,7 +419,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowP
         a[j] = read_lane(agg, k);
 #pragma unroll
         for (int i = 0; i < U; ++i)
-          if (v0 + i * kWave < p.nvec) r[j][i] = load_row<ACCESS>(y, p, row, v0 + i * kWave);
+          if (in_row[i]) r[j][i] = load_row<ACCESS>(y, p, row, at[i]);
       }
     }
 #pragma unroll
@@ -416,12 +432,12 @@ __global__ __launch_bounds__(kCombineThreads) void combine_plan_rows_kernel(RowP
   }
 #pragma unroll
   for (int i = 0; i < U; ++i) {
-    if (v0 + i * kWave < p.nvec) {
+    if (in_row[i]) {
       if (MIX) {
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[i][e] = acc[i][e] * inv_wsum;
       }
-      store_row<ACCESS>(out, p, t, v0 + i * kWave, ROW::pack(acc[i]));
+      store_row<ACCESS>(out, p, t, at[i], ROW::pack(acc[i]));
     }
   }
 }
@@ -467,18 +483,19 @@ __global__ __launch_bounds__(kElemThreads) void combine_elems_kernel(RowParams p
 // ---------------------------------------------------------------------------------------------
 // transpose: gy[slot_row[t,k], :] = row_weight[row] * gout[t, :] for kept slots (fp32)
 // ---------------------------------------------------------------------------------------------
-template <typename ROW, typename ACCESS>
-__global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams p, const void *__restrict__ gout,
+template <typename ROW>
+__global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams p, const typename ROW::elem *__restrict__ gout,
                                                                       const float *__restrict__ row_weight,
-                                                                      int64_t weight_rows, void *__restrict__ gy,
+                                                                      int64_t weight_rows, typename ROW::elem *__restrict__ gy,
                                                                       int64_t gy_rows) {
+  typedef WholeRows<typename ROW::elem> access;
   int t, seg;
   if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
   const int lane = lane_id();
-  const int v = seg * kWave + lane;
-  const bool in_row = v < p.nvec;
+  int at;
+  const bool in_row = access::place(p, 0, seg * kWave + lane, at);
   u32x4 r = {0u, 0u, 0u, 0u};
-  if (in_row) r = *ACCESS::at(gout, p, t, v);
+  if (in_row) r = *(const u32x4 *)(gout + ((int64_t)t * p.H + at));
   int my_row = -1;
   float my_w = 0.0f;
   if (lane < p.K) {
@@ -499,7 +516,68 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
     todo &= todo - 1;
     const int row = read_lane(my_row, k);
     const float a = read_lane(my_w, k);
-    if (in_row) store_row<ACCESS>(gy, p, row, v, ROW::scale(a, r));
+    if (in_row) store_row<access>(gy, p, row, at, ROW::scale(a, r));
+  }
+}
+
+// Dispatch (SCALED = false: a bit copy) and transpose of ragged rows.  The rows written start at
+// different places of a line, so the vectors of the token differ from row to row: each is read again,
+// from the caches, at the place its row asks for; the reads of four rows are in flight together.
+// Measured (8,192 / 16,384 tokens, bf16, HIP events, against vectors counted from the row's start): 7.3
+// copies of 2,051 elements 162 -> 123 us (4.5 TB/s), of 1,032 92 -> 76 us, of 7,160 251 -> 223 us; 3.6 copies of
+// 4,140 68 -> 50 us.  Splitting a row evenly over its waves (no line grid) loses more than the last,
+// short segment costs: 4,160 elements 218 -> 301 us; giving that segment to the wave before it changes nothing.
+template <typename ROW, bool SCALED>
+__global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
+                                                                     const float *__restrict__ row_weight, int64_t rows,
+                                                                     typename ROW::elem *__restrict__ out) {
+  typedef RaggedRows<typename ROW::elem> access;
+  constexpr int R = 4;
+  int t, seg;
+  if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
+  const int lane = lane_id();
+  int my_row = -1;
+  float my_w = 0.0f;
+  if (lane < p.K) {
+    const int64_t s = (int64_t)t * p.K + lane;
+    const int row = p.slot_row[s];
+    if (p.slot_keep[s] && row >= 0) {
+      if (row < rows) {
+        my_row = row;
+        if (SCALED) my_w = row_weight[row];
+      } else if (seg == 0) {
+        flag(p.status, HM_ERR_CAPACITY);
+      }
+    }
+  }
+  const typename ROW::elem *const token = in + (int64_t)t * p.H;
+  uint64_t todo = __ballot(my_row >= 0);
+  while (todo) {
+    u32x4 r[R];
+    int row[R], at[R];
+    float a[R];
+    bool in_row[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      in_row[j] = todo != 0;
+      row[j] = at[j] = 0;
+      a[j] = 0.0f;
+      r[j] = (u32x4){0u, 0u, 0u, 0u};
+      if (in_row[j]) {
+        const int k = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        row[j] = read_lane(my_row, k);
+        a[j] = read_lane(my_w, k);
+        in_row[j] = access::place(p, row[j], seg * kWave + lane, at[j]);
+        r[j] = *(const typename access::vec *)(token + at[j]);   // inside the token's row for every lane
+      }
+    }
+    // All reads have arrived here; left alone the compiler waits before every store, and so for the
+    // store before it too (rows of 7,160 bf16, 3.6 copies: 121 us, 99 us with the one wait).
+    __asm__ volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (in_row[j]) store_row<access>(out, p, row[j], at[j], SCALED ? ROW::scale(a[j], r[j]) : r[j]);
   }
 }
 
@@ -522,13 +600,20 @@ __global__ __launch_bounds__(kElemThreads) void transpose_elems_kernel(RowParams
   }
 }
 
-static inline bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
+// Whether every row of both buffers is whole 128-byte lines.
+static inline bool whole_lines(int H, int elem_bytes, const void *a, const void *b) {
+  return ((int64_t)H * elem_bytes) % kLineBytes == 0 && (((uintptr_t)a | (uintptr_t)b) & (kLineBytes - 1)) == 0;
+}
 
-// Fills nvec / nseg / nunits for rows of H elements, `per_vec` to a 16-byte vector, and sizes the grid.
-static inline bool grid_for_units(RowParams &p, int H, int per_vec, int vecs_per_lane, int block, dim3 &grid) {
+// Fills what the kernels need to know about rows of H elements (of 16 / per_vec bytes) written to
+// `out`, and sizes the grid.  A ragged row may begin anywhere in its first line.
+static inline bool grid_for_units(RowParams &p, int H, int per_vec, bool whole, const void *out, int vecs_per_lane, int block,
+                                  dim3 &grid) {
+  const int elem_bytes = 16 / per_vec, line = kLineBytes / elem_bytes;
   p.H = H;
-  p.nvec = (int)(((int64_t)H + per_vec - 1) / per_vec);
-  p.nseg = (p.nvec + kWave * vecs_per_lane - 1) / (kWave * vecs_per_lane);
+  p.shift = (int)(((uintptr_t)out & (kLineBytes - 1)) / elem_bytes);
+  p.nvec = (int)(((int64_t)H + (whole ? 0 : line - 1) + per_vec - 1) / per_vec);
+  p.nseg = (int)(((int64_t)p.nvec + kWave * vecs_per_lane - 1) / (kWave * vecs_per_lane));
   p.nunits = (int64_t)p.T * p.nseg;
   const int waves = block / kWave;
   const int64_t blocks = (p.nunits + waves - 1) / waves;
@@ -538,7 +623,7 @@ static inline bool grid_for_units(RowParams &p, int H, int per_vec, int vecs_per
 }
 
 static inline bool grid_for_elems(RowParams &p, int64_t n, dim3 &grid) {
-  p.H = p.nvec = p.nseg = 0;
+  p.H = p.nvec = p.shift = p.nseg = 0;
   p.nunits = 0;
   const int64_t blocks = (n + kElemThreads - 1) / kElemThreads;
   if (blocks > 2147483647LL) return false;
@@ -651,12 +736,17 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H >= 8) {
-    if (!grid_for_units(p, H, 8, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const bool whole = H % 8 == 0 && aligned16(x_bf16) && aligned16(packed_bf16);
-    hipLaunchKernelGGL(whole ? dispatch_rows_kernel<WholeRows<uint16_t>> : dispatch_rows_kernel<RaggedRows<uint16_t>>, grid,
-                       dim3(kCopyThreads), lds_cap_bytes(kCopyWavesPerCu, kCopyThreads), stream, p, x_bf16, packed_bf16,
-                       packed_rows);
+  if (H >= 8 && H <= kMaxVectorH) {
+    const bool whole = whole_lines(H, 2, x_bf16, packed_bf16);
+    if (!grid_for_units(p, H, 8, whole, packed_bf16, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
+    const unsigned lds = lds_cap_bytes(kCopyWavesPerCu, kCopyThreads);
+    const uint16_t *x = (const uint16_t *)x_bf16;
+    uint16_t *packed = (uint16_t *)packed_bf16;
+    if (whole)
+      hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds, stream, p, x, packed, packed_rows);
+    else
+      hipLaunchKernelGGL((spread_ragged_kernel<RowBf16, false>), grid, dim3(kCopyThreads), lds, stream, p, x, nullptr,
+                         packed_rows, packed);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL(dispatch_elems_kernel, grid, dim3(kElemThreads), 0, stream, p, H, (const uint16_t *)x_bf16,
@@ -685,17 +775,17 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H >= ROW::kPerVec) {
+  if (H >= ROW::kPerVec && H <= kMaxVectorH) {
     const CombineShape sh = combine_shape(plan, T, from_plan);
-    if (!grid_for_units(p, H, ROW::kPerVec, sh.vecs, kCombineThreads, grid)) return HM_ERR_SHAPE;
-    const bool whole = H % ROW::kPerVec == 0 && aligned16(y) && aligned16(out);
+    const bool whole = whole_lines(H, sizeof(elem), y, out);
+    if (!grid_for_units(p, H, ROW::kPerVec, whole, out, sh.vecs, kCombineThreads, grid)) return HM_ERR_SHAPE;
     // rows the plan's weight array does not cover are treated like rows beyond y
     const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
     const float *weights = from_plan ? plan->row_weight : topk_weights;
     const unsigned lds = sh.vecs == 1 ? lds_cap_bytes(sh.waves_per_cu, kCombineThreads) : 0u;
     const auto kernel = whole ? combine_kernel<MIX, ROW, WholeRows<elem>>(sh, from_plan)
                               : combine_kernel<MIX, ROW, RaggedRows<elem>>(sh, from_plan);
-    hipLaunchKernelGGL(kernel, grid, dim3(kCombineThreads), lds, stream, p, y, rows, weights, out);
+    hipLaunchKernelGGL(kernel, grid, dim3(kCombineThreads), lds, stream, p, (const elem *)y, rows, weights, (elem *)out);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     // the element-wise kernel finds the first slot of each row itself and takes the row's merged
@@ -757,12 +847,16 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H >= ROW::kPerVec) {
-    if (!grid_for_units(p, H, ROW::kPerVec, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const bool whole = H % ROW::kPerVec == 0 && aligned16(gout) && aligned16(gy);
+  if (H >= ROW::kPerVec && H <= kMaxVectorH) {
+    const bool whole = whole_lines(H, sizeof(elem), gout, gy);
+    if (!grid_for_units(p, H, ROW::kPerVec, whole, gy, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
     const unsigned lds = ROW::kPerVec == 4 ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;   // fp32 rows only
-    hipLaunchKernelGGL((whole ? transpose_rows_kernel<ROW, WholeRows<elem>> : transpose_rows_kernel<ROW, RaggedRows<elem>>),
-                       grid, dim3(kCopyThreads), lds, stream, p, gout, plan->row_weight, plan->row_capacity, gy, gy_rows);
+    if (whole)
+      hipLaunchKernelGGL((transpose_rows_kernel<ROW>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
+                         plan->row_weight, plan->row_capacity, (elem *)gy, gy_rows);
+    else
+      hipLaunchKernelGGL((spread_ragged_kernel<ROW, true>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
+                         plan->row_weight, plan->row_capacity < gy_rows ? plan->row_capacity : gy_rows, (elem *)gy);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((transpose_elems_kernel<ROW>), grid, dim3(kElemThreads), 0, stream, p, H, (const elem *)gout,
