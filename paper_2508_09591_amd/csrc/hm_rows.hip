@@ -56,18 +56,24 @@ struct RowParams {
   int32_t nvec;   // 16-byte vectors per row (whole rows)
   int32_t shift;  // elements between a 128-byte line and the start of the buffer written (ragged rows)
   int32_t nseg;   // segments per row
-  int64_t nunits; // T * nseg
+  int64_t nunits; // T * nseg (flat kernels: T * nvec)
+  uint64_t recip; // ceil(2^64 / nseg) (flat kernels: / nvec), 0 for 1
   const int32_t *slot_row;
   const uint8_t *slot_keep;
   int32_t *status;
 };
 
+// n / d for the reciprocal ceil(2^64 / d) (0 for d = 1): exact while n d < 2^64.
+__device__ __forceinline__ int64_t divided(int64_t n, uint64_t recip) {
+  return recip ? (int64_t)__umul64hi((uint64_t)n, recip) : n;
+}
+
 // Wave-uniform (token, segment) of this wave, or false when past the end.
 template <int BLOCK>
 __device__ __forceinline__ bool unit_of_wave(const RowParams &p, int &t, int &seg) {
-  const int64_t unit = (int64_t)blockIdx.x * (BLOCK / kWave) + (threadIdx.x >> 6);
+  const int64_t unit = (int64_t)blockIdx.x * (BLOCK / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (unit >= p.nunits) return false;
-  t = (int)(unit / p.nseg);
+  t = (int)divided(unit, p.recip);
   seg = (int)(unit - (int64_t)t * p.nseg);
   return true;
 }
@@ -581,6 +587,131 @@ __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Narrow rows: of fewer vectors than a wave has lanes.  One lane per (token, vector), tokens side by
+// side, so that the lanes are busy however short the rows are; a lane reads its token's slots itself
+// (the lanes of a token read the same words), several at a time.
+// ---------------------------------------------------------------------------------------------
+constexpr int kFlatThreads = 256;
+
+// Vectors from the row's start; the last one is moved inside the row.
+template <typename ELEM>
+struct NarrowRows : RaggedRows<ELEM> {
+  static __device__ __forceinline__ int place(const RowParams &p, int v) {
+    constexpr int P = 16 / sizeof(ELEM);
+    return min(v * P, p.H - P);
+  }
+};
+
+// (token, vector) of this lane, or false when past the end.  The workgroup's first unit is divided by a
+// 64-bit reciprocal, the rest is a numerator below 64 + kFlatThreads.
+__device__ __forceinline__ bool unit_of_lane(const RowParams &p, int &t, int &v) {
+  const int64_t first = (int64_t)blockIdx.x * kFlatThreads;
+  const int64_t t0 = divided(first, p.recip);
+  const unsigned n = (unsigned)(first - t0 * p.nvec) + threadIdx.x;
+  const unsigned dt = (n * (((1u << 22) + (unsigned)p.nvec - 1u) / (unsigned)p.nvec)) >> 22;
+  t = (int)t0 + (int)dt;
+  v = (int)(n - dt * (unsigned)p.nvec);
+  return first + threadIdx.x < p.nunits;
+}
+
+// The rows that slots k0 .. k0 + N - 1 of token t own, -1 for a slot that owns none in [0, rows).
+template <int N>
+__device__ __forceinline__ void owned_rows(const RowParams &p, int t, int k0, int64_t rows, bool report, int (&row)[N]) {
+  const int64_t s = (int64_t)t * p.K + k0;
+  uint8_t keep[N];
+  __builtin_memcpy(row, p.slot_row + s, sizeof(row));
+  __builtin_memcpy(keep, p.slot_keep + s, sizeof(keep));
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    if (!keep[j] || row[j] < 0) {
+      row[j] = -1;
+    } else if (row[j] >= rows) {
+      if (report) flag(p.status, HM_ERR_CAPACITY);
+      row[j] = -1;
+    }
+  }
+}
+
+// fn(N, k0) over the K slots in pieces of eight, four and one.
+template <typename FN>
+__device__ __forceinline__ void for_slots(int K, FN fn) {
+  int k0 = 0;
+  for (; k0 + 8 <= K; k0 += 8) fn(std::integral_constant<int, 8>{}, k0);
+  if (k0 + 4 <= K) {
+    fn(std::integral_constant<int, 4>{}, k0);
+    k0 += 4;
+  }
+  for (; k0 < K; ++k0) fn(std::integral_constant<int, 1>{}, k0);
+}
+
+// Dispatch (SCALED = false) and transpose.
+template <typename ROW, bool SCALED>
+__global__ __launch_bounds__(kFlatThreads) void spread_flat_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
+                                                                   const float *__restrict__ row_weight, int64_t rows,
+                                                                   typename ROW::elem *__restrict__ out) {
+  typedef NarrowRows<typename ROW::elem> access;
+  int t, v;
+  if (!unit_of_lane(p, t, v)) return;
+  const int at = access::place(p, v);
+  const u32x4 r = *(const typename access::vec *)(in + ((int64_t)t * p.H + at));
+  for_slots(p.K, [&](auto n, int k0) {
+    constexpr int N = decltype(n)::value;
+    int row[N];
+    float a[N];
+    owned_rows<N>(p, t, k0, rows, v == 0, row);
+#pragma unroll
+    for (int j = 0; j < N; ++j) a[j] = SCALED ? row_weight[max(row[j], 0)] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+      if (row[j] >= 0) store_row<access>(out, p, row[j], at, SCALED ? ROW::scale(a[j], r) : r);
+  });
+}
+
+// Combine with the plan's weights: the sums of combine_plan_rows_kernel, in the same order.
+template <bool MIX, typename ROW>
+__global__ __launch_bounds__(kFlatThreads) void combine_flat_kernel(RowParams p, const typename ROW::elem *__restrict__ y,
+                                                                    int64_t y_rows, const float *__restrict__ row_weight,
+                                                                    typename ROW::elem *__restrict__ out) {
+  typedef NarrowRows<typename ROW::elem> access;
+  constexpr int E = ROW::kPerVec;
+  int t, v;
+  if (!unit_of_lane(p, t, v)) return;
+  const int at = access::place(p, v);
+  float acc[E], wsum = 0.0f;
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[e] = 0.0f;
+  for_slots(p.K, [&](auto n, int k0) {
+    constexpr int N = decltype(n)::value;
+    int row[N];
+    float a[N];
+    u32x4 r[N];
+    owned_rows<N>(p, t, k0, y_rows, v == 0, row);
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      a[j] = 0.0f;
+      r[j] = (u32x4){0u, 0u, 0u, 0u};
+      if (row[j] >= 0) {
+        a[j] = row_weight[row[j]];
+        r[j] = load_row<access>(y, p, row[j], at);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (row[j] >= 0) {
+        ROW::fma_into(acc, a[j], r[j]);
+        wsum = wsum + a[j];
+      }
+    }
+  });
+  if (MIX) {
+    const float inv = wsum != 0.0f ? 1.0f / wsum : 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = acc[e] * inv;
+  }
+  store_row<access>(out, p, t, at, ROW::pack(acc));
+}
+
 template <typename ROW>
 __global__ __launch_bounds__(kElemThreads) void transpose_elems_kernel(RowParams p, int32_t H,
                                                                       const typename ROW::elem *__restrict__ gout,
@@ -605,6 +736,8 @@ static inline bool whole_lines(int H, int elem_bytes, const void *a, const void 
   return ((int64_t)H * elem_bytes) % kLineBytes == 0 && (((uintptr_t)a | (uintptr_t)b) & (kLineBytes - 1)) == 0;
 }
 
+static inline uint64_t reciprocal(int64_t d) { return d > 1 ? ~0ull / (uint64_t)d + 1 : 0; }
+
 // Fills what the kernels need to know about rows of H elements (of 16 / per_vec bytes) written to
 // `out`, and sizes the grid.  A ragged row may begin anywhere in its first line.
 static inline bool grid_for_units(RowParams &p, int H, int per_vec, bool whole, const void *out, int vecs_per_lane, int block,
@@ -615,6 +748,7 @@ static inline bool grid_for_units(RowParams &p, int H, int per_vec, bool whole, 
   p.nvec = (int)(((int64_t)H + (whole ? 0 : line - 1) + per_vec - 1) / per_vec);
   p.nseg = (int)(((int64_t)p.nvec + kWave * vecs_per_lane - 1) / (kWave * vecs_per_lane));
   p.nunits = (int64_t)p.T * p.nseg;
+  p.recip = reciprocal(p.nseg);
   const int waves = block / kWave;
   const int64_t blocks = (p.nunits + waves - 1) / waves;
   if (blocks > 2147483647LL) return false;
@@ -622,9 +756,37 @@ static inline bool grid_for_units(RowParams &p, int H, int per_vec, bool whole, 
   return true;
 }
 
+// The same for the flat kernels.
+static inline bool grid_for_flat(RowParams &p, int H, int per_vec, dim3 &grid) {
+  p.H = H;
+  p.shift = p.nseg = 0;
+  p.nvec = (H + per_vec - 1) / per_vec;
+  p.nunits = (int64_t)p.T * p.nvec;
+  p.recip = reciprocal(p.nvec);
+  const int64_t blocks = (p.nunits + kFlatThreads - 1) / kFlatThreads;
+  if (blocks > 2147483647LL) return false;
+  grid = dim3((unsigned)blocks);
+  return true;
+}
+// Whether rows go to the flat kernels: where the waves of the other kernels would have a quarter of
+// their lanes idle or more, i.e. up to 48 vectors, 65 to 96, and so on.  HIP events, 65,536 tokens, 3.6 bf16
+// rows each, wave per segment -> flat: dispatch / combine of 16 elements 24.5 / 28.6 -> 8.3 / 8.1 us, of
+// 128 19.1 / 31.6 -> 15.6 / 18.4, of 256 26.8 / 35.6 -> 26.4 / 30.2, of 384 38.1 / 42.0 -> 37.2 / 42.0, of 448
+// (kept per wave) 43.3 / 46.9 -> 43.0 / 47.6, of 576 57.3 / 68.7 -> 54.1 / 59.3; of 832 (kept) 88.1 / 82.1 ->
+// 89.2 / 82.6.  Ragged rows are written better along the line grid from 33 vectors on (7.3 copies of 301
+// elements 113 -> 116 us, of 1,030 71 -> 84 us); a combine writes little and is better flat (59 -> 57 us).
+static inline bool flat_rows(int H, int per_vec, bool whole, bool spread) {
+  const int64_t vecs = ((int64_t)H + per_vec - 1) / per_vec;
+  if (spread && !whole) return H >= per_vec && vecs <= 32;
+  const int64_t in_waves = whole ? vecs : ((int64_t)H + kLineBytes / 16 * per_vec - 1 + per_vec - 1) / per_vec;
+  const int64_t lanes = (in_waves + kWave - 1) / kWave * kWave;
+  return H >= per_vec && 4 * in_waves <= 3 * lanes;
+}
+
 static inline bool grid_for_elems(RowParams &p, int64_t n, dim3 &grid) {
   p.H = p.nvec = p.shift = p.nseg = 0;
   p.nunits = 0;
+  p.recip = 0;
   const int64_t blocks = (n + kElemThreads - 1) / kElemThreads;
   if (blocks > 2147483647LL) return false;
   grid = dim3((unsigned)blocks);
@@ -736,12 +898,16 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H >= 8 && H <= kMaxVectorH) {
-    const bool whole = whole_lines(H, 2, x_bf16, packed_bf16);
+  const bool whole = whole_lines(H, 2, x_bf16, packed_bf16);
+  const uint16_t *x = (const uint16_t *)x_bf16;
+  uint16_t *packed = (uint16_t *)packed_bf16;
+  if (flat_rows(H, 8, whole, true)) {
+    if (!grid_for_flat(p, H, 8, grid)) return HM_ERR_SHAPE;
+    hipLaunchKernelGGL((spread_flat_kernel<RowBf16, false>), grid, dim3(kFlatThreads), 0, stream, p, x, nullptr, packed_rows,
+                       packed);
+  } else if (H >= 8 && H <= kMaxVectorH) {
     if (!grid_for_units(p, H, 8, whole, packed_bf16, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
     const unsigned lds = lds_cap_bytes(kCopyWavesPerCu, kCopyThreads);
-    const uint16_t *x = (const uint16_t *)x_bf16;
-    uint16_t *packed = (uint16_t *)packed_bf16;
     if (whole)
       hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds, stream, p, x, packed, packed_rows);
     else
@@ -749,8 +915,7 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
                          packed_rows, packed);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
-    hipLaunchKernelGGL(dispatch_elems_kernel, grid, dim3(kElemThreads), 0, stream, p, H, (const uint16_t *)x_bf16,
-                       (uint16_t *)packed_bf16, packed_rows);
+    hipLaunchKernelGGL(dispatch_elems_kernel, grid, dim3(kElemThreads), 0, stream, p, H, x, packed, packed_rows);
   }
   return hm_launch_status();
 }
@@ -775,12 +940,16 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H >= ROW::kPerVec && H <= kMaxVectorH) {
+  const bool whole = whole_lines(H, sizeof(elem), y, out);
+  // rows the plan's weight array does not cover are treated like rows beyond y
+  const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
+  if (from_plan && flat_rows(H, ROW::kPerVec, whole, false)) {
+    if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
+    hipLaunchKernelGGL((combine_flat_kernel<MIX, ROW>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)y, rows,
+                       plan->row_weight, (elem *)out);
+  } else if (H >= ROW::kPerVec && H <= kMaxVectorH) {
     const CombineShape sh = combine_shape(plan, T, from_plan);
-    const bool whole = whole_lines(H, sizeof(elem), y, out);
     if (!grid_for_units(p, H, ROW::kPerVec, whole, out, sh.vecs, kCombineThreads, grid)) return HM_ERR_SHAPE;
-    // rows the plan's weight array does not cover are treated like rows beyond y
-    const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
     const float *weights = from_plan ? plan->row_weight : topk_weights;
     const unsigned lds = sh.vecs == 1 ? lds_cap_bytes(sh.waves_per_cu, kCombineThreads) : 0u;
     const auto kernel = whole ? combine_kernel<MIX, ROW, WholeRows<elem>>(sh, from_plan)
@@ -791,7 +960,7 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
     // the element-wise kernel finds the first slot of each row itself and takes the row's merged
     // weight from the plan when the caller passed none
     hipLaunchKernelGGL((combine_elems_kernel<MIX, ROW>), grid, dim3(kElemThreads), 0, stream, p, H, (const elem *)y,
-                       from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows, topk_weights,
+                       rows, topk_weights,
                        from_plan ? plan->row_weight : nullptr, (elem *)out);
   }
   return hm_launch_status();
@@ -847,8 +1016,13 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  if (H >= ROW::kPerVec && H <= kMaxVectorH) {
-    const bool whole = whole_lines(H, sizeof(elem), gout, gy);
+  const bool whole = whole_lines(H, sizeof(elem), gout, gy);
+  const int64_t rows = plan->row_capacity < gy_rows ? plan->row_capacity : gy_rows;
+  if (flat_rows(H, ROW::kPerVec, whole, true)) {
+    if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
+    hipLaunchKernelGGL((spread_flat_kernel<ROW, true>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)gout,
+                       plan->row_weight, rows, (elem *)gy);
+  } else if (H >= ROW::kPerVec && H <= kMaxVectorH) {
     if (!grid_for_units(p, H, ROW::kPerVec, whole, gy, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
     const unsigned lds = ROW::kPerVec == 4 ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;   // fp32 rows only
     if (whole)
@@ -856,7 +1030,7 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
                          plan->row_weight, plan->row_capacity, (elem *)gy, gy_rows);
     else
       hipLaunchKernelGGL((spread_ragged_kernel<ROW, true>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
-                         plan->row_weight, plan->row_capacity < gy_rows ? plan->row_capacity : gy_rows, (elem *)gy);
+                         plan->row_weight, rows, (elem *)gy);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((transpose_elems_kernel<ROW>), grid, dim3(kElemThreads), 0, stream, p, H, (const elem *)gout,

@@ -368,16 +368,18 @@ def test_vector_and_elementwise_kernels_agree_on_misaligned_views(hw, oracle):
     assert bf16_ulp_distance(hw.bf16_to_host(oa), x).max() == 0
 
 
-@pytest.mark.parametrize("H", [3, 5, 7, 9, 15, 505, 511, 513, 1030, 2049])
+@pytest.mark.parametrize("H,K", [(3, 5), (5, 5), (7, 2), (9, 8), (15, 13), (257, 4), (305, 8), (505, 5), (511, 5), (513, 8),
+                                 (1030, 6), (2049, 5),                        # no whole vectors
+                                 (16, 8), (64, 1), (256, 2), (384, 5), (448, 8), (768, 3), (832, 8)])   # whole ones, few and more
 @pytest.mark.parametrize("off", [0, 1])
-def test_rows_that_are_no_multiple_of_a_vector(hw, oracle, H, off):
-    """Every row call on rows of H elements, shorter than a vector, one past it and around the 64-vector
-    segments, at the start of an allocation and one element behind it: against the oracle, with poison
-    on both sides of every output that has to survive."""
+def test_rows_of_any_length(hw, oracle, H, K, off):
+    """Every row call on rows of H elements -- shorter than a vector, one past it, on both sides of the
+    lengths at which another kernel takes over -- at the start of an allocation and one element behind
+    it: against the oracle, with poison on both sides of every output that has to survive."""
     import torch
     from paper_2508_09591_amd import binding as B
     rng = np.random.default_rng(H)
-    T, K, E, nodes, rpn = 37, 5, 24, 2, 3
+    T, E, nodes, rpn = 37, 24, 2, 3
     ids = rng.integers(0, E, (T, K), dtype=np.int32)
     ids[4] = -1                                                # a token without a row
     w = rng.random((T, K), dtype=np.float32) + np.float32(0.05)
@@ -414,7 +416,7 @@ def test_rows_that_are_no_multiple_of_a_vector(hw, oracle, H, off):
             got = [call(fn, (T, H), torch.bfloat16, y_d, weights, g.plan) for weights in (g.w_d, None)]
             assert bf16_ulp_distance(got[0], ref).max() <= 1 and np.array_equal(got[0], got[1]), (ctx, fn)
         got = [call(B.hm_combine_f32, (T, H), torch.float32, y32_d, weights, g.plan) for weights in (g.w_d, None)]
-        ref = oracle.combine_f32(y32, w, ora.slot_row)
+        ref = oracle.combine_f32(y32, w, ora.slot_row).astype(np.float64)
         # all terms positive: the bound 2K * 2^-24 * sum |w y| is relative to the result
         assert (np.abs(got[0].astype(np.float64) - ref) <= 2 * K * 2.0 ** -24 * ref).all() and np.array_equal(got[0], got[1]), ctx
         gy = call(B.hm_combine_transpose, (n, H), torch.float32, shifted(x32, torch.float32), g.plan)
@@ -422,6 +424,14 @@ def test_rows_that_are_no_multiple_of_a_vector(hw, oracle, H, off):
         gy = call(B.hm_combine_transpose_bf16, (n, H), torch.bfloat16, shifted(x, torch.bfloat16), g.plan)
         assert np.array_equal(gy, oracle.combine_transpose_bf16(x, ora.row_token, ora.row_weight)), ctx
         assert B.hm_plan_status(g.plan)[0] == 0, ctx
+        # two rows more than the buffers hold: skipped and flagged, whichever kernel the length selects
+        short = n - 2
+        ref = oracle.dispatch_pack(x, ora.row_token)[:short]
+        assert np.array_equal(call(B.hm_dispatch_pack, (short, H), torch.bfloat16, shifted(x, torch.bfloat16), g.plan), ref), ctx
+        assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
+        g.plan.status.zero_()
+        call(B.hm_combine, (T, H), torch.bfloat16, y_d[:short], None, g.plan)
+        assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
 
 
 def test_bad_ids_and_small_buffers_are_flagged_not_faulted(hw, oracle):
