@@ -32,6 +32,42 @@ __device__ __forceinline__ int rank_of(const int32_t *__restrict__ expert_to_ran
   return ((unsigned)g >= (unsigned)G) ? -1 : g;
 }
 
+// The same with the table staged in LDS as rank_code() wrote it, for E up to kStagedExperts; a lane that
+// looks up several ids then waits for LDS, not for a second trip to memory per id.
+constexpr int kStagedExperts = 4096;
+__device__ __forceinline__ int8_t rank_code(int G, int g) { return (unsigned)g >= (unsigned)G ? -1 : (int8_t)g; }
+__device__ __forceinline__ int staged_rank_of(const int8_t *ranks, int E, int id) {
+  if (id == -1) return -2;
+  return (unsigned)id >= (unsigned)E ? -1 : ranks[id];
+}
+
+// Eight ids of a token from k0 on (-1, the marker of a dropped slot, past its end), loaded together.
+__device__ __forceinline__ void load_ids(const int32_t *__restrict__ tok, int K, int k0, int (&id)[8]) {
+  if (k0 + 8 <= K) {
+    __builtin_memcpy(id, tok + k0, sizeof(id));
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) id[j] = k0 + j < K ? tok[k0 + j] : -1;
+  }
+}
+
+// How many of the wave's lanes have a bit of group j of `mask` set, in lane j < n: the mask is cut into n
+// groups of `per` bits.  Eight groups at a time: a ballot and its population count are a chain
+// between the vector and the scalar unit that one wave alone does not hide.
+__device__ __forceinline__ int lanes_per_group(uint64_t mask, int n, int per) {
+  const int lane = lane_id();
+  const uint64_t field = per >= 64 ? ~0ull : (1ull << per) - 1ull;
+  int mine = 0;
+  for (int j0 = 0; j0 < n; j0 += 8) {
+    int c[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = __popcll(__ballot((mask & (field << min((j0 + i) * per, 63))) != 0));
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mine = lane == j0 + i ? c[i] : mine;
+  }
+  return lane < n ? mine : 0;
+}
+
 // Value held by lane `src` (src must be wave-uniform).
 __device__ __forceinline__ int read_lane(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 __device__ __forceinline__ float read_lane(float v, int src) {

@@ -2,14 +2,16 @@
 // (the p^(1,G) and p^(1,U[1]) vectors of HierMoE Eq.(7)) for the expert-swap planner of Section IV.
 //
 // One lane owns one token.  Expert counts go through an LDS histogram; rank and node counts come
-// from ballots over the per-token bit masks (lane g accumulates the popcount for group g), so a
-// token is counted once per group however many of its experts live there.  A first tiny launch
-// clears the outputs, then integer atomics merge the workgroups, which keeps the result exact and
-// order-independent.  The call is launch-latency bound (two launches, ~11 us on T=8192, K=8);
-// two single-launch designs were measured and dropped: one 1024-lane workgroup doing everything
-// (56 us) and 64 workgroups that each scan the whole table but own a slice of the outputs
-// (44 us) -- both serialise dependent id -> placement loads that the token-split version spreads
-// over the chip.
+// from ballots over the per-token rank masks (lane g accumulates the popcount for group g), so a
+// token is counted once per group however many of its experts live there.  The call is bound by
+// launches and by the chain ids -> placement -> counts, so the ids of a token are loaded together,
+// while the placement is staged in LDS, and the look-ups never leave the chip (T=8192, K=8, kernel
+// trace: 6.9 -> 5.7 us).  Up to kAloneTokens tokens are one launch of one workgroup, which owns the
+// outputs (T=1024: 5.8 us instead of a clearing launch, 1.4, a gap, and 5.6); beyond that a tiny launch
+// clears them and integer atomics merge the workgroups, which keeps the result exact and
+// order-independent.  Tried and slower: the masks of ranks and nodes as one 64-bit word per expert in
+// LDS and the counts by turning the wave's 64 x 64 bits round (6.6 us: more code to fetch, and the
+// ballots are not what it waits for).
 #include "hm_device.h"
 
 namespace hm {
@@ -22,7 +24,8 @@ struct LoadParams {
 };
 
 constexpr int kLoadThreads = 256;
-constexpr int kLdsExperts = 8192;  // experts histogrammed in LDS; beyond that, global atomics
+constexpr int kAloneTokens = 1024;  // = lanes of the one workgroup: one token each
+constexpr int kLdsExperts = 8192;   // experts histogrammed in LDS; beyond that, global atomics
 
 __global__ __launch_bounds__(kLoadThreads) void load_clear_kernel(LoadParams p) {
   const int i = blockIdx.x * kLoadThreads + threadIdx.x;
@@ -32,60 +35,72 @@ __global__ __launch_bounds__(kLoadThreads) void load_clear_kernel(LoadParams p) 
   if (i == 0 && p.status) *p.status = 0;
 }
 
-__global__ __launch_bounds__(kLoadThreads) void load_count_kernel(LoadParams p) {
+// ALONE: the only workgroup; it stores the outputs instead of adding to cleared ones.
+template <int THREADS, bool ALONE>
+__global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
   __shared__ int32_t hist[kLdsExperts];
+  __shared__ int8_t ranks[kStagedExperts];
   __shared__ int32_t rank_cnt[kWave];
   __shared__ int32_t node_cnt[kWave];
-  const bool lds_hist = p.E <= kLdsExperts;
+  __shared__ int32_t bad;
+  const bool lds_hist = p.E <= kLdsExperts, staged = p.E <= kStagedExperts;
+  const int64_t stride = (int64_t)gridDim.x * THREADS;
+  int64_t t = (int64_t)blockIdx.x * THREADS + threadIdx.x;
+  int id[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
+  if (t < p.T) load_ids(p.ids + t * p.K, p.K, 0, id);   // on their way while the tables are prepared
+  if (staged)
+    for (int e = threadIdx.x; e < p.E; e += THREADS) ranks[e] = rank_code(p.G, p.expert_to_rank[e]);
   if (lds_hist)
-    for (int e = threadIdx.x; e < p.E; e += kLoadThreads) hist[e] = 0;
+    for (int e = threadIdx.x; e < p.E; e += THREADS) hist[e] = 0;
   if (threadIdx.x < kWave) {
     rank_cnt[threadIdx.x] = 0;
     node_cnt[threadIdx.x] = 0;
   }
+  if (threadIdx.x == 0) bad = 0;
   __syncthreads();
 
   const int lane = lane_id();
   int my_rank_cnt = 0, my_node_cnt = 0;  // lane g: tokens of this wave's share that reach group g
-  const int64_t stride = (int64_t)gridDim.x * kLoadThreads;
+  bool my_bad = false;
   // every lane of a wave runs the same number of rounds so the ballots stay convergent
   const int64_t rounds = ((int64_t)p.T + stride - 1) / stride;
-  for (int64_t it = 0; it < rounds; ++it) {
-    const int64_t t = it * stride + (int64_t)blockIdx.x * kLoadThreads + threadIdx.x;
+  for (int64_t it = 0; it < rounds; ++it, t += stride) {
     uint64_t rm = 0;
-    uint32_t nm = 0;
     if (t < p.T) {
-      const int32_t *tok = p.ids + t * p.K;
-      for (int k = 0; k < p.K; ++k) {
-        const int id = tok[k];
-        const int g = rank_of(p.expert_to_rank, p.E, p.G, id);
-        if (g < 0) {
-          if (g == -1) flag(p.status, HM_ERR_BAD_ID);
-          continue;
+      for (int k0 = 0; k0 < p.K; k0 += 8) {
+        if (it > 0 || k0 > 0) load_ids(p.ids + t * p.K, p.K, k0, id);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int g = staged ? staged_rank_of(ranks, p.E, id[j]) : rank_of(p.expert_to_rank, p.E, p.G, id[j]);
+          my_bad = my_bad || g == -1;
+          if (g < 0) continue;
+          if (lds_hist) atomicAdd(&hist[id[j]], 1);
+          else atomicAdd(&p.load_expert[id[j]], 1);
+          rm |= 1ull << g;
         }
-        if (lds_hist) atomicAdd(&hist[id], 1);
-        else atomicAdd(&p.load_expert[id], 1);
-        rm |= 1ull << g;
-        nm |= 1u << (g / p.R);
       }
     }
-    for (int g = 0; g < p.G; ++g) {
-      const uint64_t bal = __ballot((rm >> g) & 1ull);
-      if (lane == g) my_rank_cnt += __popcll(bal);
-    }
-    for (int n = 0; n < p.N; ++n) {
-      const uint64_t bal = __ballot((nm >> n) & 1u);
-      if (lane == n) my_node_cnt += __popcll(bal);
-    }
+    if (__ballot(rm != 0) == 0) continue;
+    my_rank_cnt += lanes_per_group(rm, p.G, 1);
+    my_node_cnt += lanes_per_group(rm, p.N, p.R);   // the ranks of a node are neighbours
   }
+  if (my_bad) bad = 1;
   if (lane < p.G && my_rank_cnt) atomicAdd(&rank_cnt[lane], my_rank_cnt);
   if (lane < p.N && my_node_cnt) atomicAdd(&node_cnt[lane], my_node_cnt);
   __syncthreads();
+  if (ALONE) {
+    for (int e = threadIdx.x; e < p.E; e += THREADS) p.load_expert[e] = hist[e];
+    if ((int)threadIdx.x < p.G) p.load_rank[threadIdx.x] = rank_cnt[threadIdx.x];
+    if ((int)threadIdx.x < p.N) p.load_node[threadIdx.x] = node_cnt[threadIdx.x];
+    if (threadIdx.x == 0 && p.status) *p.status = bad ? HM_ERR_BAD_ID : 0;
+    return;
+  }
   if (lds_hist)
-    for (int e = threadIdx.x; e < p.E; e += kLoadThreads)
+    for (int e = threadIdx.x; e < p.E; e += THREADS)
       if (hist[e]) atomicAdd(&p.load_expert[e], hist[e]);
   if ((int)threadIdx.x < p.G && rank_cnt[threadIdx.x]) atomicAdd(&p.load_rank[threadIdx.x], rank_cnt[threadIdx.x]);
   if ((int)threadIdx.x < p.N && node_cnt[threadIdx.x]) atomicAdd(&p.load_node[threadIdx.x], node_cnt[threadIdx.x]);
+  if (threadIdx.x == 0 && bad) flag(p.status, HM_ERR_BAD_ID);
 }
 
 }  // namespace hm
@@ -116,12 +131,15 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   p.load_rank = load_rank;
   p.load_node = load_node;
   p.status = status;
+  if (T <= kAloneTokens && E <= kLdsExperts) {
+    hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
+    return hm_launch_status();
+  }
   const int most = E > kWave ? E : kWave;
   hipLaunchKernelGGL(load_clear_kernel, dim3((most + kLoadThreads - 1) / kLoadThreads), dim3(kLoadThreads), 0, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-  if (T == 0) return HM_OK;
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
   if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(load_count_kernel, dim3((unsigned)blocks), dim3(kLoadThreads), 0, stream, p);
+  hipLaunchKernelGGL((load_count_kernel<kLoadThreads, false>), dim3((unsigned)blocks), dim3(kLoadThreads), 0, stream, p);
   return hm_launch_status();
 }

@@ -45,6 +45,41 @@ def test_group_counts_parity(hw, oracle, name, T):
     assert not counts_d[:1].any() and int(st_d.item()) == 0
 
 
+@pytest.mark.parametrize("T,K,E,nodes,rpn", [(0, 3, 8, 2, 2), (1, 1, 3, 1, 1), (1023, 7, 30, 3, 5), (1024, 8, 256, 8, 8),
+                                             (1025, 9, 64, 1, 64), (700, 64, 128, 32, 2), (2500, 17, 5000, 4, 8),
+                                             (900, 8, 5000, 4, 8), (900, 8, 9000, 4, 4), (300000, 2, 16, 2, 2)])
+def test_counts_at_the_edges(hw, oracle, T, K, E, nodes, rpn):
+    """hm_expert_load and hm_group_counts around one workgroup's worth of tokens and around pieces of
+    eight slots, with placement tables that fit LDS and that do not, and with dropped and invalid
+    slots: the oracle's integers."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(T + K)
+    G = nodes * rpn
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    ids[rng.random((T, K)) < 0.05] = -1
+    e2r = rng.integers(0, G, E, dtype=np.int32)
+    for bad in (False, True):
+        if bad:
+            if not T:
+                break
+            ids[T - 1, K - 1] = E
+            ids[0, 0] = -7
+            e2r[E // 2] = G
+        le, lr, ln, st = oracle.expert_load(ids, e2r, nodes, rpn)
+        got = [torch.full((n,), -3, dtype=torch.int32, device="cuda") for n in (E, G, nodes, 1)]
+        B.hm_expert_load(hw.dev(ids), hw.dev(e2r), nodes, rpn, *got)
+        for a, b in zip(got, (le, lr, ln, [st])):
+            assert np.array_equal(a.cpu().numpy(), b), (T, K, E, bad)
+        groups = [G, nodes, 1]
+        ref, st = oracle.group_counts(ids, e2r, G, groups)
+        counts_d = torch.full((3, 64), -5, dtype=torch.int32, device="cuda")
+        st_d = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+        B.hm_group_counts(hw.dev(ids), hw.dev(e2r), G, groups, counts_d, st_d)
+        assert np.array_equal(counts_d.cpu().numpy(), ref) and int(st_d.item()) == st, (T, K, E, bad)
+        assert (st == B.HM_ERR_BAD_ID) == bad
+
+
 def test_alltoall_times_parity(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
