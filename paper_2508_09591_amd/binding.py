@@ -151,8 +151,12 @@ def _dev(t: Optional[torch.Tensor], dtype: torch.dtype, name: str) -> Optional[i
 
 
 def _stream(stream) -> Optional[int]:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream or None
+    """The given stream's handle, or the current stream's on the current device.  The latter is asked
+    for as a number: building torch's Stream object around it took 2.7 us a call, about as much as
+    the launch itself (plan + dispatch + combine of a small layer, host time: 24 -> 16 us)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    return stream.cuda_stream or None
 
 
 def _check(fn: str, rc: int):

@@ -906,6 +906,22 @@ def test_step_under_hip_graph_capture(hw, oracle):
         assert np.array_equal(plan.load_expert.cpu().numpy(), le) and np.array_equal(plan.load_node.cpu().numpy(), ln)
 
 
+def test_calls_go_to_the_current_stream(hw):
+    """The handle the binding passes on is the current stream's: the default one, the innermost
+    torch.cuda.stream(), a given one whatever is current."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    for s in (torch.cuda.default_stream(), a, b):
+        with torch.cuda.stream(s):
+            assert B._stream(None) == (torch.cuda.current_stream().cuda_stream or None) == (s.cuda_stream or None)
+            assert B._stream(b) == b.cuda_stream
+    with torch.cuda.stream(a):
+        with torch.cuda.stream(b):
+            assert B._stream(None) == b.cuda_stream
+        assert B._stream(None) == a.cuda_stream != b.cuda_stream
+
+
 def test_table2_duplication_rates_on_the_gpu(hw):
     """The duplication rates printed in the paper's Table II, from hm_plan's own counts (uniform
     K-subsets of 256 experts, R groups): within 1.5 points of every printed entry."""
