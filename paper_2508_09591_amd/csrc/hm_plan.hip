@@ -39,7 +39,6 @@ namespace hm {
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kPlanHalo = 63;                              // K - 1 <= 63
-constexpr int kPlanStaged = kPlanThreads + 2 * kPlanHalo;
 constexpr int64_t kPlanScanMinEntries = 16384;             // count-matrix entries from which the scan launch pays
 constexpr int kPlanFusedMaxBlocks = 256;                   // largest plan (in workgroups) the one-launch kernel takes
 constexpr int kPlanSpinLimit = 1 << 18;                    // polls of the grid barrier before a wave gives up
@@ -64,85 +63,119 @@ struct PlanParams {
   int32_t *load_expert, *load_rank, *load_node;  // optional: the counts of hm_expert_load, fused
 };
 
-// What one lane knows about its slot after staging.
-struct Slot {
-  bool live;   // inside the table
-  int t, k;    // token and position in the token
-  int tok0;    // LDS index of the token's slot 0
-  int rank;    // -1: invalid expert id or table entry; -2: valid, but no copy at this hop
-  int dest;    // destination at the chosen level, -1 if there is none
-  bool keep;   // owns the row of (token, dest)
+// ---- the tokens of a workgroup in LDS --------------------------------------------------------------
+// The ranks (hop tables: destinations) and nodes of the workgroup's tokens lie in LDS as bytes, token by
+// token, each token padded to whole 8-byte words (0xFF: invalid, dropped or no slot).  Which other slots of its token
+// share a lane's destination is then one comparison of eight bytes at a time instead of a loop over
+// the slots, and the position among the wave's slots of one destination comes from one ballot per
+// bit of the destination instead of one per destination.  The kernel was bound by issuing those loops
+// (sixteen waves share a CU): 22 -> @WRITE@ us for the write launch of the 64 Ki-token layer.
+struct Tokens {
+  int first_slot, first_token, tokens, words;   // of the workgroup; 8-byte words per token
+  unsigned recip;                               // ceil(2^22 / K): exact for numerators below 1024 + 128, K <= 64
 };
+__device__ __forceinline__ Tokens tokens_of_block(const PlanParams &p) {
+  Tokens k;
+  k.first_slot = (int)blockIdx.x * kPlanThreads;
+  k.first_token = (int)((unsigned)k.first_slot / (unsigned)p.K);
+  const int slots = min(kPlanThreads, p.nslots - k.first_slot);   // none in an empty plan
+  k.tokens = slots < 1 ? 0 : (int)((unsigned)(k.first_slot + slots - 1) / (unsigned)p.K) - k.first_token + 1;
+  k.words = (p.K + 7) >> 3;
+  k.recip = ((1u << 22) + (unsigned)p.K - 1u) / (unsigned)p.K;
+  return k;
+}
+// Token (counted from the workgroup's first) and place in it of a slot of the workgroup's tokens.
+__device__ __forceinline__ int token_of(const PlanParams &p, const Tokens &k, int s, int &place) {
+  const unsigned q = (unsigned)(s - k.first_token * p.K);
+  const int t = (int)((q * k.recip) >> 22);
+  place = (int)q - t * p.K;
+  return t;
+}
+// 0x80 in every byte of w that equals the byte repeated in `same`.
+__device__ __forceinline__ uint64_t equal_bytes(uint64_t w, uint64_t same) {
+  const uint64_t x = w ^ same, low = 0x7F7F7F7F7F7F7F7Full;
+  return ~(((x & low) + low) | x | low);
+}
+__device__ __forceinline__ uint64_t repeated(int byte) { return (uint64_t)(uint32_t)(byte & 0xFF) * 0x0101010101010101ull; }
+// Whether no slot before `place` has this byte.
+__device__ __forceinline__ bool first_with(const uint64_t *token, int place, int byte) {
+  const uint64_t same = repeated(byte);
+  bool first = true;
+  for (int w = 0; w < place >> 3; ++w) first = first && equal_bytes(token[w], same) == 0;
+  const uint64_t before = (1ull << (8 * (place & 7))) - 1ull;
+  return first && (equal_bytes(token[place >> 3], same) & before) == 0;
+}
+// The lanes of the wave that hold the same value in [0, n) as this one, among those with `in`.
+__device__ __forceinline__ uint64_t peers_of(int value, bool in, int n) {
+  uint64_t peers = __ballot(in);
+  for (int bit = 0; (1 << bit) < n; ++bit) {
+    const bool set = (value >> bit) & 1;
+    const uint64_t b = __ballot(set);
+    peers &= set ? b : ~b;
+  }
+  return peers;
+}
 
-// Stage rank / destination of slots [first - halo, first + 1024 + halo) and classify this lane's
-// slot.  A slot owns its (token, destination) row at level none always, else iff no earlier slot
-// of the token has the same destination: the OR over a group's experts in Eq.(7) leaves one copy
-// per group, and the lowest k keeps it.
-__device__ __forceinline__ Slot stage_and_classify(const PlanParams &p, int8_t *s_rank, int8_t *s_dest) {
-  const int halo = p.K - 1;
-  const int64_t first = (int64_t)blockIdx.x * kPlanThreads;
-  for (int i = threadIdx.x; i < kPlanThreads + 2 * halo; i += kPlanThreads) {
-    const int64_t s = first - halo + i;
-    int r = -1, d = -1;
-    if (s >= 0 && s < p.nslots) {
-      if (p.dest_map) {
-        const int id = p.ids[s];
-        if (id == -1) {
-          r = -2;   // slot dropped by the router
-        } else if ((unsigned)id < (unsigned)p.E) {
-          const int v = p.dest_map[id];
-          if (v >= 0 && v < p.Dn) r = d = v;
-          else if (v == -1) r = -2;
-        }
-      } else {
-        r = rank_of(p.expert_to_rank, p.E, p.G, p.ids[s]);
-        if (r >= 0) d = p.level == HM_DEDUP_NODE ? r / p.R : r;
-      }
-    }
-    s_rank[i] = (int8_t)r;
-    s_dest[i] = (int8_t)d;
+// Rank (or hop-table destination) of an expert id: -1 invalid, -2 no copy at this hop / slot dropped by
+// the router.
+__device__ __forceinline__ int lookup_global(const PlanParams &p, int id) {
+  if (p.dest_map) {
+    if (id == -1) return -2;
+    if ((unsigned)id >= (unsigned)p.E) return -1;
+    const int v = p.dest_map[id];
+    return (v >= 0 && v < p.Dn) ? v : (v == -1 ? -2 : -1);
   }
-  __syncthreads();
-  Slot me;
-  const int64_t s = first + threadIdx.x;
-  me.live = s < p.nslots;
-  me.t = me.k = me.tok0 = 0;
-  me.rank = me.dest = -1;
-  me.keep = false;
-  if (me.live) {
-    me.t = (int)(s / p.K);
-    me.k = (int)(s - (int64_t)me.t * p.K);
-    const int own = halo + (int)threadIdx.x;
-    me.tok0 = own - me.k;
-    me.rank = s_rank[own];
-    me.dest = s_dest[own];
-    me.keep = me.dest >= 0;
-    if (me.keep && p.level != HM_DEDUP_NONE)
-      for (int k1 = 0; k1 < me.k; ++k1)
-        if (s_dest[me.tok0 + k1] == me.dest) me.keep = false;
-  }
-  return me;
+  return rank_of(p.expert_to_rank, p.E, p.G, id);
+}
+// The same from the table staged in LDS.
+__device__ __forceinline__ int lookup_staged(const PlanParams &p, const int8_t *s_map, int id) {
+  if (id == -1) return -2;
+  if ((unsigned)id >= (unsigned)p.E) return -1;
+  return s_map[id];
+}
+
+// Bytes of a workgroup's tokens: most with K = 1, a word per slot.
+constexpr int kPlanTokenWords = kPlanThreads + 2;
+
+// A halo slot of this lane, if it has one: the slots of the first token before the workgroup's, those of
+// the last token behind it.
+__device__ __forceinline__ int halo_slot(const PlanParams &p, const Tokens &k) {
+  const int before = k.first_slot - k.first_token * p.K;               // < K
+  const int i = (int)threadIdx.x;
+  if (i < before) return k.first_token * p.K + i;
+  const int64_t s = (int64_t)k.first_slot + kPlanThreads + (i - before);
+  return s < (int64_t)(k.first_token + k.tokens) * p.K ? (int)s : -1;
 }
 
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void plan_count_kernel(PlanParams p) {
-  __shared__ int8_t s_rank[kPlanStaged];
-  __shared__ int8_t s_dest[kPlanStaged];
-  __shared__ int32_t wave_cnt[kPlanWaves][kWave];
-  const int lane = lane_id(), wv = (int)(threadIdx.x >> 6);
-  const Slot me = stage_and_classify(p, s_rank, s_dest);
-  const int kept_dest = me.keep ? me.dest : -1;
-  int mine = 0;  // lane d ends up with the wave's count for destination d
-  for (int d = 0; d < p.Dn; ++d) {
-    const uint64_t b = __ballot(kept_dest == d);
-    if (lane == d) mine = __popcll(b);
+  __shared__ uint64_t dest_bytes[kPlanTokenWords];
+  __shared__ int32_t cnt[kWave];
+  const Tokens k = tokens_of_block(p);
+  const int s = k.first_slot + (int)threadIdx.x, s2 = halo_slot(p, k);
+  const bool live = s < p.nslots;
+  const int id = live ? p.ids[s] : -1, id2 = s2 >= 0 ? p.ids[s2] : -1;
+  for (int i = threadIdx.x; i < k.tokens * k.words; i += kPlanThreads) dest_bytes[i] = ~0ull;
+  if (threadIdx.x < kWave) cnt[threadIdx.x] = 0;
+  int dest = lookup_global(p, id), dest2 = lookup_global(p, id2);
+  if (p.level == HM_DEDUP_NODE && !p.dest_map) {
+    dest = dest >= 0 ? dest / p.R : dest;
+    dest2 = dest2 >= 0 ? dest2 / p.R : dest2;
   }
-  wave_cnt[wv][lane] = mine;
   __syncthreads();
-  if ((int)threadIdx.x < p.Dn) {
-    int sum = 0;
-    for (int w = 0; w < kPlanWaves; ++w) sum += wave_cnt[w][threadIdx.x];
-    p.counts[(int64_t)blockIdx.x * p.Dn + threadIdx.x] = sum;
+  int place = 0, place2 = 0;
+  const int t = live ? token_of(p, k, s, place) : 0;
+  uint8_t *const bytes = (uint8_t *)dest_bytes;
+  if (live && dest >= 0) bytes[t * k.words * 8 + place] = (uint8_t)dest;
+  if (s2 >= 0 && dest2 >= 0) {
+    const int t2 = token_of(p, k, s2, place2);
+    bytes[t2 * k.words * 8 + place2] = (uint8_t)dest2;
   }
+  __syncthreads();
+  const bool keep = live && dest >= 0 && (p.level == HM_DEDUP_NONE || first_with(dest_bytes + t * k.words, place, dest));
+  const uint64_t peers = peers_of(dest, keep, p.Dn);
+  if (keep && (peers & ((1ull << lane_id()) - 1ull)) == 0) atomicAdd(&cnt[dest], __popcll(peers));
+  __syncthreads();
+  if ((int)threadIdx.x < p.Dn) p.counts[(int64_t)blockIdx.x * p.Dn + threadIdx.x] = cnt[threadIdx.x];
   if (blockIdx.x == 0 && threadIdx.x == 0) *p.status = 0;
   if (p.load_expert) {   // the write kernel accumulates into these with atomics
     const int64_t stride = (int64_t)gridDim.x * kPlanThreads;
@@ -201,24 +234,6 @@ __device__ __forceinline__ void wait_for_own_stores() { __asm__ volatile("s_wait
 
 constexpr int kTagShift = 11;   // a workgroup keeps at most 1024 slots per destination: the count takes 11 bits
 
-// Rank (or hop-table destination) of an expert id from the table staged in LDS; the codes of
-// stage_and_classify: -1 invalid, -2 no copy at this hop / slot dropped by the router.
-__device__ __forceinline__ int lookup_staged(const PlanParams &p, const int8_t *s_map, int id) {
-  if (id == -1) return -2;
-  if ((unsigned)id >= (unsigned)p.E) return -1;
-  return s_map[id];
-}
-// The same from global memory, for tables too large to stage.
-__device__ __forceinline__ int lookup_global(const PlanParams &p, int id) {
-  if (p.dest_map) {
-    if (id == -1) return -2;
-    if ((unsigned)id >= (unsigned)p.E) return -1;
-    const int v = p.dest_map[id];
-    return (v >= 0 && v < p.Dn) ? v : (v == -1 ? -2 : -1);
-  }
-  return rank_of(p.expert_to_rank, p.E, p.G, id);
-}
-
 // The grid-wide step without a separate barrier: a workgroup publishes its per-destination
 // counts as 64-bit words (launch tag << 11 | count), one atomic store each, and every workgroup
 // reads the whole matrix, waiting on each word until it carries the tag of this launch -- the
@@ -235,43 +250,41 @@ __device__ __forceinline__ int lookup_global(const PlanParams &p, int id) {
 // slots are fetched in the same round as the workgroup's own, and everything that does not need
 // the other workgroups' counts -- slot_keep, the masks, the LDS partials of the load counts --
 // is done while the counts are on their way.
-template <bool FUSED>
+enum class PlanMode { kAlone, kFused, kWrite };   // the only workgroup; one launch of several; counts already there
+
+template <PlanMode MODE>
 __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix, uint64_t *passed, uint64_t tag,
                                           int staged_table) {
-  __shared__ int8_t s_rank[kPlanStaged];
-  __shared__ int8_t s_node[kPlanStaged];
-  __shared__ int8_t s_dest[kPlanStaged];
-  __shared__ float s_weight[kPlanStaged];
-  __shared__ uint64_t ballots[kPlanWaves][kWave];
-  __shared__ int32_t wave_base[kPlanWaves][kWave];
-  __shared__ int32_t part_tot[kPlanWaves][kWave];
-  __shared__ int32_t part_pre[kPlanWaves][kWave];
+  constexpr bool ALONE = MODE == PlanMode::kAlone, FUSED = MODE == PlanMode::kFused;
+  __shared__ uint64_t rank_bytes[kPlanTokenWords];
+  __shared__ uint64_t node_bytes[kPlanTokenWords];
+  __shared__ unsigned long long token_ranks[kPlanThreads];   // per token: the rank mask
+  __shared__ float s_weight[kPlanThreads + kPlanHalo];
+  __shared__ uint16_t wave_cnt[kPlanWaves][kWave];
+  __shared__ uint16_t wave_base[kPlanWaves][kWave];
+  __shared__ int32_t all_tot[kWave], all_pre[kWave];   // per destination: rows of the plan, of the workgroups before
   __shared__ int32_t block_base[kWave];
   __shared__ int32_t blk_rank[kWave], blk_node[kWave];
-  __shared__ int32_t gave_up;
+  __shared__ int32_t gave_up, error;
   extern __shared__ int32_t dyn_lds[];   // if staged_table: [hist: E int32 if the load arrays are asked for][rank: E int8][node: E int8]
   const int lane = lane_id(), wv = (int)(threadIdx.x >> 6);
   const int bid = (int)blockIdx.x;
-  const bool loads = p.load_expert != nullptr;
+  const bool loads = p.load_expert != nullptr, masks = p.rank_mask || p.node_mask;
   int32_t *hist = dyn_lds;
   int8_t *s_map = (int8_t *)(dyn_lds + (loads ? p.E : 0));
   int8_t *s_nmap = s_map + p.E;
-  const int halo = p.K - 1;
-  const int first = bid * kPlanThreads;   // slot indices fit 31 bits
+  const Tokens k = tokens_of_block(p);
 
   // ---- phase 1a: everything that comes from memory, issued in one round
-  const int s = first + (int)threadIdx.x;                     // own slot, LDS entry halo + threadIdx.x
-  const bool has2 = (int)threadIdx.x < 2 * halo;              // a halo slot as well:
-  const int i2 = (int)threadIdx.x < halo ? (int)threadIdx.x : kPlanThreads + (int)threadIdx.x;   // its LDS entry
-  const int64_t s2 = (int64_t)first - halo + i2;
-  const bool live = s < p.nslots, live2 = has2 && s2 >= 0 && s2 < p.nslots;
+  const int s = k.first_slot + (int)threadIdx.x, s2 = halo_slot(p, k);
+  const bool live = s < p.nslots;
   int id = -1, id2 = -1;
   float w = 0.0f, w2 = 0.0f;
   if (live) {
     id = p.ids[s];
     w = p.weights[s];
   }
-  if (live2) {
+  if (s2 >= 0) {
     id2 = p.ids[s2];
     w2 = p.weights[s2];
   }
@@ -292,8 +305,11 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
     if (loads)
       for (int e = threadIdx.x; e < p.E; e += kPlanThreads) hist[e] = 0;
   }
-  if (threadIdx.x < kWave) blk_rank[threadIdx.x] = blk_node[threadIdx.x] = 0;
-  if (threadIdx.x == 0) gave_up = 0;
+  for (int i = threadIdx.x; i < k.tokens * k.words; i += kPlanThreads) rank_bytes[i] = node_bytes[i] = ~0ull;
+  token_ranks[threadIdx.x] = 0;
+  wave_cnt[wv][lane] = 0;
+  if (threadIdx.x < kWave) blk_rank[threadIdx.x] = blk_node[threadIdx.x] = all_tot[threadIdx.x] = all_pre[threadIdx.x] = 0;
+  if (threadIdx.x == 0) gave_up = error = 0;
   if (FUSED && bid == 0) {   // what the atomics of the other workgroups add to: out before this workgroup's counts are
     if (threadIdx.x == 0) st_device(p.status, 0);
     if (loads) {
@@ -305,107 +321,95 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
   }
   __syncthreads();
 
-  // ---- phase 1b: ranks, nodes and destinations of the staged slots into LDS
+  // ---- phase 1b: ranks and nodes of the workgroup's tokens into LDS
+  int rank = -1, node = -1, place = 0, tok = 0;
   {
-    int r = -1, n = -1;
-    if (live) {
+    uint8_t *const rb = (uint8_t *)rank_bytes, *const nb = (uint8_t *)node_bytes;
+    auto find = [&](int i, int &r, int &n) {
       if (staged_table) {
-        r = lookup_staged(p, s_map, id);
-        if (r >= 0) n = s_nmap[id];
+        r = lookup_staged(p, s_map, i);
+        if (r >= 0) n = s_nmap[i];
       } else {
-        r = lookup_global(p, id);
+        r = lookup_global(p, i);
         if (r >= 0 && !p.dest_map) n = r / p.R;
       }
+    };
+    auto put = [&](int t, int at, int r, int n) {
+      if (r < 0) return;
+      rb[t * k.words * 8 + at] = (uint8_t)r;
+      if (masks) atomicOr(&token_ranks[t], 1ull << r);
+      if (n >= 0) nb[t * k.words * 8 + at] = (uint8_t)n;
+    };
+    if (live) {
+      find(id, rank, node);
+      tok = token_of(p, k, s, place);
+      put(tok, place, rank, node);
     }
-    const int own = halo + (int)threadIdx.x;
-    s_rank[own] = (int8_t)r;
-    s_node[own] = (int8_t)n;
-    s_dest[own] = (int8_t)(r < 0 ? -1 : (p.level == HM_DEDUP_NODE && !p.dest_map ? n : r));
-    s_weight[own] = w;
-    if (has2) {
-      int r2 = -1, n2 = -1;
-      if (live2) {
-        if (staged_table) {
-          r2 = lookup_staged(p, s_map, id2);
-          if (r2 >= 0) n2 = s_nmap[id2];
-        } else {
-          r2 = lookup_global(p, id2);
-          if (r2 >= 0 && !p.dest_map) n2 = r2 / p.R;
-        }
-      }
-      s_rank[i2] = (int8_t)r2;
-      s_node[i2] = (int8_t)n2;
-      s_dest[i2] = (int8_t)(r2 < 0 ? -1 : (p.level == HM_DEDUP_NODE && !p.dest_map ? n2 : r2));
-      s_weight[i2] = w2;
+    s_weight[threadIdx.x] = w;
+    if (s2 >= 0) {
+      int r2 = -1, n2 = -1, place2;
+      find(id2, r2, n2);
+      const int t2 = token_of(p, k, s2, place2);
+      put(t2, place2, r2, n2);
+      if (s2 > s) s_weight[s2 - k.first_slot] = w2;   // behind the workgroup's own
     }
   }
   __syncthreads();
-  Slot me;
-  me.live = live;
-  me.t = me.k = me.tok0 = 0;
-  me.rank = me.dest = -1;
-  me.keep = false;
-  if (live) {
-    // s / K without a per-lane division: the workgroup's first slot is divided once (uniform),
-    // the rest is a numerator below 1024 + K, for which a 22-bit reciprocal is exact (K <= 64)
-    const unsigned t0 = (unsigned)first / (unsigned)p.K, r0 = (unsigned)first - t0 * (unsigned)p.K;
-    const unsigned recip = ((1u << 22) + (unsigned)p.K - 1u) / (unsigned)p.K;
-    me.t = (int)(t0 + (((r0 + threadIdx.x) * recip) >> 22));
-    me.k = s - me.t * p.K;
-    const int own = halo + (int)threadIdx.x;
-    me.tok0 = own - me.k;
-    me.rank = s_rank[own];
-    me.dest = s_dest[own];
-    me.keep = me.dest >= 0;
-    if (me.keep && p.level != HM_DEDUP_NONE)
-      for (int k1 = 0; k1 < me.k; ++k1)
-        if (s_dest[me.tok0 + k1] == me.dest) me.keep = false;
-  }
-  const int kept_dest = me.keep ? me.dest : -1;
-  for (int d = 0; d < p.Dn; ++d) {
-    const uint64_t b = __ballot(kept_dest == d);
-    if (lane == d) ballots[wv][d] = b;
+  const bool by_node = p.level == HM_DEDUP_NODE && !p.dest_map;
+  const int dest = rank < 0 ? -1 : by_node ? node : rank;
+  const uint64_t *const my_ranks = rank_bytes + tok * k.words, *const my_nodes = node_bytes + tok * k.words;
+  const uint64_t *const my_dests = by_node ? my_nodes : my_ranks;
+  // A slot owns its (token, destination) row at level none always, else iff no earlier slot of the token
+  // has the same destination: the OR over a group's experts in Eq.(7) leaves one copy per group, and
+  // the lowest k keeps it.
+  const bool dedup = p.level != HM_DEDUP_NONE;
+  const bool first_dest = (dedup || loads) && dest >= 0 && first_with(my_dests, place, dest);
+  const bool keep = dest >= 0 && (!dedup || first_dest);
+  const uint64_t peers = peers_of(dest, keep, p.Dn);
+  const int pos = __popcll(peers & ((1ull << lane) - 1ull));
+  if (keep && pos == 0) wave_cnt[wv][dest] = (uint16_t)__popcll(peers);
+  if (loads && rank >= 0) {
+    // the first slot of a token with a rank / a node counts the token there: the duplicate-free loads of
+    // hm_expert_load, as LDS partials
+    const bool first_rank = by_node ? first_with(my_ranks, place, rank) : first_dest;
+    const bool first_node = by_node ? first_dest : first_with(my_nodes, place, node);
+    if (first_rank) atomicAdd(&blk_rank[rank], 1);
+    if (first_node) atomicAdd(&blk_node[node], 1);
+    if (staged_table) atomicAdd(&hist[id], 1);   // slots per expert
   }
   __syncthreads();
   if (lane < p.Dn) {
-    int a = 0;
-    for (int w1 = 0; w1 < wv; ++w1) a += __popcll(ballots[w1][lane]);
-    wave_base[wv][lane] = a;
-    if (FUSED && wv == kPlanWaves - 1)   // the last wave's base plus its own count is the workgroup's count
-      st_device(matrix + (int64_t)bid * p.Dn + lane, (tag << kTagShift) | (uint64_t)(a + __popcll(ballots[wv][lane])));
+    int a = 0, all = 0;
+#pragma unroll
+    for (int w1 = 0; w1 < kPlanWaves; ++w1) {
+      const int c = wave_cnt[w1][lane];
+      a += w1 < wv ? c : 0;
+      all += c;
+    }
+    wave_base[wv][lane] = (uint16_t)a;
+    if (FUSED && wv == 0) st_device(matrix + (int64_t)bid * p.Dn + lane, (tag << kTagShift) | (uint64_t)all);
+    if (ALONE && wv == 0) all_tot[lane] = all;
   }
 
   // ---- while the counts travel: what needs no other workgroup
-  uint64_t rm = 0;
-  uint32_t nm = 0;
-  if (me.live) {
-    if (me.dest < 0) {
-      p.slot_row[s] = -1;
-      p.slot_keep[s] = 0;
-    } else {
-      p.slot_keep[s] = me.keep ? 1 : 0;
-    }
-    if (me.k == 0 && (p.rank_mask || p.node_mask || loads)) {   // per-token masks, owned by the token's slot 0
-      for (int k2 = 0; k2 < p.K; ++k2) {
-        const int r2 = s_rank[me.tok0 + k2];
-        if (r2 >= 0) {
-          // the first slot that sets a bit also counts the token for that rank / node: the
-          // duplicate-free loads of hm_expert_load, as LDS partials (the wave-wide ballots per
-          // group this replaces were a third of the kernel's vector instructions)
-          if (loads && !((rm >> r2) & 1ull)) atomicAdd(&blk_rank[r2], 1);
-          rm |= 1ull << r2;
-          if (!p.dest_map) {
-            const int n2 = s_node[me.tok0 + k2];
-            if (loads && !((nm >> n2) & 1u)) atomicAdd(&blk_node[n2], 1);
-            nm |= 1u << n2;
-          }
-        }
+  if (live) {
+    if (dest < 0) p.slot_row[s] = -1;
+    p.slot_keep[s] = keep ? 1 : 0;
+  }
+  if (masks && (int)threadIdx.x < k.tokens) {   // the masks of the tokens whose first slot is this workgroup's
+    const int t = k.first_token + (int)threadIdx.x;
+    if (t * p.K >= k.first_slot) {
+      const uint64_t ranks = token_ranks[threadIdx.x];
+      if (p.rank_mask) p.rank_mask[t] = ranks;
+      if (p.node_mask) {   // a node's bit from the bits of its ranks, which are neighbours
+        const uint64_t field = p.R >= 64 ? ~0ull : (1ull << p.R) - 1ull;
+        uint32_t nodes = 0;
+        if (!p.dest_map)
+          for (int n = 0; n < p.G / p.R; ++n) nodes |= ((ranks >> (n * p.R)) & field) ? 1u << n : 0u;
+        p.node_mask[t] = nodes;
       }
-      if (p.rank_mask) p.rank_mask[me.t] = rm;
-      if (p.node_mask) p.node_mask[me.t] = nm;
     }
   }
-  if (loads && me.live && me.rank >= 0 && staged_table) atomicAdd(&hist[id], 1);   // slots per expert, LDS partial
 
   // ---- the count matrix: wave wv reads rows wv, wv+16, ..., lane = destination
   if (FUSED) {   // ... and reads them again, as a whole wave, until every word carries this launch's tag
@@ -435,10 +439,10 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
       if (ready) break;
       __builtin_amdgcn_s_sleep(2);
     }
-    part_tot[wv][lane] = tot;
-    part_pre[wv][lane] = pre;
+    if (tot) atomicAdd(&all_tot[lane], tot);
+    if (pre) atomicAdd(&all_pre[lane], pre);
     if (!ready && lane == 0) gave_up = 1;
-  } else {   // an earlier launch left the counts (or, scanned, their prefixes and a row of totals) in p.counts
+  } else if (!ALONE) {   // an earlier launch left the counts (or, scanned, their prefixes and a row of totals) in p.counts
     int tot = 0, pre = 0;
     if (p.scanned) {
       if (wv == 0 && lane < p.Dn) {
@@ -460,32 +464,37 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
         }
       }
     }
-    part_tot[wv][lane] = tot;
-    part_pre[wv][lane] = pre;
+    if (tot) atomicAdd(&all_tot[lane], tot);
+    if (pre) atomicAdd(&all_pre[lane], pre);
   }
-  __syncthreads();
+  if (!ALONE) __syncthreads();
   const bool go = gave_up == 0;   // uniform over the workgroup
   if (go) {
     if (FUSED && threadIdx.x == 0) st_device(passed + bid, tag);
     if (loads) {   // global atomics first: they complete in the shadow of the map stores
       const int nodes = p.G / p.R;
-      if (staged_table) {
+      if (ALONE && staged_table) {
+        for (int e = threadIdx.x; e < p.E; e += kPlanThreads) p.load_expert[e] = hist[e];
+      } else if (staged_table) {
         for (int e = threadIdx.x; e < p.E; e += kPlanThreads)
           if (hist[e]) atomicAdd(&p.load_expert[e], hist[e]);
-      } else if (me.live && me.rank >= 0) {
+      } else if (rank >= 0) {
         atomicAdd(&p.load_expert[id], 1);
       }
-      if ((int)threadIdx.x < p.G && blk_rank[threadIdx.x]) atomicAdd(&p.load_rank[threadIdx.x], blk_rank[threadIdx.x]);
-      if ((int)threadIdx.x < nodes && blk_node[threadIdx.x]) atomicAdd(&p.load_node[threadIdx.x], blk_node[threadIdx.x]);
+      if (ALONE) {
+        if ((int)threadIdx.x < p.G) p.load_rank[threadIdx.x] = blk_rank[threadIdx.x];
+        if ((int)threadIdx.x < nodes) p.load_node[threadIdx.x] = blk_node[threadIdx.x];
+      } else {
+        if ((int)threadIdx.x < p.G && blk_rank[threadIdx.x]) atomicAdd(&p.load_rank[threadIdx.x], blk_rank[threadIdx.x]);
+        if ((int)threadIdx.x < nodes && blk_node[threadIdx.x]) atomicAdd(&p.load_node[threadIdx.x], blk_node[threadIdx.x]);
+      }
     }
-    if (me.live && me.rank == -1) flag(p.status, HM_ERR_BAD_ID);
+    if (live && rank == -1) {
+      if (ALONE) atomicMin(&error, HM_ERR_BAD_ID);
+      else flag(p.status, HM_ERR_BAD_ID);
+    }
     if (wv == 0) {
-      int tot = 0, pre = 0;
-      if (lane < p.Dn)
-        for (int w1 = 0; w1 < kPlanWaves; ++w1) {
-          tot += part_tot[w1][lane];
-          pre += part_pre[w1][lane];
-        }
+      const int tot = all_tot[lane], pre = all_pre[lane];
       int incl = tot;  // inclusive scan over destinations (lanes >= Dn hold 0)
       for (int off = 1; off < kWave; off <<= 1) {
         const int v = __shfl_up(incl, off, kWave);
@@ -505,26 +514,33 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
   __syncthreads();
 
   // ---- rows: the slot that owns a row numbers it and serves the later slots that share it
-  if (go && me.live && me.keep) {
-    const uint64_t b = ballots[wv][me.dest];
-    const int pos = __popcll(b & ((1ull << lane) - 1ull));
-    const int row = block_base[me.dest] + wave_base[wv][me.dest] + pos;
+  if (go && keep) {
+    const int row = block_base[dest] + wave_base[wv][dest] + pos;
     p.slot_row[s] = row;
-    float wsum = s_weight[me.tok0 + me.k];
-    if (p.level != HM_DEDUP_NONE) {
-      for (int k2 = me.k + 1; k2 < p.K; ++k2) {
-        if (s_dest[me.tok0 + k2] == me.dest) {
-          p.slot_row[s + (k2 - me.k)] = row;
-          wsum = wsum + s_weight[me.tok0 + k2];  // ascending k, fp32
+    float wsum = w;
+    if (dedup) {
+      const uint64_t same = repeated(dest);
+      uint64_t later = ~((2ull << (8 * (place & 7) + 7)) - 1ull);   // the bytes behind mine
+      for (int wd = place >> 3; wd < k.words; ++wd, later = ~0ull) {
+        for (uint64_t m = equal_bytes(my_dests[wd], same) & later; m; m &= m - 1) {
+          const int ahead = wd * 8 + (__builtin_ctzll(m) >> 3) - place;
+          p.slot_row[s + ahead] = row;
+          wsum = wsum + s_weight[(int)threadIdx.x + ahead];  // ascending k, fp32
         }
       }
     }
     if (row < p.row_capacity) {
-      p.row_token[row] = me.t;
+      p.row_token[row] = k.first_token + tok;
       p.row_weight[row] = wsum;
+    } else if (ALONE) {
+      atomicMin(&error, HM_ERR_CAPACITY);
     } else {
       flag(p.status, HM_ERR_CAPACITY);
     }
+  }
+  if (ALONE) {
+    __syncthreads();
+    if (threadIdx.x == 0) *p.status = error;
   }
 
   // ---- workgroup 0 leaves matrix and flags clean (also when a wait gave up: the status word says so)
@@ -549,7 +565,13 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
 // scalar registers the compiler wants (106: the many pointers of PlanParams).
 __global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(PlanParams p, uint64_t *matrix, uint64_t *passed,
                                                                   uint64_t tag, int staged_table) {
-  plan_body<true>(p, matrix, passed, tag, staged_table);
+  plan_body<PlanMode::kFused>(p, matrix, passed, tag, staged_table);
+}
+
+// A plan of one workgroup: nothing to wait for, nothing to clear, no atomics outside LDS (except for
+// expert tables too large for it).
+__global__ __launch_bounds__(kPlanThreads) void plan_alone_kernel(PlanParams p) {
+  plan_body<PlanMode::kAlone>(p, nullptr, nullptr, 0, 1);
 }
 
 // The last launch of a large plan: the same body without the grid-wide wait.  Held to 96 scalar
@@ -558,7 +580,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(PlanParams p, 
 // cheaper than a second round).
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void plan_write_kernel(PlanParams p,
                                                                                                       int staged_table) {
-  plan_body<false>(p, nullptr, nullptr, 0, staged_table);
+  plan_body<PlanMode::kWrite>(p, nullptr, nullptr, 0, staged_table);
 }
 
 // Table of one hop for a (parent, child) pair of group cuts: purely elementwise.
@@ -684,6 +706,10 @@ static inline hm_status launch_plan(PlanParams &p, hipStream_t stream) {
   const bool loads = p.load_expert != nullptr;
   const int staged = p.E <= kPlanStagedExperts ? 1 : 0;   // tables (and histogram) in LDS
   const unsigned lds = staged ? ((loads ? (unsigned)p.E * sizeof(int32_t) : 0u) + ((2u * (unsigned)p.E + 15u) & ~15u)) : 0u;
+  if (p.nblocks == 1 && staged) {
+    hipLaunchKernelGGL(plan_alone_kernel, dim3(1), dim3(kPlanThreads), lds, stream, p);
+    return hm_launch_status();
+  }
   if (p.nblocks <= one_launch_limit.load(std::memory_order_relaxed) && p.nblocks <= fused_capacity()) {
     p.scanned = 0;
     uint64_t *matrix = (uint64_t *)((char *)p.counts + plan_counts_bytes(p.nslots, p.Dn));
