@@ -598,53 +598,68 @@ struct SelectParams {
   double *best_time;
 };
 
-// x[i0 .. i0+16) of a term's counts, 0 beyond n: sixteen loads in flight instead of a wait per
-// entry (counts are >= 0, so the padding changes neither the maximum nor, skipped, the sum).
-__device__ __forceinline__ void load16(const int32_t *x, int n, int i0, int (&v)[16]) {
-  if ((n & 3) == 0) {   // rows of n ints start 16-byte aligned
+typedef i32x4 i32x4_align4 __attribute__((aligned(4)));
+
+// x[0 .. N) of a term's counts, 0 beyond n <= N: all loads in flight together, and the counts stay in
+// registers for the sum after the maximum (counts are >= 0, so the padding changes neither the maximum
+// nor, skipped, the sum).
+template <int N>
+__device__ __forceinline__ void load_counts(const int32_t *x, int n, int (&v)[N]) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      i32x4 w = {0, 0, 0, 0};
-      if (i0 + 4 * j < n) w = *(const i32x4 *)(x + i0 + 4 * j);
+  for (int j = 0; j < N; j += 4) {
+    i32x4 w = {0, 0, 0, 0};
+    if (j + 4 <= n) {
+      w = *(const i32x4_align4 *)(x + j);
+    } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * j + e] = w[e];
+      for (int e = 0; e < 3; ++e)
+        if (j + e < n) w[e] = x[j + e];
     }
-  } else {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = i0 + j < n ? x[i0 + j] : 0;
+    for (int e = 0; e < 4; ++e) v[j + e] = w[e];
   }
 }
 
+// The smooth maximum of Eq.(11) of n <= N counts.  Every lane is a chain of fp64 operations and there
+// is about one wave per SIMD, so the chain is what counts: a whole gamma is raised for sixteen counts
+// side by side, one pass over its bits for all of them; the sum itself stays in the order of the
+// counts.
+template <int N>
 __device__ __forceinline__ double smooth_max(const int32_t *x, int n, double gamma) {
+  int v[N];
+  load_counts<N>(x, n, v);
   int mi = 0;
-  for (int i0 = 0; i0 < n; i0 += 16) {
-    int v[16];
-    load16(x, n, i0, v);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) mi = max(mi, v[j]);
-  }
+  for (int j = 0; j < N; ++j) mi = max(mi, v[j]);
   const double m = (double)mi;
   if (gamma <= 0.0 || m == 0.0) return m;
   // A small whole gamma (the paper uses 10) needs no pow per entry: square-and-multiply gives the
   // same power to a few ulp, and a lane is otherwise a serial chain of up to 64 pow calls.
   const int whole = (gamma <= 64.0 && gamma == (double)(int)gamma) ? (int)gamma : 0;
-  const double inv_m = 1.0 / m;
   double sum = 0.0;
   if (whole) {
-    for (int i0 = 0; i0 < n; i0 += 16) {
-      int v[16];
-      load16(x, n, i0, v);
+    const double inv_m = 1.0 / m;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        if (i0 + j < n) {
-          const double ratio = (double)v[j] * inv_m;   // within an ulp of the quotient
-          double acc = 1.0, sq = ratio;
-          for (int e = whole; e; e >>= 1) {
-            if (e & 1) acc *= sq;
-            sq *= sq;
-          }
-          sum += acc;
+    for (int i0 = 0; i0 < N; i0 += 16) {
+      if (i0 < n) {
+        double acc[16], sq[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          sq[j] = (double)v[i0 + j] * inv_m;   // within an ulp of the quotient
+          acc[j] = 1.0;
         }
+        for (int e = whole;;) {
+          if (e & 1) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[j] *= sq[j];
+          }
+          if ((e >>= 1) == 0) break;
+#pragma unroll
+          for (int j = 0; j < 16; ++j) sq[j] *= sq[j];
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          if (i0 + j < n) sum += acc[j];
       }
     }
   } else {
@@ -653,14 +668,25 @@ __device__ __forceinline__ double smooth_max(const int32_t *x, int n, double gam
   return m * pow(sum, 1.0 / gamma);
 }
 
+__device__ __forceinline__ void keep_better(double &val, int32_t &arg, double v, int32_t a) {
+  const bool better = a >= 0 && (arg < 0 || v < val || (v == val && a < arg));   // among equal times the lower pair index
+  val = better ? v : val;
+  arg = better ? a : arg;
+}
+__device__ __forceinline__ void wave_argmin(double &val, int32_t &arg) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) keep_better(val, arg, __shfl_xor(val, off, kWave), __shfl_xor(arg, off, kWave));
+}
+
 // Q of one pair by four lanes: the terms of Eq.(8) (the Inter levels 1 .. d-1, then the Intra
 // level) side by side, one lane each, through one code path (a term is a pointer, a length and
 // four factors).  The terms are then added in the order of the levels, so Q has the bits of a
 // serial evaluation.
+template <int N>   // most groups of a term: 32 or 64
 __global__ __launch_bounds__(kSelectThreads) void swap_q_kernel(SelectParams p) {
 #pragma clang fp contract(off)
-  __shared__ double s_val[kSelectPairs];
-  __shared__ int32_t s_arg[kSelectPairs];
+  __shared__ double s_val[kSelectThreads / kWave];
+  __shared__ int32_t s_arg[kSelectThreads / kWave];
   const int lane = lane_id();
   const int term = lane & (kPairLanes - 1);
   const int pair_in_block = threadIdx.x / kPairLanes;
@@ -677,67 +703,64 @@ __global__ __launch_bounds__(kSelectThreads) void swap_q_kernel(SelectParams p) 
     const double fan = intra ? (double)(p.G / p.U[p.d - 1]) : (double)(p.U[i] / p.U[intra ? 0 : i - 1]);
     const double scale = intra ? p.scale_intra : p.scale_inter[i];
     const double beta = intra ? p.beta_intra : p.beta_inter[i], alpha = intra ? p.alpha_intra : p.alpha_inter[i];
-    const double volume = fan * scale * smooth_max(x, n, p.gamma) * p.M * p.v;
+    const double volume = fan * scale * smooth_max<N>(x, n, p.gamma) * p.M * p.v;
     mine = volume * beta + alpha;
   }
   double q = 0.0;
   const int lane0 = lane & ~(kPairLanes - 1);
   for (int j = 0; j < p.d; ++j) q = q + __shfl(mine, lane0 + j, kWave);
-  if (term == 0) {
-    if (live) p.Q[rc] = q;
-    s_val[pair_in_block] = q;
-    s_arg[pair_in_block] = live ? (int32_t)rc : -1;
+  if (term == 0 && live) p.Q[rc] = q;
+  // the block's minimum: the pairs of a wave by shuffles (the four lanes of a pair hold the same q)
+  double best = q;
+  int32_t arg = live ? (int32_t)rc : -1;
+  wave_argmin(best, arg);
+  if (lane == 0) {
+    s_val[threadIdx.x / kWave] = best;
+    s_arg[threadIdx.x / kWave] = arg;
   }
   __syncthreads();
-  for (int off = kSelectPairs / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const int o = threadIdx.x + off;
-      const bool take = s_arg[o] >= 0 && (s_arg[threadIdx.x] < 0 || s_val[o] < s_val[threadIdx.x] ||
-                                          (s_val[o] == s_val[threadIdx.x] && s_arg[o] < s_arg[threadIdx.x]));
-      if (take) {   // among equal times the lower pair index survives
-        s_val[threadIdx.x] = s_val[o];
-        s_arg[threadIdx.x] = s_arg[o];
-      }
-    }
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    p.block_min[blockIdx.x] = s_val[0];
-    p.block_arg[blockIdx.x] = s_arg[0];
+    for (int w = 1; w < kSelectThreads / kWave; ++w) keep_better(best, arg, s_val[w], s_arg[w]);
+    p.block_min[blockIdx.x] = best;
+    p.block_arg[blockIdx.x] = arg;
   }
 }
 
-__global__ __launch_bounds__(kSwapThreads) void swap_argmin_kernel(SelectParams p) {
-  __shared__ double s_val[kSwapThreads];
-  __shared__ int32_t s_arg[kSwapThreads];
+// The first of the smallest block minima.  One workgroup, bound by its trip to memory and the steps to
+// one value: four minima per lane in flight, then shuffles within the waves and one step across them.
+constexpr int kArgminThreads = 1024;
+__global__ __launch_bounds__(kArgminThreads) void swap_argmin_kernel(SelectParams p) {
+  __shared__ double s_val[kArgminThreads / kWave];
+  __shared__ int32_t s_arg[kArgminThreads / kWave];
   double best = 0.0;
   int32_t arg = -1;
-  for (int b = threadIdx.x; b < p.nblocks; b += kSwapThreads) {   // ascending blocks: first minimum wins
-    const int32_t a = p.block_arg[b];
-    if (a >= 0 && (arg < 0 || p.block_min[b] < best)) {
-      best = p.block_min[b];
-      arg = a;
+  for (int b0 = 0; b0 < p.nblocks; b0 += 4 * kArgminThreads) {
+    double v[4];
+    int32_t a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int b = b0 + j * kArgminThreads + (int)threadIdx.x;
+      v[j] = b < p.nblocks ? p.block_min[b] : 0.0;
+      a[j] = b < p.nblocks ? p.block_arg[b] : -1;
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) keep_better(best, arg, v[j], a[j]);
   }
-  s_val[threadIdx.x] = best;
-  s_arg[threadIdx.x] = arg;
+  wave_argmin(best, arg);
+  if (lane_id() == 0) {
+    s_val[threadIdx.x / kWave] = best;
+    s_arg[threadIdx.x / kWave] = arg;
+  }
   __syncthreads();
-  for (int off = kSwapThreads / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const int o = threadIdx.x + off;
-      const bool better = s_arg[o] >= 0 && (s_arg[threadIdx.x] < 0 || s_val[o] < s_val[threadIdx.x] ||
-                                            (s_val[o] == s_val[threadIdx.x] && s_arg[o] < s_arg[threadIdx.x]));
-      if (better) {
-        s_val[threadIdx.x] = s_val[o];
-        s_arg[threadIdx.x] = s_arg[o];
-      }
-    }
-    __syncthreads();
-  }
+  if (threadIdx.x >= kWave) return;
+  constexpr int kWaves = kArgminThreads / kWave;
+  best = s_val[threadIdx.x & (kWaves - 1)];
+  arg = s_arg[threadIdx.x & (kWaves - 1)];
+  wave_argmin(best, arg);
   if (threadIdx.x == 0) {
-    p.best_pair[0] = s_arg[0] / p.E;
-    p.best_pair[1] = s_arg[0] % p.E;
-    *p.best_time = s_val[0];
+    p.best_pair[0] = arg / p.E;
+    p.best_pair[1] = arg % p.E;
+    *p.best_time = best;
   }
 }
 
@@ -858,8 +881,10 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
     p.ws_ints = 0;
     p.use_lds = 0;
     p.transposed = 1;
-    hipLaunchKernelGGL(swap_clear_kernel, dim3(1), dim3(kSwapThreads), 0, stream, p);
-    if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+    if (status) {
+      hipLaunchKernelGGL(swap_clear_kernel, dim3(1), dim3(kSwapThreads), 0, stream, p);
+      if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+    }
     CoocParams cp;
     cp.ids = topk_ids;
     cp.expert_to_rank = expert_to_rank;
@@ -1023,9 +1048,9 @@ extern "C" hm_status hm_swap_select(int32_t d, const int32_t *U, int32_t G, int3
   p.best_pair = best_pair;
   p.best_time = best_time;
   hipStream_t stream = (hipStream_t)hip_stream;
-  hipLaunchKernelGGL(swap_q_kernel, dim3(p.nblocks), dim3(kSelectThreads), 0, stream, p);
+  hipLaunchKernelGGL(G <= 32 ? swap_q_kernel<32> : swap_q_kernel<64>, dim3(p.nblocks), dim3(kSelectThreads), 0, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-  hipLaunchKernelGGL(swap_argmin_kernel, dim3(1), dim3(kSwapThreads), 0, stream, p);
+  hipLaunchKernelGGL(swap_argmin_kernel, dim3(1), dim3(kArgminThreads), 0, stream, p);
   return hm_launch_status();
 }
 
