@@ -69,7 +69,7 @@ struct PlanParams {
 // share a lane's destination is then one comparison of eight bytes at a time instead of a loop over
 // the slots, and the position among the wave's slots of one destination comes from one ballot per
 // bit of the destination instead of one per destination.  The kernel was bound by issuing those loops
-// (sixteen waves share a CU): 22 -> @WRITE@ us for the write launch of the 64 Ki-token layer.
+// (sixteen waves share a CU): 22 -> 20 us for the write launch of the 64 Ki-token layer.
 struct Tokens {
   int first_slot, first_token, tokens, words;   // of the workgroup; 8-byte words per token
   unsigned recip;                               // ceil(2^22 / K): exact for numerators below 1024 + 128, K <= 64

@@ -189,6 +189,38 @@ def test_swap_select_parity(hw, oracle):
     print("d=4 gamma=5 best pair", pair, "time", float(bt.item()), "no swap", Qg[0, 0])
 
 
+@pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (12, [1, 2, 6], 33), (33, [1, 3], 9), (6, [1, 3], 300), (1, [1], 5)])
+def test_swap_select_on_any_counts(hw, oracle, G, U, E):
+    """Terms of up to 64 groups and of lengths that are no multiple of four, counts that no swap tensor
+    would hold (not symmetric, zero rows), buffers one element into an allocation."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(G + E)
+    d = len(U)
+
+    def counts(n):
+        z = rng.integers(0, 5000, (E, E, n)).astype(np.int32)
+        z[E // 2, 1] = 0
+        store = torch.zeros(z.size + 1, dtype=torch.int32, device="cuda")
+        store[1:].copy_(hw.dev(z).view(-1))
+        return z, store[1:].view(E, E, n)
+
+    zi = [(None, None)] + [counts(U[i]) for i in range(1, d)]
+    intra_h, intra_d = counts(G)
+    alpha, beta, scale = [0.1 * i for i in range(d)], [1e-7 * (i + 1) for i in range(d)], [0.0] + [1.5] * (d - 1)
+    for gamma in (0.0, 10.0, 1.0, 2.5):
+        Qr, best_r, bt_r = oracle.swap_select(U, G, 64, 2.0, [z[0] for z in zi], intra_h, scale, 2.0, alpha, beta, 0.3, 1e-7, gamma)
+        Q = torch.full((E, E), float("nan"), dtype=torch.float64, device="cuda")
+        bp = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+        bt = torch.zeros(1, dtype=torch.float64, device="cuda")
+        B.hm_swap_select(U, G, 64, 2.0, [z[1] for z in zi], intra_d, scale, 2.0, alpha, beta, 0.3, 1e-7, gamma, Q, bp, bt)
+        Qg = Q.cpu().numpy()
+        # plain maximum: the same fp64 operations; otherwise at most 64 powers of a few ulp each and their root
+        assert np.array_equal(Qg, Qr) if gamma <= 0 else np.allclose(Qg, Qr, rtol=1e-12, atol=0), (G, U, gamma)
+        flat = int(np.argmin(Qg))
+        assert tuple(bp.tolist()) == (flat // E, flat % E) and float(bt.item()) == Qg.min()
+
+
 def test_planner_loop_stays_on_the_device(hw, oracle):
     """(Z, select, apply) repeated on the device with no host step in between; afterwards every
     iteration is replayed on the oracle.  gamma <= 0 keeps Q bit-exact, so the chosen pairs and
