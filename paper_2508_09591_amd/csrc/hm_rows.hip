@@ -824,6 +824,18 @@ static inline double rows_per_token(const hm_plan_out *plan, int32_t T) {
   return 0.0;
 }
 
+// Waves per CU of the dispatch of whole-line rows.  A wave with seven stores for its one load wants fewer
+// neighbours than one with three, as long as what it loads comes from the Infinity Cache (256 MB) and
+// not from memory.  HIP events, 24 -> 12 waves: 8,192 x 2,048 at rank level (7.36 rows per token) 51.8 -> 49.3 us,
+// 4,096 x 4,096 50.9 -> 48.4, 16,384 x 2,048 with 6.6 rows 86.4 -> 81.6, with 8.98 rows 123.1 -> 119.4; 8,192 x 7,168
+// 164.7 -> 164.8; but 16,384 x 4,096 with 5.4 rows 145 -> 159, the DeepSeek-V3 layer (3.1 rows) 81 -> 106,
+// and a token buffer of 470 MB 642 -> 651.  Only a known row count counts: the bound that hm_plan leaves is 8 for
+// the layer with 5.4.
+static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int32_t H) {
+  const bool many = plan->expected_rows > 6 * (int64_t)T;
+  return many && (int64_t)T * H * 2 <= (256ll << 20) ? 12 : kCopyWavesPerCu;
+}
+
 // Launch shape of the combine kernels: 16-byte vectors per lane, rows in flight per wave, and the
 // cap on resident waves per CU (32 = none).  Kept in one place so that the launcher and
 // hm_combine_launch_shape agree.
@@ -907,7 +919,7 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
                        packed);
   } else if (H >= 8 && H <= kMaxVectorH) {
     if (!grid_for_units(p, H, 8, whole, packed_bf16, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const unsigned lds = lds_cap_bytes(kCopyWavesPerCu, kCopyThreads);
+    const unsigned lds = lds_cap_bytes(whole ? dispatch_waves_per_cu(plan, T, H) : kCopyWavesPerCu, kCopyThreads);
     if (whole)
       hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds, stream, p, x, packed, packed_rows);
     else
