@@ -17,9 +17,10 @@
 // reads) seven or eight 1 KiB pieces per wave has several hundred KiB per CU queued at the
 // memory system, and the rate drops (a flat 1-read + 7-write stream: 64 % of peak with 32 waves
 // per CU, 78 % with 8); with too few waves the index lookups are no longer hidden.  The cap is
-// set with an unused dynamic LDS allocation: dispatch and the fp32 transpose run 24 waves per CU
-// (-5 % on the 64 Ki-token layer at node level, -9 % at rank level, neutral elsewhere; the bf16
-// transpose does more arithmetic per byte and is faster uncapped); combine keeps about 128 KiB
+// set with an unused dynamic LDS allocation: dispatch runs 24 waves per CU (-5 % on the 64 Ki-token
+// layer at node level, -9 % at rank level, neutral elsewhere), or 12 where many rows per token meet
+// cached tokens; the transposes, with an index more to wait for and (bf16) more arithmetic per byte,
+// are mostly faster uncapped; combine keeps about 128 KiB
 // of row loads in flight per CU (32 waves up to four rows per token, 16 at eight).
 //
 // Combine has two forms.  With the caller's weights (topk_weights != NULL) every wave merges the
@@ -38,7 +39,7 @@ namespace hm {
 
 constexpr int kElemThreads = 256;     // element-wise fallback kernels
 constexpr int kCopyThreads = 128;     // dispatch / transpose: two waves per workgroup ...
-constexpr int kCopyWavesPerCu = 24;   // ... and this many waves resident per CU (dispatch, fp32 transpose)
+constexpr int kCopyWavesPerCu = 24;   // ... and this many waves resident per CU, where they are capped
 constexpr int kCombineThreads = 256;
 constexpr int kCombineVecs = 4;       // combine with the caller's weights: 16-byte vectors per lane (4 KiB segments),
 constexpr int kCombineRows = 4;       //   rows whose loads are in flight together
@@ -836,6 +837,15 @@ static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int3
   return many && (int64_t)T * H * 2 <= (256ll << 20) ? 12 : kCopyWavesPerCu;
 }
 
+// Whether the transpose of whole-line fp32 rows keeps dispatch's 24 waves per CU.  It waits once more than
+// dispatch (for the row's weight, behind its index), so all wave slots are better unless the gradients
+// are cached and the rows many.  HIP events, 24 -> 32 waves: 16,384 x 2,048 with 7.1 rows 205 -> 192 us, with 3.4
+// 105 -> 101, 8,192 x 7,168 with 3.1 158.7 -> 155.1, 32,768 x 7,168 with 4 758 -> 733; but 8,192 x 2,048 with 7.4
+// (67 MB) 97.1 -> 98.5, 2,048 x 4,096 with 7.4 (34 MB) 48.6 -> 50.2.
+static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t H) {
+  return plan->expected_rows > 6 * (int64_t)T && (int64_t)T * H * 4 <= (96ll << 20);
+}
+
 // Launch shape of the combine kernels: 16-byte vectors per lane, rows in flight per wave, and the
 // cap on resident waves per CU (32 = none).  Kept in one place so that the launcher and
 // hm_combine_launch_shape agree.
@@ -1036,7 +1046,7 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
                        plan->row_weight, rows, (elem *)gy);
   } else if (H >= ROW::kPerVec && H <= kMaxVectorH) {
     if (!grid_for_units(p, H, ROW::kPerVec, whole, gy, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const unsigned lds = ROW::kPerVec == 4 ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;   // fp32 rows only
+    const unsigned lds = ROW::kPerVec == 4 && (!whole || transpose_capped(plan, T, H)) ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;
     if (whole)
       hipLaunchKernelGGL((transpose_rows_kernel<ROW>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
                          plan->row_weight, plan->row_capacity, (elem *)gy, gy_rows);
