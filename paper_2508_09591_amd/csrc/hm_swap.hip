@@ -191,10 +191,10 @@ __global__ __launch_bounds__(kFactorThreads) void swap_factors_kernel(SwapParams
 // expert of its group, and M[t][g] = 1 when t selects something in group g (all 0/1 bytes):
 //   C  = A^T S   (its diagonal is L)        CG = S^T M   (L0[a] = CG[a][group of a])
 // so the read-modify-write updates of popular expert pairs, which serialise on one address, become
-// int8 matrix products with int32 accumulators held in registers.  A first kernel, one lane per
-// routing slot over the whole chip, works out what only the token's other slots can tell (is this
-// the first occurrence of the expert, is it alone in its group under each cut) and leaves one byte
-// per slot.  In the second a workgroup takes one cut and a contiguous chunk of the tokens, builds
+// int8 matrix products with int32 accumulators held in registers.  What only the token's other slots
+// can tell (is this the first occurrence of the expert, is it alone in its group under the cut) is worked
+// out where the slots are read, or, for K > 8, by a kernel of its own that leaves one byte per slot.  In
+// the matrix kernel a workgroup takes one cut and a contiguous chunk of the tokens, builds
 // the three indicator tiles for 128 tokens at a time in LDS (expert-major, so that a lane's MFMA
 // operand is 16 contiguous bytes), and stores its partial tables with plain stores; a third kernel
 // sums the chunks.  No table is touched by an atomic.
@@ -231,8 +231,8 @@ struct CoocParams {
 __host__ __device__ static inline int64_t cooc_part_ints(int64_t E, int64_t ng) { return E * E + E * ng + 64; }   // values per chunk
 __host__ __device__ static inline int64_t cooc_part_words(int64_t E, int64_t ng) { return (cooc_part_ints(E, ng) + 1) / 2; }   // 32-bit words they take
 
-// One lane per routing slot; the K slots of a token sit in 2^sub_log2 consecutive lanes and learn
-// about each other through shuffles, eight in flight at a time.
+// One lane per routing slot (K > 8); the K slots of a token sit in 2^sub_log2 consecutive lanes and
+// learn about each other through shuffles, eight in flight at a time.
 __global__ __launch_bounds__(kSwapThreads) void swap_slots_kernel(CoocParams p) {
   const int sub = 1 << p.sub_log2;
   const int lane = lane_id();
@@ -303,7 +303,23 @@ __device__ __forceinline__ i32x16 mfma_i8(i32x4 a, i32x4 b, i32x16 acc) {
 // Workgroup (chunk, cut, panel).  Every wave holds one 32x32 tile of C, so a workgroup covers 16 of
 // them: all of C for E <= 128, and for E <= 256 one of four panels of two tile columns (the panels
 // repeat the cheap filling of the tiles and split the products, which is what E = 256 is bound by).
-template <int NE>   // experts padded to 32 * NE
+//
+// OWN_SLOTS (K <= 8): the workgroup works the slots out itself instead of reading the bytes of
+// swap_slots_kernel, which saves that launch (4 us and the gap before it, and the host's time for it; the work here is about 3 us per
+// 1,024 tokens): the experts and the groups of a token's slots meet in two 8-byte words, and a slot
+// compares its own with all of them at once.
+__device__ __forceinline__ uint32_t or_of_token(uint32_t v, int sub_log2) {   // over the 2^sub_log2 <= 8 lanes of a token
+  if (sub_log2 > 0) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);    // lane ^ 1
+  if (sub_log2 > 1) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);    // lane ^ 2
+  if (sub_log2 > 2) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);   // 7 - lane, of each eight
+  return v;
+}
+__device__ __forceinline__ uint64_t zero_bytes(uint64_t x) {   // 0x80 in every zero byte
+  const uint64_t low = 0x7F7F7F7F7F7F7F7Full;
+  return ~(((x & low) + low) | x | low);
+}
+
+template <int NE, bool OWN_SLOTS>   // experts padded to 32 * NE
 __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   constexpr int kPanels = NE * NE > kCoocWaves ? NE * NE / kCoocWaves : 1;   // gridDim.z
   constexpr int kCols = NE / kPanels;                                         // tile columns of a panel
@@ -322,7 +338,7 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
     i32x4 *z = (i32x4 *)tiles;
     for (int i = tid; i < kVecs; i += kCoocThreads) z[i] = i32x4{0, 0, 0, 0};
     if (tid < 32 * NE) {
-      int g = 0;   // an expert with no valid placement is never marked first, so its entry is not read
+      int g = 0xFF;   // no valid placement
       if (tid < p.E) {
         const int r = p.expert_to_rank[tid];
         if ((unsigned)r < (unsigned)p.G) g = r / per;
@@ -375,7 +391,36 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
       for (int j = 0; j < kCoocStaged; ++j) {
         const int64_t t = min(stage0 + (int64_t)j * tok_pass + tp1, t_end - 1);
         id[j] = p.ids[t * p.K + k];
-        bits[j] = p.slot_bits[t * p.K + k];
+        if (!OWN_SLOTS) bits[j] = p.slot_bits[t * p.K + k];
+      }
+      if (OWN_SLOTS) {
+        bool bad = false;
+        const int lane_place = tid & (sub - 1), at = 8 * (lane_place & 3);
+        const bool upper = lane_place >= 4;
+        const uint64_t no_slot = p.sub_log2 < 3 ? ~0ull << (8 * sub) : 0ull;   // bytes without a lane
+        const uint64_t before = (1ull << (8 * lane_place)) - 1ull;
+#pragma unroll
+        for (int j = 0; j < kCoocStaged; ++j) {
+          bits[j] = 0;
+          if (stage0 + (int64_t)j * tok_pass >= t_end) continue;   // uniform: the chunk may be shorter than a stage
+          const bool in = mine && stage0 + (int64_t)j * tok_pass + tp1 < t_end;
+          const bool known = (unsigned)id[j] < (unsigned)p.E;
+          const uint32_t g = known ? group_of_expert[id[j]] : 0xFFu;
+          const bool valid = in && g != 0xFFu;
+          bad = bad || (in && !valid && id[j] != -1);
+          const uint32_t e = valid ? (uint32_t)id[j] : 0u, gb = valid ? g : 0xFFu;
+          const uint64_t experts = (uint64_t)or_of_token(upper ? e << at : 0u, p.sub_log2) << 32 |
+                                   or_of_token(upper ? 0u : e << at, p.sub_log2);
+          const uint64_t groups = ((uint64_t)or_of_token(upper ? gb << at : 0u, p.sub_log2) << 32 |
+                                   or_of_token(upper ? 0u : gb << at, p.sub_log2)) | no_slot;
+          const uint64_t there = ~groups & 0x8080808080808080ull;   // groups are below 64
+          const uint64_t same = zero_bytes(experts ^ (e * 0x0101010101010101ull)) & there;
+          const uint64_t together = zero_bytes(groups ^ (gb * 0x0101010101010101ull)) & there;
+          const bool first = valid && (same & before) == 0;
+          const bool alone = (together & ~same) == 0;   // nothing but copies of itself in its group
+          bits[j] = first ? 1 | (alone ? alone_bit : 0) : 0;
+        }
+        if (bad && cut == 0 && panel == 0) flag(p.status, HM_ERR_BAD_ID);
       }
 #pragma unroll
       for (int j = 0; j < kCoocStaged; ++j) {
@@ -908,18 +953,24 @@ static inline int64_t swap_slot_ints(int64_t T, int64_t K, int64_t E) { return s
 
 // The matrix kernel for E experts, its dynamic LDS, and whether the device grants that much.
 typedef void (*cooc_kernel_t)(CoocParams);
+template <bool OWN_SLOTS>
 static inline cooc_kernel_t cooc_kernel(int E, size_t *lds_bytes) {
   const int ne = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8;
   *lds_bytes = (size_t)(2 * 32 * ne + kCoocGroups) * kCoocStride;
-  return ne == 1 ? swap_cooc_kernel<1> : ne == 2 ? swap_cooc_kernel<2> : ne == 4 ? swap_cooc_kernel<4> : swap_cooc_kernel<8>;
+  return ne == 1 ? swap_cooc_kernel<1, OWN_SLOTS> : ne == 2 ? swap_cooc_kernel<2, OWN_SLOTS>
+       : ne == 4 ? swap_cooc_kernel<4, OWN_SLOTS> : swap_cooc_kernel<8, OWN_SLOTS>;
 }
 static bool cooc_lds_ready() {
   static const bool ok = [] {
-    size_t bytes = 0;
-    const cooc_kernel_t k = cooc_kernel(kCoocMaxE, &bytes);   // only the largest needs more than the default
-    const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e != hipSuccess) (void)hipGetLastError();
-    return e == hipSuccess;
+    bool granted = true;
+    for (int own = 0; own < 2; ++own) {   // only the largest need more than the default
+      size_t bytes = 0;
+      const cooc_kernel_t k = own ? cooc_kernel<true>(kCoocMaxE, &bytes) : cooc_kernel<false>(kCoocMaxE, &bytes);
+      const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+      if (e != hipSuccess) (void)hipGetLastError();
+      granted = granted && e == hipSuccess;
+    }
+    return granted;
   }();
   return ok;
 }
@@ -973,7 +1024,9 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
   }
   p.status = status;
   size_t cooc_lds = 0;
-  const cooc_kernel_t cooc = swap_by_matrices(E, T) ? cooc_kernel(E, &cooc_lds) : nullptr;
+  const bool own_slots = K <= 8;
+  const cooc_kernel_t cooc = !swap_by_matrices(E, T) ? nullptr
+                             : own_slots ? cooc_kernel<true>(E, &cooc_lds) : cooc_kernel<false>(E, &cooc_lds);
   if (cooc && (cooc_lds <= 65536 || cooc_lds_ready())) {
     // Every table is written in full by the kernels below: only the status word needs clearing.
     p.ws_ints = 0;
@@ -1010,7 +1063,7 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
       if (c < ncuts && reduce_tiles(E, ng[c]) > max_tiles) max_tiles = reduce_tiles(E, ng[c]);
     }
     cp.status = status;
-    if (T > 0) {
+    if (T > 0 && !own_slots) {
       const int64_t lanes = (int64_t)T << cp.sub_log2;
       hipLaunchKernelGGL(swap_slots_kernel, dim3((unsigned)((lanes + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0,
                          stream, cp);

@@ -150,6 +150,29 @@ def test_swap_counts_long_chunks(hw, oracle, E, G, K, T, cuts):
         assert np.array_equal(z.cpu().numpy(), ref), (E, G, K, T, u)
 
 
+@pytest.mark.parametrize("E,G,ng,K,T", [(256, 64, 64, 8, 1700), (255, 8, 4, 7, 513), (37, 32, 32, 5, 130), (256, 16, 1, 4, 257),
+                                        (12, 4, 2, 3, 128), (5, 5, 5, 2, 129), (1, 1, 1, 1, 60), (64, 32, 8, 9, 700)])
+def test_swap_counts_on_crowded_tokens(hw, oracle, E, G, ng, K, T):
+    """Tokens full of repeated experts and of experts that share a group, the highest expert id and
+    experts without a valid placement, around the eight slots up to which the matrix kernel works the
+    slots out itself and around its tile of 128 tokens."""
+    rng = np.random.default_rng(E + K)
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    crowd = rng.random(T) < 0.5
+    ids[crowd] = np.where(rng.random((int(crowd.sum()), K)) < 0.5, E - 1, ids[crowd, :1])   # two experts per token at most
+    ids[rng.random((T, K)) < 0.1] = -1
+    e2r = rng.integers(0, G, E).astype(np.int32)
+    for bad in (False, True):
+        if bad:
+            ids[T // 2, K - 1] = E
+            ids[0, 0] = -9
+            e2r[E // 2] = G
+        ref, st_ref = oracle.swap_counts(ids, e2r, G, ng, "incremental")
+        Z, st = _gpu_z(hw, ids, e2r, G, ng)
+        assert st == st_ref and (st != 0) == bad
+        assert np.array_equal(Z.cpu().numpy(), ref), (E, G, ng, K, T, bad)
+
+
 def test_swap_select_parity(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
