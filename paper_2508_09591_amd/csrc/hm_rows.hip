@@ -838,12 +838,15 @@ static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int3
 }
 
 // Whether the transpose of whole-line fp32 rows keeps dispatch's 24 waves per CU.  It waits once more than
-// dispatch (for the row's weight, behind its index), so all wave slots are better unless the gradients
-// are cached and the rows many.  HIP events, 24 -> 32 waves: 16,384 x 2,048 with 7.1 rows 205 -> 192 us, with 3.4
-// 105 -> 101, 8,192 x 7,168 with 3.1 158.7 -> 155.1, 32,768 x 7,168 with 4 758 -> 733; but 8,192 x 2,048 with 7.4
-// (67 MB) 97.1 -> 98.5, 2,048 x 4,096 with 7.4 (34 MB) 48.6 -> 50.2.
+// dispatch (for the row's weight, behind its index), so all wave slots are better, except where the rows
+// are many and the gradients either cached or very large.  HIP events, 24 -> 32 waves, two runs of each: 16,384 x
+// 2,048 with 7.1 rows 204 -> 191 us, 65,536 x 2,048 with 7.4 825 -> 792, 16,384 x 7,168 with 7.5 724 -> 626, 32,768 x
+// 7,168 1,401 -> 1,305, 16,384 x 4,096 with 8 454 -> 432, 8,192 x 7,168 with 3.1 158.7 -> 155.1, 32,768 x 7,168 with 4
+// 758 -> 733; but 8,192 x 2,048 with 7.4 (67 MB) 97.1 -> 98.5, 2,048 x 4,096 with 7.4 (34 MB) 48.6 -> 50.2, 65,536 x
+// 7,168 with 7.5 (1.9 GB) 2,870 -> 3,000.
 static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t H) {
-  return plan->expected_rows > 6 * (int64_t)T && (int64_t)T * H * 4 <= (96ll << 20);
+  const int64_t bytes = (int64_t)T * H * 4;
+  return plan->expected_rows > 6 * (int64_t)T && (bytes <= (96ll << 20) || bytes > (1ll << 30));
 }
 
 // Launch shape of the combine kernels: 16-byte vectors per lane, rows in flight per wave, and the
