@@ -51,8 +51,11 @@ struct PlanParams {
   const float *weights;
   const int32_t *expert_to_rank;
   const int32_t *dest_map;  // non-null: destinations come from this table (hm_plan_mapped)
-  int32_t T, K, E, G, R, Dn, level;
+  int32_t T, K, E, G, R, N, Dn, level;   // N = G / R nodes
   int32_t nslots, nblocks;
+  uint64_t k_recip;      // ceil(2^64 / K), 0 for K = 1
+  uint32_t k_recip22;    // ceil(2^22 / K): exact for numerators below 1024 + 128, K <= 64
+  uint32_t r_recip16;    // ceil(2^16 / R): exact for ranks (below 64)
   int32_t scanned;  // counts holds exclusive prefixes over workgroups and the totals in row nblocks
   int64_t row_capacity;
   int32_t *counts;  // workspace [nblocks + 1][Dn]
@@ -74,22 +77,24 @@ struct PlanParams {
 // (sixteen waves share a CU): 22 -> 20 us for the write launch of the 64 Ki-token layer.
 struct Tokens {
   int first_slot, first_token, tokens, words;   // of the workgroup; 8-byte words per token
-  unsigned recip;                               // ceil(2^22 / K): exact for numerators below 1024 + 128, K <= 64
 };
+__device__ __forceinline__ int token_of_slot(const PlanParams &p, int s) {
+  return p.k_recip ? (int)__umul64hi((uint64_t)(unsigned)s, p.k_recip) : s;
+}
+__device__ __forceinline__ int node_of(const PlanParams &p, int rank) { return (int)(((uint32_t)rank * p.r_recip16) >> 16); }
 __device__ __forceinline__ Tokens tokens_of_block(const PlanParams &p) {
   Tokens k;
   k.first_slot = (int)blockIdx.x * kPlanThreads;
-  k.first_token = (int)((unsigned)k.first_slot / (unsigned)p.K);
+  k.first_token = token_of_slot(p, k.first_slot);
   const int slots = min(kPlanThreads, p.nslots - k.first_slot);   // none in an empty plan
-  k.tokens = slots < 1 ? 0 : (int)((unsigned)(k.first_slot + slots - 1) / (unsigned)p.K) - k.first_token + 1;
+  k.tokens = slots < 1 ? 0 : token_of_slot(p, k.first_slot + slots - 1) - k.first_token + 1;
   k.words = (p.K + 7) >> 3;
-  k.recip = ((1u << 22) + (unsigned)p.K - 1u) / (unsigned)p.K;
   return k;
 }
 // Token (counted from the workgroup's first) and place in it of a slot of the workgroup's tokens.
 __device__ __forceinline__ int token_of(const PlanParams &p, const Tokens &k, int s, int &place) {
   const unsigned q = (unsigned)(s - k.first_token * p.K);
-  const int t = (int)((q * k.recip) >> 22);
+  const int t = (int)((q * p.k_recip22) >> 22);
   place = (int)q - t * p.K;
   return t;
 }
@@ -160,8 +165,8 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8,
   if (threadIdx.x < kWave) cnt[threadIdx.x] = 0;
   int dest = lookup_global(p, id), dest2 = lookup_global(p, id2);
   if (p.level == HM_DEDUP_NODE && !p.dest_map) {
-    dest = dest >= 0 ? dest / p.R : dest;
-    dest2 = dest2 >= 0 ? dest2 / p.R : dest2;
+    dest = dest >= 0 ? node_of(p, dest) : dest;
+    dest2 = dest2 >= 0 ? node_of(p, dest2) : dest2;
   }
   __syncthreads();
   int place = 0, place2 = 0;
@@ -183,7 +188,7 @@ __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8,
     const int64_t stride = (int64_t)gridDim.x * kPlanThreads;
     for (int64_t i = (int64_t)blockIdx.x * kPlanThreads + threadIdx.x; i < p.E; i += stride) p.load_expert[i] = 0;
     if (blockIdx.x == 0 && (int)threadIdx.x < p.G) p.load_rank[threadIdx.x] = 0;
-    if (blockIdx.x == 0 && (int)threadIdx.x < p.G / p.R) p.load_node[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && (int)threadIdx.x < p.N) p.load_node[threadIdx.x] = 0;
   }
 }
 
@@ -299,7 +304,7 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
       } else {
         const int g = p.expert_to_rank[e];
         v = ((unsigned)g >= (unsigned)p.G) ? -1 : g;
-        if (v >= 0) n = v / p.R;
+        if (v >= 0) n = node_of(p, v);
       }
       s_map[e] = (int8_t)v;
       s_nmap[e] = (int8_t)n;
@@ -317,7 +322,7 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
     if (loads) {
       for (int i = threadIdx.x; i < p.E; i += kPlanThreads) st_device(p.load_expert + i, 0);
       if ((int)threadIdx.x < p.G) st_device(p.load_rank + threadIdx.x, 0);
-      if ((int)threadIdx.x < p.G / p.R) st_device(p.load_node + threadIdx.x, 0);
+      if ((int)threadIdx.x < p.N) st_device(p.load_node + threadIdx.x, 0);
     }
     wait_for_own_stores();
   }
@@ -333,7 +338,7 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
         if (r >= 0) n = s_nmap[i];
       } else {
         r = lookup_global(p, i);
-        if (r >= 0 && !p.dest_map) n = r / p.R;
+        if (r >= 0 && !p.dest_map) n = node_of(p, r);
       }
     };
     auto put = [&](int t, int at, int r, int n) {
@@ -407,7 +412,7 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
         const uint64_t field = p.R >= 64 ? ~0ull : (1ull << p.R) - 1ull;
         uint32_t nodes = 0;
         if (!p.dest_map)
-          for (int n = 0; n < p.G / p.R; ++n) nodes |= ((ranks >> (n * p.R)) & field) ? 1u << n : 0u;
+          for (int n = 0; n < p.N; ++n) nodes |= ((ranks >> (n * p.R)) & field) ? 1u << n : 0u;
         p.node_mask[t] = nodes;
       }
     }
@@ -474,7 +479,7 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
   if (go) {
     if (FUSED && threadIdx.x == 0) st_device(passed + bid, tag);
     if (loads) {   // global atomics first: they complete in the shadow of the map stores
-      const int nodes = p.G / p.R;
+      const int nodes = p.N;
       if (ALONE && staged_table) {
         for (int e = threadIdx.x; e < p.E; e += kPlanThreads) p.load_expert[e] = hist[e];
       } else if (staged_table) {
@@ -706,6 +711,10 @@ static std::atomic<int> one_launch_limit{kPlanFusedMaxBlocks};
 // p.nblocks, p.Dn and p.counts are set.
 static inline hm_status launch_plan(PlanParams &p, hipStream_t stream) {
   const bool loads = p.load_expert != nullptr;
+  p.N = p.G / p.R;
+  p.k_recip = p.K > 1 ? ~0ull / (uint64_t)p.K + 1 : 0;
+  p.k_recip22 = ((1u << 22) + (uint32_t)p.K - 1u) / (uint32_t)p.K;
+  p.r_recip16 = (65536u + (uint32_t)p.R - 1u) / (uint32_t)p.R;
   const int staged = p.E <= kPlanStagedExperts ? 1 : 0;   // tables (and histogram) in LDS
   const unsigned lds = staged ? ((loads ? (unsigned)p.E * sizeof(int32_t) : 0u) + ((2u * (unsigned)p.E + 15u) & ~15u)) : 0u;
   if (p.nblocks == 1 && staged) {
