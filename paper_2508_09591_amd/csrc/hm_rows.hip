@@ -646,7 +646,9 @@ __device__ __forceinline__ void for_slots(int K, FN fn) {
   for (; k0 < K; ++k0) fn(std::integral_constant<int, 1>{}, k0);
 }
 
-// Dispatch (SCALED = false) and transpose.
+// Dispatch (SCALED = false) and transpose.  A lane reads a weight for every slot, that of row 0 for a slot
+// without a row, so the transpose is launched only where there is a row 0 (rows > 0): a read
+// under the slot's own condition costs 0.5 to 0.8 us (8,192 tokens, 3.6 rows of 64 bf16: 5.2 -> 6.0).
 template <typename ROW, bool SCALED>
 __global__ __launch_bounds__(kFlatThreads) void spread_flat_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
                                                                    const float *__restrict__ row_weight, int64_t rows,
@@ -1043,7 +1045,7 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   dim3 grid;
   const bool whole = whole_lines(H, sizeof(elem), gout, gy);
   const int64_t rows = plan->row_capacity < gy_rows ? plan->row_capacity : gy_rows;
-  if (flat_rows(H, ROW::kPerVec, whole, true)) {
+  if (rows > 0 && flat_rows(H, ROW::kPerVec, whole, true)) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((spread_flat_kernel<ROW, true>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)gout,
                        plan->row_weight, rows, (elem *)gy);

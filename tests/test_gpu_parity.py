@@ -434,6 +434,34 @@ def test_rows_of_any_length(hw, oracle, H, K, off):
         assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
 
 
+@pytest.mark.parametrize("H", [7, 8, 16, 130, 384, 448])
+def test_transposes_with_room_for_no_row(hw, oracle, H):
+    """A plan whose row arrays hold no row (row_capacity 0) and a gy of no rows: nothing is written, no
+    weight is read (there is none), and rows that exist are flagged.  Slots the router dropped own no row,
+    so a table of nothing else is not an error."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(H)
+    T, K, E, nodes, rpn = 70, 9, 12, 2, 2
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    dropped = np.full((T, K), -1, dtype=np.int32)
+    w = rng.random((T, K), dtype=np.float32)
+    e2r = rng.integers(0, nodes * rpn, E, dtype=np.int32)
+    calls = ((B.hm_combine_transpose, torch.float32), (B.hm_combine_transpose_bf16, torch.bfloat16))
+    for table, capacity, rows in ((ids, 0, 5), (ids, 0, 0), (ids, None, 0), (dropped, 0, 5), (dropped, 0, 0)):
+        for fn, dtype in calls:
+            ctx = "no room H=%d %s capacity=%s rows=%d" % (H, fn.__name__, capacity, rows)
+            print("case:", ctx, flush=True)
+            g = hw.GpuPlan(table, w, e2r, nodes, rpn, GPU, row_capacity=capacity)
+            assert g.status == (B.HM_ERR_CAPACITY if capacity == 0 and table is ids else 0), ctx
+            g.plan.status.zero_()
+            gout = torch.ones((T, H), dtype=dtype, device="cuda")
+            gy = torch.full((rows + 1, H), 77.0, dtype=dtype, device="cuda")
+            fn(gout, g.plan, gy[:rows])
+            assert (gy == 77.0).all(), ctx
+            assert B.hm_plan_status(g.plan)[0] == (B.HM_ERR_CAPACITY if table is ids else 0), ctx
+
+
 def test_bad_ids_and_small_buffers_are_flagged_not_faulted(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
