@@ -138,6 +138,7 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   const int most = E > kWave ? E : kWave;
   hipLaunchKernelGGL(load_clear_kernel, dim3((most + kLoadThreads - 1) / kLoadThreads), dim3(kLoadThreads), 0, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+  if (T == 0) return HM_OK;   // cleared outputs are the counts
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
   if (blocks > 1024) blocks = 1024;
   hipLaunchKernelGGL((load_count_kernel<kLoadThreads, false>), dim3((unsigned)blocks), dim3(kLoadThreads), 0, stream, p);

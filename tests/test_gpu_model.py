@@ -80,6 +80,20 @@ def test_counts_at_the_edges(hw, oracle, T, K, E, nodes, rpn):
         assert (st == B.HM_ERR_BAD_ID) == bad
 
 
+@pytest.mark.parametrize("E", [1, 4096, 8192, 8193, 20000])
+def test_counts_of_no_tokens(hw, E):
+    """No tokens, placement tables on either side of what the one-launch form and LDS take: every count and
+    the status word are cleared, without an error."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    ids, e2r = torch.empty((0, 8), dtype=torch.int32, device="cuda"), torch.zeros(E, dtype=torch.int32, device="cuda")
+    out = [torch.full((n,), -3, dtype=torch.int32, device="cuda") for n in (E, 8, 2, 1)]
+    B.hm_expert_load(ids, e2r, 2, 4, *out)
+    counts, status = torch.full((3, 64), -5, dtype=torch.int32, device="cuda"), torch.full((1,), -5, dtype=torch.int32, device="cuda")
+    B.hm_group_counts(ids, e2r, 8, [8, 2, 1], counts, status)
+    assert not any(t.any() for t in out + [counts, status])
+
+
 def test_alltoall_times_parity(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
