@@ -70,11 +70,11 @@ __device__ __forceinline__ int64_t divided(int64_t n, uint64_t recip) {
 }
 
 // Wave-uniform (token, segment) of this wave, or false when past the end.
-template <int BLOCK>
+template <int BLOCK, bool DIVIDE = false>
 __device__ __forceinline__ bool unit_of_wave(const RowParams &p, int &t, int &seg) {
   const int64_t unit = (int64_t)blockIdx.x * (BLOCK / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (unit >= p.nunits) return false;
-  t = (int)divided(unit, p.recip);
+  t = (int)(DIVIDE ? unit / p.nseg : divided(unit, p.recip));
   seg = (int)(unit - (int64_t)t * p.nseg);
   return true;
 }
@@ -490,14 +490,19 @@ __global__ __launch_bounds__(kElemThreads) void combine_elems_kernel(RowParams p
 // ---------------------------------------------------------------------------------------------
 // transpose: gy[slot_row[t,k], :] = row_weight[row] * gout[t, :] for kept slots (fp32)
 // ---------------------------------------------------------------------------------------------
-template <typename ROW>
+// DIVIDE: the wave's token by a division, which takes a wave some two hundred cycles longer than the multiplication
+// everywhere else: bf16 rows of several GB are written faster by waves that start that much later (65,536 x
+// 7,168, 7.5 rows per token: 1,437 us, 1,514 with the multiplication, 1,449 with it and a sleep of 512 cycles, 1,510
+// with it and 24 waves per CU; 32,768 x 7,168 715 and 724, 65,536 x 4,096 with 7.3 rows 794 and 802; no
+// difference below 2 GB), while with one row per token the multiplication is better (16,384 x 2,048 25.6 -> 24.9).
+template <typename ROW, bool DIVIDE>
 __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams p, const typename ROW::elem *__restrict__ gout,
                                                                       const float *__restrict__ row_weight,
                                                                       int64_t weight_rows, typename ROW::elem *__restrict__ gy,
                                                                       int64_t gy_rows) {
   typedef WholeRows<typename ROW::elem> access;
   int t, seg;
-  if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
+  if (!unit_of_wave<kCopyThreads, DIVIDE>(p, t, seg)) return;
   const int lane = lane_id();
   int at;
   const bool in_row = access::place(p, 0, seg * kWave + lane, at);
@@ -1052,12 +1057,15 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   } else if (H >= ROW::kPerVec && H <= kMaxVectorH) {
     if (!grid_for_units(p, H, ROW::kPerVec, whole, gy, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
     const unsigned lds = ROW::kPerVec == 4 && (!whole || transpose_capped(plan, T, H)) ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;
-    if (whole)
-      hipLaunchKernelGGL((transpose_rows_kernel<ROW>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
-                         plan->row_weight, plan->row_capacity, (elem *)gy, gy_rows);
-    else
+    if (whole) {
+      const bool divide = ROW::kPerVec == 8 && (double)T * H * 2 * rows_per_token(plan, T) > 2e9;   // bytes written
+      hipLaunchKernelGGL((divide ? transpose_rows_kernel<ROW, ROW::kPerVec == 8> : transpose_rows_kernel<ROW, false>), grid,
+                         dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, plan->row_capacity,
+                         (elem *)gy, gy_rows);
+    } else {
       hipLaunchKernelGGL((spread_ragged_kernel<ROW, true>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
                          plan->row_weight, rows, (elem *)gy);
+    }
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((transpose_elems_kernel<ROW>), grid, dim3(kElemThreads), 0, stream, p, H, (const elem *)gout,

@@ -434,6 +434,25 @@ def test_rows_of_any_length(hw, oracle, H, K, off):
         assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
 
 
+@pytest.mark.parametrize("T,H", [(1, 64), (37, 512), (100, 576), (129, 7168)])
+def test_bf16_transpose_where_many_rows_are_expected(hw, oracle, T, H):
+    """The launch depends on the bytes the plan says will be written: the same bits whatever it expects."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(H)
+    ids, w = rng.integers(0, 24, (T, 6), dtype=np.int32), rng.random((T, 6), dtype=np.float32)
+    e2r = rng.integers(0, 8, 24, dtype=np.int32)
+    gout = W.f32_to_bf16_bits(rng.standard_normal((T, H)).astype(np.float32))
+    ora = oracle.plan(ids, w, e2r, 2, 4, GPU)
+    ref = oracle.combine_transpose_bf16(gout, ora.row_token, ora.row_weight)
+    g = hw.GpuPlan(ids, w, e2r, 2, 4, GPU)
+    for expected in (0, ora.total_rows, 1 << 40):
+        g.plan.c.expected_rows = expected
+        gy = torch.full((ora.total_rows, H), 77.0, dtype=torch.bfloat16, device="cuda")
+        B.hm_combine_transpose_bf16(hw.to_dev_bf16(gout), g.plan, gy)
+        assert np.array_equal(hw.bf16_to_host(gy), ref), expected
+
+
 @pytest.mark.parametrize("H", [7, 8, 16, 130, 384, 448])
 def test_transposes_with_room_for_no_row(hw, oracle, H):
     """A plan whose row arrays hold no row (row_capacity 0) and a gy of no rows: nothing is written, no
