@@ -19,8 +19,8 @@
 // per CU, 78 % with 8); with too few waves the index lookups are no longer hidden.  The cap is
 // set with an unused dynamic LDS allocation: dispatch runs 24 waves per CU (-5 % on the 64 Ki-token
 // layer at node level, -9 % at rank level, neutral elsewhere), or 12 where many rows per token meet
-// cached tokens; the transposes, with an index more to wait for and (bf16) more arithmetic per byte,
-// are mostly faster uncapped; combine keeps about 128 KiB
+// cached tokens; the bf16 transpose does more arithmetic per byte and is faster uncapped, the fp32 one is
+// capped where transpose_capped says so; combine keeps about 128 KiB
 // of row loads in flight per CU (32 waves up to four rows per token, 16 at eight).
 //
 // Combine has two forms.  With the caller's weights (topk_weights != NULL) every wave merges the
@@ -844,16 +844,24 @@ static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int3
   return many && (int64_t)T * H * 2 <= (256ll << 20) ? 12 : kCopyWavesPerCu;
 }
 
-// Whether the transpose of whole-line fp32 rows keeps dispatch's 24 waves per CU.  It waits once more than
-// dispatch (for the row's weight, behind its index), so all wave slots are better, except where the rows
-// are many and the gradients either cached or very large.  HIP events, 24 -> 32 waves, two runs of each: 16,384 x
-// 2,048 with 7.1 rows 204 -> 191 us, 65,536 x 2,048 with 7.4 825 -> 792, 16,384 x 7,168 with 7.5 724 -> 626, 32,768 x
-// 7,168 1,401 -> 1,305, 16,384 x 4,096 with 8 454 -> 432, 8,192 x 7,168 with 3.1 158.7 -> 155.1, 32,768 x 7,168 with 4
-// 758 -> 733; but 8,192 x 2,048 with 7.4 (67 MB) 97.1 -> 98.5, 2,048 x 4,096 with 7.4 (34 MB) 48.6 -> 50.2, 65,536 x
-// 7,168 with 7.5 (1.9 GB) 2,870 -> 3,000.
+// Whether the fp32 transpose of rows cut by WholeRows keeps dispatch's 24 waves per CU.  A wave waits once
+// more than dispatch does (for the row's weight, behind its index), which more waves hide, but more waves also
+// queue more stores.  HIP events, graphs of ten calls, both forms in turn on the same buffers, two seeds each, capped ->
+// uncapped in us (runs of one form differ by 0.5 %):
+//   about one row per token: uncapped 4 to 15 % faster at every size (2,048 x 7,168 23.0 -> 20.3, 16,384 x 2,048
+//     48.8 -> 42.4, 65,536 x 2,048 200 -> 179, 65,536 x 7,168 676 -> 618);
+//   two rows: capped (2,048 x 2,048 6.8 -> 6.9, 16,384 x 1,024 30.7 -> 30.9, 65,536 x 7,168 903 -> 969);
+//   three or four rows: uncapped above 1 GB written (32,768 x 2,048 182.2 -> 180.2, 65,536 x 2,048 401 -> 389.5, 65,536 x
+//     4,096 795 -> 773, 32,768 x 7,168 613 -> 603), capped below (8,192 x 7,168 138.7 -> 139.9, 8,192 x 2,048 equal);
+//   seven rows: uncapped above 2.5 GB written as long as the gradients are below 0.75 GB (65,536 x 2,048 842 -> 789,
+//     65,536 x 2,560 1,043 -> 1,017, 32,768 x 4,096 827 -> 794 and 845 -> 775, 16,384 x 7,168 722 -> 696), else capped (4,096
+//     x 4,096 91.3 -> 93.0, 16,384 x 2,048 170.2 -> 170.6, 32,768 x 2,048 354 -> 361, 16,384 x 4,096 366 -> 369; 32,768
+//     x 7,168 1,506 -> 1,549, 65,536 x 7,168 2,979 -> 3,130).
 static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t H) {
-  const int64_t bytes = (int64_t)T * H * 4;
-  return plan->expected_rows > 6 * (int64_t)T && (bytes <= (96ll << 20) || bytes > (1ll << 30));
+  const double c = rows_per_token(plan, T), in = (double)T * H * 4, out = in * c;
+  if (c > 6.0) return out < 2.5e9 || in > 0.75e9;
+  if (c > 2.5) return out < 1e9;
+  return c <= 0.0 || c >= 1.5;   // an unknown number of rows: capped
 }
 
 // Launch shape of the combine kernels: 16-byte vectors per lane, rows in flight per wave, and the
