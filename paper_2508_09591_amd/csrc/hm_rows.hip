@@ -80,14 +80,15 @@ __device__ __forceinline__ bool unit_of_wave(const RowParams &p, int &t, int &se
 }
 
 // How a row is cut into 16-byte vectors.
-// WholeRows: the rows of every buffer are whole 128-byte lines; vector v is elements [v P, v P + P).
+// WholeRows: the rows of both buffers are whole, aligned 16-byte vectors; vector v is elements [v P, v P + P).
 // RaggedRows: any length of at least one vector, at the alignment of the elements.  The vectors follow
 // the 16-byte grid of the buffer that is WRITTEN, counted from the 128-byte line that holds the row's
 // first element, so that two waves share no line inside a row: a wave that stores part of a line
 // leaves the rest to a wave behind another die's L2, and each of them then writes a piece of it to
-// memory.  Reads take whatever alignment results.  A vector that reaches over the row's first or last element is moved inside the row
-// instead: its values are computed twice from the same inputs, to the same bits, and stored twice,
-// which needs neither a tail loop nor a mask.
+// memory.  Reads take whatever alignment results.  A vector that reaches over the row's first or last
+// element is moved inside the row instead: its values are computed twice from the same inputs, to the same
+// bits, and stored twice, which needs neither a tail loop nor a mask.  (Where the last vector is the first
+// of a wave's segment, that wave stores into the last line of the wave before it, too.)
 template <typename ELEM>
 struct WholeRows {
   typedef u32x4 vec;
@@ -594,11 +595,12 @@ __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p
 }
 
 // ---------------------------------------------------------------------------------------------
-// Narrow rows: of fewer vectors than a wave has lanes.  One lane per (token, vector), tokens side by
-// side, so that the lanes are busy however short the rows are; a lane reads its token's slots itself
-// (the lanes of a token read the same words), several at a time.
+// Narrow rows: of fewer vectors than a wave has lanes, or of little more than a multiple of that.  One lane
+// per (token, vector), tokens side by side, so that the lanes are busy however short the rows are; a lane
+// reads its token's slots itself (the lanes of a token read the same words), several at a time.
 // ---------------------------------------------------------------------------------------------
 constexpr int kFlatThreads = 256;
+constexpr int kFlatVecs = 144;   // most vectors per row that unit_of_lane divides exactly (and more than any rule asks for)
 
 // Vectors from the row's start; the last one is moved inside the row.
 template <typename ELEM>
@@ -610,7 +612,8 @@ struct NarrowRows : RaggedRows<ELEM> {
 };
 
 // (token, vector) of this lane, or false when past the end.  The workgroup's first unit is divided by a
-// 64-bit reciprocal, the rest is a numerator below 64 + kFlatThreads.
+// 64-bit reciprocal, the rest is a numerator n below nvec + kFlatThreads <= 400, for which the 22-bit one is
+// exact: it is too large by less than nvec / 2^22 of itself, and n nvec < 2^16.
 __device__ __forceinline__ bool unit_of_lane(const RowParams &p, int &t, int &v) {
   const int64_t first = (int64_t)blockIdx.x * kFlatThreads;
   const int64_t t0 = divided(first, p.recip);
@@ -739,11 +742,6 @@ __global__ __launch_bounds__(kElemThreads) void transpose_elems_kernel(RowParams
   }
 }
 
-// Whether every row of both buffers is whole 128-byte lines.
-static inline bool whole_lines(int H, int elem_bytes, const void *a, const void *b) {
-  return ((int64_t)H * elem_bytes) % kLineBytes == 0 && (((uintptr_t)a | (uintptr_t)b) & (kLineBytes - 1)) == 0;
-}
-
 static inline uint64_t reciprocal(int64_t d) { return d > 1 ? ~0ull / (uint64_t)d + 1 : 0; }
 
 // Fills what the kernels need to know about rows of H elements (of 16 / per_vec bytes) written to
@@ -776,21 +774,6 @@ static inline bool grid_for_flat(RowParams &p, int H, int per_vec, dim3 &grid) {
   grid = dim3((unsigned)blocks);
   return true;
 }
-// Whether rows go to the flat kernels: where the waves of the other kernels would have a quarter of
-// their lanes idle or more, i.e. up to 48 vectors, 65 to 96, and so on.  HIP events, 65,536 tokens, 3.6 bf16
-// rows each, wave per segment -> flat: dispatch / combine of 16 elements 24.5 / 28.6 -> 8.3 / 8.1 us, of
-// 128 19.1 / 31.6 -> 15.6 / 18.4, of 256 26.8 / 35.6 -> 26.4 / 30.2, of 384 38.1 / 42.0 -> 37.2 / 42.0, of 448
-// (kept per wave) 43.3 / 46.9 -> 43.0 / 47.6, of 576 57.3 / 68.7 -> 54.1 / 59.3; of 832 (kept) 88.1 / 82.1 ->
-// 89.2 / 82.6.  Ragged rows are written better along the line grid from 33 vectors on (7.3 copies of 301
-// elements 113 -> 116 us, of 1,030 71 -> 84 us); a combine writes little and is better flat (59 -> 57 us).
-static inline bool flat_rows(int H, int per_vec, bool whole, bool spread) {
-  const int64_t vecs = ((int64_t)H + per_vec - 1) / per_vec;
-  if (spread && !whole) return H >= per_vec && vecs <= 32;
-  const int64_t in_waves = whole ? vecs : ((int64_t)H + kLineBytes / 16 * per_vec - 1 + per_vec - 1) / per_vec;
-  const int64_t lanes = (in_waves + kWave - 1) / kWave * kWave;
-  return H >= per_vec && 4 * in_waves <= 3 * lanes;
-}
-
 static inline bool grid_for_elems(RowParams &p, int64_t n, dim3 &grid) {
   p.H = p.nvec = p.shift = p.nseg = 0;
   p.nunits = 0;
@@ -839,8 +822,9 @@ static inline double rows_per_token(const hm_plan_out *plan, int32_t T) {
 // 164.7 -> 164.8; but 16,384 x 4,096 with 5.4 rows 145 -> 159, the DeepSeek-V3 layer (3.1 rows) 81 -> 106,
 // and a token buffer of 470 MB 642 -> 651.  Only a known row count counts: the bound that hm_plan leaves is 8 for
 // the layer with 5.4.
+// Nor are rows of less than a segment, whose waves are short: 8,192 x 192 with 7.7 rows 5.6 -> 6.6.
 static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int32_t H) {
-  const bool many = plan->expected_rows > 6 * (int64_t)T;
+  const bool many = plan->expected_rows > 6 * (int64_t)T && H >= 8 * kWave;
   return many && (int64_t)T * H * 2 <= (256ll << 20) ? 12 : kCopyWavesPerCu;
 }
 
@@ -910,6 +894,132 @@ static inline auto combine_kernel(const CombineShape &sh, bool weights_from_plan
   return combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW, ACCESS>;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Which kernel takes the rows of a call.
+// ---------------------------------------------------------------------------------------------
+enum class Route {
+  kWhole,    // a wave per (token, segment), WholeRows
+  kRagged,   // ... RaggedRows
+  kFlat,     // a lane per (token, vector)
+  kElems,    // a lane per (token, element)
+};
+
+struct RowForm {
+  int T, K, H, elem_bytes;
+  int vecs;       // 16-byte vectors per row, the last one possibly in part
+  bool vectors;   // every row of both buffers is whole, aligned vectors
+  bool lines;     // ... and every row written is whole 128-byte lines
+  bool apart;     // the buffers begin at different places of a line
+};
+static inline RowForm row_form(int T, int K, int H, int elem_bytes, const void *in, const void *out) {
+  RowForm f;
+  f.T = T;
+  f.K = K;
+  f.H = H;
+  f.elem_bytes = elem_bytes;
+  f.vecs = (int)(((int64_t)H * elem_bytes + 15) / 16);
+  f.vectors = (int64_t)H * elem_bytes % 16 == 0 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
+  f.lines = f.vectors && (int64_t)H * elem_bytes % kLineBytes == 0 && ((uintptr_t)out & (kLineBytes - 1)) == 0;
+  f.apart = (((uintptr_t)in ^ (uintptr_t)out) & (kLineBytes - 1)) != 0;
+  return f;
+}
+static inline bool in_vectors(const RowForm &f) { return f.H * (int64_t)f.elem_bytes >= 16 && f.H <= kMaxVectorH; }
+
+// All figures below: us per call, graphs of ten calls, the kernels in turn on the same buffers.
+//
+// Tokens from which a lane per vector pays: with fewer, all waves of a wave per token are resident at once and a call
+// lasts as long as one wave's chain, which is longer where a lane walks its token's K slots itself (512 tokens,
+// K = 8, 64 bf16, in waves -> flat: dispatch 2.7 -> 3.0, bf16 transpose 3.6 -> 4.8; 4,096 tokens, 7.7 rows: 4.3 -> 3.5
+// and 7.1 -> 5.3).  One or two slots are no such chain: combine is flat at any T there (512 tokens, K = 1, 16 bf16:
+// 3.2 -> 2.7).
+constexpr int kFlatTokens = 4096;
+
+// Dispatch (scaled = false) and transpose.
+//  * Vectors, narrow: flat up to the widths at which it still gains.  65,536 tokens, 3.6 rows each, in waves ->
+//    flat: dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 192 18.4 -> 17.8 (but 7.7 rows, or 32,768 tokens:
+//    8 % slower); bf16 transpose of 192 32.6 -> 22.0, of 256 33.4 -> 26.9; fp32 transpose of 16 12.3 -> 5.8, of 64 16.9 ->
+//    12.5, of 96 21.1 -> 19.6 (but 8,192 tokens: 5 % slower).  With K <= 2 further (K = 1: 320 bf16 16.8 -> 15.3).
+//    And just above 64 vectors, where waves leave most of their second segment idle: bf16 transpose (16,384 tokens, 576
+//    elements 17.7 -> 14.8), dispatch for K <= 2 (K = 1: 6.7 -> 4.6; but K = 8: 12.7 -> 13.3), fp32 transpose for K = 1
+//    (384 elements 8.1 -> 6.3); just above 128 for K = 1 (8,192 tokens, 1,088 bf16, dispatch 5.7 -> 4.5).
+//  * Vectors, not narrow: whole lines are written by kWhole.  Rows that begin inside a line are written
+//    in line-sized pieces by kRagged, which reads the token again for each row: better once that saves more
+//    in partial lines than it costs, i.e. with more rows per token the shorter the rows are (the extra segment for the
+//    slack of a line is a larger part of them) and some 24 MB to write.  16,384 tokens of 7,168 bf16 in a packed
+//    buffer 16 bytes off a line, kWhole -> kRagged: 7.7 rows 495 -> 371, 3.6 rows 215 -> 157, one row 72 -> 78 (but the bf16
+//    transpose, whose waves have more to do before they store, 80 -> 72); 1,000 elements: 3.6 rows 30 -> 26, 1.9 rows
+//    16.6 -> 18.6; 512 elements, 3.6 rows: 16.9 -> 17.7; 1,024 tokens of 2,048, 3.6 rows: bf16 transpose 5.8 -> 6.8.
+//  * Elements, few of them: kElems, whose lanes are all resident and have the shortest chain (2,048 tokens,
+//    K = 1, 65 bf16, transpose: 2.7, flat 3.2, ragged 3.4), up to 512 Ki elements for K <= 2 and the bf16
+//    transpose (2,048 x 100, 7.7 rows: 5.8, ragged 6.9), else up to 128 Ki (dispatch of 2,048 x 250, 7.7 rows: 5.8, ragged 5.3;
+//    fp32 transpose of 64 x 7,168 6.8 and 5.5).
+//  * Elements, many copies of rows of at most 320 bytes: kElems, whose neighbouring lanes write neighbouring elements
+//    where vectors straddle lines (65,536 tokens, 7.7 rows, kElems / flat: dispatch of 33 bf16 20 / 30, of 130 55 / 61; fp32
+//    transpose of 65 48 / 64; but dispatch of 250 with 32,768 tokens 52 / 46).  The bf16 transpose, dearer per
+//    element, only up to 80 bytes and from 65,536 tokens on (33: 32 / 36; with 32,768 tokens 19 / 15).
+//  * Elements, narrow: flat up to 32 vectors, 20 for fp32 with K > 2 (65,536 tokens, 3.6 rows, ragged -> flat: 33 fp32 25 ->
+//    16, 130 33 -> 39), else ragged (7.3 copies of 301 bf16: 113, flat 116).
+static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool scaled) {
+  if (!in_vectors(f)) return Route::kElems;
+  const bool wide = f.elem_bytes == 4, scaled_bf16 = scaled && !wide;
+  const int64_t elems = (int64_t)f.T * f.H;
+  if (f.vectors) {
+    const int narrow = f.K == 1 ? 48 : f.K == 2 ? (wide ? 24 : 48) : wide ? 16 : scaled ? 32 : 16;
+    const int above = f.K == 1 ? (wide ? 96 : 88) : scaled_bf16 || (f.K == 2 && !wide) ? 80 : 0;
+    const bool few_lanes = (f.vecs > kWave && f.vecs <= above) || (f.K == 1 && f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
+    if (f.T >= kFlatTokens && (f.vecs <= narrow || few_lanes)) return Route::kFlat;
+    const double rows = rows_per_token(plan, f.T);
+    const bool enough = rows >= 2.5 ? f.vecs > 80 : rows >= 1.5 ? f.vecs > 2 * kWave : scaled_bf16 && rows > 0.0 && f.vecs >= 4 * kWave;
+    return !f.lines && enough && (double)elems * f.elem_bytes * rows >= 24e6 ? Route::kRagged : Route::kWhole;
+  }
+  if (elems <= (scaled_bf16 || f.K <= 2 ? 512 : 128) * 1024) return Route::kElems;
+  const bool many_copies = plan->expected_rows > 6 * (int64_t)f.T;
+  if (many_copies && f.T >= (scaled_bf16 ? 65536 : 32768) && f.vecs <= (scaled_bf16 ? 5 : 20)) return Route::kElems;
+  return f.T >= kFlatTokens && f.vecs <= (wide && f.K > 2 ? 20 : 32) ? Route::kFlat : Route::kRagged;
+}
+
+// Combine; vecs_per_lane is that of the wave kernels' launch shape.
+//  * With the caller's weights there is no flat kernel.  Elements: kElems where K slots of H elements are less work than
+//    a wave's merging of the slots (65,536 tokens, kElems / ragged: K = 1, 100 bf16 16 / 36; K = 2, 65 32 / 49; K = 8, 3.6 rows,
+//    17 43 / 68; but K = 1, 250 56 / 41; K = 8, 33 77 / 71; fp32, K = 8, 9 32 / 43, but 17 50 / 45) or there are few of them
+//    (1,024 tokens, K = 1, 513: 3.5 / 4.0), as long as its chain over K slots squared is hidden (8,192 tokens, K =
+//    8, 9 elements: 13.7 / 10.7).
+//  * With the plan's weights.  Vectors: flat where narrow (65,536 tokens, 3.6 rows, in waves -> flat: 64 bf16 27.6 -> 9.4,
+//    320 35.1 -> 32.2, 384 38.3 -> 37.7; 64 fp32 27.7 -> 14.5, 100 31.3 -> 22.7; K = 1 further, 16,384 x 456 bf16 11.0 -> 8.6),
+//    and where segments of one vector per lane would leave the last one mostly idle (16,384 tokens, 576 bf16: 18.6 ->
+//    16.1, 1,088 28.8 -> 27.3, 320 fp32 18.5 -> 16.6); segments of four only for K = 1 (65 to 88 bf16 vectors 4 to 30 %) or
+//    few tokens (1,024 x 1,000 bf16, K = 1: 3.4 -> 3.0; 8,192 x 576, K = 2: equal, 1,152 20 % slower).  Elements: flat where waves would have a quarter of their lanes idle or more (65,536
+//    tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344), kElems for K <= 2 and few elements (2,048 tokens, K
+//    = 1, 65 bf16: 2.6, flat 3.1).
+//  * In waves: kWhole for whole lines and where the slack of a line would cost kRagged one more segment, of few or long
+//    ones (4,096 tokens, K = 1, 2,048 bf16 16 bytes off a line, the caller's weights: 6.4 whole, 9.4 ragged) or with reads
+//    off a line that kWhole would do in lines (8,192 x 4,096, 7.7 rows, only out off a line: 97 and 101); else kRagged
+//    (16,384 x 7,168, 3.6 rows, both 16 bytes off: bf16 173 whole, 163 ragged; fp32 354 and 326).
+static inline Route combine_route(const RowForm &f, bool from_plan, int vecs_per_lane) {
+  if (!in_vectors(f)) return Route::kElems;
+  const bool wide = f.elem_bytes == 4, many = f.T >= kFlatTokens || f.K <= 2;
+  const int64_t elems = (int64_t)f.T * f.H;
+  const int slack = kLineBytes / 16 - 1, segment = kWave * vecs_per_lane;
+  const bool extra = (f.vecs + slack + segment - 1) / segment > (f.vecs + segment - 1) / segment;   // segment for the slack
+  const bool dear = extra && (vecs_per_lane > 1 || f.vecs < 8 * kWave || f.apart);
+  const Route waves = f.vectors && (f.lines || f.vecs <= kWave || dear) ? Route::kWhole : Route::kRagged;
+  if (!from_plan) {
+    if (f.vectors) return waves;
+    const bool light = (int64_t)f.H * f.K <= (wide ? 130 : 200) || elems <= 512 * 1024 / (f.K * f.K);
+    return light && (f.K <= 2 || f.T >= 2048 * f.K) ? Route::kElems : waves;
+  }
+  if (f.vectors) {
+    const bool few_lanes = (f.vecs > kWave && f.vecs <= 88) || (f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
+    const bool above = vecs_per_lane == 1 ? few_lanes && f.T >= kFlatTokens
+                       : !wide && f.vecs > kWave && f.vecs <= (f.K <= 2 && f.T <= 1024 ? kFlatVecs : f.K == 1 ? 88 : 0);
+    const bool flat = f.vecs <= (f.K == 1 ? kWave : wide ? 32 : 48) || above;
+    return many && flat ? Route::kFlat : waves;
+  }
+  if (f.K <= 2 && elems <= 512 * 1024) return Route::kElems;
+  const int in_waves = f.vecs + slack, lanes = (in_waves + kWave - 1) / kWave * kWave;
+  return many && f.vecs <= kFlatVecs && 4 * in_waves <= 3 * lanes ? Route::kFlat : waves;
+}
+
 }  // namespace hm
 
 static hm_status check_rows_args(int32_t T, int32_t K, int32_t H, const hm_plan_out *plan, bool need_keep) {
@@ -938,16 +1048,18 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  const bool whole = whole_lines(H, 2, x_bf16, packed_bf16);
   const uint16_t *x = (const uint16_t *)x_bf16;
   uint16_t *packed = (uint16_t *)packed_bf16;
-  if (flat_rows(H, 8, whole, true)) {
+  const RowForm form = row_form(T, K, H, 2, x_bf16, packed_bf16);
+  const Route route = spread_route(form, plan, false);
+  if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, 8, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((spread_flat_kernel<RowBf16, false>), grid, dim3(kFlatThreads), 0, stream, p, x, nullptr, packed_rows,
                        packed);
-  } else if (H >= 8 && H <= kMaxVectorH) {
+  } else if (route != Route::kElems) {
+    const bool whole = route == Route::kWhole;
     if (!grid_for_units(p, H, 8, whole, packed_bf16, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const unsigned lds = lds_cap_bytes(whole ? dispatch_waves_per_cu(plan, T, H) : kCopyWavesPerCu, kCopyThreads);
+    const unsigned lds = lds_cap_bytes(form.lines ? dispatch_waves_per_cu(plan, T, H) : kCopyWavesPerCu, kCopyThreads);
     if (whole)
       hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds, stream, p, x, packed, packed_rows);
     else
@@ -980,15 +1092,16 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  const bool whole = whole_lines(H, sizeof(elem), y, out);
   // rows the plan's weight array does not cover are treated like rows beyond y
   const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
-  if (from_plan && flat_rows(H, ROW::kPerVec, whole, false)) {
+  const CombineShape sh = combine_shape(plan, T, from_plan);
+  const Route route = combine_route(row_form(T, K, H, sizeof(elem), y, out), from_plan, sh.vecs);
+  if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((combine_flat_kernel<MIX, ROW>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)y, rows,
                        plan->row_weight, (elem *)out);
-  } else if (H >= ROW::kPerVec && H <= kMaxVectorH) {
-    const CombineShape sh = combine_shape(plan, T, from_plan);
+  } else if (route != Route::kElems) {
+    const bool whole = route == Route::kWhole;
     if (!grid_for_units(p, H, ROW::kPerVec, whole, out, sh.vecs, kCombineThreads, grid)) return HM_ERR_SHAPE;
     const float *weights = from_plan ? plan->row_weight : topk_weights;
     const unsigned lds = sh.vecs == 1 ? lds_cap_bytes(sh.waves_per_cu, kCombineThreads) : 0u;
@@ -1056,15 +1169,18 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   p.slot_keep = plan->slot_keep;
   p.status = plan->status;
   dim3 grid;
-  const bool whole = whole_lines(H, sizeof(elem), gout, gy);
   const int64_t rows = plan->row_capacity < gy_rows ? plan->row_capacity : gy_rows;
-  if (rows > 0 && flat_rows(H, ROW::kPerVec, whole, true)) {
+  Route route = spread_route(row_form(T, K, H, sizeof(elem), gout, gy), plan, true);
+  if (route == Route::kFlat && rows == 0) route = Route::kElems;   // the flat kernel reads the weight of row 0
+  if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((spread_flat_kernel<ROW, true>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)gout,
                        plan->row_weight, rows, (elem *)gy);
-  } else if (H >= ROW::kPerVec && H <= kMaxVectorH) {
+  } else if (route != Route::kElems) {
+    const bool whole = route == Route::kWhole;
     if (!grid_for_units(p, H, ROW::kPerVec, whole, gy, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const unsigned lds = ROW::kPerVec == 4 && (!whole || transpose_capped(plan, T, H)) ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;
+    const bool capped = ROW::kPerVec == 4 && (!whole || transpose_capped(plan, T, H));
+    const unsigned lds = capped ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;
     if (whole) {
       const bool divide = ROW::kPerVec == 8 && (double)T * H * 2 * rows_per_token(plan, T) > 2e9;   // bytes written
       hipLaunchKernelGGL((divide ? transpose_rows_kernel<ROW, ROW::kPerVec == 8> : transpose_rows_kernel<ROW, false>), grid,

@@ -434,6 +434,77 @@ def test_rows_of_any_length(hw, oracle, H, K, off):
         assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
 
 
+# (T, K, H, first element): sizes on either side of the lines at which the row calls change kernels, so that a lane per
+# vector, a lane per element, a wave per segment of whole vectors and one along the line grid all run, for vectors and
+# for odd lengths, few and many tokens and slots, up to the widest rows a lane per vector takes.
+ROW_ROUTES = [
+    (4095, 8, 64, 0), (4096, 8, 64, 0), (4096, 8, 48, 0), (4096, 8, 128, 0), (4096, 8, 136, 0), (4096, 8, 256, 0), (4096, 8, 264, 0),
+    (4096, 8, 384, 0), (4096, 8, 392, 0), (4096, 2, 96, 8), (4096, 2, 104, 8), (4096, 2, 384, 8), (4096, 1, 192, 8), (4096, 1, 512, 0),
+    (4097, 1, 520, 0), (4096, 1, 384, 8), (4096, 3, 640, 0), (4096, 3, 648, 0), (4096, 9, 17, 1), (8193, 9, 64, 1), (4096, 3, 130, 3),
+    (4200, 3, 257, 0), (4200, 3, 300, 2), (4200, 2, 65, 0), (8192, 1, 576, 1), (600, 2, 400, 1), (1030, 2, 513, 1), (515, 5, 255, 0),
+    (513, 6, 257, 1), (1024, 6, 1024, 8), (1200, 6, 2056, 8), (1200, 6, 648, 8), (2600, 6, 1000, 8), (1024, 1, 2048, 8), (1024, 2, 1152, 8),
+    (1024, 1, 1160, 8), (500, 8, 4104, 0), (300, 8, 7168, 8), (64, 8, 2048, 1), (5, 64, 520, 0), (32768, 8, 33, 0), (32768, 8, 9, 1),
+    (32769, 4, 161, 0), (65536, 8, 20, 1), (65536, 8, 41, 1), (16384, 8, 17, 0), (16384, 8, 16, 1), (16384, 8, 25, 1), (8192, 2, 100, 1),
+    (2049, 1, 257, 1), (2048, 1, 255, 1), (8192, 3, 77, 1), (8192, 3, 81, 1),
+    (4096, 1, 704, 0), (4096, 1, 712, 8), (4096, 1, 1152, 0), (4096, 3, 704, 0), (4096, 3, 1152, 8), (4096, 3, 1160, 8), (4096, 3, 576, 8)]
+
+
+@pytest.mark.parametrize("T,K,H,off", ROW_ROUTES)
+def test_row_calls_where_their_kernels_change(hw, oracle, T, K, H, off):
+    """Every row call on each side of the lines at which another kernel takes it, with a known and with an unknown
+    number of rows, at rank level (many rows per token) and at node level (about one): the oracle's bits for copies and
+    transposes, one bf16 ulp / the fp32 bound for the sums."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(T * 131 + H)
+    E, nodes, rpn = 64, 2, 16
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    ids[rng.random((T, K)) < 0.03] = -1
+    w = rng.random((T, K), dtype=np.float32) + np.float32(0.05)
+    e2r = rng.integers(0, nodes * rpn, E, dtype=np.int32)
+    x32 = rng.standard_normal((T, H), dtype=np.float32)
+    x = W.f32_to_bf16_bits(x32)
+
+    def shifted(a, dtype):
+        store = torch.full((a.size + 32,), 77.0, dtype=dtype, device="cuda")
+        view = store[off:off + a.size].view(a.shape)
+        view.copy_(hw.to_dev_bf16(a) if dtype == torch.bfloat16 else hw.dev(a))
+        return view
+
+    def call(fn, shape, dtype, *args):
+        n = shape[0] * shape[1]
+        store = torch.full((n + 96,), 77.0, dtype=dtype, device="cuda")
+        out = store[off + 32:off + 32 + n].view(shape)
+        fn(*args, out)
+        assert (store[:off + 32] == 77.0).all() and (store[off + 32 + n:] == 77.0).all(), fn
+        return hw.bf16_to_host(out) if dtype == torch.bfloat16 else out.cpu().numpy()
+
+    for level in (GPU, NODE):
+        ctx = "row routes T=%d K=%d H=%d off=%d level=%s" % (T, K, H, off, LEVEL[level])
+        print("case:", ctx, flush=True)
+        ora = oracle.plan(ids, w, e2r, nodes, rpn, level)
+        g = hw.GpuPlan(ids, w, e2r, nodes, rpn, level)
+        n = ora.total_rows
+        y32 = rng.random((n, H), dtype=np.float32) + np.float32(0.5)              # same-sign terms
+        y = W.f32_to_bf16_bits(y32)
+        x_d, x32_d, y_d, y32_d = shifted(x, torch.bfloat16), shifted(x32, torch.float32), shifted(y, torch.bfloat16), shifted(y32, torch.float32)
+        packed, gy16 = oracle.dispatch_pack(x, ora.row_token), oracle.combine_transpose_bf16(x, ora.row_token, ora.row_weight)
+        gy32 = oracle.combine_transpose(x32, ora.row_token, ora.row_weight)
+        out16, mix, out32 = oracle.combine(y, w, ora.slot_row), oracle.combine_mix(y, w, ora.slot_row), oracle.combine_f32(y32, w, ora.slot_row)
+        for known in (True, False):
+            g.plan.c.expected_rows = n if known else 0
+            assert np.array_equal(call(B.hm_dispatch_pack, (n, H), torch.bfloat16, x_d, g.plan), packed), ctx
+            assert np.array_equal(call(B.hm_combine_transpose_bf16, (n, H), torch.bfloat16, x_d, g.plan), gy16), ctx
+            assert np.array_equal(call(B.hm_combine_transpose, (n, H), torch.float32, x32_d, g.plan).view(np.uint32), gy32.view(np.uint32)), ctx
+            for fn, ref in ((B.hm_combine, out16), (B.hm_combine_mix, mix)):
+                got = [call(fn, (T, H), torch.bfloat16, y_d, weights, g.plan) for weights in (g.w_d, None)]
+                assert bf16_ulp_distance(got[0], ref).max() <= 1 and np.array_equal(got[0], got[1]), (ctx, fn)
+            got = [call(B.hm_combine_f32, (T, H), torch.float32, y32_d, weights, g.plan) for weights in (g.w_d, None)]
+            # all terms positive: the bound 2K * 2^-24 * sum |w y| is relative to the result
+            assert (np.abs(got[0].astype(np.float64) - out32) <= 2 * K * 2.0 ** -24 * out32).all() and np.array_equal(got[0], got[1]), ctx
+        assert B.hm_plan_status(g.plan)[0] == 0, ctx
+
+
 @pytest.mark.parametrize("T,H", [(1, 64), (37, 512), (100, 576), (129, 7168)])
 def test_bf16_transpose_where_many_rows_are_expected(hw, oracle, T, H):
     """The launch depends on the bytes the plan says will be written: the same bits whatever it expects."""
