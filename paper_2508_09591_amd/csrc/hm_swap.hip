@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kFactorThreads) void swap_factors_kernel(SwapParams
 // so the read-modify-write updates of popular expert pairs, which serialise on one address, become
 // int8 matrix products with int32 accumulators held in registers.  What only the token's other slots
 // can tell (is this the first occurrence of the expert, is it alone in its group under the cut) is worked
-// out where the slots are read, or, for K > 8, by a kernel of its own that leaves one byte per slot.  In
+// out where the slots are read, or, for K > 8 or many tokens, by a kernel of its own that leaves one byte per slot.  In
 // the matrix kernel a workgroup takes one cut and a contiguous chunk of the tokens, builds
 // the three indicator tiles for 128 tokens at a time in LDS (expert-major, so that a lane's MFMA
 // operand is 16 contiguous bytes), and stores its partial tables with plain stores; a third kernel
@@ -209,6 +209,7 @@ constexpr int kCoocChunkTokensMax = 32640;   // a chunk's counts are stored as 1
 constexpr int kCoocMaxE = 256;
 constexpr int kCoocStaged = 8;       // passes whose slots are fetched together (16 KiB of LDS)
 constexpr int kCoocTokensPerChunkMin = 512;   // below this a chunk is not worth a workgroup of its own
+constexpr int kCoocOwnTokens = 1024;          // most tokens of a chunk whose slots the matrix kernel works out itself
 
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef i32x4 i32x4_align4 __attribute__((aligned(4)));
@@ -231,7 +232,7 @@ struct CoocParams {
 __host__ __device__ static inline int64_t cooc_part_ints(int64_t E, int64_t ng) { return E * E + E * ng + 64; }   // values per chunk
 __host__ __device__ static inline int64_t cooc_part_words(int64_t E, int64_t ng) { return (cooc_part_ints(E, ng) + 1) / 2; }   // 32-bit words they take
 
-// One lane per routing slot (K > 8); the K slots of a token sit in 2^sub_log2 consecutive lanes and
+// One lane per routing slot (K > 8 or many tokens); the K slots of a token sit in 2^sub_log2 consecutive lanes and
 // learn about each other through shuffles, eight in flight at a time.
 __global__ __launch_bounds__(kSwapThreads) void swap_slots_kernel(CoocParams p) {
   const int sub = 1 << p.sub_log2;
@@ -305,9 +306,13 @@ __device__ __forceinline__ i32x16 mfma_i8(i32x4 a, i32x4 b, i32x16 acc) {
 // repeat the cheap filling of the tiles and split the products, which is what E = 256 is bound by).
 //
 // OWN_SLOTS (K <= 8): the workgroup works the slots out itself instead of reading the bytes of
-// swap_slots_kernel, which saves that launch (4 us and the gap before it, and the host's time for it; the work here is about 3 us per
-// 1,024 tokens): the experts and the groups of a token's slots meet in two 8-byte words, and a slot
-// compares its own with all of them at once.
+// swap_slots_kernel, which saves that launch, the gap before it and the host's time for it: the experts and the groups of
+// a token's slots meet in two 8-byte words, and a slot compares its own with all of them at once.  Every cut
+// and panel repeats the work, 1 us per 1,024 tokens of a chunk for K <= 2 and 2.5 us for K = 8, on sixteen chunks
+// instead of the whole chip, so it is for chunks of up to 1,024 tokens (graphs of ten calls, four cuts, E = 128, slots
+// kernel -> own slots in us: 8,192 tokens K = 2 20.7 -> 19.2, K = 8 22.1 -> 21.3; 16,384 tokens K = 2 23.5 -> 23.2, K = 8 26.3 ->
+// 27.6, which is less than the 3 us the host needs for a launch; 32,768 tokens 30.5 -> 32.4 and 35.4 -> 40.3, 500,000
+// tokens K = 8 324 -> 425).
 __device__ __forceinline__ uint32_t or_of_token(uint32_t v, int sub_log2) {   // over the 2^sub_log2 <= 8 lanes of a token
   if (sub_log2 > 0) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);    // lane ^ 1
   if (sub_log2 > 1) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);    // lane ^ 2
@@ -1024,7 +1029,7 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
   }
   p.status = status;
   size_t cooc_lds = 0;
-  const bool own_slots = K <= 8;
+  const bool own_slots = K <= 8 && T <= kCoocOwnTokens * kCoocChunksMax;
   const cooc_kernel_t cooc = !swap_by_matrices(E, T) ? nullptr
                              : own_slots ? cooc_kernel<true>(E, &cooc_lds) : cooc_kernel<false>(E, &cooc_lds);
   if (cooc && (cooc_lds <= 65536 || cooc_lds_ready())) {

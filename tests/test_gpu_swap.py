@@ -212,6 +212,18 @@ def test_swap_select_parity(hw, oracle):
     print("d=4 gamma=5 best pair", pair, "time", float(bt.item()), "no swap", Qg[0, 0])
 
 
+@pytest.mark.parametrize("E,K,T", [(24, 8, 16384), (24, 8, 16385), (130, 3, 16385), (40, 1, 17000)])
+def test_swap_counts_where_the_slots_get_a_kernel(hw, oracle, E, K, T):
+    """Token counts on either side of the one up to which the matrix kernel works the slots out itself."""
+    rng = np.random.default_rng(T + K)
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    ids[rng.random((T, K)) < 0.1] = -1
+    e2r = rng.integers(0, 8, E).astype(np.int32)
+    ref, st_ref = oracle.swap_counts(ids, e2r, 8, 4, "incremental")
+    Z, st = _gpu_z(hw, ids, e2r, 8, 4)
+    assert st == st_ref == 0 and np.array_equal(Z.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (12, [1, 2, 6], 33), (33, [1, 3], 9), (6, [1, 3], 300), (1, [1], 5)])
 def test_swap_select_on_any_counts(hw, oracle, G, U, E):
     """Terms of up to 64 groups and of lengths that are no multiple of four, counts that no swap tensor
