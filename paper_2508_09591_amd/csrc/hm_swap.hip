@@ -564,11 +564,16 @@ __global__ __launch_bounds__(kSwapThreads) void swap_reduce_kernel(SwapParams p,
       for (int c = 0; c < kCoocChunksMax; ++c)
 #pragma unroll
         for (int e = 0; e < 4; ++e) sum[e] += c < cp.chunks ? v[c][e] : 0;
-    } else {
-      for (int c = 0; c < cp.chunks; ++c)
+    } else {   // up to three values left: the last one again for what is missing, for the same reason
+      uint16_t v[kCoocChunksMax][3];
 #pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (b + e < width) sum[e] += at[c * stride + e];
+      for (int c = 0; c < kCoocChunksMax; ++c)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) v[c][e] = at[min(c, cp.chunks - 1) * stride + min(e, width - 1 - b)];
+#pragma unroll
+      for (int c = 0; c < kCoocChunksMax; ++c)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) sum[e] += c < cp.chunks && b + e < width ? v[c][e] : 0;
     }
     int32_t *const out = (of_c ? p.C[cut] : p.CG[cut]) + (int64_t)a * width + b;
     const int rank = p.expert_to_rank[a];
