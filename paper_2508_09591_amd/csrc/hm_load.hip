@@ -20,6 +20,7 @@ struct LoadParams {
   const int32_t *ids;
   const int32_t *expert_to_rank;
   int32_t T, K, E, G, R, N;
+  int32_t staged;   // the placement goes through LDS
   int32_t *load_expert, *load_rank, *load_node, *status;
 };
 
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
   __shared__ int32_t rank_cnt[kWave];
   __shared__ int32_t node_cnt[kWave];
   __shared__ int32_t bad;
-  const bool lds_hist = p.E <= kLdsExperts, staged = p.E <= kStagedExperts;
+  const bool lds_hist = p.E <= kLdsExperts, staged = p.staged;
   const int64_t stride = (int64_t)gridDim.x * THREADS;
   int64_t t = (int64_t)blockIdx.x * THREADS + threadIdx.x;
   int id[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
@@ -69,14 +70,23 @@ __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
     if (t < p.T) {
       for (int k0 = 0; k0 < p.K; k0 += 8) {
         if (it > 0 || k0 > 0) load_ids(p.ids + t * p.K, p.K, k0, id);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int g = staged ? staged_rank_of(ranks, p.E, id[j]) : rank_of(p.expert_to_rank, p.E, p.G, id[j]);
+        auto count = [&](int slot) {
+          const int g = staged ? staged_rank_of(ranks, p.E, slot) : rank_of(p.expert_to_rank, p.E, p.G, slot);
           my_bad = my_bad || g == -1;
-          if (g < 0) continue;
-          if (lds_hist) atomicAdd(&hist[id[j]], 1);
-          else atomicAdd(&p.load_expert[id[j]], 1);
+          if (g < 0) return;
+          if (lds_hist) atomicAdd(&hist[slot], 1);
+          else atomicAdd(&p.load_expert[slot], 1);
           rm |= 1ull << g;
+        };
+        if (k0 + 8 <= p.K) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) count(id[j]);
+        } else {   // uniform: an absent slot would cost its share of the chain all the same
+#pragma unroll
+          for (int j = 0; j < 7; ++j) {
+            if (k0 + j >= p.K) break;
+            count(id[j]);
+          }
         }
       }
     }
@@ -131,7 +141,16 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   p.load_rank = load_rank;
   p.load_node = load_node;
   p.status = status;
-  if (T <= kAloneTokens && E <= kLdsExperts) {
+  const bool alone = T <= kAloneTokens && E <= kLdsExperts;
+  int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
+  if (blocks > 1024) blocks = 1024;
+  // Staging pays where a lane looks more slots up than it stages entries (us, staged / from memory: E = 4,096, 1,025 tokens, K = 1
+  // 10.1 / 7.9, K = 8 10.4 / 9.4, K = 16 11.7 / 11.4; E = 2,048, K = 16 9.9 / 10.4; 300,000 tokens, two per lane, E = 2,048,
+  // K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).  The one workgroup has four times the lanes to stage with (1,024 tokens, E =
+  // 4,096 staged, E = 5,000 from memory: K = 1 6.5 and 6.2, K = 8 7.1 and 7.6).
+  const int64_t lookups = blocks ? ((int64_t)T + blocks * kLoadThreads - 1) / (blocks * kLoadThreads) * K : 0;
+  p.staged = E <= kStagedExperts && (alone || lookups * kLoadThreads > E);
+  if (alone) {
     hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
     return hm_launch_status();
   }
@@ -139,8 +158,6 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   hipLaunchKernelGGL(load_clear_kernel, dim3((most + kLoadThreads - 1) / kLoadThreads), dim3(kLoadThreads), 0, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
   if (T == 0) return HM_OK;   // cleared outputs are the counts
-  int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
-  if (blocks > 1024) blocks = 1024;
   hipLaunchKernelGGL((load_count_kernel<kLoadThreads, false>), dim3((unsigned)blocks), dim3(kLoadThreads), 0, stream, p);
   return hm_launch_status();
 }
