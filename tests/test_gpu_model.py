@@ -80,6 +80,27 @@ def test_counts_at_the_edges(hw, oracle, T, K, E, nodes, rpn):
         assert (st == B.HM_ERR_BAD_ID) == bad
 
 
+@pytest.mark.parametrize("T,K,E", [(512, 64, 5000), (513, 64, 5000), (1024, 32, 4097), (1100, 4, 1023), (1100, 4, 1024), (1100, 12, 3071),
+                                   (1100, 11, 3072), (300000, 1, 511), (300000, 1, 512), (1025, 7, 300)])
+def test_counts_where_the_placement_is_staged(hw, oracle, T, K, E):
+    """Sizes on either side of those at which the placement table goes through LDS, and at which one workgroup
+    counts, with pieces of fewer than eight slots."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(T + K)
+    ids, e2r = rng.integers(0, E, (T, K), dtype=np.int32), rng.integers(0, 8, E, dtype=np.int32)
+    ids[rng.random((T, K)) < 0.05] = -1
+    le, lr, ln, st = oracle.expert_load(ids, e2r, 2, 4)
+    got = [torch.full((n,), -3, dtype=torch.int32, device="cuda") for n in (E, 8, 2, 1)]
+    B.hm_expert_load(hw.dev(ids), hw.dev(e2r), 2, 4, *got)
+    for a, b in zip(got, (le, lr, ln, [st])):
+        assert np.array_equal(a.cpu().numpy(), b), (T, K, E)
+    ref, st = oracle.group_counts(ids, e2r, 8, [8, 2])
+    counts, status = torch.full((2, 64), -5, dtype=torch.int32, device="cuda"), torch.full((1,), -5, dtype=torch.int32, device="cuda")
+    B.hm_group_counts(hw.dev(ids), hw.dev(e2r), 8, [8, 2], counts, status)
+    assert np.array_equal(counts.cpu().numpy(), ref) and int(status.item()) == st == 0
+
+
 @pytest.mark.parametrize("E", [1, 4096, 8192, 8193, 20000])
 def test_counts_of_no_tokens(hw, E):
     """No tokens, placement tables on either side of what the one-launch form and LDS take: every count and

@@ -434,6 +434,99 @@ def test_rows_of_any_length(hw, oracle, H, K, off):
         assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
 
 
+@pytest.mark.parametrize("T,K,H,off", [(37, 5, 512, 0), (37, 5, 520, 1), (600, 4, 1030, 1), (1024, 6, 2056, 8), (4096, 4, 64, 0),
+                                       (4096, 4, 128, 8), (4096, 5, 129, 1), (4096, 5, 70, 1), (40, 9, 5, 0), (4096, 1, 576, 0)])
+def test_every_row_call_with_short_buffers(hw, oracle, T, K, H, off):
+    """Buffers two rows short of the plan's, and a plan whose row arrays are: every row call, through each kind of
+    kernel, leaves out the rows that are not there, touches nothing behind them and flags them."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(T + H)
+    E, nodes, rpn = 24, 2, 4
+    ids, w = rng.integers(0, E, (T, K), dtype=np.int32), rng.random((T, K), dtype=np.float32) + np.float32(0.05)
+    e2r = rng.integers(0, nodes * rpn, E, dtype=np.int32)
+    x32 = rng.standard_normal((T, H), dtype=np.float32)
+    x = W.f32_to_bf16_bits(x32)
+    ora = oracle.plan(ids, w, e2r, nodes, rpn, GPU)
+    n, short = ora.total_rows, ora.total_rows - 2
+    y32 = rng.random((n, H), dtype=np.float32) + np.float32(0.5)              # same-sign terms
+    y = W.f32_to_bf16_bits(y32)
+    left = np.where(ora.slot_row < short, ora.slot_row, -1).astype(np.int32)   # the slots whose row is there
+    out16, mix, out32 = oracle.combine(y, w, left), oracle.combine_mix(y, w, left), oracle.combine_f32(y32, w, left)
+    rows16 = oracle.combine_transpose_bf16(x, ora.row_token, ora.row_weight)[:short]
+    rows32 = oracle.combine_transpose(x32, ora.row_token, ora.row_weight)[:short]
+
+    def shifted(a, dtype):
+        store = torch.full((a.size + 32,), 77.0, dtype=dtype, device="cuda")
+        view = store[off:off + a.size].view(a.shape)
+        view.copy_(hw.to_dev_bf16(a) if dtype == torch.bfloat16 else hw.dev(a))
+        return view
+
+    def call(ctx, fn, rows, written, dtype, *args):   # of `rows` rows, `written` are to be
+        store = torch.full((rows * H + 96,), 77.0, dtype=dtype, device="cuda")
+        out = store[off + 32:off + 32 + rows * H].view(rows, H)
+        g.plan.status.zero_()
+        fn(*args, out)
+        assert (store[:off + 32] == 77.0).all() and (store[off + 32 + written * H:] == 77.0).all(), ctx
+        assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
+        return hw.bf16_to_host(out[:written]) if dtype == torch.bfloat16 else out[:written].cpu().numpy()
+
+    for capacity, rows in ((None, short), (short, short), (short, n)):       # of the plan's arrays, of the buffers
+        g = hw.GpuPlan(ids, w, e2r, nodes, rpn, GPU, row_capacity=capacity)
+        assert g.status == (0 if capacity is None else B.HM_ERR_CAPACITY) and g.total_rows == n
+        for expected in (n, 0):
+            g.plan.c.expected_rows = expected
+            ctx = "short T=%d K=%d H=%d off=%d capacity=%s rows=%d expected=%d" % (T, K, H, off, capacity, rows, expected)
+            print("case:", ctx, flush=True)
+            x_d, x32_d = shifted(x, torch.bfloat16), shifted(x32, torch.float32)
+            y_d, y32_d = shifted(y, torch.bfloat16)[:rows], shifted(y32, torch.float32)[:rows]
+            if rows == short:                        # these do not look at the plan's row arrays
+                got = call(ctx, B.hm_dispatch_pack, short, short, torch.bfloat16, x_d, g.plan)
+                assert np.array_equal(got, oracle.dispatch_pack(x, ora.row_token)[:short]), ctx
+            got = call(ctx, B.hm_combine_transpose, rows, short, torch.float32, x32_d, g.plan)
+            assert np.array_equal(got.view(np.uint32), rows32.view(np.uint32)), ctx
+            got = call(ctx, B.hm_combine_transpose_bf16, rows, short, torch.bfloat16, x_d, g.plan)
+            assert np.array_equal(got, rows16), ctx
+            for weights in ([g.w_d, None] if rows == short else [None]):
+                for fn, ref in ((B.hm_combine, out16), (B.hm_combine_mix, mix)):
+                    got = call(ctx, fn, T, T, torch.bfloat16, y_d, weights, g.plan)
+                    assert bf16_ulp_distance(got, ref).max() <= 1, (ctx, fn)
+                got = call(ctx, B.hm_combine_f32, T, T, torch.float32, y32_d, weights, g.plan).astype(np.float64)
+                # all terms positive: the bound 2K * 2^-24 * sum |w y| is relative to the result
+                assert (np.abs(got - out32) <= 2 * K * 2.0 ** -24 * out32).all(), ctx
+
+
+def test_ragged_rows_beyond_32_bits_of_elements(hw):
+    """1,048,576 packed rows of 4,099 elements, more than 2^32 of them: every row is a copy of its token, scaled by an
+    exact weight on the way back, and the sum of a token's eight rows of ones and zeros is exact too."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    T, K, H, E = 131072, 8, 4099, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    ids = torch.randint(0, E, (T, K), generator=g, device="cuda", dtype=torch.int32)
+    w = torch.full((T, K), 2.0, device="cuda")
+    e2r = (torch.arange(E, device="cuda") // 8).to(torch.int32)
+    x = torch.randn((T, H), generator=g, device="cuda", dtype=torch.bfloat16)
+    plan = B.hm_plan(ids, w, e2r, 2, 4, NONE)
+    status, n = B.hm_plan_status(plan)
+    assert status == 0 and n == T * K and n * H > 1 << 32
+    token = plan.row_token[:n].long()
+    packed = torch.empty((n, H), device="cuda", dtype=torch.bfloat16)
+    for fn, factor in ((B.hm_dispatch_pack, 1.0), (B.hm_combine_transpose_bf16, 2.0)):
+        packed.fill_(float("nan"))
+        fn(x, plan, packed)
+        for a in range(0, n, 65536):
+            assert torch.equal(packed[a:a + 65536], x[token[a:a + 65536]] * factor), (fn, a)
+    packed.zero_()
+    packed[::2] = 1.0                              # rows of ones and of zeros, weight 2 each
+    ones = (plan.slot_row.view(T, K) % 2 == 0).sum(1)
+    out = torch.empty((T, H), device="cuda", dtype=torch.bfloat16)
+    for weights in (w, None):
+        out.fill_(float("nan"))
+        B.hm_combine(packed, weights, plan, out)
+        assert torch.equal(out, (2.0 * ones).to(torch.bfloat16)[:, None].expand(T, H)), weights is None
+
+
 # (T, K, H, first element): sizes on either side of the lines at which the row calls change kernels, so that a lane per
 # vector, a lane per element, a wave per segment of whole vectors and one along the line grid all run, for vectors and
 # for odd lengths, few and many tokens and slots, up to the widest rows a lane per vector takes.
