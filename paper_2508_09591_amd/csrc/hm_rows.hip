@@ -830,22 +830,24 @@ static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int3
 
 // Whether the fp32 transpose of rows cut by WholeRows keeps dispatch's 24 waves per CU.  A wave waits once
 // more than dispatch does (for the row's weight, behind its index), which more waves hide, but more waves also
-// queue more stores.  HIP events, graphs of ten calls, both forms in turn on the same buffers, two seeds each, capped ->
-// uncapped in us (runs of one form differ by 0.5 %):
-//   about one row per token: uncapped 4 to 15 % faster at every size (2,048 x 7,168 23.0 -> 20.3, 16,384 x 2,048
-//     48.8 -> 42.4, 65,536 x 2,048 200 -> 179, 65,536 x 7,168 676 -> 618);
-//   two rows: capped (2,048 x 2,048 6.8 -> 6.9, 16,384 x 1,024 30.7 -> 30.9, 65,536 x 7,168 903 -> 969);
-//   three or four rows: uncapped above 1 GB written (32,768 x 2,048 182.2 -> 180.2, 65,536 x 2,048 401 -> 389.5, 65,536 x
-//     4,096 795 -> 773, 32,768 x 7,168 613 -> 603), capped below (8,192 x 7,168 138.7 -> 139.9, 8,192 x 2,048 equal);
-//   seven rows: uncapped above 2.5 GB written as long as the gradients are below 0.75 GB (65,536 x 2,048 842 -> 789,
-//     65,536 x 2,560 1,043 -> 1,017, 32,768 x 4,096 827 -> 794 and 845 -> 775, 16,384 x 7,168 722 -> 696), else capped (4,096
-//     x 4,096 91.3 -> 93.0, 16,384 x 2,048 170.2 -> 170.6, 32,768 x 2,048 354 -> 361, 16,384 x 4,096 366 -> 369; 32,768
-//     x 7,168 1,506 -> 1,549, 65,536 x 7,168 2,979 -> 3,130).
-static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t H) {
-  const double c = rows_per_token(plan, T), in = (double)T * H * 4, out = in * c;
-  if (c > 6.0) return out < 2.5e9 || in > 0.75e9;
-  if (c > 2.5) return out < 1e9;
-  return c <= 0.0 || c >= 1.5;   // an unknown number of rows: capped
+// queue more stores.  HIP events, graphs of ten calls, both forms in turn over two to ten pairs of buffers (one pair
+// alone leaves gradients of up to 256 MB in the Infinity Cache, and capped is then up to 2 % better at many rows),
+// capped -> uncapped in us; runs of one form differ by 0.5 %:
+//   about one row per token: uncapped 7 to 11 % faster (8,192 x 2,048 28.4 -> 26.4, 65,536 x 2,048 202 -> 182, 65,536 x
+//     7,168 680 -> 623);
+//   two rows: capped (16,384 x 2,048 69.1 -> 69.9, 65,536 x 2,048 268 -> 274, 16,384 x 7,168 232 -> 243, 65,536 x 7,168 915 -> 977);
+//   three or four rows: uncapped (8,192 x 2,048 52.6 -> 52.1, 65,536 x 2,048 403 -> 392, 65,536 x 4,096 800 -> 780, 32,768 x
+//     7,168 615 -> 609; 8,192 x 7,168 alone 154 -> 156);
+//   seven rows: uncapped (16,384 x 2,048 194 -> 188, 32,768 x 2,048 397 -> 381, 32,768 x 4,096 806 -> 754, 65,536 x 2,048 844 ->
+//     803, 16,384 x 7,168 726 -> 705), but capped for gradients of up to 96 MB (8,192 x 1,024 51.4 -> 53.9, 8,192 x 2,048 101.4 ->
+//     104.6, 4,096 x 4,096 101.1 -> 103.7) or of more than 0.75 GB (32,768 x 7,168 1,509 -> 1,567, 65,536 x 7,168 2,992 -> 3,149;
+//     65,536 x 4,096 1,661 -> 1,637).
+// Rows that begin inside a line (lines = false), whose edges are written in part: capped from two rows per token on.
+static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t H, bool lines) {
+  const double c = rows_per_token(plan, T), in = (double)T * H * 4;
+  if (!lines) return c <= 0.0 || c >= 1.5;
+  if (c > 6.0) return in <= (double)(96 << 20) || in > 0.75e9;
+  return c <= 0.0 || (c >= 1.5 && c < 2.5);   // an unknown number of rows: capped
 }
 
 // Launch shape of the combine kernels: 16-byte vectors per lane, rows in flight per wave, and the
@@ -1170,7 +1172,8 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   p.status = plan->status;
   dim3 grid;
   const int64_t rows = plan->row_capacity < gy_rows ? plan->row_capacity : gy_rows;
-  Route route = spread_route(row_form(T, K, H, sizeof(elem), gout, gy), plan, true);
+  const RowForm form = row_form(T, K, H, sizeof(elem), gout, gy);
+  Route route = spread_route(form, plan, true);
   if (route == Route::kFlat && rows == 0) route = Route::kElems;   // the flat kernel reads the weight of row 0
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
@@ -1179,7 +1182,7 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   } else if (route != Route::kElems) {
     const bool whole = route == Route::kWhole;
     if (!grid_for_units(p, H, ROW::kPerVec, whole, gy, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
-    const bool capped = ROW::kPerVec == 4 && (!whole || transpose_capped(plan, T, H));
+    const bool capped = ROW::kPerVec == 4 && (!whole || transpose_capped(plan, T, H, form.lines));
     const unsigned lds = capped ? lds_cap_bytes(kCopyWavesPerCu, kCopyThreads) : 0u;
     if (whole) {
       const bool divide = ROW::kPerVec == 8 && (double)T * H * 2 * rows_per_token(plan, T) > 2e9;   // bytes written
