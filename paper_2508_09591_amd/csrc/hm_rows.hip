@@ -946,21 +946,27 @@ constexpr int kFlatTokens = 4096;
 //    (384 elements 8.1 -> 6.3); just above 128 for K = 1 (8,192 tokens, 1,088 bf16, dispatch 5.7 -> 4.5).
 //  * Vectors, not narrow: whole lines are written by kWhole.  Rows that begin inside a line are written
 //    in line-sized pieces by kRagged, which reads the token again for each row: better once that saves more
-//    in partial lines than it costs, i.e. with more rows per token the shorter the rows are (the extra segment for the
-//    slack of a line is a larger part of them) and some 24 MB to write.  16,384 tokens of 7,168 bf16 in a packed
-//    buffer 16 bytes off a line, kWhole -> kRagged: 7.7 rows 495 -> 371, 3.6 rows 215 -> 157, one row 72 -> 78 (but the bf16
-//    transpose, whose waves have more to do before they store, 80 -> 72); 1,000 elements: 3.6 rows 30 -> 26, 1.9 rows
-//    16.6 -> 18.6; 512 elements, 3.6 rows: 16.9 -> 17.7; 1,024 tokens of 2,048, 3.6 rows: bf16 transpose 5.8 -> 6.8.
+//    in partial lines than it costs, i.e. with many rows per token that are long (the extra segment for the
+//    slack of a line is a larger part of short ones) and some 24 MB to write.  A weight to multiply by makes the second
+//    reading dearer, fp32 twice.  Buffers taken in turn so that none is still in the cache, packed rows 16 bytes off a
+//    line, kWhole -> kRagged, 16,384 tokens of 1,024 / 2,048 / 7,168 elements:
+//      7.7 rows: dispatch 72 -> 69, 144 -> 123, 488 -> 369; bf16 transpose 79 -> 76, 158 -> 131, 533 -> 382; fp32 157 -> 124, 301 -> 223,
+//        1,033 -> 839 (but 504 bf16 36.2 -> 37.1 and 38.9 -> 35.9);
+//      3.6 rows: dispatch 31.7 -> 32.6 (1,032: 36.4 -> 33.6), 60 -> 58, 202 -> 187; bf16 transpose 34.6 -> 37.2 (1,032: 37.5 -> 38.2),
+//        64.5 -> 63.4, 210 -> 191; fp32 61 -> 68, 120 -> 127, 397 -> 443 (but small gradients, below 24 MB: 4,096 tokens of 512
+//        10.1 -> 9.3, of 1,024 17.0 -> 14.3, of 2,048 32.5 -> 34.4; 1,024 tokens of 4,096 16.8 -> 13.8);
+//      1.9 rows: dispatch 20.9 -> 24.2, 40.2 -> 39.8, 130 -> 121; bf16 transpose 22.7 -> 28.2, 42 -> 46, 131 -> 136; fp32 39 -> 50,
+//        73 -> 95, 248 -> 319.
 //  * Elements, few of them: kElems, whose lanes are all resident and have the shortest chain (2,048 tokens,
 //    K = 1, 65 bf16, transpose: 2.7, flat 3.2, ragged 3.4), up to 512 Ki elements for K <= 2 and the bf16
 //    transpose (2,048 x 100, 7.7 rows: 5.8, ragged 6.9), else up to 128 Ki (dispatch of 2,048 x 250, 7.7 rows: 5.8, ragged 5.3;
 //    fp32 transpose of 64 x 7,168 6.8 and 5.5).
-//  * Elements, many copies of rows of at most 320 bytes: kElems, whose neighbouring lanes write neighbouring elements
-//    where vectors straddle lines (65,536 tokens, 7.7 rows, kElems / flat: dispatch of 33 bf16 20 / 30, of 130 55 / 61; fp32
-//    transpose of 65 48 / 64; but dispatch of 250 with 32,768 tokens 52 / 46).  The bf16 transpose, dearer per
-//    element, only up to 80 bytes and from 65,536 tokens on (33: 32 / 36; with 32,768 tokens 19 / 15).
+//  * Elements, many copies of short rows: kElems, whose neighbouring lanes write neighbouring elements
+//    where vectors straddle lines (65,536 tokens, 7.7 rows, fresh buffers, kElems / flat: dispatch of 17 bf16 15 / 23, of 33 27 / 33,
+//    but of 65 41 / 41, of 130 84 / 61; fp32 transpose of 33 40 / 45, but of 65 69 / 65; bf16 transpose, dearer per
+//    element, of 17 23 / 25, but of 33 38 / 35; and with 32,768 tokens of 17 13.7 / 12.4).
 //  * Elements, narrow: flat up to 32 vectors, 20 for fp32 with K > 2 (65,536 tokens, 3.6 rows, ragged -> flat: 33 fp32 25 ->
-//    16, 130 33 -> 39), else ragged (7.3 copies of 301 bf16: 113, flat 116).
+//    16, 130 33 -> 39), 12 with many copies (7.7 rows, 65 fp32: 57 -> 65), else ragged (7.3 copies of 301 bf16: 113, flat 116).
 static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool scaled) {
   if (!in_vectors(f)) return Route::kElems;
   const bool wide = f.elem_bytes == 4, scaled_bf16 = scaled && !wide;
@@ -970,29 +976,32 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
     const int above = f.K == 1 ? (wide ? 96 : 88) : scaled_bf16 || (f.K == 2 && !wide) ? 80 : 0;
     const bool few_lanes = (f.vecs > kWave && f.vecs <= above) || (f.K == 1 && f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
     if (f.T >= kFlatTokens && (f.vecs <= narrow || few_lanes)) return Route::kFlat;
-    const double rows = rows_per_token(plan, f.T);
-    const bool enough = rows >= 2.5 ? f.vecs > 80 : rows >= 1.5 ? f.vecs > 2 * kWave : scaled_bf16 && rows > 0.0 && f.vecs >= 4 * kWave;
-    return !f.lines && enough && (double)elems * f.elem_bytes * rows >= 24e6 ? Route::kRagged : Route::kWhole;
+    const double rows = rows_per_token(plan, f.T), bytes = (double)elems * f.elem_bytes;
+    const bool enough = rows > 6.0   ? f.vecs > 120
+                        : rows > 2.5 ? (wide ? bytes < 24e6 && f.vecs >= 2 * kWave : f.vecs >= (scaled ? 4 * kWave : 2 * kWave + 1))
+                                     : rows > 1.5 && !scaled && f.vecs >= 4 * kWave;
+    return !f.lines && enough && bytes * rows >= 24e6 ? Route::kRagged : Route::kWhole;
   }
   if (elems <= (scaled_bf16 || f.K <= 2 ? 512 : 128) * 1024) return Route::kElems;
   const bool many_copies = plan->expected_rows > 6 * (int64_t)f.T;
-  if (many_copies && f.T >= (scaled_bf16 ? 65536 : 32768) && f.vecs <= (scaled_bf16 ? 5 : 20)) return Route::kElems;
-  return f.T >= kFlatTokens && f.vecs <= (wide && f.K > 2 ? 20 : 32) ? Route::kFlat : Route::kRagged;
+  if (many_copies && f.T >= (scaled_bf16 ? 65536 : 32768) && f.vecs <= (wide ? 9 : scaled ? 3 : 5)) return Route::kElems;
+  return f.T >= kFlatTokens && f.vecs <= (wide && f.K > 2 ? (many_copies ? 12 : 20) : 32) ? Route::kFlat : Route::kRagged;
 }
 
 // Combine; vecs_per_lane is that of the wave kernels' launch shape.
 //  * With the caller's weights there is no flat kernel.  Elements: kElems where K slots of H elements are less work than
-//    a wave's merging of the slots (65,536 tokens, kElems / ragged: K = 1, 100 bf16 16 / 36; K = 2, 65 32 / 49; K = 8, 3.6 rows,
-//    17 43 / 68; but K = 1, 250 56 / 41; K = 8, 33 77 / 71; fp32, K = 8, 9 32 / 43, but 17 50 / 45) or there are few of them
+//    a wave's merging of the slots (65,536 tokens, fresh buffers, kElems / ragged: K = 1, 99 bf16 23 / 38, 161 46 / 40; K = 2, 65 33 / 50,
+//    99 58 / 51; K = 8, 3.6 rows, 17 53 / 70; K = 4, fp32, 17 27 / 39, 33 55 / 40; K = 1, fp32, 99 32 / 30) or there are few of them
 //    (1,024 tokens, K = 1, 513: 3.5 / 4.0), as long as its chain over K slots squared is hidden (8,192 tokens, K =
-//    8, 9 elements: 13.7 / 10.7).
+//    8, 17 elements: 14.3 / 11.1).
 //  * With the plan's weights.  Vectors: flat where narrow (65,536 tokens, 3.6 rows, in waves -> flat: 64 bf16 27.6 -> 9.4,
 //    320 35.1 -> 32.2, 384 38.3 -> 37.7; 64 fp32 27.7 -> 14.5, 100 31.3 -> 22.7; K = 1 further, 16,384 x 456 bf16 11.0 -> 8.6),
 //    and where segments of one vector per lane would leave the last one mostly idle (16,384 tokens, 576 bf16: 18.6 ->
-//    16.1, 1,088 28.8 -> 27.3, 320 fp32 18.5 -> 16.6); segments of four only for K = 1 (65 to 88 bf16 vectors 4 to 30 %) or
-//    few tokens (1,024 x 1,000 bf16, K = 1: 3.4 -> 3.0; 8,192 x 576, K = 2: equal, 1,152 20 % slower).  Elements: flat where waves would have a quarter of their lanes idle or more (65,536
-//    tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344), kElems for K <= 2 and few elements (2,048 tokens, K
-//    = 1, 65 bf16: 2.6, flat 3.1).
+//    16.1, 1,088 28.8 -> 27.3, 320 fp32 18.5 -> 16.6); segments of four only for K = 1 (65 to 88 bf16 vectors 4 to 30 %,
+//    320 fp32 16,384 tokens 10.2 -> 9.7, 65,536 32.9 -> 29.1) or few tokens of bf16 (1,024 x 1,000, K = 1: 3.4 -> 3.0; 8,192
+//    x 576, K = 2: equal, 1,152 20 % slower).  Elements: flat where waves would have a quarter of their lanes idle
+//    or more (65,536 tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344), kElems for K <= 2 and few elements
+//    (2,048 tokens, K = 1, 65 bf16: 2.6, flat 3.1).
 //  * In waves: kWhole for whole lines and where the slack of a line would cost kRagged one more segment, of few or long
 //    ones (4,096 tokens, K = 1, 2,048 bf16 16 bytes off a line, the caller's weights: 6.4 whole, 9.4 ragged) or with reads
 //    off a line that kWhole would do in lines (8,192 x 4,096, 7.7 rows, only out off a line: 97 and 101); else kRagged
@@ -1007,13 +1016,13 @@ static inline Route combine_route(const RowForm &f, bool from_plan, int vecs_per
   const Route waves = f.vectors && (f.lines || f.vecs <= kWave || dear) ? Route::kWhole : Route::kRagged;
   if (!from_plan) {
     if (f.vectors) return waves;
-    const bool light = (int64_t)f.H * f.K <= (wide ? 130 : 200) || elems <= 512 * 1024 / (f.K * f.K);
+    const bool light = (int64_t)f.H * f.K <= (wide ? 90 : 150) || elems <= 512 * 1024 / (f.K * f.K);
     return light && (f.K <= 2 || f.T >= 2048 * f.K) ? Route::kElems : waves;
   }
   if (f.vectors) {
     const bool few_lanes = (f.vecs > kWave && f.vecs <= 88) || (f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
     const bool above = vecs_per_lane == 1 ? few_lanes && f.T >= kFlatTokens
-                       : !wide && f.vecs > kWave && f.vecs <= (f.K <= 2 && f.T <= 1024 ? kFlatVecs : f.K == 1 ? 88 : 0);
+                       : f.vecs > kWave && f.vecs <= (!wide && f.K <= 2 && f.T <= 1024 ? kFlatVecs : f.K == 1 ? 88 : 0);
     const bool flat = f.vecs <= (f.K == 1 ? kWave : wide ? 32 : 48) || above;
     return many && flat ? Route::kFlat : waves;
   }

@@ -539,7 +539,10 @@ ROW_ROUTES = [
     (1024, 1, 1160, 8), (500, 8, 4104, 0), (300, 8, 7168, 8), (64, 8, 2048, 1), (5, 64, 520, 0), (32768, 8, 33, 0), (32768, 8, 9, 1),
     (32769, 4, 161, 0), (65536, 8, 20, 1), (65536, 8, 41, 1), (16384, 8, 17, 0), (16384, 8, 16, 1), (16384, 8, 25, 1), (8192, 2, 100, 1),
     (2049, 1, 257, 1), (2048, 1, 255, 1), (8192, 3, 77, 1), (8192, 3, 81, 1),
-    (4096, 1, 704, 0), (4096, 1, 712, 8), (4096, 1, 1152, 0), (4096, 3, 704, 0), (4096, 3, 1152, 8), (4096, 3, 1160, 8), (4096, 3, 576, 8)]
+    (4096, 1, 704, 0), (4096, 1, 712, 8), (4096, 1, 1152, 0), (4096, 3, 704, 0), (4096, 3, 1152, 8), (4096, 3, 1160, 8), (4096, 3, 576, 8),
+    (4096, 8, 952, 8), (4096, 8, 968, 8), (3100, 8, 2040, 8), (3100, 8, 2048, 8), (4000, 4, 1024, 8), (4000, 4, 1032, 8), (2000, 4, 2048, 8),
+    (32768, 8, 37, 0), (32768, 8, 40, 1), (65536, 8, 25, 1), (8192, 1, 91, 1), (8192, 2, 75, 1), (8192, 2, 76, 1), (8192, 3, 30, 1),
+    (8192, 3, 31, 1), (4096, 1, 352, 0), (4096, 1, 356, 0), (8192, 8, 48, 1), (8192, 8, 49, 1)]
 
 
 @pytest.mark.parametrize("T,K,H,off", ROW_ROUTES)
