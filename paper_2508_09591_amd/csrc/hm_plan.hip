@@ -12,7 +12,7 @@
 //
 // Every workgroup needs the counts of all the others (the destination totals give dest_offset),
 // so the plan has a grid-wide dependency in the middle.  A plan of one workgroup has none
-// (plan_alone_kernel: 128 tokens of 8 slots 6.4 us by kernel trace, 9.5 with the grid-wide step and
+// (plan_alone_kernel: 128 tokens of 8 slots 6.0 us by kernel trace, 9.5 with the grid-wide step and
 // loops over the slots).  Otherwise there are two ways through it:
 //   * plans of at most 256 workgroups (262,144 slots) run as ONE launch, plan_fused_kernel: the
 //     workgroups publish their counts, meet at a grid barrier and go on to write the maps from

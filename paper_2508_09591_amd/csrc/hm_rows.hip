@@ -20,8 +20,12 @@
 // set with an unused dynamic LDS allocation: dispatch runs 24 waves per CU (-5 % on the 64 Ki-token
 // layer at node level, -9 % at rank level, neutral elsewhere), or 12 where many rows per token meet
 // cached tokens; the bf16 transpose does more arithmetic per byte and is faster uncapped, the fp32 one is
-// capped where transpose_capped says so; combine keeps about 128 KiB
-// of row loads in flight per CU (32 waves up to four rows per token, 16 at eight).
+// capped where transpose_capped says so; combine keeps about 128 KiB of row loads in flight per CU (32 waves
+// up to four rows per token, 16 at eight).
+//
+// That is the form for rows of whole 128-byte lines that are wider than a wave's lanes.  Rows that begin inside a
+// line, of any length, narrow, odd or few have forms of their own: spread_route and combine_route, at the end, say
+// which call takes which, and the kernels say what each is bound by.
 //
 // Combine has two forms.  With the caller's weights (topk_weights != NULL) every wave merges the
 // K slots of its token itself (2K readlanes) and handles 4 KiB of the row, four rows in flight.
@@ -927,7 +931,9 @@ static inline RowForm row_form(int T, int K, int H, int elem_bytes, const void *
 }
 static inline bool in_vectors(const RowForm &f) { return f.H * (int64_t)f.elem_bytes >= 16 && f.H <= kMaxVectorH; }
 
-// All figures below: us per call, graphs of ten calls, the kernels in turn on the same buffers.
+// All figures below: us per call, graphs of ten calls, the kernels in turn.  Those with fresh buffers (or buffers taken
+// in turn) go round enough pairs that none is still in the 256 MB Infinity Cache, as in a training step; the others use
+// one pair, and the lines that they draw were measured again with fresh ones.
 //
 // Tokens from which a lane per vector pays: with fewer, all waves of a wave per token are resident at once and a call
 // lasts as long as one wave's chain, which is longer where a lane walks its token's K slots itself (512 tokens,

@@ -529,8 +529,8 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
 // Sums the chunks' partial tables into the tables swap_build_kernel reads; blockIdx.y is the cut and
 // blockIdx.x a 32 x 32 tile of C, then of CG.  A lane sums four neighbouring values, all chunks' loads in
 // flight, and the tile is turned round in LDS, so that the transposes are written in whole lines too (one lane per
-// value wrote them a word per line: 6.6 us for 128 experts and four cuts, 9.2 us for 256; now 4.2 and
-// 5.6).  L is the diagonal of C and L0[a] the entry of CG in a's own group (every token that selects a
+// value wrote them a word per line: kernel trace 6.6 us for 128 experts and four cuts, 9.2 us for 256; now 4.7 and
+// 6.2).  L is the diagonal of C and L0[a] the entry of CG in a's own group (every token that selects a
 // selects something there), so neither needs a table of its own upstream.
 constexpr int kTile = 32;
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
@@ -630,7 +630,7 @@ constexpr int kBuildRows = 4;
 // The same for cuts of a multiple of four groups, where a lane takes four neighbouring groups j of its c:
 // their unswapped counts are read once for all rows, a row costs one 16-byte store, and only the lanes
 // that hold the group of c or of r look anything up (a quarter of the lanes, each of whose rows is
-// a few instructions: 256 experts, four cuts, kernel trace 12.8 -> 7.6 us for 15.7 MB of Z).
+// a few instructions: 256 experts, four cuts, 15.7 MB of Z, kernel trace 12.8 -> 9.3 us, where the fastest launches take 7.5).
 __device__ __forceinline__ void build_quads(const SwapParams &p, int cut, int l, int r0) {
   const int ng = p.ng[cut], nq = ng / 4;
   const int32_t *__restrict__ const C = p.C[cut];
