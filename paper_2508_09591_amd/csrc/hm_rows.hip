@@ -935,63 +935,73 @@ static inline bool in_vectors(const RowForm &f) { return f.H * (int64_t)f.elem_b
 // in turn) go round enough pairs that none is still in the 256 MB Infinity Cache, as in a training step; the others use
 // one pair, and the lines that they draw were measured again with fresh ones.
 //
-// Tokens from which a lane per vector pays: with fewer, all waves of a wave per token are resident at once and a call
-// lasts as long as one wave's chain, which is longer where a lane walks its token's K slots itself (512 tokens,
-// K = 8, 64 bf16, in waves -> flat: dispatch 2.7 -> 3.0, bf16 transpose 3.6 -> 4.8; 4,096 tokens, 7.7 rows: 4.3 -> 3.5
-// and 7.1 -> 5.3).  One or two slots are no such chain: combine is flat at any T there (512 tokens, K = 1, 16 bf16:
-// 3.2 -> 2.7).
+// Tokens from which a lane per vector pays where a row is whole vectors: with fewer, all waves of a wave per token are
+// resident at once and a call lasts as long as one wave's chain, which is longer where a lane walks its token's K
+// slots itself (512 tokens, K = 8, 64 bf16, in waves -> flat: dispatch 2.7 -> 3.0, bf16 transpose 3.6 -> 4.8; 4,096
+// tokens, 7.7 rows: 4.3 -> 3.5 and 7.1 -> 5.3).  One or two slots are no such chain: combine is flat at any T there (512
+// tokens, K = 1, 16 bf16: 3.2 -> 2.7).
 constexpr int kFlatTokens = 4096;
 
 // Dispatch (scaled = false) and transpose.
 //  * Vectors, narrow: flat up to the widths at which it still gains.  65,536 tokens, 3.6 rows each, in waves ->
-//    flat: dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 192 18.4 -> 17.8 (but 7.7 rows, or 32,768 tokens:
-//    8 % slower); bf16 transpose of 192 32.6 -> 22.0, of 256 33.4 -> 26.9; fp32 transpose of 16 12.3 -> 5.8, of 64 16.9 ->
-//    12.5, of 96 21.1 -> 19.6 (but 8,192 tokens: 5 % slower).  With K <= 2 further (K = 1: 320 bf16 16.8 -> 15.3).
-//    And just above 64 vectors, where waves leave most of their second segment idle: bf16 transpose (16,384 tokens, 576
-//    elements 17.7 -> 14.8), dispatch for K <= 2 (K = 1: 6.7 -> 4.6; but K = 8: 12.7 -> 13.3), fp32 transpose for K = 1
-//    (384 elements 8.1 -> 6.3); just above 128 for K = 1 (8,192 tokens, 1,088 bf16, dispatch 5.7 -> 4.5).
+//    flat: dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 256 32.8 -> 28.8 (but 32,768 tokens: 3 % slower, or 7.7
+//    rows: 14 % slower); bf16 transpose of 192 32.6 -> 22.0, of 256 33.4 -> 26.9; fp32 transpose of 16 12.3 -> 5.8, of 64
+//    16.9 -> 12.5, of 96 21.1 -> 19.6 (but 8,192 tokens: 5 % slower).  With K <= 2 further (K = 1: 320 bf16 16.8 -> 15.3).
+//    And just above 64 vectors, where waves leave most of their second segment idle: bf16 transpose (16,384 tokens of
+//    576, 3.6 rows 17.7 -> 14.8; of 640 up to six rows only, with 7.7 31.5 -> 33.7; not off a line: 8,192 of 520 11.8 ->
+//    12.4), dispatch for K <= 2 (K = 1: 6.7 -> 4.6; but K = 8: 12.7 -> 13.3), fp32 transpose for K = 1 (384 elements 8.1 ->
+//    6.3); just above 128 for K = 1 (8,192 tokens, 1,088 bf16, dispatch 5.7 -> 4.5).
 //  * Vectors, not narrow: whole lines are written by kWhole.  Rows that begin inside a line are written
 //    in line-sized pieces by kRagged, which reads the token again for each row: better once that saves more
 //    in partial lines than it costs, i.e. with many rows per token that are long (the extra segment for the
 //    slack of a line is a larger part of short ones) and some 24 MB to write.  A weight to multiply by makes the second
-//    reading dearer, fp32 twice.  Buffers taken in turn so that none is still in the cache, packed rows 16 bytes off a
-//    line, kWhole -> kRagged, 16,384 tokens of 1,024 / 2,048 / 7,168 elements:
+//    reading dearer, fp32 twice.  Fresh buffers, packed rows 16 bytes off a line, kWhole -> kRagged, 16,384 tokens of
+//    1,024 / 2,048 / 7,168 elements:
 //      7.7 rows: dispatch 72 -> 69, 144 -> 123, 488 -> 369; bf16 transpose 79 -> 76, 158 -> 131, 533 -> 382; fp32 157 -> 124, 301 -> 223,
-//        1,033 -> 839 (but 504 bf16 36.2 -> 37.1 and 38.9 -> 35.9);
+//        1,033 -> 839; from 36 MB on just above 64 vectors, too (584 bf16: dispatch 46.6 -> 42.9, 8,192 tokens bf16 transpose
+//        26.7 -> 23.8; but 456: 37.1 -> 39.3);
 //      3.6 rows: dispatch 31.7 -> 32.6 (1,032: 36.4 -> 33.6), 60 -> 58, 202 -> 187; bf16 transpose 34.6 -> 37.2 (1,032: 37.5 -> 38.2),
 //        64.5 -> 63.4, 210 -> 191; fp32 61 -> 68, 120 -> 127, 397 -> 443 (but small gradients, below 24 MB: 4,096 tokens of 512
 //        10.1 -> 9.3, of 1,024 17.0 -> 14.3, of 2,048 32.5 -> 34.4; 1,024 tokens of 4,096 16.8 -> 13.8);
 //      1.9 rows: dispatch 20.9 -> 24.2, 40.2 -> 39.8, 130 -> 121; bf16 transpose 22.7 -> 28.2, 42 -> 46, 131 -> 136; fp32 39 -> 50,
 //        73 -> 95, 248 -> 319.
-//  * Elements, few of them: kElems, whose lanes are all resident and have the shortest chain (2,048 tokens,
-//    K = 1, 65 bf16, transpose: 2.7, flat 3.2, ragged 3.4), up to 512 Ki elements for K <= 2 and the bf16
-//    transpose (2,048 x 100, 7.7 rows: 5.8, ragged 6.9), else up to 128 Ki (dispatch of 2,048 x 250, 7.7 rows: 5.8, ragged 5.3;
-//    fp32 transpose of 64 x 7,168 6.8 and 5.5).
+//  * Elements, few of them: kElems, whose lanes are all resident and have the shortest chain, for K <= 2 up to 512 Ki
+//    elements (2,048 tokens, K = 1, 65 bf16, transpose: 2.7, flat 3.2, ragged 3.4), for the bf16 transpose up to 256 Ki
+//    (2,048 x 33, 7.7 rows: 5.1, flat 5.6, ragged 7.6; but 16,384 x 17: 7.3, flat 6.5), for dispatch of many copies of up to nine
+//    vectors up to 128 Ki (2,048 x 33: 3.9, flat 4.2; but x 100: 4.5, flat 4.0; 16 x 17: 3.5, flat 2.8).
 //  * Elements, many copies of short rows: kElems, whose neighbouring lanes write neighbouring elements
 //    where vectors straddle lines (65,536 tokens, 7.7 rows, fresh buffers, kElems / flat: dispatch of 17 bf16 15 / 23, of 33 27 / 33,
 //    but of 65 41 / 41, of 130 84 / 61; fp32 transpose of 33 40 / 45, but of 65 69 / 65; bf16 transpose, dearer per
 //    element, of 17 23 / 25, but of 33 38 / 35; and with 32,768 tokens of 17 13.7 / 12.4).
-//  * Elements, narrow: flat up to 32 vectors, 20 for fp32 with K > 2 (65,536 tokens, 3.6 rows, ragged -> flat: 33 fp32 25 ->
-//    16, 130 33 -> 39), 12 with many copies (7.7 rows, 65 fp32: 57 -> 65), else ragged (7.3 copies of 301 bf16: 113, flat 116).
+//  * Elements, narrow: flat at any number of tokens (fp32 transpose of 16 x 5, 7.8 rows: 3.0, ragged 3.9), but from 2,048 on
+//    for the bf16 transpose (512 x 250 5.3, ragged 5.7, but 3.6 rows 4.7 and 4.2; 2,048: 6.5 and 7.6, 5.2 and 5.0).  Up to 32
+//    vectors, for fp32 with K > 2 up to 20 (65,536 tokens, 3.6 rows, ragged -> flat: 33 fp32 25 -> 16, 130 33 -> 39), 12 with
+//    many copies of many tokens (7.7 rows, 65 fp32: 57 -> 65, but 8,192 tokens 9.2 -> 8.6), for K = 1 up to 76, as far as the ragged kernel's slack of a line fills a
+//    second segment badly (65,536 x 250 fp32: 55 -> 28); else ragged (7.3 copies of 301 bf16: 113, flat 116).
 static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool scaled) {
   if (!in_vectors(f)) return Route::kElems;
   const bool wide = f.elem_bytes == 4, scaled_bf16 = scaled && !wide;
   const int64_t elems = (int64_t)f.T * f.H;
+  const double rows = rows_per_token(plan, f.T), bytes = (double)elems * f.elem_bytes;
   if (f.vectors) {
-    const int narrow = f.K == 1 ? 48 : f.K == 2 ? (wide ? 24 : 48) : wide ? 16 : scaled ? 32 : 16;
-    const int above = f.K == 1 ? (wide ? 96 : 88) : scaled_bf16 || (f.K == 2 && !wide) ? 80 : 0;
-    const bool few_lanes = (f.vecs > kWave && f.vecs <= above) || (f.K == 1 && f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
-    if (f.T >= kFlatTokens && (f.vecs <= narrow || few_lanes)) return Route::kFlat;
-    const double rows = rows_per_token(plan, f.T), bytes = (double)elems * f.elem_bytes;
-    const bool enough = rows > 6.0   ? f.vecs > 120
+    const bool enough = rows > 6.0   ? f.vecs > (bytes * rows >= 36e6 ? kWave : 120)
                         : rows > 2.5 ? (wide ? bytes < 24e6 && f.vecs >= 2 * kWave : f.vecs >= (scaled ? 4 * kWave : 2 * kWave + 1))
                                      : rows > 1.5 && !scaled && f.vecs >= 4 * kWave;
-    return !f.lines && enough && bytes * rows >= 24e6 ? Route::kRagged : Route::kWhole;
+    const bool ragged = !f.lines && enough && bytes * rows >= 24e6;
+    const int many = f.T >= 65536 && rows <= 6.0 ? 32 : 16;
+    const int narrow = f.K == 1 ? 48 : f.K == 2 ? (wide ? 24 : 48) : wide ? 16 : scaled ? 32 : many;
+    const int above = f.K == 1 ? (wide ? 96 : 88) : f.K == 2 ? (wide ? 0 : 80) : scaled_bf16 && f.lines ? (rows > 6.0 ? 72 : 80) : 0;
+    const bool few_lanes = (f.vecs > kWave && f.vecs <= above) || (f.K == 1 && f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
+    if (f.T >= kFlatTokens && (f.vecs <= narrow || (few_lanes && !ragged))) return Route::kFlat;
+    return ragged ? Route::kRagged : Route::kWhole;
   }
-  if (elems <= (scaled_bf16 || f.K <= 2 ? 512 : 128) * 1024) return Route::kElems;
   const bool many_copies = plan->expected_rows > 6 * (int64_t)f.T;
-  if (many_copies && f.T >= (scaled_bf16 ? 65536 : 32768) && f.vecs <= (wide ? 9 : scaled ? 3 : 5)) return Route::kElems;
-  return f.T >= kFlatTokens && f.vecs <= (wide && f.K > 2 ? (many_copies ? 12 : 20) : 32) ? Route::kFlat : Route::kRagged;
+  const bool few = f.K <= 2       ? elems <= 512 * 1024
+                   : scaled_bf16 ? elems <= 256 * 1024
+                                 : !wide && many_copies && elems <= 128 * 1024 && f.T >= 256 && f.vecs <= 9;
+  if (few || (many_copies && f.T >= (scaled_bf16 ? 65536 : 32768) && f.vecs <= (wide ? 9 : scaled ? 3 : 5))) return Route::kElems;
+  const int narrow = f.K == 1 ? 76 : wide && f.K > 2 ? (many_copies && f.T >= 32768 ? 12 : 20) : 32;
+  return f.vecs <= narrow && (!scaled_bf16 || f.T >= 2048) ? Route::kFlat : Route::kRagged;
 }
 
 // Combine; vecs_per_lane is that of the wave kernels' launch shape.
@@ -1006,7 +1016,8 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
 //    16.1, 1,088 28.8 -> 27.3, 320 fp32 18.5 -> 16.6); segments of four only for K = 1 (65 to 88 bf16 vectors 4 to 30 %,
 //    320 fp32 16,384 tokens 10.2 -> 9.7, 65,536 32.9 -> 29.1) or few tokens of bf16 (1,024 x 1,000, K = 1: 3.4 -> 3.0; 8,192
 //    x 576, K = 2: equal, 1,152 20 % slower).  Elements: flat where waves would have a quarter of their lanes idle
-//    or more (65,536 tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344), kElems for K <= 2 and few elements
+//    or more (65,536 tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344) or, for K = 1, three of four vectors of a
+//    lane (65,536 x 451: ragged 37, flat 28), kElems for K <= 2 and few elements
 //    (2,048 tokens, K = 1, 65 bf16: 2.6, flat 3.1).
 //  * In waves: kWhole for whole lines and where the slack of a line would cost kRagged one more segment, of few or long
 //    ones (4,096 tokens, K = 1, 2,048 bf16 16 bytes off a line, the caller's weights: 6.4 whole, 9.4 ragged) or with reads
@@ -1034,7 +1045,8 @@ static inline Route combine_route(const RowForm &f, bool from_plan, int vecs_per
   }
   if (f.K <= 2 && elems <= 512 * 1024) return Route::kElems;
   const int in_waves = f.vecs + slack, lanes = (in_waves + kWave - 1) / kWave * kWave;
-  return many && f.vecs <= kFlatVecs && 4 * in_waves <= 3 * lanes ? Route::kFlat : waves;
+  const bool idle = 4 * in_waves <= 3 * lanes || (f.K == 1 && f.vecs <= kWave);
+  return many && f.vecs <= kFlatVecs && idle ? Route::kFlat : waves;
 }
 
 }  // namespace hm

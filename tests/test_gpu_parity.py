@@ -542,7 +542,10 @@ ROW_ROUTES = [
     (4096, 1, 704, 0), (4096, 1, 712, 8), (4096, 1, 1152, 0), (4096, 3, 704, 0), (4096, 3, 1152, 8), (4096, 3, 1160, 8), (4096, 3, 576, 8),
     (4096, 8, 952, 8), (4096, 8, 968, 8), (3100, 8, 2040, 8), (3100, 8, 2048, 8), (4000, 4, 1024, 8), (4000, 4, 1032, 8), (2000, 4, 2048, 8),
     (32768, 8, 37, 0), (32768, 8, 40, 1), (65536, 8, 25, 1), (8192, 1, 91, 1), (8192, 2, 75, 1), (8192, 2, 76, 1), (8192, 3, 30, 1),
-    (8192, 3, 31, 1), (4096, 1, 352, 0), (4096, 1, 356, 0), (8192, 8, 48, 1), (8192, 8, 49, 1)]
+    (8192, 3, 31, 1), (4096, 1, 352, 0), (4096, 1, 356, 0), (8192, 8, 48, 1), (8192, 8, 49, 1),
+    (32768, 8, 48, 1), (32768, 8, 49, 1), (16, 8, 17, 1), (255, 8, 65, 1), (256, 8, 65, 1), (256, 8, 73, 1), (2048, 8, 128, 1), (2048, 8, 129, 1),
+    (2047, 8, 129, 1), (2048, 1, 607, 1), (2048, 1, 609, 1), (2048, 1, 303, 1), (2048, 1, 305, 1), (4700, 8, 520, 8), (5200, 8, 520, 8),
+    (5200, 8, 512, 8), (65536, 3, 256, 0), (65536, 3, 264, 0), (4096, 8, 576, 0), (4096, 8, 640, 0), (4096, 8, 584, 0), (4096, 1, 401, 1), (4096, 1, 449, 1)]
 
 
 @pytest.mark.parametrize("T,K,H,off", ROW_ROUTES)
