@@ -814,7 +814,7 @@ def run_planner(args, emit=True, workload=None):
     # The co-occurrence tables are int8 matrix products over 0/1 indicator tiles (E <= 256): per cut
     # C = A^T S (E_pad x E_pad x T) and CG = S^T M (E_pad x 32 ceil(ng/32) x T).  Their dense operation count
     # against the int8 MFMA peak is what the line reports; the products themselves are a small part of the
-    # call (filling the tiles, barriers and LDS latency, and five short launches, set its time).
+    # call (filling the tiles, barriers and LDS latency, and three short launches, set its time).
     e_pad = 32 * (1 if E <= 32 else 2 if E <= 64 else 4 if E <= 128 else 8)
     dense_ops = sum(2 * e_pad * (e_pad + 32 * ((u + 31) // 32)) * T for u in cuts) if E <= 256 else 0
     peak_ops = 5.0e15
