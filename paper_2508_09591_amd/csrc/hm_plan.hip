@@ -4,24 +4,22 @@
 // Rows of a destination are numbered in ascending slot order, so a lane's row is
 //     dest_offset[d] + (kept slots of d in earlier workgroups) + (in earlier waves of this
 //     workgroup) + (in lower lanes of this wave),
-// and the last term is a popcount over wavefront ballots.  No atomics decide positions, so the
-// plan is deterministic and stable.  A workgroup first stages the ranks and nodes of its tokens (its
-// 1024 slots and the rest of its first and last token) in LDS: each expert id is looked up once and
-// all "same destination as an earlier / later slot of my token" questions become comparisons of
-// eight bytes.
+// and the last term is a count of bits below the lane's own in a 64-bit word per (wave, destination).  No order
+// of atomics decides positions, so the plan is deterministic and stable.  A workgroup first stages the
+// destinations of its tokens (its 1024 slots and the rest of its first and last token) in LDS: each expert id is
+// looked up once and all "same destination as an earlier / later slot of my token" questions become
+// comparisons of eight bytes.
 //
 // Every workgroup needs the counts of all the others (the destination totals give dest_offset),
 // so the plan has a grid-wide dependency in the middle.  A plan of one workgroup has none
-// (plan_alone_kernel: 128 tokens of 8 slots 6.0 us by kernel trace, 9.5 with the grid-wide step and
-// loops over the slots).  Otherwise there are two ways through it:
+// (plan_alone_kernel: 128 tokens of 8 slots 5.2 us by kernel trace).  Otherwise there are two ways through it:
 //   * plans of at most 256 workgroups (262,144 slots) run as ONE launch, plan_fused_kernel: the
-//     workgroups publish their counts, meet at a grid barrier and go on to write the maps from
+//     workgroups publish their counts, wait for one another's and go on to write the maps from
 //     what they staged.  At these sizes the work is a few microseconds and a second launch (its
 //     gap, and staging everything again) cost more than the kernels themselves.  All workgroups
-//     are resident together (the launcher checks the device's capacity), the barrier spins on
-//     per-workgroup flags holding a value unique to the launch, so the caller's workspace needs
-//     no initialisation, and every wait is bounded: a wave that gives up flags HM_ERR_HIP and
-//     exits.
+//     are resident together (the launcher checks the device's capacity), the counts carry a value
+//     unique to the launch, so the caller's workspace needs no initialisation, and every wait is
+//     bounded: a wave that gives up flags HM_ERR_HIP and exits.
 //   * larger plans take separate launches: plan_count_kernel (per-workgroup counts ->
 //     workspace), plan_scan_kernel once the matrix has kPlanScanMinEntries entries (one
 //     workgroup per destination turns it into exclusive prefixes plus a row of totals; below
@@ -68,13 +66,38 @@ struct PlanParams {
   int32_t *load_expert, *load_rank, *load_node;  // optional: the counts of hm_expert_load, fused
 };
 
-// ---- the tokens of a workgroup in LDS --------------------------------------------------------------
-// The ranks (hop tables: destinations) and nodes of the workgroup's tokens lie in LDS as bytes, token by
-// token, each token padded to whole 8-byte words (0xFF: invalid, dropped or no slot).  Which other slots of its token
-// share a lane's destination is then one comparison of eight bytes at a time instead of a loop over
-// the slots, and the position among the wave's slots of one destination comes from one ballot per
-// bit of the destination instead of one per destination.  The kernel was bound by issuing those loops
-// (sixteen waves share a CU): 22 -> 20 us for the write launch of the 64 Ki-token layer.
+// Words that another workgroup of the same launch reads or writes are accessed with device-scope
+// atomic loads and stores (the workgroups sit on different dies with caches of their own).
+__device__ __forceinline__ void st_device(int32_t *a, int32_t v) {
+  __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t ld_device(const uint64_t *a) {
+  return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_device(uint64_t *a, uint64_t v) {
+  __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The calling wave's earlier device-scope stores have been acknowledged when this returns.
+__device__ __forceinline__ void wait_for_own_stores() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// ---- the slots of a workgroup --------------------------------------------------------------------
+// The destinations of the workgroup's tokens lie in LDS as bytes, token by token, each token padded to whole
+// 8-byte words (kNoCopy and above: no copy).  Which other slots of its token share a lane's destination is then one
+// comparison of eight bytes at a time instead of a loop over the slots.
+//
+// What a plan kernel spends its time on is neither memory nor arithmetic but the instruction stream: a workgroup
+// runs its code once, from a cold instruction cache, at about 0.5 ns per byte (a probe of straight-line code: 7 KB 4.2
+// us, 28 KB 14.9), and sixteen waves issue each instruction in turn.  So the steps below are chosen for few
+// instructions, and nothing is unrolled or expanded twice that need not be:
+//   * an expert's rank and node come from one 16-bit LDS entry;
+//   * the slots of a wave with the same destination are a 64-bit LDS word per (wave, destination), one `or` per
+//     slot, instead of a ballot per bit of the destination; its bits below a lane are the lane's position, its
+//     number of bits the wave's count, kept as a byte, so that the sums over sixteen waves are a few byte sums;
+//   * masks and duplicate-free loads are worked out while the workgroups wait for one another, and of the loads
+//     only those that are not the rows' own counts.  (Atomic `or`s and adds in LDS for them, by which eight and more
+//     lanes meet at one word, took 0.2 to 0.4 us each, a loop over the ranks with a ballot each 60 ns a turn.)
+// Kernel trace, before -> after, us: 1,024 x 2 slots 7.9 -> 5.8, 128 x 8 6.2 -> 5.2, 8,192 x 8 at rank level 8.1 -> 6.8, at node
+// level 9.1 -> 6.8, 4,097 x 6 without dedup 8.2 -> 6.4, 25,600 x 8 through a hop table 12.5 -> 10.3.
 struct Tokens {
   int first_slot, first_token, tokens, words;   // of the workgroup; 8-byte words per token
 };
@@ -103,42 +126,25 @@ __device__ __forceinline__ uint64_t equal_bytes(uint64_t w, uint64_t same) {
   const uint64_t x = w ^ same, low = 0x7F7F7F7F7F7F7F7Full;
   return ~(((x & low) + low) | x | low);
 }
-__device__ __forceinline__ uint64_t repeated(int byte) { return (uint64_t)(uint32_t)(byte & 0xFF) * 0x0101010101010101ull; }
-// Whether no slot before `place` has this byte.
-__device__ __forceinline__ bool first_with(const uint64_t *token, int place, int byte) {
-  const uint64_t same = repeated(byte);
-  bool first = true;
-  for (int w = 0; w < place >> 3; ++w) first = first && equal_bytes(token[w], same) == 0;
-  const uint64_t before = (1ull << (8 * (place & 7))) - 1ull;
-  return first && (equal_bytes(token[place >> 3], same) & before) == 0;
-}
-// The lanes of the wave that hold the same value in [0, n) as this one, among those with `in`.
-__device__ __forceinline__ uint64_t peers_of(int value, bool in, int n) {
-  uint64_t peers = __ballot(in);
-  for (int bit = 0; (1 << bit) < n; ++bit) {
-    const bool set = (value >> bit) & 1;
-    const uint64_t b = __ballot(set);
-    peers &= set ? b : ~b;
-  }
-  return peers;
+__device__ __forceinline__ uint64_t repeated(int byte) {
+  const uint32_t four = (uint32_t)byte * 0x01010101u;
+  return (uint64_t)four << 32 | four;
 }
 
-// Rank (or hop-table destination) of an expert id: -1 invalid, -2 no copy at this hop / slot dropped by
-// the router.
-__device__ __forceinline__ int lookup_global(const PlanParams &p, int id) {
-  if (p.dest_map) {
-    if (id == -1) return -2;
-    if ((unsigned)id >= (unsigned)p.E) return -1;
-    const int v = p.dest_map[id];
-    return (v >= 0 && v < p.Dn) ? v : (v == -1 ? -2 : -1);
-  }
-  return rank_of(p.expert_to_rank, p.E, p.G, id);
+// What an expert id stands for: the rank (hop tables: the destination) in the low byte, its node in the next one.
+// 0xFF in both is an error, 0xFE in both no copy: an id of -1 (a slot the router dropped) or a hop table's -1.
+constexpr uint32_t kBadEntry = 0xFFFFu, kNoCopy = 0xFEFEu;
+__device__ __forceinline__ uint32_t table_entry(const PlanParams &p, int e) {
+  const int g = p.dest_map ? p.dest_map[e] : p.expert_to_rank[e];
+  const uint32_t entry = (uint32_t)g | (uint32_t)node_of(p, g) << 8;   // hop tables: ranks_per_node is 1
+  return (unsigned)g < (unsigned)p.G ? entry : p.dest_map && g == -1 ? kNoCopy : kBadEntry;
 }
-// The same from the table staged in LDS.
-__device__ __forceinline__ int lookup_staged(const PlanParams &p, const int8_t *s_map, int id) {
-  if (id == -1) return -2;
-  if ((unsigned)id >= (unsigned)p.E) return -1;
-  return s_map[id];
+// staged: the table in LDS, with an entry for ids out of range behind the last expert's.
+__device__ __forceinline__ uint32_t entry_of(const PlanParams &p, const uint16_t *staged, int id) {
+  uint32_t entry;
+  if (staged) entry = staged[min((unsigned)id, (unsigned)p.E)];
+  else entry = (unsigned)id < (unsigned)p.E ? table_entry(p, id) : kBadEntry;
+  return id == -1 ? kNoCopy : entry;
 }
 
 // Bytes of a workgroup's tokens: most with K = 1, a word per slot.
@@ -154,36 +160,179 @@ __device__ __forceinline__ int halo_slot(const PlanParams &p, const Tokens &k) {
   return s < (int64_t)(k.first_token + k.tokens) * p.K ? (int)s : -1;
 }
 
-__global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void plan_count_kernel(PlanParams p) {
-  __shared__ uint64_t dest_bytes[kPlanTokenWords];
-  __shared__ int32_t cnt[kWave];
+struct PlanShared {
+  alignas(16) uint32_t wave_cnt[kWave][kPlanWaves / 4];   // per (destination, wave): rows it owns, as bytes
+  uint64_t dest_bytes[kPlanTokenWords];
+  uint64_t other_bytes[kPlanTokenWords];             // ranks where the destinations are nodes, nodes where they are ranks
+  float weight[kPlanThreads + kPlanHalo];
+  unsigned long long same_dest[kPlanWaves][kWave];   // per (wave, destination): the lanes that own a row there
+  int32_t rank_cnt[kWave], node_cnt[kWave];          // the workgroup's tokens per rank and node
+  int32_t all_tot[kWave], all_pre[kWave];            // per destination: rows of the plan, of the workgroups before
+  int32_t gave_up;
+};
+
+// One lane's slot.
+struct Slot {
+  int s, id, tok, place, dest;   // dest: kNoCopy's or kBadEntry's byte if there is none
+  uint32_t entry;
+  float w;
+  int other;                     // the node if dest is a rank, the rank if it is a node
+  bool live, has_dest, first, keep;   // first slot of its token with this destination; owner of a row
+  int pos;                       // among the rows of the wave with the same destination
+};
+
+// Whether no slot of the token before `place` has this byte.
+__device__ __forceinline__ bool first_in_token(const uint64_t *bytes, const Tokens &k, int tok, int place, int byte) {
+  const uint64_t same = repeated(byte);
+  bool first = true;
+#pragma unroll 1
+  for (int wd = 0; wd < k.words; ++wd) {
+    const int at = place - 8 * wd;   // counted from this word's first
+    const uint64_t not_before = at <= 0 ? ~0ull : at >= 8 ? 0ull : ~0ull << (8 * at);
+    first = first && (equal_bytes(bytes[tok * k.words + wd], same) & ~not_before) == 0;
+  }
+  return first;
+}
+
+// The bits of a token's bytes.
+template <typename MASK>
+__device__ __forceinline__ MASK mask_of_token(const uint64_t *bytes, const Tokens &k, int K, int tok) {
+  MASK mask = 0;
+#pragma unroll 1
+  for (int wd = 0; wd < k.words; ++wd) {
+    const uint64_t w = bytes[tok * k.words + wd];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (8 * wd + j >= K) break;
+      const uint32_t b = (uint32_t)(w >> (8 * j)) & 0xFFu;
+      mask |= b < kWave ? (MASK)1 << b : (MASK)0;
+    }
+  }
+  return mask;
+}
+
+// Everything up to the wave's counts, in two steps with the barriers between: COUNT_ONLY leaves out what only the
+// maps need.  `hist` and `table` are LDS behind PlanShared, null if not used.
+template <bool COUNT_ONLY>
+__device__ __forceinline__ Slot plan_slots(const PlanParams &p, PlanShared &sh, const Tokens &k, int32_t *hist, uint16_t *table,
+                                           bool own_status) {
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), tid = (int)threadIdx.x;
+  const bool loads = !COUNT_ONLY && p.load_expert != nullptr, tokens = loads || (!COUNT_ONLY && (p.rank_mask || p.node_mask));
+  Slot me;
+  // everything that comes from memory, in one round: this lane's slot, its halo slot, the table
+  me.s = k.first_slot + tid;
+  me.live = me.s < p.nslots;
+  const bool halo = (kPlanThreads % (unsigned)p.K) != 0;
+  const int s2 = halo ? halo_slot(p, k) : -1;
+  int id2 = -1;
+  float w2 = 0.0f;
+  me.id = -1;
+  me.w = 0.0f;
+  if (me.live) {
+    me.id = p.ids[me.s];
+    if (!COUNT_ONLY) me.w = p.weights[me.s];
+  }
+  if (halo && s2 >= 0) {
+    id2 = p.ids[s2];
+    if (!COUNT_ONLY) w2 = p.weights[s2];
+  }
+  if (own_status && tid == 0) st_device(p.status, 0);
+  if (table)
+    for (int e = tid; e <= p.E; e += kPlanThreads) table[e] = (uint16_t)(e < p.E ? table_entry(p, e) : kBadEntry);
+  if (loads && hist)
+    for (int e = tid; e < p.E; e += kPlanThreads) hist[e] = 0;
+  for (int i = tid; i < k.tokens * k.words; i += kPlanThreads) sh.dest_bytes[i] = sh.other_bytes[i] = ~0ull;
+  sh.same_dest[wv][lane] = 0;
+  if (tid < kWave) {
+    sh.rank_cnt[tid] = sh.node_cnt[tid] = sh.all_tot[tid] = sh.all_pre[tid] = 0;
+    sh.gave_up = 0;
+  }
+  if (own_status) wait_for_own_stores();   // status and cleared loads: out before anything adds to them
+  __syncthreads();
+
+  // ranks and nodes of the workgroup's tokens into LDS: this lane's slot, then its halo slot
+  const int shift = p.level == HM_DEDUP_NODE && !p.dest_map ? 8 : 0;
+  me.tok = token_of(p, k, me.s, me.place);
+  me.entry = entry_of(p, table, me.id);
+  me.dest = (int)(me.entry >> shift & 0xFFu);
+  me.has_dest = me.entry < (kNoCopy & 0xFF00u);
+  if (!COUNT_ONLY) sh.weight[tid] = me.w;
+  if (loads && me.has_dest && hist) atomicAdd(&hist[me.id], 1);
+  {
+    int tok = me.tok, place = me.place, dest = me.dest;
+    uint32_t entry = me.entry;
+    bool in = me.live;
+#pragma unroll 1
+    for (int pass = 0;; ++pass) {
+      if (in && entry < (kNoCopy & 0xFF00u)) {
+        const int at = tok * k.words * 8 + place;
+        ((uint8_t *)sh.dest_bytes)[at] = (uint8_t)dest;
+        if (tokens) ((uint8_t *)sh.other_bytes)[at] = (uint8_t)(entry >> (8 - shift));
+      }
+      if (!halo || pass) break;
+      in = s2 >= 0;
+      tok = token_of(p, k, in ? s2 : me.s, place);
+      entry = entry_of(p, table, id2);
+      dest = (int)(entry >> shift & 0xFFu);
+      if (!COUNT_ONLY && in && s2 > me.s) sh.weight[s2 - k.first_slot] = w2;   // behind the workgroup's own
+    }
+  }
+  __syncthreads();
+
+  // A slot owns its (token, destination) row at level none always, else iff no earlier slot of the token
+  // has the same destination: the OR over a group's experts in Eq.(7) leaves one copy per group, and
+  // the lowest k keeps it.
+  me.other = (int)(me.entry >> (8 - shift) & 0xFFu);
+  me.first = me.has_dest;
+  if (p.level != HM_DEDUP_NONE || loads) me.first = me.first && first_in_token(sh.dest_bytes, k, me.tok, me.place, me.dest);
+  me.keep = p.level != HM_DEDUP_NONE ? me.first : me.has_dest;
+  // LDS operations of one wave are carried out in order: no barrier up to the counts
+  if (me.keep) atomicOr(&sh.same_dest[wv][me.dest], 1ull << lane);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // for the compiler: no instruction
+  const uint64_t peers = sh.same_dest[wv][me.dest & (kWave - 1)];
+  me.pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0));
+  ((uint8_t *)sh.wave_cnt)[lane * kPlanWaves + wv] = (uint8_t)__popcll(sh.same_dest[wv][lane]);
+  __syncthreads();
+  return me;
+}
+
+// Rows that the waves of the workgroup own at destination `lane`: all of them, and those of the waves before wv.
+__device__ __forceinline__ int byte_sum(uint32_t v, int sum) { return (int)__builtin_amdgcn_sad_u8(v, 0u, (uint32_t)sum); }
+__device__ __forceinline__ int rows_of_block(const PlanShared &sh, int wv, int &before) {
+  const u32x4 c = *(const u32x4 *)sh.wave_cnt[lane_id()];
+  int all = 0;
+  before = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int n = wv - 4 * i;   // waves of this word that come before
+    all = byte_sum(c[i], all);
+    before = byte_sum(n >= 4 ? c[i] : n <= 0 ? 0u : c[i] & ~(~0u << (8 * n)), before);
+  }
+  return all;
+}
+
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ int lane_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // from the lane one below, within rows of sixteen
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of a row to the next one, rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2 and 3
+  return v;
+}
+
+// The LDS behind PlanShared, if the tables are staged: [hist: E int32 if the load arrays are asked for][table: E + 1 uint16].
+extern __shared__ int32_t plan_dyn_lds[];
+
+__global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void plan_count_kernel(PlanParams p, int staged) {
+  __shared__ PlanShared sh;
   const Tokens k = tokens_of_block(p);
-  const int s = k.first_slot + (int)threadIdx.x, s2 = halo_slot(p, k);
-  const bool live = s < p.nslots;
-  const int id = live ? p.ids[s] : -1, id2 = s2 >= 0 ? p.ids[s2] : -1;
-  for (int i = threadIdx.x; i < k.tokens * k.words; i += kPlanThreads) dest_bytes[i] = ~0ull;
-  if (threadIdx.x < kWave) cnt[threadIdx.x] = 0;
-  int dest = lookup_global(p, id), dest2 = lookup_global(p, id2);
-  if (p.level == HM_DEDUP_NODE && !p.dest_map) {
-    dest = dest >= 0 ? node_of(p, dest) : dest;
-    dest2 = dest2 >= 0 ? node_of(p, dest2) : dest2;
+  plan_slots<true>(p, sh, k, nullptr, staged ? (uint16_t *)plan_dyn_lds : nullptr, blockIdx.x == 0);
+  if ((int)threadIdx.x < p.Dn) {
+    int before;
+    p.counts[(int64_t)blockIdx.x * p.Dn + threadIdx.x] = rows_of_block(sh, 0, before);
   }
-  __syncthreads();
-  int place = 0, place2 = 0;
-  const int t = live ? token_of(p, k, s, place) : 0;
-  uint8_t *const bytes = (uint8_t *)dest_bytes;
-  if (live && dest >= 0) bytes[t * k.words * 8 + place] = (uint8_t)dest;
-  if (s2 >= 0 && dest2 >= 0) {
-    const int t2 = token_of(p, k, s2, place2);
-    bytes[t2 * k.words * 8 + place2] = (uint8_t)dest2;
-  }
-  __syncthreads();
-  const bool keep = live && dest >= 0 && (p.level == HM_DEDUP_NONE || first_with(dest_bytes + t * k.words, place, dest));
-  const uint64_t peers = peers_of(dest, keep, p.Dn);
-  if (keep && (peers & ((1ull << lane_id()) - 1ull)) == 0) atomicAdd(&cnt[dest], __popcll(peers));
-  __syncthreads();
-  if ((int)threadIdx.x < p.Dn) p.counts[(int64_t)blockIdx.x * p.Dn + threadIdx.x] = cnt[threadIdx.x];
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p.status = 0;
   if (p.load_expert) {   // the write kernel accumulates into these with atomics
     const int64_t stride = (int64_t)gridDim.x * kPlanThreads;
     for (int64_t i = (int64_t)blockIdx.x * kPlanThreads + threadIdx.x; i < p.E; i += stride) p.load_expert[i] = 0;
@@ -225,20 +374,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_scan_kernel(PlanParams p) {
 }
 
 // ---- one-launch plan ---------------------------------------------------------------------------
-// Words that another workgroup of the same launch reads or writes are accessed with device-scope
-// atomic loads and stores (the workgroups sit on different dies with caches of their own).
-__device__ __forceinline__ void st_device(int32_t *a, int32_t v) {
-  __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t ld_device(const uint64_t *a) {
-  return __hip_atomic_load(a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_device(uint64_t *a, uint64_t v) {
-  __hip_atomic_store(a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// The calling wave's earlier device-scope stores have been acknowledged when this returns.
-__device__ __forceinline__ void wait_for_own_stores() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 constexpr int kTagShift = 11;   // a workgroup keeps at most 1024 slots per destination: the count takes 11 bits
 
 // The grid-wide step without a separate barrier: a workgroup publishes its per-destination
@@ -251,307 +386,177 @@ constexpr int kTagShift = 11;   // a workgroup keeps at most 1024 slots per dest
 // Every wait is bounded by kPlanSpinLimit polls; a wave that gives up makes the workgroup skip
 // its writes, flags HM_ERR_HIP and exits.
 //
-// The kernel is a chain of dependent memory round trips, so it is ordered to keep that chain
-// short: the expert -> rank table is staged in LDS while the ids are in flight (no dependent
-// lookup, and the division by ranks_per_node is done once per expert, not per slot), the halo
-// slots are fetched in the same round as the workgroup's own, and everything that does not need
-// the other workgroups' counts -- slot_keep, the masks, the LDS partials of the load counts --
-// is done while the counts are on their way.
+// The chain of dependent memory trips is kept short: the expert -> rank table is staged in LDS while the ids are
+// in flight (no dependent lookup), the halo slots are fetched in the same round as the workgroup's own, and what needs no
+// other workgroup's counts -- slot_keep, the masks -- is stored while the counts are on their way.
+//
+// `clean` is set for launches that are captured: a replay carries the same tag, so workgroup 0 waits until all have
+// read the matrix (passed) and zeroes both.  A tag that is used once needs no such end, which is a trip to memory
+// and back longer than the kernel otherwise is.
 enum class PlanMode { kAlone, kFused, kWrite };   // the only workgroup; one launch of several; counts already there
 
 template <PlanMode MODE>
-__device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix, uint64_t *passed, uint64_t tag,
-                                          int staged_table) {
+__device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix, uint64_t *passed, uint64_t tag, int staged,
+                                          int clean) {
   constexpr bool ALONE = MODE == PlanMode::kAlone, FUSED = MODE == PlanMode::kFused;
-  __shared__ uint64_t rank_bytes[kPlanTokenWords];
-  __shared__ uint64_t node_bytes[kPlanTokenWords];
-  __shared__ unsigned long long token_ranks[kPlanThreads];   // per token: the rank mask
-  __shared__ float s_weight[kPlanThreads + kPlanHalo];
-  __shared__ uint16_t wave_cnt[kPlanWaves][kWave];
-  __shared__ uint16_t wave_base[kPlanWaves][kWave];
-  __shared__ int32_t all_tot[kWave], all_pre[kWave];   // per destination: rows of the plan, of the workgroups before
-  __shared__ int32_t block_base[kWave];
-  __shared__ int32_t blk_rank[kWave], blk_node[kWave];
-  __shared__ int32_t gave_up, error;
-  extern __shared__ int32_t dyn_lds[];   // if staged_table: [hist: E int32 if the load arrays are asked for][rank: E int8][node: E int8]
-  const int lane = lane_id(), wv = (int)(threadIdx.x >> 6);
+  __shared__ PlanShared sh;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), tid = (int)threadIdx.x;
   const int bid = (int)blockIdx.x;
-  const bool loads = p.load_expert != nullptr, masks = p.rank_mask || p.node_mask;
-  int32_t *hist = dyn_lds;
-  int8_t *s_map = (int8_t *)(dyn_lds + (loads ? p.E : 0));
-  int8_t *s_nmap = s_map + p.E;
+  const bool loads = p.load_expert != nullptr;
+  int32_t *const hist = staged && loads ? plan_dyn_lds : nullptr;
+  uint16_t *const table = staged ? (uint16_t *)(plan_dyn_lds + (loads ? p.E : 0)) : nullptr;
   const Tokens k = tokens_of_block(p);
-
-  // ---- phase 1a: everything that comes from memory, issued in one round
-  const int s = k.first_slot + (int)threadIdx.x, s2 = halo_slot(p, k);
-  const bool live = s < p.nslots;
-  int id = -1, id2 = -1;
-  float w = 0.0f, w2 = 0.0f;
-  if (live) {
-    id = p.ids[s];
-    w = p.weights[s];
+  if (FUSED && bid == 0 && loads) {   // what the atomics of the other workgroups add to: out before this workgroup's counts are
+    for (int i = tid; i < p.E; i += kPlanThreads) st_device(p.load_expert + i, 0);
+    if (tid < p.G) st_device(p.load_rank + tid, 0);
+    if (tid < p.N) st_device(p.load_node + tid, 0);
   }
-  if (s2 >= 0) {
-    id2 = p.ids[s2];
-    w2 = p.weights[s2];
-  }
-  if (staged_table) {
-    for (int e = threadIdx.x; e < p.E; e += kPlanThreads) {
-      int v, n = -1;
-      if (p.dest_map) {
-        const int m = p.dest_map[e];
-        v = (m >= 0 && m < p.Dn) ? m : (m == -1 ? -2 : -1);
-      } else {
-        const int g = p.expert_to_rank[e];
-        v = ((unsigned)g >= (unsigned)p.G) ? -1 : g;
-        if (v >= 0) n = node_of(p, v);
-      }
-      s_map[e] = (int8_t)v;
-      s_nmap[e] = (int8_t)n;
-    }
-    if (loads)
-      for (int e = threadIdx.x; e < p.E; e += kPlanThreads) hist[e] = 0;
-  }
-  for (int i = threadIdx.x; i < k.tokens * k.words; i += kPlanThreads) rank_bytes[i] = node_bytes[i] = ~0ull;
-  token_ranks[threadIdx.x] = 0;
-  wave_cnt[wv][lane] = 0;
-  if (threadIdx.x < kWave) blk_rank[threadIdx.x] = blk_node[threadIdx.x] = all_tot[threadIdx.x] = all_pre[threadIdx.x] = 0;
-  if (threadIdx.x == 0) gave_up = error = 0;
-  if (FUSED && bid == 0) {   // what the atomics of the other workgroups add to: out before this workgroup's counts are
-    if (threadIdx.x == 0) st_device(p.status, 0);
-    if (loads) {
-      for (int i = threadIdx.x; i < p.E; i += kPlanThreads) st_device(p.load_expert + i, 0);
-      if ((int)threadIdx.x < p.G) st_device(p.load_rank + threadIdx.x, 0);
-      if ((int)threadIdx.x < p.N) st_device(p.load_node + threadIdx.x, 0);
-    }
-    wait_for_own_stores();
-  }
-  __syncthreads();
-
-  // ---- phase 1b: ranks and nodes of the workgroup's tokens into LDS
-  int rank = -1, node = -1, place = 0, tok = 0;
-  {
-    uint8_t *const rb = (uint8_t *)rank_bytes, *const nb = (uint8_t *)node_bytes;
-    auto find = [&](int i, int &r, int &n) {
-      if (staged_table) {
-        r = lookup_staged(p, s_map, i);
-        if (r >= 0) n = s_nmap[i];
-      } else {
-        r = lookup_global(p, i);
-        if (r >= 0 && !p.dest_map) n = node_of(p, r);
-      }
-    };
-    auto put = [&](int t, int at, int r, int n) {
-      if (r < 0) return;
-      rb[t * k.words * 8 + at] = (uint8_t)r;
-      if (masks) atomicOr(&token_ranks[t], 1ull << r);
-      if (n >= 0) nb[t * k.words * 8 + at] = (uint8_t)n;
-    };
-    if (live) {
-      find(id, rank, node);
-      tok = token_of(p, k, s, place);
-      put(tok, place, rank, node);
-    }
-    s_weight[threadIdx.x] = w;
-    if (s2 >= 0) {
-      int r2 = -1, n2 = -1, place2;
-      find(id2, r2, n2);
-      const int t2 = token_of(p, k, s2, place2);
-      put(t2, place2, r2, n2);
-      if (s2 > s) s_weight[s2 - k.first_slot] = w2;   // behind the workgroup's own
-    }
-  }
-  __syncthreads();
-  const bool by_node = p.level == HM_DEDUP_NODE && !p.dest_map;
-  const int dest = rank < 0 ? -1 : by_node ? node : rank;
-  const uint64_t *const my_ranks = rank_bytes + tok * k.words, *const my_nodes = node_bytes + tok * k.words;
-  const uint64_t *const my_dests = by_node ? my_nodes : my_ranks;
-  // A slot owns its (token, destination) row at level none always, else iff no earlier slot of the token
-  // has the same destination: the OR over a group's experts in Eq.(7) leaves one copy per group, and
-  // the lowest k keeps it.
-  const bool dedup = p.level != HM_DEDUP_NONE;
-  const bool first_dest = (dedup || loads) && dest >= 0 && first_with(my_dests, place, dest);
-  const bool keep = dest >= 0 && (!dedup || first_dest);
-  const uint64_t peers = peers_of(dest, keep, p.Dn);
-  const int pos = __popcll(peers & ((1ull << lane) - 1ull));
-  if (keep && pos == 0) wave_cnt[wv][dest] = (uint16_t)__popcll(peers);
-  if (loads && rank >= 0) {
-    // the first slot of a token with a rank / a node counts the token there: the duplicate-free loads of
-    // hm_expert_load, as LDS partials
-    const bool first_rank = by_node ? first_with(my_ranks, place, rank) : first_dest;
-    const bool first_node = by_node ? first_dest : first_with(my_nodes, place, node);
-    if (first_rank) atomicAdd(&blk_rank[rank], 1);
-    if (first_node) atomicAdd(&blk_node[node], 1);
-    if (staged_table) atomicAdd(&hist[id], 1);   // slots per expert
-  }
-  __syncthreads();
-  if (lane < p.Dn) {
-    int a = 0, all = 0;
-#pragma unroll
-    for (int w1 = 0; w1 < kPlanWaves; ++w1) {
-      const int c = wave_cnt[w1][lane];
-      a += w1 < wv ? c : 0;
-      all += c;
-    }
-    wave_base[wv][lane] = (uint16_t)a;
-    if (FUSED && wv == 0) st_device(matrix + (int64_t)bid * p.Dn + lane, (tag << kTagShift) | (uint64_t)all);
-    if (ALONE && wv == 0) all_tot[lane] = all;
-  }
+  const Slot me = plan_slots<false>(p, sh, k, hist, table, !(MODE == PlanMode::kWrite) && bid == 0);
+  int before;
+  const int rows = rows_of_block(sh, wv, before);   // lane: destination
+  if (FUSED && wv == 0 && lane < p.Dn) st_device(matrix + (int64_t)bid * p.Dn + lane, (tag << kTagShift) | (uint64_t)rows);
 
   // ---- while the counts travel: what needs no other workgroup
-  if (live) {
-    if (dest < 0) p.slot_row[s] = -1;
-    p.slot_keep[s] = keep ? 1 : 0;
+  if (me.live) {
+    if (!me.has_dest) p.slot_row[me.s] = -1;
+    p.slot_keep[me.s] = me.keep ? 1 : 0;
   }
-  if (masks && (int)threadIdx.x < k.tokens) {   // the masks of the tokens whose first slot is this workgroup's
-    const int t = k.first_token + (int)threadIdx.x;
+  if (tid < k.tokens) {   // the masks of the tokens whose first slot is this workgroup's
+    const int t = k.first_token + tid;
     if (t * p.K >= k.first_slot) {
-      const uint64_t ranks = token_ranks[threadIdx.x];
-      if (p.rank_mask) p.rank_mask[t] = ranks;
-      if (p.node_mask) {   // a node's bit from the bits of its ranks, which are neighbours
-        const uint64_t field = p.R >= 64 ? ~0ull : (1ull << p.R) - 1ull;
-        uint32_t nodes = 0;
-        if (!p.dest_map)
-          for (int n = 0; n < p.N; ++n) nodes |= ((ranks >> (n * p.R)) & field) ? 1u << n : 0u;
-        p.node_mask[t] = nodes;
-      }
+      const bool by_node = p.level == HM_DEDUP_NODE && !p.dest_map;
+      const uint64_t *const ranks = by_node ? sh.other_bytes : sh.dest_bytes, *const nodes = by_node ? sh.dest_bytes : sh.other_bytes;
+      if (p.rank_mask) p.rank_mask[t] = mask_of_token<uint64_t>(ranks, k, p.K, tid);
+      if (p.node_mask) p.node_mask[t] = p.dest_map ? 0u : mask_of_token<uint32_t>(nodes, k, p.K, tid);
     }
+  }
+  // The duplicate-free loads of hm_expert_load: the first slot of a token with a rank or a node counts it there.  Where
+  // rows are per rank (node) their counts are those of the ranks (nodes) already.
+  if (loads && me.has_dest) {
+    if (first_in_token(sh.other_bytes, k, me.tok, me.place, me.other))
+      atomicAdd(p.level == HM_DEDUP_NODE ? &sh.rank_cnt[me.other] : &sh.node_cnt[me.other], 1);
+    if (p.level == HM_DEDUP_NONE && me.first) atomicAdd(&sh.rank_cnt[me.dest], 1);
   }
 
-  // ---- the count matrix: wave wv reads rows wv, wv+16, ..., lane = destination
-  if (FUSED) {   // ... and reads them again, as a whole wave, until every word carries this launch's tag
-    int tot = 0, pre = 0;
-    bool ready = false;
-    for (int spin = 0; spin < kPlanSpinLimit; ++spin) {
-      tot = pre = 0;
-      bool mine = true;
-      if (lane < p.Dn) {
-        for (int b0 = wv; b0 < p.nblocks; b0 += 4 * kPlanWaves) {   // four rows in flight
-          uint64_t v[4];
+  // ---- rows of all workgroups and of those before this one, per destination
+  int tot = rows, pre = 0;
+  if (!ALONE) {
+    tot = 0;
+    bool ready = true;
+    if (FUSED) {   // wave wv reads rows wv, wv + 16, ..., again as a whole wave until every word carries this launch's tag
+      for (int spin = 0; spin < kPlanSpinLimit; ++spin) {
+        tot = pre = 0;
+        bool mine = true;
+        if (lane < p.Dn) {
+          for (int b0 = wv; b0 < p.nblocks; b0 += 4 * kPlanWaves) {   // four rows in flight
+            uint64_t v[4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int b = b0 + j * kPlanWaves;
-            v[j] = b < p.nblocks ? ld_device(matrix + (int64_t)b * p.Dn + lane) : (tag << kTagShift);
+            for (int j = 0; j < 4; ++j) {
+              const int b = b0 + j * kPlanWaves;
+              v[j] = b < p.nblocks ? ld_device(matrix + (int64_t)b * p.Dn + lane) : (tag << kTagShift);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              mine = mine && (v[j] >> kTagShift) == tag;
+              const int c = (int)(v[j] & ((1u << kTagShift) - 1u));
+              tot += c;
+              if (b0 + j * kPlanWaves < bid) pre += c;
+            }
           }
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            mine = mine && (v[j] >> kTagShift) == tag;
-            const int c = (int)(v[j] & ((1u << kTagShift) - 1u));
-            tot += c;
-            if (b0 + j * kPlanWaves < bid) pre += c;
-          }
         }
+        ready = __ballot(!mine) == 0ull;
+        if (ready) break;
+        __builtin_amdgcn_s_sleep(2);
       }
-      ready = __ballot(!mine) == 0ull;
-      if (ready) break;
-      __builtin_amdgcn_s_sleep(2);
-    }
-    if (tot) atomicAdd(&all_tot[lane], tot);
-    if (pre) atomicAdd(&all_pre[lane], pre);
-    if (!ready && lane == 0) gave_up = 1;
-  } else if (!ALONE) {   // an earlier launch left the counts (or, scanned, their prefixes and a row of totals) in p.counts
-    int tot = 0, pre = 0;
-    if (p.scanned) {
-      if (wv == 0 && lane < p.Dn) {
-        tot = p.counts[(int64_t)p.nblocks * p.Dn + lane];
-        pre = p.counts[(int64_t)bid * p.Dn + lane];
-      }
-    } else if (lane < p.Dn) {
-      for (int b0 = wv; b0 < p.nblocks; b0 += 8 * kPlanWaves) {   // eight rows in flight
-        int c[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int b = b0 + j * kPlanWaves;
-          c[j] = b < p.nblocks ? p.counts[(int64_t)b * p.Dn + lane] : 0;
+    } else if (lane < p.Dn) {   // an earlier launch left the counts (or, scanned, their prefixes and a row of totals)
+      if (p.scanned) {
+        if (wv == 0) {
+          tot = p.counts[(int64_t)p.nblocks * p.Dn + lane];
+          pre = p.counts[(int64_t)bid * p.Dn + lane];
         }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          tot += c[j];
-          if (b0 + j * kPlanWaves < bid) pre += c[j];
-        }
-      }
-    }
-    if (tot) atomicAdd(&all_tot[lane], tot);
-    if (pre) atomicAdd(&all_pre[lane], pre);
-  }
-  if (!ALONE) __syncthreads();
-  const bool go = gave_up == 0;   // uniform over the workgroup
-  if (go) {
-    if (FUSED && threadIdx.x == 0) st_device(passed + bid, tag);
-    if (loads) {   // global atomics first: they complete in the shadow of the map stores
-      const int nodes = p.N;
-      if (ALONE && staged_table) {
-        for (int e = threadIdx.x; e < p.E; e += kPlanThreads) p.load_expert[e] = hist[e];
-      } else if (staged_table) {
-        for (int e = threadIdx.x; e < p.E; e += kPlanThreads)
-          if (hist[e]) atomicAdd(&p.load_expert[e], hist[e]);
-      } else if (rank >= 0) {
-        atomicAdd(&p.load_expert[id], 1);
-      }
-      if (ALONE) {
-        if ((int)threadIdx.x < p.G) p.load_rank[threadIdx.x] = blk_rank[threadIdx.x];
-        if ((int)threadIdx.x < nodes) p.load_node[threadIdx.x] = blk_node[threadIdx.x];
       } else {
-        if ((int)threadIdx.x < p.G && blk_rank[threadIdx.x]) atomicAdd(&p.load_rank[threadIdx.x], blk_rank[threadIdx.x]);
-        if ((int)threadIdx.x < nodes && blk_node[threadIdx.x]) atomicAdd(&p.load_node[threadIdx.x], blk_node[threadIdx.x]);
+        for (int b0 = wv; b0 < p.nblocks; b0 += 8 * kPlanWaves) {   // eight rows in flight
+          int c[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int b = b0 + j * kPlanWaves;
+            c[j] = b < p.nblocks ? p.counts[(int64_t)b * p.Dn + lane] : 0;
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            tot += c[j];
+            if (b0 + j * kPlanWaves < bid) pre += c[j];
+          }
+        }
       }
     }
-    if (live && rank == -1) {
-      if (ALONE) atomicMin(&error, HM_ERR_BAD_ID);
-      else flag(p.status, HM_ERR_BAD_ID);
-    }
-    if (wv == 0) {
-      const int tot = all_tot[lane], pre = all_pre[lane];
-      int incl = tot;  // inclusive scan over destinations (lanes >= Dn hold 0)
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int v = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += v;
+    if (tot) atomicAdd(&sh.all_tot[lane], tot);
+    if (pre) atomicAdd(&sh.all_pre[lane], pre);
+    if (!ready && lane == 0) sh.gave_up = 1;
+    __syncthreads();
+    tot = sh.all_tot[lane];
+    pre = sh.all_pre[lane];
+  }
+  const bool go = ALONE || sh.gave_up == 0;   // uniform over the workgroup
+  if (go) {
+    if (FUSED && clean && tid == 0) st_device(passed + bid, tag);
+    if (loads) {   // global atomics first: they complete in the shadow of the map stores
+      for (int e = tid; hist && e < p.E; e += kPlanThreads) {
+        if (ALONE) p.load_expert[e] = hist[e];
+        else if (hist[e]) atomicAdd(&p.load_expert[e], hist[e]);
       }
-      const int offset = incl - tot;
-      block_base[lane] = offset + pre;
-      if (bid == 0 && lane < p.Dn) {
-        p.dest_count[lane] = tot;
-        p.dest_offset[lane] = offset;
-        if (lane == p.Dn - 1) p.dest_offset[p.Dn] = incl;
+      if (!hist && me.has_dest) atomicAdd(&p.load_expert[me.id], 1);
+      if (!ALONE && tid < kWave) {
+        const int r = p.level == HM_DEDUP_GPU ? rows : sh.rank_cnt[tid], n = p.level == HM_DEDUP_NODE ? rows : sh.node_cnt[tid];
+        if (r) atomicAdd(&p.load_rank[tid], r);
+        if (n) atomicAdd(&p.load_node[tid], n);
       }
     }
-  } else if (threadIdx.x == 0) {
+    if (me.entry == kBadEntry && me.live) flag(p.status, HM_ERR_BAD_ID);
+
+    // ---- rows: the slot that owns a row numbers it and serves the later slots that share it
+    const int incl = lane_scan(tot), offset = incl - tot;   // over the destinations (lanes from Dn on hold 0)
+    if (bid == 0 && wv == 0 && lane < p.Dn) {
+      p.dest_count[lane] = tot;
+      p.dest_offset[lane] = offset;
+      if (lane == p.Dn - 1) p.dest_offset[p.Dn] = incl;
+    }
+    const int row = __shfl(offset + pre + before, me.dest & (kWave - 1), kWave) + me.pos;
+    if (me.keep) {
+      p.slot_row[me.s] = row;
+      float wsum = me.w;
+      if (p.level != HM_DEDUP_NONE) {
+        const uint64_t *const token = sh.dest_bytes + me.tok * k.words;
+        const uint64_t same = repeated(me.dest);
+        uint64_t later = ~0xFFull << (8 * (me.place & 7));   // the bytes behind mine
+#pragma unroll 1
+        for (int wd = me.place >> 3; wd < k.words; ++wd, later = ~0ull) {
+#pragma unroll 1
+          for (uint64_t m = equal_bytes(token[wd], same) & later; m; m &= m - 1) {
+            const int ahead = wd * 8 + (__builtin_ctzll(m) >> 3) - me.place;
+            p.slot_row[me.s + ahead] = row;
+            wsum = wsum + sh.weight[tid + ahead];  // ascending k, fp32
+          }
+        }
+      }
+      if (row < p.row_capacity) {
+        p.row_token[row] = k.first_token + me.tok;
+        p.row_weight[row] = wsum;
+      } else {
+        flag(p.status, HM_ERR_CAPACITY);
+      }
+    }
+  } else if (tid == 0) {
     flag(p.status, HM_ERR_HIP);
   }
-  __syncthreads();
-
-  // ---- rows: the slot that owns a row numbers it and serves the later slots that share it
-  if (go && keep) {
-    const int row = block_base[dest] + wave_base[wv][dest] + pos;
-    p.slot_row[s] = row;
-    float wsum = w;
-    if (dedup) {
-      const uint64_t same = repeated(dest);
-      uint64_t later = ~((2ull << (8 * (place & 7) + 7)) - 1ull);   // the bytes behind mine
-      for (int wd = place >> 3; wd < k.words; ++wd, later = ~0ull) {
-        for (uint64_t m = equal_bytes(my_dests[wd], same) & later; m; m &= m - 1) {
-          const int ahead = wd * 8 + (__builtin_ctzll(m) >> 3) - place;
-          p.slot_row[s + ahead] = row;
-          wsum = wsum + s_weight[(int)threadIdx.x + ahead];  // ascending k, fp32
-        }
-      }
-    }
-    if (row < p.row_capacity) {
-      p.row_token[row] = k.first_token + tok;
-      p.row_weight[row] = wsum;
-    } else if (ALONE) {
-      atomicMin(&error, HM_ERR_CAPACITY);
-    } else {
-      flag(p.status, HM_ERR_CAPACITY);
-    }
-  }
-  if (ALONE) {
+  if (ALONE && loads) {   // the other modes have had a barrier since the tokens were counted
     __syncthreads();
-    if (threadIdx.x == 0) *p.status = error;
+    if (tid < p.G) p.load_rank[tid] = p.level == HM_DEDUP_GPU ? rows : sh.rank_cnt[tid];
+    if (tid < p.N) p.load_node[tid] = p.level == HM_DEDUP_NODE ? rows : sh.node_cnt[tid];
   }
 
   // ---- workgroup 0 leaves matrix and flags clean (also when a wait gave up: the status word says so)
-  if (FUSED && bid == 0) {
+  if (FUSED && clean && bid == 0) {
     if (wv == 0 && go) {
       bool ok = true;
       for (int spin = 0; spin < kPlanSpinLimit; ++spin) {
@@ -563,22 +568,21 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
       if (__ballot(!ok) != 0ull && lane == 0) flag(p.status, HM_ERR_HIP);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < p.nblocks * p.Dn; i += kPlanThreads) st_device(matrix + i, 0ull);
-    for (int b = threadIdx.x; b < p.nblocks; b += kPlanThreads) st_device(passed + b, 0ull);
+    for (int i = tid; i < p.nblocks * p.Dn; i += kPlanThreads) st_device(matrix + i, 0ull);
+    for (int b = tid; b < p.nblocks; b += kPlanThreads) st_device(passed + b, 0ull);
   }
 }
 
 // The one-launch plan.  It runs one workgroup per CU at the sizes it is used for, so it takes the
 // scalar registers the compiler wants (106: the many pointers of PlanParams).
 __global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(PlanParams p, uint64_t *matrix, uint64_t *passed,
-                                                                  uint64_t tag, int staged_table) {
-  plan_body<PlanMode::kFused>(p, matrix, passed, tag, staged_table);
+                                                                  uint64_t tag, int staged, int clean) {
+  plan_body<PlanMode::kFused>(p, matrix, passed, tag, staged, clean);
 }
 
-// A plan of one workgroup: nothing to wait for, nothing to clear, no atomics outside LDS (except for
-// expert tables too large for it).
+// A plan of one workgroup: nothing to wait for, nothing to clear, no atomics outside LDS.
 __global__ __launch_bounds__(kPlanThreads) void plan_alone_kernel(PlanParams p) {
-  plan_body<PlanMode::kAlone>(p, nullptr, nullptr, 0, 1);
+  plan_body<PlanMode::kAlone>(p, nullptr, nullptr, 0, 1, 0);
 }
 
 // The last launch of a large plan: the same body without the grid-wide wait.  Held to 96 scalar
@@ -586,8 +590,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_alone_kernel(PlanParams p) 
 // 64 Ki-token layer run in one round (thirty-odd scalars then live in vector lanes, which is
 // cheaper than a second round).
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void plan_write_kernel(PlanParams p,
-                                                                                                      int staged_table) {
-  plan_body<PlanMode::kWrite>(p, nullptr, nullptr, 0, staged_table);
+                                                                                                      int staged) {
+  plan_body<PlanMode::kWrite>(p, nullptr, nullptr, 0, staged, 0);
 }
 
 // Table of one hop for a (parent, child) pair of group cuts: purely elementwise.
@@ -680,7 +684,7 @@ static inline int fused_capacity() {
     v = -1;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, plan_fused_kernel, kPlanThreads,
-                                                     kPlanStagedExperts * 6) == hipSuccess &&
+                                                     kPlanStagedExperts * 6 + 16) == hipSuccess &&
         cus > 0 && per_cu > 0)
       v = cus * per_cu;
     cached[dev].store(v, std::memory_order_relaxed);
@@ -704,6 +708,14 @@ static inline uint64_t next_tag() {
   return e;
 }
 
+// Whether launches on the stream go into a graph; also when that cannot be told.
+static inline int is_captured(hipStream_t stream) {
+  hipStreamCaptureStatus now = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &now) == hipSuccess) return now != hipStreamCaptureStatusNone ? 1 : 0;
+  if (hipPeekAtLastError() != hm_pending_at_entry) (void)hipGetLastError();   // not a failed launch
+  return 1;
+}
+
 // Largest plan, in workgroups, that takes the one-launch kernel (hm_plan_one_launch_limit).
 static std::atomic<int> one_launch_limit{kPlanFusedMaxBlocks};
 
@@ -716,7 +728,8 @@ static inline hm_status launch_plan(PlanParams &p, hipStream_t stream) {
   p.k_recip22 = ((1u << 22) + (uint32_t)p.K - 1u) / (uint32_t)p.K;
   p.r_recip16 = (65536u + (uint32_t)p.R - 1u) / (uint32_t)p.R;
   const int staged = p.E <= kPlanStagedExperts ? 1 : 0;   // tables (and histogram) in LDS
-  const unsigned lds = staged ? ((loads ? (unsigned)p.E * sizeof(int32_t) : 0u) + ((2u * (unsigned)p.E + 15u) & ~15u)) : 0u;
+  const unsigned table_lds = staged ? (2u * ((unsigned)p.E + 1u) + 15u) & ~15u : 0u;
+  const unsigned lds = staged && loads ? (unsigned)p.E * sizeof(int32_t) + table_lds : table_lds;
   if (p.nblocks == 1 && staged) {
     hipLaunchKernelGGL(plan_alone_kernel, dim3(1), dim3(kPlanThreads), lds, stream, p);
     return hm_launch_status();
@@ -725,11 +738,11 @@ static inline hm_status launch_plan(PlanParams &p, hipStream_t stream) {
     p.scanned = 0;
     uint64_t *matrix = (uint64_t *)((char *)p.counts + plan_counts_bytes(p.nslots, p.Dn));
     hipLaunchKernelGGL(plan_fused_kernel, dim3(p.nblocks), dim3(kPlanThreads), lds, stream, p, matrix,
-                       matrix + (size_t)p.nblocks * p.Dn, next_tag(), staged);
+                       matrix + (size_t)p.nblocks * p.Dn, next_tag(), staged, is_captured(stream));
     return hm_launch_status();
   }
   p.scanned = (int64_t)p.nblocks * p.Dn >= kPlanScanMinEntries ? 1 : 0;
-  hipLaunchKernelGGL(plan_count_kernel, dim3(p.nblocks), dim3(kPlanThreads), 0, stream, p);
+  hipLaunchKernelGGL(plan_count_kernel, dim3(p.nblocks), dim3(kPlanThreads), table_lds, stream, p, staged);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
   if (p.scanned) {
     hipLaunchKernelGGL(plan_scan_kernel, dim3(p.Dn), dim3(kPlanThreads), 0, stream, p);

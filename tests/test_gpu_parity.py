@@ -859,6 +859,75 @@ def test_plan_does_not_depend_on_the_launch_path(hw, oracle):
     assert B.hm_plan_one_launch_limit(256) == 0
 
 
+@pytest.mark.parametrize("K", [1, 3, 7, 8, 9, 17, 64])
+def test_plan_slots_at_the_edges_of_workgroups(hw, oracle, K):
+    """Tokens that straddle workgroups of 1,024 slots and words of eight, repeated, dropped and invalid ids, placements
+    with invalid entries, tables in LDS and too large for it: every field through each kind of launch."""
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(1000 + K)
+    per = 1024 // K
+    try:
+        for limit in (256, 0):
+            B.hm_plan_one_launch_limit(limit)
+            for case, (T, E, nodes, rpn) in enumerate([(per, 5, 1, 4), (per + 1, 300, 4, 8), (3 * per + 2, 4200, 8, 8), (2 * per - 1, 40, 3, 5)]):
+                ids = rng.integers(0, E, (T, K), dtype=np.int32)
+                ids[rng.random((T, K)) < 0.1] = -1
+                w = (rng.random((T, K), dtype=np.float32) - np.float32(0.3))
+                e2r = rng.integers(0, nodes * rpn, E).astype(np.int32)
+                if case % 2:
+                    ids[rng.integers(0, T), rng.integers(0, K)] = E + (0 if case == 1 else 2 ** 30)
+                    e2r[rng.integers(0, E)] = nodes * rpn
+                loads = oracle.expert_load(ids, e2r, nodes, rpn)[:3]
+                for level in (NONE, GPU, NODE):
+                    ctx = "limit=%d T=%d K=%d E=%d %dx%d level=%s" % (limit, T, K, E, nodes, rpn, LEVEL[level])
+                    g = hw.GpuPlan(ids, w, e2r, nodes, rpn, level, loads=True)
+                    hw.assert_plan_equal(g, oracle.plan(ids, w, e2r, nodes, rpn, level), ctx)
+                    h = g.host()
+                    for name, want in zip(("load_expert", "load_rank", "load_node"), loads):
+                        assert np.array_equal(h[name], want), (ctx, name)
+    finally:
+        B.hm_plan_one_launch_limit(256)
+
+
+def test_captured_and_eager_plans_share_a_workspace(hw, oracle):
+    """A captured plan is replayed with the same launch tag and leaves its scratch clean; an eager one does not need to.
+    Replays in turn with eager plans of another size on the same workspace, every one compared."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(77)
+    K, E, nodes, rpn = 8, 64, 4, 8
+    make = lambda T: (rng.integers(0, E, (T, K), dtype=np.int32), rng.random((T, K), dtype=np.float32))
+    e2r = W.contiguous_placement(E, nodes * rpn)
+    e2r_d = hw.dev(e2r)
+    big, small = B.alloc_plan(3000, K, E, nodes, rpn, GPU, loads=True), B.alloc_plan(700, K, E, nodes, rpn, GPU, loads=True)
+    small.workspace = big.workspace
+    ids_d, w_d = hw.dev(make(3000)[0]), hw.dev(make(3000)[1])
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        B.hm_plan(ids_d, w_d, e2r_d, nodes, rpn, GPU, plan=big)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.hm_plan(ids_d, w_d, e2r_d, nodes, rpn, GPU, plan=big)
+    for i in range(6):
+        ids, w = make(3000)
+        ids_d.copy_(hw.dev(ids))
+        w_d.copy_(hw.dev(w))
+        graph.replay()
+        if i % 2:
+            graph.replay()
+        st, total = B.hm_plan_status(big)
+        ora = oracle.plan(ids, w, e2r, nodes, rpn, GPU)
+        assert st == 0 and total == ora.total_rows, i
+        assert np.array_equal(big.slot_row.cpu().numpy().reshape(3000, K), ora.slot_row), i
+        assert np.array_equal(big.load_expert.cpu().numpy(), oracle.expert_load(ids, e2r, nodes, rpn)[0]), i
+        ids, w = make(700)
+        B.hm_plan(hw.dev(ids), hw.dev(w), e2r_d, nodes, rpn, GPU, plan=small)
+        st, total = B.hm_plan_status(small)
+        ora = oracle.plan(ids, w, e2r, nodes, rpn, GPU)
+        assert st == 0 and total == ora.total_rows and np.array_equal(small.slot_row.cpu().numpy().reshape(700, K), ora.slot_row), i
+
+
 def test_random_shapes_against_the_oracle(hw, oracle):
     """Seeded sweep over shapes nobody picked by hand: topology, K, E, H (vector and element-wise
     paths), uneven placements, repeated experts, dropped and invalid slots, all three levels."""
