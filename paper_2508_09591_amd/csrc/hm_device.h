@@ -68,6 +68,107 @@ __device__ __forceinline__ int lanes_per_group(uint64_t mask, int n, int per) {
   return lane < n ? mine : 0;
 }
 
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ int lane_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // from the lane one below, within rows of sixteen
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of a row to the next one, rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2 and 3
+  return v;
+}
+
+// ---- counts by owners ----------------------------------------------------------------------------------
+// Counts of a routing table in one launch without cleared outputs: a workgroup owns a few outputs (seven groups, or
+// some experts), goes through all the tokens and stores its counts.  The workgroups read the same table, so this is for
+// tables of a few hundred KB; beyond that each should read a part of it once and add atomically to cleared outputs.
+// A round of 1,024 tokens, one per lane, is bound by issuing its instructions (sixteen waves on a CU, four cycles
+// each: 0.4 us for eight ids), so there are few per id.  More rounds in flight, or four ids per lane, gained nothing.
+constexpr int kOwnerThreads = 1024;   // = tokens of a round
+constexpr int kOwnerGroups = 7;       // groups of a workgroup: the bits of a byte, but for the one that marks an error
+constexpr int kOwnerExperts = 64;     // experts of a workgroup ...
+constexpr int kOwnerCopies = 4;       // ... each counted in four places, so that fewer lanes meet at one
+constexpr int kOwnerMaxE = 4096;      // experts whose groups fit the LDS table
+
+// count(id) for every id of this lane's tokens, eight lookups side by side, end() after the last of a token.  The next
+// eight are on their way meanwhile; prepare() runs while the first are.  Lanes without a token count ids of -1.
+template <typename PREPARE, typename COUNT, typename END>
+__device__ __forceinline__ void for_ids(const int32_t *__restrict__ ids, int T, int K, PREPARE prepare, COUNT count, END end) {
+  int t = (int)threadIdx.x, k0 = 0;
+  const int32_t *at = ids + (int64_t)t * K;
+  const int steps = (T + kOwnerThreads - 1) / kOwnerThreads * ((K + 7) >> 3);
+  int next[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) next[j] = -1;
+#pragma unroll 1
+  for (int step = -1; step < steps; ++step) {
+    int id[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) id[j] = next[j];
+    const int n = K - k0;   // ids of the token that are left
+    if (step >= 0) {
+      at += n > 8 ? 8 : (int64_t)kOwnerThreads * K - k0;
+      t += n > 8 ? 0 : kOwnerThreads;
+      k0 = n > 8 ? k0 + 8 : 0;
+    }
+    if (t < T) {
+      load_ids(at, K - k0, 0, next);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) next[j] = -1;
+    }
+    if (step < 0) {
+      prepare();
+      continue;
+    }
+    if (n >= 8) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) count(id[j]);
+    } else {   // an absent id would cost as much as any other
+#pragma unroll
+      for (int j = 0; j < 7; ++j) {
+        if (j >= n) break;
+        count(id[j]);
+      }
+    }
+    if (n <= 8) end();
+  }
+}
+
+// Tokens with a copy in groups [first, first + 7) of `per` ranks each -> cnt[0 .. 7) of the workgroup's LDS, valid after the
+// call for every lane; returns whether any id or placement is invalid.  The table holds one bit per group an expert
+// may be in, so a token's groups are the `or` of its entries; a lane keeps its counts as bytes (at most 255 rounds).
+__device__ __forceinline__ bool count_owned_groups(const int32_t *__restrict__ ids, const int32_t *__restrict__ expert_to_rank, int T, int K,
+                                                   int E, int G, int per, int first, uint8_t *table, int32_t *cnt) {
+  const uint32_t per_recip16 = (65536u + (uint32_t)per - 1u) / (uint32_t)per;   // exact for ranks (below 64)
+  uint32_t low = 0, high = 0, mask = 0;
+  for_ids(ids, T, K, [&] {   // entry 0 is that of id -1, E + 1 of ids out of range
+    for (int e = threadIdx.x; e < E + 2; e += kOwnerThreads) {
+      const int g = e >= 1 && e <= E ? expert_to_rank[e - 1] : -1;
+      const uint32_t in = (((uint32_t)g * per_recip16) >> 16) - (uint32_t)first;
+      table[e] = (uint8_t)((unsigned)g >= (unsigned)G ? (e == 0 ? 0u : 0x80u) : in < (uint32_t)kOwnerGroups ? 1u << in : 0u);
+    }
+    if (threadIdx.x < 8) cnt[threadIdx.x] = 0;
+    __syncthreads();
+  }, [&](int id) { mask |= table[min((uint32_t)id + 1u, (uint32_t)E + 1u)]; }, [&] {
+    low += (mask & 0xFu) * 0x00204081u & 0x01010101u;   // bit i of four to byte i
+    high += (mask >> 4) * 0x00204081u & 0x01010101u;
+    mask = 0;
+  });
+  // two sums of sixteen bits in a word, over the lanes and then over the waves; the eighth counts tokens with an error
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int v = lane_scan((int)((j < 2 ? low : high) >> (8 * (j & 1)) & 0x00FF00FFu));
+    if (lane_id() == kWave - 1) {
+      atomicAdd(&cnt[4 * (j >> 1) + (j & 1)], v & 0xFFFF);
+      atomicAdd(&cnt[4 * (j >> 1) + (j & 1) + 2], v >> 16);
+    }
+  }
+  __syncthreads();
+  return cnt[kOwnerGroups] != 0;
+}
+
 // Value held by lane `src` (src must be wave-uniform).
 __device__ __forceinline__ int read_lane(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 __device__ __forceinline__ float read_lane(float v, int src) {
@@ -89,6 +190,17 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 }  // namespace hm
+
+// Whether the counts of a table are taken by owners (hm_expert_load, hm_group_counts): where their steps (of 1,024 tokens and up
+// to eight ids) cost less than the clearing launch, the gap behind it and the atomics.  Graphs of twenty calls, us, clear + count
+// -> owners, load / four levels of groups; eight ids: 1,024 tokens 6.1 -> 3.7 / 8.0 -> 4.0 (one workgroup before), 2,048 6.8 -> 4.0 / 7.2 ->
+// 4.4, 8,192 7.0 -> 6.4 / 7.3 -> 6.7, 16,384 7.6 -> 9.6 / 7.6 -> 9.9; sixteen ids: 4,096 9.0 -> 6.7 / 9.8 -> 7.1, 8,192 9.2 -> 10.2 / 10.0 ->
+// 10.5; one id: 4,096 6.0 -> 5.6 / 7.2 -> 5.9, 8,192 6.2 -> 7.9 / 7.2 -> 8.2.  With few experts many lanes meet at one count (E =
+// 16, 8,192 x 8: 6.4 -> 7.5 / 6.6 -> 6.7).  And a launch less takes 2.4 us off the host.
+static inline bool counts_by_owners(int64_t T, int64_t K, int64_t E) {
+  const int64_t steps = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads * ((K + 7) / 8);
+  return steps <= (K < 8 || E < 32 ? 4 : 8) && E <= hm::kOwnerMaxE;
+}
 
 // Host-side argument checks shared by the entry points.
 static inline hm_status hm_check_topology(hm_topology topo) {

@@ -1,17 +1,14 @@
 // hm_expert_load: per-expert slot counts and duplicate-free per-rank / per-node token counts
 // (the p^(1,G) and p^(1,U[1]) vectors of HierMoE Eq.(7)) for the expert-swap planner of Section IV.
 //
-// One lane owns one token.  Expert counts go through an LDS histogram; rank and node counts come
-// from ballots over the per-token rank masks (lane g accumulates the popcount for group g), so a
-// token is counted once per group however many of its experts live there.  The call is bound by
-// launches and by the chain ids -> placement -> counts, so the ids of a token are loaded together,
-// while the placement is staged in LDS, and the look-ups never leave the chip (T=8192, K=8, kernel
-// trace: 6.9 -> 5.7 us).  Up to kAloneTokens tokens are one launch of one workgroup, which owns the
-// outputs (T=1024: 5.8 us instead of a clearing launch, 1.4, a gap, and 5.6); beyond that a tiny launch
-// clears them and integer atomics merge the workgroups, which keeps the result exact and
-// order-independent.  Tried and slower: the masks of ranks and nodes as one 64-bit word per expert in
-// LDS and the counts by turning the wave's 64 x 64 bits round (6.6 us: more code to fetch, and the
-// ballots are not what it waits for).
+// Small tables are one launch: workgroups that own a few outputs each go through all the tokens (load_owner_kernel; T =
+// 1,024, K = 8: 6.1 us by the one workgroup that did it before, 3.7 now).  Larger ones: one lane per token, expert counts
+// in an LDS histogram, rank and node counts from ballots over the per-token rank masks (lane g accumulates the
+// popcount for group g), so a token is counted once per group however many of its experts live there; a tiny launch clears
+// the outputs and integer atomics merge the workgroups, which keeps the result exact and order-independent.  The ids of a
+// token are loaded together, while the placement is staged in LDS.  Tried there and slower: the masks of ranks and
+// nodes as one 64-bit word per expert in LDS and the counts by turning the wave's 64 x 64 bits round (6.6 us against 5.7:
+// more code to fetch, and the ballots are not what it waits for).
 #include "hm_device.h"
 
 namespace hm {
@@ -113,6 +110,41 @@ __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
   if (threadIdx.x == 0 && bad) flag(p.status, HM_ERR_BAD_ID);
 }
 
+// Small tables: workgroups [0, expert_blocks) own kOwnerExperts experts each, the next ones seven ranks each, the
+// last ones seven nodes each.
+__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks) {
+  __shared__ uint8_t table[kOwnerMaxE + 2];
+  __shared__ int32_t cnt[kOwnerExperts * kOwnerCopies];
+  int block = (int)blockIdx.x;
+  if (block < expert_blocks) {   // an id is counted whether its expert's placement is valid or not, and stored if it is
+    const int e0 = block * kOwnerExperts;
+    const uint32_t copy = threadIdx.x & (kOwnerCopies - 1);
+    for_ids(p.ids, p.T, p.K, [&] {
+      if (threadIdx.x < kOwnerExperts * kOwnerCopies) cnt[threadIdx.x] = 0;
+      __syncthreads();
+    }, [&](int id) {
+      const uint32_t e = (uint32_t)id - (uint32_t)e0;
+      if (e < (uint32_t)kOwnerExperts) atomicAdd(&cnt[e * kOwnerCopies + copy], 1);
+    }, [] {});
+    __syncthreads();
+    const int e = e0 + (int)threadIdx.x;
+    if (threadIdx.x < kOwnerExperts && e < p.E) {
+      int sum = 0;
+#pragma unroll
+      for (int i = 0; i < kOwnerCopies; ++i) sum += cnt[threadIdx.x * kOwnerCopies + i];
+      p.load_expert[e] = (unsigned)p.expert_to_rank[e] < (unsigned)p.G ? sum : 0;
+    }
+    return;
+  }
+  block -= expert_blocks;
+  const bool ranks = block < rank_blocks;
+  const int first = (ranks ? block : block - rank_blocks) * kOwnerGroups;
+  const bool bad = count_owned_groups(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, ranks ? 1 : p.R, first, table, cnt);
+  const int i = first + (int)threadIdx.x;
+  if (threadIdx.x < kOwnerGroups && i < (ranks ? p.G : p.N)) (ranks ? p.load_rank : p.load_node)[i] = cnt[threadIdx.x];
+  if (block == 0 && threadIdx.x == 0 && p.status) *p.status = bad ? HM_ERR_BAD_ID : 0;
+}
+
 }  // namespace hm
 
 extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expert_to_rank, int32_t T, int32_t K,
@@ -141,15 +173,21 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   p.load_rank = load_rank;
   p.load_node = load_node;
   p.status = status;
-  const bool alone = T <= kAloneTokens && E <= kLdsExperts;
+  if (counts_by_owners(T, K, E)) {
+    const int expert_blocks = (E + kOwnerExperts - 1) / kOwnerExperts, rank_blocks = (p.G + kOwnerGroups - 1) / kOwnerGroups;
+    const int node_blocks = (p.N + kOwnerGroups - 1) / kOwnerGroups;
+    hipLaunchKernelGGL(load_owner_kernel, dim3((unsigned)(expert_blocks + rank_blocks + node_blocks)), dim3(kOwnerThreads), 0, stream, p,
+                       expert_blocks, rank_blocks);
+    return hm_launch_status();
+  }
+  const bool alone = T <= kAloneTokens && E <= kLdsExperts;   // more experts than the owners' table holds
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
   if (blocks > 1024) blocks = 1024;
   // Staging pays where a lane looks more slots up than it stages entries (us, staged / from memory: E = 4,096, 1,025 tokens, K = 1
   // 10.1 / 7.9, K = 8 10.4 / 9.4, K = 16 11.7 / 11.4; E = 2,048, K = 16 9.9 / 10.4; 300,000 tokens, two per lane, E = 2,048,
-  // K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).  The one workgroup has four times the lanes to stage with (1,024 tokens, E =
-  // 4,096 staged, E = 5,000 from memory: K = 1 6.5 and 6.2, K = 8 7.1 and 7.6).
+  // K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).
   const int64_t lookups = blocks ? ((int64_t)T + blocks * kLoadThreads - 1) / (blocks * kLoadThreads) * K : 0;
-  p.staged = E <= kStagedExperts && (alone || lookups * kLoadThreads > E);
+  p.staged = E <= kStagedExperts && lookups * kLoadThreads > E;
   if (alone) {
     hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
     return hm_launch_status();

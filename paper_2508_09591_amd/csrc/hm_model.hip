@@ -88,6 +88,20 @@ __global__ __launch_bounds__(THREADS) void group_count_kernel(GroupParams p) {
   }
 }
 
+// Small tables: a workgroup owns seven groups of a level.
+__global__ __launch_bounds__(kOwnerThreads) void group_owner_kernel(GroupParams p) {
+  __shared__ uint8_t table[kOwnerMaxE + 2];
+  __shared__ int32_t cnt[kOwnerGroups + 1];
+  int level = 0, block = (int)blockIdx.x;
+  while (block >= (p.groups[level] + kOwnerGroups - 1) / kOwnerGroups) block -= (p.groups[level++] + kOwnerGroups - 1) / kOwnerGroups;
+  const int first = block * kOwnerGroups;
+  const bool bad = count_owned_groups(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, p.per[level], first, table, cnt);
+  const int i = first + (int)threadIdx.x, n = p.groups[level];   // the last owner of a level clears what is behind its groups
+  if (i < kWave && ((int)threadIdx.x < kOwnerGroups || first + kOwnerGroups >= n))
+    p.counts[level * kWave + i] = (int)threadIdx.x < kOwnerGroups && i < n ? cnt[threadIdx.x] : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && p.status) *p.status = bad ? HM_ERR_BAD_ID : 0;
+}
+
 struct TimeParams {
   int32_t D, G;
   int32_t U[kMaxDepth];
@@ -179,6 +193,12 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
   p.counts = counts;
   p.status = status;
   hipStream_t stream = (hipStream_t)hip_stream;
+  if (counts_by_owners(T, K, E)) {
+    int blocks = 0;
+    for (int l = 0; l < depth; ++l) blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
+    hipLaunchKernelGGL(group_owner_kernel, dim3((unsigned)blocks), dim3(kOwnerThreads), 0, stream, p);
+    return hm_launch_status();
+  }
   // one workgroup that looks many slots up in memory is slower than several (E = 5,000, 1,024 tokens, K = 64: 32.4 us, 19.8)
   if (T <= kAloneTokens && (E <= kStagedExperts || (int64_t)T * K <= 32768)) {
     hipLaunchKernelGGL((group_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);

@@ -311,17 +311,6 @@ __device__ __forceinline__ int rows_of_block(const PlanShared &sh, int wv, int &
   return all;
 }
 
-// Inclusive sum over the lanes of a wave.
-__device__ __forceinline__ int lane_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // from the lane one below, within rows of sixteen
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // lane 15 of a row to the next one, rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2 and 3
-  return v;
-}
-
 // The LDS behind PlanShared, if the tables are staged: [hist: E int32 if the load arrays are asked for][table: E + 1 uint16].
 extern __shared__ int32_t plan_dyn_lds[];
 

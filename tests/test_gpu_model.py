@@ -115,6 +115,38 @@ def test_counts_of_no_tokens(hw, E):
     assert not any(t.any() for t in out + [counts, status])
 
 
+@pytest.mark.parametrize("T,K,E,nodes,rpn", [
+    (1, 1, 1, 1, 1), (1024, 3, 65, 3, 5), (4096, 7, 64, 32, 2), (4097, 7, 64, 32, 2),        # up to four steps of fewer than eight ids
+    (8192, 8, 4096, 8, 8), (8193, 8, 63, 2, 7), (4096, 9, 128, 1, 64), (1023, 64, 130, 4, 4),   # up to eight steps of eight
+    (2049, 8, 4097, 4, 8)])                                                                  # one expert too many for the owners' table
+def test_counts_by_owners_and_beyond(hw, oracle, T, K, E, nodes, rpn):
+    """Both calls on both sides of the rule that gives each workgroup its own outputs: dropped, repeated and invalid ids, an
+    invalid placement, outputs that hold rubbish, entries behind a level's groups cleared."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(T * 7 + K)
+    G = nodes * rpn
+    ids = rng.integers(0, E, (T, K), dtype=np.int32)
+    ids[rng.random((T, K)) < 0.1] = -1
+    e2r = rng.integers(0, G, E).astype(np.int32)
+    for broken in (False, True):
+        if broken:
+            ids[T - 1, K - 1] = (E, -2, 2 ** 31 - 1, -2 ** 31)[T % 4]
+            e2r[E // 2] = G
+        le, lr, ln, st = oracle.expert_load(ids, e2r, nodes, rpn)
+        full = lambda *n: torch.full(n, -77, dtype=torch.int32, device="cuda")
+        out = [full(E), full(G), full(nodes), full(1)]
+        ids_d, e2r_d = hw.dev(ids), hw.dev(e2r)
+        B.hm_expert_load(ids_d, e2r_d, nodes, rpn, *out[:3], status=out[3])
+        for got, want in zip(out, (le, lr, ln, [st])):
+            assert np.array_equal(got.cpu().numpy(), want), (broken, len(got))
+        groups = [G, nodes, 1]
+        ref, st = oracle.group_counts(ids, e2r, G, groups)
+        counts, status = full(3, 64), full(1)
+        B.hm_group_counts(ids_d, e2r_d, G, groups, counts, status)
+        assert np.array_equal(counts.cpu().numpy(), ref) and int(status.item()) == st, broken
+
+
 def test_alltoall_times_parity(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
