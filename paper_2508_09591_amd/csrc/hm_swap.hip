@@ -8,8 +8,8 @@
 // For g_r != g_c:  Z[r][c][g_c] = base[g_c] + (L0[r] - CG[r][g_c]) - (L[c] - C[c][r])   and the same
 // with r and c exchanged for g_r: no O(T K E) walk over all unselected experts, and the per-pair
 // work is an embarrassingly parallel E^2 ng kernel.  The tables come from int8 matrix products on
-// the matrix cores for E <= 256 (further down), from O(T K (K + ng)) atomic updates, one lane per
-// routing slot, beyond that.
+// the matrix cores for E <= 512 (further down), from O(T K (K + ng)) atomic updates, one lane per
+// routing slot, beyond that (and for E > 256 with more than eight slots per token).
 #include "hm_device.h"
 
 namespace hm {
@@ -46,6 +46,7 @@ struct SwapParams {
   int32_t *C[kMaxCuts];        // [copies][E][E]
   int32_t *CT[kMaxCuts];       // [E][E]   C transposed   } matrix path only: swap_build_kernel then reads
   int32_t *CGT[kMaxCuts];      // [ng][E]  CG transposed  } along rows whichever expert of a pair a lane needs
+  int32_t cg_by_group[kMaxCuts];   // whether there is room for CGT; else CGT is CG itself, [E][ng]
   int32_t transposed;
   int32_t *Z[kMaxCuts];
   int32_t *ws;                 // start of the workspace and its size in ints (cleared first)
@@ -185,31 +186,28 @@ __global__ __launch_bounds__(kFactorThreads) void swap_factors_kernel(SwapParams
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same tables as contractions over the tokens (E <= 256).
+// The same tables as contractions over the tokens (E <= 512).
 //
 // With S[t][a] = 1 when token t selects expert a, A[t][a] = 1 when a is moreover the only selected
 // expert of its group, and M[t][g] = 1 when t selects something in group g (all 0/1 bytes):
 //   C  = A^T S   (its diagonal is L)        CG = S^T M   (L0[a] = CG[a][group of a])
 // so the read-modify-write updates of popular expert pairs, which serialise on one address, become
-// int8 matrix products with int32 accumulators held in registers.  What only the token's other slots
-// can tell (is this the first occurrence of the expert, is it alone in its group under the cut) is worked
-// out where the slots are read, or, for K > 8 or many tokens, by a kernel of its own that leaves one byte per slot.  In
-// the matrix kernel a workgroup takes one cut and a contiguous chunk of the tokens, builds
-// the three indicator tiles for 128 tokens at a time in LDS (expert-major, so that a lane's MFMA
-// operand is 16 contiguous bytes), and stores its partial tables with plain stores; a third kernel
-// sums the chunks.  No table is touched by an atomic.
+// int8 matrix products with int32 accumulators held in registers.  A workgroup takes one cut, a contiguous chunk of
+// the tokens and a panel of columns of C, builds the three indicator tiles for 128 tokens at a time in LDS
+// (expert-major, so that a lane's MFMA operand is 16 contiguous bytes), and stores its partial tables with plain
+// stores; a second kernel sums the chunks.  (With many tokens, or E > 256, for which the workspace has no room
+// for partial tables, the chunks are added to cleared tables by atomics.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kCoocThreads = 1024;
-constexpr int kCoocWaves = kCoocThreads / kWave;
 constexpr int kCoocTokens = 128;     // tokens per tile: four k-steps of the 32x32x32 int8 MFMA
 constexpr int kCoocStride = 144;     // bytes per tile row: 128 tokens + 16, which spreads 32 rows over all banks
 constexpr int kCoocGroups = 64;      // rows of the group tile
 constexpr int kCoocChunksMax = 16;   // partial tables per cut
 constexpr int kCoocChunkTokensMax = 32640;   // a chunk's counts are stored as 16-bit values
-constexpr int kCoocMaxE = 256;
-constexpr int kCoocStaged = 8;       // passes whose slots are fetched together (16 KiB of LDS)
-constexpr int kCoocTokensPerChunkMin = 512;   // below this a chunk is not worth a workgroup of its own
-constexpr int kCoocOwnTokens = 1024;          // most tokens of a chunk whose slots the matrix kernel works out itself
+constexpr int kCoocMaxE = 512;
+constexpr int kCoocPartMaxE = 256;   // experts up to which the workspace holds partial tables
+constexpr int kCoocStaged = 8192;    // slots worked out together (32 KiB of LDS): a lane per token of eight
+constexpr int kCoocAddedGroups = 256;   // workgroups aimed at where chunks are added up (512: E = 320, 4,096 tokens 33 -> 39 us)
+constexpr int kCoocOwnK = 8;         // most slots of a token that the matrix kernel works out itself
 
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef i32x4 i32x4_align4 __attribute__((aligned(4)));
@@ -219,20 +217,22 @@ struct CoocParams {
   const int32_t *ids;
   const int32_t *expert_to_rank;
   int32_t T, K, E, G;
-  int32_t sub_log2;            // lanes per token: 2^sub_log2 >= K
+  int32_t sub_log2;            // places per token: 2^sub_log2 >= K
   int32_t ncuts;
   int32_t chunks;              // gridDim.x of the matrix kernel
   int32_t tokens_per_chunk;    // a multiple of kCoocTokens
+  int32_t added;               // the tables are added to C, CG and base instead of stored as parts
   int32_t ng[kMaxCuts], per[kMaxCuts];
   uint8_t *slot_bits;          // [T * K]: bit 0 first valid occurrence, bit 1 + c alone in its group under cut c
   uint16_t *part[kMaxCuts];    // [chunks][E*E + E*ng + 64 (+1)]: C, CG and base of one chunk; a chunk has < 2^15 tokens
+  int32_t *C[kMaxCuts], *CG[kMaxCuts], *base[kMaxCuts];
   int32_t *status;
 };
 
 __host__ __device__ static inline int64_t cooc_part_ints(int64_t E, int64_t ng) { return E * E + E * ng + 64; }   // values per chunk
 __host__ __device__ static inline int64_t cooc_part_words(int64_t E, int64_t ng) { return (cooc_part_ints(E, ng) + 1) / 2; }   // 32-bit words they take
 
-// One lane per routing slot (K > 8 or many tokens); the K slots of a token sit in 2^sub_log2 consecutive lanes and
+// One lane per routing slot (K > 8); the K slots of a token sit in 2^sub_log2 consecutive lanes and
 // learn about each other through shuffles, eight in flight at a time.
 __global__ __launch_bounds__(kSwapThreads) void swap_slots_kernel(CoocParams p) {
   const int sub = 1 << p.sub_log2;
@@ -301,229 +301,250 @@ __device__ __forceinline__ i32x16 mfma_i8(i32x4 a, i32x4 b, i32x16 acc) {
   return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
 }
 
-// Workgroup (chunk, cut, panel).  Every wave holds one 32x32 tile of C, so a workgroup covers 16 of
-// them: all of C for E <= 128, and for E <= 256 one of four panels of two tile columns (the panels
-// repeat the cheap filling of the tiles and split the products, which is what E = 256 is bound by).
-//
-// OWN_SLOTS (K <= 8): the workgroup works the slots out itself instead of reading the bytes of
-// swap_slots_kernel, which saves that launch, the gap before it and the host's time for it: the experts and the groups of
-// a token's slots meet in two 8-byte words, and a slot compares its own with all of them at once.  Every cut
-// and panel repeats the work, 1 us per 1,024 tokens of a chunk for K <= 2 and 2.5 us for K = 8, on sixteen chunks
-// instead of the whole chip, so it is for chunks of up to 1,024 tokens (graphs of ten calls, four cuts, E = 128, slots
-// kernel -> own slots in us: 8,192 tokens K = 2 20.7 -> 19.2, K = 8 22.1 -> 21.3; 16,384 tokens K = 2 23.5 -> 23.2, K = 8 26.3 ->
-// 27.6, which is less than the 3 us the host needs for a launch; 32,768 tokens 30.5 -> 32.4 and 35.4 -> 40.3, 500,000
-// tokens K = 8 324 -> 425).
-__device__ __forceinline__ uint32_t or_of_token(uint32_t v, int sub_log2) {   // over the 2^sub_log2 <= 8 lanes of a token
-  if (sub_log2 > 0) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);    // lane ^ 1
-  if (sub_log2 > 1) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);    // lane ^ 2
-  if (sub_log2 > 2) v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);   // 7 - lane, of each eight
-  return v;
-}
-__device__ __forceinline__ uint64_t zero_bytes(uint64_t x) {   // 0x80 in every zero byte
-  const uint64_t low = 0x7F7F7F7F7F7F7F7Full;
-  return ~(((x & low) + low) | x | low);
+// What a slot marks in the tiles: its expert, the expert's group, whether it is alone there; 0 if it marks nothing (no valid
+// expert, or not the first with it in its token).
+constexpr uint32_t kMarks = 1u << 31, kAlone = 1u << 15;
+__device__ __forceinline__ uint32_t mark_of(int expert, uint32_t group, bool alone) {
+  return kMarks | group << 16 | (alone ? kAlone : 0u) | (uint32_t)expert;
 }
 
+// The marks of a token of up to eight slots, by the one lane that holds it.  Groups are bits of BITS: one that has been seen
+// twice, copies of an expert aside, is nobody's alone.  (A lane per slot that compares itself with the others
+// took four times the instructions for a token, and the workgroups of all cuts and panels repeat them: 6.5 us for the 1,024
+// tokens of a chunk on one CU.)
+template <typename BITS>
+__device__ __forceinline__ void mark_token(const int (&id)[kCoocOwnK], int E, const uint8_t *group_of, bool &bad, uint32_t (&mark)[kCoocOwnK]) {
+  uint32_t expert[kCoocOwnK], group[kCoocOwnK];
+  BITS once = 0, twice = 0;
+#pragma unroll
+  for (int k = 0; k < kCoocOwnK; ++k) {
+    group[k] = group_of[min((uint32_t)id[k] + 1u, (uint32_t)E + 1u)];   // entry 0: id -1, E + 1: out of range
+    bad = bad || group[k] == 0xFEu;
+    expert[k] = group[k] < kWave ? (uint32_t)id[k] : 0x10000u + k;   // equal to no other
+  }
+  __builtin_amdgcn_sched_barrier(0);   // here and below: all comparisons at once would need more registers than there are
+#pragma unroll
+  for (int k = 0; k < kCoocOwnK; ++k) {
+    uint32_t same = 1;   // 0 if an earlier slot has the expert
+#pragma unroll
+    for (int j = 0; j < k; ++j) same = min(same, expert[j] ^ expert[k]);
+    const bool first = same != 0 && group[k] < kWave;
+    const BITS bit = first ? (BITS)1 << group[k] : (BITS)0;
+    mark[k] = first ? expert[k] | group[k] << 16 | kMarks : 0u;
+    twice |= once & bit;
+    once |= bit;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int k = 0; k < kCoocOwnK; ++k)
+    if (mark[k] && !((twice >> group[k]) & 1)) mark[k] |= kAlone;
+}
+
+// A lane's column of a 32x32 tile, rows 8 (r / 4) + r % 4 from element `at` on, as far as they are below `rows`.
+__device__ __forceinline__ void store_tile(uint16_t *part, const i32x16 &acc, int at, int width, int rows) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (8 * (r / 4) + r % 4 < rows) part[at + (8 * (r / 4) + r % 4) * width] = (uint16_t)acc[r];
+}
+__device__ __forceinline__ void add_tile(int32_t *table, const i32x16 &acc, int at, int width, int rows) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (8 * (r / 4) + r % 4 < rows && acc[r]) atomicAdd(&table[at + (8 * (r / 4) + r % 4) * width], acc[r]);
+}
+
+// Workgroup (chunk, cut, panel of 32 or 64 columns of C); the first waves hold one 32x32 tile of C each.  A workgroup
+// needs the S tile of its own columns only; the panels repeat the marks of the chunk's slots and the A tile.  All
+// sixteen waves mark.  One column of tiles up to 128 experts, so that four cuts and sixteen chunks are a workgroup per
+// CU, two for 256 (E = 256, four cuts, the whole call: 8,192 tokens 33.7 us with one, 28.1 with two, 65,536 92 and 58).
+// The whole call, graphs of ten, four cuts, K = 8, with a lane per slot and panels of 64 and 128 columns -> now, us: E = 128 1,024
+// tokens 19.8 -> 14.6, 16,384 26.6 -> 21.1, 65,536 48.3 -> 40.2; E = 256 1,024 23.8 -> 21.5, 8,192 30.9 -> 28.1, 65,536 59.3 -> 58.4; by
+// atomics per slot -> now: E = 320 4,096 77 -> 33, 30,000 131 -> 74, E = 512 (64 ranks, Zipf) 4,096 339 -> 54, 30,000 1,622 -> 124.
+// Loops stay loops: unrolled, they cost the registers of the accumulators, which then live in memory.
+//
+// Per tile: mark | barrier | multiply | barrier.  Nothing waits for a tile to be cleared: with one column of tiles the rows of A
+// are read by one wave, which clears them behind its reads; with two, the lanes that marked them clear them (a
+// token's places belong to one wave, so it may mark the next tile without a barrier).  S and M, which several
+// waves read, are there twice, and the one not in use is cleared while the other is multiplied.
+constexpr int kCoocThreads = 1024;
+constexpr int kCoocWaves = kCoocThreads / kWave;
+constexpr int cooc_cols(int ne) { return ne == 8 ? 2 : 1; }   // tile columns of a panel
 template <int NE, bool OWN_SLOTS>   // experts padded to 32 * NE
 __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
-  constexpr int kPanels = NE * NE > kCoocWaves ? NE * NE / kCoocWaves : 1;   // gridDim.z
-  constexpr int kCols = NE / kPanels;                                         // tile columns of a panel
-  constexpr int kVecs = (2 * 32 * NE + kCoocGroups) * kCoocStride / 16;
+  constexpr int COLS = cooc_cols(NE), kCoocPanel = 32 * COLS;
+  constexpr int kRows = kCoocPanel + kCoocGroups;   // of S and M
+  constexpr int kVecs = (32 * NE + 2 * kRows) * kCoocStride / 16;
   extern __shared__ __align__(16) uint8_t tiles[];
-  uint8_t *const s_tile = tiles;                                        // [32 NE][stride]  S
-  uint8_t *const a_tile = s_tile + 32 * NE * kCoocStride;               // [32 NE][stride]  A
-  uint8_t *const m_tile = a_tile + 32 * NE * kCoocStride;               // [64][stride]     M
-  __shared__ uint8_t group_of_expert[32 * NE];
-  __shared__ uint16_t staged[kCoocStaged][kCoocThreads];
+  uint8_t *const a_tile = tiles;                                   // [32 NE][stride]     A
+  uint8_t *const sm_tiles = a_tile + 32 * NE * kCoocStride;        // twice [panel][stride] S, its experts, [64][stride] M
+  uint32_t *const staged = (uint32_t *)(sm_tiles + 2 * kRows * kCoocStride);   // [tokens of a stage][2^sub_log2] marks
+  __shared__ uint8_t group_of[32 * NE + 2];   // of expert e at e + 1; 0xFF none, 0xFE an error
 
   const int cut = blockIdx.y, panel = blockIdx.z;
   const int ng = p.ng[cut], per = p.per[cut];
-  const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const i32x4 zero = {0, 0, 0, 0};
+#pragma unroll 1
+  for (int i = tid; i < kVecs; i += kCoocThreads) ((i32x4 *)tiles)[i] = zero;
   {
-    i32x4 *z = (i32x4 *)tiles;
-    for (int i = tid; i < kVecs; i += kCoocThreads) z[i] = i32x4{0, 0, 0, 0};
-    if (tid < 32 * NE) {
-      int g = 0xFF;   // no valid placement
-      if (tid < p.E) {
-        const int r = p.expert_to_rank[tid];
-        if ((unsigned)r < (unsigned)p.G) g = r / per;
-      }
-      group_of_expert[tid] = (uint8_t)g;
+    const uint32_t per_recip16 = (65536u + (uint32_t)per - 1u) / (uint32_t)per;   // exact for ranks (below 64)
+#pragma unroll 1
+    for (int e = tid; e < p.E + 2; e += kCoocThreads) {
+      const int r = e >= 1 && e <= p.E ? p.expert_to_rank[e - 1] : -1;
+      group_of[e] = (uint8_t)(e == 0 ? 0xFFu : (unsigned)r < (unsigned)p.G ? ((uint32_t)r * per_recip16) >> 16 : 0xFEu);
     }
   }
   __syncthreads();
 
-  // A pass: every lane looks at one routing slot, 2^sub_log2 lanes per token.  A tile takes `passes`
-  // passes; kCoocStaged passes are fetched at a time, so that the latency of global memory is paid
-  // once per kCoocStaged passes and not once per tile.
-  const int sub = 1 << p.sub_log2;
-  const int k = min(tid & (sub - 1), p.K - 1);                        // my slot in the token (clamped: see `mine`)
-  const int tp1 = tid >> p.sub_log2;                                  // my token within a pass
-  const int tok_pass = min(kCoocThreads >> p.sub_log2, kCoocTokens);  // tokens one pass covers
-  const int passes = kCoocTokens / tok_pass;
-  const bool mine = tp1 < tok_pass && (tid & (sub - 1)) < p.K;
-  const int alone_bit = 2 << cut;
+  const int sub_log2 = p.sub_log2, sub = 1 << sub_log2;
+  const int places = kCoocTokens << sub_log2;                    // of a tile
+  const int stage_tokens = kCoocStaged >> sub_log2;              // 128 at least
   const int64_t t_begin = (int64_t)blockIdx.x * p.tokens_per_chunk;
   const int64_t t_end = min((int64_t)p.T, t_begin + p.tokens_per_chunk);
 
-  // What this wave accumulates: one tile of C and, counted from the last wave down and dealt round
-  // the panels, at most one tile of CG.
-  const bool has_c = w < NE * kCols;
-  const int c_row = has_c ? w / kCols : 0, c_col = has_c ? panel * kCols + w % kCols : 0;
-  const int ngt = (ng + 31) / 32;
-  const int g_job = (kCoocWaves - 1 - w) * kPanels + panel;
-  const bool has_g = g_job < NE * ngt;
-  const int g_row = has_g ? g_job / ngt : 0, g_col = has_g ? g_job % ngt : 0;
+  // What this wave accumulates: one tile of C, and from the last wave down at most one tile of this panel's CG.
+  const int c_row = w / COLS, c_col = w % COLS;
+  const bool has_c = c_row < NE && c_row < (p.E + 31) / 32;
+  const int g_tiles = (ng + 31) / 32, g_job = kCoocWaves - 1 - w, g_row = g_job / g_tiles, g_col = g_job % g_tiles;
+  const bool has_g = g_row < COLS;
   const bool counts_base = panel == 0 && w == kCoocWaves / 2;   // lane g: tokens of this chunk that touch group g
-  i32x16 acc, acc_g;
+  constexpr bool kEither = NE * COLS + 4 <= kCoocWaves;   // no wave has both
+  i32x16 acc, second;
+  i32x16 &acc_g = kEither ? acc : second;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = acc_g[r] = 0;
+  for (int r = 0; r < 16; ++r) acc[r] = second[r] = 0;
   int my_base = 0;
-
   const int op_at = (lane & 31) * kCoocStride + (lane >> 5) * 16;
-  const uint8_t *const c_a = a_tile + 32 * c_row * kCoocStride + op_at;
-  const uint8_t *const c_b = s_tile + 32 * c_col * kCoocStride + op_at;
-  const uint8_t *const g_a = s_tile + 32 * g_row * kCoocStride + op_at;
-  const uint8_t *const g_b = m_tile + 32 * g_col * kCoocStride + op_at;
+  uint8_t *const c_a = a_tile + 32 * (has_c ? c_row : 0) * kCoocStride + op_at;
+  const int c_s = 32 * c_col * kCoocStride + op_at, g_s = 32 * (has_g ? g_row : 0) * kCoocStride + op_at;
+  const int g_m = (kCoocPanel + 32 * g_col) * kCoocStride + op_at;
 
-  for (int64_t stage0 = t_begin; stage0 < t_end; stage0 += (int64_t)kCoocStaged * tok_pass) {
-    // My slots of the next kCoocStaged passes: expert | bits << 8, 0 for a slot that marks nothing.
-    // The loads are unconditional (clamped to the chunk) so that all of them are in flight at once.
-    // A lane reads back only what it wrote itself, so this needs no barrier.
-    {
-      int id[kCoocStaged], bits[kCoocStaged];
+  bool bad = false;
+  uint8_t *sm = sm_tiles, *sm_next = sm_tiles + kRows * kCoocStride;
+#pragma unroll 1
+  for (int64_t stage0 = t_begin; stage0 < t_end; stage0 += stage_tokens) {
+    const int tokens = (int)min((int64_t)stage_tokens, t_end - stage0);
+    const int last = (tokens + kCoocTokens - 1) / kCoocTokens * places;   // places of the tiles to come
+    if (OWN_SLOTS) {
+#pragma unroll 1
+      for (int t = tid; t < (last >> sub_log2); t += kCoocThreads) {
+        int id[kCoocOwnK];
+        uint32_t m[kCoocOwnK];
 #pragma unroll
-      for (int j = 0; j < kCoocStaged; ++j) {
-        const int64_t t = min(stage0 + (int64_t)j * tok_pass + tp1, t_end - 1);
-        id[j] = p.ids[t * p.K + k];
-        if (!OWN_SLOTS) bits[j] = p.slot_bits[t * p.K + k];
-      }
-      if (OWN_SLOTS) {
-        bool bad = false;
-        const int lane_place = tid & (sub - 1), at = 8 * (lane_place & 3);
-        const bool upper = lane_place >= 4;
-        const uint64_t no_slot = p.sub_log2 < 3 ? ~0ull << (8 * sub) : 0ull;   // bytes without a lane
-        const uint64_t before = (1ull << (8 * lane_place)) - 1ull;
+        for (int k = 0; k < kCoocOwnK; ++k) id[k] = -1;
+        if (t < tokens) load_ids(p.ids + (stage0 + t) * p.K, p.K, 0, id);
+        if (ng <= 32) mark_token<uint32_t>(id, p.E, group_of, bad, m);
+        else mark_token<uint64_t>(id, p.E, group_of, bad, m);
+        if (sub == kCoocOwnK) {
+          *(i32x4 *)(staged + t * kCoocOwnK) = i32x4{(int)m[0], (int)m[1], (int)m[2], (int)m[3]};
+          *(i32x4 *)(staged + t * kCoocOwnK + 4) = i32x4{(int)m[4], (int)m[5], (int)m[6], (int)m[7]};
+        } else {
 #pragma unroll
-        for (int j = 0; j < kCoocStaged; ++j) {
-          bits[j] = 0;
-          if (stage0 + (int64_t)j * tok_pass >= t_end) continue;   // uniform: the chunk may be shorter than a stage
-          const bool in = mine && stage0 + (int64_t)j * tok_pass + tp1 < t_end;
-          const bool known = (unsigned)id[j] < (unsigned)p.E;
-          const uint32_t g = known ? group_of_expert[id[j]] : 0xFFu;
-          const bool valid = in && g != 0xFFu;
-          bad = bad || (in && !valid && id[j] != -1);
-          const uint32_t e = valid ? (uint32_t)id[j] : 0u, gb = valid ? g : 0xFFu;
-          const uint64_t experts = (uint64_t)or_of_token(upper ? e << at : 0u, p.sub_log2) << 32 |
-                                   or_of_token(upper ? 0u : e << at, p.sub_log2);
-          const uint64_t groups = ((uint64_t)or_of_token(upper ? gb << at : 0u, p.sub_log2) << 32 |
-                                   or_of_token(upper ? 0u : gb << at, p.sub_log2)) | no_slot;
-          const uint64_t there = ~groups & 0x8080808080808080ull;   // groups are below 64
-          const uint64_t same = zero_bytes(experts ^ (e * 0x0101010101010101ull)) & there;
-          const uint64_t together = zero_bytes(groups ^ (gb * 0x0101010101010101ull)) & there;
-          const bool first = valid && (same & before) == 0;
-          const bool alone = (together & ~same) == 0;   // nothing but copies of itself in its group
-          bits[j] = first ? 1 | (alone ? alone_bit : 0) : 0;
+          for (int k = 0; k < kCoocOwnK / 2; ++k)
+            if (k < sub) staged[(t << sub_log2) + k] = m[k];
         }
-        if (bad && cut == 0 && panel == 0) flag(p.status, HM_ERR_BAD_ID);
       }
+    } else {
+      constexpr int kAhead = 8;   // loads of a lane in flight together
+#pragma unroll 1
+      for (int i0 = tid; i0 < last; i0 += kAhead * kCoocThreads) {
+        int id[kAhead], bits[kAhead];
 #pragma unroll
-      for (int j = 0; j < kCoocStaged; ++j) {
-        const bool in = mine && stage0 + (int64_t)j * tok_pass + tp1 < t_end && (bits[j] & 1);
-        staged[j][tid] = (uint16_t)(in ? ((id[j] & 0xFF) | (bits[j] << 8)) : 0);
+        for (int j = 0; j < kAhead; ++j) {
+          const int i = i0 + j * kCoocThreads, t = min(i >> sub_log2, tokens - 1), k = min(i & (sub - 1), p.K - 1);
+          const int64_t slot = (stage0 + t) * p.K + k;
+          id[j] = p.ids[slot];
+          bits[j] = p.slot_bits[slot];
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+          const int i = i0 + j * kCoocThreads;
+          const bool in = (i >> sub_log2) < tokens && (i & (sub - 1)) < p.K && (bits[j] & 1);
+          if (i < last) staged[i] = in ? mark_of(id[j], group_of[id[j] + 1], (bits[j] >> (1 + cut)) & 1) : 0u;
+        }
       }
     }
-    int entry = staged[0][tid];
-    int group_row = group_of_expert[entry & 0xFF] * kCoocStride;
-    for (int tile = 0; tile < kCoocStaged / passes && stage0 + (int64_t)tile * kCoocTokens < t_end; ++tile) {
-      int wrote_s = -1, wrote_a = -1, wrote_m = -1;   // LDS offsets to clear again
-      for (int pass = 0; pass < passes; ++pass) {
-        const int tp = pass * tok_pass + tp1;
-        if (entry) {   // a valid expert with a valid placement, first time in this token
-          wrote_s = (entry & 0xFF) * kCoocStride + tp;
-          wrote_m = group_row + tp;
-          s_tile[wrote_s] = 1;
-          m_tile[wrote_m] = 1;
-          if ((entry >> 8) & alone_bit) {
-            wrote_a = wrote_s;
-            a_tile[wrote_a] = 1;
-          }
+    __syncthreads();
+#pragma unroll 1
+    for (int first_place = 0; first_place < last; first_place += places) {
+      int wrote = -1;   // where in A this lane's first mark went
+#pragma unroll 1
+      for (int i = tid; i < places; i += kCoocThreads) {
+        const uint32_t m = staged[first_place + i];
+        if (!(m & kMarks)) continue;
+        const int token = i >> sub_log2, expert = (int)(m & 0x1FFu), column = expert - kCoocPanel * panel;
+        if (m & kAlone) {
+          const int at = expert * kCoocStride + token;
+          a_tile[at] = 1;
+          wrote = i == tid ? at : wrote;
         }
-        // the next pass's entry and its group: fetched here, off the path between the barriers
-        const int next = tile * passes + pass + 1;
-        entry = next < kCoocStaged ? staged[next][tid] : 0;
-        group_row = group_of_expert[entry & 0xFF] * kCoocStride;
+        if ((unsigned)column < (unsigned)kCoocPanel) sm[column * kCoocStride + token] = 1;
+        sm[(kCoocPanel + (m >> 16 & 0x3Fu)) * kCoocStride + token] = 1;
       }
       __syncthreads();
-
-      {
-        i32x4 a_op[kCoocTokens / 32], b_op[kCoocTokens / 32];
+      if (has_c) {
+        i32x4 a_op[kCoocTokens / 32], s_op[kCoocTokens / 32];
 #pragma unroll
         for (int step = 0; step < kCoocTokens / 32; ++step) {
           a_op[step] = *(const i32x4 *)(c_a + 32 * step);
-          b_op[step] = *(const i32x4 *)(c_b + 32 * step);
+          s_op[step] = *(const i32x4 *)(sm + c_s + 32 * step);
+        }
+        if (COLS == 1) {
+#pragma unroll
+          for (int step = 0; step < kCoocTokens / 32; ++step) *(i32x4 *)(c_a + 32 * step) = zero;
         }
 #pragma unroll
-        for (int step = 0; step < kCoocTokens / 32; ++step) acc = mfma_i8(a_op[step], b_op[step], acc);
+        for (int step = 0; step < kCoocTokens / 32; ++step) acc = mfma_i8(a_op[step], s_op[step], acc);
       }
       if (has_g) {
-        i32x4 a_op[kCoocTokens / 32], b_op[kCoocTokens / 32];
 #pragma unroll
-        for (int step = 0; step < kCoocTokens / 32; ++step) {
-          a_op[step] = *(const i32x4 *)(g_a + 32 * step);
-          b_op[step] = *(const i32x4 *)(g_b + 32 * step);
-        }
-#pragma unroll
-        for (int step = 0; step < kCoocTokens / 32; ++step) acc_g = mfma_i8(a_op[step], b_op[step], acc_g);
+        for (int step = 0; step < kCoocTokens / 32; ++step)
+          acc_g = mfma_i8(*(const i32x4 *)(sm + g_s + 32 * step), *(const i32x4 *)(sm + g_m + 32 * step), acc_g);
       }
       if (counts_base) {   // bytes are 0 / 1, so a word's population count is its number of tokens
-        const i32x4 *row = (const i32x4 *)(m_tile + lane * kCoocStride);
+        const i32x4 *row = (const i32x4 *)(sm + (kCoocPanel + lane) * kCoocStride);
 #pragma unroll
         for (int i = 0; i < kCoocTokens / 16; ++i) {
           const i32x4 v = row[i];
           my_base += __popc(v[0]) + __popc(v[1]) + __popc(v[2]) + __popc(v[3]);
         }
       }
+#pragma unroll 1
+      for (int i = tid; i < kRows * kCoocStride / 16; i += kCoocThreads) ((i32x4 *)sm_next)[i] = zero;
+      uint8_t *const used = sm;
+      sm = sm_next;
+      sm_next = used;
       __syncthreads();
-
-      // Leave the tiles clean for the next 128 tokens.  A token's column is written by the lanes of
-      // one wave only, so clearing it and filling it again need no barrier in between.
-      if (passes == 1) {
-        if (wrote_s >= 0) {
-          s_tile[wrote_s] = 0;
-          m_tile[wrote_m] = 0;
-          if (wrote_a >= 0) a_tile[wrote_a] = 0;
+      if (COLS > 1) {    // two waves read a row of A: cleared by the lanes that marked it
+        if (wrote >= 0) a_tile[wrote] = 0;
+#pragma unroll 1
+        for (int i = tid + kCoocThreads; i < places; i += kCoocThreads) {
+          const uint32_t m = staged[first_place + i];
+          if (m & kAlone) a_tile[(m & 0x1FFu) * kCoocStride + (i >> sub_log2)] = 0;
         }
-      } else {
-        i32x4 *z = (i32x4 *)tiles;
-        for (int i = tid; i < kVecs; i += kCoocThreads) z[i] = i32x4{0, 0, 0, 0};
-        __syncthreads();
       }
     }
   }
+  if (OWN_SLOTS && bad && cut == 0 && panel == 0) flag(p.status, HM_ERR_BAD_ID);
 
   // Accumulator layout of a 32x32 tile: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4,
   // column l % 32.
+  const int64_t cg_at = (int64_t)p.E * p.E, base_at = cg_at + (int64_t)p.E * ng;
   uint16_t *const part = p.part[cut] + (int64_t)blockIdx.x * 2 * cooc_part_words(p.E, ng);
-  uint16_t *const part_c = part, *const part_cg = part + (int64_t)p.E * p.E, *const part_base = part_cg + (int64_t)p.E * ng;
   const int col = lane & 31, row_hi = (lane >> 5) * 4;
-  if (has_c) {
-    const int b = 32 * c_col + col;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int a = 32 * c_row + 8 * (r / 4) + row_hi + (r % 4);
-      if (a < p.E && b < p.E) part_c[(int64_t)a * p.E + b] = (uint16_t)acc[r];
-    }
+  if (has_c && kCoocPanel * panel + 32 * c_col + col < p.E) {
+    const int a0 = 32 * c_row + row_hi, at = a0 * p.E + kCoocPanel * panel + 32 * c_col + col;   // E <= 512
+    if (!p.added) store_tile(part, acc, at, p.E, p.E - a0);
+    else add_tile(p.C[cut], acc, at, p.E, p.E - a0);
   }
-  if (has_g) {
-    const int g = 32 * g_col + col;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int a = 32 * g_row + 8 * (r / 4) + row_hi + (r % 4);
-      if (a < p.E && g < ng) part_cg[(int64_t)a * ng + g] = (uint16_t)acc_g[r];
-    }
+  if (has_g && 32 * g_col + col < ng) {
+    const int a0 = kCoocPanel * panel + 32 * g_row + row_hi, at = a0 * ng + 32 * g_col + col;
+    if (!p.added) store_tile(part + cg_at, acc_g, at, ng, p.E - a0);
+    else add_tile(p.CG[cut], acc_g, at, ng, p.E - a0);
   }
-  if (counts_base) part_base[lane] = (uint16_t)my_base;
+  if (counts_base) {
+    if (!p.added) part[base_at + lane] = (uint16_t)my_base;
+    else if (my_base) atomicAdd(&p.base[cut][lane], my_base);
+  }
 }
 
 // Sums the chunks' partial tables into the tables swap_build_kernel reads; blockIdx.y is the cut and
@@ -531,7 +552,8 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
 // flight, and the tile is turned round in LDS, so that the transposes are written in whole lines too (one lane per
 // value wrote them a word per line: kernel trace 6.6 us for 128 experts and four cuts, 9.2 us for 256; now 4.7 and
 // 6.2).  L is the diagonal of C and L0[a] the entry of CG in a's own group (every token that selects a
-// selects something there), so neither needs a table of its own upstream.
+// selects something there), so neither needs a table of its own upstream.  Where the chunks were added up by atomics
+// already (cp.added), the tables are read back for the transposes, L and L0.
 constexpr int kTile = 32;
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef u16x4 u16x4_align2 __attribute__((aligned(2)));
@@ -556,7 +578,11 @@ __global__ __launch_bounds__(kSwapThreads) void swap_reduce_kernel(SwapParams p,
   int sum[4] = {0, 0, 0, 0};
   if (a < E && b < width) {
     const uint16_t *at = part + (of_c ? 0 : (int64_t)E * E) + (int64_t)a * width + b;
-    if (b + 4 <= width) {
+    int32_t *const out = (of_c ? p.C[cut] : p.CG[cut]) + (int64_t)a * width + b;
+    if (cp.added) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] = b + e < width ? out[e] : 0;
+    } else if (b + 4 <= width) {
       u16x4 v[kCoocChunksMax];   // every load unconditional (the last chunk again), so that none waits for another
 #pragma unroll
       for (int c = 0; c < kCoocChunksMax; ++c) v[c] = *(const u16x4_align2 *)(at + min(c, cp.chunks - 1) * stride);
@@ -575,11 +601,11 @@ __global__ __launch_bounds__(kSwapThreads) void swap_reduce_kernel(SwapParams p,
 #pragma unroll
         for (int e = 0; e < 3; ++e) sum[e] += c < cp.chunks && b + e < width ? v[c][e] : 0;
     }
-    int32_t *const out = (of_c ? p.C[cut] : p.CG[cut]) + (int64_t)a * width + b;
     const int rank = p.expert_to_rank[a];
     const bool placed = (unsigned)rank < (unsigned)p.G;
     const int own = of_c ? a : placed ? rank / p.per[cut] : 0;   // the column L or L0 is taken from
-    if (b + 4 <= width) {
+    if (cp.added) {
+    } else if (b + 4 <= width) {
       *(i32x4_align4 *)out = (i32x4){sum[0], sum[1], sum[2], sum[3]};
     } else {
 #pragma unroll
@@ -598,7 +624,7 @@ __global__ __launch_bounds__(kSwapThreads) void swap_reduce_kernel(SwapParams p,
   for (int e = 0; e < 4; ++e) turned[row][col + e] = sum[e];
   __syncthreads();
   const int b_out = b0 + row, a_out = a0 + col;   // a row of the transpose
-  if (b_out < width && a_out < E) {
+  if (b_out < width && a_out < E && (of_c || p.cg_by_group[cut])) {
     int32_t *const out = (of_c ? p.CT[cut] : p.CGT[cut]) + (int64_t)b_out * E + a_out;
     if (a_out + 4 <= E) {
       *(i32x4_align4 *)out = (i32x4){turned[col][row], turned[col + 1][row], turned[col + 2][row], turned[col + 3][row]};
@@ -608,7 +634,7 @@ __global__ __launch_bounds__(kSwapThreads) void swap_reduce_kernel(SwapParams p,
         if (a_out + e < E) out[e] = turned[col + e][row];
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x < kWave) {
+  if (!cp.added && blockIdx.x == 0 && threadIdx.x < kWave) {
     const uint16_t *at = part + (int64_t)E * E + (int64_t)E * ng + threadIdx.x;
     int v[kCoocChunksMax], base = 0;
 #pragma unroll
@@ -637,6 +663,7 @@ __device__ __forceinline__ void build_quads(const SwapParams &p, int cut, int l,
   const int32_t *__restrict__ const CT = p.CT[cut];
   const int32_t *__restrict__ const CG = p.CG[cut];
   const int32_t *__restrict__ const CGT = p.CGT[cut];
+  const int by_group = p.cg_by_group[cut];
   const int32_t *__restrict__ const L = p.L[cut];
   const int32_t *__restrict__ const L0 = p.L0;
   const unsigned per_reciprocal = p.per_reciprocal[cut];
@@ -669,7 +696,7 @@ __device__ __forceinline__ void build_quads(const SwapParams &p, int cut, int l,
       ct[i] = CT[(int64_t)r * p.E + c];
     }
     if (group_r[i] >= 0) {
-      cgt[i] = CGT[(int64_t)gr * p.E + c];
+      cgt[i] = CGT[by_group ? gr * p.E + c : c * ng + gr];
       cc[i] = C[(int64_t)r * p.E + c];
     }
   }
@@ -729,7 +756,7 @@ __global__ __launch_bounds__(kSwapThreads) void swap_build_kernel(SwapParams p) 
       int cba = 0, cg;
       if (p.transposed) {   // every read runs along row r of a table, or along c
         cba = j == gc ? CT[(int64_t)r * p.E + c] : C[(int64_t)r * p.E + c];
-        cg = j == gc ? CG[(int64_t)r * ng + j] : CGT[(int64_t)j * p.E + c];
+        cg = j == gc ? CG[(int64_t)r * ng + j] : CGT[p.cg_by_group[cut] ? j * p.E + c : c * ng + j];
       } else {
 #pragma unroll 8
         for (int k = 0; k < p.copies; ++k) cba += C[((int64_t)k * p.E + b) * p.E + a];
@@ -946,10 +973,11 @@ static bool swap_factors_lds_ready() {
 // Private copies of C on the path with atomics: as many as fit 2 MiB per cut, at most
 // kSwapCopiesMax (32 for E <= 128, 8 for E = 256): more copies spread the atomics of popular pairs,
 // but each is cleared and summed again.  The matrix path keeps one summed C.
-// The matrix path: E <= 256 and chunks short enough for 16-bit counts.
-static inline bool swap_by_matrices(int64_t E, int64_t T) { return E <= kCoocMaxE && T <= (int64_t)kCoocChunksMax * kCoocChunkTokensMax; }
+// Whether the workspace has partial tables of chunks (and a byte per slot): E <= 256 and chunks short enough for
+// 16-bit counts.
+static inline bool swap_has_parts(int64_t E, int64_t T) { return E <= kCoocPartMaxE && T <= (int64_t)kCoocChunksMax * kCoocChunkTokensMax; }
 static inline int64_t swap_copies(int64_t E, int64_t T) {
-  if (swap_by_matrices(E, T)) return 1;
+  if (swap_has_parts(E, T)) return 1;
   int64_t n = kSwapCopiesMax;   // a power of two, so that a workgroup finds its copy with a mask
   while (n > 1 && n * E * E > (int64_t)(1 << 19)) n /= 2;
   return n;
@@ -959,33 +987,36 @@ static inline int64_t swap_copies(int64_t E, int64_t T) {
 // matrix path the partial tables of kCoocChunksMax chunks and the transposes of C and CG after that.
 static inline int64_t swap_cut_ints(int64_t E, int64_t ng, int64_t T) {
   return 64 + E + E * ng + swap_copies(E, T) * E * E +
-         (swap_by_matrices(E, T) ? kCoocChunksMax * cooc_part_words(E, ng) + E * E + E * ng : 0);
+         (swap_has_parts(E, T) ? kCoocChunksMax * cooc_part_words(E, ng) + E * E + E * ng : 0);
 }
 // ... and, on the matrix path, one byte per routing slot at the very end.
-static inline int64_t swap_slot_ints(int64_t T, int64_t K, int64_t E) { return swap_by_matrices(E, T) ? (T * K + 3) / 4 : 0; }
+static inline int64_t swap_slot_ints(int64_t T, int64_t K, int64_t E) { return swap_has_parts(E, T) ? (T * K + 3) / 4 : 0; }
 
-// The matrix kernel for E experts, its dynamic LDS, and whether the device grants that much.
+// The matrix kernel for E experts and K slots, the columns of a panel and the dynamic LDS (0: the device does not grant that much).
 typedef void (*cooc_kernel_t)(CoocParams);
-template <bool OWN_SLOTS>
-static inline cooc_kernel_t cooc_kernel(int E, size_t *lds_bytes) {
-  const int ne = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8;
-  *lds_bytes = (size_t)(2 * 32 * ne + kCoocGroups) * kCoocStride;
-  return ne == 1 ? swap_cooc_kernel<1, OWN_SLOTS> : ne == 2 ? swap_cooc_kernel<2, OWN_SLOTS>
-       : ne == 4 ? swap_cooc_kernel<4, OWN_SLOTS> : swap_cooc_kernel<8, OWN_SLOTS>;
-}
-static bool cooc_lds_ready() {
-  static const bool ok = [] {
-    bool granted = true;
-    for (int own = 0; own < 2; ++own) {   // only the largest need more than the default
-      size_t bytes = 0;
-      const cooc_kernel_t k = own ? cooc_kernel<true>(kCoocMaxE, &bytes) : cooc_kernel<false>(kCoocMaxE, &bytes);
-      const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-      if (e != hipSuccess) (void)hipGetLastError();
-      granted = granted && e == hipSuccess;
-    }
-    return granted;
+struct CoocLaunch {
+  cooc_kernel_t kernel;
+  int panel;
+  size_t lds;
+};
+template <int NE, bool OWN_SLOTS>
+static CoocLaunch cooc_launch() {
+  constexpr size_t tiles = (size_t)(32 * NE + 2 * (32 * cooc_cols(NE) + kCoocGroups)) * kCoocStride, bytes = tiles + 4 * kCoocStaged;
+  static const bool granted = [] {
+    const hipError_t e = hipFuncSetAttribute((const void *)swap_cooc_kernel<NE, OWN_SLOTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)bytes);
+    if (e != hipSuccess) (void)hipGetLastError();   // not sticky: do not let it fail the next launch check
+    return e == hipSuccess;
   }();
-  return ok;
+  return {swap_cooc_kernel<NE, OWN_SLOTS>, 32 * cooc_cols(NE), granted ? bytes : 0};
+}
+template <bool OWN_SLOTS>
+static CoocLaunch cooc_launch_for(int E) {
+  return E <= 32    ? cooc_launch<1, OWN_SLOTS>()
+         : E <= 64  ? cooc_launch<2, OWN_SLOTS>()
+         : E <= 128 ? cooc_launch<4, OWN_SLOTS>()
+         : E <= 256 ? cooc_launch<8, OWN_SLOTS>()
+                    : cooc_launch<16, true>();   // there is no room for the bytes of swap_slots_kernel beyond
 }
 
 static inline bool swap_cuts_ok(int32_t G, int32_t ncuts, const int32_t *ng) {
@@ -1036,43 +1067,50 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
     }
   }
   p.status = status;
-  size_t cooc_lds = 0;
-  const bool own_slots = K <= 8 && T <= kCoocOwnTokens * kCoocChunksMax;
-  const cooc_kernel_t cooc = !swap_by_matrices(E, T) ? nullptr
-                             : own_slots ? cooc_kernel<true>(E, &cooc_lds) : cooc_kernel<false>(E, &cooc_lds);
-  if (cooc && (cooc_lds <= 65536 || cooc_lds_ready())) {
-    // Every table is written in full by the kernels below: only the status word needs clearing.
-    p.ws_ints = 0;
+  // By matrices where there is room for the chunks' tables; beyond that (E > 256, or more than 522,240 tokens) the chunks
+  // are added to cleared tables, as long as the marks of the slots need no room either.
+  const bool parts = swap_has_parts(E, T), own_slots = K <= kCoocOwnK;
+  CoocParams cp;
+  cp.sub_log2 = 0;
+  while ((1 << cp.sub_log2) < K) ++cp.sub_log2;
+  CoocLaunch cooc = {nullptr, 0, 0};
+  if (parts || (own_slots && E <= kCoocMaxE)) cooc = own_slots ? cooc_launch_for<true>(E) : cooc_launch_for<false>(E);
+  if (cooc.lds != 0) {
+    p.ws_ints = parts ? 0 : at;   // parts are written in full by the kernels below: only the status word needs clearing
     p.use_lds = 0;
     p.transposed = 1;
-    if (status) {
-      hipLaunchKernelGGL(swap_clear_kernel, dim3(1), dim3(kSwapThreads), 0, stream, p);
+    if (status || p.ws_ints) {
+      const int64_t n = p.ws_ints > 0 ? p.ws_ints : 1;
+      hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((n + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0, stream, p);
       if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
     }
-    CoocParams cp;
     cp.ids = topk_ids;
     cp.expert_to_rank = expert_to_rank;
     cp.T = T;
     cp.K = K;
     cp.E = E;
     cp.G = G;
-    cp.sub_log2 = 0;
-    while ((1 << cp.sub_log2) < K) ++cp.sub_log2;
     cp.ncuts = ncuts;
+    cp.added = parts ? 0 : 1;
     cp.slot_bits = (uint8_t *)(p.ws + at);
-    int64_t chunks = ((int64_t)T + kCoocTokensPerChunkMin - 1) / kCoocTokensPerChunkMin;
-    chunks = chunks < 1 ? 1 : chunks > kCoocChunksMax ? kCoocChunksMax : chunks;
-    const int64_t per_chunk = ((int64_t)T + chunks - 1) / chunks;
-    cp.chunks = (int32_t)chunks;
-    cp.tokens_per_chunk = (int32_t)((per_chunk + kCoocTokens - 1) / kCoocTokens * kCoocTokens);
-    if (cp.tokens_per_chunk < kCoocTokens) cp.tokens_per_chunk = kCoocTokens;
+    const int panels = (E + cooc.panel - 1) / cooc.panel, tiles = (int)(((int64_t)T + kCoocTokens - 1) / kCoocTokens);
+    int chunks = parts ? kCoocChunksMax : kCoocAddedGroups / (panels * ncuts);
+    chunks = chunks > tiles ? tiles : chunks;
+    chunks = chunks < 1 ? 1 : chunks;
+    cp.chunks = chunks;
+    cp.tokens_per_chunk = (tiles + chunks - 1) / chunks * kCoocTokens;
     int max_tiles = 0;
     for (int c = 0; c < kMaxCuts; ++c) {
+      const int64_t table = (int64_t)E * E, cg = (int64_t)E * p.ng[c];
       cp.ng[c] = p.ng[c];
       cp.per[c] = p.per[c];
-      cp.part[c] = (uint16_t *)(p.C[c] + (int64_t)E * E);   // behind the summed C of the cut
-      p.CT[c] = p.C[c] + (int64_t)E * E + kCoocChunksMax * cooc_part_words(E, p.ng[c]);
-      p.CGT[c] = p.CT[c] + (int64_t)E * E;
+      cp.C[c] = p.C[c];
+      cp.CG[c] = p.CG[c];
+      cp.base[c] = p.base[c];
+      cp.part[c] = (uint16_t *)(p.C[c] + table);   // behind the summed C of the cut, and behind them the transposes;
+      p.CT[c] = p.C[c] + table + (parts ? kCoocChunksMax * cooc_part_words(E, p.ng[c]) : 0);   // else they take copies of C
+      p.cg_by_group[c] = parts || (p.copies - 2) * table >= cg;
+      p.CGT[c] = p.cg_by_group[c] ? p.CT[c] + table : p.CG[c];
       if (c < ncuts && reduce_tiles(E, ng[c]) > max_tiles) max_tiles = reduce_tiles(E, ng[c]);
     }
     cp.status = status;
@@ -1082,13 +1120,16 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
                          stream, cp);
       if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
     }
-    hipLaunchKernelGGL(cooc, dim3((unsigned)chunks, (unsigned)ncuts, E > 128 ? 4u : 1u), dim3(kCoocThreads), cooc_lds, stream, cp);
+    hipLaunchKernelGGL(cooc.kernel, dim3((unsigned)chunks, (unsigned)ncuts, (unsigned)panels), dim3(kCoocThreads), cooc.lds, stream, cp);
     if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
     hipLaunchKernelGGL(swap_reduce_kernel, dim3((unsigned)max_tiles, (unsigned)ncuts), dim3(kSwapThreads), 0, stream, p, cp);
     if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
   } else {
     p.transposed = 0;
-    for (int c = 0; c < kMaxCuts; ++c) p.CT[c] = p.CGT[c] = nullptr;
+    for (int c = 0; c < kMaxCuts; ++c) {
+      p.CT[c] = p.CGT[c] = nullptr;
+      p.cg_by_group[c] = 0;
+    }
     p.ws_ints = at;
     p.use_lds = (lds_at <= kSwapLds && swap_factors_lds_ready()) ? 1 : 0;
     hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((p.ws_ints + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads),

@@ -224,6 +224,32 @@ def test_swap_counts_where_the_slots_get_a_kernel(hw, oracle, E, K, T):
     assert st == st_ref == 0 and np.array_equal(Z.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("E,K,G,ng,T", [
+    (32, 8, 8, 8, 128), (33, 1, 64, 64, 129), (64, 4, 16, 4, 2047), (65, 7, 33, 33, 500), (128, 8, 32, 8, 8193), (129, 5, 6, 3, 700),
+    (256, 8, 64, 64, 2049), (96, 9, 12, 12, 1500), (200, 33, 8, 4, 300),        # partial tables, own marks or a byte per slot
+    (257, 8, 32, 32, 1100), (362, 3, 8, 4, 900), (363, 6, 64, 64, 900), (512, 8, 64, 16, 2000),   # added tables; room for CGT or none
+    (300, 9, 8, 8, 400), (513, 4, 8, 8, 300), (300, 2, 4, 2, 0)])               # atomics per slot; no tokens
+def test_swap_counts_at_the_lines_between_the_kernels(hw, oracle, E, K, G, ng, T):
+    """Repeated, dropped and invalid ids, an invalid placement, a workspace full of rubbish, run twice on it."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(E * 100 + K)
+    ids = rng.integers(0, max(2, E if T % 2 else E // 2), (T, K), dtype=np.int32)
+    ids[rng.random((T, K)) < 0.05] = -1
+    e2r = rng.integers(0, G, E).astype(np.int32)
+    ws = torch.randint(-2 ** 31, 2 ** 31 - 1, (int(B.lib().hm_swap_workspace_bytes(T, K, E, ng)) // 4 + 4,), dtype=torch.int32, device="cuda")
+    for broken in (False, True):
+        if broken:
+            e2r[E // 3] = G
+            if T:
+                ids[T // 2, 0] = (-2, E, 2 ** 31 - 1)[T % 3]
+        ref, st_ref = oracle.swap_counts(ids, e2r, G, ng, "incremental")
+        Z, st = torch.full((E, E, ng), -9, dtype=torch.int32, device="cuda"), torch.full((1,), 5, dtype=torch.int32, device="cuda")
+        B.hm_swap_counts(hw.dev(ids), hw.dev(e2r), G, ng, Z, st, workspace=ws)
+        assert np.array_equal(Z.cpu().numpy(), ref), (E, K, G, ng, T, broken)
+        assert int(st.item()) == st_ref, broken
+
+
 @pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (12, [1, 2, 6], 33), (33, [1, 3], 9), (6, [1, 3], 300), (1, [1], 5)])
 def test_swap_select_on_any_counts(hw, oracle, G, U, E):
     """Terms of up to 64 groups and of lengths that are no multiple of four, counts that no swap tensor
