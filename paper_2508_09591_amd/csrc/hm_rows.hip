@@ -27,11 +27,11 @@
 // line, of any length, narrow, odd or few have forms of their own: spread_route and combine_route, at the end, say
 // which call takes which, and the kernels say what each is bound by.
 //
-// Combine has two forms.  With the caller's weights (topk_weights != NULL) every wave merges the
-// K slots of its token itself (2K readlanes) and handles 4 KiB of the row, four rows in flight.
-// With the plan's merged weights (topk_weights == NULL) the first slot of each row is the one
-// slot_keep marks and its weight is one gathered load from row_weight, so the prologue is short
-// enough for 1 KiB segments with all of a token's rows (up to eight) in flight: 3-9 % faster.
+// Combine has two forms.  With the caller's weights (topk_weights != NULL) every wave finds the rows of its
+// token and merges its K slots itself (3K readlanes), the weights behind the first loads.  With the plan's
+// merged weights (topk_weights == NULL) the first slot of each row is the one slot_keep marks and its
+// weight is one gathered load from row_weight: 1 to 3 % faster.  Either way a wave takes 1 KiB of the row
+// with all of the token's rows (up to eight) in flight.
 // Tokens with about one row each (the local-expert stage of a receiver) keep 4 KiB segments, two
 // rows in flight: a 1 KiB segment would be mostly prologue there (0.36 vs 0.28 ms on that stage).
 #include "hm_device.h"
@@ -372,6 +372,71 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
       store_row<ACCESS>(out, p, t, at[i], ROW::pack(acc[i]));
     }
   }
+}
+
+// The same for tokens of two rows or more: a wave owns 1 KiB of the row, like combine_plan_rows_kernel, and goes by slots, eight
+// at a time.  What bounds the call is the rows on their way, so a row's load is issued as soon as its slot is known to be
+// the first with it, and the weights are merged behind the loads.  HIP events, three to sixteen pairs of buffers in turn, segments
+// of 4 KiB with the weights first -> now (the plan's weights), us: 16,384 x 2,048 fp32 with 7 rows 192 -> 183 (180), 8,192 x 7,168
+// with 3.1 rows 79.3 -> 75.9 (74.9), 8,192 x 2,048 with 7.4 49.9 -> 48.1 (47.6), 1,024 x 2,048 9.6 -> 8.2 (7.9), 256 x 4,096 7.7 -> 5.6
+// (5.3).
+template <bool MIX, typename ROW, typename ACCESS>
+__global__ __launch_bounds__(kCombineThreads) void combine_slots_kernel(RowParams p, const typename ROW::elem *__restrict__ y,
+                                                                        int64_t y_rows, const float *__restrict__ topk_weights,
+                                                                        typename ROW::elem *__restrict__ out) {
+  constexpr int R = 8, E = ROW::kPerVec;
+  int t, seg;
+  if (!unit_of_wave<kCombineThreads>(p, t, seg)) return;
+  const int lane = lane_id();
+  int my_row = -1;
+  float my_w = 0.0f;
+  if (lane < p.K) {
+    const int64_t s = (int64_t)t * p.K + lane;
+    const int row = p.slot_row[s];
+    my_w = topk_weights[s];   // on its way with the row; not used where there is none
+    if (row >= 0) {
+      if (row < y_rows) my_row = row;
+      else if (seg == 0) flag(p.status, HM_ERR_CAPACITY);
+    }
+  }
+  int at;
+  const bool in_row = ACCESS::place(p, t, seg * kWave + lane, at);
+  float acc[E], agg = 0.0f, wsum = 0.0f;
+#pragma unroll
+  for (int e = 0; e < E; ++e) acc[e] = 0.0f;
+  for (int k0 = 0; k0 < p.K; k0 += R) {
+    u32x4 r[R];
+    bool first[R];   // slot k0 + j is the first of its row (uniform)
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      r[j] = (u32x4){0u, 0u, 0u, 0u};
+      const int row = k0 + j < p.K ? read_lane(my_row, k0 + j) : -1;
+      first[j] = row >= 0 && __builtin_ctzll(__ballot(my_row == row)) == k0 + j;
+      if (first[j] && in_row) r[j] = load_row<ACCESS>(y, p, row, at);
+    }
+    if (k0 == 0) {   // the fp32 sum, in ascending k, of the weights of the slots that share lane k's row
+      for (int k = 0; k < p.K; ++k) {
+        const int row = read_lane(my_row, k);
+        const float w = read_lane(my_w, k);
+        if (row == my_row) agg = agg + w;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (first[j]) {
+        const float a = read_lane(agg, k0 + j);
+        ROW::fma_into(acc, a, r[j]);
+        wsum = wsum + a;
+      }
+    }
+  }
+  if (!in_row) return;
+  if (MIX) {
+    const float inv_wsum = wsum != 0.0f ? 1.0f / wsum : 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = acc[e] * inv_wsum;
+  }
+  store_row<ACCESS>(out, p, t, at, ROW::pack(acc));
 }
 
 // The same sum with the weights the plan merged: lane k < K holds slot k; the slot slot_keep marks
@@ -892,9 +957,15 @@ static inline CombineShape combine_shape(const hm_plan_out *plan, int32_t T, boo
   sh.waves_per_cu = waves;
   return sh;
 }
+// With the caller's weights, tokens known to have two rows or more take segments of 1 KiB under the same cap (combine_slots_kernel);
+// hm_combine_launch_shape answers for the others.
+static inline CombineShape launched_shape(const hm_plan_out *plan, int32_t T, bool weights_from_plan) {
+  return combine_shape(plan, T, weights_from_plan || rows_per_token(plan, T) >= 2.0);
+}
 template <bool MIX, typename ROW, typename ACCESS>
 static inline auto combine_kernel(const CombineShape &sh, bool weights_from_plan) {
-  if (!weights_from_plan) return combine_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW, ACCESS>;
+  if (!weights_from_plan)
+    return sh.vecs == 1 ? combine_slots_kernel<MIX, ROW, ACCESS> : combine_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW, ACCESS>;
   if (sh.vecs == 1) return combine_plan_rows_kernel<MIX, 1, kCombineRowsPlan, ROW, ACCESS>;
   if (sh.rows == kCombineRowsFew) return combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRowsFew, ROW, ACCESS>;
   return combine_plan_rows_kernel<MIX, kCombineVecs, kCombineRows, ROW, ACCESS>;
@@ -1123,7 +1194,7 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
   dim3 grid;
   // rows the plan's weight array does not cover are treated like rows beyond y
   const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
-  const CombineShape sh = combine_shape(plan, T, from_plan);
+  const CombineShape sh = launched_shape(plan, T, from_plan);
   const Route route = combine_route(row_form(T, K, H, sizeof(elem), y, out), from_plan, sh.vecs);
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
