@@ -98,26 +98,31 @@ __device__ __forceinline__ void for_ids(const int32_t *__restrict__ ids, int T, 
   int t = (int)threadIdx.x, k0 = 0;
   const int32_t *at = ids + (int64_t)t * K;
   const int steps = (T + kOwnerThreads - 1) / kOwnerThreads * ((K + 7) >> 3);
-  int next[8];
+  int id[8], next[8];
+  auto load = [&](int n) {   // n ids of the token are left
 #pragma unroll
-  for (int j = 0; j < 8; ++j) next[j] = -1;
+    for (int j = 0; j < 8; ++j) next[j] = -1;
+    if (t < T) {
+      if (n >= 8) {
+        __builtin_memcpy(next, at, sizeof(next));
+      } else {
+#pragma unroll
+        for (int j = 0; j < 7; ++j)
+          if (j < n) next[j] = at[j];
+      }
+    }
+  };
 #pragma unroll 1
   for (int step = -1; step < steps; ++step) {
-    int id[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) id[j] = next[j];
-    const int n = K - k0;   // ids of the token that are left
+    for (int j = 0; j < 8; ++j) id[j] = step < 0 ? -1 : next[j];
+    const int n = K - k0;
     if (step >= 0) {
       at += n > 8 ? 8 : (int64_t)kOwnerThreads * K - k0;
       t += n > 8 ? 0 : kOwnerThreads;
       k0 = n > 8 ? k0 + 8 : 0;
     }
-    if (t < T) {
-      load_ids(at, K - k0, 0, next);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) next[j] = -1;
-    }
+    load(K - k0);
     if (step < 0) {
       prepare();
       continue;
@@ -127,10 +132,8 @@ __device__ __forceinline__ void for_ids(const int32_t *__restrict__ ids, int T, 
       for (int j = 0; j < 8; ++j) count(id[j]);
     } else {   // an absent id would cost as much as any other
 #pragma unroll
-      for (int j = 0; j < 7; ++j) {
-        if (j >= n) break;
-        count(id[j]);
-      }
+      for (int j = 0; j < 7; ++j)
+        if (j < n) count(id[j]);
     }
     if (n <= 8) end();
   }
@@ -193,10 +196,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 // Whether the counts of a table are taken by owners (hm_expert_load, hm_group_counts): where their steps (of 1,024 tokens and up
 // to eight ids) cost less than the clearing launch, the gap behind it and the atomics.  Graphs of twenty calls, us, clear + count
-// -> owners, load / four levels of groups; eight ids: 1,024 tokens 6.1 -> 3.7 / 8.0 -> 4.0 (one workgroup before), 2,048 6.8 -> 4.0 / 7.2 ->
-// 4.4, 8,192 7.0 -> 6.4 / 7.3 -> 6.7, 16,384 7.6 -> 9.6 / 7.6 -> 9.9; sixteen ids: 4,096 9.0 -> 6.7 / 9.8 -> 7.1, 8,192 9.2 -> 10.2 / 10.0 ->
-// 10.5; one id: 4,096 6.0 -> 5.6 / 7.2 -> 5.9, 8,192 6.2 -> 7.9 / 7.2 -> 8.2.  With few experts many lanes meet at one count (E =
-// 16, 8,192 x 8: 6.4 -> 7.5 / 6.6 -> 6.7).  And a launch less takes 2.4 us off the host.
+// -> owners, load / four levels of groups; eight ids: 1,024 tokens 6.1 -> 3.7 / 8.0 -> 3.9 (one workgroup before), 2,048 6.8 -> 4.0 / 7.2 ->
+// 4.3, 8,192 7.0 -> 6.2 / 7.3 -> 6.5, 16,384 7.6 -> 9.4 / 7.6 -> 9.5; sixteen ids: 4,096 9.0 -> 6.7 / 9.8 -> 7.0, 8,192 9.2 -> 10.1 / 10.0 ->
+// 10.4; one id: 4,096 6.0 -> 5.0 / 7.2 -> 5.2, 8,192 6.2 -> 6.8 / 7.2 -> 7.0.  With few experts many lanes meet at one count (E =
+// 16, 8,192 x 8: 6.4 -> 7.4 / 6.6 -> 6.5).  And a launch less takes 2.4 us off the host.
 static inline bool counts_by_owners(int64_t T, int64_t K, int64_t E) {
   const int64_t steps = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads * ((K + 7) / 8);
   return steps <= (K < 8 || E < 32 ? 4 : 8) && E <= hm::kOwnerMaxE;
