@@ -212,8 +212,9 @@ __device__ __forceinline__ MASK mask_of_token(const uint64_t *bytes, const Token
 }
 
 // Everything up to the wave's counts, in two steps with the barriers between: COUNT_ONLY leaves out what only the
-// maps need.  `hist` and `table` are LDS behind PlanShared, null if not used.
-template <bool COUNT_ONLY>
+// maps need.  `hist` and `table` are LDS behind PlanShared, null if not used.  THREADS: lanes of the workgroup, kPlanThreads
+// unless it is the only one.
+template <bool COUNT_ONLY, int THREADS>
 __device__ __forceinline__ Slot plan_slots(const PlanParams &p, PlanShared &sh, const Tokens &k, int32_t *hist, uint16_t *table,
                                            bool own_status) {
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), tid = (int)threadIdx.x;
@@ -222,7 +223,7 @@ __device__ __forceinline__ Slot plan_slots(const PlanParams &p, PlanShared &sh, 
   // everything that comes from memory, in one round: this lane's slot, its halo slot, the table
   me.s = k.first_slot + tid;
   me.live = me.s < p.nslots;
-  const bool halo = (kPlanThreads % (unsigned)p.K) != 0;
+  const bool halo = p.nblocks > 1 && (kPlanThreads % (unsigned)p.K) != 0;   // one workgroup has all of its tokens
   const int s2 = halo ? halo_slot(p, k) : -1;
   int id2 = -1;
   float w2 = 0.0f;
@@ -238,10 +239,10 @@ __device__ __forceinline__ Slot plan_slots(const PlanParams &p, PlanShared &sh, 
   }
   if (own_status && tid == 0) st_device(p.status, 0);
   if (table)
-    for (int e = tid; e <= p.E; e += kPlanThreads) table[e] = (uint16_t)(e < p.E ? table_entry(p, e) : kBadEntry);
+    for (int e = tid; e <= p.E; e += THREADS) table[e] = (uint16_t)(e < p.E ? table_entry(p, e) : kBadEntry);
   if (loads && hist)
-    for (int e = tid; e < p.E; e += kPlanThreads) hist[e] = 0;
-  for (int i = tid; i < k.tokens * k.words; i += kPlanThreads) sh.dest_bytes[i] = sh.other_bytes[i] = ~0ull;
+    for (int e = tid; e < p.E; e += THREADS) hist[e] = 0;
+  for (int i = tid; i < k.tokens * k.words; i += THREADS) sh.dest_bytes[i] = sh.other_bytes[i] = ~0ull;
   sh.same_dest[wv][lane] = 0;
   if (tid < kWave) {
     sh.rank_cnt[tid] = sh.node_cnt[tid] = sh.all_tot[tid] = sh.all_pre[tid] = 0;
@@ -298,12 +299,13 @@ __device__ __forceinline__ Slot plan_slots(const PlanParams &p, PlanShared &sh, 
 
 // Rows that the waves of the workgroup own at destination `lane`: all of them, and those of the waves before wv.
 __device__ __forceinline__ int byte_sum(uint32_t v, int sum) { return (int)__builtin_amdgcn_sad_u8(v, 0u, (uint32_t)sum); }
+template <int THREADS>
 __device__ __forceinline__ int rows_of_block(const PlanShared &sh, int wv, int &before) {
   const u32x4 c = *(const u32x4 *)sh.wave_cnt[lane_id()];
   int all = 0;
   before = 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < THREADS / kWave / 4; ++i) {
     const int n = wv - 4 * i;   // waves of this word that come before
     all = byte_sum(c[i], all);
     before = byte_sum(n >= 4 ? c[i] : n <= 0 ? 0u : c[i] & ~(~0u << (8 * n)), before);
@@ -317,10 +319,10 @@ extern __shared__ int32_t plan_dyn_lds[];
 __global__ __launch_bounds__(kPlanThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void plan_count_kernel(PlanParams p, int staged) {
   __shared__ PlanShared sh;
   const Tokens k = tokens_of_block(p);
-  plan_slots<true>(p, sh, k, nullptr, staged ? (uint16_t *)plan_dyn_lds : nullptr, blockIdx.x == 0);
+  plan_slots<true, kPlanThreads>(p, sh, k, nullptr, staged ? (uint16_t *)plan_dyn_lds : nullptr, blockIdx.x == 0);
   if ((int)threadIdx.x < p.Dn) {
     int before;
-    p.counts[(int64_t)blockIdx.x * p.Dn + threadIdx.x] = rows_of_block(sh, 0, before);
+    p.counts[(int64_t)blockIdx.x * p.Dn + threadIdx.x] = rows_of_block<kPlanThreads>(sh, 0, before);
   }
   if (p.load_expert) {   // the write kernel accumulates into these with atomics
     const int64_t stride = (int64_t)gridDim.x * kPlanThreads;
@@ -384,7 +386,7 @@ constexpr int kTagShift = 11;   // a workgroup keeps at most 1024 slots per dest
 // and back longer than the kernel otherwise is.
 enum class PlanMode { kAlone, kFused, kWrite };   // the only workgroup; one launch of several; counts already there
 
-template <PlanMode MODE>
+template <PlanMode MODE, int THREADS = kPlanThreads>
 __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix, uint64_t *passed, uint64_t tag, int staged,
                                           int clean) {
   constexpr bool ALONE = MODE == PlanMode::kAlone, FUSED = MODE == PlanMode::kFused;
@@ -400,9 +402,9 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
     if (tid < p.G) st_device(p.load_rank + tid, 0);
     if (tid < p.N) st_device(p.load_node + tid, 0);
   }
-  const Slot me = plan_slots<false>(p, sh, k, hist, table, !(MODE == PlanMode::kWrite) && bid == 0);
+  const Slot me = plan_slots<false, THREADS>(p, sh, k, hist, table, !(MODE == PlanMode::kWrite) && bid == 0);
   int before;
-  const int rows = rows_of_block(sh, wv, before);   // lane: destination
+  const int rows = rows_of_block<THREADS>(sh, wv, before);   // lane: destination
   if (FUSED && wv == 0 && lane < p.Dn) st_device(matrix + (int64_t)bid * p.Dn + lane, (tag << kTagShift) | (uint64_t)rows);
 
   // ---- while the counts travel: what needs no other workgroup
@@ -490,7 +492,7 @@ __device__ __forceinline__ void plan_body(const PlanParams &p, uint64_t *matrix,
   if (go) {
     if (FUSED && clean && tid == 0) st_device(passed + bid, tag);
     if (loads) {   // global atomics first: they complete in the shadow of the map stores
-      for (int e = tid; hist && e < p.E; e += kPlanThreads) {
+      for (int e = tid; hist && e < p.E; e += THREADS) {
         if (ALONE) p.load_expert[e] = hist[e];
         else if (hist[e]) atomicAdd(&p.load_expert[e], hist[e]);
       }
@@ -569,9 +571,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(PlanParams p, 
   plan_body<PlanMode::kFused>(p, matrix, passed, tag, staged, clean);
 }
 
-// A plan of one workgroup: nothing to wait for, nothing to clear, no atomics outside LDS.
-__global__ __launch_bounds__(kPlanThreads) void plan_alone_kernel(PlanParams p) {
-  plan_body<PlanMode::kAlone>(p, nullptr, nullptr, 0, 1, 0);
+// A plan of one workgroup: nothing to wait for, nothing to clear, no atomics outside LDS.  Few slots take few waves,
+// which issue their instructions one after the other (graphs of twenty calls, 1,024 lanes -> as many as the slots want, us: 16 x 8
+// slots 4.45 -> 4.16, 64 x 8 4.60 -> 4.31, 300 x 3 without dedup 4.78 -> 4.40, at rank level 5.06 -> 4.69).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void plan_alone_kernel(PlanParams p) {
+  plan_body<PlanMode::kAlone, THREADS>(p, nullptr, nullptr, 0, 1, 0);
 }
 
 // The last launch of a large plan: the same body without the grid-wide wait.  Held to 96 scalar
@@ -720,7 +725,9 @@ static inline hm_status launch_plan(PlanParams &p, hipStream_t stream) {
   const unsigned table_lds = staged ? (2u * ((unsigned)p.E + 1u) + 15u) & ~15u : 0u;
   const unsigned lds = staged && loads ? (unsigned)p.E * sizeof(int32_t) + table_lds : table_lds;
   if (p.nblocks == 1 && staged) {
-    hipLaunchKernelGGL(plan_alone_kernel, dim3(1), dim3(kPlanThreads), lds, stream, p);
+    if (p.nslots <= 256) hipLaunchKernelGGL(plan_alone_kernel<256>, dim3(1), dim3(256), lds, stream, p);
+    else if (p.nslots <= 512) hipLaunchKernelGGL(plan_alone_kernel<512>, dim3(1), dim3(512), lds, stream, p);
+    else hipLaunchKernelGGL(plan_alone_kernel<kPlanThreads>, dim3(1), dim3(kPlanThreads), lds, stream, p);
     return hm_launch_status();
   }
   if (p.nblocks <= one_launch_limit.load(std::memory_order_relaxed) && p.nblocks <= fused_capacity()) {
