@@ -45,10 +45,10 @@ constexpr int kElemThreads = 256;     // element-wise fallback kernels
 constexpr int kCopyThreads = 128;     // dispatch / transpose: two waves per workgroup ...
 constexpr int kCopyWavesPerCu = 24;   // ... and this many waves resident per CU, where they are capped
 constexpr int kCombineThreads = 256;
-constexpr int kCombineVecs = 4;       // combine with the caller's weights: 16-byte vectors per lane (4 KiB segments),
+constexpr int kCombineVecs = 4;       // combine of tokens with few rows, or an unknown number: 16-byte vectors per lane (4 KiB segments),
 constexpr int kCombineRows = 4;       //   rows whose loads are in flight together
 constexpr int kCombineRowsFew = 2;    //   ... or two, when the tokens are known to have fewer than two rows
-constexpr int kCombineRowsPlan = 8;   // combine with the plan's weights, two rows per token or more: 1 KiB segments,
+constexpr int kCombineRowsPlan = 8;   // combine, two rows per token or more: 1 KiB segments,
                                       //   up to eight rows in flight
 constexpr int kCombineBytesInFlight = 128 * 1024;   // per CU, what the cap on resident waves aims at
 
@@ -384,7 +384,7 @@ template <bool MIX, typename ROW, typename ACCESS>
 __global__ __launch_bounds__(kCombineThreads) void combine_slots_kernel(RowParams p, const typename ROW::elem *__restrict__ y,
                                                                         int64_t y_rows, const float *__restrict__ topk_weights,
                                                                         typename ROW::elem *__restrict__ out) {
-  constexpr int R = 8, E = ROW::kPerVec;
+  constexpr int R = kCombineRowsPlan, E = ROW::kPerVec;
   int t, seg;
   if (!unit_of_wave<kCombineThreads>(p, t, seg)) return;
   const int lane = lane_id();
