@@ -213,8 +213,8 @@ hm_status hm_combine(const void *y_bf16, int64_t y_rows, const float *topk_weigh
  * For tests and tuning: it shows what plan->expected_rows / max_rows_per_token select.  (Narrow rows
  * in the topk_weights == NULL form, and rows that are few, short or no whole 16-byte vectors in
  * either, may take a kernel of a lane per vector or per element; those have no such choice.  With the
- * caller's weights the answer is that of tokens with fewer than two rows; others are merged in the
- * shape of the topk_weights == NULL form, going by slots.)
+ * caller's weights the answer is that of tokens with fewer than two rows; others may be merged in the
+ * shape of the topk_weights == NULL form, going by slots, which depends on T and H too.)
  */
 hm_status hm_combine_launch_shape(int32_t T, int32_t K, int32_t H, const hm_plan_out *plan, int32_t weights_from_plan,
                                   int32_t *vectors_per_lane /* host */, int32_t *rows_in_flight /* host */,

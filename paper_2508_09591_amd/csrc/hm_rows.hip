@@ -30,8 +30,8 @@
 // Combine has two forms.  With the caller's weights (topk_weights != NULL) every wave finds the rows of its
 // token and merges its K slots itself (3K readlanes), the weights behind the first loads.  With the plan's
 // merged weights (topk_weights == NULL) the first slot of each row is the one slot_keep marks and its
-// weight is one gathered load from row_weight: 1 to 3 % faster.  Either way a wave takes 1 KiB of the row
-// with all of the token's rows (up to eight) in flight.
+// weight is one gathered load from row_weight: 1 to 3 % faster.  A wave takes 1 KiB of the row with all of
+// the token's rows (up to eight) in flight, with the caller's weights where short_segments says so, else 4 KiB.
 // Tokens with about one row each (the local-expert stage of a receiver) keep 4 KiB segments, two
 // rows in flight: a 1 KiB segment would be mostly prologue there (0.36 vs 0.28 ms on that stage).
 #include "hm_device.h"
@@ -48,7 +48,7 @@ constexpr int kCombineThreads = 256;
 constexpr int kCombineVecs = 4;       // combine of tokens with few rows, or an unknown number: 16-byte vectors per lane (4 KiB segments),
 constexpr int kCombineRows = 4;       //   rows whose loads are in flight together
 constexpr int kCombineRowsFew = 2;    //   ... or two, when the tokens are known to have fewer than two rows
-constexpr int kCombineRowsPlan = 8;   // combine, two rows per token or more: 1 KiB segments,
+constexpr int kCombineRowsPlan = 8;   // combine, 1 KiB segments (two rows per token or more):
                                       //   up to eight rows in flight
 constexpr int kCombineBytesInFlight = 128 * 1024;   // per CU, what the cap on resident waves aims at
 
@@ -957,11 +957,6 @@ static inline CombineShape combine_shape(const hm_plan_out *plan, int32_t T, boo
   sh.waves_per_cu = waves;
   return sh;
 }
-// With the caller's weights, tokens known to have two rows or more take segments of 1 KiB under the same cap (combine_slots_kernel);
-// hm_combine_launch_shape answers for the others.
-static inline CombineShape launched_shape(const hm_plan_out *plan, int32_t T, bool weights_from_plan) {
-  return combine_shape(plan, T, weights_from_plan || rows_per_token(plan, T) >= 2.0);
-}
 template <bool MIX, typename ROW, typename ACCESS>
 static inline auto combine_kernel(const CombineShape &sh, bool weights_from_plan) {
   if (!weights_from_plan)
@@ -1073,6 +1068,27 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
   if (few || (many_copies && f.T >= (scaled_bf16 ? 65536 : 32768) && f.vecs <= (wide ? 9 : scaled ? 3 : 5))) return Route::kElems;
   const int narrow = f.K == 1 ? 76 : wide && f.K > 2 ? (many_copies && f.T >= 32768 ? 12 : 20) : 32;
   return f.vecs <= narrow && (!scaled_bf16 || f.T >= 2048) ? Route::kFlat : Route::kRagged;
+}
+
+// With the caller's weights: segments of 1 KiB (combine_slots_kernel, under combine_shape's cap) or of 4 KiB (combine_rows_kernel) for
+// tokens known to have two rows or more.  Rows of one short segment always: the lanes of a long one would be idle.  Longer rows
+// where the waves of short segments still run all at once (16 per CU), as each has less to wait for, and where not even
+// those of long ones do, if there are bytes enough to hide that every segment finds the token's rows again, three rows or so for each, and
+// few idle lanes in the last segment.  HIP events, buffers in turn, 4 KiB -> 1 KiB, us: 8,192 x 256 bf16 with 7 rows
+// 15.0 -> 10.2, 16,384 x 512 with 4 22.6 -> 16.6; 1,024 x 1,030 7.5 -> 6.2, but 4,096 x 1,030 14.8 -> 16.6, 4,096 x 640 10.4 ->
+// 11.0, 4,096 x 1,792 with 5 8 % slower; 8,192 x 7,160 158.8 -> 153.6, 3,072 x 2,304 up to 7 % faster, 32,768 x 1,920 8 %, but 16,384 x
+// 1,030 50.7 -> 57.2 and x 4,097 4 % slower.  Of two rows: 32,768 x 1,664 9 % slower, 2,048 x 7,168 4 %.
+static inline bool short_segments(const RowForm &f, double rows) {
+  if (rows < 2.0) return false;
+  if (f.vecs <= kWave) return true;
+  constexpr int64_t kAtOnce = 4096;
+  const int64_t segments = (f.vecs + kWave - 1) / kWave, of_long = (f.vecs + kCombineVecs * kWave - 1) / (kCombineVecs * kWave);
+  if (f.T * segments <= kAtOnce) return true;
+  return f.T * of_long > kAtOnce && (int64_t)f.T * f.vecs * 16 >= 14000000 && rows >= 2.5 &&
+         10 * (int64_t)f.vecs >= 9 * kWave * segments;
+}
+static inline CombineShape launched_shape(const RowForm &f, const hm_plan_out *plan, bool weights_from_plan) {
+  return combine_shape(plan, f.T, weights_from_plan || short_segments(f, rows_per_token(plan, f.T)));
 }
 
 // Combine; vecs_per_lane is that of the wave kernels' launch shape.
@@ -1194,8 +1210,9 @@ static hm_status launch_combine(const void *y, int64_t y_rows, const float *topk
   dim3 grid;
   // rows the plan's weight array does not cover are treated like rows beyond y
   const int64_t rows = from_plan && plan->row_capacity < y_rows ? plan->row_capacity : y_rows;
-  const CombineShape sh = launched_shape(plan, T, from_plan);
-  const Route route = combine_route(row_form(T, K, H, sizeof(elem), y, out), from_plan, sh.vecs);
+  const RowForm form = row_form(T, K, H, sizeof(elem), y, out);
+  const CombineShape sh = launched_shape(form, plan, from_plan);
+  const Route route = combine_route(form, from_plan, sh.vecs);
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((combine_flat_kernel<MIX, ROW>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)y, rows,

@@ -282,6 +282,18 @@ def test_worst_case_buffers_without_a_sync(hw, oracle):
     assert bf16_ulp_distance(hw.bf16_to_host(out_d), refm).max() <= 1
 
 
+@pytest.mark.parametrize("T,H,level", [
+    (1024, 2048, GPU), (1025, 2048, GPU),        # as many waves of 1 KiB as run at once, and four more
+    (1365, 1032, GPU), (1366, 1032, GPU),        # the same with a last segment of one vector
+    (7000, 1000, GPU), (6999, 1000, GPU),        # many bytes, and a few less
+    (3420, 2051, GPU), (3420, 2305, GPU),        # many bytes, last segment of one vector / of half a wave
+    (4096, 1792, NODE), (4097, 1792, NODE),      # as many waves of 4 KiB as run at once, and one more
+])
+def test_segments_of_combine_with_the_callers_weights(hw, oracle, T, H, level):
+    """Both sides of each line between segments of 1 KiB and of 4 KiB."""
+    _run_layer(hw, oracle, W.WORKLOADS["qwen3"], T, H, level, expert_model="scaled")
+
+
 def test_table4_grid(hw, oracle):
     """K in {6,8,10}, E in {64,128,256}, G in {8,16,32} (the grid of the paper's Table IV), all
     three levels, reduced T."""
