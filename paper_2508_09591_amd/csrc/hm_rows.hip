@@ -920,8 +920,7 @@ static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t 
 }
 
 // Launch shape of the combine kernels: 16-byte vectors per lane, rows in flight per wave, and the
-// cap on resident waves per CU (32 = none).  Kept in one place so that the launcher and
-// hm_combine_launch_shape agree.
+// cap on resident waves per CU (32 = none).  The launcher and hm_combine_launch_shape both take it from launched_shape().
 struct CombineShape {
   int vecs, rows, waves_per_cu;
 };
@@ -1242,7 +1241,8 @@ extern "C" hm_status hm_combine_launch_shape(int32_t T, int32_t K, int32_t H, co
   HM_ENTRY_SCOPE;
   hm_status st = check_rows_args(T, K, H, plan, false);
   if (st != HM_OK) return st;
-  const hm::CombineShape sh = hm::combine_shape(plan, T, weights_from_plan != 0);
+  const hm::RowForm rows = hm::row_form(T, K, H, 2, nullptr, nullptr);   // of bf16, aligned
+  const hm::CombineShape sh = hm::launched_shape(rows, plan, weights_from_plan != 0);
   if (vectors_per_lane) *vectors_per_lane = sh.vecs;
   if (rows_in_flight) *rows_in_flight = sh.rows;
   if (waves_per_cu) *waves_per_cu = sh.waves_per_cu;

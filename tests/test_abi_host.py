@@ -247,7 +247,15 @@ def test_combine_launch_shape_follows_the_plan_not_the_buffers(B):
     assert shape(0, int(6.0 * T)) == (1, 8, 20)         # 128 KiB / 6 KiB = 21 waves -> whole workgroups of four
     assert shape(4, int(7.49 * T)) == (1, 8, 16)
     assert shape(8, 64 * T) == (1, 8, 16)               # never below 16 waves per CU
-    assert shape(8, int(7.49 * T), from_plan=0) == (4, 4, 32)   # caller's weights: the merging kernel, no cap
+    # the caller's weights: the same shape where 1 KiB segments are taken, else 4 KiB, four rows in flight, no cap
+    assert shape(8, int(7.49 * T), from_plan=0) == (1, 8, 16)
+    assert shape(8, int(2.51 * T), from_plan=0) == (1, 8, 32)
+    assert shape(8, int(2.49 * T), from_plan=0) == (4, 4, 32)   # too few rows for each segment to find them again
+    assert shape(8, int(1.99 * T), from_plan=0) == (4, 4, 32)
+    assert shape(8, 4 * 292, from_plan=0, tokens=292) == (1, 8, 32)     # 14 waves a token: all run at once
+    assert shape(8, 4 * 293, from_plan=0, tokens=293) == (4, 4, 32)
+    assert shape(8, 4 * 1024, from_plan=0, tokens=1024) == (4, 4, 32)   # 4 KiB segments still run all at once
+    assert shape(8, 4 * 1025, from_plan=0, tokens=1025) == (1, 8, 32)
     assert shape(8, 0, tokens=0) == (1, 8, 16)
     assert L.hm_combine_launch_shape(T, K, H, None, 1, None, None, None) == B.HM_ERR_NULL
     assert L.hm_combine_launch_shape(T, 0, H, ctypes.byref(_plan_struct(B)), 1, None, None, None) == B.HM_ERR_SHAPE

@@ -242,7 +242,7 @@ def test_worst_case_buffers_without_a_sync(hw, oracle):
         plan = B.hm_plan(ids_d, w_d, e2r_d, wl.nodes, wl.ranks_per_node, level)       # no hm_plan_status
         assert plan.c.expected_rows == 0 and plan.c.max_rows_per_token == bound
         assert B.hm_combine_launch_shape(plan, H) == shape, ctx
-        assert B.hm_combine_launch_shape(plan, H, weights_from_plan=False) == (4, 4, 32)
+        assert B.hm_combine_launch_shape(plan, H, weights_from_plan=False) == shape, ctx
         cap = plan.row_capacity                                                       # T * min(K, destinations)
         packed_d = torch.full((cap, H), float("nan"), dtype=torch.bfloat16, device="cuda")
         B.hm_dispatch_pack(x_d, plan, packed_d)
@@ -282,16 +282,21 @@ def test_worst_case_buffers_without_a_sync(hw, oracle):
     assert bf16_ulp_distance(hw.bf16_to_host(out_d), refm).max() <= 1
 
 
-@pytest.mark.parametrize("T,H,level", [
-    (1024, 2048, GPU), (1025, 2048, GPU),        # as many waves of 1 KiB as run at once, and four more
-    (1365, 1032, GPU), (1366, 1032, GPU),        # the same with a last segment of one vector
-    (7000, 1000, GPU), (6999, 1000, GPU),        # many bytes, and a few less
-    (3420, 2051, GPU), (3420, 2305, GPU),        # many bytes, last segment of one vector / of half a wave
-    (4096, 1792, NODE), (4097, 1792, NODE),      # as many waves of 4 KiB as run at once, and one more
+@pytest.mark.parametrize("T,H,level,vecs", [
+    (1024, 2048, GPU, 1), (1025, 2048, GPU, 4),        # as many waves of 1 KiB as run at once, and four more
+    (1365, 1032, GPU, 1), (1366, 1032, GPU, 4),        # the same with a last segment of one vector
+    (7000, 1000, GPU, 1), (6999, 1000, GPU, 4),        # many bytes, and a few less
+    (3420, 2305, GPU, 1), (3420, 2051, GPU, 4),        # many bytes, last segment of half a wave / of one vector
+    (4097, 1856, NODE, 1), (4096, 1856, NODE, 4),      # as many waves of 4 KiB as run at once, and one more
 ])
-def test_segments_of_combine_with_the_callers_weights(hw, oracle, T, H, level):
-    """Both sides of each line between segments of 1 KiB and of 4 KiB."""
-    _run_layer(hw, oracle, W.WORKLOADS["qwen3"], T, H, level, expert_model="scaled")
+def test_segments_of_combine_with_the_callers_weights(hw, oracle, T, H, level, vecs):
+    """Both sides of each line between segments of 1 KiB and of 4 KiB, and that it is there."""
+    from paper_2508_09591_amd import binding as B
+    wl = W.WORKLOADS["qwen3"]
+    r = W.make_routing(wl, T=T)
+    g = hw.GpuPlan(r.topk_ids, r.topk_weights, r.expert_to_rank, wl.nodes, wl.ranks_per_node, level)
+    assert B.hm_combine_launch_shape(g.plan, H, weights_from_plan=False)[0] == vecs
+    _run_layer(hw, oracle, wl, T, H, level, expert_model="scaled")
 
 
 def test_table4_grid(hw, oracle):
