@@ -210,9 +210,9 @@ hm_status hm_combine(const void *y_bf16, int64_t y_rows, const float *topk_weigh
  * hm_combine_mix launch with for this plan where a wave takes a piece of a row: 16-byte vectors
  * per lane, rows whose loads are in flight per wave, resident waves per CU the launch allows (32 =
  * no cap).  weights_from_plan != 0 asks about the topk_weights == NULL form.
- * For tests and tuning: it shows what plan->expected_rows / max_rows_per_token select.  The caller's
- * weights make it depend on T and on the bytes of a row too: H counts elements of two bytes, so ask
- * with 2 H for hm_combine_f32.  (Narrow rows in the topk_weights == NULL form, and rows that are few,
+ * For tests and tuning: it shows what plan->expected_rows / max_rows_per_token select.  With the
+ * caller's weights only expected_rows counts, and T and the bytes of a row too: H counts elements
+ * of two bytes, so ask with 2 H for hm_combine_f32.  (Narrow rows in the topk_weights == NULL form, and rows that are few,
  * short or no whole 16-byte vectors in either, may take a kernel of a lane per vector or per
  * element; those have no such choice.)
  */

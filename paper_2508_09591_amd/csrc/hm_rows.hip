@@ -1076,8 +1076,11 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
 // few idle lanes in the last segment.  HIP events, buffers in turn, 4 KiB -> 1 KiB, us: 8,192 x 256 bf16 with 7 rows
 // 15.0 -> 10.2, 16,384 x 512 with 4 22.6 -> 16.6; 1,024 x 1,030 7.5 -> 6.2, but 4,096 x 1,030 14.8 -> 16.6, 4,096 x 640 10.4 ->
 // 11.0, 4,096 x 1,792 with 5 8 % slower; 8,192 x 7,160 158.8 -> 153.6, 3,072 x 2,304 up to 7 % faster, 32,768 x 1,920 8 %, but 16,384 x
-// 1,030 50.7 -> 57.2 and x 4,097 4 % slower.  Of two rows: 32,768 x 1,664 9 % slower, 2,048 x 7,168 4 %.
-static inline bool short_segments(const RowForm &f, double rows) {
+// 1,030 50.7 -> 57.2 and x 4,097 4 % slower.  Of two rows: 32,768 x 1,664 9 % slower, 2,048 x 7,168 4 %.  Only a known row count
+// counts: tokens of one row or so under a bound of eight take 49 -> 81 us (8,192 x 7,168 bf16, 1.2 rows), 18 -> 25 (x 2,048), 62 -> 96
+// (32,768 x 2,048, 1.6 rows), which is more than the 3 to 12 % that those of many rows would gain.
+static inline bool short_segments(const RowForm &f, const hm_plan_out *plan) {
+  const double rows = plan->expected_rows > 0 && f.T > 0 ? (double)plan->expected_rows / (double)f.T : 0.0;
   if (rows < 2.0) return false;
   if (f.vecs <= kWave) return true;
   constexpr int64_t kAtOnce = 4096;
@@ -1087,7 +1090,7 @@ static inline bool short_segments(const RowForm &f, double rows) {
          10 * (int64_t)f.vecs >= 9 * kWave * segments;
 }
 static inline CombineShape launched_shape(const RowForm &f, const hm_plan_out *plan, bool weights_from_plan) {
-  return combine_shape(plan, f.T, weights_from_plan || short_segments(f, rows_per_token(plan, f.T)));
+  return combine_shape(plan, f.T, weights_from_plan || short_segments(f, plan));
 }
 
 // Combine; vecs_per_lane is that of the wave kernels' launch shape.

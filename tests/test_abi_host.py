@@ -256,6 +256,7 @@ def test_combine_launch_shape_follows_the_plan_not_the_buffers(B):
     assert shape(8, 4 * 293, from_plan=0, tokens=293) == (4, 4, 32)
     assert shape(8, 4 * 1024, from_plan=0, tokens=1024) == (4, 4, 32)   # 4 KiB segments still run all at once
     assert shape(8, 4 * 1025, from_plan=0, tokens=1025) == (1, 8, 32)
+    assert shape(8, 0, from_plan=0) == shape(4, 0, from_plan=0) == (4, 4, 32)   # a bound: the tokens may have one row each
     assert shape(8, 0, tokens=0) == (1, 8, 16)
     assert L.hm_combine_launch_shape(T, K, H, None, 1, None, None, None) == B.HM_ERR_NULL
     assert L.hm_combine_launch_shape(T, 0, H, ctypes.byref(_plan_struct(B)), 1, None, None, None) == B.HM_ERR_SHAPE
