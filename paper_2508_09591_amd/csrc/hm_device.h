@@ -194,15 +194,29 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 }  // namespace hm
 
-// Whether the counts of a table are taken by owners (hm_expert_load, hm_group_counts): where their steps (of 1,024 tokens and up
-// to eight ids) cost less than the clearing launch, the gap behind it and the atomics.  Graphs of twenty calls, us, clear + count
-// -> owners, load / four levels of groups; eight ids: 1,024 tokens 6.1 -> 3.7 / 8.0 -> 3.9 (one workgroup before), 2,048 6.8 -> 4.0 / 7.2 ->
-// 4.3, 8,192 7.0 -> 6.2 / 7.3 -> 6.5, 16,384 7.6 -> 9.4 / 7.6 -> 9.5; sixteen ids: 4,096 9.0 -> 6.7 / 9.8 -> 7.0, 8,192 9.2 -> 10.1 / 10.0 ->
-// 10.4; one id: 4,096 6.0 -> 5.0 / 7.2 -> 5.2, 8,192 6.2 -> 6.8 / 7.2 -> 7.0.  With few experts many lanes meet at one count (E =
-// 16, 8,192 x 8: 6.4 -> 7.4 / 6.6 -> 6.5).  And a launch less takes 2.4 us off the host.
-static inline bool counts_by_owners(int64_t T, int64_t K, int64_t E) {
-  const int64_t steps = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads * ((K + 7) / 8);
-  return steps <= (K < 8 || E < 32 ? 4 : 8) && E <= hm::kOwnerMaxE;
+// Which kernel takes the counts of a table (hm_expert_load, hm_group_counts); outputs: the groups of all levels, or ranks and nodes.
+//  * kOwners where the rounds of 1,024 tokens cost less than the clearing launch, the gap behind it and the atomics.  A round costs
+//    0.38 us per eight ids (0.47 if there are more) and for the ids that are left, which take a load of a word each, 0.45 up to
+//    three, 0.8 for four and five, 1.0 and 1.35 for six and seven, the more the longer the tokens; what it saves is 2 us, 0.036 per output (the
+//    ballots of the other kernels), 0.1 per id of a load and 0.06 per id beyond eight.  Graphs of ten calls, us, clear + count
+//    -> owners: group counts of 8,192 x 8 with four levels of 32 ranks 7.9 -> 7.1, with one of 16 6.5 -> 6.9 (6,144 tokens: 6.4 -> 6.1);
+//    4,096 x 2 6.1 -> 5.6, x 4 6.1 -> 7.0, x 7 6.2 -> 8.6 (2,048 x 7 with four levels 7.7 -> 6.1); loads of 8,192 x 8 on 32 ranks 7.7 -> 6.7,
+//    4,096 x 7 7.5 -> 8.7, x 12 8.3 -> 8.7, 2,048 x 31 10.5 -> 11.8.  Few experts make many lanes meet at one count (E = 32, 16
+//    ranks, 8,192 x 8: 7.1 -> 7.5).  And a launch less takes 2.4 us off the host.
+//  * kAlone, one workgroup, for a few tokens with few outputs (and, for loads, ids), as an owner works out an entry of a table per
+//    expert: 64 tokens, groups of 8 ranks, E = 128 3.85, owners 4.05, E = 2,048 4.05, 4.5; loads of one id, 8 ranks 3.75, 4.1; but
+//    four levels of 32 ranks 5.6, 4.4.  And, as far as it goes, where the owners' table has no room.
+enum class CountRoute { kAlone, kOwners, kAdded };
+static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t outputs, bool loads, bool alone_fits) {
+  const int64_t few = E / 128 + (!loads ? 8 : K == 1 ? 20 : K <= 3 ? 10 : -E / 128);
+  if (alone_fits && outputs <= few && (T <= 256 || (T <= 512 && K <= 2 && outputs <= 10 + E / 128)) && K <= 8) return CountRoute::kAlone;
+  static const int left[8] = {0, 45, 45, 45, 80, 80, 100, 135}, longer[4] = {4, 5, 6, 9};   // hundredths of a us, quarters
+  const int64_t rounds = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads, steps = rounds * ((K + 7) / 8);
+  const int64_t round = K / 8 * (K > 8 || (loads && E < 64) ? 47 : 38) + left[K % 8] * longer[K < 32 ? K / 8 : 3] / 4;
+  const int64_t saved = 200 + outputs * 36 / 10 + (loads ? 10 * K : 0) + (K > 8 ? 6 * (K - 8) : 0);
+  const bool pays = steps <= (K < 8 || E < 32 ? 4 : 8) && (rounds <= 1 || rounds * round <= saved);
+  if (pays && E <= hm::kOwnerMaxE) return CountRoute::kOwners;
+  return alone_fits ? CountRoute::kAlone : CountRoute::kAdded;
 }
 
 // Host-side argument checks shared by the entry points.

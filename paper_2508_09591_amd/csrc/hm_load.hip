@@ -173,14 +173,14 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   p.load_rank = load_rank;
   p.load_node = load_node;
   p.status = status;
-  if (counts_by_owners(T, K, E)) {
+  const CountRoute route = count_route(T, K, E, p.G + p.N, true, T <= kAloneTokens && E <= kLdsExperts);
+  if (route == CountRoute::kOwners) {
     const int expert_blocks = (E + kOwnerExperts - 1) / kOwnerExperts, rank_blocks = (p.G + kOwnerGroups - 1) / kOwnerGroups;
     const int node_blocks = (p.N + kOwnerGroups - 1) / kOwnerGroups;
     hipLaunchKernelGGL(load_owner_kernel, dim3((unsigned)(expert_blocks + rank_blocks + node_blocks)), dim3(kOwnerThreads), 0, stream, p,
                        expert_blocks, rank_blocks);
     return hm_launch_status();
   }
-  const bool alone = T <= kAloneTokens && E <= kLdsExperts;   // more experts than the owners' table holds
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
   if (blocks > 1024) blocks = 1024;
   // Staging pays where a lane looks more slots up than it stages entries (us, staged / from memory: E = 4,096, 1,025 tokens, K = 1
@@ -188,7 +188,7 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   // K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).
   const int64_t lookups = blocks ? ((int64_t)T + blocks * kLoadThreads - 1) / (blocks * kLoadThreads) * K : 0;
   p.staged = E <= kStagedExperts && lookups * kLoadThreads > E;
-  if (alone) {
+  if (route == CountRoute::kAlone) {
     hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
     return hm_launch_status();
   }

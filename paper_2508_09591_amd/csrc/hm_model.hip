@@ -193,14 +193,18 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
   p.counts = counts;
   p.status = status;
   hipStream_t stream = (hipStream_t)hip_stream;
-  if (counts_by_owners(T, K, E)) {
+  int outputs = 0;
+  for (int l = 0; l < depth; ++l) outputs += groups[l];
+  // one workgroup that looks many slots up in memory is slower than several (E = 5,000, 1,024 tokens, K = 64: 32.4 us, 19.8)
+  const bool alone_fits = T <= kAloneTokens && (E <= kStagedExperts || (int64_t)T * K <= 32768);
+  const CountRoute route = count_route(T, K, E, outputs, false, alone_fits);
+  if (route == CountRoute::kOwners) {
     int blocks = 0;
     for (int l = 0; l < depth; ++l) blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
     hipLaunchKernelGGL(group_owner_kernel, dim3((unsigned)blocks), dim3(kOwnerThreads), 0, stream, p);
     return hm_launch_status();
   }
-  // one workgroup that looks many slots up in memory is slower than several (E = 5,000, 1,024 tokens, K = 64: 32.4 us, 19.8)
-  if (T <= kAloneTokens && (E <= kStagedExperts || (int64_t)T * K <= 32768)) {
+  if (route == CountRoute::kAlone) {
     hipLaunchKernelGGL((group_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
     return hm_launch_status();
   }

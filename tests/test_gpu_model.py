@@ -116,9 +116,12 @@ def test_counts_of_no_tokens(hw, E):
 
 
 @pytest.mark.parametrize("T,K,E,nodes,rpn", [
-    (1, 1, 1, 1, 1), (1024, 3, 65, 3, 5), (4096, 7, 64, 32, 2), (4097, 7, 64, 32, 2),        # up to four steps of fewer than eight ids
+    (1, 1, 1, 1, 1), (256, 3, 16, 2, 2), (512, 2, 300, 2, 4), (513, 2, 300, 2, 4), (257, 8, 2048, 1, 16),   # one workgroup, then owners
+    (1024, 3, 65, 3, 5), (4096, 7, 64, 32, 2), (4097, 7, 64, 32, 2),        # up to four steps of fewer than eight ids
+    (3072, 4, 40, 2, 2), (2049, 6, 40, 2, 8), (1025, 7, 40, 2, 2), (2048, 15, 64, 2, 8), (3072, 12, 128, 4, 8),   # loads by owners, groups added
     (8192, 8, 4096, 8, 8), (8193, 8, 63, 2, 7), (4096, 9, 128, 1, 64), (1023, 64, 130, 4, 4),   # up to eight steps of eight
-    (2049, 8, 4097, 4, 8)])                                                                  # one expert too many for the owners' table
+    (7168, 8, 32, 2, 8), (8192, 8, 32, 2, 8), (1024, 33, 64, 2, 2), (1025, 33, 64, 2, 2),       # few experts, long tokens
+    (2049, 8, 4097, 4, 8), (600, 8, 5000, 4, 8), (1024, 40, 20, 2, 2)])     # no room in the owners' table; many ids of few experts
 def test_counts_by_owners_and_beyond(hw, oracle, T, K, E, nodes, rpn):
     """Both calls on both sides of the rule that gives each workgroup its own outputs: dropped, repeated and invalid ids, an
     invalid placement, outputs that hold rubbish, entries behind a level's groups cleared."""
