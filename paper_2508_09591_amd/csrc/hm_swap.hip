@@ -363,7 +363,8 @@ __device__ __forceinline__ void add_tile(int32_t *table, const i32x16 &acc, int 
 //
 // Per tile: mark | barrier | multiply | barrier.  Nothing waits for a tile to be cleared: with one column of tiles the rows of A
 // are read by one wave, which clears them behind its reads; with two, the lanes that marked them clear them (a
-// token's places belong to one wave, so it may mark the next tile without a barrier).  S and M, which several
+// token's places belong to one wave, so it may mark the next tile without a barrier), or, for K > 8, whose tokens are
+// spread over waves, all of them clear A behind a third barrier.  S and M, which several
 // waves read, are there twice, and the one not in use is cleared while the other is multiplied.
 constexpr int kCoocThreads = 1024;
 constexpr int kCoocWaves = kCoocThreads / kWave;
@@ -395,9 +396,12 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   }
   __syncthreads();
 
+  // A token's marks lie in 2^sub_log2 places where a lane works a token out, one after the other where they are read: with places
+  // padded to a power of two too, a tile of 33 slots cost twice the turns (E = 256, 40,000 tokens, four cuts: 165 us, now 128).
   const int sub_log2 = p.sub_log2, sub = 1 << sub_log2;
-  const int places = kCoocTokens << sub_log2;                    // of a tile
-  const int stage_tokens = kCoocStaged >> sub_log2;              // 128 at least
+  const int per_token = OWN_SLOTS ? sub : p.K, places = kCoocTokens * per_token;   // of a tile
+  const int stage_tokens = OWN_SLOTS ? kCoocStaged >> sub_log2 : kCoocStaged / places * kCoocTokens;   // 128 at least
+  const uint32_t k_recip20 = ((1u << 20) + (uint32_t)p.K - 1u) / (uint32_t)p.K;   // exact below 8,192 for K <= 64
   const int64_t t_begin = (int64_t)blockIdx.x * p.tokens_per_chunk;
   const int64_t t_end = min((int64_t)p.T, t_begin + p.tokens_per_chunk);
 
@@ -445,37 +449,41 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
       }
     } else {
       constexpr int kAhead = 8;   // loads of a lane in flight together
+      const int slots = tokens * p.K;
+      const int32_t *const ids = p.ids + stage0 * p.K;
+      const uint8_t *const slot_bits = p.slot_bits + stage0 * p.K;
 #pragma unroll 1
       for (int i0 = tid; i0 < last; i0 += kAhead * kCoocThreads) {
         int id[kAhead], bits[kAhead];
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
-          const int i = i0 + j * kCoocThreads, t = min(i >> sub_log2, tokens - 1), k = min(i & (sub - 1), p.K - 1);
-          const int64_t slot = (stage0 + t) * p.K + k;
-          id[j] = p.ids[slot];
-          bits[j] = p.slot_bits[slot];
+          const int i = min(i0 + j * kCoocThreads, slots - 1);
+          id[j] = ids[i];
+          bits[j] = slot_bits[i];
         }
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
           const int i = i0 + j * kCoocThreads;
-          const bool in = (i >> sub_log2) < tokens && (i & (sub - 1)) < p.K && (bits[j] & 1);
-          if (i < last) staged[i] = in ? mark_of(id[j], group_of[id[j] + 1], (bits[j] >> (1 + cut)) & 1) : 0u;
+          const uint32_t group = group_of[min((uint32_t)id[j] + 1u, (uint32_t)p.E + 1u)];
+          const uint32_t m = mark_of(id[j], group, (bits[j] >> (1 + cut)) & 1);
+          if (i < last) staged[i] = i < slots && (bits[j] & 1) ? m : 0u;
         }
       }
     }
     __syncthreads();
 #pragma unroll 1
     for (int first_place = 0; first_place < last; first_place += places) {
-      int wrote = -1;   // where in A this lane's first mark went
+      int wrote = -1;   // where in A this lane's mark went
 #pragma unroll 1
       for (int i = tid; i < places; i += kCoocThreads) {
         const uint32_t m = staged[first_place + i];
         if (!(m & kMarks)) continue;
-        const int token = i >> sub_log2, expert = (int)(m & 0x1FFu), column = expert - kCoocPanel * panel;
+        const int token = OWN_SLOTS ? i >> sub_log2 : (int)((uint32_t)i * k_recip20 >> 20);
+        const int expert = (int)(m & 0x1FFu), column = expert - kCoocPanel * panel;
         if (m & kAlone) {
           const int at = expert * kCoocStride + token;
           a_tile[at] = 1;
-          wrote = i == tid ? at : wrote;
+          if (OWN_SLOTS) wrote = at;
         }
         if ((unsigned)column < (unsigned)kCoocPanel) sm[column * kCoocStride + token] = 1;
         sm[(kCoocPanel + (m >> 16 & 0x3Fu)) * kCoocStride + token] = 1;
@@ -514,12 +522,13 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
       sm = sm_next;
       sm_next = used;
       __syncthreads();
-      if (COLS > 1) {    // two waves read a row of A: cleared by the lanes that marked it
-        if (wrote >= 0) a_tile[wrote] = 0;
+      if (COLS > 1) {   // two waves read a row of A
+        if (OWN_SLOTS) {   // a lane has one place of a tile: it clears what it marked
+          if (wrote >= 0) a_tile[wrote] = 0;
+        } else {   // the slots of a token are spread over waves
 #pragma unroll 1
-        for (int i = tid + kCoocThreads; i < places; i += kCoocThreads) {
-          const uint32_t m = staged[first_place + i];
-          if (m & kAlone) a_tile[(m & 0x1FFu) * kCoocStride + (i >> sub_log2)] = 0;
+          for (int i = tid; i < 32 * NE * kCoocStride / 16; i += kCoocThreads) ((i32x4 *)a_tile)[i] = zero;
+          __syncthreads();
         }
       }
     }

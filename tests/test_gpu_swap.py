@@ -227,6 +227,7 @@ def test_swap_counts_where_the_slots_get_a_kernel(hw, oracle, E, K, T):
 @pytest.mark.parametrize("E,K,G,ng,T", [
     (32, 8, 8, 8, 128), (33, 1, 64, 64, 129), (64, 4, 16, 4, 2047), (65, 7, 33, 33, 500), (128, 8, 32, 8, 8193), (129, 5, 6, 3, 700),
     (256, 8, 64, 64, 2049), (96, 9, 12, 12, 1500), (200, 33, 8, 4, 300),        # partial tables, own marks or a byte per slot
+    (130, 9, 8, 8, 18500), (64, 17, 8, 4, 9001), (256, 33, 64, 64, 5000), (100, 64, 32, 32, 4500),   # ... several tiles and stages
     (257, 8, 32, 32, 1100), (362, 3, 8, 4, 900), (363, 6, 64, 64, 900), (512, 8, 64, 16, 2000),   # added tables; room for CGT or none
     (300, 9, 8, 8, 400), (513, 4, 8, 8, 300), (300, 2, 4, 2, 0)])               # atomics per slot; no tokens
 def test_swap_counts_at_the_lines_between_the_kernels(hw, oracle, E, K, G, ng, T):
