@@ -9,7 +9,8 @@
 // with r and c exchanged for g_r: no O(T K E) walk over all unselected experts, and the per-pair
 // work is an embarrassingly parallel E^2 ng kernel.  The tables come from int8 matrix products on
 // the matrix cores for E <= 512 (further down), from O(T K (K + ng)) atomic updates, one lane per
-// routing slot, beyond that (and for E > 256 with more than eight slots per token).
+// routing slot, beyond that, for E > 256 with more than eight slots per token, and where the products would have
+// too little to do (atomics_pay).
 #include "hm_device.h"
 
 namespace hm {
@@ -1005,7 +1006,7 @@ static inline int64_t swap_slot_ints(int64_t T, int64_t K, int64_t E) { return s
 typedef void (*cooc_kernel_t)(CoocParams);
 struct CoocLaunch {
   cooc_kernel_t kernel;
-  int panel;
+  int ne, panel;
   size_t lds;
 };
 template <int NE, bool OWN_SLOTS>
@@ -1017,7 +1018,7 @@ static CoocLaunch cooc_launch() {
     if (e != hipSuccess) (void)hipGetLastError();   // not sticky: do not let it fail the next launch check
     return e == hipSuccess;
   }();
-  return {swap_cooc_kernel<NE, OWN_SLOTS>, 32 * cooc_cols(NE), granted ? bytes : 0};
+  return {swap_cooc_kernel<NE, OWN_SLOTS>, NE, 32 * cooc_cols(NE), granted ? bytes : 0};
 }
 template <bool OWN_SLOTS>
 static CoocLaunch cooc_launch_for(int E) {
@@ -1026,6 +1027,43 @@ static CoocLaunch cooc_launch_for(int E) {
          : E <= 128 ? cooc_launch<4, OWN_SLOTS>()
          : E <= 256 ? cooc_launch<8, OWN_SLOTS>()
                     : cooc_launch<16, true>();   // there is no room for the bytes of swap_slots_kernel beyond
+}
+
+static inline int cooc_chunks(const CoocLaunch &cooc, bool parts, int64_t T, int64_t E, int ncuts) {
+  const int64_t panels = (E + cooc.panel - 1) / cooc.panel, tiles = (T + kCoocTokens - 1) / kCoocTokens;
+  const int64_t most = parts ? kCoocChunksMax : kCoocAddedGroups / (panels * ncuts), chunks = most > tiles ? tiles : most;
+  return (int)(chunks < 1 ? 1 : chunks);
+}
+
+// Whether atomics per slot are faster than matrix products whose chunks are added up: with few slots per token or few groups, as
+// the products take the same time however few marks a tile holds.  Two straight lines, us, through 4,701 shapes (256 < E <= 512, up to 520,000
+// tokens; E <= 256, 522,241 to 800,000; one to eight slots, one to four cuts; ids drawn evenly): Z, the updates of C (a slot's K - 1
+// others where it is alone in its group) and of L0, L and CG (in LDS or in memory), and the workgroups that put their tables
+// together; against a time per tile of 128 tokens.  One or two tiles are matrices at any rate, but for next to no groups.  A popular few
+// experts make only the atomics slower, so they have to be ahead by a fifth: of 4,105 shapes of more than two groups with even ids 277 lose
+// more than 3 % by that (one half as much again) and 9 the other way round, of 2,980 with a Zipf router 71 and 131.
+// Atomics / matrices: E = 512, cuts of 4 and 32, 65,536 tokens: K = 1 53 / 107, 2 63 / 110, 4 103 / 117 (Zipf 181 / 112), 8 (30,000
+// tokens) 131 / 74; E = 260, 2, 4 and 8, 16,384 tokens: K = 1 24 / 34, 8 53 / 40; E = 256, 530,000 tokens: K = 1 46 / 145, 2 108 /
+// 153, 3 220 / 157.
+static bool atomics_pay(int64_t T, int64_t K, int64_t E, int ncuts, const int32_t *ng, bool in_lds, int ne, int chunks) {
+  double groups = 0.0, others = 0.0, touched = 1.0;   // per slot: updates of C, words of L0, L and CG
+  for (int c = 0; c < ncuts; ++c) {
+    double alone = (double)(K - 1);
+    for (int64_t k = 1; k < K; ++k) alone *= 1.0 - 1.0 / ng[c];
+    groups += ng[c];
+    others += alone;
+    touched += 1.0 + (double)(K < ng[c] ? K : ng[c]);
+  }
+  const int64_t tiles = ((T + kCoocTokens - 1) / kCoocTokens + chunks - 1) / chunks;   // of a workgroup
+  if (tiles <= 2 && groups > 4.0) return false;
+  int64_t lanes = 1;
+  while (lanes < K) lanes *= 2;
+  const double pairs = (double)(E * E) * 1e-6, slots = (double)(T * K) * 1e-6, filled = (double)(T * lanes) / (256.0 * kFactorThreads);
+  const double flush = filled < 1.0 ? filled : 1.0;   // of 256 workgroups
+  const double atomics = in_lds ? 10.0 + 4.3 * pairs * groups + slots * (28.0 * others + 1.4 * touched) + 3.2 * ncuts + 6.6 * flush
+                                : 45.0 + 2.4 * pairs * groups + 54.0 * slots * touched + 59.0 * flush;
+  const double matrices = 15.0 + 6.0 * pairs * ncuts + 0.86 * pairs * groups + (double)tiles * (0.64 + 0.031 * (double)(ne + K));
+  return 1.2 * atomics < matrices;
 }
 
 static inline bool swap_cuts_ok(int32_t G, int32_t ncuts, const int32_t *ng) {
@@ -1077,14 +1115,16 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
   }
   p.status = status;
   // By matrices where there is room for the chunks' tables; beyond that (E > 256, or more than 522,240 tokens) the chunks
-  // are added to cleared tables, as long as the marks of the slots need no room either.
+  // are added to cleared tables, as long as the marks of the slots need no room either and that is the faster way.
   const bool parts = swap_has_parts(E, T), own_slots = K <= kCoocOwnK;
+  const bool in_lds = lds_at <= kSwapLds && swap_factors_lds_ready();
   CoocParams cp;
   cp.sub_log2 = 0;
   while ((1 << cp.sub_log2) < K) ++cp.sub_log2;
-  CoocLaunch cooc = {nullptr, 0, 0};
+  CoocLaunch cooc = {nullptr, 0, 0, 0};
   if (parts || (own_slots && E <= kCoocMaxE)) cooc = own_slots ? cooc_launch_for<true>(E) : cooc_launch_for<false>(E);
-  if (cooc.lds != 0) {
+  const int chunks = cooc.lds != 0 ? cooc_chunks(cooc, parts, T, E, ncuts) : 0;
+  if (cooc.lds != 0 && (parts || !atomics_pay(T, K, E, ncuts, ng, in_lds, cooc.ne, chunks))) {
     p.ws_ints = parts ? 0 : at;   // parts are written in full by the kernels below: only the status word needs clearing
     p.use_lds = 0;
     p.transposed = 1;
@@ -1103,9 +1143,6 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
     cp.added = parts ? 0 : 1;
     cp.slot_bits = (uint8_t *)(p.ws + at);
     const int panels = (E + cooc.panel - 1) / cooc.panel, tiles = (int)(((int64_t)T + kCoocTokens - 1) / kCoocTokens);
-    int chunks = parts ? kCoocChunksMax : kCoocAddedGroups / (panels * ncuts);
-    chunks = chunks > tiles ? tiles : chunks;
-    chunks = chunks < 1 ? 1 : chunks;
     cp.chunks = chunks;
     cp.tokens_per_chunk = (tiles + chunks - 1) / chunks * kCoocTokens;
     int max_tiles = 0;
@@ -1140,7 +1177,7 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
       p.cg_by_group[c] = 0;
     }
     p.ws_ints = at;
-    p.use_lds = (lds_at <= kSwapLds && swap_factors_lds_ready()) ? 1 : 0;
+    p.use_lds = in_lds ? 1 : 0;
     hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((p.ws_ints + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads),
                        0, stream, p);
     if (hm_launch_status() != HM_OK) return HM_ERR_HIP;

@@ -49,7 +49,9 @@ def test_swap_counts_small_against_definition(hw, oracle):
 
 @pytest.mark.parametrize("G,ng,E,T,K", [(8, 4, 200, 500, 12), (64, 64, 256, 300, 20), (8, 8, 300, 400, 5),
                                           (4, 2, 33, 1000, 64), (32, 32, 256, 5000, 8), (16, 8, 96, 4097, 3),
-                                          (64, 64, 512, 700, 6)])      # the last: tables too large for LDS
+                                          (64, 64, 512, 700, 6),       # chunks added up, with tables that atomics would keep in memory
+                                          (64, 64, 520, 40011, 6),     # atomics per slot, L0, L and CG in memory, several rounds per wave
+                                          (8, 8, 300, 20000, 9), (16, 4, 600, 3000, 3)])   # ... in LDS
 def test_swap_counts_other_shapes(hw, oracle, G, ng, E, T, K):
     """K from 3 to 64 (sub-groups of 4 to 64 lanes per token), several rounds per workgroup, expert
     counts from 33 to 300, dropped slots: against the oracle's incremental update (itself pinned
@@ -129,7 +131,11 @@ def test_swap_counts_full_size(hw, oracle, name, placement):
                                           (128, 32, 8, 40000, [4, 32]),       # ragged: the last chunk ends inside a stage
                                           (96, 16, 3, 20000, [16]),           # four lanes per token: lanes beyond 128 tokens idle
                                           (200, 8, 24, 9000, [2, 8]),         # 32 lanes per token: four passes per tile
-                                          (48, 8, 2, 523000, [4])])           # more tokens than 16 chunks of 16-bit counts hold: the path with atomics
+                                          (48, 8, 2, 523000, [4]),            # more tokens than 16 chunks of 16-bit counts hold: chunks added up
+                                          (250, 8, 6, 523001, [8]),           # ... two columns of tiles
+                                          (64, 8, 1, 523000, [8]),            # ... and few slots: atomics per slot
+                                          (512, 64, 8, 9001, [8, 16, 32, 64]), (320, 32, 5, 12001, [4, 8, 16, 32]), (300, 32, 3, 30000, [32]),   # added, E > 256
+                                          (300, 32, 3, 30000, [4, 32]), (300, 32, 2, 60000, [4, 32]), (600, 32, 3, 5000, [4, 16])])   # ... the last two atomics, several cuts
 def test_swap_counts_long_chunks(hw, oracle, E, G, K, T, cuts):
     """Token counts beyond what one fetch stage of a chunk covers (16 chunks x 1,024 slots-per-lane
     passes), so the matrix kernel's outer loop, its clamped loads at a ragged end and the
@@ -212,9 +218,9 @@ def test_swap_select_parity(hw, oracle):
     print("d=4 gamma=5 best pair", pair, "time", float(bt.item()), "no swap", Qg[0, 0])
 
 
-@pytest.mark.parametrize("E,K,T", [(24, 8, 16384), (24, 8, 16385), (130, 3, 16385), (40, 1, 17000)])
+@pytest.mark.parametrize("E,K,T", [(24, 8, 16384), (24, 8, 16385), (130, 3, 16385), (40, 1, 17000), (24, 9, 16385), (130, 9, 16384), (40, 16, 17000)])
 def test_swap_counts_where_the_slots_get_a_kernel(hw, oracle, E, K, T):
-    """Token counts on either side of the one up to which the matrix kernel works the slots out itself."""
+    """Up to eight slots, which the matrix kernel works out itself for any number of tokens, and more, which have a kernel of their own."""
     rng = np.random.default_rng(T + K)
     ids = rng.integers(0, E, (T, K), dtype=np.int32)
     ids[rng.random((T, K)) < 0.1] = -1
@@ -228,8 +234,8 @@ def test_swap_counts_where_the_slots_get_a_kernel(hw, oracle, E, K, T):
     (32, 8, 8, 8, 128), (33, 1, 64, 64, 129), (64, 4, 16, 4, 2047), (65, 7, 33, 33, 500), (128, 8, 32, 8, 8193), (129, 5, 6, 3, 700),
     (256, 8, 64, 64, 2049), (96, 9, 12, 12, 1500), (200, 33, 8, 4, 300),        # partial tables, own marks or a byte per slot
     (130, 9, 8, 8, 18500), (64, 17, 8, 4, 9001), (256, 33, 64, 64, 5000), (100, 64, 32, 32, 4500),   # ... several tiles and stages
-    (257, 8, 32, 32, 1100), (362, 3, 8, 4, 900), (363, 6, 64, 64, 900), (512, 8, 64, 16, 2000),   # added tables; room for CGT or none
-    (300, 9, 8, 8, 400), (513, 4, 8, 8, 300), (300, 2, 4, 2, 0)])               # atomics per slot; no tokens
+    (257, 8, 32, 32, 1100), (362, 3, 8, 8, 900), (363, 6, 64, 64, 900), (512, 8, 64, 16, 2000), (512, 7, 64, 64, 9100),   # added tables; room for CGT or none
+    (300, 9, 8, 8, 400), (513, 4, 8, 8, 300), (362, 3, 8, 4, 900), (512, 2, 8, 8, 24000), (300, 2, 4, 2, 300), (300, 2, 8, 8, 0)])   # atomics per slot but for the third; no tokens
 def test_swap_counts_at_the_lines_between_the_kernels(hw, oracle, E, K, G, ng, T):
     """Repeated, dropped and invalid ids, an invalid placement, a workspace full of rubbish, run twice on it."""
     import torch
