@@ -15,14 +15,16 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
 import torch  # must be imported before the library so both share one HIP runtime
 
 
-class _Unbuilt:
-    """Stands for _hmcall where it is not built: every call falls through to lib(), which raises."""
+class _Absent:
+    """Stands for _hmcall where it cannot be loaded (not built, or built against another torch): every call is left to
+    the Python code, which makes the same calls of the same library; lib() warns once."""
     def __init__(self, why):
         self.why = why
 
@@ -33,7 +35,7 @@ class _Unbuilt:
 try:
     from . import _hmcall as _native
 except ImportError as e:
-    _native = _Unbuilt(str(e))
+    _native = _Absent(str(e))
 
 HM_DEDUP_NONE, HM_DEDUP_GPU, HM_DEDUP_NODE = 0, 1, 2
 HM_RECV_INTRA_NODE, HM_RECV_LOCAL_EXPERTS = 0, 1
@@ -88,8 +90,9 @@ def lib():
         if not os.path.exists(_LIB_PATH):
             raise RuntimeError("libhiermoe.so is not built (run __graft_entry__.build()); "
                                "there is no fallback path")
-        if isinstance(_native, _Unbuilt):
-            raise RuntimeError("_hmcall.so is not built or cannot be loaded (run __graft_entry__.build()): " + _native.why)
+        if isinstance(_native, _Absent):
+            warnings.warn("_hmcall.so cannot be loaded (run __graft_entry__.build()), the host takes 2 us more per call: " + _native.why,
+                          RuntimeWarning, stacklevel=2)
         L = ctypes.CDLL(_LIB_PATH)
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         L.hm_plan_workspace_bytes.restype = ctypes.c_size_t

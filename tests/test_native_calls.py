@@ -1,4 +1,7 @@
-"""_hmcall: what it takes, and what it leaves to the binding's Python code.  No GPU: nothing is launched."""
+"""_hmcall: what it takes, and what it leaves to the binding's Python code."""
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -36,3 +39,16 @@ def test_a_refused_call_changes_nothing():
     assert (plan.T, plan.K, plan.num_dest) == (4, 2, 4)
     with pytest.raises(TypeError):
         B.hm_plan(e(2, 2), e(2, 2, dtype=torch.float32), e(8), 2, 2, 1, plan=plan)
+
+
+def test_the_library_works_without_the_native_half():
+    """A binding that cannot load _hmcall says so and has every entry point all the same."""
+    code = ("import sys, warnings; sys.modules['paper_2508_09591_amd._hmcall'] = None\n"
+            "from paper_2508_09591_amd import binding as B\n"
+            "with warnings.catch_warnings(record=True) as w:\n"
+            "    warnings.simplefilter('always'); L = B.lib(); B.lib()\n"
+            "assert [x.category for x in w] == [RuntimeWarning] and '_hmcall' in str(w[0].message), w\n"
+            "assert all(hasattr(L, n) for n in B.EXPORTS) and B.status_string(-2) == 'bad shape'\n"
+            "assert B.hm_plan_workspace_bytes(8192, 8, 256, 4, 8, 2) > 0 and B._native.plan(1, 2) is None\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=B.os.path.dirname(B.os.path.dirname(B.__file__)))
+    assert r.returncode == 0, r.stderr
