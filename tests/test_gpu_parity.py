@@ -1210,7 +1210,7 @@ def test_step_under_hip_graph_capture(hw, oracle):
 
 
 def test_calls_go_to_the_current_stream(hw):
-    """The handle the binding passes on is the current stream's: the default one, the innermost
+    """The handle the Python code passes on (_hmcall has its own) is the current stream's: the default one, the innermost
     torch.cuda.stream(), a given one whatever is current."""
     import torch
     from paper_2508_09591_amd import binding as B
