@@ -375,6 +375,7 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   constexpr int COLS = cooc_cols(NE), kCoocPanel = 32 * COLS;
   constexpr int kRows = kCoocPanel + kCoocGroups;   // of S and M
   constexpr int kVecs = (32 * NE + 2 * kRows) * kCoocStride / 16;
+  constexpr int kRowVecs = kCoocTokens / 16;        // of a row without its pad, which nothing marks: a vector per lane clears S and M
   extern __shared__ __align__(16) uint8_t tiles[];
   uint8_t *const a_tile = tiles;                                   // [32 NE][stride]     A
   uint8_t *const sm_tiles = a_tile + 32 * NE * kCoocStride;        // twice [panel][stride] S, its experts, [64][stride] M
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
         }
       }
 #pragma unroll 1
-      for (int i = tid; i < kRows * kCoocStride / 16; i += kCoocThreads) ((i32x4 *)sm_next)[i] = zero;
+      for (int i = tid; i < kRows * kRowVecs; i += kCoocThreads) ((i32x4 *)(sm_next + i / kRowVecs * kCoocStride))[i % kRowVecs] = zero;
       uint8_t *const used = sm;
       sm = sm_next;
       sm_next = used;
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
           if (wrote >= 0) a_tile[wrote] = 0;
         } else {   // the slots of a token are spread over waves
 #pragma unroll 1
-          for (int i = tid; i < 32 * NE * kCoocStride / 16; i += kCoocThreads) ((i32x4 *)a_tile)[i] = zero;
+          for (int i = tid; i < 32 * NE * kRowVecs; i += kCoocThreads) ((i32x4 *)(a_tile + i / kRowVecs * kCoocStride))[i % kRowVecs] = zero;
           __syncthreads();
         }
       }
