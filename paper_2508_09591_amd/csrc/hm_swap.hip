@@ -197,7 +197,7 @@ __global__ __launch_bounds__(kFactorThreads) void swap_factors_kernel(SwapParams
 // the tokens and a panel of columns of C, builds the three indicator tiles for 128 tokens at a time in LDS
 // (expert-major, so that a lane's MFMA operand is 16 contiguous bytes), and stores its partial tables with plain
 // stores; a second kernel sums the chunks.  (With many tokens, or E > 256, for which the workspace has no room
-// for partial tables, the chunks are added to cleared tables by atomics.)
+// for partial tables, the chunks are added to cleared tables by atomics, or the slots are: atomics_pay.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kCoocTokens = 128;     // tokens per tile: four k-steps of the 32x32x32 int8 MFMA
 constexpr int kCoocStride = 144;     // bytes per tile row: 128 tokens + 16, which spreads 32 rows over all banks
@@ -358,7 +358,7 @@ __device__ __forceinline__ void add_tile(int32_t *table, const i32x16 &acc, int 
 // sixteen waves mark.  One column of tiles up to 128 experts, so that four cuts and sixteen chunks are a workgroup per
 // CU, two for 256 (E = 256, four cuts, the whole call: 8,192 tokens 33.7 us with one, 28.1 with two, 65,536 92 and 58).
 // The whole call, graphs of ten, four cuts, K = 8, with a lane per slot and panels of 64 and 128 columns -> now, us: E = 128 1,024
-// tokens 19.8 -> 14.6, 16,384 26.6 -> 21.1, 65,536 48.3 -> 40.2; E = 256 1,024 23.8 -> 21.5, 8,192 30.9 -> 28.1, 65,536 59.3 -> 58.4; by
+// tokens 19.8 -> 14.6, 16,384 26.6 -> 21.1, 65,536 48.3 -> 40.2; E = 256 1,024 23.7 -> 21.2, 8,192 30.7 -> 27.7, 65,536 64.5 -> 57.4; by
 // atomics per slot -> now: E = 320 4,096 77 -> 33, 30,000 131 -> 74, E = 512 (64 ranks, Zipf) 4,096 339 -> 54, 30,000 1,622 -> 124.
 // Loops stay loops: unrolled, they cost the registers of the accumulators, which then live in memory.
 //
