@@ -7,11 +7,13 @@
 //   L[a]     tokens where a is alone in its group    C[a][b]   ... that also select b
 // For g_r != g_c:  Z[r][c][g_c] = base[g_c] + (L0[r] - CG[r][g_c]) - (L[c] - C[c][r])   and the same
 // with r and c exchanged for g_r: no O(T K E) walk over all unselected experts, and the per-pair
-// work is an embarrassingly parallel E^2 ng kernel.  The tables come from int8 matrix products on
+// work is an embarrassingly parallel E^2 ng kernel.  The tables come from matrix products on
 // the matrix cores for E <= 512 (further down), from O(T K (K + ng)) atomic updates, one lane per
 // routing slot, beyond that, for E > 256 with more than eight slots per token, and where the products would have
 // too little to do (atomics_pay).
 #include "hm_device.h"
+
+#include <type_traits>
 
 namespace hm {
 
@@ -36,8 +38,6 @@ struct SwapParams {
   int32_t ng[kMaxCuts], per[kMaxCuts];
   uint32_t ng_reciprocal[kMaxCuts];   // ceil(2^32 / ng), for the division by ng in swap_build_kernel (unused when ng = 1)
   uint32_t per_reciprocal[kMaxCuts];  // ceil(2^32 / per), 0 when per = 1
-  uint32_t quad_reciprocal[kMaxCuts]; // ceil(2^32 / (ng / 4))
-  int32_t quads[kMaxCuts];            // swap_build_kernel takes four groups per lane
   int32_t build_blocks[kMaxCuts];     // column blocks of swap_build_kernel per cut
   int32_t lds_off[kMaxCuts];   // ints: where cut c's [L (E) | CG (E * ng)] starts in LDS; L0 is at 0
   int32_t *L0;                 // [E]                                  (workspace, shared by the cuts)
@@ -45,10 +45,6 @@ struct SwapParams {
   int32_t *L[kMaxCuts];        // [E]
   int32_t *CG[kMaxCuts];       // [E][ng]
   int32_t *C[kMaxCuts];        // [copies][E][E]
-  int32_t *CT[kMaxCuts];       // [E][E]   C transposed   } matrix path only: swap_build_kernel then reads
-  int32_t *CGT[kMaxCuts];      // [ng][E]  CG transposed  } along rows whichever expert of a pair a lane needs
-  int32_t cg_by_group[kMaxCuts];   // whether there is room for CGT; else CGT is CG itself, [E][ng]
-  int32_t transposed;
   int32_t *Z[kMaxCuts];
   int32_t *ws;                 // start of the workspace and its size in ints (cleared first)
   int64_t ws_ints;
@@ -190,48 +186,72 @@ __global__ __launch_bounds__(kFactorThreads) void swap_factors_kernel(SwapParams
 // The same tables as contractions over the tokens (E <= 512).
 //
 // With S[t][a] = 1 when token t selects expert a, A[t][a] = 1 when a is moreover the only selected
-// expert of its group, and M[t][g] = 1 when t selects something in group g (all 0/1 bytes):
+// expert of its group, and M[t][g] = 1 when t selects something in group g (all 0 or 1):
 //   C  = A^T S   (its diagonal is L)        CG = S^T M   (L0[a] = CG[a][group of a])
 // so the read-modify-write updates of popular expert pairs, which serialise on one address, become
-// int8 matrix products with int32 accumulators held in registers.  A workgroup takes one cut, a contiguous chunk of
-// the tokens and a panel of columns of C, builds the three indicator tiles for 128 tokens at a time in LDS
-// (expert-major, so that a lane's MFMA operand is 16 contiguous bytes), and stores its partial tables with plain
-// stores; a second kernel sums the chunks.  (With many tokens, or E > 256, for which the workspace has no room
-// for partial tables, the chunks are added to cleared tables by atomics, or the slots are: atomics_pay.)
+// matrix products whose sums are held in registers.  A workgroup takes one cut, a contiguous chunk of the tokens and
+// a panel of columns of C, builds the three indicator tiles in LDS (expert-major, a mark is a nibble: 1.0 in FP4, so that
+// a lane's MFMA operand of 32 tokens is 16 contiguous bytes and 1,024 tokens of 128 experts fit at once), and stores
+// its partial tables with plain stores; swap_pairs_kernel sums the chunks where it puts Z together.  The products add up
+// zeros and ones in binary32, which is exact below 2^24; a chunk has fewer than 2^15 tokens, or, added, a workgroup as many.
+// (With many tokens, or E > 256, for which the workspace has no room for partial tables, the chunks are added to
+// cleared tables by atomics, or the slots are: atomics_pay.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kCoocTokens = 128;     // tokens per tile: four k-steps of the 32x32x32 int8 MFMA
-constexpr int kCoocStride = 144;     // bytes per tile row: 128 tokens + 16, which spreads 32 rows over all banks
-constexpr int kCoocGroups = 64;      // rows of the group tile
-constexpr int kCoocChunksMax = 16;   // partial tables per cut
+constexpr int kCoocChunks = 16;      // partial tables per cut, some of them of no token where there are few: whoever sums them need not ask how many there are
 constexpr int kCoocChunkTokensMax = 32640;   // a chunk's counts are stored as 16-bit values
+constexpr int kCoocAddedTokensMax = 1 << 24; // a workgroup's sums are binary32
 constexpr int kCoocMaxE = 512;
 constexpr int kCoocPartMaxE = 256;   // experts up to which the workspace holds partial tables
-constexpr int kCoocStaged = 8192;    // slots worked out together (32 KiB of LDS): a lane per token of eight
 constexpr int kCoocAddedGroups = 256;   // workgroups aimed at where chunks are added up (512: E = 320, 4,096 tokens 33 -> 39 us)
 constexpr int kCoocOwnK = 8;         // most slots of a token that the matrix kernel works out itself
+constexpr int kCoocThreads = 1024;   // = most tokens of a tile: a lane per token
+constexpr int kCoocWaves = kCoocThreads / kWave;
+constexpr int kCoocStep = 64;        // tokens of one 32x32x64 product
+constexpr int kCoocPad = 16;         // bytes behind a tile row, which spread 32 rows over all banks
+constexpr int kCoocLds = 162816;     // dynamic LDS of a workgroup, most
+constexpr int kBlock = 16;           // experts of a block of the tables
 
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef i32x4 i32x4_align4 __attribute__((aligned(4)));
-typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+typedef u16x4 u16x4_align2 __attribute__((aligned(2)));
 
 struct CoocParams {
   const int32_t *ids;
   const int32_t *expert_to_rank;
   int32_t T, K, E, G;
-  int32_t sub_log2;            // places per token: 2^sub_log2 >= K
+  int32_t sub_log2;            // lanes per token of swap_slots_kernel: 2^sub_log2 >= K
   int32_t ncuts;
   int32_t chunks;              // gridDim.x of the matrix kernel
-  int32_t tokens_per_chunk;    // a multiple of kCoocTokens
-  int32_t added;               // the tables are added to C, CG and base instead of stored as parts
+  int32_t tokens_per_chunk;    // a multiple of kCoocStep
+  int32_t tile_tokens, stride; // tokens of a tile, bytes of a tile row
+  uint32_t per_recip16[kMaxCuts];   // ceil(2^16 / per): exact for ranks (below 64)
+  uint32_t words_recip17;      // ceil(2^17 / (tile_tokens / 8))
+  uint32_t k_reciprocal;       // ceil(2^32 / K) for K > 1
   int32_t ng[kMaxCuts], per[kMaxCuts];
   uint8_t *slot_bits;          // [T * K]: bit 0 first valid occurrence, bit 1 + c alone in its group under cut c
-  uint16_t *part[kMaxCuts];    // [chunks][E*E + E*ng + 64 (+1)]: C, CG and base of one chunk; a chunk has < 2^15 tokens
-  int32_t *C[kMaxCuts], *CG[kMaxCuts], *base[kMaxCuts];
+  void *tables[kMaxCuts];      // 16-bit counts of every chunk (parts) or 32-bit counts, as Tables lays them out
   int32_t *status;
 };
 
-__host__ __device__ static inline int64_t cooc_part_ints(int64_t E, int64_t ng) { return E * E + E * ng + 64; }   // values per chunk
-__host__ __device__ static inline int64_t cooc_part_words(int64_t E, int64_t ng) { return (cooc_part_ints(E, ng) + 1) / 2; }   // 32-bit words they take
+// The tables of a cut, in blocks of up to 16 experts a (h of them) by up to 16 columns, chunk by chunk, a block's values with
+// the experts side by side: [C: E blocks by E][CG: E by ng][L: E][base: 64].  A block of all chunks is contiguous, so
+// whoever sums the chunks of a block reads whole lines, and four neighbouring experts of a lane's accumulators are one store.
+// Tables that chunks are added to are plain rows, [C: E by E][CG: E by ng][L][base], as the lanes of an atomic should be neighbours.
+struct Tables {
+  int E, ng, chunks;
+  __host__ __device__ static int64_t values(int64_t E, int64_t ng) { return E * E + E * ng + E + 64; }   // of a chunk
+  __device__ int height(int i) const { return min(kBlock, E - kBlock * i); }
+  // Where block i of a table begins, and a column or chunk of columns from there, in heights of the block.
+  __device__ int c(int i) const { return kBlock * i * E * chunks; }
+  __device__ int c_column(int b, int chunk) const { return b / kBlock * kBlock * chunks + chunk * height(b / kBlock) + b % kBlock; }
+  __device__ int cg(int i) const { return (E * E + kBlock * i * ng) * chunks; }
+  __device__ int cg_column(int g, int chunk) const { return chunk * ng + g; }
+  __device__ int l(int i) const { return (E * E + E * ng + kBlock * i) * chunks; }   // columns: chunks
+  __device__ int base(int chunk) const { return (E * E + E * ng + E) * chunks + chunk * kWave; }
+};
 
 // One lane per routing slot (K > 8); the K slots of a token sit in 2^sub_log2 consecutive lanes and
 // learn about each other through shuffles, eight in flight at a time.
@@ -297,241 +317,221 @@ __global__ __launch_bounds__(kSwapThreads) void swap_slots_kernel(CoocParams p) 
   }
 }
 
-// D += A B for one 32x32 tile over 32 tokens; a lane's operand: 16 token bytes of row (lane % 32).
-__device__ __forceinline__ i32x16 mfma_i8(i32x4 a, i32x4 b, i32x16 acc) {
-  return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc, 0, 0, 0);
+// D += A B for one 32x32 tile over 64 tokens; a lane's operand: 32 tokens, FP4, of row (lane % 32).
+__device__ __forceinline__ f32x16 mfma_fp4(i32x4 a, i32x4 b, f32x16 acc) {
+  const i32x8 a8 = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, b8 = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, acc, 4, 4, 0, 0, 0, 0);   // 4: FP4; no scales
 }
+constexpr uint32_t kOne = 2;   // 1.0 in FP4
 
-// What a slot marks in the tiles: its expert, the expert's group, whether it is alone there; 0 if it marks nothing (no valid
-// expert, or not the first with it in its token).
-constexpr uint32_t kMarks = 1u << 31, kAlone = 1u << 15;
-__device__ __forceinline__ uint32_t mark_of(int expert, uint32_t group, bool alone) {
-  return kMarks | group << 16 | (alone ? kAlone : 0u) | (uint32_t)expert;
-}
+// An expert's group as the matrix kernel looks it up: below 64, or one of these.
+constexpr uint32_t kNoGroup = 0x80, kBadGroup = 0xC0;   // id -1; an id or a placement out of range
 
-// The marks of a token of up to eight slots, by the one lane that holds it.  Groups are bits of BITS: one that has been seen
-// twice, copies of an expert aside, is nobody's alone.  (A lane per slot that compares itself with the others
-// took four times the instructions for a token, and the workgroups of all cuts and panels repeat them: 6.5 us for the 1,024
-// tokens of a chunk on one CU.)
+// A product below 2^24: one instruction at the full rate.
+__device__ __forceinline__ int row_at(uint32_t row, int stride) { return (int)__umul24(row, (uint32_t)stride); }
+
+// The marks of a lane's token of up to eight slots, written for few instructions: the sixteen waves of a workgroup issue each of them
+// in turn.  Groups are bits of BITS: one that has been seen twice, copies of an expert aside, is nobody's alone.  `m`, `a`: the
+// token's word in row 0 of the tiles, a_to_s: from an expert's row of A to its row of S, `value`: the token's bit.
 template <typename BITS>
-__device__ __forceinline__ void mark_token(const int (&id)[kCoocOwnK], int E, const uint8_t *group_of, bool &bad, uint32_t (&mark)[kCoocOwnK]) {
-  uint32_t expert[kCoocOwnK], group[kCoocOwnK];
-  BITS once = 0, twice = 0;
+__device__ __forceinline__ void mark_token(const int (&id)[kCoocOwnK], int E, const uint8_t *group_of, int stride, int panel0, int panel, uint8_t *m,
+                                           uint8_t *a, int a_to_s, uint32_t value, bool &bad) {
+  uint32_t expert[kCoocOwnK], group[kCoocOwnK], all = 0;
+  uint32_t same = 1;   // 0 if two slots have one expert
+#pragma unroll
+  for (int k = 0; k < kCoocOwnK; ++k) group[k] = group_of[min((uint32_t)id[k] + 1u, (uint32_t)E + 1u)];   // entry 0: id -1, E + 1: out of range
 #pragma unroll
   for (int k = 0; k < kCoocOwnK; ++k) {
-    group[k] = group_of[min((uint32_t)id[k] + 1u, (uint32_t)E + 1u)];   // entry 0: id -1, E + 1: out of range
-    bad = bad || group[k] == 0xFEu;
+    all |= group[k];
     expert[k] = group[k] < kWave ? (uint32_t)id[k] : 0x10000u + k;   // equal to no other
-  }
-  __builtin_amdgcn_sched_barrier(0);   // here and below: all comparisons at once would need more registers than there are
-#pragma unroll
-  for (int k = 0; k < kCoocOwnK; ++k) {
-    uint32_t same = 1;   // 0 if an earlier slot has the expert
 #pragma unroll
     for (int j = 0; j < k; ++j) same = min(same, expert[j] ^ expert[k]);
-    const bool first = same != 0 && group[k] < kWave;
-    const BITS bit = first ? (BITS)1 << group[k] : (BITS)0;
-    mark[k] = first ? expert[k] | group[k] << 16 | kMarks : 0u;
-    twice |= once & bit;
-    once |= bit;
-    __builtin_amdgcn_sched_barrier(0);
   }
+  bad = bad || (all & kBadGroup & ~kNoGroup) != 0;
+  BITS bit[kCoocOwnK], once = 0, twice = 0;
 #pragma unroll
-  for (int k = 0; k < kCoocOwnK; ++k)
-    if (mark[k] && !((twice >> group[k]) & 1)) mark[k] |= kAlone;
-}
-
-// A lane's column of a 32x32 tile, rows 8 (r / 4) + r % 4 from element `at` on, as far as they are below `rows`.
-__device__ __forceinline__ void store_tile(uint16_t *part, const i32x16 &acc, int at, int width, int rows) {
+  for (int k = 0; k < kCoocOwnK; ++k) bit[k] = group[k] < kWave ? (BITS)1 << (group[k] & (8 * sizeof(BITS) - 1)) : (BITS)0;
+  if (__builtin_expect(__ballot(same == 0) != 0, 0)) {   // routers do not select an expert twice, callers may
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if (8 * (r / 4) + r % 4 < rows) part[at + (8 * (r / 4) + r % 4) * width] = (uint16_t)acc[r];
-}
-__device__ __forceinline__ void add_tile(int32_t *table, const i32x16 &acc, int at, int width, int rows) {
+    for (int k = 1; k < kCoocOwnK; ++k) {
+      bool again = false;
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if (8 * (r / 4) + r % 4 < rows && acc[r]) atomicAdd(&table[at + (8 * (r / 4) + r % 4) * width], acc[r]);
-}
-
-// Workgroup (chunk, cut, panel of 32 or 64 columns of C); the first waves hold one 32x32 tile of C each.  A workgroup
-// needs the S tile of its own columns only; the panels repeat the marks of the chunk's slots and the A tile.  All
-// sixteen waves mark.  One column of tiles up to 128 experts, so that four cuts and sixteen chunks are a workgroup per
-// CU, two for 256 (E = 256, four cuts, the whole call: 8,192 tokens 33.7 us with one, 28.1 with two, 65,536 92 and 58).
-// The whole call, graphs of ten, four cuts, K = 8, with a lane per slot and panels of 64 and 128 columns -> now, us: E = 128 1,024
-// tokens 19.8 -> 14.6, 16,384 26.6 -> 21.1, 65,536 48.3 -> 40.2; E = 256 1,024 23.7 -> 21.2, 8,192 30.7 -> 27.7, 65,536 64.5 -> 57.4; by
-// atomics per slot -> now: E = 320 4,096 77 -> 33, 30,000 131 -> 74, E = 512 (64 ranks, Zipf) 4,096 339 -> 54, 30,000 1,622 -> 124.
-// Loops stay loops: unrolled, they cost the registers of the accumulators, which then live in memory.
-//
-// Per tile: mark | barrier | multiply | barrier.  Nothing waits for a tile to be cleared: with one column of tiles the rows of A
-// are read by one wave, which clears them behind its reads; with two, the lanes that marked them clear them (a
-// token's places belong to one wave, so it may mark the next tile without a barrier), or, for K > 8, whose tokens are
-// spread over waves, all of them clear A behind a third barrier.  S and M, which several
-// waves read, are there twice, and the one not in use is cleared while the other is multiplied.
-constexpr int kCoocThreads = 1024;
-constexpr int kCoocWaves = kCoocThreads / kWave;
-constexpr int cooc_cols(int ne) { return ne == 8 ? 2 : 1; }   // tile columns of a panel
-template <int NE, bool OWN_SLOTS>   // experts padded to 32 * NE
-__global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
-  constexpr int COLS = cooc_cols(NE), kCoocPanel = 32 * COLS;
-  constexpr int kRows = kCoocPanel + kCoocGroups;   // of S and M
-  constexpr int kVecs = (32 * NE + 2 * kRows) * kCoocStride / 16;
-  constexpr int kRowVecs = kCoocTokens / 16;        // of a row without its pad, which nothing marks: a vector per lane clears S and M
-  extern __shared__ __align__(16) uint8_t tiles[];
-  uint8_t *const a_tile = tiles;                                   // [32 NE][stride]     A
-  uint8_t *const sm_tiles = a_tile + 32 * NE * kCoocStride;        // twice [panel][stride] S, its experts, [64][stride] M
-  uint32_t *const staged = (uint32_t *)(sm_tiles + 2 * kRows * kCoocStride);   // [tokens of a stage][2^sub_log2] marks
-  __shared__ uint8_t group_of[32 * NE + 2];   // of expert e at e + 1; 0xFF none, 0xFE an error
-
-  const int cut = blockIdx.y, panel = blockIdx.z;
-  const int ng = p.ng[cut], per = p.per[cut];
-  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const i32x4 zero = {0, 0, 0, 0};
-#pragma unroll 1
-  for (int i = tid; i < kVecs; i += kCoocThreads) ((i32x4 *)tiles)[i] = zero;
-  {
-    const uint32_t per_recip16 = (65536u + (uint32_t)per - 1u) / (uint32_t)per;   // exact for ranks (below 64)
-#pragma unroll 1
-    for (int e = tid; e < p.E + 2; e += kCoocThreads) {
-      const int r = e >= 1 && e <= p.E ? p.expert_to_rank[e - 1] : -1;
-      group_of[e] = (uint8_t)(e == 0 ? 0xFFu : (unsigned)r < (unsigned)p.G ? ((uint32_t)r * per_recip16) >> 16 : 0xFEu);
+      for (int j = 0; j < k; ++j) again = again || expert[j] == expert[k];
+      if (again) bit[k] = 0;
     }
   }
-  __syncthreads();
-
-  // A token's marks lie in 2^sub_log2 places where a lane works a token out, one after the other where they are read: with places
-  // padded to a power of two too, a tile of 33 slots cost twice the turns (E = 256, 40,000 tokens, four cuts: 165 us, now 128).
-  const int sub_log2 = p.sub_log2, sub = 1 << sub_log2;
-  const int per_token = OWN_SLOTS ? sub : p.K, places = kCoocTokens * per_token;   // of a tile
-  const int stage_tokens = OWN_SLOTS ? kCoocStaged >> sub_log2 : kCoocStaged / places * kCoocTokens;   // 128 at least
-  const uint32_t k_recip20 = ((1u << 20) + (uint32_t)p.K - 1u) / (uint32_t)p.K;   // exact below 8,192 for K <= 64
-  const int64_t t_begin = (int64_t)blockIdx.x * p.tokens_per_chunk;
-  const int64_t t_end = min((int64_t)p.T, t_begin + p.tokens_per_chunk);
-
-  // What this wave accumulates: one tile of C, and from the last wave down at most one tile of this panel's CG.
-  const int c_row = w / COLS, c_col = w % COLS;
-  const bool has_c = c_row < NE && c_row < (p.E + 31) / 32;
-  const int g_tiles = (ng + 31) / 32, g_job = kCoocWaves - 1 - w, g_row = g_job / g_tiles, g_col = g_job % g_tiles;
-  const bool has_g = g_row < COLS;
-  const bool counts_base = panel == 0 && w == kCoocWaves / 2;   // lane g: tokens of this chunk that touch group g
-  constexpr bool kEither = NE * COLS + 4 <= kCoocWaves;   // no wave has both
-  i32x16 acc, second;
-  i32x16 &acc_g = kEither ? acc : second;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = second[r] = 0;
+  for (int k = 0; k < kCoocOwnK; ++k) {
+    twice |= once & bit[k];
+    once |= bit[k];
+  }
+#pragma unroll
+  for (int k = 0; k < kCoocOwnK; ++k) {
+    const bool marks = bit[k] != 0;   // another copy of an expert has the same marks
+    const uint32_t column = expert[k] - (uint32_t)panel0;
+    atomicOr((uint32_t *)(m + row_at(group[k] & (kWave / 2 * sizeof(BITS) / 4 - 1), stride)), marks ? value : 0u);
+    uint8_t *const row = a + row_at(expert[k], stride);
+    if (marks && column < (uint32_t)panel) atomicOr((uint32_t *)(row + a_to_s), value);
+    if ((bit[k] & ~twice) != 0) atomicOr((uint32_t *)row, value);
+  }
+}
+
+// Four neighbouring values of a block, as far as they are below `left`.
+__device__ __forceinline__ void store_four(uint16_t *out, const int (&v)[4], int left) {
+  if (left >= 4) {
+    *(u16x4_align2 *)out = (u16x4){(uint16_t)v[0], (uint16_t)v[1], (uint16_t)v[2], (uint16_t)v[3]};
+  } else {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (i < left) out[i] = (uint16_t)v[i];
+  }
+}
+// Workgroup (chunk, cut, panel of 32 COLS columns of C); a wave holds one row of 32x32 tiles of the panel, the last waves a tile of
+// its CG each.  A workgroup needs the S tile of its own columns only; the panels repeat the marks of the chunk's slots and
+// the A tile.  One column of tiles up to 128 experts, so that four cuts and sixteen chunks are a workgroup per CU, two
+// for 256, one again beyond, where a wave per tile row is all there are.
+//
+// Per tile of up to 1,024 tokens: load and clear | barrier | mark | barrier | multiply, and a barrier if there are more tiles.  All
+// marks of a chunk of that many tokens are made at once: with a byte per mark a tile held 128, and the chain of marks,
+// barrier, LDS operands, products and barrier, 0.5 us per tile, was half of the kernel.  What bounds it now is the marks, which
+// sixteen waves issue in turn, 1.0 to 1.7 us of 7 (products 0.6, clearing 0.5, stores 0.6), and cold code, 8 KB of it.  Kernel trace,
+// four cuts, K = 8, before -> now: 16,384 tokens, 128 experts 11.8 -> 6.9 us, 8,192, 256 12.2 -> 7.7.  The whole call (graphs
+// of ten), 4,096, 65,536, 500,000 tokens: 128 experts 16.0 -> 11.5, 42.4 -> 21.9, 223 -> 99; 256 25.8 -> 18.3, 57.7 -> 37.1, 272 -> 157.
+template <int COLS, bool OWN_SLOTS, bool ADDED>   // ADDED: to cleared tables, instead of stored as a part
+__global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
+  constexpr int kPanel = 32 * COLS, kAhead = 4 / COLS;   // products whose operands are on their way together
+  constexpr bool kBoth = ADDED && COLS == 1;             // more than 448 experts: the last waves have tiles of C and of CG
+  typedef std::conditional_t<ADDED, int32_t, uint16_t> value_t;
+  extern __shared__ __align__(16) uint8_t tiles[];
+  __shared__ uint8_t group_of[kCoocMaxE + 2];   // of expert e at e + 1
+  __shared__ int32_t base_cnt[kWave];
+
+  const int cut = blockIdx.y, panel = blockIdx.z, chunk = blockIdx.x;
+  const int E = p.E, ng = p.ng[cut], stride = p.stride;
+  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row_tiles = (int)((uint32_t)E + 31u) >> 5, g_tiles = (int)((uint32_t)ng + 31u) >> 5;
+  uint8_t *const a_tile = tiles;                               // [32 row_tiles][stride] A
+  uint8_t *const s_tile = a_tile + 32 * row_tiles * stride;    // [panel][stride]        S, its experts
+  uint8_t *const m_tile = s_tile + kPanel * stride;            // [32 g_tiles][stride]   M
+  const int vecs = (32 * row_tiles + kPanel + 32 * g_tiles) * (stride / 16);
+
+  // Where a token of the tile is marked: in the row's word (token % words) and there in nibble (token / words), so that the lanes of a
+  // wave, which hold neighbouring tokens, meet at a bank only where their rows do, and never at a word.  The products take
+  // the tokens in any order.
+  const int words = p.tile_tokens >> 3;
+  auto place = [&](int token, int &at) {
+    const uint32_t nibble = __umul24((uint32_t)token, p.words_recip17) >> 17;   // token < 1,024, 16 to 128 words
+    at = (token - (int)__umul24(nibble, (uint32_t)words)) * 4;
+    return kOne << (4 * nibble);
+  };
+
+  // What this wave accumulates: a row of tiles of C, or, from the last wave down, one tile of the panel's CG.
+  const int g_job = kCoocWaves - 1 - w, g_row = g_job >> (g_tiles - 1), g_col = g_job & (g_tiles - 1);
+  const bool has_c = w < row_tiles, has_g = g_row < COLS;
+  const int quarter = w - kCoocWaves / 2;   // of the tokens whose groups the wave counts, a lane per group
+  const bool counts_base = panel == 0 && (unsigned)quarter < 4u;
+  f32x16 acc[COLS], second;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    if (kBoth) second[r] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < COLS; ++c) acc[c][r] = 0.0f;
+  }
   int my_base = 0;
-  const int op_at = (lane & 31) * kCoocStride + (lane >> 5) * 16;
-  uint8_t *const c_a = a_tile + 32 * (has_c ? c_row : 0) * kCoocStride + op_at;
-  const int c_s = 32 * c_col * kCoocStride + op_at, g_s = 32 * (has_g ? g_row : 0) * kCoocStride + op_at;
-  const int g_m = (kCoocPanel + 32 * g_col) * kCoocStride + op_at;
+  if (tid < kWave) base_cnt[tid] = 0;
+  const int op_at = (lane & 31) * stride + (lane >> 5) * 16, steps = p.tile_tokens / kCoocStep;   // whole batches
+  // acc[c] += rows' tile by the tile of columns c
+  auto multiply = [&](auto &sums, const uint8_t *rows, const uint8_t *columns) {
+    constexpr int N = sizeof(sums) / sizeof(f32x16);
+    rows += op_at;
+    columns += op_at;
+#pragma unroll 1
+    for (int step = 0; step < steps; step += kAhead, rows += 32 * kAhead, columns += 32 * kAhead) {
+      i32x4 r_op[kAhead], c_op[kAhead][N];
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) {
+        r_op[j] = *(const i32x4 *)(rows + 32 * j);
+#pragma unroll
+        for (int c = 0; c < N; ++c) c_op[j][c] = *(const i32x4 *)(columns + 32 * c * stride + 32 * j);
+      }
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j)
+#pragma unroll
+        for (int c = 0; c < N; ++c) sums[c] = mfma_fp4(r_op[j], c_op[j][c], sums[c]);
+    }
+  };
+  // the tile rows and columns of this wave's products; a tile of CG is multiplied as often as a wave has tiles
+  const uint8_t *const rows = has_c ? a_tile + 32 * w * stride : s_tile + 32 * (has_g ? g_row : 0) * stride;
+  const uint8_t *const columns = has_c ? s_tile : m_tile + 32 * (has_g ? g_col : 0) * stride;
 
+  const uint32_t T = (uint32_t)p.T, t_begin = (uint32_t)chunk * (uint32_t)p.tokens_per_chunk;
+  const uint32_t t_end = min(T, t_begin + (uint32_t)p.tokens_per_chunk);
   bool bad = false;
-  uint8_t *sm = sm_tiles, *sm_next = sm_tiles + kRows * kCoocStride;
 #pragma unroll 1
-  for (int64_t stage0 = t_begin; stage0 < t_end; stage0 += stage_tokens) {
-    const int tokens = (int)min((int64_t)stage_tokens, t_end - stage0);
-    const int last = (tokens + kCoocTokens - 1) / kCoocTokens * places;   // places of the tiles to come
+  for (uint32_t t0 = t_begin; t0 < t_end; t0 += (uint32_t)p.tile_tokens) {
+    const int tokens = (int)min((uint32_t)p.tile_tokens, t_end - t0);
+    int id[kCoocOwnK], rank = -1;
+    if (OWN_SLOTS) {   // on their way, as the placement, while the tiles are cleared
+#pragma unroll
+      for (int k = 0; k < kCoocOwnK; ++k) id[k] = -1;
+      if (tid < tokens) load_ids(p.ids + (int64_t)(t0 + (uint32_t)tid) * p.K, p.K, 0, id);
+    }
+    if (t0 == t_begin && tid >= 1 && tid <= E) rank = p.expert_to_rank[tid - 1];
+    if (t0 != t_begin) __syncthreads();
+    const i32x4 zero = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int i = tid; i < vecs; i += kCoocThreads) ((i32x4 *)tiles)[i] = zero;
+    if (t0 == t_begin) {
+      if (tid < E + 2) group_of[tid] = (uint8_t)(tid == 0 ? kNoGroup : (unsigned)rank < (unsigned)p.G ? __umul24((uint32_t)rank, p.per_recip16[cut]) >> 16 : kBadGroup);
+    }
+    __syncthreads();
     if (OWN_SLOTS) {
-#pragma unroll 1
-      for (int t = tid; t < (last >> sub_log2); t += kCoocThreads) {
-        int id[kCoocOwnK];
-        uint32_t m[kCoocOwnK];
-#pragma unroll
-        for (int k = 0; k < kCoocOwnK; ++k) id[k] = -1;
-        if (t < tokens) load_ids(p.ids + (stage0 + t) * p.K, p.K, 0, id);
-        if (ng <= 32) mark_token<uint32_t>(id, p.E, group_of, bad, m);
-        else mark_token<uint64_t>(id, p.E, group_of, bad, m);
-        if (sub == kCoocOwnK) {
-          *(i32x4 *)(staged + t * kCoocOwnK) = i32x4{(int)m[0], (int)m[1], (int)m[2], (int)m[3]};
-          *(i32x4 *)(staged + t * kCoocOwnK + 4) = i32x4{(int)m[4], (int)m[5], (int)m[6], (int)m[7]};
-        } else {
-#pragma unroll
-          for (int k = 0; k < kCoocOwnK / 2; ++k)
-            if (k < sub) staged[(t << sub_log2) + k] = m[k];
-        }
+      if (w * kWave < tokens) {
+        int at;
+        const uint32_t value = place(tid, at);
+        const int a_to_s = (32 * row_tiles - kPanel * panel) * stride;
+        if (__builtin_expect(ng <= 32, 1)) mark_token<uint32_t>(id, E, group_of, stride, kPanel * panel, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
+        else mark_token<uint64_t>(id, E, group_of, stride, kPanel * panel, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
       }
     } else {
-      constexpr int kAhead = 8;   // loads of a lane in flight together
+      constexpr int kLoads = 8;   // of a lane in flight together
       const int slots = tokens * p.K;
-      const int32_t *const ids = p.ids + stage0 * p.K;
-      const uint8_t *const slot_bits = p.slot_bits + stage0 * p.K;
+      const int32_t *const ids = p.ids + (int64_t)t0 * p.K;
+      const uint8_t *const slot_bits = p.slot_bits + (int64_t)t0 * p.K;
 #pragma unroll 1
-      for (int i0 = tid; i0 < last; i0 += kAhead * kCoocThreads) {
-        int id[kAhead], bits[kAhead];
+      for (int i0 = tid; i0 < slots; i0 += kLoads * kCoocThreads) {
+        int expert[kLoads], bits[kLoads];
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
+        for (int j = 0; j < kLoads; ++j) {
           const int i = min(i0 + j * kCoocThreads, slots - 1);
-          id[j] = ids[i];
+          expert[j] = ids[i];
           bits[j] = slot_bits[i];
         }
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
+        for (int j = 0; j < kLoads; ++j) {
           const int i = i0 + j * kCoocThreads;
-          const uint32_t group = group_of[min((uint32_t)id[j] + 1u, (uint32_t)p.E + 1u)];
-          const uint32_t m = mark_of(id[j], group, (bits[j] >> (1 + cut)) & 1);
-          if (i < last) staged[i] = i < slots && (bits[j] & 1) ? m : 0u;
+          if (i < slots && (bits[j] & 1)) {   // a valid expert
+            int at;
+            const uint32_t value = place((int)__umulhi((uint32_t)i, p.k_reciprocal), at), column = (uint32_t)(expert[j] - kPanel * panel);
+            atomicOr((uint32_t *)(m_tile + row_at(group_of[expert[j] + 1], stride) + at), value);
+            if (column < (uint32_t)kPanel) atomicOr((uint32_t *)(s_tile + row_at(column, stride) + at), value);
+            if ((bits[j] >> (1 + cut)) & 1) atomicOr((uint32_t *)(a_tile + row_at((uint32_t)expert[j], stride) + at), value);
+          }
         }
       }
     }
     __syncthreads();
+    if (has_c || has_g) multiply(acc, rows, columns);
+    if (kBoth && has_c && has_g) {
+      f32x16(&one)[1] = *(f32x16(*)[1])&second;
+      multiply(one, s_tile + 32 * g_row * stride, m_tile + 32 * g_col * stride);
+    }
+    if (counts_base) {   // a mark is one bit, so a word's population count is its number of tokens
+      const i32x4 *row = (const i32x4 *)(m_tile + min(lane, 32 * g_tiles - 1) * stride);
 #pragma unroll 1
-    for (int first_place = 0; first_place < last; first_place += places) {
-      int wrote = -1;   // where in A this lane's mark went
-#pragma unroll 1
-      for (int i = tid; i < places; i += kCoocThreads) {
-        const uint32_t m = staged[first_place + i];
-        if (!(m & kMarks)) continue;
-        const int token = OWN_SLOTS ? i >> sub_log2 : (int)((uint32_t)i * k_recip20 >> 20);
-        const int expert = (int)(m & 0x1FFu), column = expert - kCoocPanel * panel;
-        if (m & kAlone) {
-          const int at = expert * kCoocStride + token;
-          a_tile[at] = 1;
-          if (OWN_SLOTS) wrote = at;
-        }
-        if ((unsigned)column < (unsigned)kCoocPanel) sm[column * kCoocStride + token] = 1;
-        sm[(kCoocPanel + (m >> 16 & 0x3Fu)) * kCoocStride + token] = 1;
-      }
-      __syncthreads();
-      if (has_c) {
-        i32x4 a_op[kCoocTokens / 32], s_op[kCoocTokens / 32];
-#pragma unroll
-        for (int step = 0; step < kCoocTokens / 32; ++step) {
-          a_op[step] = *(const i32x4 *)(c_a + 32 * step);
-          s_op[step] = *(const i32x4 *)(sm + c_s + 32 * step);
-        }
-        if (COLS == 1) {
-#pragma unroll
-          for (int step = 0; step < kCoocTokens / 32; ++step) *(i32x4 *)(c_a + 32 * step) = zero;
-        }
-#pragma unroll
-        for (int step = 0; step < kCoocTokens / 32; ++step) acc = mfma_i8(a_op[step], s_op[step], acc);
-      }
-      if (has_g) {
-#pragma unroll
-        for (int step = 0; step < kCoocTokens / 32; ++step)
-          acc_g = mfma_i8(*(const i32x4 *)(sm + g_s + 32 * step), *(const i32x4 *)(sm + g_m + 32 * step), acc_g);
-      }
-      if (counts_base) {   // bytes are 0 / 1, so a word's population count is its number of tokens
-        const i32x4 *row = (const i32x4 *)(sm + (kCoocPanel + lane) * kCoocStride);
-#pragma unroll
-        for (int i = 0; i < kCoocTokens / 16; ++i) {
-          const i32x4 v = row[i];
-          my_base += __popc(v[0]) + __popc(v[1]) + __popc(v[2]) + __popc(v[3]);
-        }
-      }
-#pragma unroll 1
-      for (int i = tid; i < kRows * kRowVecs; i += kCoocThreads) ((i32x4 *)(sm_next + i / kRowVecs * kCoocStride))[i % kRowVecs] = zero;
-      uint8_t *const used = sm;
-      sm = sm_next;
-      sm_next = used;
-      __syncthreads();
-      if (COLS > 1) {   // two waves read a row of A
-        if (OWN_SLOTS) {   // a lane has one place of a tile: it clears what it marked
-          if (wrote >= 0) a_tile[wrote] = 0;
-        } else {   // the slots of a token are spread over waves
-#pragma unroll 1
-          for (int i = tid; i < 32 * NE * kRowVecs; i += kCoocThreads) ((i32x4 *)(a_tile + i / kRowVecs * kCoocStride))[i % kRowVecs] = zero;
-          __syncthreads();
-        }
+      for (int i = quarter; i < 2 * steps; i += 4) {
+        const i32x4 v = row[i];
+        my_base += __popc(v[0]) + __popc(v[1]) + __popc(v[2]) + __popc(v[3]);
       }
     }
   }
@@ -539,208 +539,249 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
 
   // Accumulator layout of a 32x32 tile: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4,
   // column l % 32.
-  const int64_t cg_at = (int64_t)p.E * p.E, base_at = cg_at + (int64_t)p.E * ng;
-  uint16_t *const part = p.part[cut] + (int64_t)blockIdx.x * 2 * cooc_part_words(p.E, ng);
-  const int col = lane & 31, row_hi = (lane >> 5) * 4;
-  if (has_c && kCoocPanel * panel + 32 * c_col + col < p.E) {
-    const int a0 = 32 * c_row + row_hi, at = a0 * p.E + kCoocPanel * panel + 32 * c_col + col;   // E <= 512
-    if (!p.added) store_tile(part, acc, at, p.E, p.E - a0);
-    else add_tile(p.C[cut], acc, at, p.E, p.E - a0);
-  }
-  if (has_g && 32 * g_col + col < ng) {
-    const int a0 = kCoocPanel * panel + 32 * g_row + row_hi, at = a0 * ng + 32 * g_col + col;
-    if (!p.added) store_tile(part + cg_at, acc_g, at, ng, p.E - a0);
-    else add_tile(p.CG[cut], acc_g, at, ng, p.E - a0);
-  }
-  if (counts_base) {
-    if (!p.added) part[base_at + lane] = (uint16_t)my_base;
-    else if (my_base) atomicAdd(&p.base[cut][lane], my_base);
-  }
-}
-
-// Sums the chunks' partial tables into the tables swap_build_kernel reads; blockIdx.y is the cut and
-// blockIdx.x a 32 x 32 tile of C, then of CG.  A lane sums four neighbouring values, all chunks' loads in
-// flight, and the tile is turned round in LDS, so that the transposes are written in whole lines too (one lane per
-// value wrote them a word per line: kernel trace 6.6 us for 128 experts and four cuts, 9.2 us for 256; now 4.7 and
-// 6.2).  L is the diagonal of C and L0[a] the entry of CG in a's own group (every token that selects a
-// selects something there), so neither needs a table of its own upstream.  Where the chunks were added up by atomics
-// already (cp.added), the tables are read back for the transposes, L and L0.
-constexpr int kTile = 32;
-typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
-typedef u16x4 u16x4_align2 __attribute__((aligned(2)));
-__host__ __device__ static inline int reduce_tiles(int E, int ng) {
-  const int rows = (E + kTile - 1) / kTile;
-  return rows * (rows + (ng + kTile - 1) / kTile);
-}
-__global__ __launch_bounds__(kSwapThreads) void swap_reduce_kernel(SwapParams p, CoocParams cp) {
-  __shared__ int32_t turned[kTile][kTile + 1];
-  const int cut = blockIdx.y;
-  const int E = p.E, ng = p.ng[cut];
-  if ((int)blockIdx.x >= reduce_tiles(E, ng)) return;
-  const int64_t stride = 2 * cooc_part_words(E, ng);   // 16-bit values per chunk
-  const uint16_t *const part = cp.part[cut];
-  const int tile_rows = (E + kTile - 1) / kTile;
-  const bool of_c = (int)blockIdx.x < tile_rows * tile_rows;
-  const int index = of_c ? (int)blockIdx.x : (int)blockIdx.x - tile_rows * tile_rows;
-  const int tile_cols = of_c ? tile_rows : (ng + kTile - 1) / kTile, width = of_c ? E : ng;
-  const int a0 = index / tile_cols * kTile, b0 = index % tile_cols * kTile;
-  const int row = threadIdx.x >> 3, col = (threadIdx.x & 7) * 4;
-  const int a = a0 + row, b = b0 + col;
-  int sum[4] = {0, 0, 0, 0};
-  if (a < E && b < width) {
-    const uint16_t *at = part + (of_c ? 0 : (int64_t)E * E) + (int64_t)a * width + b;
-    int32_t *const out = (of_c ? p.C[cut] : p.CG[cut]) + (int64_t)a * width + b;
-    if (cp.added) {
+  const Tables table = {E, ng, ADDED ? 1 : p.chunks};
+  const int part = ADDED ? 0 : chunk, col = lane & 31, row_hi = (lane >> 5) * 4;
+  value_t *const out = (value_t *)p.tables[cut];
+  // the four 4 x 1 pieces of a lane's column of the tile whose first block is `block`: where the table begins, its width, the
+  // column, for parts in heights
+  auto put = [&](const f32x16 &sums, int block, int begin, int width, int column) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) sum[e] = b + e < width ? out[e] : 0;
-    } else if (b + 4 <= width) {
-      u16x4 v[kCoocChunksMax];   // every load unconditional (the last chunk again), so that none waits for another
+    for (int q = 0; q < 4; ++q) {
+      const int h = table.height(block + q / 2), row = 8 * (q & 1) + row_hi;
+      if (row >= h) continue;
+      const int v[4] = {(int)sums[4 * q], (int)sums[4 * q + 1], (int)sums[4 * q + 2], (int)sums[4 * q + 3]};
+      if constexpr (ADDED) {
 #pragma unroll
-      for (int c = 0; c < kCoocChunksMax; ++c) v[c] = *(const u16x4_align2 *)(at + min(c, cp.chunks - 1) * stride);
-#pragma unroll
-      for (int c = 0; c < kCoocChunksMax; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] += c < cp.chunks ? v[c][e] : 0;
-    } else {   // up to three values left: the last one again for what is missing, for the same reason
-      uint16_t v[kCoocChunksMax][3];
-#pragma unroll
-      for (int c = 0; c < kCoocChunksMax; ++c)
-#pragma unroll
-        for (int e = 0; e < 3; ++e) v[c][e] = at[min(c, cp.chunks - 1) * stride + min(e, width - 1 - b)];
-#pragma unroll
-      for (int c = 0; c < kCoocChunksMax; ++c)
-#pragma unroll
-        for (int e = 0; e < 3; ++e) sum[e] += c < cp.chunks && b + e < width ? v[c][e] : 0;
-    }
-    const int rank = p.expert_to_rank[a];
-    const bool placed = (unsigned)rank < (unsigned)p.G;
-    const int own = of_c ? a : placed ? rank / p.per[cut] : 0;   // the column L or L0 is taken from
-    if (cp.added) {
-    } else if (b + 4 <= width) {
-      *(i32x4_align4 *)out = (i32x4){sum[0], sum[1], sum[2], sum[3]};
-    } else {
-#pragma unroll
-      for (int e = 0; e < 3; ++e)
-        if (b + e < width) out[e] = sum[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (b + e == own) {
-        if (of_c) p.L[cut][a] = sum[e];
-        else if (cut == 0) p.L0[a] = placed ? sum[e] : 0;
+        for (int i = 0; i < 4; ++i)
+          if (i < h - row && v[i]) atomicAdd(out + begin + (kBlock * (block + q / 2) + row + i) * width + column, v[i]);
+      } else {
+        store_four(out + (begin + (block + q / 2) * kBlock * width * table.chunks) + ((int)__umul24((uint32_t)h, (uint32_t)column) + row), v, h - row);
       }
     }
-  }
+  };
+  auto put_groups = [&](const f32x16 &sums) {
+    const int g = 32 * g_col + col;
+    if (g < ng) put(sums, (kPanel * panel + 32 * g_row) / kBlock, table.cg(0), ng, ADDED ? g : table.cg_column(g, part));
+  };
+  if (has_c) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) turned[row][col + e] = sum[e];
-  __syncthreads();
-  const int b_out = b0 + row, a_out = a0 + col;   // a row of the transpose
-  if (b_out < width && a_out < E && (of_c || p.cg_by_group[cut])) {
-    int32_t *const out = (of_c ? p.CT[cut] : p.CGT[cut]) + (int64_t)b_out * E + a_out;
-    if (a_out + 4 <= E) {
-      *(i32x4_align4 *)out = (i32x4){turned[col][row], turned[col + 1][row], turned[col + 2][row], turned[col + 3][row]};
-    } else {
+    for (int c = 0; c < COLS; ++c) {
+      const int b = kPanel * panel + 32 * c + col;
+      if (b >= E) continue;
+      put(acc[c], 2 * w, 0, E, ADDED ? b : table.c_column(b, part));
+      if (kPanel * panel + 32 * c == 32 * w && (col & 4) == row_hi) {   // the diagonal: row = col
+        float diagonal = 0.0f;
 #pragma unroll
-      for (int e = 0; e < 3; ++e)
-        if (a_out + e < E) out[e] = turned[col + e][row];
+        for (int r = 0; r < 16; ++r) diagonal = (col >> 3) * 4 + (col & 3) == r ? acc[c][r] : diagonal;
+        value_t *const at = out + table.l(b / kBlock) + part * table.height(b / kBlock) + b % kBlock;
+        if constexpr (!ADDED) *at = (uint16_t)(int)diagonal;
+        else if (diagonal != 0.0f) atomicAdd(at, (int)diagonal);
+      }
     }
+    if (kBoth && has_g) put_groups(second);
+  } else if (has_g) {
+    put_groups(acc[0]);
   }
-  if (!cp.added && blockIdx.x == 0 && threadIdx.x < kWave) {
-    const uint16_t *at = part + (int64_t)E * E + (int64_t)E * ng + threadIdx.x;
-    int v[kCoocChunksMax], base = 0;
-#pragma unroll
-    for (int c = 0; c < kCoocChunksMax; ++c) v[c] = at[min(c, cp.chunks - 1) * stride];
-#pragma unroll
-    for (int c = 0; c < kCoocChunksMax; ++c) base += c < cp.chunks ? v[c] : 0;
-    p.base[cut][threadIdx.x] = base;
+  if (panel != 0) return;
+  __syncthreads();   // a chunk without a token has had none
+  if (counts_base && lane < ng && my_base) atomicAdd(&base_cnt[lane], my_base);
+  __syncthreads();
+  if (tid < kWave) {
+    if constexpr (!ADDED) out[table.base(part) + tid] = (uint16_t)base_cnt[tid];
+    else if (base_cnt[tid]) atomicAdd(out + table.base(part) + tid, base_cnt[tid]);
   }
 }
 
-// One lane per (c, j) of a cut and kBuildRows row experts r: blockIdx.y is the block of rows and
+// Z from the tables: a workgroup takes the pairs of two blocks of up to 16 experts, (r, c) and (c, r), as Z[r][c] = Z[c][r].
+// It sums the chunks of what these pairs need (two blocks of C, the CG rows of 32 experts, every value of C once for the whole
+// chip), puts the two changed counts of every pair together in LDS, and writes both orientations.  What bounds it is
+// the code, which runs once and cold, the trip to the parts, which the kernel before has just written, and the store of Z.  Kernel
+// trace, 128 experts, 16,384 tokens, four cuts: a kernel that summed the chunks and wrote transposes of C and CG, and one that looked them up
+// per value of Z, 4.4 + 5.7 us, now 6.3; 256 experts, 8,192 tokens (15.7 MB of Z) 6.2 + 7.6, now 8.9.
+constexpr int kPairThreads = 512;
+struct PairCut {
+  const void *tables;
+  int32_t *Z;
+  int32_t ng;
+  uint32_t per_recip16;   // ceil(2^16 / ranks of a group): exact for ranks (below 64)
+  int32_t wide, of_pair;                  // groups of a lane's store, 4 or 1; lanes that take a pair: ng / wide
+  int32_t of_pair_recip20, pairs_at_once;   // ceil(2^20 / of_pair), kPairThreads / of_pair
+};
+struct PairParams {
+  const int32_t *expert_to_rank;
+  int32_t *status;
+  int32_t E, G, ncuts, blocks;   // blocks of experts
+  PairCut cut[kMaxCuts];
+};
+__device__ __forceinline__ i32x4 load_four(const int32_t *at) { return *(const i32x4_align4 *)at; }
+__device__ __forceinline__ u16x4 load_four(const uint16_t *at) { return *(const u16x4_align2 *)at; }
+
+// N chunks, every STEP-th, of four values that begin at i of the n of a chunk; `at` is the first of these chunks.  SUM: type in which
+// the chunks are added, 16 bits where all tokens together cannot exceed them (two values per instruction), else 32.
+template <int N, int STEP, typename V>
+struct Chunks {
+  decltype(load_four((const V *)nullptr)) v[N];
+  __device__ __forceinline__ void load(const V *at, int n, int i) {
+    const uint32_t bytes = (uint32_t)i * sizeof(V);
+#pragma unroll
+    for (int j = 0; j < N; ++j, at += STEP * n) v[j] = load_four((const V *)((const char *)at + bytes));
+  }
+  template <typename SUM>
+  __device__ __forceinline__ void sum(int32_t *out) const {
+    typedef SUM four __attribute__((ext_vector_type(4)));
+    four sum = __builtin_convertvector(v[0], four);
+#pragma unroll
+    for (int j = 1; j < N; ++j) sum += __builtin_convertvector(v[j], four);
+    *(i32x4_align4 *)out = __builtin_convertvector(sum, i32x4);
+  }
+};
+// Blocks of fewer than four values (the last of a few experts with a few groups): a lane per value.
+template <typename V>
+__device__ __forceinline__ void sum_few(int32_t *out, const V *at, int n, int i, int count, int step) {
+  if (i >= n) return;
+  int sum = 0;
+  for (int c = 0; c < count; ++c) sum += at[c * step * n + i];
+  out[i] = sum;
+}
+
+// V, SUM: types of a count in the tables and of the sum of all chunks'.
+template <typename V, typename SUM, int CHUNKS>   // one chunk: tables that chunks were added to
+__global__ __launch_bounds__(kPairThreads) void swap_pairs_kernel(PairParams p) {
+  constexpr int kOfC = CHUNKS > 4 ? 4 : 1, kOfCG = CHUNKS > 4 ? 2 : 1;   // waves that share the chunks of a value
+  __shared__ __align__(16) int32_t s_c[2][kOfC][kBlock * kBlock];    // [block (I, J), (J, I)]
+  __shared__ __align__(16) int32_t s_cg[2][kOfCG][kBlock * kWave];   // [block I, J][group][expert]
+  __shared__ __align__(16) i32x4 s_pair[kBlock][kBlock + 1];         // [r][c]: what the groups of c and of r gain, and which they are
+  __shared__ int32_t s_l[2 * kBlock], s_group[2 * kBlock], s_base[kWave];   // of I, of J
+
+  const PairCut cut = p.cut[p.ncuts - 1 - (int)blockIdx.z];   // the last cut first: usually the finest, whose workgroups last longest
+  const int ng = cut.ng, E = p.E, blocks = p.blocks;
+  // every unordered pair of blocks once: (I, I + y) round the circle, of the opposite ones half
+  const int I = blockIdx.x, y = blockIdx.y, J = I + y < blocks ? I + y : I + y - blocks;
+  if (2 * y == blocks && I >= y) return;
+  const Tables table = {E, ng, CHUNKS};
+  const V *const part = (const V *)cut.tables;
+  const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int height_i = table.height(I), height_j = table.height(J);
+
+  // Waves 0 to 3 have block (I, J) of C and the CG of I, 4 to 7 block (J, I) and J.  Every load is on its way before the first is used.
+  const int side = w >> 2, of_c = w & (kOfC - 1), of_cg = w >> 1 & (kOfCG - 1), n_c = height_i * height_j, n_cg = (side ? height_j : height_i) * ng;
+  const int c_i = min(4 * lane, n_c - 4), q0 = (w & 1) * kWave + lane, cg_i = min(4 * q0, n_cg - 4);   // the last four may be values of another lane, too
+  const int rows_of = side ? J : I, cols_of = side ? I : J, rows = side ? height_j : height_i, cols = side ? height_i : height_j;
+  const V *const c_at = part + table.c(rows_of) + rows * table.c_column(kBlock * cols_of, of_c);
+  const V *const cg_at = part + table.cg(rows_of) + rows * table.cg_column(0, of_cg);
+  Chunks<CHUNKS / kOfC, kOfC, V> c;
+  Chunks<CHUNKS / kOfCG, kOfCG, V> cg;
+  V plain = 0;   // of plain rows: a value of the block per lane of its waves
+  if (CHUNKS > 1) {
+    if (n_c >= 4) c.load(c_at, n_c, c_i);
+  } else {
+    const int i = tid & (kBlock * kBlock - 1);
+    plain = part[(kBlock * rows_of + min(i & (kBlock - 1), rows - 1)) * E + kBlock * cols_of + min(i >> 4, cols - 1)];
+  }
+  if (n_cg >= 4) cg.load(cg_at, n_cg, cg_i);
+  const int a = lane & (kBlock - 1), of_j = lane >> 4 & 1, h = of_j ? height_j : height_i;
+  int l = 0, base[2] = {0, 0}, rank = -1;   // of one chunk or two
+  {
+    const int chunk = 2 * w + (lane >> 5);
+    if (chunk < CHUNKS && a < h) l = part[table.l(of_j ? J : I) + chunk * h + a];
+    if (w < CHUNKS) base[0] = part[table.base(w) + lane];
+    if (CHUNKS > kPairThreads / kWave) base[1] = part[table.base(w + kPairThreads / kWave) + lane];
+    if (w == 0 && lane < 2 * kBlock && a < h) rank = p.expert_to_rank[kBlock * (of_j ? J : I) + a];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (CHUNKS == 1) {
+    const int i = tid & (kBlock * kBlock - 1), row = i & (kBlock - 1), col = i >> 4;
+    if (row < rows && col < cols) s_c[side][0][col * rows + row] = (int)plain;
+  } else if (n_c >= 4) c.template sum<SUM>(&s_c[side][of_c][c_i]);
+  else sum_few(s_c[side][of_c], c_at, n_c, lane, CHUNKS / kOfC, kOfC);
+  if (__builtin_expect(n_cg < 4, 0)) {
+    sum_few(s_cg[side][of_cg], cg_at, n_cg, q0, CHUNKS / kOfCG, kOfCG);
+  } else {
+    cg.template sum<SUM>(&s_cg[side][of_cg][cg_i]);
+    if (__builtin_expect(n_cg > 8 * kWave, 0)) {   // more than 32 groups
+      const int i = min(4 * (q0 + 2 * kWave), n_cg - 4);
+      cg.load(cg_at, n_cg, i);
+      cg.template sum<SUM>(&s_cg[side][of_cg][i]);
+    }
+  }
+  if (tid < 2 * kBlock) s_l[tid] = 0;
+  if (tid < kWave) s_base[tid] = 0;
+  __syncthreads();
+  if (l) atomicAdd(&s_l[lane & (2 * kBlock - 1)], l);
+  if (base[0] + base[1]) atomicAdd(&s_base[lane], base[0] + base[1]);
+  if (tid < 2 * kBlock) {
+    s_group[tid] = (unsigned)rank < (unsigned)p.G ? (int)(((uint32_t)rank * cut.per_recip16) >> 16) : -1;
+  }
+  __syncthreads();
+
+  if (tid < kBlock * kBlock) {
+    const int r = tid & (kBlock - 1), c = tid >> 4;
+    if (r < height_i && c < height_j) {
+      const int gr = s_group[r], gc = s_group[kBlock + c];
+      i32x4 pair = {0, 0, -1, -1};
+      if (gr < 0 || gc < 0) flag(p.status, HM_ERR_BAD_ID);
+      if (gr >= 0 && gc >= 0 && gr != gc) {
+        int gain_c = -s_l[kBlock + c], gain_r = -s_l[r];
+#pragma unroll
+        for (int i = 0; i < kOfC; ++i) {
+          gain_c += s_c[1][i][r * height_j + c];   // C[c][r]
+          gain_r += s_c[0][i][c * height_i + r];   // C[r][c]
+        }
+#pragma unroll
+        for (int i = 0; i < kOfCG; ++i) {
+          auto of_r = [&](int g) { return s_cg[0][i][CHUNKS > 1 ? g * height_i + r : r * ng + g]; };
+          auto of_c = [&](int g) { return s_cg[1][i][CHUNKS > 1 ? g * height_j + c : c * ng + g]; };
+          gain_c += of_r(gr) - of_r(gc);   // L0[r] - CG[r][gc]
+          gain_r += of_c(gc) - of_c(gr);
+        }
+        pair = (i32x4){gain_c, gain_r, gc, gr};
+      }
+      s_pair[r][c] = pair;
+    }
+  }
+  __syncthreads();
+
+  // `of_pair` neighbouring lanes take a pair, a lane the same groups of every pair it takes.
+  const int of_pair = cut.of_pair, wide = cut.wide;
+  const int first = (int)((uint32_t)tid * (uint32_t)cut.of_pair_recip20 >> 20), j = wide * (tid - first * of_pair), at_once = cut.pairs_at_once;
+  if (first >= at_once) return;
+  i32x4 base4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) base4[e] = s_base[min(j + e, kWave - 1)];
+#pragma unroll 1
+  for (int turned = 0; turned < (I == J ? 1 : 2); ++turned) {
+    const int cols = turned ? height_i : height_j, pairs = height_i * height_j;
+    const uint32_t recip16 = cols == kBlock ? 65536u / kBlock : (65536u + (uint32_t)cols - 1u) / (uint32_t)cols;
+    int32_t *const out = cut.Z + ((int64_t)(kBlock * (turned ? J : I)) * E + kBlock * (turned ? I : J)) * ng + j;
+#pragma unroll 1
+    for (int i = first; i < pairs; i += at_once) {
+      const int row = (int)((uint32_t)i * recip16 >> 16), col = i - row * cols;
+      const i32x4 pair = turned ? s_pair[col][row] : s_pair[row][col];
+      i32x4 z = base4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] += (pair[2] == j + e ? pair[0] : 0) + (pair[3] == j + e ? pair[1] : 0);
+      int32_t *const at = out + (row * E + col) * ng;
+      if (wide == 4) *(i32x4_align4 *)at = z;
+      else *at = z[0];
+    }
+  }
+}
+
+// Z by the atomics' tables: one lane per (c, j) of a cut and kBuildRows row experts r: blockIdx.y is the block of rows and
 // blockIdx.x runs over the column blocks (256 consecutive (c, j)) of all cuts, one cut after the
 // other.  The loads of all rows are issued before the first value is put together, so a lane
 // waits for memory once, and the waves are long enough for the chip not to be bound by starting
 // them.  The two divisions a lane needs are multiplications by rounded-up reciprocals: c = l / ng
 // (exact for l < 2^32 / ng, and l < 64 E < 2^19) and group = rank / per (rank < 64).
 constexpr int kBuildRows = 4;
-
-// The same for cuts of a multiple of four groups, where a lane takes four neighbouring groups j of its c:
-// their unswapped counts are read once for all rows, a row costs one 16-byte store, and only the lanes
-// that hold the group of c or of r look anything up (a quarter of the lanes, each of whose rows is
-// a few instructions: 256 experts, four cuts, 15.7 MB of Z, kernel trace 12.8 -> 9.3 us, where the fastest launches take 7.5).
-__device__ __forceinline__ void build_quads(const SwapParams &p, int cut, int l, int r0) {
-  const int ng = p.ng[cut], nq = ng / 4;
-  const int32_t *__restrict__ const C = p.C[cut];
-  const int32_t *__restrict__ const CT = p.CT[cut];
-  const int32_t *__restrict__ const CG = p.CG[cut];
-  const int32_t *__restrict__ const CGT = p.CGT[cut];
-  const int by_group = p.cg_by_group[cut];
-  const int32_t *__restrict__ const L = p.L[cut];
-  const int32_t *__restrict__ const L0 = p.L0;
-  const unsigned per_reciprocal = p.per_reciprocal[cut];
-  const int c = nq == 1 ? l : (int)__umulhi((unsigned)l, p.quad_reciprocal[cut]);
-  const int jq = l - c * nq;
-  const int rk = p.expert_to_rank[c];
-  const bool c_ok = (unsigned)rk < (unsigned)p.G;
-  const int gc = !c_ok ? -1 : per_reciprocal ? (int)__umulhi((unsigned)rk, per_reciprocal) : rk;
-  const i32x4 base = *(const i32x4_align4 *)(p.base[cut] + 4 * jq);
-  const int L_c = L[c], L0_c = L0[c];
-  const bool holds_c = c_ok && (gc >> 2) == jq;
-  int group_r[kBuildRows];   // r's group if it is one of the four and not c's
-  int cg[kBuildRows], ct[kBuildRows], cgt[kBuildRows], cc[kBuildRows], L_r[kBuildRows], L0_r[kBuildRows];
-  bool gains[kBuildRows], bad = false;
-#pragma unroll
-  for (int i = 0; i < kBuildRows; ++i) {
-    const int r = min(r0 + i, p.E - 1);   // uniform
-    const int rr = p.expert_to_rank[r];
-    const bool r_ok = (unsigned)rr < (unsigned)p.G;
-    const int gr = !r_ok ? -1 : per_reciprocal ? (int)__umulhi((unsigned)rr, per_reciprocal) : rr;
-    bad = bad || !r_ok || !c_ok;
-    const bool moves = r_ok && c_ok && gr != gc;
-    gains[i] = moves && holds_c;
-    group_r[i] = moves && (gr >> 2) == jq ? gr & 3 : -1;
-    cg[i] = ct[i] = cgt[i] = cc[i] = 0;
-    L_r[i] = L[r];
-    L0_r[i] = L0[r];
-    if (gains[i]) {
-      cg[i] = CG[(int64_t)r * ng + gc];
-      ct[i] = CT[(int64_t)r * p.E + c];
-    }
-    if (group_r[i] >= 0) {
-      cgt[i] = CGT[by_group ? gr * p.E + c : c * ng + gr];
-      cc[i] = C[(int64_t)r * p.E + c];
-    }
-  }
-  if (bad && jq == 0) flag(p.status, HM_ERR_BAD_ID);
-#pragma unroll
-  for (int i = 0; i < kBuildRows; ++i) {
-    i32x4 z = base;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      z[e] += gains[i] && (gc & 3) == e ? (L0_r[i] - cg[i]) - (L_c - ct[i]) : 0;
-      z[e] += group_r[i] == e ? (L0_c - cgt[i]) - (L_r[i] - cc[i]) : 0;
-    }
-    if (r0 + i < p.E) *(i32x4_align4 *)(p.Z[cut] + ((int64_t)(r0 + i) * p.E * ng + 4 * (int64_t)l)) = z;
-  }
-}
-
-// QUADS: whether any cut takes four groups per lane; the registers that takes slow the other form down (E = 300 through
-// the atomics, four cuts, 1,024 tokens, K = 2, the whole call: 56.8 -> 55.3 us).
-template <bool QUADS>
 __global__ __launch_bounds__(kSwapThreads) void swap_build_kernel(SwapParams p) {
   int cut = 0, block = blockIdx.x;
   while (cut + 1 < p.ncuts && block >= p.build_blocks[cut]) block -= p.build_blocks[cut++];
   const int ng = p.ng[cut], r0 = blockIdx.y * kBuildRows;
   const int l = block * kSwapThreads + threadIdx.x;
-  if (QUADS && p.quads[cut]) {
-    if (l < p.E * (ng / 4)) build_quads(p, cut, l, r0);
-    return;
-  }
   if (l >= p.E * ng) return;
   const int32_t *__restrict__ const C = p.C[cut];
-  const int32_t *__restrict__ const CT = p.CT[cut];
   const int32_t *__restrict__ const CG = p.CG[cut];
-  const int32_t *__restrict__ const CGT = p.CGT[cut];
   const int32_t *__restrict__ const L = p.L[cut];
   const int32_t *__restrict__ const L0 = p.L0;
   int32_t *__restrict__ const Z = p.Z[cut];
@@ -764,16 +805,10 @@ __global__ __launch_bounds__(kSwapThreads) void swap_build_kernel(SwapParams p) 
       bad = true;
     } else if (gr != gc && (j == gc || j == gr)) {
       const int a = j == gc ? r : c, b = j == gc ? c : r;   // group j gains tokens of a, loses tokens of b
-      int cba = 0, cg;
-      if (p.transposed) {   // every read runs along row r of a table, or along c
-        cba = j == gc ? CT[(int64_t)r * p.E + c] : C[(int64_t)r * p.E + c];
-        cg = j == gc ? CG[(int64_t)r * ng + j] : CGT[p.cg_by_group[cut] ? j * p.E + c : c * ng + j];
-      } else {
+      int cba = 0;
 #pragma unroll 8
-        for (int k = 0; k < p.copies; ++k) cba += C[((int64_t)k * p.E + b) * p.E + a];
-        cg = CG[(int64_t)a * ng + j];
-      }
-      add[i] = L0[a] - cg;
+      for (int k = 0; k < p.copies; ++k) cba += C[((int64_t)k * p.E + b) * p.E + a];
+      add[i] = L0[a] - CG[(int64_t)a * ng + j];
       sub_[i] = L[b] - cba;
     }
   }
@@ -986,7 +1021,7 @@ static bool swap_factors_lds_ready() {
 // but each is cleared and summed again.  The matrix path keeps one summed C.
 // Whether the workspace has partial tables of chunks (and a byte per slot): E <= 256 and chunks short enough for
 // 16-bit counts.
-static inline bool swap_has_parts(int64_t E, int64_t T) { return E <= kCoocPartMaxE && T <= (int64_t)kCoocChunksMax * kCoocChunkTokensMax; }
+static inline bool swap_has_parts(int64_t E, int64_t T) { return E <= kCoocPartMaxE && T <= (int64_t)kCoocChunks * kCoocChunkTokensMax; }
 static inline int64_t swap_copies(int64_t E, int64_t T) {
   if (swap_has_parts(E, T)) return 1;
   int64_t n = kSwapCopiesMax;   // a power of two, so that a workgroup finds its copy with a mask
@@ -994,59 +1029,69 @@ static inline int64_t swap_copies(int64_t E, int64_t T) {
   return n;
 }
 
-// Workspace, in ints: L0 [E], then per cut base [64] | L [E] | CG [E * ng] | C [copies * E * E], and on the
-// matrix path the partial tables of kCoocChunksMax chunks and the transposes of C and CG after that.
+// Workspace, in ints: L0 [E], then per cut base [64] | L [E] | CG [E * ng] | C [copies * E * E], and where there is room
+// for parts as much again as the tables of kCoocChunks chunks and a second C and CG take.  The matrix path lays its
+// tables out over all of it, cut after cut: they need less.
+static inline int64_t cooc_part_words(int64_t E, int64_t ng) { return (E * E + E * ng + 65) / 2; }
 static inline int64_t swap_cut_ints(int64_t E, int64_t ng, int64_t T) {
   return 64 + E + E * ng + swap_copies(E, T) * E * E +
-         (swap_has_parts(E, T) ? kCoocChunksMax * cooc_part_words(E, ng) + E * E + E * ng : 0);
+         (swap_has_parts(E, T) ? kCoocChunks * cooc_part_words(E, ng) + E * E + E * ng : 0);
 }
 // ... and, on the matrix path, one byte per routing slot at the very end.
 static inline int64_t swap_slot_ints(int64_t T, int64_t K, int64_t E) { return swap_has_parts(E, T) ? (T * K + 3) / 4 : 0; }
 
-// The matrix kernel for E experts and K slots, the columns of a panel and the dynamic LDS (0: the device does not grant that much).
+// The matrix kernel for E experts, the columns of a panel, the tokens of a tile (0: the device does not grant the LDS).
 typedef void (*cooc_kernel_t)(CoocParams);
 struct CoocLaunch {
   cooc_kernel_t kernel;
-  int ne, panel;
+  int panel, tile_tokens, stride;
   size_t lds;
 };
-template <int NE, bool OWN_SLOTS>
-static CoocLaunch cooc_launch() {
-  constexpr size_t tiles = (size_t)(32 * NE + 2 * (32 * cooc_cols(NE) + kCoocGroups)) * kCoocStride, bytes = tiles + 4 * kCoocStaged;
+template <int COLS, bool OWN_SLOTS, bool ADDED>
+static CoocLaunch cooc_launch(int E, int groups, int64_t tokens) {   // groups of the finest cut, tokens of a chunk
   static const bool granted = [] {
-    const hipError_t e = hipFuncSetAttribute((const void *)swap_cooc_kernel<NE, OWN_SLOTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)bytes);
+    const hipError_t e = hipFuncSetAttribute((const void *)swap_cooc_kernel<COLS, OWN_SLOTS, ADDED>, hipFuncAttributeMaxDynamicSharedMemorySize, kCoocLds);
     if (e != hipSuccess) (void)hipGetLastError();   // not sticky: do not let it fail the next launch check
     return e == hipSuccess;
   }();
-  return {swap_cooc_kernel<NE, OWN_SLOTS>, NE, 32 * cooc_cols(NE), granted ? bytes : 0};
+  constexpr int kBatch = 4 / COLS * kCoocStep;   // a tile is whole batches of products
+  const int rows = (E + 31) / 32 * 32 + 32 * COLS + (groups + 31) / 32 * 32;
+  int most = 2 * (kCoocLds / rows - kCoocPad) / kBatch * kBatch;
+  if (most > kCoocThreads) most = kCoocThreads;
+  CoocLaunch l = {swap_cooc_kernel<COLS, OWN_SLOTS, ADDED>, 32 * COLS, 0, 0, 0};
+  if (!granted) return l;
+  const int64_t tiles = tokens > most ? (tokens + most - 1) / most : 1;   // all of a size
+  l.tile_tokens = (int)(((tokens + tiles - 1) / tiles + kBatch - 1) / kBatch * kBatch);
+  if (l.tile_tokens < kBatch) l.tile_tokens = kBatch;   // no tokens at all
+  l.stride = l.tile_tokens / 2 + kCoocPad;
+  l.lds = (size_t)rows * l.stride;
+  return l;
 }
-template <bool OWN_SLOTS>
-static CoocLaunch cooc_launch_for(int E) {
-  return E <= 32    ? cooc_launch<1, OWN_SLOTS>()
-         : E <= 64  ? cooc_launch<2, OWN_SLOTS>()
-         : E <= 128 ? cooc_launch<4, OWN_SLOTS>()
-         : E <= 256 ? cooc_launch<8, OWN_SLOTS>()
-                    : cooc_launch<16, true>();   // there is no room for the bytes of swap_slots_kernel beyond
+static inline int cooc_columns(int E) { return E > 128 && E <= kCoocPartMaxE ? 2 : 1; }   // tile columns of a panel
+template <int COLS>
+static inline CoocLaunch cooc_launch_for(int E, bool own_slots, bool parts, int groups, int64_t tokens) {
+  if (!parts) return cooc_launch<COLS, true, true>(E, groups, tokens);
+  return own_slots ? cooc_launch<COLS, true, false>(E, groups, tokens) : cooc_launch<COLS, false, false>(E, groups, tokens);
 }
-
-static inline int cooc_chunks(const CoocLaunch &cooc, bool parts, int64_t T, int64_t E, int ncuts) {
-  const int64_t panels = (E + cooc.panel - 1) / cooc.panel, tiles = (T + kCoocTokens - 1) / kCoocTokens;
-  const int64_t most = parts ? kCoocChunksMax : kCoocAddedGroups / (panels * ncuts), chunks = most > tiles ? tiles : most;
-  return (int)(chunks < 1 ? 1 : chunks);
+static inline int cooc_chunks(bool parts, int64_t T, int64_t E, int ncuts) {
+  if (parts) return kCoocChunks;
+  const int64_t panel = 32 * cooc_columns((int)E), panels = (E + panel - 1) / panel, tiles = (T + 127) / 128;
+  const int64_t most = kCoocAddedGroups / (panels * ncuts), least = (T + kCoocAddedTokensMax - 1) / kCoocAddedTokensMax;
+  const int64_t chunks = most > tiles ? tiles : most;
+  return (int)(chunks < least ? least : chunks < 1 ? 1 : chunks);
 }
 
 // Whether atomics per slot are faster than matrix products whose chunks are added up: with few slots per token or few groups, as
-// the products take the same time however few marks a tile holds.  Two straight lines, us, through 4,701 shapes (256 < E <= 512, up to 520,000
-// tokens; E <= 256, 522,241 to 800,000; one to eight slots, one to four cuts; ids drawn evenly): Z, the updates of C (a slot's K - 1
-// others where it is alone in its group) and of L0, L and CG (in LDS or in memory), and the workgroups that put their tables
-// together; against a time per tile of 128 tokens.  One or two tiles are matrices at any rate, but for next to no groups.  A popular few
-// experts make only the atomics slower, so they have to be ahead by a fifth: of 4,105 shapes of more than two groups with even ids 277 lose
-// more than 3 % by that (one half as much again) and 9 the other way round, of 2,980 with a Zipf router 71 and 131.
-// Atomics / matrices: E = 512, cuts of 4 and 32, 65,536 tokens: K = 1 53 / 107, 2 63 / 110, 4 103 / 117 (Zipf 181 / 112), 8 (30,000
-// tokens) 131 / 74; E = 260, 2, 4 and 8, 16,384 tokens: K = 1 24 / 34, 8 53 / 40; E = 256, 530,000 tokens: K = 1 46 / 145, 2 108 /
-// 153, 3 220 / 157.
-static bool atomics_pay(int64_t T, int64_t K, int64_t E, int ncuts, const int32_t *ng, bool in_lds, int ne, int chunks) {
+// the products take the same time however few marks a tile holds.  Two straight lines, us, through some 4,000 shapes (256 < E <= 512,
+// up to 520,000 tokens; E <= 256, 522,241 to 800,000; one to eight slots, one to four cuts; ids drawn evenly): Z, the
+// updates of C (a slot's K - 1 others where it is alone in its group) and of L0, L and CG (in LDS or in memory), and the
+// workgroups that put their tables together; against Z and a time per tile, for its barriers, its tokens and the bytes cleared (within
+// 10 % for nine in ten).  A popular few experts make only the atomics slower, and those of C most, so they have to be ahead by a tenth
+// if there are such; without (one slot, or one group) they may be estimated behind by an eighth, by which the line for them is
+// too high there.  Of 1,500 shapes, half of them with a Zipf router, the rule loses more than 3 % in 122 (95 Zipf ids by atomics).
+// Atomics / matrices: E = 320, one group, 18,696 tokens, K = 1 11.2 / 15.9; E = 288, 46,004 tokens, cuts of 1 and 8, K = 2 23 / 30; E = 512,
+// cuts of 16 and 64, 373,641 tokens, K = 2, Zipf 4,663 / 399; E = 64, one group, 700,000 tokens, K = 2 24 / 45.
+static bool atomics_pay(int64_t T, int64_t K, int64_t E, int ncuts, const int32_t *ng, bool in_lds, int64_t tiles, const CoocLaunch &cooc) {
   double groups = 0.0, others = 0.0, touched = 1.0;   // per slot: updates of C, words of L0, L and CG
   for (int c = 0; c < ncuts; ++c) {
     double alone = (double)(K - 1);
@@ -1055,16 +1100,15 @@ static bool atomics_pay(int64_t T, int64_t K, int64_t E, int ncuts, const int32_
     others += alone;
     touched += 1.0 + (double)(K < ng[c] ? K : ng[c]);
   }
-  const int64_t tiles = ((T + kCoocTokens - 1) / kCoocTokens + chunks - 1) / chunks;   // of a workgroup
-  if (tiles <= 2 && groups > 4.0) return false;
   int64_t lanes = 1;
   while (lanes < K) lanes *= 2;
   const double pairs = (double)(E * E) * 1e-6, slots = (double)(T * K) * 1e-6, filled = (double)(T * lanes) / (256.0 * kFactorThreads);
   const double flush = filled < 1.0 ? filled : 1.0;   // of 256 workgroups
   const double atomics = in_lds ? 10.0 + 4.3 * pairs * groups + slots * (28.0 * others + 1.4 * touched) + 3.2 * ncuts + 6.6 * flush
                                 : 45.0 + 2.4 * pairs * groups + 54.0 * slots * touched + 59.0 * flush;
-  const double matrices = 15.0 + 6.0 * pairs * ncuts + 0.86 * pairs * groups + (double)tiles * (0.64 + 0.031 * (double)(ne + K));
-  return 1.2 * atomics < matrices;
+  const double tile = 0.4 + 0.0019 * cooc.tile_tokens + 0.175 * (double)cooc.lds / 16384.0;
+  const double matrices = 9.7 + 6.3 * pairs * ncuts + 0.7 * pairs * groups + (double)tiles * tile;
+  return (others < 0.05 ? 0.85 : 1.1) * atomics < matrices;
 }
 
 static inline bool swap_cuts_ok(int32_t G, int32_t ncuts, const int32_t *ng) {
@@ -1119,90 +1163,98 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
   // are added to cleared tables, as long as the marks of the slots need no room either and that is the faster way.
   const bool parts = swap_has_parts(E, T), own_slots = K <= kCoocOwnK;
   const bool in_lds = lds_at <= kSwapLds && swap_factors_lds_ready();
-  CoocParams cp;
-  cp.sub_log2 = 0;
-  while ((1 << cp.sub_log2) < K) ++cp.sub_log2;
-  CoocLaunch cooc = {nullptr, 0, 0, 0};
-  if (parts || (own_slots && E <= kCoocMaxE)) cooc = own_slots ? cooc_launch_for<true>(E) : cooc_launch_for<false>(E);
-  const int chunks = cooc.lds != 0 ? cooc_chunks(cooc, parts, T, E, ncuts) : 0;
-  if (cooc.lds != 0 && (parts || !atomics_pay(T, K, E, ncuts, ng, in_lds, cooc.ne, chunks))) {
-    p.ws_ints = parts ? 0 : at;   // parts are written in full by the kernels below: only the status word needs clearing
-    p.use_lds = 0;
-    p.transposed = 1;
-    if (status || p.ws_ints) {
-      const int64_t n = p.ws_ints > 0 ? p.ws_ints : 1;
-      hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((n + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0, stream, p);
+  if (parts || (own_slots && E <= kCoocMaxE)) {   // parts imply E <= 256
+    CoocParams cp;
+    int groups = 1;
+    for (int c = 0; c < ncuts; ++c) groups = ng[c] > groups ? ng[c] : groups;
+    cp.chunks = cooc_chunks(parts, T, E, ncuts);
+    const int64_t steps = ((int64_t)T + kCoocStep - 1) / kCoocStep;
+    cp.tokens_per_chunk = (int32_t)((steps + cp.chunks - 1) / cp.chunks * kCoocStep);
+    const CoocLaunch cooc = cooc_columns(E) == 2 ? cooc_launch_for<2>(E, own_slots, parts, groups, cp.tokens_per_chunk)
+                                                   : cooc_launch_for<1>(E, own_slots, parts, groups, cp.tokens_per_chunk);
+    const int tiles = cooc.lds ? (cp.tokens_per_chunk + cooc.tile_tokens - 1) / cooc.tile_tokens : 0;
+    if (cooc.lds != 0 && (parts || !atomics_pay(T, K, E, ncuts, ng, in_lds, tiles, cooc))) {
+      PairParams pp;
+      cp.ids = topk_ids;
+      cp.expert_to_rank = expert_to_rank;
+      cp.T = T;
+      cp.K = K;
+      cp.E = E;
+      cp.G = G;
+      cp.ncuts = ncuts;
+      cp.sub_log2 = 0;
+      while ((1 << cp.sub_log2) < K) ++cp.sub_log2;
+      cp.k_reciprocal = K > 1 ? (uint32_t)((0x100000000ull + (uint64_t)K - 1) / (uint64_t)K) : 0u;
+      cp.tile_tokens = cooc.tile_tokens;
+      cp.stride = cooc.stride;
+      cp.words_recip17 = (uint32_t)((1 << 17) + cooc.tile_tokens / 8 - 1) / (uint32_t)(cooc.tile_tokens / 8);
+      cp.slot_bits = (uint8_t *)(p.ws + at);
+      cp.status = status;
+      int64_t tables = 0;   // they take less room than a cut has for its tables by atomics, or its parts
+      for (int c = 0; c < kMaxCuts; ++c) {
+        const int cc = c < ncuts ? c : 0;
+        cp.ng[c] = p.ng[cc];
+        cp.per[c] = p.per[cc];
+        cp.per_recip16[c] = (uint32_t)((65536 + cp.per[c] - 1) / cp.per[c]);
+        cp.tables[c] = c < ncuts ? p.ws + tables : cp.tables[0];
+        if (c < ncuts) tables += parts ? (Tables::values(E, ng[c]) * cp.chunks + 1) / 2 : Tables::values(E, ng[c]);
+        PairCut &cut = pp.cut[c];
+        cut.tables = cp.tables[c];
+        cut.Z = p.Z[cc];
+        cut.ng = cp.ng[c];
+        cut.per_recip16 = cp.per_recip16[c];
+        cut.wide = cut.ng % 4 == 0 ? 4 : 1;
+        cut.of_pair = cut.ng / cut.wide;
+        cut.of_pair_recip20 = ((1 << 20) + cut.of_pair - 1) / cut.of_pair;
+        cut.pairs_at_once = kPairThreads / cut.of_pair;
+      }
+      p.ws_ints = parts ? 0 : tables;   // parts are written in full: only the status word needs clearing
+      if (status || p.ws_ints) {
+        const int64_t n = p.ws_ints > 0 ? p.ws_ints : 1;
+        hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((n + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0, stream, p);
+        if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+      }
+      if (T > 0 && !own_slots) {
+        const int64_t lanes = (int64_t)T << cp.sub_log2;
+        hipLaunchKernelGGL(swap_slots_kernel, dim3((unsigned)((lanes + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0,
+                           stream, cp);
+        if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+      }
+      const int panels = (E + cooc.panel - 1) / cooc.panel;
+      hipLaunchKernelGGL(cooc.kernel, dim3((unsigned)cp.chunks, (unsigned)ncuts, (unsigned)panels), dim3(kCoocThreads), cooc.lds, stream, cp);
       if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+      pp.expert_to_rank = expert_to_rank;
+      pp.E = E;
+      pp.G = G;
+      pp.ncuts = ncuts;
+      pp.blocks = (E + kBlock - 1) / kBlock;
+      pp.status = status;
+      const unsigned blocks = (unsigned)pp.blocks;
+      hipLaunchKernelGGL((!parts ? swap_pairs_kernel<int32_t, uint32_t, 1> : T <= 65535 ? swap_pairs_kernel<uint16_t, uint16_t, kCoocChunks> : swap_pairs_kernel<uint16_t, uint32_t, kCoocChunks>),
+                         dim3(blocks, blocks / 2 + 1, (unsigned)ncuts), dim3(kPairThreads), 0, stream, pp);
+      return hm_launch_status();
     }
-    cp.ids = topk_ids;
-    cp.expert_to_rank = expert_to_rank;
-    cp.T = T;
-    cp.K = K;
-    cp.E = E;
-    cp.G = G;
-    cp.ncuts = ncuts;
-    cp.added = parts ? 0 : 1;
-    cp.slot_bits = (uint8_t *)(p.ws + at);
-    const int panels = (E + cooc.panel - 1) / cooc.panel, tiles = (int)(((int64_t)T + kCoocTokens - 1) / kCoocTokens);
-    cp.chunks = chunks;
-    cp.tokens_per_chunk = (tiles + chunks - 1) / chunks * kCoocTokens;
-    int max_tiles = 0;
-    for (int c = 0; c < kMaxCuts; ++c) {
-      const int64_t table = (int64_t)E * E, cg = (int64_t)E * p.ng[c];
-      cp.ng[c] = p.ng[c];
-      cp.per[c] = p.per[c];
-      cp.C[c] = p.C[c];
-      cp.CG[c] = p.CG[c];
-      cp.base[c] = p.base[c];
-      cp.part[c] = (uint16_t *)(p.C[c] + table);   // behind the summed C of the cut, and behind them the transposes;
-      p.CT[c] = p.C[c] + table + (parts ? kCoocChunksMax * cooc_part_words(E, p.ng[c]) : 0);   // else they take copies of C
-      p.cg_by_group[c] = parts || (p.copies - 2) * table >= cg;
-      p.CGT[c] = p.cg_by_group[c] ? p.CT[c] + table : p.CG[c];
-      if (c < ncuts && reduce_tiles(E, ng[c]) > max_tiles) max_tiles = reduce_tiles(E, ng[c]);
-    }
-    cp.status = status;
-    if (T > 0 && !own_slots) {
-      const int64_t lanes = (int64_t)T << cp.sub_log2;
-      hipLaunchKernelGGL(swap_slots_kernel, dim3((unsigned)((lanes + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0,
-                         stream, cp);
-      if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-    }
-    hipLaunchKernelGGL(cooc.kernel, dim3((unsigned)chunks, (unsigned)ncuts, (unsigned)panels), dim3(kCoocThreads), cooc.lds, stream, cp);
+  }
+  p.ws_ints = at;
+  p.use_lds = in_lds ? 1 : 0;
+  hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((p.ws_ints + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads), 0, stream,
+                     p);
+  if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+  if (T > 0) {
+    const int64_t tokens_per_block = (int64_t)(kFactorThreads / kWave) * (kWave / p.sub);
+    int64_t blocks = ((int64_t)T + tokens_per_block - 1) / tokens_per_block;
+    if (blocks > 256) blocks = 256;   // one per CU; every block flushes its LDS tables with atomics
+    hipLaunchKernelGGL(swap_factors_kernel, dim3((unsigned)blocks), dim3(kFactorThreads), p.use_lds ? (size_t)lds_at * sizeof(int32_t) : 0,
+                       stream, p);
     if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-    hipLaunchKernelGGL(swap_reduce_kernel, dim3((unsigned)max_tiles, (unsigned)ncuts), dim3(kSwapThreads), 0, stream, p, cp);
-    if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-  } else {
-    p.transposed = 0;
-    for (int c = 0; c < kMaxCuts; ++c) {
-      p.CT[c] = p.CGT[c] = nullptr;
-      p.cg_by_group[c] = 0;
-    }
-    p.ws_ints = at;
-    p.use_lds = in_lds ? 1 : 0;
-    hipLaunchKernelGGL(swap_clear_kernel, dim3((unsigned)((p.ws_ints + kSwapThreads - 1) / kSwapThreads)), dim3(kSwapThreads),
-                       0, stream, p);
-    if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-    if (T > 0) {
-      const int64_t tokens_per_block = (int64_t)(kFactorThreads / kWave) * (kWave / p.sub);
-      int64_t blocks = ((int64_t)T + tokens_per_block - 1) / tokens_per_block;
-      if (blocks > 256) blocks = 256;   // one per CU; every block flushes its LDS tables with atomics
-      hipLaunchKernelGGL(swap_factors_kernel, dim3((unsigned)blocks), dim3(kFactorThreads),
-                         p.use_lds ? (size_t)lds_at * sizeof(int32_t) : 0, stream, p);
-      if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-    }
   }
   int64_t build_blocks = 0;
-  bool any_quads = false;
   for (int c = 0; c < kMaxCuts; ++c) {
-    p.quads[c] = p.transposed && p.ng[c] % 4 == 0 ? 1 : 0;
-    p.quad_reciprocal[c] = p.quads[c] && p.ng[c] > 4 ? (uint32_t)((0x100000000ull + p.ng[c] / 4 - 1) / (p.ng[c] / 4)) : 0u;
-    const int64_t lanes = (int64_t)E * (p.quads[c] ? p.ng[c] / 4 : p.ng[c]);
-    p.build_blocks[c] = c < ncuts ? (int32_t)((lanes + kSwapThreads - 1) / kSwapThreads) : 0;
+    p.build_blocks[c] = c < ncuts ? (int32_t)(((int64_t)E * p.ng[c] + kSwapThreads - 1) / kSwapThreads) : 0;
     build_blocks += p.build_blocks[c];
-    any_quads = any_quads || (c < ncuts && p.quads[c]);
   }
-  hipLaunchKernelGGL(any_quads ? swap_build_kernel<true> : swap_build_kernel<false>, dim3((unsigned)build_blocks, (unsigned)((E + kBuildRows - 1) / kBuildRows)),
-                     dim3(kSwapThreads), 0, stream, p);
+  hipLaunchKernelGGL(swap_build_kernel, dim3((unsigned)build_blocks, (unsigned)((E + kBuildRows - 1) / kBuildRows)), dim3(kSwapThreads), 0,
+                     stream, p);
   return hm_launch_status();
 }
 

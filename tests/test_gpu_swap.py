@@ -257,6 +257,23 @@ def test_swap_counts_at_the_lines_between_the_kernels(hw, oracle, E, K, G, ng, T
         assert int(st.item()) == st_ref, broken
 
 
+@pytest.mark.parametrize("E,K,G,ng,T", [
+    (17, 3, 4, 4, 1025), (31, 8, 35, 35, 2000), (47, 5, 40, 40, 700), (128, 8, 32, 32, 16384), (128, 8, 32, 32, 16385),   # blocks of one and of fifteen experts, more than 32 groups; a tile per chunk, two
+    (256, 8, 32, 32, 12288), (256, 8, 32, 32, 12289), (200, 12, 8, 8, 12300),   # ... of 768 tokens
+    (20, 2, 4, 4, 65535), (20, 2, 4, 4, 65536),   # sums of sixteen bits, of 32
+    (470, 4, 64, 64, 3000), (512, 8, 33, 33, 1000)])   # waves with tiles of C and of CG
+def test_swap_counts_at_the_edges_of_blocks_and_tiles(hw, oracle, E, K, G, ng, T):
+    """Every token selects expert 0, which is alone in its group, so that its counts are as large as they can be."""
+    rng = np.random.default_rng(E + T)
+    ids = rng.integers(1, E, (T, K), dtype=np.int32)
+    ids[:, 0] = 0
+    e2r = rng.integers(1, G, E).astype(np.int32)
+    e2r[0] = 0
+    ref, st_ref = oracle.swap_counts(ids, e2r, G, ng, "incremental")
+    Z, st = _gpu_z(hw, ids, e2r, G, ng)
+    assert st == st_ref == 0 and np.array_equal(Z.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (12, [1, 2, 6], 33), (33, [1, 3], 9), (6, [1, 3], 300), (1, [1], 5)])
 def test_swap_select_on_any_counts(hw, oracle, G, U, E):
     """Terms of up to 64 groups and of lengths that are no multiple of four, counts that no swap tensor
