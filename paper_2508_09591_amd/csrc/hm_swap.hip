@@ -831,6 +831,8 @@ struct SelectParams {
   const int32_t *z_intra;
   double scale_inter[kMaxDim], alpha_inter[kMaxDim], beta_inter[kMaxDim];
   double scale_intra, alpha_intra, beta_intra;
+  double fan[kMaxDim];      // of term i: U[i + 1] / U[i], G / U[d - 1] of the last
+  int32_t tile[kMaxDim];    // where the counts of term i are staged in LDS, in 16 bytes; -1: they are not
   double *Q;
   double *block_min;    // workspace [nblocks]
   int32_t *block_arg;   // workspace [nblocks]
@@ -839,12 +841,10 @@ struct SelectParams {
   double *best_time;
 };
 
-// x[0 .. N) of a term's counts, 0 beyond n <= N: all loads in flight together, and the counts stay in
-// registers for the sum after the maximum (counts are >= 0, so the padding changes neither the maximum
-// nor, skipped, the sum).
+// x[0 .. N) of a term's counts, 0 beyond n <= N (counts are >= 0, so the padding changes neither the maximum
+// nor, skipped, the sum).  Every load unconditional (the last count again beyond n), so that none waits for another.
 template <int N>
 __device__ __forceinline__ void load_counts(const int32_t *x, int n, int (&v)[N]) {
-  // every load unconditional (the last counts again beyond n), so that none waits for another
   if ((n & 3) == 0) {
 #pragma unroll
     for (int j = 0; j < N; j += 4) {
@@ -860,14 +860,39 @@ __device__ __forceinline__ void load_counts(const int32_t *x, int n, int (&v)[N]
   for (int j = 0; j < N; ++j) v[j] = j < n ? v[j] : 0;
 }
 
-// The smooth maximum of Eq.(11) of n <= N counts.  Every lane is a chain of fp64 operations and there
+// The same for whole fours, through LDS: a lane that reads its pair's counts from memory touches a line of its own, so a wave's load
+// is 64 lines, and a CU's cache holds the lines of few waves.  It pays where lanes read up to 64 counts (256 experts, terms of 8, 16,
+// 32 and 64 groups, the whole selection 16.0 -> 14.3 us; of 4, 8, 16 and 32 11.0 from memory, 11.3 so; 512 experts 23.8, 25.7).  The wave takes its 64 pairs in order, straight into LDS
+// (`tile`, 256 n bytes), `first` its first four of the `fours` there are in all.  Within the fours of a pair, if they are a power of two,
+// the places are exchanged from pair to pair, so that the lanes, which then read one pair each, spread over all banks.
+template <int N>
+__device__ __forceinline__ void stage_counts(i32x4 *tile, const i32x4 *z, int64_t first, int64_t fours, int n, int (&v)[N]) {
+  const int lane = lane_id(), nq = n >> 2, log2_nq = 31 - __builtin_clz(nq);
+  const int mask = (nq & (nq - 1)) == 0 && nq <= 16 ? nq - 1 : 0, shift = mask ? 4 - log2_nq : 0;
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) {
+    if (i >= nq) break;
+    const int slot = i * kWave + lane, pair = mask ? slot >> log2_nq : 0;
+    const int64_t four = min(first + (slot ^ ((pair >> shift) & mask)), fours - 1);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(z + four),
+                                     (__attribute__((address_space(3))) void *)(tile + i * kWave), 16, 0, 0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the wave's own loads are in LDS
+  __asm__ volatile("" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) {
+    const i32x4 w = tile[lane * nq + (min(i, nq - 1) ^ ((lane >> shift) & mask))];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[4 * i + e] = i < nq ? w[e] : 0;
+  }
+}
+
+// The smooth maximum of Eq.(11) of n <= N counts x, which v holds.  Every lane is a chain of fp64 operations and there
 // is about one wave per SIMD, so the chain is what counts: a whole gamma is raised for eight counts
 // side by side, one pass over its bits for all of them; the sum itself stays in the order of the
 // counts.
 template <int N>
-__device__ __forceinline__ double smooth_max(const int32_t *x, int n, double gamma) {
-  int v[N];
-  load_counts<N>(x, n, v);
+__device__ __forceinline__ double smooth_max(const int (&v)[N], const int32_t *x, int n, double gamma) {
   int mi = 0;
 #pragma unroll
   for (int j = 0; j < N; ++j) mi = max(mi, v[j]);
@@ -903,7 +928,7 @@ __device__ __forceinline__ double smooth_max(const int32_t *x, int n, double gam
       }
     }
   } else {
-    for (int i = 0; i < n; ++i) sum += pow((double)x[i] / m, gamma);
+    for (int j = 0; j < n; ++j) sum += pow((double)x[j] / m, gamma);
   }
   return m * pow(sum, 1.0 / gamma);
 }
@@ -913,37 +938,71 @@ __device__ __forceinline__ void keep_better(double &val, int32_t &arg, double v,
   val = better ? v : val;
   arg = better ? a : arg;
 }
+// The words of the lane `OFF` away (OFF a power of two): within rows of sixteen by the data paths of the vector unit, across them by swaps of
+// rows.  (Through LDS, as shuffles, the six steps of an argmin wait for three trips each.)
+template <int OFF>
+__device__ __forceinline__ uint32_t from_lane(uint32_t v) {
+  if constexpr (OFF == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return lane_id() & 32 ? r[0] : r[1];
+  } else if constexpr (OFF == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return lane_id() & 16 ? r[0] : r[1];
+  } else {   // by 8; 7 - i within eight lanes, which are alike in pairs of four by then; quads
+    constexpr int kControl = OFF == 8 ? 0x128 : OFF == 4 ? 0x141 : OFF == 2 ? 0x4E : 0xB1;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kControl, 0xF, 0xF, true);
+  }
+}
+template <int OFF>
+__device__ __forceinline__ void argmin_step(double &val, int32_t &arg) {
+  const uint64_t bits = __builtin_bit_cast(uint64_t, val);
+  const uint64_t other = (uint64_t)from_lane<OFF>((uint32_t)(bits >> 32)) << 32 | from_lane<OFF>((uint32_t)bits);
+  keep_better(val, arg, __builtin_bit_cast(double, other), (int32_t)from_lane<OFF>((uint32_t)arg));
+}
 __device__ __forceinline__ void wave_argmin(double &val, int32_t &arg) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) keep_better(val, arg, __shfl_xor(val, off, kWave), __shfl_xor(arg, off, kWave));
+  argmin_step<32>(val, arg);
+  argmin_step<16>(val, arg);
+  argmin_step<8>(val, arg);
+  argmin_step<4>(val, arg);
+  argmin_step<2>(val, arg);
+  argmin_step<1>(val, arg);
 }
 
 // Q of 64 pairs by a workgroup: a wave per term of Eq.(8) (the Inter levels 1 .. d-1, then the Intra
 // level), a lane per pair, so that the waves with few groups are done early instead of waiting for the
-// lanes of the widest cut, and everything about a term is uniform.  The terms are then added in the
-// order of the levels, so Q has the bits of a serial evaluation.  Kernel trace, four terms: 128 experts
-// 6.8 us, 256 experts 10.2 us (four lanes per pair side by side: 8.1 and 14.1).
+// lanes of the widest cut, and everything about a term is uniform.  Neighbouring workgroups begin with another term, so that the
+// widest ones do not meet on one SIMD.  The terms are then added in the order of the levels, so Q has the bits of
+// a serial evaluation.  The whole selection (graphs of twenty), every workgroup beginning with the first term and argmins by
+// shuffles -> now: 128 experts 8.9 -> 8.5 us, 256 11.7 -> 11.0.  Tried: the root by one step of Halley's method from a guess in
+// binary32 (0.3 and 0.7 us less, but one Q in 25 differs in the last bit, which decides between pairs of equal time).
 template <int N>   // most groups of a term: 32 or 64
 __global__ __launch_bounds__(kSelectThreads) void swap_q_kernel(SelectParams p) {
 #pragma clang fp contract(off)
+  extern __shared__ __align__(16) i32x4 count_tiles[];
   __shared__ double s_term[kMaxDim][kSelectPairs];
-  const int lane = lane_id();
-  const int term = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int64_t rc = (int64_t)blockIdx.x * kSelectPairs + lane;
-  const bool live = rc < (int64_t)p.E * p.E;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int term = (w + (int)blockIdx.x) & (kMaxDim - 1);
+  const int64_t rc = (int64_t)blockIdx.x * kSelectPairs + lane, pairs = (int64_t)p.E * p.E;
+  const bool live = rc < pairs;
   if (term < p.d) {
     const bool intra = term == p.d - 1;
     const int i = intra ? 0 : term + 1;
     const int n = intra ? p.G : p.U[i];
-    const int32_t *x = (intra ? p.z_intra : p.z_inter[i]) + (live ? rc : 0) * n;
-    const double fan = intra ? (double)(p.G / p.U[p.d - 1]) : (double)(p.U[i] / p.U[intra ? 0 : i - 1]);
+    const int32_t *const z = intra ? p.z_intra : p.z_inter[i];
+    const double fan = p.fan[term];
     const double scale = intra ? p.scale_intra : p.scale_inter[i];
     const double beta = intra ? p.beta_intra : p.beta_inter[i], alpha = intra ? p.alpha_intra : p.alpha_inter[i];
-    const double volume = fan * scale * smooth_max<N>(x, n, p.gamma) * p.M * p.v;
+    const int32_t *const x = z + (live ? rc : 0) * n;
+    int v[N];
+    if (N > 32 && p.tile[term] >= 0)
+      stage_counts<N>(count_tiles + p.tile[term], (const i32x4 *)z, (int64_t)blockIdx.x * (kSelectPairs / 4) * n, pairs * (n >> 2), n, v);
+    else
+      load_counts<N>(x, n, v);
+    const double volume = fan * scale * smooth_max<N>(v, x, n, p.gamma) * p.M * p.v;
     s_term[term][lane] = volume * beta + alpha;
   }
   __syncthreads();
-  if (term != 0) return;
+  if (w != 0) return;
   double q = 0.0;
   for (int j = 0; j < p.d; ++j) q = q + s_term[j][lane];
   if (live) p.Q[rc] = q;
@@ -956,19 +1015,21 @@ __global__ __launch_bounds__(kSelectThreads) void swap_q_kernel(SelectParams p) 
 }
 
 // The first of the smallest block minima.  One workgroup, bound by its trip to memory and the steps to
-// one value: four minima per lane in flight, then shuffles within the waves and one step across them.
-constexpr int kArgminThreads = 1024;
-__global__ __launch_bounds__(kArgminThreads) void swap_argmin_kernel(SelectParams p) {
-  __shared__ double s_val[kArgminThreads / kWave];
-  __shared__ int32_t s_arg[kArgminThreads / kWave];
+// one value: four minima per lane in flight, then steps within the waves and one across them.
+constexpr int kArgminThreads = 1024, kArgminFew = 256;   // lanes; for up to four minima each of the few
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void swap_argmin_kernel(SelectParams p) {
+  constexpr int kWaves = THREADS / kWave;
+  __shared__ double s_val[kWaves];
+  __shared__ int32_t s_arg[kWaves];
   double best = 0.0;
   int32_t arg = -1;
-  for (int b0 = 0; b0 < p.nblocks; b0 += 4 * kArgminThreads) {
+  for (int b0 = 0; b0 < p.nblocks; b0 += 4 * THREADS) {
     double v[4];
     int32_t a[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int b = b0 + j * kArgminThreads + (int)threadIdx.x;
+      const int b = b0 + j * THREADS + (int)threadIdx.x;
       v[j] = b < p.nblocks ? p.block_min[b] : 0.0;
       a[j] = b < p.nblocks ? p.block_arg[b] : -1;
     }
@@ -982,7 +1043,6 @@ __global__ __launch_bounds__(kArgminThreads) void swap_argmin_kernel(SelectParam
   }
   __syncthreads();
   if (threadIdx.x >= kWave) return;
-  constexpr int kWaves = kArgminThreads / kWave;
   best = s_val[threadIdx.x & (kWaves - 1)];
   arg = s_arg[threadIdx.x & (kWaves - 1)];
   wave_argmin(best, arg);
@@ -1356,9 +1416,19 @@ extern "C" hm_status hm_swap_select(int32_t d, const int32_t *U, int32_t G, int3
   p.best_pair = best_pair;
   p.best_time = best_time;
   hipStream_t stream = (hipStream_t)hip_stream;
-  hipLaunchKernelGGL(G <= 32 ? swap_q_kernel<32> : swap_q_kernel<64>, dim3(p.nblocks), dim3(kSelectThreads), 0, stream, p);
+  int fours = 0;
+  for (int i = 0; i < kMaxDim; ++i) {
+    const bool intra = i == d - 1;
+    const int n = intra ? G : i < d ? U[i + 1] : 1;
+    const int32_t *const z = intra ? z_intra : i < d ? z_inter[i + 1] : nullptr;
+    p.fan[i] = intra ? (double)(G / U[d - 1]) : i < d ? (double)(U[i + 1] / U[i]) : 0.0;
+    p.tile[i] = G > 32 && n % 4 == 0 && ((uintptr_t)z & 15) == 0 ? fours : -1;   // the loads into LDS are of 16 bytes
+    if (i < d && p.tile[i] >= 0) fours += kSelectPairs * n / 4;
+  }
+  hipLaunchKernelGGL(G <= 32 ? swap_q_kernel<32> : swap_q_kernel<64>, dim3(p.nblocks), dim3(kSelectThreads), (size_t)fours * 16, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-  hipLaunchKernelGGL(swap_argmin_kernel, dim3(1), dim3(kArgminThreads), 0, stream, p);
+  if (p.nblocks <= 4 * kArgminFew) hipLaunchKernelGGL(swap_argmin_kernel<kArgminFew>, dim3(1), dim3(kArgminFew), 0, stream, p);
+  else hipLaunchKernelGGL(swap_argmin_kernel<kArgminThreads>, dim3(1), dim3(kArgminThreads), 0, stream, p);
   return hm_launch_status();
 }
 

@@ -306,6 +306,35 @@ def test_swap_select_on_any_counts(hw, oracle, G, U, E):
         assert tuple(bp.tolist()) == (flat // E, flat % E) and float(bt.item()) == Qg.min()
 
 
+@pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (64, [1, 2, 4], 5), (40, [1, 5, 20], 33), (48, [1, 12, 24], 17), (36, [1], 9)])
+def test_swap_select_with_counts_staged_in_lds(hw, oracle, G, U, E):
+    """More than 32 groups in whole, aligned fours go through LDS; the same counts four bytes further on do not: the same bits."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(G + E)
+    d = len(U)
+    host = [rng.integers(0, 5000, (E, E, n)).astype(np.int32) for n in U[1:] + [G]]
+    alpha, beta, scale = [0.1 * i for i in range(d)], [1e-7 * (i + 1) for i in range(d)], [0.0] + [1.5] * (d - 1)
+    for gamma in (0.0, 10.0, 2.5):
+        got = []
+        for off in (0, 1):
+            z = []
+            for h in host:
+                store = torch.zeros(h.size + 4, dtype=torch.int32, device="cuda")
+                store[off:off + h.size].copy_(hw.dev(h).view(-1))
+                z.append(store[off:off + h.size].view(h.shape))
+            Q = torch.full((E, E), float("nan"), dtype=torch.float64, device="cuda")
+            bp, bt = torch.full((2,), -1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float64, device="cuda")
+            B.hm_swap_select(U, G, 64, 2.0, [None] + z[:-1], z[-1], scale, 2.0, alpha, beta, 0.3, 1e-7, gamma, Q, bp, bt)
+            got.append((Q.cpu().numpy(), tuple(bp.tolist()), float(bt.item())))
+        Qr, best_r, bt_r = oracle.swap_select(U, G, 64, 2.0, [None] + host[:-1], host[-1], scale, 2.0, alpha, beta, 0.3, 1e-7, gamma)
+        assert np.array_equal(got[0][0], got[1][0]) and got[0][1:] == got[1][1:], gamma
+        # plain maximum: the same fp64 operations; otherwise at most 64 powers of a few ulp each and their root
+        assert np.array_equal(got[0][0], Qr) if gamma <= 0 else np.allclose(got[0][0], Qr, rtol=1e-12, atol=0), gamma
+        flat = int(np.argmin(got[0][0]))
+        assert got[0][1] == (flat // E, flat % E)
+
+
 def test_planner_loop_stays_on_the_device(hw, oracle):
     """(Z, select, apply) repeated on the device with no host step in between; afterwards every
     iteration is replayed on the oracle.  gamma <= 0 keeps Q bit-exact, so the chosen pairs and
