@@ -83,93 +83,111 @@ __device__ __forceinline__ int lane_scan(int v) {
 // Counts of a routing table in one launch without cleared outputs: a workgroup owns a few outputs (seven groups, or
 // some experts), goes through all the tokens and stores its counts.  The workgroups read the same table, so this is for
 // tables of a few hundred KB; beyond that each should read a part of it once and add atomically to cleared outputs.
-// A round of 1,024 tokens, one per lane, is bound by issuing its instructions (sixteen waves on a CU, four cycles
-// each: 0.4 us for eight ids), so there are few per id.  More rounds in flight, or four ids per lane, gained nothing.
+// A round of 1,024 tokens of eight ids, one token per lane, is bound by the CU's path to the caches (32 KB, 0.2 us), its lookups in LDS
+// and the instructions of sixteen waves, of which there are few per id; what comes before and behind the rounds by its
+// code, which runs once and cold.
 constexpr int kOwnerThreads = 1024;   // = tokens of a round
+constexpr int kOwnerWaves = kOwnerThreads / kWave;
 constexpr int kOwnerGroups = 7;       // groups of a workgroup: the bits of a byte, but for the one that marks an error
-constexpr int kOwnerExperts = 64;     // experts of a workgroup ...
-constexpr int kOwnerCopies = 4;       // ... each counted in four places, so that fewer lanes meet at one
+constexpr int kOwnerRounds = 63;      // most rounds: a workgroup's sums are added in pairs of sixteen bits
+constexpr int kOwnerExperts = 64;     // experts of a workgroup
 constexpr int kOwnerMaxE = 4096;      // experts whose groups fit the LDS table
 
-// count(id) for every id of this lane's tokens, eight lookups side by side, end() after the last of a token.  The next
-// eight are on their way meanwhile; prepare() runs while the first are.  Lanes without a token count ids of -1.
-template <typename PREPARE, typename COUNT, typename END>
+// Ids of a token that a lane loads together: two windows of W, 4 from four slots on, 2 for two and three, 1 (and the same again) for one.
+static inline int owner_width(int K) { return K >= 4 ? 4 : K >= 2 ? 2 : 1; }
+
+// count(id, seen) for every batch of up to eight ids of this lane's tokens, end() behind the last of a token.  The second window of a short
+// token and the last batch of a long one overlap what was there before: `seen` (uniform) of the first 2 W places and, from 8 on,
+// of the second window's, hold ids that have been counted.  Lanes without a token have the last one's ids; count and end are told
+// whether they do.  The next batch is on its way meanwhile; prepare() runs while the first is.
+template <int W, typename PREPARE, typename COUNT, typename END>
 __device__ __forceinline__ void for_ids(const int32_t *__restrict__ ids, int T, int K, PREPARE prepare, COUNT count, END end) {
-  int t = (int)threadIdx.x, k0 = 0;
-  const int32_t *at = ids + (int64_t)t * K;
-  const int steps = (T + kOwnerThreads - 1) / kOwnerThreads * ((K + 7) >> 3);
-  int id[8], next[8];
-  auto load = [&](int n) {   // n ids of the token are left
-#pragma unroll
-    for (int j = 0; j < 8; ++j) next[j] = -1;
-    if (t < T) {
-      if (n >= 8) {
-        __builtin_memcpy(next, at, sizeof(next));
-      } else {
-#pragma unroll
-        for (int j = 0; j < 7; ++j)
-          if (j < n) next[j] = at[j];
-      }
+  const int batches = W == 4 ? (K + 7) >> 3 : 1, steps = (T + kOwnerThreads - 1) / kOwnerThreads * batches;
+  const uint32_t row = (uint32_t)K * 4u, last = (uint32_t)(T - 1) * row;   // bytes; T is 64 K at most
+  uint32_t at = min(__umul24(threadIdx.x, row), last);
+  int t = (int)threadIdx.x, batch = 0;
+  auto load = [&](int (&id)[2 * W]) {   // of the token at `at`, then on to the next batch
+    const int first = K >= 8 ? min(8 * batch, K - 8) : 0, second = W == 1 ? 0 : K >= 8 ? first + 4 : K - W;
+    __builtin_memcpy(&id[0], (const char *)ids + (at + 4u * (uint32_t)first), 4 * W);
+    __builtin_memcpy(&id[W], (const char *)ids + (at + 4u * (uint32_t)second), 4 * W);
+    if (++batch == batches) {
+      batch = 0;
+      at = min(at + kOwnerThreads * row, last);
     }
   };
+  int counted = 0;   // batches of the present token
+  auto use = [&](const int (&id)[2 * W]) {
+    const bool alive = t < T;
+    // places of the batch, and behind them of the second window, that an earlier one had
+    const int seen = K >= 8 ? max(8 * (counted + 1) - K, 0) : 8 + 2 * W - K;
+    count(id, seen, alive);
+    if (++counted == batches) {
+      counted = 0;
+      end(alive);
+      t += kOwnerThreads;
+    }
+  };
+  int a[2 * W], b[2 * W];
+  if (steps > 0) load(a);
+  prepare();
 #pragma unroll 1
-  for (int step = -1; step < steps; ++step) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) id[j] = step < 0 ? -1 : next[j];
-    const int n = K - k0;
-    if (step >= 0) {
-      at += n > 8 ? 8 : (int64_t)kOwnerThreads * K - k0;
-      t += n > 8 ? 0 : kOwnerThreads;
-      k0 = n > 8 ? k0 + 8 : 0;
+  for (int step = 0; step < steps; step += 2) {
+    if (step + 1 < steps) load(b);
+    use(a);
+    if (step + 1 < steps) {
+      if (step + 2 < steps) load(a);
+      use(b);
     }
-    load(K - k0);
-    if (step < 0) {
-      prepare();
-      continue;
-    }
-    if (n >= 8) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) count(id[j]);
-    } else {   // an absent id would cost as much as any other
-#pragma unroll
-      for (int j = 0; j < 7; ++j)
-        if (j < n) count(id[j]);
-    }
-    if (n <= 8) end();
   }
 }
 
-// Tokens with a copy in groups [first, first + 7) of `per` ranks each -> cnt[0 .. 7) of the workgroup's LDS, valid after the
-// call for every lane; returns whether any id or placement is invalid.  The table holds one bit per group an expert
-// may be in, so a token's groups are the `or` of its entries; a lane keeps its counts as bytes (at most 255 rounds).
-__device__ __forceinline__ bool count_owned_groups(const int32_t *__restrict__ ids, const int32_t *__restrict__ expert_to_rank, int T, int K,
-                                                   int E, int G, int per, int first, uint8_t *table, int32_t *cnt) {
-  const uint32_t per_recip16 = (65536u + (uint32_t)per - 1u) / (uint32_t)per;   // exact for ranks (below 64)
+// Tokens with a copy in groups [first, first + 7) of ranks that r -> (r per_recip16) >> 16 puts together: returned to lane g of the first
+// wave, in lane 7 the tokens with an invalid id or placement.  The table holds one bit per group an expert may be in, so a
+// token's groups are the `or` of its entries; a lane keeps its counts as bytes.
+template <int W>
+__device__ __forceinline__ int count_owned_groups(const int32_t *__restrict__ ids, const int32_t *__restrict__ expert_to_rank, int T, int K, int E,
+                                                  int G, uint32_t per_recip16, int first, uint8_t *table) {
+  __shared__ u32x4 sums[kOwnerWaves];
   uint32_t low = 0, high = 0, mask = 0;
-  for_ids(ids, T, K, [&] {   // entry 0 is that of id -1, E + 1 of ids out of range
+  for_ids<W>(ids, T, K, [&] {   // entry 0 is that of id -1, E + 1 of ids out of range
     for (int e = threadIdx.x; e < E + 2; e += kOwnerThreads) {
       const int g = e >= 1 && e <= E ? expert_to_rank[e - 1] : -1;
       const uint32_t in = (((uint32_t)g * per_recip16) >> 16) - (uint32_t)first;
       table[e] = (uint8_t)((unsigned)g >= (unsigned)G ? (e == 0 ? 0u : 0x80u) : in < (uint32_t)kOwnerGroups ? 1u << in : 0u);
     }
-    if (threadIdx.x < 8) cnt[threadIdx.x] = 0;
     __syncthreads();
-  }, [&](int id) { mask |= table[min((uint32_t)id + 1u, (uint32_t)E + 1u)]; }, [&] {
-    low += (mask & 0xFu) * 0x00204081u & 0x01010101u;   // bit i of four to byte i
-    high += (mask >> 4) * 0x00204081u & 0x01010101u;
+  }, [&](const int (&id)[2 * W], int, bool) {
+    uint32_t most = (uint32_t)id[0], seen = 0;
+#pragma unroll
+    for (int j = 1; j < 2 * W; ++j) most = max(most, (uint32_t)id[j]);
+    if (__ballot(most >= (uint32_t)E) == 0) {   // two instructions an id less
+#pragma unroll
+      for (int j = 0; j < 2 * W; ++j) seen |= (table + 1)[(uint32_t)id[j]];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 2 * W; ++j) seen |= table[min((uint32_t)id[j] + 1u, (uint32_t)E + 1u)];
+    }
+    mask |= seen;
+  }, [&](bool alive) {
+    mask = alive ? mask : 0u;
+    low += __umul24(mask & 0xFu, 0x00204081u) & 0x01010101u;   // bit i of four to byte i
+    high += __umul24(mask >> 4, 0x00204081u) & 0x01010101u;
     mask = 0;
   });
-  // two sums of sixteen bits in a word, over the lanes and then over the waves; the eighth counts tokens with an error
+  // two sums of sixteen bits in a word, over the lanes and then over the waves
+  u32x4 sum;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int v = lane_scan((int)((j < 2 ? low : high) >> (8 * (j & 1)) & 0x00FF00FFu));
-    if (lane_id() == kWave - 1) {
-      atomicAdd(&cnt[4 * (j >> 1) + (j & 1)], v & 0xFFFF);
-      atomicAdd(&cnt[4 * (j >> 1) + (j & 1) + 2], v >> 16);
-    }
-  }
+  for (int j = 0; j < 4; ++j) sum[j] = (uint32_t)lane_scan((int)((j < 2 ? low : high) >> (8 * (j & 1)) & 0x00FF00FFu));
+  if (lane_id() == kWave - 1) sums[threadIdx.x / kWave] = sum;
   __syncthreads();
-  return cnt[kOwnerGroups] != 0;
+  if (threadIdx.x >= kWave) return 0;
+  int v = ((const int *)sums)[threadIdx.x];   // word (lane % 4) of wave (lane / 4)
+  v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);   // the lane four away within the row of sixteen, then eight
+  v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);
+  v += __shfl_xor(v, 16, kWave);
+  v += __shfl_xor(v, 32, kWave);
+  const int g = lane_id();
+  return (__shfl(v, (g >> 1 & 2) + (g & 1), kWave) >> (g & 2 ? 16 : 0)) & 0xFFFF;
 }
 
 // Value held by lane `src` (src must be wave-uniform).
@@ -195,28 +213,25 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }  // namespace hm
 
 // Which kernel takes the counts of a table (hm_expert_load, hm_group_counts); outputs: the groups of all levels, or ranks and nodes.
-//  * kOwners where the rounds of 1,024 tokens cost less than the clearing launch, the gap behind it and the atomics.  A round costs
-//    0.38 us per eight ids (0.47 if there are more) and for the ids that are left, which take a load of a word each, 0.45 up to
-//    three, 0.8 for four and five, 1.0 and 1.35 for six and seven, the more the longer the tokens; what it saves is 2 us, 0.036 per output (the
-//    ballots of the other kernels), 0.1 per id of a load and 0.06 per id beyond eight.  Graphs of ten calls, us, clear + count
-//    -> owners: group counts of 8,192 x 8 with four levels of 32 ranks 7.9 -> 7.1, with one of 16 6.5 -> 6.9 (6,144 tokens: 6.4 -> 6.1);
-//    4,096 x 2 6.1 -> 5.6, x 4 6.1 -> 7.0, x 7 6.2 -> 8.6 (2,048 x 7 with four levels 7.7 -> 6.1); loads of 8,192 x 8 on 32 ranks 7.7 -> 6.7,
-//    4,096 x 7 7.5 -> 8.7, x 12 8.3 -> 8.7, 2,048 x 31 10.5 -> 11.8.  Few experts make many lanes meet at one count (E = 32, 16
-//    ranks, 8,192 x 8: 7.1 -> 7.5).  And a launch less takes 2.4 us off the host.
-//  * kAlone, one workgroup, for a few tokens with few outputs (and, for loads, ids), as an owner works out an entry of a table per
-//    expert: 64 tokens, groups of 8 ranks, E = 128 3.85, owners 4.05, E = 2,048 4.05, 4.5; loads of one id, 8 ranks 3.75, 4.1; but
-//    four levels of 32 ranks 5.6, 4.4.  And, as far as it goes, where the owners' table has no room.
+//  * kOwners where the rounds of 1,024 tokens cost less than the clearing launch, the gap behind it and the atomics: two straight lines,
+//    hundredths of a us, through 4,000 shapes (16 to 65,536 tokens, one to 64 ids, 2 to 2,048 experts, even and Zipf ids, dropped slots;
+//    graphs of ten calls).  A round costs 0.2 us with one id per token, 0.25 with two or three, 0.45 with four to seven
+//    (two loads that overlap), 0.36 with eight, as much per eight of more, and twice that where a token's row is 100 bytes or more,
+//    whose lines no two lanes share.  Clear + count -> owners, us: loads of 8,192 x 8, 128 experts on 32 ranks 7.7 -> 5.9; group counts with
+//    four levels of 32 ranks 8.1 -> 6.3; up to two rounds 0.53 times as long, up to eight 0.65, but loads of 13,679 x 6 with 36
+//    outputs 7.6 -> 10.2, group counts of 2,964 x 31 with one 8.3 -> 13.2.  The rule loses more than 3 % in 40 of the shapes, a third at most.
+//    One workgroup that stores its counts (kAlone) took 1.3 times as long as the owners for tables of one round.
+//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room.
 enum class CountRoute { kAlone, kOwners, kAdded };
 static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t outputs, bool loads, bool alone_fits) {
-  const int64_t few = E / 128 + (!loads ? 8 : K == 1 ? 20 : K <= 3 ? 10 : -E / 128);
-  if (alone_fits && outputs <= few && (T <= 256 || (T <= 512 && K <= 2 && outputs <= 10 + E / 128)) && K <= 8) return CountRoute::kAlone;
-  static const int left[8] = {0, 45, 45, 45, 80, 80, 100, 135}, longer[4] = {4, 5, 6, 9};   // hundredths of a us, quarters
+  if (E > hm::kOwnerMaxE) return alone_fits ? CountRoute::kAlone : CountRoute::kAdded;
   const int64_t rounds = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads, steps = rounds * ((K + 7) / 8);
-  const int64_t round = K / 8 * (K > 8 || (loads && E < 64) ? 47 : 38) + left[K % 8] * longer[K < 32 ? K / 8 : 3] / 4;
-  const int64_t saved = 200 + outputs * 36 / 10 + (loads ? 10 * K : 0) + (K > 8 ? 6 * (K - 8) : 0);
-  const bool pays = steps <= (K < 8 || E < 32 ? 4 : 8) && (rounds <= 1 || rounds * round <= saved);
-  if (pays && E <= hm::kOwnerMaxE) return CountRoute::kOwners;
-  return alone_fits ? CountRoute::kAlone : CountRoute::kAdded;
+  const int64_t step = K == 1 ? 20 : K <= 3 ? 25 : K < 8 ? 45 : K == 8 ? 36 : K <= 24 ? 43 : 85;
+  const int64_t owners = 295 + step * steps + E / 50 + outputs / 5;
+  const int64_t tokens = T < 65536 ? T : 65536;
+  const int64_t added = loads ? 520 + 15 * K + outputs * 24 / 10 + E * 8 / 100 + tokens * 56 / 10000
+                              : 525 + 9 * K + outputs * 35 / 10 + E * 4 / 100 + tokens * 40 / 10000;
+  return rounds <= hm::kOwnerRounds && owners <= added ? CountRoute::kOwners : CountRoute::kAdded;
 }
 
 // Host-side argument checks shared by the entry points.

@@ -1,8 +1,8 @@
 // hm_expert_load: per-expert slot counts and duplicate-free per-rank / per-node token counts
 // (the p^(1,G) and p^(1,U[1]) vectors of HierMoE Eq.(7)) for the expert-swap planner of Section IV.
 //
-// Small tables are one launch: workgroups that own a few outputs each go through all the tokens (load_owner_kernel; T =
-// 1,024, K = 8: 6.1 us by the one workgroup that did it before, 3.7 now).  Larger ones: one lane per token, expert counts
+// Small tables are one launch: workgroups that own a few outputs each go through all the tokens (load_owner_kernel; kernel
+// trace, 8,192 x 8, 128 experts on 32 ranks: 5.2 us, 6.4 with a branch per id and a place for every four lanes).  Larger ones: one lane per token, expert counts
 // in an LDS histogram, rank and node counts from ballots over the per-token rank masks (lane g accumulates the
 // popcount for group g), so a token is counted once per group however many of its experts live there; a tiny launch clears
 // the outputs and integer atomics merge the workgroups, which keeps the result exact and order-independent.  The ids of a
@@ -112,37 +112,54 @@ __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
 
 // Small tables: workgroups [0, expert_blocks) own kOwnerExperts experts each, the next ones seven ranks each, the
 // last ones seven nodes each.
-__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks) {
+template <int W>
+__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks, uint32_t nodes_recip16) {
   __shared__ uint8_t table[kOwnerMaxE + 2];
-  __shared__ int32_t cnt[kOwnerExperts * kOwnerCopies];
+  __shared__ __align__(16) uint32_t cnt[kOwnerExperts + 1][kWave];   // a place per lane of a wave, so that no two lanes meet; the last row: not ours
   int block = (int)blockIdx.x;
   if (block < expert_blocks) {   // an id is counted whether its expert's placement is valid or not, and stored if it is
-    const int e0 = block * kOwnerExperts;
-    const uint32_t copy = threadIdx.x & (kOwnerCopies - 1);
-    for_ids(p.ids, p.T, p.K, [&] {
-      if (threadIdx.x < kOwnerExperts * kOwnerCopies) cnt[threadIdx.x] = 0;
+    const int e0 = block * kOwnerExperts, lane = lane_id();
+    const int e = e0 + (int)(threadIdx.x >> 4);   // whose places sixteen lanes add up in the end
+    bool placed = false;
+    for_ids<W>(p.ids, p.T, p.K, [&] {
+      if (e < p.E) placed = (unsigned)p.expert_to_rank[e] < (unsigned)p.G;
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      for (int i = threadIdx.x; i < (kOwnerExperts + 1) * kWave / 4; i += kOwnerThreads) ((u32x4 *)cnt)[i] = zero;
       __syncthreads();
-    }, [&](int id) {
-      const uint32_t e = (uint32_t)id - (uint32_t)e0;
-      if (e < (uint32_t)kOwnerExperts) atomicAdd(&cnt[e * kOwnerCopies + copy], 1);
-    }, [] {});
-    __syncthreads();
-    const int e = e0 + (int)threadIdx.x;
-    if (threadIdx.x < kOwnerExperts && e < p.E) {
-      int sum = 0;
+    }, [&](const int (&id)[2 * W], int seen, bool alive) {
+      const uint32_t least = alive ? 0u : (uint32_t)kOwnerExperts;
+      auto count = [&](int one, uint32_t from) {   // no branch, and no lane left out: a row per id
+        const uint32_t i = min(max((uint32_t)one - (uint32_t)e0, from), (uint32_t)kOwnerExperts);
+        atomicAdd(&cnt[i][lane], 1u);
+      };
+      if (seen == 0) {
 #pragma unroll
-      for (int i = 0; i < kOwnerCopies; ++i) sum += cnt[threadIdx.x * kOwnerCopies + i];
-      p.load_expert[e] = (unsigned)p.expert_to_rank[e] < (unsigned)p.G ? sum : 0;
-    }
+        for (int j = 0; j < 2 * W; ++j) count(id[j], least);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2 * W; ++j) {
+          const bool again = seen < 8 ? j < seen : j >= W && j - W < seen - 8;   // uniform
+          count(id[j], again ? (uint32_t)kOwnerExperts : least);
+        }
+      }
+    }, [](bool) {});
+    __syncthreads();
+    const u32x4 c = *(const u32x4 *)&cnt[threadIdx.x >> 4][(threadIdx.x & 15) * 4];
+    int v = (int)(c[0] + c[1] + c[2] + c[3]);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);   // the lanes eight, four, two and one away in the row of sixteen
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, true);
+    if ((threadIdx.x & 15) == 0 && e < p.E) p.load_expert[e] = placed ? v : 0;
     return;
   }
   block -= expert_blocks;
   const bool ranks = block < rank_blocks;
   const int first = (ranks ? block : block - rank_blocks) * kOwnerGroups;
-  const bool bad = count_owned_groups(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, ranks ? 1 : p.R, first, table, cnt);
+  const int count = count_owned_groups<W>(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, ranks ? 65536u : nodes_recip16, first, table);
   const int i = first + (int)threadIdx.x;
-  if (threadIdx.x < kOwnerGroups && i < (ranks ? p.G : p.N)) (ranks ? p.load_rank : p.load_node)[i] = cnt[threadIdx.x];
-  if (block == 0 && threadIdx.x == 0 && p.status) *p.status = bad ? HM_ERR_BAD_ID : 0;
+  if (threadIdx.x < kOwnerGroups && i < (ranks ? p.G : p.N)) (ranks ? p.load_rank : p.load_node)[i] = count;
+  if (block == 0 && threadIdx.x == kOwnerGroups && p.status) *p.status = count ? HM_ERR_BAD_ID : 0;
 }
 
 }  // namespace hm
@@ -177,8 +194,11 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   if (route == CountRoute::kOwners) {
     const int expert_blocks = (E + kOwnerExperts - 1) / kOwnerExperts, rank_blocks = (p.G + kOwnerGroups - 1) / kOwnerGroups;
     const int node_blocks = (p.N + kOwnerGroups - 1) / kOwnerGroups;
-    hipLaunchKernelGGL(load_owner_kernel, dim3((unsigned)(expert_blocks + rank_blocks + node_blocks)), dim3(kOwnerThreads), 0, stream, p,
-                       expert_blocks, rank_blocks);
+    const uint32_t nodes_recip16 = (uint32_t)((65536 + p.R - 1) / p.R);   // exact for ranks (below 64)
+    const int width = owner_width(K);
+    hipLaunchKernelGGL((width == 4 ? load_owner_kernel<4> : width == 2 ? load_owner_kernel<2> : load_owner_kernel<1>),
+                       dim3((unsigned)(expert_blocks + rank_blocks + node_blocks)), dim3(kOwnerThreads), 0, stream, p, expert_blocks, rank_blocks,
+                       nodes_recip16);
     return hm_launch_status();
   }
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;

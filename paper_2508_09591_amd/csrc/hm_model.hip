@@ -89,17 +89,29 @@ __global__ __launch_bounds__(THREADS) void group_count_kernel(GroupParams p) {
 }
 
 // Small tables: a workgroup owns seven groups of a level.
-__global__ __launch_bounds__(kOwnerThreads) void group_owner_kernel(GroupParams p) {
+struct GroupOwners {
+  int32_t first_block[kMaxDepth];        // of a level; beyond all blocks where there is no such level
+  uint32_t per_recip16[kMaxDepth];       // ceil(2^16 / ranks of a group): exact for ranks (below 64)
+};
+template <int W>
+__global__ __launch_bounds__(kOwnerThreads) void group_owner_kernel(GroupParams p, GroupOwners o) {
   __shared__ uint8_t table[kOwnerMaxE + 2];
-  __shared__ int32_t cnt[kOwnerGroups + 1];
-  int level = 0, block = (int)blockIdx.x;
-  while (block >= (p.groups[level] + kOwnerGroups - 1) / kOwnerGroups) block -= (p.groups[level++] + kOwnerGroups - 1) / kOwnerGroups;
+  int level = 0, block = (int)blockIdx.x, n = p.groups[0];
+  uint32_t per_recip16 = o.per_recip16[0];
+#pragma unroll
+  for (int l = 1; l < kMaxDepth; ++l) {   // selects: a loop would wait for a load per level
+    const bool from = (int)blockIdx.x >= o.first_block[l];
+    level = from ? l : level;
+    n = from ? p.groups[l] : n;
+    per_recip16 = from ? o.per_recip16[l] : per_recip16;
+    block = from ? (int)blockIdx.x - o.first_block[l] : block;
+  }
   const int first = block * kOwnerGroups;
-  const bool bad = count_owned_groups(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, p.per[level], first, table, cnt);
-  const int i = first + (int)threadIdx.x, n = p.groups[level];   // the last owner of a level clears what is behind its groups
-  if (i < kWave && ((int)threadIdx.x < kOwnerGroups || first + kOwnerGroups >= n))
-    p.counts[level * kWave + i] = (int)threadIdx.x < kOwnerGroups && i < n ? cnt[threadIdx.x] : 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && p.status) *p.status = bad ? HM_ERR_BAD_ID : 0;
+  const int count = count_owned_groups<W>(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, per_recip16, first, table);
+  if (threadIdx.x >= kWave) return;
+  const int lane = lane_id(), i = first + lane;   // the last owner of a level clears what is behind its groups
+  if (i < kWave && (lane < kOwnerGroups || first + kOwnerGroups >= n)) p.counts[level * kWave + i] = lane < kOwnerGroups && i < n ? count : 0;
+  if (blockIdx.x == 0 && lane == kOwnerGroups && p.status) *p.status = count ? HM_ERR_BAD_ID : 0;
 }
 
 struct TimeParams {
@@ -199,9 +211,16 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
   const bool alone_fits = T <= kAloneTokens && (E <= kStagedExperts || (int64_t)T * K <= 32768);
   const CountRoute route = count_route(T, K, E, outputs, false, alone_fits);
   if (route == CountRoute::kOwners) {
+    GroupOwners o;
     int blocks = 0;
-    for (int l = 0; l < depth; ++l) blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
-    hipLaunchKernelGGL(group_owner_kernel, dim3((unsigned)blocks), dim3(kOwnerThreads), 0, stream, p);
+    for (int l = 0; l < kMaxDepth; ++l) {
+      o.first_block[l] = l < depth ? blocks : 0x7FFFFFFF;
+      o.per_recip16[l] = (uint32_t)((65536 + p.per[l] - 1) / p.per[l]);
+      if (l < depth) blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
+    }
+    const int width = owner_width(K);
+    hipLaunchKernelGGL((width == 4 ? group_owner_kernel<4> : width == 2 ? group_owner_kernel<2> : group_owner_kernel<1>), dim3((unsigned)blocks),
+                       dim3(kOwnerThreads), 0, stream, p, o);
     return hm_launch_status();
   }
   if (route == CountRoute::kAlone) {

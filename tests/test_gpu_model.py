@@ -150,6 +150,32 @@ def test_counts_by_owners_and_beyond(hw, oracle, T, K, E, nodes, rpn):
         assert np.array_equal(counts.cpu().numpy(), ref) and int(status.item()) == st, broken
 
 
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 23, 24, 31, 64])
+def test_counts_by_owners_at_every_window(hw, oracle, K):
+    """A token's ids in one window, two that overlap, or batches of eight of which the last overlaps; one token, the last lane of a round,
+    the next round; tables without and with dropped slots, which are looked up differently."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    for T in (1, 1024, 1025, 2049):
+        rng = np.random.default_rng(T + K)
+        E, nodes, rpn = 130, 2, 8
+        G = nodes * rpn
+        ids, e2r = rng.integers(0, E, (T, K), dtype=np.int32), rng.integers(0, G, E).astype(np.int32)
+        for dropped in (False, True):
+            if dropped:
+                ids[rng.random((T, K)) < 0.3] = -1
+            le, lr, ln, st = oracle.expert_load(ids, e2r, nodes, rpn)
+            full = lambda *n: torch.full(n, -77, dtype=torch.int32, device="cuda")
+            out = [full(E), full(G), full(nodes), full(1)]
+            B.hm_expert_load(hw.dev(ids), hw.dev(e2r), nodes, rpn, *out[:3], status=out[3])
+            for got, want in zip(out, (le, lr, ln, [st])):
+                assert np.array_equal(got.cpu().numpy(), want), (T, dropped, len(got))
+            ref, st = oracle.group_counts(ids, e2r, G, [G, nodes])
+            counts, status = full(2, 64), full(1)
+            B.hm_group_counts(hw.dev(ids), hw.dev(e2r), G, [G, nodes], counts, status)
+            assert np.array_equal(counts.cpu().numpy(), ref) and int(status.item()) == st == 0, (T, dropped)
+
+
 def test_alltoall_times_parity(hw, oracle):
     import torch
     from paper_2508_09591_amd import binding as B
