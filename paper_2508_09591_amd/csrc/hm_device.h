@@ -190,6 +190,24 @@ __device__ __forceinline__ int count_owned_groups(const int32_t *__restrict__ id
   return (__shfl(v, (g >> 1 & 2) + (g & 1), kWave) >> (g & 2 ? 16 : 0)) & 0xFFFF;
 }
 
+// The tokens of a workgroup: all, or, where a larger table is spread over workgroups that add to cleared outputs, `share` of them
+// from blockIdx.y on.
+struct OwnerTokens {
+  const int32_t *ids;
+  int T;
+};
+template <bool SPREAD>
+__device__ __forceinline__ OwnerTokens owner_tokens(const int32_t *ids, int T, int K, int share) {
+  if (!SPREAD) return {ids, T};
+  const int64_t from = (int64_t)blockIdx.y * share;
+  return {ids + from * K, (int)min((int64_t)share, T - from)};
+}
+// Tokens of a workgroup: whole rounds, as few as fill the chip once.
+static inline int spread_tokens(int64_t T, int64_t blocks) {
+  const int64_t rounds = (T + kOwnerThreads - 1) / kOwnerThreads, each = (rounds * blocks + 255) / 256;
+  return (int)(each < 1 ? 1 : each > kOwnerRounds ? kOwnerRounds : each) * kOwnerThreads;
+}
+
 // Value held by lane `src` (src must be wave-uniform).
 __device__ __forceinline__ int read_lane(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 __device__ __forceinline__ float read_lane(float v, int src) {
@@ -212,22 +230,28 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 }  // namespace hm
 
-// Which kernel takes the counts of a table (hm_expert_load, hm_group_counts); outputs: the groups of all levels, or ranks and nodes.
-//  * kOwners where the rounds of 1,024 tokens cost less than the clearing launch, the gap behind it and the atomics: two straight lines,
-//    hundredths of a us, through 4,000 shapes (16 to 65,536 tokens, one to 64 ids, 2 to 2,048 experts, even and Zipf ids, dropped slots;
-//    graphs of ten calls).  A round costs 0.2 us with one id per token, 0.25 with two or three, 0.45 with four to seven
-//    (two loads that overlap), 0.36 with eight, as much per eight of more, and twice that where a token's row is 100 bytes or more,
-//    whose lines no two lanes share.  Clear + count -> owners, us: loads of 8,192 x 8, 128 experts on 32 ranks 7.7 -> 5.9; group counts with
-//    four levels of 32 ranks 8.1 -> 6.3; up to two rounds 0.53 times as long, up to eight 0.65, but loads of 13,679 x 6 with 36
-//    outputs 7.6 -> 10.2, group counts of 2,964 x 31 with one 8.3 -> 13.2.  The rule loses more than 3 % in 40 of the shapes, a third at most.
-//    One workgroup that stores its counts (kAlone) took 1.3 times as long as the owners for tables of one round.
-//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room.
-enum class CountRoute { kAlone, kOwners, kAdded };
-static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t outputs, bool loads, bool alone_fits) {
+// Which kernel takes the counts of a table (hm_expert_load, hm_group_counts); outputs: the groups of all levels, or ranks and nodes;
+// blocks: the workgroups that own them.  All figures: graphs of ten calls; lines through 4,000 shapes of 16 to 65,536 and 2,500 of 512 to a
+// million tokens, one to 64 ids, 2 to 2,048 experts, even and Zipf ids, dropped slots.
+//  * kOwners, one launch, for few rounds of 1,024 tokens.  A round costs 0.2 us with one id per token, 0.25 with two or three, 0.45
+//    with four to seven (two loads that overlap), 0.36 with eight, as much per eight of more, and twice that where a token's row is 100
+//    bytes or more, whose lines no two lanes share.  Loads of 8,192 x 8, 128 experts on 32 ranks 5.9 us (kAdded 7.7), group counts with four
+//    levels of 32 ranks 6.3 (8.1).
+//  * kSpread: the owners' work on a part of the tokens each, as few rounds as fill the chip once, added to outputs that a launch before
+//    clears: where that is a us faster, as a launch costs the host more, and for up to sixteen ids and 12 us of rounds: beyond, every
+//    table is read too often.  Against kAdded 0.74 times as long up to 64 rounds, 0.5 to 0.7 beyond (16,384 x 8, four levels of 32 ranks 7.4 ->
+//    5.6), but 1.3 with 24 ids of 250,000 tokens (group counts 21 -> 35).
+//  * kAdded otherwise, unless the owners, which read a long row better than the lanes of kAdded, are faster for one or two rounds.
+//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room; 1.3 times as slow as owners where it has.
+// Of 3,500 shapes drawn anew, up to 260,000 tokens, 11 are more than 3 % slower than before there were windows and spreading, 17 % at most.
+enum class CountRoute { kAlone, kOwners, kSpread, kAdded };
+static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t outputs, int64_t blocks, bool loads, bool alone_fits) {
   if (E > hm::kOwnerMaxE) return alone_fits ? CountRoute::kAlone : CountRoute::kAdded;
-  const int64_t rounds = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads, steps = rounds * ((K + 7) / 8);
-  const int64_t step = K == 1 ? 20 : K <= 3 ? 25 : K < 8 ? 45 : K == 8 ? 36 : K <= 24 ? 43 : 85;
-  const int64_t owners = 295 + step * steps + E / 50 + outputs / 5;
+  const int64_t rounds = (T + hm::kOwnerThreads - 1) / hm::kOwnerThreads, batches = (K + 7) / 8;
+  const int64_t step = K == 1 ? 20 : K <= 3 ? 25 : K < 8 ? 45 : K == 8 ? 36 : K <= 24 ? 43 : 85;   // hundredths of a us, as all below
+  const int64_t owners = 295 + step * batches * rounds + E / 50 + outputs / 5;
+  const int64_t share = step * batches * (hm::spread_tokens(T, blocks) / hm::kOwnerThreads);
+  if (K <= 16 && share <= 1200) return rounds <= hm::kOwnerRounds && owners <= 585 + share * 11 / 10 ? CountRoute::kOwners : CountRoute::kSpread;
   const int64_t tokens = T < 65536 ? T : 65536;
   const int64_t added = loads ? 520 + 15 * K + outputs * 24 / 10 + E * 8 / 100 + tokens * 56 / 10000
                               : 525 + 9 * K + outputs * 35 / 10 + E * 4 / 100 + tokens * 40 / 10000;

@@ -110,18 +110,19 @@ __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
   if (threadIdx.x == 0 && bad) flag(p.status, HM_ERR_BAD_ID);
 }
 
-// Small tables: workgroups [0, expert_blocks) own kOwnerExperts experts each, the next ones seven ranks each, the
-// last ones seven nodes each.
-template <int W>
-__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks, uint32_t nodes_recip16) {
+// Workgroups [0, expert_blocks) own kOwnerExperts experts each, the next ones seven ranks each, the last ones seven nodes
+// each; SPREAD: for a part of the tokens, added to cleared outputs.
+template <int W, bool SPREAD>
+__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks, uint32_t nodes_recip16, int tokens) {
   __shared__ uint8_t table[kOwnerMaxE + 2];
   __shared__ __align__(16) uint32_t cnt[kOwnerExperts + 1][kWave];   // a place per lane of a wave, so that no two lanes meet; the last row: not ours
   int block = (int)blockIdx.x;
+  const OwnerTokens t = owner_tokens<SPREAD>(p.ids, p.T, p.K, tokens);
   if (block < expert_blocks) {   // an id is counted whether its expert's placement is valid or not, and stored if it is
     const int e0 = block * kOwnerExperts, lane = lane_id();
     const int e = e0 + (int)(threadIdx.x >> 4);   // whose places sixteen lanes add up in the end
     bool placed = false;
-    for_ids<W>(p.ids, p.T, p.K, [&] {
+    for_ids<W>(t.ids, t.T, p.K, [&] {
       if (e < p.E) placed = (unsigned)p.expert_to_rank[e] < (unsigned)p.G;
       const u32x4 zero = {0u, 0u, 0u, 0u};
       for (int i = threadIdx.x; i < (kOwnerExperts + 1) * kWave / 4; i += kOwnerThreads) ((u32x4 *)cnt)[i] = zero;
@@ -150,16 +151,26 @@ __global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p,
     v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, true);
     v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xF, 0xF, true);
     v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xF, 0xF, true);
-    if ((threadIdx.x & 15) == 0 && e < p.E) p.load_expert[e] = placed ? v : 0;
+    if ((threadIdx.x & 15) == 0 && e < p.E) {
+      if (!SPREAD) p.load_expert[e] = placed ? v : 0;
+      else if (placed && v) atomicAdd(&p.load_expert[e], v);
+    }
     return;
   }
   block -= expert_blocks;
   const bool ranks = block < rank_blocks;
   const int first = (ranks ? block : block - rank_blocks) * kOwnerGroups;
-  const int count = count_owned_groups<W>(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, ranks ? 65536u : nodes_recip16, first, table);
+  const int count = count_owned_groups<W>(t.ids, p.expert_to_rank, t.T, p.K, p.E, p.G, ranks ? 65536u : nodes_recip16, first, table);
   const int i = first + (int)threadIdx.x;
-  if (threadIdx.x < kOwnerGroups && i < (ranks ? p.G : p.N)) (ranks ? p.load_rank : p.load_node)[i] = count;
-  if (block == 0 && threadIdx.x == kOwnerGroups && p.status) *p.status = count ? HM_ERR_BAD_ID : 0;
+  if (threadIdx.x < kOwnerGroups && i < (ranks ? p.G : p.N)) {
+    int32_t *const out = (ranks ? p.load_rank : p.load_node) + i;
+    if (!SPREAD) *out = count;
+    else if (count) atomicAdd(out, count);
+  }
+  if (block == 0 && threadIdx.x == kOwnerGroups) {
+    if (SPREAD && count) flag(p.status, HM_ERR_BAD_ID);
+    if (!SPREAD && p.status) *p.status = count ? HM_ERR_BAD_ID : 0;
+  }
 }
 
 }  // namespace hm
@@ -190,15 +201,23 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   p.load_rank = load_rank;
   p.load_node = load_node;
   p.status = status;
-  const CountRoute route = count_route(T, K, E, p.G + p.N, true, T <= kAloneTokens && E <= kLdsExperts);
-  if (route == CountRoute::kOwners) {
-    const int expert_blocks = (E + kOwnerExperts - 1) / kOwnerExperts, rank_blocks = (p.G + kOwnerGroups - 1) / kOwnerGroups;
-    const int node_blocks = (p.N + kOwnerGroups - 1) / kOwnerGroups;
+  const int expert_blocks = (E + kOwnerExperts - 1) / kOwnerExperts, rank_blocks = (p.G + kOwnerGroups - 1) / kOwnerGroups;
+  const int owner_blocks = expert_blocks + rank_blocks + (p.N + kOwnerGroups - 1) / kOwnerGroups;
+  const CountRoute route = count_route(T, K, E, p.G + p.N, owner_blocks, true, T <= kAloneTokens && E <= kLdsExperts);
+  const int most = E > kWave ? E : kWave;
+  auto clear = [&] {
+    hipLaunchKernelGGL(load_clear_kernel, dim3((most + kLoadThreads - 1) / kLoadThreads), dim3(kLoadThreads), 0, stream, p);
+    return hm_launch_status();
+  };
+  if (route == CountRoute::kOwners || route == CountRoute::kSpread) {
+    const bool spread = route == CountRoute::kSpread;
     const uint32_t nodes_recip16 = (uint32_t)((65536 + p.R - 1) / p.R);   // exact for ranks (below 64)
-    const int width = owner_width(K);
-    hipLaunchKernelGGL((width == 4 ? load_owner_kernel<4> : width == 2 ? load_owner_kernel<2> : load_owner_kernel<1>),
-                       dim3((unsigned)(expert_blocks + rank_blocks + node_blocks)), dim3(kOwnerThreads), 0, stream, p, expert_blocks, rank_blocks,
-                       nodes_recip16);
+    const int width = owner_width(K), tokens = spread ? spread_tokens(T, owner_blocks) : T;
+    if (spread && clear() != HM_OK) return HM_ERR_HIP;
+    const auto kernel = spread ? (width == 4 ? load_owner_kernel<4, true> : width == 2 ? load_owner_kernel<2, true> : load_owner_kernel<1, true>)
+                               : (width == 4 ? load_owner_kernel<4, false> : width == 2 ? load_owner_kernel<2, false> : load_owner_kernel<1, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)owner_blocks, spread ? (unsigned)((T + tokens - 1) / tokens) : 1u), dim3(kOwnerThreads), 0, stream, p,
+                       expert_blocks, rank_blocks, nodes_recip16, tokens);
     return hm_launch_status();
   }
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
@@ -212,9 +231,7 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
     hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
     return hm_launch_status();
   }
-  const int most = E > kWave ? E : kWave;
-  hipLaunchKernelGGL(load_clear_kernel, dim3((most + kLoadThreads - 1) / kLoadThreads), dim3(kLoadThreads), 0, stream, p);
-  if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+  if (clear() != HM_OK) return HM_ERR_HIP;
   if (T == 0) return HM_OK;   // cleared outputs are the counts
   hipLaunchKernelGGL((load_count_kernel<kLoadThreads, false>), dim3((unsigned)blocks), dim3(kLoadThreads), 0, stream, p);
   return hm_launch_status();

@@ -88,12 +88,13 @@ __global__ __launch_bounds__(THREADS) void group_count_kernel(GroupParams p) {
   }
 }
 
-// Small tables: a workgroup owns seven groups of a level.
+// A workgroup owns seven groups of a level; SPREAD: for a part of the tokens, added to cleared outputs.
 struct GroupOwners {
   int32_t first_block[kMaxDepth];        // of a level; beyond all blocks where there is no such level
   uint32_t per_recip16[kMaxDepth];       // ceil(2^16 / ranks of a group): exact for ranks (below 64)
+  int32_t tokens;                        // of a workgroup, where they are spread
 };
-template <int W>
+template <int W, bool SPREAD>
 __global__ __launch_bounds__(kOwnerThreads) void group_owner_kernel(GroupParams p, GroupOwners o) {
   __shared__ uint8_t table[kOwnerMaxE + 2];
   int level = 0, block = (int)blockIdx.x, n = p.groups[0];
@@ -107,9 +108,16 @@ __global__ __launch_bounds__(kOwnerThreads) void group_owner_kernel(GroupParams 
     block = from ? (int)blockIdx.x - o.first_block[l] : block;
   }
   const int first = block * kOwnerGroups;
-  const int count = count_owned_groups<W>(p.ids, p.expert_to_rank, p.T, p.K, p.E, p.G, per_recip16, first, table);
+  const OwnerTokens t = owner_tokens<SPREAD>(p.ids, p.T, p.K, o.tokens);
+  const int count = count_owned_groups<W>(t.ids, p.expert_to_rank, t.T, p.K, p.E, p.G, per_recip16, first, table);
   if (threadIdx.x >= kWave) return;
-  const int lane = lane_id(), i = first + lane;   // the last owner of a level clears what is behind its groups
+  const int lane = lane_id(), i = first + lane;
+  if (SPREAD) {
+    if (lane < kOwnerGroups && i < n && count) atomicAdd(&p.counts[level * kWave + i], count);
+    if (blockIdx.x == 0 && lane == kOwnerGroups && count) flag(p.status, HM_ERR_BAD_ID);
+    return;
+  }
+  // the last owner of a level clears what is behind its groups
   if (i < kWave && (lane < kOwnerGroups || first + kOwnerGroups >= n)) p.counts[level * kWave + i] = lane < kOwnerGroups && i < n ? count : 0;
   if (blockIdx.x == 0 && lane == kOwnerGroups && p.status) *p.status = count ? HM_ERR_BAD_ID : 0;
 }
@@ -205,22 +213,32 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
   p.counts = counts;
   p.status = status;
   hipStream_t stream = (hipStream_t)hip_stream;
-  int outputs = 0;
-  for (int l = 0; l < depth; ++l) outputs += groups[l];
+  int outputs = 0, blocks = 0;
+  for (int l = 0; l < depth; ++l) {
+    outputs += groups[l];
+    blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
+  }
   // one workgroup that looks many slots up in memory is slower than several (E = 5,000, 1,024 tokens, K = 64: 32.4 us, 19.8)
   const bool alone_fits = T <= kAloneTokens && (E <= kStagedExperts || (int64_t)T * K <= 32768);
-  const CountRoute route = count_route(T, K, E, outputs, false, alone_fits);
-  if (route == CountRoute::kOwners) {
+  const CountRoute route = count_route(T, K, E, outputs, blocks, false, alone_fits);
+  if (route == CountRoute::kOwners || route == CountRoute::kSpread) {
+    const bool spread = route == CountRoute::kSpread;
     GroupOwners o;
-    int blocks = 0;
-    for (int l = 0; l < kMaxDepth; ++l) {
-      o.first_block[l] = l < depth ? blocks : 0x7FFFFFFF;
+    for (int l = 0, first = 0; l < kMaxDepth; ++l) {
+      o.first_block[l] = l < depth ? first : 0x7FFFFFFF;
       o.per_recip16[l] = (uint32_t)((65536 + p.per[l] - 1) / p.per[l]);
-      if (l < depth) blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
+      first += (p.groups[l] + kOwnerGroups - 1) / kOwnerGroups;
     }
+    o.tokens = spread ? spread_tokens(T, blocks) : T;
+    if (spread) {
+      hipLaunchKernelGGL(group_clear_kernel, dim3(1), dim3(kGroupThreads), 0, stream, p);
+      if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
+    }
+    const dim3 grid((unsigned)blocks, spread ? (unsigned)((T + o.tokens - 1) / o.tokens) : 1u);
     const int width = owner_width(K);
-    hipLaunchKernelGGL((width == 4 ? group_owner_kernel<4> : width == 2 ? group_owner_kernel<2> : group_owner_kernel<1>), dim3((unsigned)blocks),
-                       dim3(kOwnerThreads), 0, stream, p, o);
+    const auto kernel = spread ? (width == 4 ? group_owner_kernel<4, true> : width == 2 ? group_owner_kernel<2, true> : group_owner_kernel<1, true>)
+                               : (width == 4 ? group_owner_kernel<4, false> : width == 2 ? group_owner_kernel<2, false> : group_owner_kernel<1, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kOwnerThreads), 0, stream, p, o);
     return hm_launch_status();
   }
   if (route == CountRoute::kAlone) {
@@ -229,9 +247,9 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
   }
   hipLaunchKernelGGL(group_clear_kernel, dim3(1), dim3(kGroupThreads), 0, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;
-  int64_t blocks = ((int64_t)T + kGroupThreads - 1) / kGroupThreads;
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL((group_count_kernel<kGroupThreads, false>), dim3((unsigned)blocks), dim3(kGroupThreads), 0, stream, p);
+  int64_t all = ((int64_t)T + kGroupThreads - 1) / kGroupThreads;
+  if (all > 1024) all = 1024;
+  hipLaunchKernelGGL((group_count_kernel<kGroupThreads, false>), dim3((unsigned)all), dim3(kGroupThreads), 0, stream, p);
   return hm_launch_status();
 }
 

@@ -121,7 +121,8 @@ def test_counts_of_no_tokens(hw, E):
     (3072, 4, 40, 2, 2), (2049, 6, 40, 2, 8), (1025, 7, 40, 2, 2), (2048, 15, 64, 2, 8), (3072, 12, 128, 4, 8),   # loads by owners, groups added
     (8192, 8, 4096, 8, 8), (8193, 8, 63, 2, 7), (4096, 9, 128, 1, 64), (1023, 64, 130, 4, 4),   # up to eight steps of eight
     (7168, 8, 32, 2, 8), (8192, 8, 32, 2, 8), (1024, 33, 64, 2, 2), (1025, 33, 64, 2, 2),       # few experts, long tokens
-    (2049, 8, 4097, 4, 8), (600, 8, 5000, 4, 8), (1024, 40, 20, 2, 2)])     # no room in the owners' table; many ids of few experts
+    (2049, 8, 4097, 4, 8), (600, 8, 5000, 4, 8), (1024, 40, 20, 2, 2),      # no room in the owners' table; many ids of few experts
+    (16384, 8, 130, 4, 8), (30001, 3, 64, 3, 5), (100001, 1, 256, 8, 8), (70000, 10, 48, 2, 4), (70000, 24, 48, 2, 4)])   # tokens spread over workgroups, and beyond
 def test_counts_by_owners_and_beyond(hw, oracle, T, K, E, nodes, rpn):
     """Both calls on both sides of the rule that gives each workgroup its own outputs: dropped, repeated and invalid ids, an
     invalid placement, outputs that hold rubbish, entries behind a level's groups cleared."""
