@@ -604,17 +604,20 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
 
 // Dispatch (SCALED = false: a bit copy) and transpose of ragged rows.  The rows written start at
 // different places of a line, so the vectors of the token differ from row to row: each is read again,
-// from the caches, at the place its row asks for; the reads of four rows are in flight together.
+// from the caches, at the place its row asks for; the reads of R rows are in flight together.
 // Measured (8,192 / 16,384 tokens, bf16, HIP events, against vectors counted from the row's start): 7.3
 // copies of 2,051 elements 162 -> 123 us (4.5 TB/s), of 1,032 92 -> 76 us, of 7,160 251 -> 223 us; 3.6 copies of
 // 4,140 68 -> 50 us.  Splitting a row evenly over its waves (no line grid) loses more than the last,
 // short segment costs: 4,160 elements 218 -> 301 us; giving that segment to the wave before it changes nothing.
-template <typename ROW, bool SCALED>
+// R: rows whose reads are in flight together.  Eight pay for the bf16 transpose of five to eight slots, whose rounding is hidden then (8,192 x
+// 1,030, six rows 28.5 -> 26.4 us, 4,096 x 1,030, eight 21.1 -> 19.6; but ten rows 27.4 -> 28.1, 20,000 x 2,222, three 53.7 -> 56.3;
+// dispatch and fp32 equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each row's vectors from
+// there (4,097 x 1,030, six rows: dispatch 15.2 -> 15.9, transpose 15.9 -> 16.8: the reads are not what it waits for).
+template <typename ROW, bool SCALED, int R>
 __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
                                                                      const float *__restrict__ row_weight, int64_t rows,
                                                                      typename ROW::elem *__restrict__ out) {
   typedef RaggedRows<typename ROW::elem> access;
-  constexpr int R = 4;
   int t, seg;
   if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
   const int lane = lane_id();
@@ -657,6 +660,7 @@ __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p
     // All reads have arrived here; left alone the compiler waits before every store, and so for the
     // store before it too (rows of 7,160 bf16, 3.6 copies: 121 us, 99 us with the one wait).
     __asm__ volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    if constexpr (R == 8) __asm__ volatile("" : "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
 #pragma unroll
     for (int j = 0; j < R; ++j)
       if (in_row[j]) store_row<access>(out, p, row[j], at[j], SCALED ? ROW::scale(a[j], r[j]) : r[j]);
@@ -711,16 +715,31 @@ __device__ __forceinline__ void owned_rows(const RowParams &p, int t, int k0, in
   }
 }
 
-// fn(N, k0) over the K slots in pieces of eight, four and one.
-template <typename FN>
+// fn(N, k0) over the K slots in pieces of eight and, WHOLE, the rest in one: a piece is a chain of trips to memory, its list, then its
+// rows or weights.  Else the rest goes in pieces of four and one, which a dispatch, whose stores wait for nothing, prefers by 0.1 us.
+// Combine, plan's weights, rest in pieces of four and one -> in one: 16,384 x 64, K = 7 8.2 -> 6.1 us, x 128, K = 3 7.5 -> 5.8, 4,096 x
+// 256, K = 6 7.0 -> 5.5, 8,192 x 1,030, K = 6 26.1 -> 23.6; bf16 transpose of 16,384 x 64, K = 7 7.0 -> 6.4.
+template <bool WHOLE, typename FN>
 __device__ __forceinline__ void for_slots(int K, FN fn) {
   int k0 = 0;
   for (; k0 + 8 <= K; k0 += 8) fn(std::integral_constant<int, 8>{}, k0);
-  if (k0 + 4 <= K) {
-    fn(std::integral_constant<int, 4>{}, k0);
-    k0 += 4;
+  if constexpr (WHOLE) {
+    switch (K - k0) {
+      case 1: fn(std::integral_constant<int, 1>{}, k0); break;
+      case 2: fn(std::integral_constant<int, 2>{}, k0); break;
+      case 3: fn(std::integral_constant<int, 3>{}, k0); break;
+      case 4: fn(std::integral_constant<int, 4>{}, k0); break;
+      case 5: fn(std::integral_constant<int, 5>{}, k0); break;
+      case 6: fn(std::integral_constant<int, 6>{}, k0); break;
+      case 7: fn(std::integral_constant<int, 7>{}, k0); break;
+    }
+  } else {
+    if (k0 + 4 <= K) {
+      fn(std::integral_constant<int, 4>{}, k0);
+      k0 += 4;
+    }
+    for (; k0 < K; ++k0) fn(std::integral_constant<int, 1>{}, k0);
   }
-  for (; k0 < K; ++k0) fn(std::integral_constant<int, 1>{}, k0);
 }
 
 // Dispatch (SCALED = false) and transpose.  A lane reads a weight for every slot, that of row 0 for a slot
@@ -735,7 +754,7 @@ __global__ __launch_bounds__(kFlatThreads) void spread_flat_kernel(RowParams p, 
   if (!unit_of_lane(p, t, v)) return;
   const int at = access::place(p, v);
   const u32x4 r = *(const typename access::vec *)(in + ((int64_t)t * p.H + at));
-  for_slots(p.K, [&](auto n, int k0) {
+  for_slots<SCALED>(p.K, [&](auto n, int k0) {
     constexpr int N = decltype(n)::value;
     int row[N];
     float a[N];
@@ -761,7 +780,7 @@ __global__ __launch_bounds__(kFlatThreads) void combine_flat_kernel(RowParams p,
   float acc[E], wsum = 0.0f;
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.0f;
-  for_slots(p.K, [&](auto n, int k0) {
+  for_slots<true>(p.K, [&](auto n, int k0) {
     constexpr int N = decltype(n)::value;
     int row[N];
     float a[N];
@@ -1181,7 +1200,7 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
     if (whole)
       hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds, stream, p, x, packed, packed_rows);
     else
-      hipLaunchKernelGGL((spread_ragged_kernel<RowBf16, false>), grid, dim3(kCopyThreads), lds, stream, p, x, nullptr,
+      hipLaunchKernelGGL((spread_ragged_kernel<RowBf16, false, 4>), grid, dim3(kCopyThreads), lds, stream, p, x, nullptr,
                          packed_rows, packed);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
@@ -1308,8 +1327,8 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
                          dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, plan->row_capacity,
                          (elem *)gy, gy_rows);
     } else {
-      hipLaunchKernelGGL((spread_ragged_kernel<ROW, true>), grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout,
-                         plan->row_weight, rows, (elem *)gy);
+      hipLaunchKernelGGL((ROW::kPerVec == 8 && K > 4 && K <= 8 ? spread_ragged_kernel<ROW, true, ROW::kPerVec> : spread_ragged_kernel<ROW, true, 4>),
+                         grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, rows, (elem *)gy);
     }
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;

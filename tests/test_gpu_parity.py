@@ -451,6 +451,37 @@ def test_rows_of_any_length(hw, oracle, H, K, off):
         assert B.hm_plan_status(g.plan)[0] == B.HM_ERR_CAPACITY, ctx
 
 
+@pytest.mark.parametrize("K", list(range(1, 13)))
+def test_rows_by_every_piece_of_the_slots(hw, oracle, K):
+    """Narrow rows, whose lanes take a token's slots in eights and the rest in one piece: the bits of the kernels that find the rows
+    themselves, and the oracle's. Ragged rows of up to eight slots, all of whose reads the bf16 transpose has in flight."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(K)
+    E, nodes, rpn = 24, 2, 8
+    for T, H in ((4100, 64), (4100, 70), (300, 1030)):
+        ids, w = rng.integers(0, E, (T, K), dtype=np.int32), rng.random((T, K), dtype=np.float32) + np.float32(0.05)
+        ids[rng.random((T, K)) < 0.1] = -1
+        e2r = rng.integers(0, nodes * rpn, E, dtype=np.int32)
+        ora = oracle.plan(ids, w, e2r, nodes, rpn, GPU)
+        g = hw.GpuPlan(ids, w, e2r, nodes, rpn, GPU)
+        x32 = rng.standard_normal((T, H), dtype=np.float32)
+        x, y32 = W.f32_to_bf16_bits(x32), rng.random((ora.total_rows, H), dtype=np.float32) + np.float32(0.5)
+        for fn, y, dtype in ((B.hm_combine, hw.to_dev_bf16(W.f32_to_bf16_bits(y32)), torch.bfloat16),
+                             (B.hm_combine_mix, hw.to_dev_bf16(W.f32_to_bf16_bits(y32)), torch.bfloat16), (B.hm_combine_f32, hw.dev(y32), torch.float32)):
+            out = [torch.full((T, H), float("nan"), dtype=dtype, device="cuda") for _ in range(2)]
+            for o, weights in zip(out, (None, g.w_d)):
+                fn(y, weights, g.plan, o)
+            as_bits = torch.int16 if dtype == torch.bfloat16 else torch.int32
+            assert torch.equal(out[0].view(as_bits), out[1].view(as_bits)), (T, H, fn)
+        gy = torch.full((ora.total_rows, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.hm_combine_transpose_bf16(hw.to_dev_bf16(x), g.plan, gy)
+        assert np.array_equal(hw.bf16_to_host(gy), oracle.combine_transpose_bf16(x, ora.row_token, ora.row_weight)), (T, H)
+        gy = torch.full((ora.total_rows, H), float("nan"), dtype=torch.float32, device="cuda")
+        B.hm_combine_transpose(hw.dev(x32), g.plan, gy)
+        assert np.array_equal(gy.cpu().numpy().view(np.uint32), oracle.combine_transpose(x32, ora.row_token, ora.row_weight).view(np.uint32)), (T, H)
+
+
 @pytest.mark.parametrize("T,K,H,off", [(37, 5, 512, 0), (37, 5, 520, 1), (600, 4, 1030, 1), (1024, 6, 2056, 8), (4096, 4, 64, 0),
                                        (4096, 4, 128, 8), (4096, 5, 129, 1), (4096, 5, 70, 1), (40, 9, 5, 0), (4096, 1, 576, 0)])
 def test_every_row_call_with_short_buffers(hw, oracle, T, K, H, off):
