@@ -73,10 +73,24 @@ __device__ __forceinline__ int64_t divided(int64_t n, uint64_t recip) {
   return recip ? (int64_t)__umul64hi((uint64_t)n, recip) : n;
 }
 
+// The workgroup's place among the others: as launched, or (NEAR) in groups of 128 neighbours that run on one die, the groups going round the
+// dies; a short last round is as launched.  Workgroups go round the eight dies, and each die has an L2 of its own: where rows begin inside a
+// line, the line that two workgroups share is written from two dies, twice and in part.  Those lines are what ragged rows lose: 4,097 x 1,030,
+// six rows per token, dispatch 15.2 us, 11.8 when the shared lines are left out, 14.3 grouped; 15.2 -> 19.5 when they are written through the
+// caches.  near_pays() says where the grouping is used.
+constexpr unsigned kDies = 8, kNear = 128;
+template <bool NEAR>
+__device__ __forceinline__ unsigned block_place() {
+  if constexpr (!NEAR) return blockIdx.x;
+  constexpr unsigned round = kDies * kNear;
+  const unsigned b = blockIdx.x, in = b % round, first = b - in;
+  return first + round <= gridDim.x ? first + in % kDies * kNear + in / kDies : b;
+}
+
 // Wave-uniform (token, segment) of this wave, or false when past the end.
-template <int BLOCK, bool DIVIDE = false>
+template <int BLOCK, bool DIVIDE = false, bool NEAR = false>
 __device__ __forceinline__ bool unit_of_wave(const RowParams &p, int &t, int &seg) {
-  const int64_t unit = (int64_t)blockIdx.x * (BLOCK / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t unit = (int64_t)block_place<NEAR>() * (BLOCK / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (unit >= p.nunits) return false;
   t = (int)(DIVIDE ? unit / p.nseg : divided(unit, p.recip));
   seg = (int)(unit - (int64_t)t * p.nseg);
@@ -125,10 +139,11 @@ __device__ __forceinline__ void store_row(ELEM *base, const RowParams &p, int64_
 // ---------------------------------------------------------------------------------------------
 // dispatch: packed[slot_row[t,k], :] = x[t, :] for kept slots
 // ---------------------------------------------------------------------------------------------
+template <bool NEAR>
 __global__ __launch_bounds__(kCopyThreads) void dispatch_rows_kernel(RowParams p, const uint16_t *__restrict__ x,
                                                                      uint16_t *__restrict__ packed, int64_t packed_rows) {
   int t, seg;
-  if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
+  if (!unit_of_wave<kCopyThreads, false, NEAR>(p, t, seg)) return;
   const int lane = lane_id();
   int at;
   const bool in_row = WholeRows<uint16_t>::place(p, 0, seg * kWave + lane, at);
@@ -609,17 +624,18 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
 // copies of 2,051 elements 162 -> 123 us (4.5 TB/s), of 1,032 92 -> 76 us, of 7,160 251 -> 223 us; 3.6 copies of
 // 4,140 68 -> 50 us.  Splitting a row evenly over its waves (no line grid) loses more than the last,
 // short segment costs: 4,160 elements 218 -> 301 us; giving that segment to the wave before it changes nothing.
-// R: rows whose reads are in flight together.  Eight pay for the bf16 transpose of five to eight slots, whose rounding is hidden then (8,192 x
-// 1,030, six rows 28.5 -> 26.4 us, 4,096 x 1,030, eight 21.1 -> 19.6; but ten rows 27.4 -> 28.1, 20,000 x 2,222, three 53.7 -> 56.3;
-// dispatch and fp32 equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each row's vectors from
+// R: rows whose reads are in flight together.  Eight pay for the bf16 transpose of up to eight slots that are kept nearly all, whose rounding
+// is hidden then (8,192 x 1,030, six rows 28.5 -> 26.4 us, 4,096 x 1,030, eight 21.1 -> 19.6, 4,096 x 4,140, 7.7 with the combine behind it 123.1 ->
+// 118.0; but ten rows 27.4 -> 28.1, 5.3 rows of eight slots with the combine 163.8 -> 166.4 at 16,384 x 2,050, 333 -> 343 at 65,536 x 1,030,
+// 20,000 x 2,222, three 53.7 -> 56.3; dispatch and fp32 equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each row's vectors from
 // there (4,097 x 1,030, six rows: dispatch 15.2 -> 15.9, transpose 15.9 -> 16.8: the reads are not what it waits for).
-template <typename ROW, bool SCALED, int R>
+template <typename ROW, bool SCALED, int R, bool NEAR>
 __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
                                                                      const float *__restrict__ row_weight, int64_t rows,
                                                                      typename ROW::elem *__restrict__ out) {
   typedef RaggedRows<typename ROW::elem> access;
   int t, seg;
-  if (!unit_of_wave<kCopyThreads>(p, t, seg)) return;
+  if (!unit_of_wave<kCopyThreads, false, NEAR>(p, t, seg)) return;
   const int lane = lane_id();
   int my_row = -1;
   float my_w = 0.0f;
@@ -687,8 +703,9 @@ struct NarrowRows : RaggedRows<ELEM> {
 // (token, vector) of this lane, or false when past the end.  The workgroup's first unit is divided by a
 // 64-bit reciprocal, the rest is a numerator n below nvec + kFlatThreads <= 400, for which the 22-bit one is
 // exact: it is too large by less than nvec / 2^22 of itself, and n nvec < 2^16.
+template <bool NEAR>
 __device__ __forceinline__ bool unit_of_lane(const RowParams &p, int &t, int &v) {
-  const int64_t first = (int64_t)blockIdx.x * kFlatThreads;
+  const int64_t first = (int64_t)block_place<NEAR>() * kFlatThreads;
   const int64_t t0 = divided(first, p.recip);
   const unsigned n = (unsigned)(first - t0 * p.nvec) + threadIdx.x;
   const unsigned dt = (n * (((1u << 22) + (unsigned)p.nvec - 1u) / (unsigned)p.nvec)) >> 22;
@@ -745,13 +762,13 @@ __device__ __forceinline__ void for_slots(int K, FN fn) {
 // Dispatch (SCALED = false) and transpose.  A lane reads a weight for every slot, that of row 0 for a slot
 // without a row, so the transpose is launched only where there is a row 0 (rows > 0): a read
 // under the slot's own condition costs 0.5 to 0.8 us (8,192 tokens, 3.6 rows of 64 bf16: 5.2 -> 6.0).
-template <typename ROW, bool SCALED>
+template <typename ROW, bool SCALED, bool NEAR>
 __global__ __launch_bounds__(kFlatThreads) void spread_flat_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
                                                                    const float *__restrict__ row_weight, int64_t rows,
                                                                    typename ROW::elem *__restrict__ out) {
   typedef NarrowRows<typename ROW::elem> access;
   int t, v;
-  if (!unit_of_lane(p, t, v)) return;
+  if (!unit_of_lane<NEAR>(p, t, v)) return;
   const int at = access::place(p, v);
   const u32x4 r = *(const typename access::vec *)(in + ((int64_t)t * p.H + at));
   for_slots<SCALED>(p.K, [&](auto n, int k0) {
@@ -775,7 +792,7 @@ __global__ __launch_bounds__(kFlatThreads) void combine_flat_kernel(RowParams p,
   typedef NarrowRows<typename ROW::elem> access;
   constexpr int E = ROW::kPerVec;
   int t, v;
-  if (!unit_of_lane(p, t, v)) return;
+  if (!unit_of_lane<false>(p, t, v)) return;
   const int at = access::place(p, v);
   float acc[E], wsum = 0.0f;
 #pragma unroll
@@ -1026,6 +1043,19 @@ static inline bool in_vectors(const RowForm &f) { return f.H * (int64_t)f.elem_b
 // tokens, K = 1, 16 bf16: 3.2 -> 2.7).
 constexpr int kFlatTokens = 4096;
 
+// Whether the dispatch groups its workgroups by die: many rows per token that begin inside a line, and not far
+// more of them than the 256 MB of the Infinity Cache.  HIP events, the dispatch alone and with the combine that reads what it wrote, as launched ->
+// grouped: 4,097 x 1,030 with 6 rows 15.2 -> 14.3 us and 30.7 -> 30.2, 8,192 x 1,030 57.0 -> 55.5 (both), 65,536 x 136 with 7.7 rows +20 % and 91.3 ->
+// 79.9, 262,144 x 136 +25 % and 391 -> 328, 65,536 x 100 89.8 -> 87.3 (both), 16,384 x 1,030 with 7.7 +6 % and 123.1 -> 121.0, 2,048 to 32,768 x 2,050
+// with 7.7 +2 % and equal, 32,768 x 7,161 with 7.7 (3.6 GB) -3 %.  With fewer rows the dispatch alone gains (16,384 x 1,030 with 3.6 rows
+// 29.5 -> 26.3) and the combine behind it, which no longer finds the lines where it reads, loses more: 8,192 x 7,161 with 3.6 rows 204 -> 209 for
+// both, with 5.3 301 -> 306, 65,536 x 72 with one row 11.6 -> 14.1, with 2.3 18.4 -> 20.1.  So does the transpose (16,384 x 2,050 with 7.7 rows and
+// its combine 227.5 -> 229.7), and whole lines, of which neighbours share none (8,192 x 7,168 with 3.6 rows 159.8 -> 162.3).
+static inline bool near_pays(const RowForm &f, const hm_plan_out *plan) {
+  const double c = rows_per_token(plan, f.T);
+  return !f.lines && c > 5.5 && (double)f.T * f.H * f.elem_bytes * c <= 0.85e9;
+}
+
 // Dispatch (scaled = false) and transpose.
 //  * Vectors, narrow: flat up to the widths at which it still gains.  65,536 tokens, 3.6 rows each, in waves ->
 //    flat: dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 256 32.8 -> 28.8 (but 32,768 tokens: 3 % slower, or 7.7
@@ -1189,18 +1219,20 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   uint16_t *packed = (uint16_t *)packed_bf16;
   const RowForm form = row_form(T, K, H, 2, x_bf16, packed_bf16);
   const Route route = spread_route(form, plan, false);
+  const bool near = near_pays(form, plan);
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, 8, grid)) return HM_ERR_SHAPE;
-    hipLaunchKernelGGL((spread_flat_kernel<RowBf16, false>), grid, dim3(kFlatThreads), 0, stream, p, x, nullptr, packed_rows,
-                       packed);
+    hipLaunchKernelGGL((near ? spread_flat_kernel<RowBf16, false, true> : spread_flat_kernel<RowBf16, false, false>), grid,
+                       dim3(kFlatThreads), 0, stream, p, x, nullptr, packed_rows, packed);
   } else if (route != Route::kElems) {
     const bool whole = route == Route::kWhole;
     if (!grid_for_units(p, H, 8, whole, packed_bf16, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
     const unsigned lds = lds_cap_bytes(form.lines ? dispatch_waves_per_cu(plan, T, H) : kCopyWavesPerCu, kCopyThreads);
     if (whole)
-      hipLaunchKernelGGL(dispatch_rows_kernel, grid, dim3(kCopyThreads), lds, stream, p, x, packed, packed_rows);
+      hipLaunchKernelGGL((near ? dispatch_rows_kernel<true> : dispatch_rows_kernel<false>), grid, dim3(kCopyThreads), lds, stream, p, x,
+                         packed, packed_rows);
     else
-      hipLaunchKernelGGL((spread_ragged_kernel<RowBf16, false, 4>), grid, dim3(kCopyThreads), lds, stream, p, x, nullptr,
+      hipLaunchKernelGGL((near ? spread_ragged_kernel<RowBf16, false, 4, true> : spread_ragged_kernel<RowBf16, false, 4, false>), grid, dim3(kCopyThreads), lds, stream, p, x, nullptr,
                          packed_rows, packed);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
@@ -1314,7 +1346,7 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
   if (route == Route::kFlat && rows == 0) route = Route::kElems;   // the flat kernel reads the weight of row 0
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, ROW::kPerVec, grid)) return HM_ERR_SHAPE;
-    hipLaunchKernelGGL((spread_flat_kernel<ROW, true>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)gout,
+    hipLaunchKernelGGL((spread_flat_kernel<ROW, true, false>), grid, dim3(kFlatThreads), 0, stream, p, (const elem *)gout,
                        plan->row_weight, rows, (elem *)gy);
   } else if (route != Route::kElems) {
     const bool whole = route == Route::kWhole;
@@ -1327,8 +1359,11 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
                          dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, plan->row_capacity,
                          (elem *)gy, gy_rows);
     } else {
-      hipLaunchKernelGGL((ROW::kPerVec == 8 && K > 4 && K <= 8 ? spread_ragged_kernel<ROW, true, ROW::kPerVec> : spread_ragged_kernel<ROW, true, 4>),
-                         grid, dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, rows, (elem *)gy);
+      constexpr int many = ROW::kPerVec;
+      const double c = rows_per_token(plan, T);
+      const bool eight = many == 8 && K <= 8 && c > 4.25 && c > K - 1;
+      hipLaunchKernelGGL((eight ? spread_ragged_kernel<ROW, true, many, false> : spread_ragged_kernel<ROW, true, 4, false>), grid,
+                         dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, rows, (elem *)gy);
     }
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;

@@ -482,6 +482,32 @@ def test_rows_by_every_piece_of_the_slots(hw, oracle, K):
         assert np.array_equal(gy.cpu().numpy().view(np.uint32), oracle.combine_transpose(x32, ora.row_token, ora.row_weight).view(np.uint32)), (T, H)
 
 
+@pytest.mark.parametrize("T,K,H", [(1363, 6, 1030), (1365, 6, 1030), (1366, 6, 1030), (4099, 7, 1030), (4099, 5, 1030), (1366, 8, 1030),
+                                   (16384, 6, 136), (30117, 6, 72), (33001, 6, 70), (4093, 8, 264), (5000, 7, 520)])
+def test_rows_of_workgroups_grouped_by_die(hw, oracle, T, K, H):
+    """Whole, ragged and narrow rows that begin inside a line, many per token, over no, one and more whole rounds of the dies and a rest, and on either side of five and a
+    half rows: the oracle's rows to the bit, the guard rows behind them untouched."""
+    import torch
+    from paper_2508_09591_amd import binding as B
+    rng = np.random.default_rng(T + H)
+    E, nodes, rpn = 64, 4, 4
+    ids, w = rng.integers(0, E, (T, K), dtype=np.int32), rng.random((T, K), dtype=np.float32) + np.float32(0.05)
+    e2r = rng.integers(0, nodes * rpn, E, dtype=np.int32)
+    ora = oracle.plan(ids, w, e2r, nodes, rpn, NONE)
+    g = hw.GpuPlan(ids, w, e2r, nodes, rpn, NONE)
+    assert B.hm_plan_status(g.plan)[1] == ora.total_rows
+    x32 = rng.standard_normal((T, H), dtype=np.float32)
+    x, n = W.f32_to_bf16_bits(x32), ora.total_rows
+    for fn, src, dtype, ref in ((B.hm_dispatch_pack, hw.to_dev_bf16(x), torch.bfloat16, oracle.dispatch_pack(x, ora.row_token)),
+                                (B.hm_combine_transpose_bf16, hw.to_dev_bf16(x), torch.bfloat16, oracle.combine_transpose_bf16(x, ora.row_token, ora.row_weight)),
+                                (B.hm_combine_transpose, hw.dev(x32), torch.float32, oracle.combine_transpose(x32, ora.row_token, ora.row_weight))):
+        out = torch.full((n + 2, H), float("nan"), dtype=dtype, device="cuda")
+        fn(src, g.plan, out[:n])
+        got = hw.bf16_to_host(out[:n]) if dtype == torch.bfloat16 else out[:n].cpu().numpy().view(np.uint32)
+        assert np.array_equal(got, ref if dtype == torch.bfloat16 else ref.view(np.uint32)), fn
+        assert bool(torch.isnan(out[n:]).all()), fn
+
+
 @pytest.mark.parametrize("T,K,H,off", [(37, 5, 512, 0), (37, 5, 520, 1), (600, 4, 1030, 1), (1024, 6, 2056, 8), (4096, 4, 64, 0),
                                        (4096, 4, 128, 8), (4096, 5, 129, 1), (4096, 5, 70, 1), (40, 9, 5, 0), (4096, 1, 576, 0)])
 def test_every_row_call_with_short_buffers(hw, oracle, T, K, H, off):
