@@ -811,9 +811,9 @@ def run_planner(args, emit=True, workload=None):
                "sample": "the whole %s batch once (incremental Z update for %d cuts + selection), %.2f s" % (wl.name, len(cuts), dt)}
         log("cpu oracle: %.2f s" % dt)
     swap_ms = kern[names[2]]
-    # The co-occurrence tables are int8 matrix products over 0/1 indicator tiles (E <= 256): per cut
+    # The co-occurrence tables are matrix products over 0/1 indicator tiles in FP4 (E <= 256): per cut
     # C = A^T S (E_pad x E_pad x T) and CG = S^T M (E_pad x 32 ceil(ng/32) x T).  Their dense operation count
-    # against the int8 MFMA peak is what the line reports; the products themselves are a small part of the
+    # against the int8 MFMA peak (half of the FP4 one) is what the line reports; the products themselves are a small part of the
     # call (filling the tiles, barriers and LDS latency, and three short launches, set its time).
     e_pad = 32 * (1 if E <= 32 else 2 if E <= 64 else 4 if E <= 128 else 8)
     dense_ops = sum(2 * e_pad * (e_pad + 32 * ((u + 31) // 32)) * T for u in cuts) if E <= 256 else 0
@@ -822,14 +822,14 @@ def run_planner(args, emit=True, workload=None):
               "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 5),
               "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int32", "data": "synthetic",
               "config": {"workload": "%s: T=%d K=%d E=%d G=%d, hierarchy U=%s, gamma=10" % (wl.name, T, K, E, G, U)},
-              "roofline": {"bound": "mfma", "kernel": "hm_swap_counts_multi (swap_cooc + swap_reduce + swap_build)",
+              "roofline": {"bound": "mfma", "kernel": "hm_swap_counts_multi (swap_cooc + swap_pairs)",
                            "achieved": round(dense_ops / (swap_ms * 1e-3) / 1e12, 3), "peak": round(peak_ops / 1e12, 1),
                            "unit": "int8 TOP/s (dense products of the 0/1 indicator tiles; peak: MI355X int8 MFMA)",
                            "frac": round(dense_ops / (swap_ms * 1e-3) / peak_ops, 5), "traffic": None,
                            "dense_ops_per_call": dense_ops,
                            "note": "latency-bound: eight short launches per planner step over a few hundred KiB of input; in the "
-                                   "matrix kernel the products are about a tenth of the time, filling and clearing the tiles, "
-                                   "barriers and LDS latency the rest"},
+                                   "matrix kernel the products are a small part of the time, loads, marks and stores of the tables "
+                                   "the rest"},
               "cpu_baseline": cpu, "kernels": kern, "monitored_counts": monitored}
     if not emit:
         return result
