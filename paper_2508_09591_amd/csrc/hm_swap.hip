@@ -202,7 +202,7 @@ constexpr int kCoocChunkTokensMax = 32640;   // a chunk's counts are stored as 1
 constexpr int kCoocAddedTokensMax = 1 << 24; // a workgroup's sums are binary32
 constexpr int kCoocMaxE = 512;
 constexpr int kCoocPartMaxE = 256;   // experts up to which the workspace holds partial tables
-constexpr int kCoocAddedGroups = 256;   // workgroups aimed at where chunks are added up (512: E = 320, 4,096 tokens 33 -> 39 us)
+constexpr int kCoocAddedGroups = 256;   // workgroups aimed at where chunks are added up (512, with marks as bytes: E = 320, 4,096 tokens 33 -> 39 us)
 constexpr int kCoocOwnK = 8;         // most slots of a token that the matrix kernel works out itself
 constexpr int kCoocThreads = 1024;   // = most tokens of a tile: a lane per token
 constexpr int kCoocWaves = kCoocThreads / kWave;
