@@ -11,6 +11,7 @@
 // the matrix cores for E <= 512 (further down), from O(T K (K + ng)) atomic updates, one lane per
 // routing slot, beyond that, for E > 256 with more than eight slots per token, and where the products would have
 // too little to do (atomics_pay).
+#include "hm_cooc.h"
 #include "hm_device.h"
 
 #include <type_traits>
@@ -201,11 +202,9 @@ constexpr int kCoocChunks = 16;      // partial tables per cut, some of them of 
 constexpr int kCoocChunkTokensMax = 32640;   // a chunk's counts are stored as 16-bit values
 constexpr int kCoocAddedTokensMax = 1 << 24; // a workgroup's sums are binary32
 constexpr int kCoocMaxE = 512;
-constexpr int kCoocPartMaxE = 256;   // experts up to which the workspace holds partial tables
 constexpr int kCoocAddedGroups = 256;   // workgroups aimed at where chunks are added up (512, with marks as bytes: E = 320, 4,096 tokens 33 -> 39 us)
 constexpr int kCoocOwnK = 8;         // most slots of a token that the matrix kernel works out itself
-constexpr int kCoocThreads = 1024;   // = most tokens of a tile: a lane per token
-constexpr int kCoocWaves = kCoocThreads / kWave;
+constexpr int kCoocThreads = kCoocWaves * kWave;   // = most tokens of a tile: a lane per token
 constexpr int kCoocStep = 64;        // tokens of one 32x32x64 product
 constexpr int kCoocPad = 16;         // bytes behind a tile row, which spread 32 rows over all banks
 constexpr int kCoocLds = 162816;     // dynamic LDS of a workgroup, most
@@ -409,11 +408,10 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   const int cut = blockIdx.y, panel = blockIdx.z, chunk = blockIdx.x;
   const int E = p.E, ng = p.ng[cut], stride = p.stride;
   const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int row_tiles = (int)((uint32_t)E + 31u) >> 5, g_tiles = (int)((uint32_t)ng + 31u) >> 5;
-  uint8_t *const a_tile = tiles;                               // [32 row_tiles][stride] A
-  uint8_t *const s_tile = a_tile + 32 * row_tiles * stride;    // [panel][stride]        S, its experts
-  uint8_t *const m_tile = s_tile + kPanel * stride;            // [32 g_tiles][stride]   M
-  const int vecs = (32 * row_tiles + kPanel + 32 * g_tiles) * (stride / 16);
+  typedef CoocTiles<COLS> layout_t;
+  const layout_t lay(E, ng);
+  uint8_t *const a_tile = tiles, *const s_tile = tiles + lay.s_at() * stride, *const m_tile = tiles + lay.m_at() * stride;   // rows of `stride` bytes
+  const int vecs = lay.rows() * (stride / 16);
 
   // Where a token of the tile is marked: in the row's word (token % words) and there in nibble (token / words), so that the lanes of a
   // wave, which hold neighbouring tokens, meet at a bank only where their rows do, and never at a word.  The products take
@@ -426,8 +424,7 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   };
 
   // What this wave accumulates: a row of tiles of C, or, from the last wave down, one tile of the panel's CG.
-  const int g_job = kCoocWaves - 1 - w, g_row = g_job >> (g_tiles - 1), g_col = g_job & (g_tiles - 1);
-  const bool has_c = w < row_tiles, has_g = g_row < COLS;
+  const bool has_c = lay.has_c(w), has_g = lay.has_g(w);
   const int quarter = w - kCoocWaves / 2;   // of the tokens whose groups the wave counts, a lane per group
   const bool counts_base = panel == 0 && (unsigned)quarter < 4u;
   f32x16 acc[COLS], second;
@@ -460,9 +457,9 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
         for (int c = 0; c < N; ++c) sums[c] = mfma_fp4(r_op[j], c_op[j][c], sums[c]);
     }
   };
-  // the tile rows and columns of this wave's products; a tile of CG is multiplied as often as a wave has tiles
-  const uint8_t *const rows = has_c ? a_tile + 32 * w * stride : s_tile + 32 * (has_g ? g_row : 0) * stride;
-  const uint8_t *const columns = has_c ? s_tile : m_tile + 32 * (has_g ? g_col : 0) * stride;
+  // the tile rows and columns of this wave's products
+  const uint8_t *const rows = tiles + (has_c ? lay.c_rows(w) : lay.g_rows(w)) * stride;
+  const uint8_t *const columns = tiles + (has_c ? lay.c_columns(w) : lay.g_columns(w)) * stride;
 
   const uint32_t T = (uint32_t)p.T, t_begin = (uint32_t)chunk * (uint32_t)p.tokens_per_chunk;
   const uint32_t t_end = min(T, t_begin + (uint32_t)p.tokens_per_chunk);
@@ -489,7 +486,7 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
       if (w * kWave < tokens) {
         int at;
         const uint32_t value = place(tid, at);
-        const int a_to_s = (32 * row_tiles - kPanel * panel) * stride;
+        const int a_to_s = (lay.s_at() - kPanel * panel) * stride;
         if (__builtin_expect(ng <= 32, 1)) mark_token<uint32_t>(id, E, group_of, stride, kPanel * panel, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
         else mark_token<uint64_t>(id, E, group_of, stride, kPanel * panel, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
       }
@@ -521,13 +518,17 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
       }
     }
     __syncthreads();
-    if (has_c || has_g) multiply(acc, rows, columns);
-    if (kBoth && has_c && has_g) {
-      f32x16(&one)[1] = *(f32x16(*)[1])&second;
-      multiply(one, s_tile + 32 * g_row * stride, m_tile + 32 * g_col * stride);
+    auto of_g = [](f32x16 &sums) -> f32x16(&)[layout_t::kColumnsOfG] { return *(f32x16(*)[layout_t::kColumnsOfG])&sums; };
+    if (layout_t::kColumnsOfC == layout_t::kColumnsOfG) {
+      if (has_c || has_g) multiply(acc, rows, columns);
+    } else {   // one tile of CG, not COLS: behind M's tiles LDS ends (200,000 tokens, 256 experts, four cuts: with a second product, of the
+               // same tile, whose sums are dropped, 76.6 us, 71.8 without; 8,192 18.9 and 18.7)
+      if (has_c) multiply(acc, rows, columns);
+      else if (has_g) multiply(of_g(acc[0]), rows, columns);
     }
+    if (kBoth && has_c && has_g) multiply(of_g(second), tiles + lay.g_rows(w) * stride, tiles + lay.g_columns(w) * stride);
     if (counts_base) {   // a mark is one bit, so a word's population count is its number of tokens
-      const i32x4 *row = (const i32x4 *)(m_tile + min(lane, 32 * g_tiles - 1) * stride);
+      const i32x4 *row = (const i32x4 *)(m_tile + min(lane, 32 * lay.m - 1) * stride);
 #pragma unroll 1
       for (int i = quarter; i < 2 * steps; i += 4) {
         const i32x4 v = row[i];
@@ -560,8 +561,8 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
     }
   };
   auto put_groups = [&](const f32x16 &sums) {
-    const int g = 32 * g_col + col;
-    if (g < ng) put(sums, (kPanel * panel + 32 * g_row) / kBlock, table.cg(0), ng, ADDED ? g : table.cg_column(g, part));
+    const int g = 32 * lay.g_column(w) + col;
+    if (g < ng) put(sums, (kPanel * panel + 32 * lay.g_row(w)) / kBlock, table.cg(0), ng, ADDED ? g : table.cg_column(g, part));
   };
   if (has_c) {
 #pragma unroll
@@ -1115,7 +1116,7 @@ static CoocLaunch cooc_launch(int E, int groups, int64_t tokens) {   // groups o
     return e == hipSuccess;
   }();
   constexpr int kBatch = 4 / COLS * kCoocStep;   // a tile is whole batches of products
-  const int rows = (E + 31) / 32 * 32 + 32 * COLS + (groups + 31) / 32 * 32;
+  const int rows = CoocTiles<COLS>(E, groups).rows();
   int most = 2 * (kCoocLds / rows - kCoocPad) / kBatch * kBatch;
   if (most > kCoocThreads) most = kCoocThreads;
   CoocLaunch l = {swap_cooc_kernel<COLS, OWN_SLOTS, ADDED>, 32 * COLS, 0, 0, 0};
@@ -1127,7 +1128,6 @@ static CoocLaunch cooc_launch(int E, int groups, int64_t tokens) {   // groups o
   l.lds = (size_t)rows * l.stride;
   return l;
 }
-static inline int cooc_columns(int E) { return E > 128 && E <= kCoocPartMaxE ? 2 : 1; }   // tile columns of a panel
 template <int COLS>
 static inline CoocLaunch cooc_launch_for(int E, bool own_slots, bool parts, int groups, int64_t tokens) {
   if (!parts) return cooc_launch<COLS, true, true>(E, groups, tokens);

@@ -1,0 +1,48 @@
+"""What is launched, looked at on the host: where kernels read in LDS, how much of it a launch asks for, and which kernel a call
+takes, for calls whose results would not show it."""
+import os
+import subprocess
+
+import pytest
+
+import launch_recorder
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return launch_recorder.build(tmp_path_factory.mktemp("launches"))
+
+
+def test_products_of_the_swap_tables_stay_inside_their_tiles(tmp_path):
+    """Every tile that a wave of swap_cooc_kernel multiplies lies in the rows that its launch asks LDS for, for all experts and
+    groups, also where another cut has fewer groups than the one the launch is sized for."""
+    (tmp_path / "walk.cpp").write_text(r"""
+#include <cstdio>
+#include "hm_cooc.h"
+template <int COLS> static int walk(int E, int ng) {
+  typedef hm::CoocTiles<COLS> layout;
+  const layout t(E, ng);
+  int bad = t.rows() != 32 * ((E + 31) / 32 + COLS + (ng + 31) / 32), c = 0, g = 0;
+  auto inside = [&](int first, int tiles, int from, int to) { return first >= from && first + 32 * tiles <= to; };
+  for (int w = 0; w < hm::kCoocWaves; ++w) {
+    if (t.has_c(w)) ++c, bad += !inside(t.c_rows(w), 1, 0, t.s_at()) + !inside(t.c_columns(w), layout::kColumnsOfC, t.s_at(), t.m_at());
+    if (t.has_g(w)) ++g, bad += !inside(t.g_rows(w), 1, t.s_at(), t.m_at()) + !inside(t.g_columns(w), layout::kColumnsOfG, t.m_at(), t.rows());
+    if (COLS > 1) bad += t.has_c(w) && t.has_g(w);   // these share their sums
+  }
+  bad += c != (E + 31) / 32 || g != COLS * ((ng + 31) / 32);   // every tile has a wave
+  if (bad) std::printf("E %d groups %d columns %d: %d\n", E, ng, COLS, bad);
+  return bad;
+}
+int main() {
+  int bad = 0;
+  for (int E = 1; E <= 512; ++E)
+    for (int ng = 1; ng <= 64; ++ng) bad += hm::cooc_columns(E) == 2 ? walk<2>(E, ng) : walk<1>(E, ng);
+  return bad != 0;
+}
+""")
+    exe = str(tmp_path / "walk")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2508_09591_amd", "csrc"), "-o", exe, str(tmp_path / "walk.cpp")])
+    p = subprocess.run([exe], capture_output=True, text=True)
+    assert p.returncode == 0, p.stdout[:2000]
