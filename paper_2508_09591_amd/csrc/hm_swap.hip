@@ -823,6 +823,8 @@ __global__ __launch_bounds__(kSwapThreads) void swap_build_kernel(SwapParams p) 
 // selection
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxDim = 4;
+constexpr int kSelectTerms = kMaxDim * kSelectPairs * (int)sizeof(double);   // bytes of LDS for the terms of the pairs ...
+constexpr int kSelectStaged = 65536 - kSelectTerms;                          // ... and what is left of the 64 KiB that every launch gets, for counts
 
 struct SelectParams {
   int32_t d, G, E;
@@ -1422,8 +1424,11 @@ extern "C" hm_status hm_swap_select(int32_t d, const int32_t *U, int32_t G, int3
     const int n = intra ? G : i < d ? U[i + 1] : 1;
     const int32_t *const z = intra ? z_intra : i < d ? z_inter[i + 1] : nullptr;
     p.fan[i] = intra ? (double)(G / U[d - 1]) : i < d ? (double)(U[i + 1] / U[i]) : 0.0;
-    p.tile[i] = G > 32 && n % 4 == 0 && ((uintptr_t)z & 15) == 0 ? fours : -1;   // the loads into LDS are of 16 bytes
-    if (i < d && p.tile[i] >= 0) fours += kSelectPairs * n / 4;
+    // The loads into LDS are of 16 bytes.  Four terms of 64 groups (U = 1, 64, 64, 64) do not all fit: the last is read from memory.
+    const int more = kSelectPairs * n / 4;
+    const bool staged = i < d && G > 32 && n % 4 == 0 && ((uintptr_t)z & 15) == 0 && 16 * (fours + more) <= kSelectStaged;
+    p.tile[i] = staged ? fours : -1;
+    if (staged) fours += more;
   }
   hipLaunchKernelGGL(G <= 32 ? swap_q_kernel<32> : swap_q_kernel<64>, dim3(p.nblocks), dim3(kSelectThreads), (size_t)fours * 16, stream, p);
   if (hm_launch_status() != HM_OK) return HM_ERR_HIP;

@@ -306,9 +306,10 @@ def test_swap_select_on_any_counts(hw, oracle, G, U, E):
         assert tuple(bp.tolist()) == (flat // E, flat % E) and float(bt.item()) == Qg.min()
 
 
-@pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (64, [1, 2, 4], 5), (40, [1, 5, 20], 33), (48, [1, 12, 24], 17), (36, [1], 9)])
+@pytest.mark.parametrize("G,U,E", [(64, [1, 8, 16, 32], 40), (64, [1, 2, 4], 5), (40, [1, 5, 20], 33), (48, [1, 12, 24], 17), (36, [1], 9),
+                                     (64, [1, 64, 64, 64], 24), (64, [1, 32, 64, 64], 19)])   # four terms of 64 groups: more than fits; just within
 def test_swap_select_with_counts_staged_in_lds(hw, oracle, G, U, E):
-    """More than 32 groups in whole, aligned fours go through LDS; the same counts four bytes further on do not: the same bits."""
+    """More than 32 groups in whole, aligned fours go through LDS, as far as there is room; the same counts four bytes further on do not: the same bits."""
     import torch
     from paper_2508_09591_amd import binding as B
     rng = np.random.default_rng(G + E)

@@ -46,3 +46,32 @@ int main() {
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2508_09591_amd", "csrc"), "-o", exe, str(tmp_path / "walk.cpp")])
     p = subprocess.run([exe], capture_output=True, text=True)
     assert p.returncode == 0, p.stdout[:2000]
+
+
+def test_selection_asks_for_no_more_lds_than_every_launch_gets(recorder):
+    """All hierarchies of the ranks that the call takes, steps that split nothing among them: the counts staged in LDS and the terms of
+    64 pairs (four doubles each) beside them stay inside what a kernel has without asking for more, and what fits is staged."""
+    result = launch_recorder.run(recorder, r"""
+result = []
+def chains(G, d, U):
+    if len(U) == d:
+        yield U
+        return
+    for u in range(U[-1], G + 1):
+        if u % U[-1] == 0 and G % u == 0:
+            yield from chains(G, d, U + [u])
+for G in (1, 2, 12, 32, 33, 36, 40, 48, 60, 64):
+    for d in (1, 2, 3, 4):
+        for U in chains(G, d, [1]):
+            zi, five = (ctypes.c_void_p * d)(*[at(1).value] * d), (ctypes.c_double * d)(*[0.5] * d)
+            rc = L.hm_swap_select(d, (ctypes.c_int32 * d)(*U), G, 64, 8.0, 2.0, zi, at(2), five, 1.0, five, five, 0.1, 0.1, 10.0, at(3), at(4), at(5), at(6),
+                                  1 << 30, None)
+            result.append([G, U, rc, launched()])
+""")
+    assert len(result) > 300
+    for G, U, rc, launches in result:
+        assert rc == 0 and [k["name"] for k in launches] == ["swap_q_kernel<%d>" % (32 if G <= 32 else 64), "swap_argmin_kernel<256>"], (G, U)
+        q = launches[0]
+        assert q["lds"] + 4 * 64 * 8 <= q["granted"], (G, U, q)
+        wanted = [256 * n for n in U[1:] + [G] if n % 4 == 0 and G > 32]
+        assert q["lds"] == (sum(wanted) if sum(wanted) + 4 * 64 * 8 <= 65536 else sum(wanted[:3])), (G, U, q)
