@@ -1043,17 +1043,23 @@ static inline bool in_vectors(const RowForm &f) { return f.H * (int64_t)f.elem_b
 // tokens, K = 1, 16 bf16: 3.2 -> 2.7).
 constexpr int kFlatTokens = 4096;
 
-// Whether the dispatch groups its workgroups by die: many rows per token that begin inside a line, and not far
-// more of them than the 256 MB of the Infinity Cache.  HIP events, the dispatch alone and with the combine that reads what it wrote, as launched ->
-// grouped: 4,097 x 1,030 with 6 rows 15.2 -> 14.3 us and 30.7 -> 30.2, 8,192 x 1,030 57.0 -> 55.5 (both), 65,536 x 136 with 7.7 rows +20 % and 91.3 ->
-// 79.9, 262,144 x 136 +25 % and 391 -> 328, 65,536 x 100 89.8 -> 87.3 (both), 16,384 x 1,030 with 7.7 +6 % and 123.1 -> 121.0, 2,048 to 32,768 x 2,050
-// with 7.7 +2 % and equal, 32,768 x 7,161 with 7.7 (3.6 GB) -3 %.  With fewer rows the dispatch alone gains (16,384 x 1,030 with 3.6 rows
-// 29.5 -> 26.3) and the combine behind it, which no longer finds the lines where it reads, loses more: 8,192 x 7,161 with 3.6 rows 204 -> 209 for
-// both, with 5.3 301 -> 306, 65,536 x 72 with one row 11.6 -> 14.1, with 2.3 18.4 -> 20.1.  So does the transpose (16,384 x 2,050 with 7.7 rows and
-// its combine 227.5 -> 229.7), and whole lines, of which neighbours share none (8,192 x 7,168 with 3.6 rows 159.8 -> 162.3).
-static inline bool near_pays(const RowForm &f, const hm_plan_out *plan) {
-  const double c = rows_per_token(plan, f.T);
-  return !f.lines && c > 5.5 && (double)f.T * f.H * f.elem_bytes * c <= 0.85e9;
+// Whether the dispatch groups its workgroups by die: rows that begin inside a line, of up to 80 MB of tokens, 130 MB if the rows are narrow.
+// How many rows a token has does not matter, so a plan that was never synchronised is as well off as one that was.
+// Grouping helps a dispatch that is bound by its writes: tokens that the Infinity Cache (256 MB) still holds, as a layer's output that has just
+// been written, or short rows, a large part of which is shared lines.
+// HIP events, dispatch and a combine that reads a buffer of its own, as launched -> grouped in turn, geometric means of the dispatch
+// alone over 2,200 shapes drawn (2,000 to 262,144 tokens, one to ten slots, 0.2 to ten rows per token), three to eight passes in turn / so many that no
+// token is still cached:
+//   128 to 1,400 bytes, up to 30 MB   +1 to +12 % / 0 to +8 %     30 to 80 MB   +2 to +13 % / 0 to +8 %     80 to 130 MB   +1 to +6 % / 0 to +9 %
+//   wider rows, up to 30 MB           +2 to +6 % / -2 to +2 %     30 to 80 MB   +1 to +9 % / -2 to 0 %      more           -3 to +1 % / -5 to +2 %
+// 65,536 x 136 with 3.3 rows 22.4 -> 18.4, 4.5 29.2 -> 22.0, 7.6 58.0 -> 48.8; 4,097 x 1,030 with 5.8 15.2 -> 14.3; 16,384 x 520 with 5.4
+// 27.3 -> 23.6; but 8,192 x 7,161 with 3.3 108.7 -> 111.9, 75,791 x 1,039 163 -> 174.
+// A combine that reads the very rows that dispatch has just written, with nothing between, finds fewer of them on its own die: 65,536 x 72
+// with one row 11.6 -> 14.1 for both.  The transpose keeps the launch order (16,384 x 2,050 with 7.7 rows and its combine 227.5 ->
+// 229.7), and so do whole lines, of which neighbours share none (8,192 x 7,168 with 3.6 rows 159.8 -> 162.3).
+static inline bool near_pays(const RowForm &f) {
+  const int64_t row = (int64_t)f.H * f.elem_bytes, tokens = f.T * row;
+  return !f.lines && row >= 32 && tokens <= (row <= 1400 ? 130000000 : 80000000);
 }
 
 // Dispatch (scaled = false) and transpose.
@@ -1219,7 +1225,7 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   uint16_t *packed = (uint16_t *)packed_bf16;
   const RowForm form = row_form(T, K, H, 2, x_bf16, packed_bf16);
   const Route route = spread_route(form, plan, false);
-  const bool near = near_pays(form, plan);
+  const bool near = near_pays(form);
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, 8, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL((near ? spread_flat_kernel<RowBf16, false, true> : spread_flat_kernel<RowBf16, false, false>), grid,

@@ -59,7 +59,7 @@ def run(recorder, body):
     p = subprocess.run([sys.executable, "-c", _CHILD, recorder, ROOT], input=body, capture_output=True, text=True, timeout=120)
     assert p.returncode == 0, p.stderr
     text = p.stdout[p.stdout.rindex("RESULT ") + 7:]
-    mangled = sorted(set(re.findall(r'"name": "(\w+)"', text)))
+    mangled = sorted(set(re.findall(r'"(_ZN2hm\w+)"', text)))
     if mangled:
         names = subprocess.run(["c++filt"], input="\n".join(mangled), capture_output=True, text=True, check=True).stdout.splitlines()
         for m, n in zip(mangled, names):

@@ -485,8 +485,8 @@ def test_rows_by_every_piece_of_the_slots(hw, oracle, K):
 @pytest.mark.parametrize("T,K,H", [(1363, 6, 1030), (1365, 6, 1030), (1366, 6, 1030), (4099, 7, 1030), (4099, 5, 1030), (1366, 8, 1030),
                                    (16384, 6, 136), (30117, 6, 72), (33001, 6, 70), (4093, 8, 264), (5000, 7, 520)])
 def test_rows_of_workgroups_grouped_by_die(hw, oracle, T, K, H):
-    """Whole, ragged and narrow rows that begin inside a line, many per token, over no, one and more whole rounds of the dies and a rest, and on either side of five and a
-    half rows: the oracle's rows to the bit, the guard rows behind them untouched."""
+    """Whole, ragged and narrow rows that begin inside a line, over no, one and more whole rounds of the dies and a rest: the oracle's rows to the
+    bit, the guard rows behind them untouched."""
     import torch
     from paper_2508_09591_amd import binding as B
     rng = np.random.default_rng(T + H)

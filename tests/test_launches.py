@@ -75,3 +75,39 @@ for G in (1, 2, 12, 32, 33, 36, 40, 48, 60, 64):
         assert q["lds"] + 4 * 64 * 8 <= q["granted"], (G, U, q)
         wanted = [256 * n for n in U[1:] + [G] if n % 4 == 0 and G > 32]
         assert q["lds"] == (sum(wanted) if sum(wanted) + 4 * 64 * 8 <= 65536 else sum(wanted[:3])), (G, U, q)
+
+
+# A plan of T tokens with a bound of `most` rows per token and, where `rows` is not None, a row count.
+_ROWS = r"""
+def plan(T, K, most, rows):
+    c = B.hm_plan_out()
+    c.num_dest, c.row_capacity, c.max_rows_per_token = 32, T * K, most
+    c.expected_rows = 0 if rows is None else int(rows * T)
+    for i, f in enumerate(("dest_count", "dest_offset", "row_token", "slot_row", "slot_keep", "row_weight", "status")):
+        setattr(c, f, at(20 + i).value)
+    return ctypes.byref(c)
+def kernel(rc):
+    assert rc == 0
+    one, = launched()
+    return one["name"]
+"""
+
+
+def test_dispatch_groups_workgroups_by_sizes_alone(recorder):
+    """Rows off the line grid: 128 neighbours on one die for rows of 32 bytes or more and up to 80 MB of tokens, 130 MB up to 1,400 bytes a
+    row, for each kernel that has the choice and whatever is known of the rows per token; whole lines keep the launch order."""
+    result = launch_recorder.run(recorder, _ROWS + r"""
+result = []
+for T, H, off in ((4097, 1030, 0), (38834, 1030, 0), (38835, 1030, 0), (8192, 15, 0), (8192, 17, 0), (92857, 700, 0), (92858, 700, 0), (65000, 701, 0),
+                  (65536, 72, 0), (100, 7161, 0), (4096, 1024, 16), (4096, 1024, 0), (65536, 100, 0)):
+    names = set()
+    for most, rows in ((8, None), (0, None), (8, 1.2), (8, 3.0), (8, 5.6), (8, 7.7)):
+        x, out = at(1), ctypes.c_void_p(at(2).value + off)
+        names.add(kernel(L.hm_dispatch_pack(x, T, 8, H, plan(T, 8, most, rows), out, 8 * T, None)))
+    result.append([T, H, off, sorted(names)])
+""")
+    assert len({n.split("<")[0] for r in result for n in r[3]}) >= 3   # spread_ragged, spread_flat, dispatch_rows
+    for T, H, off, names in result:
+        near = (H % 64 != 0 or off != 0) and 2 * H >= 32 and 2 * T * H <= (130e6 if 2 * H <= 1400 else 80e6)
+        for name in names:
+            assert name.startswith("dispatch_elems") or name.endswith("true>") == near, (T, H, off, name)
