@@ -624,10 +624,7 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
 // copies of 2,051 elements 162 -> 123 us (4.5 TB/s), of 1,032 92 -> 76 us, of 7,160 251 -> 223 us; 3.6 copies of
 // 4,140 68 -> 50 us.  Splitting a row evenly over its waves (no line grid) loses more than the last,
 // short segment costs: 4,160 elements 218 -> 301 us; giving that segment to the wave before it changes nothing.
-// R: rows whose reads are in flight together.  Eight pay for the bf16 transpose of up to eight slots that are kept nearly all, whose rounding
-// is hidden then (8,192 x 1,030, six rows 28.5 -> 26.4 us, 4,096 x 1,030, eight 21.1 -> 19.6, 4,096 x 4,140, 7.7 with the combine behind it 123.1 ->
-// 118.0; but ten rows 27.4 -> 28.1, 5.3 rows of eight slots with the combine 163.8 -> 166.4 at 16,384 x 2,050, 333 -> 343 at 65,536 x 1,030,
-// 20,000 x 2,222, three 53.7 -> 56.3; dispatch and fp32 equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each row's vectors from
+// R: rows whose reads are in flight together, eight where eight_reads_pay() says so, else four (dispatch and fp32: equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each row's vectors from
 // there (4,097 x 1,030, six rows: dispatch 15.2 -> 15.9, transpose 15.9 -> 16.8: the reads are not what it waits for).
 template <typename ROW, bool SCALED, int R, bool NEAR>
 __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
@@ -919,6 +916,10 @@ static inline double rows_per_token(const hm_plan_out *plan, int32_t T) {
   if (plan->max_rows_per_token > 0) return (double)plan->max_rows_per_token;
   return 0.0;
 }
+// The same from the row count alone, 0 if there is none: for what loses where a bound of eight stands for three rows or five.
+static inline double known_rows_per_token(const hm_plan_out *plan, int32_t T) {
+  return plan->expected_rows > 0 && T > 0 ? (double)plan->expected_rows / (double)T : 0.0;
+}
 
 // Waves per CU of the dispatch of whole-line rows.  A wave with seven stores for its one load wants fewer
 // neighbours than one with three, as long as what it loads comes from the Infinity Cache (256 MB) and
@@ -1062,6 +1063,16 @@ static inline bool near_pays(const RowForm &f) {
   return !f.lines && row >= 32 && tokens <= (row <= 1400 ? 130000000 : 80000000);
 }
 
+// Whether the bf16 transpose of ragged rows has the reads of eight rows in flight, which hides its rounding: for up to eight slots that are
+// known to be kept nearly all, and 7 MB of gradients or more.  Four -> eight, 1,300 shapes drawn, three to eight slots, three to eight buffers in
+// turn, geometric means: kept nearly all, from 7 MB on 0 to +4 % (16,384 x 1,030 with 7.6 rows 74.7 -> 65.0 us, 8,192 x 1,030 with six 28.5 -> 26.4),
+// below -1 to -4 % (5,114 x 363 with 7.6 11.9 -> 12.9); 4.3 rows of six to eight slots or more 0 to +6 %, but -8 % for some (70,304 x 591 with 4.7);
+// fewer rows -4 to -17 % (8,192 x 7,161 with 2.2 81.6 -> 97.3), which a bound of eight in place of a count would not show.  Ten rows 27.4 -> 28.1.
+static inline bool eight_reads_pay(const RowForm &f, const hm_plan_out *plan) {
+  const double c = known_rows_per_token(plan, f.T);
+  return f.K <= 8 && c > 4.25 && c > f.K - 1 && (int64_t)f.T * f.H * f.elem_bytes >= 7000000;
+}
+
 // Dispatch (scaled = false) and transpose.
 //  * Vectors, narrow: flat up to the widths at which it still gains.  65,536 tokens, 3.6 rows each, in waves ->
 //    flat: dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 256 32.8 -> 28.8 (but 32,768 tokens: 3 % slower, or 7.7
@@ -1135,7 +1146,7 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
 // counts: tokens of one row or so under a bound of eight take 49 -> 81 us (8,192 x 7,168 bf16, 1.2 rows), 18 -> 25 (x 2,048), 62 -> 96
 // (32,768 x 2,048, 1.6 rows), which is more than the 3 to 12 % that those of many rows would gain.
 static inline bool short_segments(const RowForm &f, const hm_plan_out *plan) {
-  const double rows = plan->expected_rows > 0 && f.T > 0 ? (double)plan->expected_rows / (double)f.T : 0.0;
+  const double rows = known_rows_per_token(plan, f.T);
   if (rows < 2.0) return false;
   if (f.vecs <= kWave) return true;
   constexpr int64_t kAtOnce = 4096;
@@ -1365,10 +1376,9 @@ static hm_status launch_transpose(const void *gout, int32_t T, int32_t K, int32_
                          dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, plan->row_capacity,
                          (elem *)gy, gy_rows);
     } else {
-      constexpr int many = ROW::kPerVec;
-      const double c = rows_per_token(plan, T);
-      const bool eight = many == 8 && K <= 8 && c > 4.25 && c > K - 1;
-      hipLaunchKernelGGL((eight ? spread_ragged_kernel<ROW, true, many, false> : spread_ragged_kernel<ROW, true, 4, false>), grid,
+      constexpr bool bf16 = std::is_same_v<ROW, RowBf16>;
+      const bool eight = bf16 && eight_reads_pay(form, plan);
+      hipLaunchKernelGGL((eight ? spread_ragged_kernel<ROW, true, bf16 ? 8 : 4, false> : spread_ragged_kernel<ROW, true, 4, false>), grid,
                          dim3(kCopyThreads), lds, stream, p, (const elem *)gout, plan->row_weight, rows, (elem *)gy);
     }
   } else {

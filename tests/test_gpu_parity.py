@@ -482,7 +482,7 @@ def test_rows_by_every_piece_of_the_slots(hw, oracle, K):
         assert np.array_equal(gy.cpu().numpy().view(np.uint32), oracle.combine_transpose(x32, ora.row_token, ora.row_weight).view(np.uint32)), (T, H)
 
 
-@pytest.mark.parametrize("T,K,H", [(1363, 6, 1030), (1365, 6, 1030), (1366, 6, 1030), (4099, 7, 1030), (4099, 5, 1030), (1366, 8, 1030),
+@pytest.mark.parametrize("T,K,H", [(1363, 6, 1030), (1365, 6, 1030), (1366, 6, 1030), (4099, 7, 1030), (4099, 5, 1030), (1366, 8, 1030), (3401, 8, 1030),
                                    (16384, 6, 136), (30117, 6, 72), (33001, 6, 70), (4093, 8, 264), (5000, 7, 520)])
 def test_rows_of_workgroups_grouped_by_die(hw, oracle, T, K, H):
     """Whole, ragged and narrow rows that begin inside a line, over no, one and more whole rounds of the dies and a rest: the oracle's rows to the

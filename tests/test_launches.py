@@ -111,3 +111,18 @@ for T, H, off in ((4097, 1030, 0), (38834, 1030, 0), (38835, 1030, 0), (8192, 15
         near = (H % 64 != 0 or off != 0) and 2 * H >= 32 and 2 * T * H <= (130e6 if 2 * H <= 1400 else 80e6)
         for name in names:
             assert name.startswith("dispatch_elems") or name.endswith("true>") == near, (T, H, off, name)
+
+
+def test_transpose_reads_eight_rows_for_a_row_count_not_for_a_bound(recorder):
+    """Ragged rows: the reads of eight rows in flight for the bf16 transpose of up to eight slots that a row count says are kept nearly all, of
+    7 MB or more; four for a plan that was never synchronised, whose bound is eight whatever it holds, and for fp32."""
+    result = launch_recorder.run(recorder, _ROWS + r"""
+result = []
+for T, H in ((16384, 1030), (4097, 1030), (3398, 1030), (3399, 1030), (16384, 2050)):
+    for K, most, rows in ((8, 8, None), (8, 0, None), (8, 8, 1.2), (8, 8, 6.9), (8, 8, 7.2), (8, 8, 8), (6, 6, None), (6, 6, 5.8), (5, 5, 4.2), (4, 4, 4), (10, 10, 9.9)):
+        for fn, bits in (("hm_combine_transpose_bf16", 16), ("hm_combine_transpose", 32)):
+            result.append([T, H, K, rows, bits, kernel(getattr(L, fn)(at(1), T, K, H, plan(T, K, most, rows), at(2), 8 * T, None))])
+""")
+    for T, H, K, rows, bits, name in result:
+        eight = bits == 16 and rows is not None and K <= 8 and rows > max(K - 1, 4.25) and 2 * T * H >= 7e6
+        assert name == "spread_ragged_kernel<RowBf16, true, %d, false>" % (8 if eight else 4) if bits == 16 else "RowF32, true, 4" in name, (T, H, K, rows, name)
