@@ -617,8 +617,9 @@ struct PairParams {
 __device__ __forceinline__ i32x4 load_four(const int32_t *at) { return *(const i32x4_align4 *)at; }
 __device__ __forceinline__ u16x4 load_four(const uint16_t *at) { return *(const u16x4_align2 *)at; }
 
-// N chunks, every STEP-th, of four values that begin at i of the n of a chunk; `at` is the first of these chunks.  SUM: type in which
-// the chunks are added, 16 bits where all tokens together cannot exceed them (two values per instruction), else 32.
+// N chunks, every STEP-th, of four values that begin at i of the n of a chunk; `at` is the first of these chunks.  The sums are of 32 bits;
+// counts of 16 come two in a word, and a product with (1, 0) or (0, 1) adds one of them in an instruction (the whole call, 128 experts, four cuts,
+// 8,192 tokens 11.9 us, with a conversion of each count 12.2, with sums of 16 bits, two in an instruction, 11.9; 256 experts 19.1, 19.4, 18.8).
 template <int N, int STEP, typename V>
 struct Chunks {
   decltype(load_four((const V *)nullptr)) v[N];
@@ -627,13 +628,20 @@ struct Chunks {
 #pragma unroll
     for (int j = 0; j < N; ++j, at += STEP * n) v[j] = load_four((const V *)((const char *)at + bytes));
   }
-  template <typename SUM>
   __device__ __forceinline__ void sum(int32_t *out) const {
-    typedef SUM four __attribute__((ext_vector_type(4)));
-    four sum = __builtin_convertvector(v[0], four);
+    i32x4 s = {0, 0, 0, 0};
 #pragma unroll
-    for (int j = 1; j < N; ++j) sum += __builtin_convertvector(v[j], four);
-    *(i32x4_align4 *)out = __builtin_convertvector(sum, i32x4);
+    for (int j = 0; j < N; ++j) {
+      if constexpr (sizeof(V) == sizeof(uint16_t)) {
+        typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s[e] = (int32_t)__builtin_amdgcn_udot2((u16x2){v[j][e & 2], v[j][e | 1]}, (u16x2){(uint16_t)(~e & 1), (uint16_t)(e & 1)}, (uint32_t)s[e], false);
+      } else {
+        s += v[j];
+      }
+    }
+    *(i32x4_align4 *)out = s;
   }
 };
 // Blocks of fewer than four values (the last of a few experts with a few groups): a lane per value.
@@ -645,8 +653,8 @@ __device__ __forceinline__ void sum_few(int32_t *out, const V *at, int n, int i,
   out[i] = sum;
 }
 
-// V, SUM: types of a count in the tables and of the sum of all chunks'.
-template <typename V, typename SUM, int CHUNKS>   // one chunk: tables that chunks were added to
+// V: type of a count in the tables.
+template <typename V, int CHUNKS>   // one chunk: tables that chunks were added to
 __global__ __launch_bounds__(kPairThreads) void swap_pairs_kernel(PairParams p) {
   constexpr int kOfC = CHUNKS > 4 ? 4 : 1, kOfCG = CHUNKS > 4 ? 2 : 1;   // waves that share the chunks of a value
   __shared__ __align__(16) int32_t s_c[2][kOfC][kBlock * kBlock];    // [block (I, J), (J, I)]
@@ -693,16 +701,16 @@ __global__ __launch_bounds__(kPairThreads) void swap_pairs_kernel(PairParams p) 
   if (CHUNKS == 1) {
     const int i = tid & (kBlock * kBlock - 1), row = i & (kBlock - 1), col = i >> 4;
     if (row < rows && col < cols) s_c[side][0][col * rows + row] = (int)plain;
-  } else if (n_c >= 4) c.template sum<SUM>(&s_c[side][of_c][c_i]);
+  } else if (n_c >= 4) c.sum(&s_c[side][of_c][c_i]);
   else sum_few(s_c[side][of_c], c_at, n_c, lane, CHUNKS / kOfC, kOfC);
   if (__builtin_expect(n_cg < 4, 0)) {
     sum_few(s_cg[side][of_cg], cg_at, n_cg, q0, CHUNKS / kOfCG, kOfCG);
   } else {
-    cg.template sum<SUM>(&s_cg[side][of_cg][cg_i]);
+    cg.sum(&s_cg[side][of_cg][cg_i]);
     if (__builtin_expect(n_cg > 8 * kWave, 0)) {   // more than 32 groups
       const int i = min(4 * (q0 + 2 * kWave), n_cg - 4);
       cg.load(cg_at, n_cg, i);
-      cg.template sum<SUM>(&s_cg[side][of_cg][i]);
+      cg.sum(&s_cg[side][of_cg][i]);
     }
   }
   if (tid < 2 * kBlock) s_l[tid] = 0;
@@ -1292,7 +1300,7 @@ static hm_status swap_counts_launch(const int32_t *topk_ids, const int32_t *expe
       pp.blocks = (E + kBlock - 1) / kBlock;
       pp.status = status;
       const unsigned blocks = (unsigned)pp.blocks;
-      hipLaunchKernelGGL((!parts ? swap_pairs_kernel<int32_t, uint32_t, 1> : T <= 65535 ? swap_pairs_kernel<uint16_t, uint16_t, kCoocChunks> : swap_pairs_kernel<uint16_t, uint32_t, kCoocChunks>),
+      hipLaunchKernelGGL((!parts ? swap_pairs_kernel<int32_t, 1> : swap_pairs_kernel<uint16_t, kCoocChunks>),
                          dim3(blocks, blocks / 2 + 1, (unsigned)ncuts), dim3(kPairThreads), 0, stream, pp);
       return hm_launch_status();
     }

@@ -260,7 +260,7 @@ def test_swap_counts_at_the_lines_between_the_kernels(hw, oracle, E, K, G, ng, T
 @pytest.mark.parametrize("E,K,G,ng,T", [
     (17, 3, 4, 4, 1025), (31, 8, 35, 35, 2000), (47, 5, 40, 40, 700), (128, 8, 32, 32, 16384), (128, 8, 32, 32, 16385),   # blocks of one and of fifteen experts, more than 32 groups; a tile per chunk, two
     (256, 8, 32, 32, 12288), (256, 8, 32, 32, 12289), (200, 12, 8, 8, 12300),   # ... of 768 tokens
-    (20, 2, 4, 4, 65535), (20, 2, 4, 4, 65536),   # sums of sixteen bits, of 32
+    (20, 2, 4, 4, 65535), (20, 2, 4, 4, 65536),   # sums that sixteen bits would just hold, and that they would not
     (470, 4, 64, 64, 3000), (512, 8, 33, 33, 1000)])   # waves with tiles of C and of CG
 def test_swap_counts_at_the_edges_of_blocks_and_tiles(hw, oracle, E, K, G, ng, T):
     """Every token selects expert 0, which is alone in its group, so that its counts are as large as they can be."""

@@ -126,3 +126,16 @@ for T, H in ((16384, 1030), (4097, 1030), (3398, 1030), (3399, 1030), (16384, 20
     for T, H, K, rows, bits, name in result:
         eight = bits == 16 and rows is not None and K <= 8 and rows > max(K - 1, 4.25) and 2 * T * H >= 7e6
         assert name == "spread_ragged_kernel<RowBf16, true, %d, false>" % (8 if eight else 4) if bits == 16 else "RowF32, true, 4" in name, (T, H, K, rows, name)
+
+
+def test_chunks_of_the_swap_tables_are_summed_by_one_kernel(recorder):
+    """Whatever the number of tokens: 16-bit counts of a chunk, up to 16 of them, summed in 32 bits."""
+    result = launch_recorder.run(recorder, r"""
+result = []
+for E in (16, 128, 256):
+    for T in (0, 100, 65535, 65536, 522240):
+        rc = L.hm_swap_counts(at(1), at(2), T, 8, E, 32, 32, at(3), None, at(4), 1 << 40, None)
+        result.append([rc, [k["name"] for k in launched()]])
+""")
+    for rc, names in result:
+        assert rc == 0 and len(names) == 2 and names[1] == "swap_pairs_kernel<unsigned short, 16>", names
