@@ -242,8 +242,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 //    table is read too often.  Against kAdded 0.74 times as long up to 64 rounds, 0.5 to 0.7 beyond (16,384 x 8, four levels of 32 ranks 7.4 ->
 //    5.6), but 1.3 with 24 ids of 250,000 tokens (group counts 21 -> 35).
 //  * kAdded otherwise, unless the owners, which read a long row better than the lanes of kAdded, are faster for one or two rounds.
-//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room; 1.3 times as slow as owners where it has.
-// Of 3,500 shapes drawn anew, up to 260,000 tokens, 11 are more than 3 % slower than before there were windows and spreading, 17 % at most.
+//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room, and so none of kStagedExperts either; 1.3 times as slow
+//    as owners where it has.
+// Of 3,500 shapes drawn anew, up to 260,000 tokens, 11 are more than 3 % slower than before there were windows and spreading: nine of 64 ids, eight
+// of a few hundred tokens, 3 to 7 % (loads of 469 x 64, 74 experts 6.9 -> 7.3; groups of 673 x 64 8.2 -> 8.6; loads of 60,530 x 64 21.4 -> 22.1),
+// loads of 193,548 x 31, 1,690 experts, 27.8 -> 29.3, and loads of 90,003 x 10, 874 experts by Zipf on 64 ranks, 17.1 -> 20.0.
+static_assert(hm::kOwnerMaxE >= hm::kStagedExperts, "kAlone looks placements up in memory");
 enum class CountRoute { kAlone, kOwners, kSpread, kAdded };
 static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t outputs, int64_t blocks, bool loads, bool alone_fits) {
   if (E > hm::kOwnerMaxE) return alone_fits ? CountRoute::kAlone : CountRoute::kAdded;

@@ -33,15 +33,15 @@ __global__ __launch_bounds__(kLoadThreads) void load_clear_kernel(LoadParams p) 
   if (i == 0 && p.status) *p.status = 0;
 }
 
-// ALONE: the only workgroup; it stores the outputs instead of adding to cleared ones.
+// ALONE: the only workgroup, for tables of more experts than can be staged; it stores the outputs instead of adding to cleared ones.
 template <int THREADS, bool ALONE>
 __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
   __shared__ int32_t hist[kLdsExperts];
-  __shared__ int8_t ranks[kStagedExperts];
+  __shared__ int8_t ranks[ALONE ? 1 : kStagedExperts];
   __shared__ int32_t rank_cnt[kWave];
   __shared__ int32_t node_cnt[kWave];
   __shared__ int32_t bad;
-  const bool lds_hist = p.E <= kLdsExperts, staged = p.staged;
+  const bool lds_hist = ALONE || p.E <= kLdsExperts, staged = !ALONE && p.staged;
   const int64_t stride = (int64_t)gridDim.x * THREADS;
   int64_t t = (int64_t)blockIdx.x * THREADS + threadIdx.x;
   int id[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
@@ -220,6 +220,10 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
                        expert_blocks, rank_blocks, nodes_recip16, tokens);
     return hm_launch_status();
   }
+  if (route == CountRoute::kAlone) {
+    hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
+    return hm_launch_status();
+  }
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
   if (blocks > 1024) blocks = 1024;
   // Staging pays where a lane looks more slots up than it stages entries (us, staged / from memory: E = 4,096, 1,025 tokens, K = 1
@@ -227,10 +231,6 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   // K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).
   const int64_t lookups = blocks ? ((int64_t)T + blocks * kLoadThreads - 1) / (blocks * kLoadThreads) * K : 0;
   p.staged = E <= kStagedExperts && lookups * kLoadThreads > E;
-  if (route == CountRoute::kAlone) {
-    hipLaunchKernelGGL((load_count_kernel<kAloneTokens, true>), dim3(1), dim3(kAloneTokens), 0, stream, p);
-    return hm_launch_status();
-  }
   if (clear() != HM_OK) return HM_ERR_HIP;
   if (T == 0) return HM_OK;   // cleared outputs are the counts
   hipLaunchKernelGGL((load_count_kernel<kLoadThreads, false>), dim3((unsigned)blocks), dim3(kLoadThreads), 0, stream, p);

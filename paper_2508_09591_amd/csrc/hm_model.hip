@@ -27,15 +27,15 @@ __global__ __launch_bounds__(kGroupThreads) void group_clear_kernel(GroupParams 
 // accumulates the popcount of the ballot over bit j (a token counts once per group).  What it waits for
 // is the chain ids -> placement -> counts: a token's ids are loaded together, while the placement is
 // staged in LDS (T=8192, K=8, four levels, kernel trace: 9.6 -> 6.2 us; it was one id after the other,
-// each with its look-up in memory).  ALONE: the only workgroup (up to kAloneTokens tokens);
-// it stores the counts instead of adding to cleared ones, which saves the clearing launch.
+// each with its look-up in memory).  ALONE: the only workgroup (up to kAloneTokens tokens and
+// more experts than can be staged); it stores the counts instead of adding to cleared ones, which saves the clearing launch.
 constexpr int kAloneTokens = 1024;
 template <int THREADS, bool ALONE>
 __global__ __launch_bounds__(THREADS) void group_count_kernel(GroupParams p) {
   __shared__ int32_t block_cnt[kMaxDepth * kWave];
-  __shared__ int8_t ranks[kStagedExperts];
+  __shared__ int8_t ranks[ALONE ? 1 : kStagedExperts];
   __shared__ int32_t bad;
-  const bool staged = p.E <= kStagedExperts;
+  const bool staged = !ALONE && p.E <= kStagedExperts;
   const int64_t stride = (int64_t)gridDim.x * THREADS;
   int64_t t = (int64_t)blockIdx.x * THREADS + threadIdx.x;
   int id[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
@@ -219,7 +219,7 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
     blocks += (groups[l] + kOwnerGroups - 1) / kOwnerGroups;
   }
   // one workgroup that looks many slots up in memory is slower than several (E = 5,000, 1,024 tokens, K = 64: 32.4 us, 19.8)
-  const bool alone_fits = T <= kAloneTokens && (E <= kStagedExperts || (int64_t)T * K <= 32768);
+  const bool alone_fits = T <= kAloneTokens && (int64_t)T * K <= 32768;
   const CountRoute route = count_route(T, K, E, outputs, blocks, false, alone_fits);
   if (route == CountRoute::kOwners || route == CountRoute::kSpread) {
     const bool spread = route == CountRoute::kSpread;
