@@ -1,5 +1,5 @@
-// Where the tiles of swap_cooc_kernel lie in its dynamic LDS, and which of them a wave multiplies.  Plain arithmetic of host and
-// device, apart from the kernel so that a host test can walk every shape.
+// Where the tiles of swap_cooc_kernel lie in its dynamic LDS, and which of them a wave multiplies.  Plain arithmetic of
+// host and device, apart from the kernel so that a host test can walk every shape.
 #pragma once
 
 namespace hm {
@@ -10,9 +10,9 @@ constexpr int kCoocPartMaxE = 256;  // experts up to which the workspace holds p
 // Tile columns of a panel of C.
 constexpr int cooc_columns(int E) { return E > 128 && E <= kCoocPartMaxE ? 2 : 1; }
 
-// Tiles of 32 rows, one behind the other: A (all experts), S (the panel's COLS tiles), M (the cut's groups, one tile or two).
-// A wave w has a row of C's tiles, its A tile by all of the panel's S tiles, or, from the last wave down, a tile of the panel's CG,
-// an S tile by one M tile; with more than 448 experts and one column the last waves have both.
+// Tiles of 32 rows, one behind the other: A (all experts), S (the panel's COLS tiles), M (the cut's groups, one tile or
+// two). A wave w has a row of C's tiles, its A tile by all of the panel's S tiles, or, from the last wave down, a tile
+// of the panel's CG, an S tile by one M tile; with more than 448 experts and one column the last waves have both.
 template <int COLS>
 struct CoocTiles {
   static constexpr int kColumnsOfC = COLS, kColumnsOfG = 1;   // tiles that a row tile is multiplied by

@@ -82,10 +82,10 @@ __device__ __forceinline__ int lane_scan(int v) {
 // ---- counts by owners ----------------------------------------------------------------------------------
 // Counts of a routing table in one launch without cleared outputs: a workgroup owns a few outputs (seven groups, or
 // some experts), goes through all the tokens and stores its counts.  The workgroups read the same table, so this is for
-// tables of a few hundred KB; beyond that each should read a part of it once and add atomically to cleared outputs.
-// A round of 1,024 tokens of eight ids, one token per lane, is bound by the CU's path to the caches (32 KB, 0.2 us), its lookups in LDS
-// and the instructions of sixteen waves, of which there are few per id; what comes before and behind the rounds by its
-// code, which runs once and cold.
+// tables of a few hundred KB; beyond that each should read a part of it once and add atomically to cleared outputs. A
+// round of 1,024 tokens of eight ids, one token per lane, is bound by the CU's path to the caches (32 KB, 0.2 us), its
+// lookups in LDS and the instructions of sixteen waves, of which there are few per id; what comes before and behind the
+// rounds by its code, which runs once and cold.
 constexpr int kOwnerThreads = 1024;   // = tokens of a round
 constexpr int kOwnerWaves = kOwnerThreads / kWave;
 constexpr int kOwnerGroups = 7;       // groups of a workgroup: the bits of a byte, but for the one that marks an error
@@ -93,13 +93,15 @@ constexpr int kOwnerRounds = 63;      // most rounds: a workgroup's sums are add
 constexpr int kOwnerExperts = 64;     // experts of a workgroup
 constexpr int kOwnerMaxE = 4096;      // experts whose groups fit the LDS table
 
-// Ids of a token that a lane loads together: two windows of W, 4 from four slots on, 2 for two and three, 1 (and the same again) for one.
+// Ids of a token that a lane loads together: two windows of W, 4 from four slots on, 2 for two and three, 1 (and the
+// same again) for one.
 static inline int owner_width(int K) { return K >= 4 ? 4 : K >= 2 ? 2 : 1; }
 
-// count(id, seen) for every batch of up to eight ids of this lane's tokens, end() behind the last of a token.  The second window of a short
-// token and the last batch of a long one overlap what was there before: `seen` (uniform) of the first 2 W places and, from 8 on,
-// of the second window's, hold ids that have been counted.  Lanes without a token have the last one's ids; count and end are told
-// whether they do.  The next batch is on its way meanwhile; prepare() runs while the first is.
+// count(id, seen) for every batch of up to eight ids of this lane's tokens, end() behind the last of a token.  The
+// second window of a short token and the last batch of a long one overlap what was there before: `seen` (uniform) of
+// the first 2 W places and, from 8 on, of the second window's, hold ids that have been counted.  Lanes without a token
+// have the last one's ids; count and end are told whether they do.  The next batch is on its way meanwhile; prepare()
+// runs while the first is.
 template <int W, typename PREPARE, typename COUNT, typename END>
 __device__ __forceinline__ void for_ids(const int32_t *__restrict__ ids, int T, int K, PREPARE prepare, COUNT count, END end) {
   const int batches = W == 4 ? (K + 7) >> 3 : 1, steps = (T + kOwnerThreads - 1) / kOwnerThreads * batches;
@@ -141,12 +143,12 @@ __device__ __forceinline__ void for_ids(const int32_t *__restrict__ ids, int T, 
   }
 }
 
-// Tokens with a copy in groups [first, first + 7) of ranks that r -> (r per_recip16) >> 16 puts together: returned to lane g of the first
-// wave, in lane 7 the tokens with an invalid id or placement.  The table holds one bit per group an expert may be in, so a
-// token's groups are the `or` of its entries; a lane keeps its counts as bytes.
+// Tokens with a copy in groups [first, first + 7) of ranks that r -> (r per_recip16) >> 16 puts together: returned to
+// lane g of the first wave, in lane 7 the tokens with an invalid id or placement.  The table holds one bit per group an
+// expert may be in, so a token's groups are the `or` of its entries; a lane keeps its counts as bytes.
 template <int W>
-__device__ __forceinline__ int count_owned_groups(const int32_t *__restrict__ ids, const int32_t *__restrict__ expert_to_rank, int T, int K, int E,
-                                                  int G, uint32_t per_recip16, int first, uint8_t *table) {
+__device__ __forceinline__ int count_owned_groups(const int32_t *__restrict__ ids, const int32_t *__restrict__ expert_to_rank,
+                                                  int T, int K, int E, int G, uint32_t per_recip16, int first, uint8_t *table) {
   __shared__ u32x4 sums[kOwnerWaves];
   uint32_t low = 0, high = 0, mask = 0;
   for_ids<W>(ids, T, K, [&] {   // entry 0 is that of id -1, E + 1 of ids out of range
@@ -190,8 +192,8 @@ __device__ __forceinline__ int count_owned_groups(const int32_t *__restrict__ id
   return (__shfl(v, (g >> 1 & 2) + (g & 1), kWave) >> (g & 2 ? 16 : 0)) & 0xFFFF;
 }
 
-// The tokens of a workgroup: all, or, where a larger table is spread over workgroups that add to cleared outputs, `share` of them
-// from blockIdx.y on.
+// The tokens of a workgroup: all, or, where a larger table is spread over workgroups that add to cleared outputs,
+// `share` of them from blockIdx.y on.
 struct OwnerTokens {
   const int32_t *ids;
   int T;
@@ -230,23 +232,27 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 }  // namespace hm
 
-// Which kernel takes the counts of a table (hm_expert_load, hm_group_counts); outputs: the groups of all levels, or ranks and nodes;
-// blocks: the workgroups that own them.  All figures: graphs of ten calls; lines through 4,000 shapes of 16 to 65,536 and 2,500 of 512 to a
-// million tokens, one to 64 ids, 2 to 2,048 experts, even and Zipf ids, dropped slots.
-//  * kOwners, one launch, for few rounds of 1,024 tokens.  A round costs 0.2 us with one id per token, 0.25 with two or three, 0.45
-//    with four to seven (two loads that overlap), 0.36 with eight, as much per eight of more, and twice that where a token's row is 100
-//    bytes or more, whose lines no two lanes share.  Loads of 8,192 x 8, 128 experts on 32 ranks 5.9 us (kAdded 7.7), group counts with four
-//    levels of 32 ranks 6.3 (8.1).
-//  * kSpread: the owners' work on a part of the tokens each, as few rounds as fill the chip once, added to outputs that a launch before
-//    clears: where that is a us faster, as a launch costs the host more, and for up to sixteen ids and 12 us of rounds: beyond, every
-//    table is read too often.  Against kAdded 0.74 times as long up to 64 rounds, 0.5 to 0.7 beyond (16,384 x 8, four levels of 32 ranks 7.4 ->
-//    5.6), but 1.3 with 24 ids of 250,000 tokens (group counts 21 -> 35).
-//  * kAdded otherwise, unless the owners, which read a long row better than the lanes of kAdded, are faster for one or two rounds.
-//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room, and so none of kStagedExperts either; 1.3 times as slow
-//    as owners where it has.
-// Of 3,500 shapes drawn anew, up to 260,000 tokens, 11 are more than 3 % slower than before there were windows and spreading: nine of 64 ids, eight
-// of a few hundred tokens, 3 to 7 % (loads of 469 x 64, 74 experts 6.9 -> 7.3; groups of 673 x 64 8.2 -> 8.6; loads of 60,530 x 64 21.4 -> 22.1),
-// loads of 193,548 x 31, 1,690 experts, 27.8 -> 29.3, and loads of 90,003 x 10, 874 experts by Zipf on 64 ranks, 17.1 -> 20.0.
+// Which kernel takes the counts of a table (hm_expert_load, hm_group_counts); outputs: the groups of all levels, or
+// ranks and nodes; blocks: the workgroups that own them.  All figures: graphs of ten calls; lines through 4,000 shapes
+// of 16 to 65,536 and 2,500 of 512 to a million tokens, one to 64 ids, 2 to 2,048 experts, even and Zipf ids, dropped
+// slots.
+//  * kOwners, one launch, for few rounds of 1,024 tokens.  A round costs 0.2 us with one id per token, 0.25 with two or
+//    three, 0.45 with four to seven (two loads that overlap), 0.36 with eight, as much per eight of more, and twice
+//    that where a token's row is 100 bytes or more, whose lines no two lanes share.  Loads of 8,192 x 8, 128 experts on
+//    32 ranks 5.9 us (kAdded 7.7), group counts with four levels of 32 ranks 6.3 (8.1).
+//  * kSpread: the owners' work on a part of the tokens each, as few rounds as fill the chip once, added to outputs that
+//    a launch before clears: where that is a us faster, as a launch costs the host more, and for up to sixteen ids and
+//    12 us of rounds: beyond, every table is read too often.  Against kAdded 0.74 times as long up to 64 rounds, 0.5 to
+//    0.7 beyond (16,384 x 8, four levels of 32 ranks 7.4 -> 5.6), but 1.3 with 24 ids of 250,000 tokens (group counts
+//    21 -> 35).
+//  * kAdded otherwise, unless the owners, which read a long row better than the lanes of kAdded, are faster for one or
+//    two rounds.
+//  * kAlone, one workgroup, as far as it goes, where the owners' table has no room, and so none of kStagedExperts
+//    either; 1.3 times as slow as owners where it has.
+// Of 3,500 shapes drawn anew, up to 260,000 tokens, 11 are more than 3 % slower than before there were windows and
+// spreading: nine of 64 ids, eight of a few hundred tokens, 3 to 7 % (loads of 469 x 64, 74 experts 6.9 -> 7.3; groups
+// of 673 x 64 8.2 -> 8.6; loads of 60,530 x 64 21.4 -> 22.1), loads of 193,548 x 31, 1,690 experts, 27.8 -> 29.3, and
+// loads of 90,003 x 10, 874 experts by Zipf on 64 ranks, 17.1 -> 20.0.
 static_assert(hm::kOwnerMaxE >= hm::kStagedExperts, "kAlone looks placements up in memory");
 enum class CountRoute { kAlone, kOwners, kSpread, kAdded };
 static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t outputs, int64_t blocks, bool loads, bool alone_fits) {
@@ -255,7 +261,8 @@ static inline CountRoute count_route(int64_t T, int64_t K, int64_t E, int64_t ou
   const int64_t step = K == 1 ? 20 : K <= 3 ? 25 : K < 8 ? 45 : K == 8 ? 36 : K <= 24 ? 43 : 85;   // hundredths of a us, as all below
   const int64_t owners = 295 + step * batches * rounds + E / 50 + outputs / 5;
   const int64_t share = step * batches * (hm::spread_tokens(T, blocks) / hm::kOwnerThreads);
-  if (K <= 16 && share <= 1200) return rounds <= hm::kOwnerRounds && owners <= 585 + share * 11 / 10 ? CountRoute::kOwners : CountRoute::kSpread;
+  if (K <= 16 && share <= 1200)
+    return rounds <= hm::kOwnerRounds && owners <= 585 + share * 11 / 10 ? CountRoute::kOwners : CountRoute::kSpread;
   const int64_t tokens = T < 65536 ? T : 65536;
   const int64_t added = loads ? 520 + 15 * K + outputs * 24 / 10 + E * 8 / 100 + tokens * 56 / 10000
                               : 525 + 9 * K + outputs * 35 / 10 + E * 4 / 100 + tokens * 40 / 10000;

@@ -1,14 +1,14 @@
-// hm_expert_load: per-expert slot counts and duplicate-free per-rank / per-node token counts
-// (the p^(1,G) and p^(1,U[1]) vectors of HierMoE Eq.(7)) for the expert-swap planner of Section IV.
+// hm_expert_load: per-expert slot counts and duplicate-free per-rank / per-node token counts (the p^(1,G) and
+// p^(1,U[1]) vectors of HierMoE Eq.(7)) for the expert-swap planner of Section IV.
 //
-// Small tables are one launch: workgroups that own a few outputs each go through all the tokens (load_owner_kernel; kernel
-// trace, 8,192 x 8, 128 experts on 32 ranks: 5.2 us, 6.4 with a branch per id and a place for every four lanes).  Larger ones: one lane per token, expert counts
-// in an LDS histogram, rank and node counts from ballots over the per-token rank masks (lane g accumulates the
-// popcount for group g), so a token is counted once per group however many of its experts live there; a tiny launch clears
-// the outputs and integer atomics merge the workgroups, which keeps the result exact and order-independent.  The ids of a
-// token are loaded together, while the placement is staged in LDS.  Tried there and slower: the masks of ranks and
-// nodes as one 64-bit word per expert in LDS and the counts by turning the wave's 64 x 64 bits round (6.6 us against 5.7:
-// more code to fetch, and the ballots are not what it waits for).
+// Small tables are one launch: workgroups that own a few outputs each go through all the tokens (load_owner_kernel;
+// kernel trace, 8,192 x 8, 128 experts on 32 ranks: 5.2 us, 6.4 with a branch per id and a place for every four lanes).
+// Larger ones: one lane per token, expert counts in an LDS histogram, rank and node counts from ballots over the
+// per-token rank masks (lane g accumulates the popcount for group g), so a token is counted once per group however many
+// of its experts live there; a tiny launch clears the outputs and integer atomics merge the workgroups, which keeps the
+// result exact and order-independent.  The ids of a token are loaded together, while the placement is staged in LDS.
+// Tried there and slower: the masks of ranks and nodes as one 64-bit word per expert in LDS and the counts by turning
+// the wave's 64 x 64 bits round (6.6 us against 5.7: more code to fetch, and the ballots are not what it waits for).
 #include "hm_device.h"
 
 namespace hm {
@@ -33,7 +33,8 @@ __global__ __launch_bounds__(kLoadThreads) void load_clear_kernel(LoadParams p) 
   if (i == 0 && p.status) *p.status = 0;
 }
 
-// ALONE: the only workgroup, for tables of more experts than can be staged; it stores the outputs instead of adding to cleared ones.
+// ALONE: the only workgroup, for tables of more experts than can be staged; it stores the outputs instead of adding to
+// cleared ones.
 template <int THREADS, bool ALONE>
 __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
   __shared__ int32_t hist[kLdsExperts];
@@ -113,9 +114,11 @@ __global__ __launch_bounds__(THREADS) void load_count_kernel(LoadParams p) {
 // Workgroups [0, expert_blocks) own kOwnerExperts experts each, the next ones seven ranks each, the last ones seven nodes
 // each; SPREAD: for a part of the tokens, added to cleared outputs.
 template <int W, bool SPREAD>
-__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks, uint32_t nodes_recip16, int tokens) {
+__global__ __launch_bounds__(kOwnerThreads) void load_owner_kernel(LoadParams p, int expert_blocks, int rank_blocks,
+                                                                   uint32_t nodes_recip16, int tokens) {
   __shared__ uint8_t table[kOwnerMaxE + 2];
-  __shared__ __align__(16) uint32_t cnt[kOwnerExperts + 1][kWave];   // a place per lane of a wave, so that no two lanes meet; the last row: not ours
+  // A place per lane of a wave, so that no two lanes meet; the last row: not ours.
+  __shared__ __align__(16) uint32_t cnt[kOwnerExperts + 1][kWave];
   int block = (int)blockIdx.x;
   const OwnerTokens t = owner_tokens<SPREAD>(p.ids, p.T, p.K, tokens);
   if (block < expert_blocks) {   // an id is counted whether its expert's placement is valid or not, and stored if it is
@@ -214,10 +217,13 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
     const uint32_t nodes_recip16 = (uint32_t)((65536 + p.R - 1) / p.R);   // exact for ranks (below 64)
     const int width = owner_width(K), tokens = spread ? spread_tokens(T, owner_blocks) : T;
     if (spread && clear() != HM_OK) return HM_ERR_HIP;
-    const auto kernel = spread ? (width == 4 ? load_owner_kernel<4, true> : width == 2 ? load_owner_kernel<2, true> : load_owner_kernel<1, true>)
-                               : (width == 4 ? load_owner_kernel<4, false> : width == 2 ? load_owner_kernel<2, false> : load_owner_kernel<1, false>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)owner_blocks, spread ? (unsigned)((T + tokens - 1) / tokens) : 1u), dim3(kOwnerThreads), 0, stream, p,
-                       expert_blocks, rank_blocks, nodes_recip16, tokens);
+    const auto whole = width == 4   ? load_owner_kernel<4, false>
+                       : width == 2 ? load_owner_kernel<2, false>
+                                    : load_owner_kernel<1, false>;
+    const auto parts = width == 4 ? load_owner_kernel<4, true> : width == 2 ? load_owner_kernel<2, true> : load_owner_kernel<1, true>;
+    const dim3 grid((unsigned)owner_blocks, spread ? (unsigned)((T + tokens - 1) / tokens) : 1u);
+    hipLaunchKernelGGL((spread ? parts : whole), grid, dim3(kOwnerThreads), 0, stream, p, expert_blocks, rank_blocks, nodes_recip16,
+                       tokens);
     return hm_launch_status();
   }
   if (route == CountRoute::kAlone) {
@@ -226,9 +232,9 @@ extern "C" hm_status hm_expert_load(const int32_t *topk_ids, const int32_t *expe
   }
   int64_t blocks = ((int64_t)T + kLoadThreads - 1) / kLoadThreads;
   if (blocks > 1024) blocks = 1024;
-  // Staging pays where a lane looks more slots up than it stages entries (us, staged / from memory: E = 4,096, 1,025 tokens, K = 1
-  // 10.1 / 7.9, K = 8 10.4 / 9.4, K = 16 11.7 / 11.4; E = 2,048, K = 16 9.9 / 10.4; 300,000 tokens, two per lane, E = 2,048,
-  // K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).
+  // Staging pays where a lane looks more slots up than it stages entries (us, staged / from memory: E = 4,096, 1,025
+  // tokens, K = 1 10.1 / 7.9, K = 8 10.4 / 9.4, K = 16 11.7 / 11.4; E = 2,048, K = 16 9.9 / 10.4; 300,000 tokens, two
+  // per lane, E = 2,048, K = 8 30.4 / 33.4, E = 4,096, K = 16 40.0 / 44.0).
   const int64_t lookups = blocks ? ((int64_t)T + blocks * kLoadThreads - 1) / (blocks * kLoadThreads) * K : 0;
   p.staged = E <= kStagedExperts && lookups * kLoadThreads > E;
   if (clear() != HM_OK) return HM_ERR_HIP;

@@ -118,7 +118,8 @@ __global__ __launch_bounds__(kOwnerThreads) void group_owner_kernel(GroupParams 
     return;
   }
   // the last owner of a level clears what is behind its groups
-  if (i < kWave && (lane < kOwnerGroups || first + kOwnerGroups >= n)) p.counts[level * kWave + i] = lane < kOwnerGroups && i < n ? count : 0;
+  if (i < kWave && (lane < kOwnerGroups || first + kOwnerGroups >= n))
+    p.counts[level * kWave + i] = lane < kOwnerGroups && i < n ? count : 0;
   if (blockIdx.x == 0 && lane == kOwnerGroups && p.status) *p.status = count ? HM_ERR_BAD_ID : 0;
 }
 
@@ -236,9 +237,13 @@ extern "C" hm_status hm_group_counts(const int32_t *topk_ids, const int32_t *exp
     }
     const dim3 grid((unsigned)blocks, spread ? (unsigned)((T + o.tokens - 1) / o.tokens) : 1u);
     const int width = owner_width(K);
-    const auto kernel = spread ? (width == 4 ? group_owner_kernel<4, true> : width == 2 ? group_owner_kernel<2, true> : group_owner_kernel<1, true>)
-                               : (width == 4 ? group_owner_kernel<4, false> : width == 2 ? group_owner_kernel<2, false> : group_owner_kernel<1, false>);
-    hipLaunchKernelGGL(kernel, grid, dim3(kOwnerThreads), 0, stream, p, o);
+    const auto whole = width == 4   ? group_owner_kernel<4, false>
+                       : width == 2 ? group_owner_kernel<2, false>
+                                    : group_owner_kernel<1, false>;
+    const auto parts = width == 4   ? group_owner_kernel<4, true>
+                       : width == 2 ? group_owner_kernel<2, true>
+                                    : group_owner_kernel<1, true>;
+    hipLaunchKernelGGL((spread ? parts : whole), grid, dim3(kOwnerThreads), 0, stream, p, o);
     return hm_launch_status();
   }
   if (route == CountRoute::kAlone) {

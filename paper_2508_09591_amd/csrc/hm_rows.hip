@@ -73,11 +73,14 @@ __device__ __forceinline__ int64_t divided(int64_t n, uint64_t recip) {
   return recip ? (int64_t)__umul64hi((uint64_t)n, recip) : n;
 }
 
-// The workgroup's place among the others: as launched, or (NEAR) in groups of 128 neighbours that run on one die, the groups going round the
-// dies; a short last round is as launched.  Workgroups go round the eight dies, and each die has an L2 of its own: where rows begin inside a
-// line, the line that two workgroups share is written from two dies, twice and in part.  Those lines are what ragged rows lose: 4,097 x 1,030,
-// six rows per token, dispatch 15.2 us, 11.8 when the shared lines are left out, 14.3 grouped; 15.2 -> 19.5 when they are written through the
-// caches.  near_pays() says where the grouping is used.
+// The workgroup's place among the others: as launched, or (NEAR) in groups of 128 neighbours that run on one die, the
+// groups going round the dies; a short last round is as launched.  Workgroups go round the eight dies, and each die has
+// an L2 of its own: where rows begin inside a line, the line that two workgroups share is written from two dies, twice
+// and in part.  Those lines are what ragged rows lose: 4,097 x 1,030, six rows per token, dispatch 15.2 us, 11.8 when
+// the shared lines are left out, 14.3 grouped; 15.2 -> 19.5 when they are written through the caches.  Counters of that
+// layer, as launched -> grouped: 791,000 write requests to memory both ways, those of less than 64 bytes 21,200 ->
+// 8,700; bytes read, as neighbours share the lines they read too, 1.25 -> 1.02 times the tokens'.  near_pays() says
+// where the grouping is used.
 constexpr unsigned kDies = 8, kNear = 128;
 template <bool NEAR>
 __device__ __forceinline__ unsigned block_place() {
@@ -389,12 +392,12 @@ __global__ __launch_bounds__(kCombineThreads) void combine_rows_kernel(RowParams
   }
 }
 
-// The same for tokens of two rows or more: a wave owns 1 KiB of the row, like combine_plan_rows_kernel, and goes by slots, eight
-// at a time.  What bounds the call is the rows on their way, so a row's load is issued as soon as its slot is known to be
-// the first with it, and the weights are merged behind the loads.  HIP events, three to sixteen pairs of buffers in turn, segments
-// of 4 KiB with the weights first -> now (the plan's weights), us: 16,384 x 2,048 fp32 with 7 rows 192 -> 183 (180), 8,192 x 7,168
-// with 3.1 rows 79.3 -> 75.9 (74.9), 8,192 x 2,048 with 7.4 49.9 -> 48.1 (47.6), 1,024 x 2,048 9.6 -> 8.2 (7.9), 256 x 4,096 7.7 -> 5.6
-// (5.3).
+// The same for tokens of two rows or more: a wave owns 1 KiB of the row, like combine_plan_rows_kernel, and goes by
+// slots, eight at a time.  What bounds the call is the rows on their way, so a row's load is issued as soon as its slot
+// is known to be the first with it, and the weights are merged behind the loads.  HIP events, three to sixteen pairs of
+// buffers in turn, segments of 4 KiB with the weights first -> now (the plan's weights), us: 16,384 x 2,048 fp32 with 7
+// rows 192 -> 183 (180), 8,192 x 7,168 with 3.1 rows 79.3 -> 75.9 (74.9), 8,192 x 2,048 with 7.4 49.9 -> 48.1 (47.6),
+// 1,024 x 2,048 9.6 -> 8.2 (7.9), 256 x 4,096 7.7 -> 5.6 (5.3).
 template <bool MIX, typename ROW, typename ACCESS>
 __global__ __launch_bounds__(kCombineThreads) void combine_slots_kernel(RowParams p, const typename ROW::elem *__restrict__ y,
                                                                         int64_t y_rows, const float *__restrict__ topk_weights,
@@ -617,15 +620,16 @@ __global__ __launch_bounds__(kCopyThreads) void transpose_rows_kernel(RowParams 
   }
 }
 
-// Dispatch (SCALED = false: a bit copy) and transpose of ragged rows.  The rows written start at
-// different places of a line, so the vectors of the token differ from row to row: each is read again,
-// from the caches, at the place its row asks for; the reads of R rows are in flight together.
-// Measured (8,192 / 16,384 tokens, bf16, HIP events, against vectors counted from the row's start): 7.3
-// copies of 2,051 elements 162 -> 123 us (4.5 TB/s), of 1,032 92 -> 76 us, of 7,160 251 -> 223 us; 3.6 copies of
-// 4,140 68 -> 50 us.  Splitting a row evenly over its waves (no line grid) loses more than the last,
-// short segment costs: 4,160 elements 218 -> 301 us; giving that segment to the wave before it changes nothing.
-// R: rows whose reads are in flight together, eight where eight_reads_pay() says so, else four (dispatch and fp32: equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each row's vectors from
-// there (4,097 x 1,030, six rows: dispatch 15.2 -> 15.9, transpose 15.9 -> 16.8: the reads are not what it waits for).
+// Dispatch (SCALED = false: a bit copy) and transpose of ragged rows.  The rows written start at different places of a
+// line, so the vectors of the token differ from row to row: each is read again, from the caches, at the place its row
+// asks for; the reads of R rows are in flight together. Measured (8,192 / 16,384 tokens, bf16, HIP events, against
+// vectors counted from the row's start): 7.3 copies of 2,051 elements 162 -> 123 us (4.5 TB/s), of 1,032 92 -> 76 us,
+// of 7,160 251 -> 223 us; 3.6 copies of 4,140 68 -> 50 us.  Splitting a row evenly over its waves (no line grid) loses
+// more than the last, short segment costs: 4,160 elements 218 -> 301 us; giving that segment to the wave before it
+// changes nothing. R: rows whose reads are in flight together, eight where eight_reads_pay() says so, else four
+// (dispatch and fp32: equal).  Tried: the wave's piece of the token in LDS, read once ahead of the row list, and each
+// row's vectors from there (4,097 x 1,030, six rows: dispatch 15.2 -> 15.9, transpose 15.9 -> 16.8: the reads are not
+// what it waits for).
 template <typename ROW, bool SCALED, int R, bool NEAR>
 __global__ __launch_bounds__(kCopyThreads) void spread_ragged_kernel(RowParams p, const typename ROW::elem *__restrict__ in,
                                                                      const float *__restrict__ row_weight, int64_t rows,
@@ -729,10 +733,11 @@ __device__ __forceinline__ void owned_rows(const RowParams &p, int t, int k0, in
   }
 }
 
-// fn(N, k0) over the K slots in pieces of eight and, WHOLE, the rest in one: a piece is a chain of trips to memory, its list, then its
-// rows or weights.  Else the rest goes in pieces of four and one, which a dispatch, whose stores wait for nothing, prefers by 0.1 us.
-// Combine, plan's weights, rest in pieces of four and one -> in one: 16,384 x 64, K = 7 8.2 -> 6.1 us, x 128, K = 3 7.5 -> 5.8, 4,096 x
-// 256, K = 6 7.0 -> 5.5, 8,192 x 1,030, K = 6 26.1 -> 23.6; bf16 transpose of 16,384 x 64, K = 7 7.0 -> 6.4.
+// fn(N, k0) over the K slots in pieces of eight and, WHOLE, the rest in one: a piece is a chain of trips to memory, its
+// list, then its rows or weights.  Else the rest goes in pieces of four and one, which a dispatch, whose stores wait
+// for nothing, prefers by 0.1 us. Combine, plan's weights, rest in pieces of four and one -> in one: 16,384 x 64, K = 7
+// 8.2 -> 6.1 us, x 128, K = 3 7.5 -> 5.8, 4,096 x 256, K = 6 7.0 -> 5.5, 8,192 x 1,030, K = 6 26.1 -> 23.6; bf16
+// transpose of 16,384 x 64, K = 7 7.0 -> 6.4.
 template <bool WHOLE, typename FN>
 __device__ __forceinline__ void for_slots(int K, FN fn) {
   int k0 = 0;
@@ -934,20 +939,22 @@ static inline int dispatch_waves_per_cu(const hm_plan_out *plan, int32_t T, int3
   return many && (int64_t)T * H * 2 <= (256ll << 20) ? 12 : kCopyWavesPerCu;
 }
 
-// Whether the fp32 transpose of rows cut by WholeRows keeps dispatch's 24 waves per CU.  A wave waits once
-// more than dispatch does (for the row's weight, behind its index), which more waves hide, but more waves also
-// queue more stores.  HIP events, graphs of ten calls, both forms in turn over two to ten pairs of buffers (one pair
-// alone leaves gradients of up to 256 MB in the Infinity Cache, and capped is then up to 2 % better at many rows),
-// capped -> uncapped in us; runs of one form differ by 0.5 %:
+// Whether the fp32 transpose of rows cut by WholeRows keeps dispatch's 24 waves per CU.  A wave waits once more than
+// dispatch does (for the row's weight, behind its index), which more waves hide, but more waves also queue more stores.
+// HIP events, graphs of ten calls, both forms in turn over two to ten pairs of buffers (one pair alone leaves gradients
+// of up to 256 MB in the Infinity Cache, and capped is then up to 2 % better at many rows), capped -> uncapped in us;
+// runs of one form differ by 0.5 %:
 //   about one row per token: uncapped 7 to 11 % faster (8,192 x 2,048 28.4 -> 26.4, 65,536 x 2,048 202 -> 182, 65,536 x
 //     7,168 680 -> 623);
-//   two rows: capped (16,384 x 2,048 69.1 -> 69.9, 65,536 x 2,048 268 -> 274, 16,384 x 7,168 232 -> 243, 65,536 x 7,168 915 -> 977);
-//   three or four rows: uncapped (8,192 x 2,048 52.6 -> 52.1, 65,536 x 2,048 403 -> 392, 65,536 x 4,096 800 -> 780, 32,768 x
+//   two rows: capped (16,384 x 2,048 69.1 -> 69.9, 65,536 x 2,048 268 -> 274, 16,384 x 7,168 232 -> 243, 65,536 x 7,168
+//   915 -> 977); three or four rows: uncapped (8,192 x 2,048 52.6 -> 52.1, 65,536 x 2,048 403 -> 392, 65,536 x 4,096
+//   800 -> 780, 32,768 x
 //     7,168 615 -> 609; 8,192 x 7,168 alone 154 -> 156);
-//   seven rows: uncapped (16,384 x 2,048 194 -> 188, 32,768 x 2,048 397 -> 381, 32,768 x 4,096 806 -> 754, 65,536 x 2,048 844 ->
-//     803, 16,384 x 7,168 726 -> 705), but capped for gradients of up to 96 MB (8,192 x 1,024 51.4 -> 53.9, 8,192 x 2,048 101.4 ->
-//     104.6, 4,096 x 4,096 101.1 -> 103.7) or of more than 0.75 GB (32,768 x 7,168 1,509 -> 1,567, 65,536 x 7,168 2,992 -> 3,149;
-//     65,536 x 4,096 1,661 -> 1,637).
+//   seven rows: uncapped (16,384 x 2,048 194 -> 188, 32,768 x 2,048 397 -> 381, 32,768 x 4,096 806 -> 754, 65,536 x
+//   2,048 844 ->
+//     803, 16,384 x 7,168 726 -> 705), but capped for gradients of up to 96 MB (8,192 x 1,024 51.4 -> 53.9, 8,192 x
+//     2,048 101.4 -> 104.6, 4,096 x 4,096 101.1 -> 103.7) or of more than 0.75 GB (32,768 x 7,168 1,509 -> 1,567,
+//     65,536 x 7,168 2,992 -> 3,149; 65,536 x 4,096 1,661 -> 1,637).
 // Rows that begin inside a line (lines = false), whose edges are written in part: capped from two rows per token on.
 static inline bool transpose_capped(const hm_plan_out *plan, int32_t T, int32_t H, bool lines) {
   const double c = rows_per_token(plan, T), in = (double)T * H * 4;
@@ -1044,71 +1051,73 @@ static inline bool in_vectors(const RowForm &f) { return f.H * (int64_t)f.elem_b
 // tokens, K = 1, 16 bf16: 3.2 -> 2.7).
 constexpr int kFlatTokens = 4096;
 
-// Whether the dispatch groups its workgroups by die: rows that begin inside a line, of up to 80 MB of tokens, 130 MB if the rows are narrow.
-// How many rows a token has does not matter, so a plan that was never synchronised is as well off as one that was.
-// Grouping helps a dispatch that is bound by its writes: tokens that the Infinity Cache (256 MB) still holds, as a layer's output that has just
-// been written, or short rows, a large part of which is shared lines.
-// HIP events, dispatch and a combine that reads a buffer of its own, as launched -> grouped in turn, geometric means of the dispatch
-// alone over 2,200 shapes drawn (2,000 to 262,144 tokens, one to ten slots, 0.2 to ten rows per token), three to eight passes in turn / so many that no
-// token is still cached:
+// Whether the dispatch groups its workgroups by die: rows that begin inside a line, of up to 80 MB of tokens, 130 MB if
+// the rows are narrow. How many rows a token has does not matter, so a plan that was never synchronised is as well off
+// as one that was. Grouping helps a dispatch that is bound by its writes: tokens that the Infinity Cache (256 MB) still
+// holds, as a layer's output that has just been written, or short rows, a large part of which is shared lines. HIP
+// events, dispatch and a combine that reads a buffer of its own, as launched -> grouped in turn, geometric means of the
+// dispatch alone over 2,200 shapes drawn (2,000 to 262,144 tokens, one to ten slots, 0.2 to ten rows per token), three
+// to eight passes in turn / so many that no token is still cached:
 //   128 to 1,400 bytes, up to 30 MB   +1 to +12 % / 0 to +8 %     30 to 80 MB   +2 to +13 % / 0 to +8 %     80 to 130 MB   +1 to +6 % / 0 to +9 %
 //   wider rows, up to 30 MB           +2 to +6 % / -2 to +2 %     30 to 80 MB   +1 to +9 % / -2 to 0 %      more           -3 to +1 % / -5 to +2 %
-// 65,536 x 136 with 3.3 rows 22.4 -> 18.4, 4.5 29.2 -> 22.0, 7.6 58.0 -> 48.8; 4,097 x 1,030 with 5.8 15.2 -> 14.3; 16,384 x 520 with 5.4
-// 27.3 -> 23.6; but 8,192 x 7,161 with 3.3 108.7 -> 111.9, 75,791 x 1,039 163 -> 174.
-// A combine that reads the very rows that dispatch has just written, with nothing between, finds fewer of them on its own die: 65,536 x 72
-// with one row 11.6 -> 14.1 for both.  The transpose keeps the launch order (16,384 x 2,050 with 7.7 rows and its combine 227.5 ->
-// 229.7), and so do whole lines, of which neighbours share none (8,192 x 7,168 with 3.6 rows 159.8 -> 162.3).
+// 65,536 x 136 with 3.3 rows 22.4 -> 18.4, 4.5 29.2 -> 22.0, 7.6 58.0 -> 48.8; 4,097 x 1,030 with 5.8 15.2 -> 14.3;
+// 16,384 x 520 with 5.4 27.3 -> 23.6; but 8,192 x 7,161 with 3.3 108.7 -> 111.9, 75,791 x 1,039 163 -> 174. A combine
+// that reads the very rows that dispatch has just written, with nothing between, finds fewer of them on its own die:
+// 65,536 x 72 with one row 11.6 -> 14.1 for both.  The transpose keeps the launch order (16,384 x 2,050 with 7.7 rows
+// and its combine 227.5 -> 229.7), and so do whole lines, of which neighbours share none (8,192 x 7,168 with 3.6 rows
+// 159.8 -> 162.3).
 static inline bool near_pays(const RowForm &f) {
   const int64_t row = (int64_t)f.H * f.elem_bytes, tokens = f.T * row;
   return !f.lines && row >= 32 && tokens <= (row <= 1400 ? 130000000 : 80000000);
 }
 
-// Whether the bf16 transpose of ragged rows has the reads of eight rows in flight, which hides its rounding: for up to eight slots that are
-// known to be kept nearly all, and 7 MB of gradients or more.  Four -> eight, 1,300 shapes drawn, three to eight slots, three to eight buffers in
-// turn, geometric means: kept nearly all, from 7 MB on 0 to +4 % (16,384 x 1,030 with 7.6 rows 74.7 -> 65.0 us, 8,192 x 1,030 with six 28.5 -> 26.4),
-// below -1 to -4 % (5,114 x 363 with 7.6 11.9 -> 12.9); 4.3 rows of six to eight slots or more 0 to +6 %, but -8 % for some (70,304 x 591 with 4.7);
-// fewer rows -4 to -17 % (8,192 x 7,161 with 2.2 81.6 -> 97.3), which a bound of eight in place of a count would not show.  Ten rows 27.4 -> 28.1.
+// Whether the bf16 transpose of ragged rows has the reads of eight rows in flight, which hides its rounding: for up to
+// eight slots that are known to be kept nearly all, and 7 MB of gradients or more.  Four -> eight, 1,300 shapes drawn,
+// three to eight slots, three to eight buffers in turn, geometric means: kept nearly all, from 7 MB on 0 to +4 %
+// (16,384 x 1,030 with 7.6 rows 74.7 -> 65.0 us, 8,192 x 1,030 with six 28.5 -> 26.4), below -1 to -4 % (5,114 x 363
+// with 7.6 11.9 -> 12.9); 4.3 rows of six to eight slots or more 0 to +6 %, but -8 % for some (70,304 x 591 with 4.7);
+// fewer rows -4 to -17 % (8,192 x 7,161 with 2.2 81.6 -> 97.3), which a bound of eight in place of a count would not
+// show.  Ten rows 27.4 -> 28.1.
 static inline bool eight_reads_pay(const RowForm &f, const hm_plan_out *plan) {
   const double c = known_rows_per_token(plan, f.T);
   return f.K <= 8 && c > 4.25 && c > f.K - 1 && (int64_t)f.T * f.H * f.elem_bytes >= 7000000;
 }
 
 // Dispatch (scaled = false) and transpose.
-//  * Vectors, narrow: flat up to the widths at which it still gains.  65,536 tokens, 3.6 rows each, in waves ->
-//    flat: dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 256 32.8 -> 28.8 (but 32,768 tokens: 3 % slower, or 7.7
-//    rows: 14 % slower); bf16 transpose of 192 32.6 -> 22.0, of 256 33.4 -> 26.9; fp32 transpose of 16 12.3 -> 5.8, of 64
-//    16.9 -> 12.5, of 96 21.1 -> 19.6 (but 8,192 tokens: 5 % slower).  With K <= 2 further (K = 1: 320 bf16 16.8 -> 15.3).
-//    And just above 64 vectors, where waves leave most of their second segment idle: bf16 transpose (16,384 tokens of
-//    576, 3.6 rows 17.7 -> 14.8; of 640 up to six rows only, with 7.7 31.5 -> 33.7; not off a line: 8,192 of 520 11.8 ->
-//    12.4), dispatch for K <= 2 (K = 1: 6.7 -> 4.6; but K = 8: 12.7 -> 13.3), fp32 transpose for K = 1 (384 elements 8.1 ->
-//    6.3); just above 128 for K = 1 (8,192 tokens, 1,088 bf16, dispatch 5.7 -> 4.5).
-//  * Vectors, not narrow: whole lines are written by kWhole.  Rows that begin inside a line are written
-//    in line-sized pieces by kRagged, which reads the token again for each row: better once that saves more
-//    in partial lines than it costs, i.e. with many rows per token that are long (the extra segment for the
-//    slack of a line is a larger part of short ones) and some 24 MB to write.  A weight to multiply by makes the second
-//    reading dearer, fp32 twice.  Fresh buffers, packed rows 16 bytes off a line, kWhole -> kRagged, 16,384 tokens of
-//    1,024 / 2,048 / 7,168 elements:
-//      7.7 rows: dispatch 72 -> 69, 144 -> 123, 488 -> 369; bf16 transpose 79 -> 76, 158 -> 131, 533 -> 382; fp32 157 -> 124, 301 -> 223,
-//        1,033 -> 839; from 36 MB on just above 64 vectors, too (584 bf16: dispatch 46.6 -> 42.9, 8,192 tokens bf16 transpose
-//        26.7 -> 23.8; but 456: 37.1 -> 39.3);
-//      3.6 rows: dispatch 31.7 -> 32.6 (1,032: 36.4 -> 33.6), 60 -> 58, 202 -> 187; bf16 transpose 34.6 -> 37.2 (1,032: 37.5 -> 38.2),
-//        64.5 -> 63.4, 210 -> 191; fp32 61 -> 68, 120 -> 127, 397 -> 443 (but small gradients, below 24 MB: 4,096 tokens of 512
-//        10.1 -> 9.3, of 1,024 17.0 -> 14.3, of 2,048 32.5 -> 34.4; 1,024 tokens of 4,096 16.8 -> 13.8);
-//      1.9 rows: dispatch 20.9 -> 24.2, 40.2 -> 39.8, 130 -> 121; bf16 transpose 22.7 -> 28.2, 42 -> 46, 131 -> 136; fp32 39 -> 50,
-//        73 -> 95, 248 -> 319.
+//  * Vectors, narrow: flat up to the widths at which it still gains.  65,536 tokens, 3.6 rows each, in waves -> flat:
+//    dispatch of 16 bf16 13.2 -> 6.6, of 128 13.1 -> 12.1, of 256 32.8 -> 28.8 (but 32,768 tokens: 3 % slower, or 7.7
+//    rows: 14 % slower); bf16 transpose of 192 32.6 -> 22.0, of 256 33.4 -> 26.9; fp32 transpose of 16 12.3 -> 5.8, of
+//    64 16.9 -> 12.5, of 96 21.1 -> 19.6 (but 8,192 tokens: 5 % slower).  With K <= 2 further (K = 1: 320 bf16 16.8 ->
+//    15.3). And just above 64 vectors, where waves leave most of their second segment idle: bf16 transpose (16,384
+//    tokens of 576, 3.6 rows 17.7 -> 14.8; of 640 up to six rows only, with 7.7 31.5 -> 33.7; not off a line: 8,192 of
+//    520 11.8 -> 12.4), dispatch for K <= 2 (K = 1: 6.7 -> 4.6; but K = 8: 12.7 -> 13.3), fp32 transpose for K = 1 (384
+//    elements 8.1 -> 6.3); just above 128 for K = 1 (8,192 tokens, 1,088 bf16, dispatch 5.7 -> 4.5).
+//  * Vectors, not narrow: whole lines are written by kWhole.  Rows that begin inside a line are written in line-sized
+//    pieces by kRagged, which reads the token again for each row: better once that saves more in partial lines than it
+//    costs, i.e. with many rows per token that are long (the extra segment for the slack of a line is a larger part of
+//    short ones) and some 24 MB to write.  A weight to multiply by makes the second reading dearer, fp32 twice.  Fresh
+//    buffers, packed rows 16 bytes off a line, kWhole -> kRagged, 16,384 tokens of 1,024 / 2,048 / 7,168 elements: 7.7
+//    rows: dispatch 72 -> 69, 144 -> 123, 488 -> 369; bf16 transpose 79 -> 76, 158 -> 131, 533 -> 382; fp32 157 -> 124,
+//    301 -> 223, 1,033 -> 839; from 36 MB on just above 64 vectors, too (584 bf16: dispatch 46.6 -> 42.9, 8,192 tokens
+//    bf16 transpose 26.7 -> 23.8; but 456: 37.1 -> 39.3); 3.6 rows: dispatch 31.7 -> 32.6 (1,032: 36.4 -> 33.6), 60 ->
+//    58, 202 -> 187; bf16 transpose 34.6 -> 37.2 (1,032: 37.5 -> 38.2), 64.5 -> 63.4, 210 -> 191; fp32 61 -> 68, 120 ->
+//    127, 397 -> 443 (but small gradients, below 24 MB: 4,096 tokens of 512 10.1 -> 9.3, of 1,024 17.0 -> 14.3, of
+//    2,048 32.5 -> 34.4; 1,024 tokens of 4,096 16.8 -> 13.8); 1.9 rows: dispatch 20.9 -> 24.2, 40.2 -> 39.8, 130 ->
+//    121; bf16 transpose 22.7 -> 28.2, 42 -> 46, 131 -> 136; fp32 39 -> 50, 73 -> 95, 248 -> 319.
 //  * Elements, few of them: kElems, whose lanes are all resident and have the shortest chain, for K <= 2 up to 512 Ki
 //    elements (2,048 tokens, K = 1, 65 bf16, transpose: 2.7, flat 3.2, ragged 3.4), for the bf16 transpose up to 256 Ki
-//    (2,048 x 33, 7.7 rows: 5.1, flat 5.6, ragged 7.6; but 16,384 x 17: 7.3, flat 6.5), for dispatch of many copies of up to nine
-//    vectors up to 128 Ki (2,048 x 33: 3.9, flat 4.2; but x 100: 4.5, flat 4.0; 16 x 17: 3.5, flat 2.8).
-//  * Elements, many copies of short rows: kElems, whose neighbouring lanes write neighbouring elements
-//    where vectors straddle lines (65,536 tokens, 7.7 rows, fresh buffers, kElems / flat: dispatch of 17 bf16 15 / 23, of 33 27 / 33,
+//    (2,048 x 33, 7.7 rows: 5.1, flat 5.6, ragged 7.6; but 16,384 x 17: 7.3, flat 6.5), for dispatch of many copies of
+//    up to nine vectors up to 128 Ki (2,048 x 33: 3.9, flat 4.2; but x 100: 4.5, flat 4.0; 16 x 17: 3.5, flat 2.8).
+//  * Elements, many copies of short rows: kElems, whose neighbouring lanes write neighbouring elements where vectors
+//    straddle lines (65,536 tokens, 7.7 rows, fresh buffers, kElems / flat: dispatch of 17 bf16 15 / 23, of 33 27 / 33,
 //    but of 65 41 / 41, of 130 84 / 61; fp32 transpose of 33 40 / 45, but of 65 69 / 65; bf16 transpose, dearer per
 //    element, of 17 23 / 25, but of 33 38 / 35; and with 32,768 tokens of 17 13.7 / 12.4).
-//  * Elements, narrow: flat at any number of tokens (fp32 transpose of 16 x 5, 7.8 rows: 3.0, ragged 3.9), but from 2,048 on
-//    for the bf16 transpose (512 x 250 5.3, ragged 5.7, but 3.6 rows 4.7 and 4.2; 2,048: 6.5 and 7.6, 5.2 and 5.0).  Up to 32
-//    vectors, for fp32 with K > 2 up to 20 (65,536 tokens, 3.6 rows, ragged -> flat: 33 fp32 25 -> 16, 130 33 -> 39), 12 with
-//    many copies of many tokens (7.7 rows, 65 fp32: 57 -> 65, but 8,192 tokens 9.2 -> 8.6), for K = 1 up to 76, as far as the ragged kernel's slack of a line fills a
-//    second segment badly (65,536 x 250 fp32: 55 -> 28); else ragged (7.3 copies of 301 bf16: 113, flat 116).
+//  * Elements, narrow: flat at any number of tokens (fp32 transpose of 16 x 5, 7.8 rows: 3.0, ragged 3.9), but from
+//    2,048 on for the bf16 transpose (512 x 250 5.3, ragged 5.7, but 3.6 rows 4.7 and 4.2; 2,048: 6.5 and 7.6, 5.2 and
+//    5.0).  Up to 32 vectors, for fp32 with K > 2 up to 20 (65,536 tokens, 3.6 rows, ragged -> flat: 33 fp32 25 -> 16,
+//    130 33 -> 39), 12 with many copies of many tokens (7.7 rows, 65 fp32: 57 -> 65, but 8,192 tokens 9.2 -> 8.6), for
+//    K = 1 up to 76, as far as the ragged kernel's slack of a line fills a second segment badly (65,536 x 250 fp32: 55
+//    -> 28); else ragged (7.3 copies of 301 bf16: 113, flat 116).
 static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool scaled) {
   if (!in_vectors(f)) return Route::kElems;
   const bool wide = f.elem_bytes == 4, scaled_bf16 = scaled && !wide;
@@ -1122,7 +1131,8 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
     const int many = f.T >= 65536 && rows <= 6.0 ? 32 : 16;
     const int narrow = f.K == 1 ? 48 : f.K == 2 ? (wide ? 24 : 48) : wide ? 16 : scaled ? 32 : many;
     const int above = f.K == 1 ? (wide ? 96 : 88) : f.K == 2 ? (wide ? 0 : 80) : scaled_bf16 && f.lines ? (rows > 6.0 ? 72 : 80) : 0;
-    const bool few_lanes = (f.vecs > kWave && f.vecs <= above) || (f.K == 1 && f.vecs > 2 * kWave && f.vecs <= kFlatVecs);   // in the last segment
+    const bool few_lanes =   // in the last segment
+        (f.vecs > kWave && f.vecs <= above) || (f.K == 1 && f.vecs > 2 * kWave && f.vecs <= kFlatVecs);
     if (f.T >= kFlatTokens && (f.vecs <= narrow || (few_lanes && !ragged))) return Route::kFlat;
     return ragged ? Route::kRagged : Route::kWhole;
   }
@@ -1135,15 +1145,16 @@ static inline Route spread_route(const RowForm &f, const hm_plan_out *plan, bool
   return f.vecs <= narrow && (!scaled_bf16 || f.T >= 2048) ? Route::kFlat : Route::kRagged;
 }
 
-// With the caller's weights: segments of 1 KiB (combine_slots_kernel, under combine_shape's cap) or of 4 KiB (combine_rows_kernel) for
-// tokens known to have two rows or more.  Rows of one short segment always: the lanes of a long one would be idle.  Longer rows
-// where the waves of short segments still run all at once (16 per CU), as each has less to wait for, and where not even
-// those of long ones do, if there are bytes enough to hide that every segment finds the token's rows again, three rows or so for each, and
-// few idle lanes in the last segment.  HIP events, buffers in turn, 4 KiB -> 1 KiB, us: 8,192 x 256 bf16 with 7 rows
-// 15.0 -> 10.2, 16,384 x 512 with 4 22.6 -> 16.6; 1,024 x 1,030 7.5 -> 6.2, but 4,096 x 1,030 14.8 -> 16.6, 4,096 x 640 10.4 ->
-// 11.0, 4,096 x 1,792 with 5 8 % slower; 8,192 x 7,160 158.8 -> 153.6, 3,072 x 2,304 up to 7 % faster, 32,768 x 1,920 8 %, but 16,384 x
-// 1,030 50.7 -> 57.2 and x 4,097 4 % slower.  Of two rows: 32,768 x 1,664 9 % slower, 2,048 x 7,168 4 %.  Only a known row count
-// counts: tokens of one row or so under a bound of eight take 49 -> 81 us (8,192 x 7,168 bf16, 1.2 rows), 18 -> 25 (x 2,048), 62 -> 96
+// With the caller's weights: segments of 1 KiB (combine_slots_kernel, under combine_shape's cap) or of 4 KiB
+// (combine_rows_kernel) for tokens known to have two rows or more.  Rows of one short segment always: the lanes of a
+// long one would be idle.  Longer rows where the waves of short segments still run all at once (16 per CU), as each has
+// less to wait for, and where not even those of long ones do, if there are bytes enough to hide that every segment
+// finds the token's rows again, three rows or so for each, and few idle lanes in the last segment.  HIP events, buffers
+// in turn, 4 KiB -> 1 KiB, us: 8,192 x 256 bf16 with 7 rows 15.0 -> 10.2, 16,384 x 512 with 4 22.6 -> 16.6; 1,024 x
+// 1,030 7.5 -> 6.2, but 4,096 x 1,030 14.8 -> 16.6, 4,096 x 640 10.4 -> 11.0, 4,096 x 1,792 with 5 8 % slower; 8,192 x
+// 7,160 158.8 -> 153.6, 3,072 x 2,304 up to 7 % faster, 32,768 x 1,920 8 %, but 16,384 x 1,030 50.7 -> 57.2 and x 4,097
+// 4 % slower.  Of two rows: 32,768 x 1,664 9 % slower, 2,048 x 7,168 4 %.  Only a known row count counts: tokens of one
+// row or so under a bound of eight take 49 -> 81 us (8,192 x 7,168 bf16, 1.2 rows), 18 -> 25 (x 2,048), 62 -> 96
 // (32,768 x 2,048, 1.6 rows), which is more than the 3 to 12 % that those of many rows would gain.
 static inline bool short_segments(const RowForm &f, const hm_plan_out *plan) {
   const double rows = known_rows_per_token(plan, f.T);
@@ -1160,24 +1171,24 @@ static inline CombineShape launched_shape(const RowForm &f, const hm_plan_out *p
 }
 
 // Combine; vecs_per_lane is that of the wave kernels' launch shape.
-//  * With the caller's weights there is no flat kernel.  Elements: kElems where K slots of H elements are less work than
-//    a wave's merging of the slots (65,536 tokens, fresh buffers, kElems / ragged: K = 1, 99 bf16 23 / 38, 161 46 / 40; K = 2, 65 33 / 50,
-//    99 58 / 51; K = 8, 3.6 rows, 17 53 / 70; K = 4, fp32, 17 27 / 39, 33 55 / 40; K = 1, fp32, 99 32 / 30) or there are few of them
-//    (1,024 tokens, K = 1, 513: 3.5 / 4.0), as long as its chain over K slots squared is hidden (8,192 tokens, K =
-//    8, 17 elements: 14.3 / 11.1).
-//  * With the plan's weights.  Vectors: flat where narrow (65,536 tokens, 3.6 rows, in waves -> flat: 64 bf16 27.6 -> 9.4,
-//    320 35.1 -> 32.2, 384 38.3 -> 37.7; 64 fp32 27.7 -> 14.5, 100 31.3 -> 22.7; K = 1 further, 16,384 x 456 bf16 11.0 -> 8.6),
-//    and where segments of one vector per lane would leave the last one mostly idle (16,384 tokens, 576 bf16: 18.6 ->
-//    16.1, 1,088 28.8 -> 27.3, 320 fp32 18.5 -> 16.6); segments of four only for K = 1 (65 to 88 bf16 vectors 4 to 30 %,
-//    320 fp32 16,384 tokens 10.2 -> 9.7, 65,536 32.9 -> 29.1) or few tokens of bf16 (1,024 x 1,000, K = 1: 3.4 -> 3.0; 8,192
-//    x 576, K = 2: equal, 1,152 20 % slower).  Elements: flat where waves would have a quarter of their lanes idle
-//    or more (65,536 tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344) or, for K = 1, three of four vectors of a
-//    lane (65,536 x 451: ragged 37, flat 28), kElems for K <= 2 and few elements
-//    (2,048 tokens, K = 1, 65 bf16: 2.6, flat 3.1).
+//  * With the caller's weights there is no flat kernel.  Elements: kElems where K slots of H elements are less work
+//    than a wave's merging of the slots (65,536 tokens, fresh buffers, kElems / ragged: K = 1, 99 bf16 23 / 38, 161 46
+//    / 40; K = 2, 65 33 / 50, 99 58 / 51; K = 8, 3.6 rows, 17 53 / 70; K = 4, fp32, 17 27 / 39, 33 55 / 40; K = 1,
+//    fp32, 99 32 / 30) or there are few of them (1,024 tokens, K = 1, 513: 3.5 / 4.0), as long as its chain over K
+//    slots squared is hidden (8,192 tokens, K = 8, 17 elements: 14.3 / 11.1).
+//  * With the plan's weights.  Vectors: flat where narrow (65,536 tokens, 3.6 rows, in waves -> flat: 64 bf16 27.6 ->
+//    9.4, 320 35.1 -> 32.2, 384 38.3 -> 37.7; 64 fp32 27.7 -> 14.5, 100 31.3 -> 22.7; K = 1 further, 16,384 x 456 bf16
+//    11.0 -> 8.6), and where segments of one vector per lane would leave the last one mostly idle (16,384 tokens, 576
+//    bf16: 18.6 -> 16.1, 1,088 28.8 -> 27.3, 320 fp32 18.5 -> 16.6); segments of four only for K = 1 (65 to 88 bf16
+//    vectors 4 to 30 %, 320 fp32 16,384 tokens 10.2 -> 9.7, 65,536 32.9 -> 29.1) or few tokens of bf16 (1,024 x 1,000,
+//    K = 1: 3.4 -> 3.0; 8,192 x 576, K = 2: equal, 1,152 20 % slower).  Elements: flat where waves would have a quarter
+//    of their lanes idle or more (65,536 tokens, 3.6 rows, 301 bf16: ragged 40, flat 39, kElems 344) or, for K = 1,
+//    three of four vectors of a lane (65,536 x 451: ragged 37, flat 28), kElems for K <= 2 and few elements (2,048
+//    tokens, K = 1, 65 bf16: 2.6, flat 3.1).
 //  * In waves: kWhole for whole lines and where the slack of a line would cost kRagged one more segment, of few or long
-//    ones (4,096 tokens, K = 1, 2,048 bf16 16 bytes off a line, the caller's weights: 6.4 whole, 9.4 ragged) or with reads
-//    off a line that kWhole would do in lines (8,192 x 4,096, 7.7 rows, only out off a line: 97 and 101); else kRagged
-//    (16,384 x 7,168, 3.6 rows, both 16 bytes off: bf16 173 whole, 163 ragged; fp32 354 and 326).
+//    ones (4,096 tokens, K = 1, 2,048 bf16 16 bytes off a line, the caller's weights: 6.4 whole, 9.4 ragged) or with
+//    reads off a line that kWhole would do in lines (8,192 x 4,096, 7.7 rows, only out off a line: 97 and 101); else
+//    kRagged (16,384 x 7,168, 3.6 rows, both 16 bytes off: bf16 173 whole, 163 ragged; fp32 354 and 326).
 static inline Route combine_route(const RowForm &f, bool from_plan, int vecs_per_lane) {
   if (!in_vectors(f)) return Route::kElems;
   const bool wide = f.elem_bytes == 4, many = f.T >= kFlatTokens || f.K <= 2;
@@ -1249,8 +1260,8 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
       hipLaunchKernelGGL((near ? dispatch_rows_kernel<true> : dispatch_rows_kernel<false>), grid, dim3(kCopyThreads), lds, stream, p, x,
                          packed, packed_rows);
     else
-      hipLaunchKernelGGL((near ? spread_ragged_kernel<RowBf16, false, 4, true> : spread_ragged_kernel<RowBf16, false, 4, false>), grid, dim3(kCopyThreads), lds, stream, p, x, nullptr,
-                         packed_rows, packed);
+      hipLaunchKernelGGL((near ? spread_ragged_kernel<RowBf16, false, 4, true> : spread_ragged_kernel<RowBf16, false, 4, false>),
+                         grid, dim3(kCopyThreads), lds, stream, p, x, nullptr, packed_rows, packed);
   } else {
     if (!grid_for_elems(p, (int64_t)T * H, grid)) return HM_ERR_SHAPE;
     hipLaunchKernelGGL(dispatch_elems_kernel, grid, dim3(kElemThreads), 0, stream, p, H, x, packed, packed_rows);

@@ -194,15 +194,19 @@ __global__ __launch_bounds__(kFactorThreads) void swap_factors_kernel(SwapParams
 // a panel of columns of C, builds the three indicator tiles in LDS (expert-major, a mark is a nibble: 1.0 in FP4, so that
 // a lane's MFMA operand of 32 tokens is 16 contiguous bytes and 1,024 tokens of 128 experts fit at once), and stores
 // its partial tables with plain stores; swap_pairs_kernel sums the chunks where it puts Z together.  The products add up
-// zeros and ones in binary32, which is exact below 2^24; a chunk has fewer than 2^15 tokens, or, added, a workgroup as many.
+// zeros and ones in binary32, which is exact below 2^24; a chunk has fewer than 2^15 tokens, or, added, at most 2^24.
 // (With many tokens, or E > 256, for which the workspace has no room for partial tables, the chunks are added to
 // cleared tables by atomics, or the slots are: atomics_pay.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kCoocChunks = 16;      // partial tables per cut, some of them of no token where there are few: whoever sums them need not ask how many there are
+// Partial tables per cut, some of them of no token where there are few: whoever sums them need not ask how many there are.
+constexpr int kCoocChunks = 16;
 constexpr int kCoocChunkTokensMax = 32640;   // a chunk's counts are stored as 16-bit values
 constexpr int kCoocAddedTokensMax = 1 << 24; // a workgroup's sums are binary32
 constexpr int kCoocMaxE = 512;
-constexpr int kCoocAddedGroups = 256;   // workgroups aimed at where chunks are added up (512, with marks as bytes: E = 320, 4,096 tokens 33 -> 39 us)
+// Workgroups aimed at where chunks are added up, one per CU: fewer leave CUs idle, more add more tables (E = 320, four
+// cuts, K = 8, with 128 / 256 / 512: 4,096 tokens 22.0 / 21.7 / 28.0 us, 16,384 40.0 / 31.5 / 38.2, 300,000 443 / 231 /
+// 226).
+constexpr int kCoocAddedGroups = 256;
 constexpr int kCoocOwnK = 8;         // most slots of a token that the matrix kernel works out itself
 constexpr int kCoocThreads = kCoocWaves * kWave;   // = most tokens of a tile: a lane per token
 constexpr int kCoocStep = 64;        // tokens of one 32x32x64 product
@@ -235,10 +239,11 @@ struct CoocParams {
   int32_t *status;
 };
 
-// The tables of a cut, in blocks of up to 16 experts a (h of them) by up to 16 columns, chunk by chunk, a block's values with
-// the experts side by side: [C: E blocks by E][CG: E by ng][L: E][base: 64].  A block of all chunks is contiguous, so
-// whoever sums the chunks of a block reads whole lines, and four neighbouring experts of a lane's accumulators are one store.
-// Tables that chunks are added to are plain rows, [C: E by E][CG: E by ng][L][base], as the lanes of an atomic should be neighbours.
+// The tables of a cut, in blocks of up to 16 experts a (h of them) by up to 16 columns, chunk by chunk, a block's
+// values with the experts side by side: [C: E blocks by E][CG: E by ng][L: E][base: 64].  A block of all chunks is
+// contiguous, so whoever sums the chunks of a block reads whole lines, and four neighbouring experts of a lane's
+// accumulators are one store. Tables that chunks are added to are plain rows, [C: E by E][CG: E by ng][L][base], as the
+// lanes of an atomic should be neighbours.
 struct Tables {
   int E, ng, chunks;
   __host__ __device__ static int64_t values(int64_t E, int64_t ng) { return E * E + E * ng + E + 64; }   // of a chunk
@@ -329,16 +334,18 @@ constexpr uint32_t kNoGroup = 0x80, kBadGroup = 0xC0;   // id -1; an id or a pla
 // A product below 2^24: one instruction at the full rate.
 __device__ __forceinline__ int row_at(uint32_t row, int stride) { return (int)__umul24(row, (uint32_t)stride); }
 
-// The marks of a lane's token of up to eight slots, written for few instructions: the sixteen waves of a workgroup issue each of them
-// in turn.  Groups are bits of BITS: one that has been seen twice, copies of an expert aside, is nobody's alone.  `m`, `a`: the
-// token's word in row 0 of the tiles, a_to_s: from an expert's row of A to its row of S, `value`: the token's bit.
+// The marks of a lane's token of up to eight slots, written for few instructions: the sixteen waves of a workgroup
+// issue each of them in turn.  Groups are bits of BITS: one that has been seen twice, copies of an expert aside, is
+// nobody's alone.  `m`, `a`: the token's word in row 0 of the tiles, a_to_s: from an expert's row of A to its row of S,
+// `value`: the token's bit.
 template <typename BITS>
-__device__ __forceinline__ void mark_token(const int (&id)[kCoocOwnK], int E, const uint8_t *group_of, int stride, int panel0, int panel, uint8_t *m,
-                                           uint8_t *a, int a_to_s, uint32_t value, bool &bad) {
+__device__ __forceinline__ void mark_token(const int (&id)[kCoocOwnK], int E, const uint8_t *group_of, int stride, int panel0,
+                                           int panel, uint8_t *m, uint8_t *a, int a_to_s, uint32_t value, bool &bad) {
   uint32_t expert[kCoocOwnK], group[kCoocOwnK], all = 0;
   uint32_t same = 1;   // 0 if two slots have one expert
 #pragma unroll
-  for (int k = 0; k < kCoocOwnK; ++k) group[k] = group_of[min((uint32_t)id[k] + 1u, (uint32_t)E + 1u)];   // entry 0: id -1, E + 1: out of range
+  for (int k = 0; k < kCoocOwnK; ++k)   // entry 0: id -1, E + 1: out of range
+    group[k] = group_of[min((uint32_t)id[k] + 1u, (uint32_t)E + 1u)];
 #pragma unroll
   for (int k = 0; k < kCoocOwnK; ++k) {
     all |= group[k];
@@ -385,17 +392,18 @@ __device__ __forceinline__ void store_four(uint16_t *out, const int (&v)[4], int
       if (i < left) out[i] = (uint16_t)v[i];
   }
 }
-// Workgroup (chunk, cut, panel of 32 COLS columns of C); a wave holds one row of 32x32 tiles of the panel, the last waves a tile of
-// its CG each.  A workgroup needs the S tile of its own columns only; the panels repeat the marks of the chunk's slots and
-// the A tile.  One column of tiles up to 128 experts, so that four cuts and sixteen chunks are a workgroup per CU, two
-// for 256, one again beyond, where a wave per tile row is all there are.
+// Workgroup (chunk, cut, panel of 32 COLS columns of C); a wave holds one row of 32x32 tiles of the panel, the last
+// waves a tile of its CG each.  A workgroup needs the S tile of its own columns only; the panels repeat the marks of
+// the chunk's slots and the A tile.  One column of tiles up to 128 experts, so that four cuts and sixteen chunks are a
+// workgroup per CU, two for 256, one again beyond, where a wave per tile row is all there are.
 //
-// Per tile of up to 1,024 tokens: load and clear | barrier | mark | barrier | multiply, and a barrier if there are more tiles.  All
-// marks of a chunk of that many tokens are made at once: with a byte per mark a tile held 128, and the chain of marks,
-// barrier, LDS operands, products and barrier, 0.5 us per tile, was half of the kernel.  What bounds it now is the marks, which
-// sixteen waves issue in turn, 1.0 to 1.7 us of 7 (products 0.6, clearing 0.5, stores 0.6), and cold code, 8 KB of it.  Kernel trace,
-// four cuts, K = 8, before -> now: 16,384 tokens, 128 experts 11.8 -> 6.9 us, 8,192, 256 12.2 -> 7.7.  The whole call (graphs
-// of ten), 4,096, 65,536, 500,000 tokens: 128 experts 16.0 -> 11.5, 42.4 -> 21.9, 223 -> 99; 256 25.8 -> 18.3, 57.7 -> 37.1, 272 -> 157.
+// Per tile of up to 1,024 tokens: load and clear | barrier | mark | barrier | multiply, and a barrier if there are more
+// tiles.  All marks of a chunk of that many tokens are made at once: with a byte per mark a tile held 128, and the
+// chain of marks, barrier, LDS operands, products and barrier, 0.5 us per tile, was half of the kernel.  What bounds it
+// now is the marks, which sixteen waves issue in turn, 1.0 to 1.7 us of 7 (products 0.6, clearing 0.5, stores 0.6), and
+// cold code, 8 KB of it.  Kernel trace, four cuts, K = 8, bytes -> nibbles: 16,384 tokens, 128 experts 11.8 -> 6.6 us,
+// 8,192, 256 12.2 -> 7.9.  The whole call (graphs of ten), 4,096, 65,536, 500,000 tokens: 128 experts 16.0 -> 11.4,
+// 42.4 -> 21.3, 223 -> 97; 256 25.8 -> 18.5, 57.7 -> 35.6, 272 -> 151.
 template <int COLS, bool OWN_SLOTS, bool ADDED>   // ADDED: to cleared tables, instead of stored as a part
 __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   constexpr int kPanel = 32 * COLS, kAhead = 4 / COLS;   // products whose operands are on their way together
@@ -410,12 +418,13 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
   typedef CoocTiles<COLS> layout_t;
   const layout_t lay(E, ng);
-  uint8_t *const a_tile = tiles, *const s_tile = tiles + lay.s_at() * stride, *const m_tile = tiles + lay.m_at() * stride;   // rows of `stride` bytes
+  // rows of `stride` bytes
+  uint8_t *const a_tile = tiles, *const s_tile = tiles + lay.s_at() * stride, *const m_tile = tiles + lay.m_at() * stride;
   const int vecs = lay.rows() * (stride / 16);
 
-  // Where a token of the tile is marked: in the row's word (token % words) and there in nibble (token / words), so that the lanes of a
-  // wave, which hold neighbouring tokens, meet at a bank only where their rows do, and never at a word.  The products take
-  // the tokens in any order.
+  // Where a token of the tile is marked: in the row's word (token % words) and there in nibble (token / words), so that
+  // the lanes of a wave, which hold neighbouring tokens, meet at a bank only where their rows do, and never at a word.
+  // The products take the tokens in any order.
   const int words = p.tile_tokens >> 3;
   auto place = [&](int token, int &at) {
     const uint32_t nibble = __umul24((uint32_t)token, p.words_recip17) >> 17;   // token < 1,024, 16 to 128 words
@@ -479,7 +488,10 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
 #pragma unroll 1
     for (int i = tid; i < vecs; i += kCoocThreads) ((i32x4 *)tiles)[i] = zero;
     if (t0 == t_begin) {
-      if (tid < E + 2) group_of[tid] = (uint8_t)(tid == 0 ? kNoGroup : (unsigned)rank < (unsigned)p.G ? __umul24((uint32_t)rank, p.per_recip16[cut]) >> 16 : kBadGroup);
+      if (tid < E + 2)
+        group_of[tid] = (uint8_t)(tid == 0                            ? kNoGroup
+                                  : (unsigned)rank < (unsigned)p.G ? __umul24((uint32_t)rank, p.per_recip16[cut]) >> 16
+                                                                   : kBadGroup);
     }
     __syncthreads();
     if (OWN_SLOTS) {
@@ -487,8 +499,11 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
         int at;
         const uint32_t value = place(tid, at);
         const int a_to_s = (lay.s_at() - kPanel * panel) * stride;
-        if (__builtin_expect(ng <= 32, 1)) mark_token<uint32_t>(id, E, group_of, stride, kPanel * panel, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
-        else mark_token<uint64_t>(id, E, group_of, stride, kPanel * panel, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
+        const int panel0 = kPanel * panel;
+        if (__builtin_expect(ng <= 32, 1))
+          mark_token<uint32_t>(id, E, group_of, stride, panel0, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
+        else
+          mark_token<uint64_t>(id, E, group_of, stride, panel0, kPanel, m_tile + at, a_tile + at, a_to_s, value, bad);
       }
     } else {
       constexpr int kLoads = 8;   // of a lane in flight together
@@ -509,7 +524,8 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
           const int i = i0 + j * kCoocThreads;
           if (i < slots && (bits[j] & 1)) {   // a valid expert
             int at;
-            const uint32_t value = place((int)__umulhi((uint32_t)i, p.k_reciprocal), at), column = (uint32_t)(expert[j] - kPanel * panel);
+            const uint32_t value = place((int)__umulhi((uint32_t)i, p.k_reciprocal), at);
+            const uint32_t column = (uint32_t)(expert[j] - kPanel * panel);
             atomicOr((uint32_t *)(m_tile + row_at(group_of[expert[j] + 1], stride) + at), value);
             if (column < (uint32_t)kPanel) atomicOr((uint32_t *)(s_tile + row_at(column, stride) + at), value);
             if ((bits[j] >> (1 + cut)) & 1) atomicOr((uint32_t *)(a_tile + row_at((uint32_t)expert[j], stride) + at), value);
@@ -521,8 +537,9 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
     auto of_g = [](f32x16 &sums) -> f32x16(&)[layout_t::kColumnsOfG] { return *(f32x16(*)[layout_t::kColumnsOfG])&sums; };
     if (layout_t::kColumnsOfC == layout_t::kColumnsOfG) {
       if (has_c || has_g) multiply(acc, rows, columns);
-    } else {   // one tile of CG, not COLS: behind M's tiles LDS ends (200,000 tokens, 256 experts, four cuts: with a second product, of the
-               // same tile, whose sums are dropped, 76.6 us, 71.8 without; 8,192 18.9 and 18.7)
+    } else {
+      // One tile of CG, not COLS: behind M's tiles LDS ends (200,000 tokens, 256 experts, four cuts: with a second product,
+      // of the same tile, whose sums are dropped, 76.6 us, 71.8 without; 8,192 18.9 and 18.7).
       if (has_c) multiply(acc, rows, columns);
       else if (has_g) multiply(of_g(acc[0]), rows, columns);
     }
@@ -556,7 +573,8 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
         for (int i = 0; i < 4; ++i)
           if (i < h - row && v[i]) atomicAdd(out + begin + (kBlock * (block + q / 2) + row + i) * width + column, v[i]);
       } else {
-        store_four(out + (begin + (block + q / 2) * kBlock * width * table.chunks) + ((int)__umul24((uint32_t)h, (uint32_t)column) + row), v, h - row);
+        value_t *const at = out + (begin + (block + q / 2) * kBlock * width * table.chunks);
+        store_four(at + ((int)__umul24((uint32_t)h, (uint32_t)column) + row), v, h - row);
       }
     }
   };
@@ -593,12 +611,14 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
   }
 }
 
-// Z from the tables: a workgroup takes the pairs of two blocks of up to 16 experts, (r, c) and (c, r), as Z[r][c] = Z[c][r].
-// It sums the chunks of what these pairs need (two blocks of C, the CG rows of 32 experts, every value of C once for the whole
-// chip), puts the two changed counts of every pair together in LDS, and writes both orientations.  What bounds it is
-// the code, which runs once and cold, the trip to the parts, which the kernel before has just written, and the store of Z.  Kernel
-// trace, 128 experts, 16,384 tokens, four cuts: a kernel that summed the chunks and wrote transposes of C and CG, and one that looked them up
-// per value of Z, 4.4 + 5.7 us, now 6.3; 256 experts, 8,192 tokens (15.7 MB of Z) 6.2 + 7.6, now 8.9.
+// Z from the tables: a workgroup takes the pairs of two blocks of up to 16 experts, (r, c) and (c, r), as Z[r][c] =
+// Z[c][r]. It sums the chunks of what these pairs need (two blocks of C, the CG rows of 32 experts, every value of C
+// once for the whole chip), puts the two changed counts of every pair together in LDS, and writes both orientations.
+// What bounds it is waiting: by the counters its waves wait for memory, LDS or one another 58 % of their time with 128
+// experts and 47 % with 256, for an instruction to be fetched or issued 17 % and 31 %; their vector instructions (some
+// 250 a wave) take 0.5 us and 2.0 us of the SIMDs' time, and it writes Z and nothing else.  Kernel trace, 128 experts,
+// 16,384 tokens, four cuts: a kernel that summed the chunks and wrote transposes of C and CG, and one that looked them
+// up per value of Z, 4.4 + 5.7 us, now 6.3; 256 experts, 8,192 tokens (15.7 MB of Z) 6.2 + 7.6, now 9.2.
 constexpr int kPairThreads = 512;
 struct PairCut {
   const void *tables;
@@ -617,9 +637,10 @@ struct PairParams {
 __device__ __forceinline__ i32x4 load_four(const int32_t *at) { return *(const i32x4_align4 *)at; }
 __device__ __forceinline__ u16x4 load_four(const uint16_t *at) { return *(const u16x4_align2 *)at; }
 
-// N chunks, every STEP-th, of four values that begin at i of the n of a chunk; `at` is the first of these chunks.  The sums are of 32 bits;
-// counts of 16 come two in a word, and a product with (1, 0) or (0, 1) adds one of them in an instruction (the whole call, 128 experts, four cuts,
-// 8,192 tokens 11.9 us, with a conversion of each count 12.2, with sums of 16 bits, two in an instruction, 11.9; 256 experts 19.1, 19.4, 18.8).
+// N chunks, every STEP-th, of four values that begin at i of the n of a chunk; `at` is the first of these chunks.  The
+// sums are of 32 bits; counts of 16 come two in a word, and a product with (1, 0) or (0, 1) adds one of them in an
+// instruction (the whole call, 128 experts, four cuts, 8,192 tokens 11.9 us, with a conversion of each count 12.2, with
+// sums of 16 bits, two in an instruction, 11.9; 256 experts 19.1, 19.4, 18.8).
 template <int N, int STEP, typename V>
 struct Chunks {
   decltype(load_four((const V *)nullptr)) v[N];
@@ -635,8 +656,10 @@ struct Chunks {
       if constexpr (sizeof(V) == sizeof(uint16_t)) {
         typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          s[e] = (int32_t)__builtin_amdgcn_udot2((u16x2){v[j][e & 2], v[j][e | 1]}, (u16x2){(uint16_t)(~e & 1), (uint16_t)(e & 1)}, (uint32_t)s[e], false);
+        for (int e = 0; e < 4; ++e) {
+          const u16x2 word = {v[j][e & 2], v[j][e | 1]}, half = {(uint16_t)(~e & 1), (uint16_t)(e & 1)};
+          s[e] = (int32_t)__builtin_amdgcn_udot2(word, half, (uint32_t)s[e], false);
+        }
       } else {
         s += v[j];
       }
@@ -672,9 +695,12 @@ __global__ __launch_bounds__(kPairThreads) void swap_pairs_kernel(PairParams p) 
   const int tid = threadIdx.x, lane = lane_id(), w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int height_i = table.height(I), height_j = table.height(J);
 
-  // Waves 0 to 3 have block (I, J) of C and the CG of I, 4 to 7 block (J, I) and J.  Every load is on its way before the first is used.
-  const int side = w >> 2, of_c = w & (kOfC - 1), of_cg = w >> 1 & (kOfCG - 1), n_c = height_i * height_j, n_cg = (side ? height_j : height_i) * ng;
-  const int c_i = min(4 * lane, n_c - 4), q0 = (w & 1) * kWave + lane, cg_i = min(4 * q0, n_cg - 4);   // the last four may be values of another lane, too
+  // Waves 0 to 3 have block (I, J) of C and the CG of I, 4 to 7 block (J, I) and J.  Every load is on its way before
+  // the first is used.
+  const int side = w >> 2, of_c = w & (kOfC - 1), of_cg = w >> 1 & (kOfCG - 1);
+  const int n_c = height_i * height_j, n_cg = (side ? height_j : height_i) * ng;
+  // the last four may be values of another lane, too
+  const int c_i = min(4 * lane, n_c - 4), q0 = (w & 1) * kWave + lane, cg_i = min(4 * q0, n_cg - 4);
   const int rows_of = side ? J : I, cols_of = side ? I : J, rows = side ? height_j : height_i, cols = side ? height_i : height_j;
   const V *const c_at = part + table.c(rows_of) + rows * table.c_column(kBlock * cols_of, of_c);
   const V *const cg_at = part + table.cg(rows_of) + rows * table.cg_column(0, of_cg);
@@ -752,7 +778,8 @@ __global__ __launch_bounds__(kPairThreads) void swap_pairs_kernel(PairParams p) 
 
   // `of_pair` neighbouring lanes take a pair, a lane the same groups of every pair it takes.
   const int of_pair = cut.of_pair, wide = cut.wide;
-  const int first = (int)((uint32_t)tid * (uint32_t)cut.of_pair_recip20 >> 20), j = wide * (tid - first * of_pair), at_once = cut.pairs_at_once;
+  const int first = (int)((uint32_t)tid * (uint32_t)cut.of_pair_recip20 >> 20), j = wide * (tid - first * of_pair);
+  const int at_once = cut.pairs_at_once;
   if (first >= at_once) return;
   i32x4 base4;
 #pragma unroll
@@ -831,8 +858,8 @@ __global__ __launch_bounds__(kSwapThreads) void swap_build_kernel(SwapParams p) 
 // selection
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxDim = 4;
-constexpr int kSelectTerms = kMaxDim * kSelectPairs * (int)sizeof(double);   // bytes of LDS for the terms of the pairs ...
-constexpr int kSelectStaged = 65536 - kSelectTerms;                          // ... and what is left of the 64 KiB that every launch gets, for counts
+// Bytes of LDS for the terms of the pairs, and for staged counts what is left of the 64 KiB that every launch gets.
+constexpr int kSelectTerms = kMaxDim * kSelectPairs * (int)sizeof(double), kSelectStaged = 65536 - kSelectTerms;
 
 struct SelectParams {
   int32_t d, G, E;
@@ -871,11 +898,13 @@ __device__ __forceinline__ void load_counts(const int32_t *x, int n, int (&v)[N]
   for (int j = 0; j < N; ++j) v[j] = j < n ? v[j] : 0;
 }
 
-// The same for whole fours, through LDS: a lane that reads its pair's counts from memory touches a line of its own, so a wave's load
-// is 64 lines, and a CU's cache holds the lines of few waves.  It pays where lanes read up to 64 counts (256 experts, terms of 8, 16,
-// 32 and 64 groups, the whole selection 16.0 -> 14.3 us; of 4, 8, 16 and 32 11.0 from memory, 11.3 so; 512 experts 23.8, 25.7).  The wave takes its 64 pairs in order, straight into LDS
-// (`tile`, 256 n bytes), `first` its first four of the `fours` there are in all.  Within the fours of a pair, if they are a power of two,
-// the places are exchanged from pair to pair, so that the lanes, which then read one pair each, spread over all banks.
+// The same for whole fours, through LDS: a lane that reads its pair's counts from memory touches a line of its own, so
+// a wave's load is 64 lines, and a CU's cache holds the lines of few waves.  It pays where lanes read up to 64 counts
+// (256 experts, terms of 8, 16, 32 and 64 groups, the whole selection 16.0 -> 14.3 us; of 4, 8, 16 and 32 11.0 from
+// memory, 11.3 so; 512 experts 23.8, 25.7).  The wave takes its 64 pairs in order, straight into LDS (`tile`, 256 n
+// bytes), `first` its first four of the `fours` there are in all.  Within the fours of a pair, if they are a power of
+// two, the places are exchanged from pair to pair, so that the lanes, which then read one pair each, spread over all
+// banks.
 template <int N>
 __device__ __forceinline__ void stage_counts(i32x4 *tile, const i32x4 *z, int64_t first, int64_t fours, int n, int (&v)[N]) {
   const int lane = lane_id(), nq = n >> 2, log2_nq = 31 - __builtin_clz(nq);
@@ -949,8 +978,8 @@ __device__ __forceinline__ void keep_better(double &val, int32_t &arg, double v,
   val = better ? v : val;
   arg = better ? a : arg;
 }
-// The words of the lane `OFF` away (OFF a power of two): within rows of sixteen by the data paths of the vector unit, across them by swaps of
-// rows.  (Through LDS, as shuffles, the six steps of an argmin wait for three trips each.)
+// The words of the lane `OFF` away (OFF a power of two): within rows of sixteen by the data paths of the vector unit,
+// across them by swaps of rows.  (Through LDS, as shuffles, the six steps of an argmin wait for three trips each.)
 template <int OFF>
 __device__ __forceinline__ uint32_t from_lane(uint32_t v) {
   if constexpr (OFF == 32) {
@@ -979,13 +1008,13 @@ __device__ __forceinline__ void wave_argmin(double &val, int32_t &arg) {
   argmin_step<1>(val, arg);
 }
 
-// Q of 64 pairs by a workgroup: a wave per term of Eq.(8) (the Inter levels 1 .. d-1, then the Intra
-// level), a lane per pair, so that the waves with few groups are done early instead of waiting for the
-// lanes of the widest cut, and everything about a term is uniform.  Neighbouring workgroups begin with another term, so that the
-// widest ones do not meet on one SIMD.  The terms are then added in the order of the levels, so Q has the bits of
-// a serial evaluation.  The whole selection (graphs of twenty), every workgroup beginning with the first term and argmins by
-// shuffles -> now: 128 experts 8.9 -> 8.5 us, 256 11.7 -> 11.0.  Tried: the root by one step of Halley's method from a guess in
-// binary32 (0.3 and 0.7 us less, but one Q in 25 differs in the last bit, which decides between pairs of equal time).
+// Q of 64 pairs by a workgroup: a wave per term of Eq.(8) (the Inter levels 1 .. d-1, then the Intra level), a lane per
+// pair, so that the waves with few groups are done early instead of waiting for the lanes of the widest cut, and
+// everything about a term is uniform.  Neighbouring workgroups begin with another term, so that the widest ones do not
+// meet on one SIMD.  The terms are then added in the order of the levels, so Q has the bits of a serial evaluation.
+// The whole selection (graphs of twenty), every workgroup beginning with the first term and argmins by shuffles -> now:
+// 128 experts 8.9 -> 8.5 us, 256 11.7 -> 11.0.  Tried: the root by one step of Halley's method from a guess in binary32
+// (0.3 and 0.7 us less, but one Q in 25 differs in the last bit, which decides between pairs of equal time).
 template <int N>   // most groups of a term: 32 or 64
 __global__ __launch_bounds__(kSelectThreads) void swap_q_kernel(SelectParams p) {
 #pragma clang fp contract(off)
@@ -1087,12 +1116,12 @@ static bool swap_factors_lds_ready() {
   return ok;
 }
 
-// Private copies of C on the path with atomics: as many as fit 2 MiB per cut, at most
-// kSwapCopiesMax (32 for E <= 128, 8 for E = 256): more copies spread the atomics of popular pairs,
-// but each is cleared and summed again.  The matrix path keeps one summed C.
 // Whether the workspace has partial tables of chunks (and a byte per slot): E <= 256 and chunks short enough for
 // 16-bit counts.
 static inline bool swap_has_parts(int64_t E, int64_t T) { return E <= kCoocPartMaxE && T <= (int64_t)kCoocChunks * kCoocChunkTokensMax; }
+// Private copies of C on the path with atomics: as many as fit 2 MiB per cut, at most
+// kSwapCopiesMax (32 for E <= 128, 8 for E = 256): more copies spread the atomics of popular pairs,
+// but each is cleared and summed again.  One where there are partial tables, which the atomics only stand in for.
 static inline int64_t swap_copies(int64_t E, int64_t T) {
   if (swap_has_parts(E, T)) return 1;
   int64_t n = kSwapCopiesMax;   // a power of two, so that a workgroup finds its copy with a mask
@@ -1100,9 +1129,9 @@ static inline int64_t swap_copies(int64_t E, int64_t T) {
   return n;
 }
 
-// Workspace, in ints: L0 [E], then per cut base [64] | L [E] | CG [E * ng] | C [copies * E * E], and where there is room
-// for parts as much again as the tables of kCoocChunks chunks and a second C and CG take.  The matrix path lays its
-// tables out over all of it, cut after cut: they need less.
+// Workspace, in ints: L0 [E], then per cut base [64] | L [E] | CG [E * ng] | C [copies * E * E], and where there are
+// parts room for those of kCoocChunks chunks and for another C and CG.  The sizes are a promise to callers who keep such
+// a buffer.  The matrix path needs less, the tables of its chunks: it lays them out over all of it, cut after cut.
 static inline int64_t cooc_part_words(int64_t E, int64_t ng) { return (E * E + E * ng + 65) / 2; }
 static inline int64_t swap_cut_ints(int64_t E, int64_t ng, int64_t T) {
   return 64 + E + E * ng + swap_copies(E, T) * E * E +
@@ -1121,7 +1150,8 @@ struct CoocLaunch {
 template <int COLS, bool OWN_SLOTS, bool ADDED>
 static CoocLaunch cooc_launch(int E, int groups, int64_t tokens) {   // groups of the finest cut, tokens of a chunk
   static const bool granted = [] {
-    const hipError_t e = hipFuncSetAttribute((const void *)swap_cooc_kernel<COLS, OWN_SLOTS, ADDED>, hipFuncAttributeMaxDynamicSharedMemorySize, kCoocLds);
+    const hipError_t e = hipFuncSetAttribute((const void *)swap_cooc_kernel<COLS, OWN_SLOTS, ADDED>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kCoocLds);
     if (e != hipSuccess) (void)hipGetLastError();   // not sticky: do not let it fail the next launch check
     return e == hipSuccess;
   }();
@@ -1151,15 +1181,16 @@ static inline int cooc_chunks(bool parts, int64_t T, int64_t E, int ncuts) {
   return (int)(chunks < least ? least : chunks < 1 ? 1 : chunks);
 }
 
-// Whether atomics per slot are faster than matrix products whose chunks are added up: with few slots per token or few groups, as
-// the products take the same time however few marks a tile holds.  Two straight lines, us, through some 4,000 shapes (256 < E <= 512,
-// up to 520,000 tokens; E <= 256, 522,241 to 800,000; one to eight slots, one to four cuts; ids drawn evenly): Z, the
-// updates of C (a slot's K - 1 others where it is alone in its group) and of L0, L and CG (in LDS or in memory), and the
-// workgroups that put their tables together; against Z and a time per tile, for its barriers, its tokens and the bytes cleared (within
-// 10 % for nine in ten).  A popular few experts make only the atomics slower, and those of C most, so they have to be ahead by a tenth
-// if there are such; without (one slot, or one group) they may be estimated behind by an eighth, by which the line for them is
-// too high there.  Of 1,500 shapes, half of them with a Zipf router, the rule loses more than 3 % in 122 (95 Zipf ids by atomics).
-// Atomics / matrices: E = 320, one group, 18,696 tokens, K = 1 11.2 / 15.9; E = 288, 46,004 tokens, cuts of 1 and 8, K = 2 23 / 30; E = 512,
+// Whether atomics per slot are faster than matrix products whose chunks are added up: with few slots per token or few
+// groups, as the products take the same time however few marks a tile holds.  Two straight lines, us, through some
+// 4,000 shapes (256 < E <= 512, up to 520,000 tokens; E <= 256, 522,241 to 800,000; one to eight slots, one to four
+// cuts; ids drawn evenly): Z, the updates of C (a slot's K - 1 others where it is alone in its group) and of L0, L and
+// CG (in LDS or in memory), and the workgroups that put their tables together; against Z and a time per tile, for its
+// barriers, its tokens and the bytes cleared (within 10 % for nine in ten).  A popular few experts make only the
+// atomics slower, and those of C most, so they have to be ahead by a tenth if there are such; without (one slot, or one
+// group) they may be estimated behind by an eighth, by which the line for them is too high there.  Of 1,500 shapes,
+// half of them with a Zipf router, the rule loses more than 3 % in 122 (95 Zipf ids by atomics). Atomics / matrices: E
+// = 320, one group, 18,696 tokens, K = 1 11.2 / 15.9; E = 288, 46,004 tokens, cuts of 1 and 8, K = 2 23 / 30; E = 512,
 // cuts of 16 and 64, 373,641 tokens, K = 2, Zipf 4,663 / 399; E = 64, one group, 700,000 tokens, K = 2 24 / 45.
 static bool atomics_pay(int64_t T, int64_t K, int64_t E, int ncuts, const int32_t *ng, bool in_lds, int64_t tiles, const CoocLaunch &cooc) {
   double groups = 0.0, others = 0.0, touched = 1.0;   // per slot: updates of C, words of L0, L and CG
@@ -1432,7 +1463,8 @@ extern "C" hm_status hm_swap_select(int32_t d, const int32_t *U, int32_t G, int3
     const int n = intra ? G : i < d ? U[i + 1] : 1;
     const int32_t *const z = intra ? z_intra : i < d ? z_inter[i + 1] : nullptr;
     p.fan[i] = intra ? (double)(G / U[d - 1]) : i < d ? (double)(U[i + 1] / U[i]) : 0.0;
-    // The loads into LDS are of 16 bytes.  Four terms of 64 groups (U = 1, 64, 64, 64) do not all fit: the last is read from memory.
+    // The loads into LDS are of 16 bytes.  Four terms of 64 groups (U = 1, 64, 64, 64) do not all fit: the last is read
+    // from memory.
     const int more = kSelectPairs * n / 4;
     const bool staged = i < d && G > 32 && n % 4 == 0 && ((uintptr_t)z & 15) == 0 && 16 * (fours + more) <= kSelectStaged;
     p.tile[i] = staged ? fours : -1;

@@ -127,19 +127,18 @@ def test_swap_counts_full_size(hw, oracle, name, placement):
         assert np.array_equal(Z.cpu().numpy(), ref) and st == st_ref == 0, (name, ng)
 
 
-@pytest.mark.parametrize("E,G,K,T,cuts", [(256, 64, 8, 65536, [8, 64]),       # 64 Ki-token layer: four fetch stages per chunk, four panels
-                                          (128, 32, 8, 40000, [4, 32]),       # ragged: the last chunk ends inside a stage
-                                          (96, 16, 3, 20000, [16]),           # four lanes per token: lanes beyond 128 tokens idle
-                                          (200, 8, 24, 9000, [2, 8]),         # 32 lanes per token: four passes per tile
+@pytest.mark.parametrize("E,G,K,T,cuts", [(256, 64, 8, 65536, [8, 64]),       # 64 Ki-token layer: chunks of several tiles, four panels
+                                          (128, 32, 8, 40000, [4, 32]),       # ragged: the last chunk ends inside a tile
+                                          (96, 16, 3, 20000, [16]),           # three slots per token, the last tile short
+                                          (200, 8, 24, 9000, [2, 8]),         # more than eight slots: a byte per slot from a kernel of its own, several loads a lane
                                           (48, 8, 2, 523000, [4]),            # more tokens than 16 chunks of 16-bit counts hold: chunks added up
                                           (250, 8, 6, 523001, [8]),           # ... two columns of tiles
                                           (64, 8, 1, 523000, [8]),            # ... and few slots: atomics per slot
                                           (512, 64, 8, 9001, [8, 16, 32, 64]), (320, 32, 5, 12001, [4, 8, 16, 32]), (300, 32, 3, 30000, [32]),   # added, E > 256
                                           (300, 32, 3, 30000, [4, 32]), (300, 32, 2, 60000, [4, 32]), (600, 32, 3, 5000, [4, 16])])   # ... the last two atomics, several cuts
 def test_swap_counts_long_chunks(hw, oracle, E, G, K, T, cuts):
-    """Token counts beyond what one fetch stage of a chunk covers (16 chunks x 1,024 slots-per-lane
-    passes), so the matrix kernel's outer loop, its clamped loads at a ragged end and the
-    multi-pass tiles are all exercised; the four-panel split of E > 128 too."""
+    """Token counts beyond what the sixteen chunks mark in one tile of up to 1,024 tokens each, so that the matrix kernel's
+    loop over the tiles and its ragged end are exercised; the panels of E > 128, added tables and atomics per slot too."""
     import torch
     from paper_2508_09591_amd import binding as B
     rng = np.random.default_rng(E + T)
@@ -161,7 +160,7 @@ def test_swap_counts_long_chunks(hw, oracle, E, G, K, T, cuts):
 def test_swap_counts_on_crowded_tokens(hw, oracle, E, G, ng, K, T):
     """Tokens full of repeated experts and of experts that share a group, the highest expert id and
     experts without a valid placement, around the eight slots up to which the matrix kernel works the
-    slots out itself and around its tile of 128 tokens."""
+    slots out itself."""
     rng = np.random.default_rng(E + K)
     ids = rng.integers(0, E, (T, K), dtype=np.int32)
     crowd = rng.random(T) < 0.5
