@@ -811,23 +811,24 @@ def run_planner(args, emit=True, workload=None):
                "sample": "the whole %s batch once (incremental Z update for %d cuts + selection), %.2f s" % (wl.name, len(cuts), dt)}
         log("cpu oracle: %.2f s" % dt)
     swap_ms = kern[names[2]]
-    # The co-occurrence tables are matrix products over 0/1 indicator tiles in FP4 (E <= 256): per cut
-    # C = A^T S (E_pad x E_pad x T) and CG = S^T M (E_pad x 32 ceil(ng/32) x T).  Their dense operation count
-    # against the int8 MFMA peak (half of the FP4 one) is what the line reports; the products themselves are a small part of the
-    # call (filling the tiles, barriers and LDS latency, and three short launches, set its time).
-    e_pad = 32 * (1 if E <= 32 else 2 if E <= 64 else 4 if E <= 128 else 8)
-    dense_ops = sum(2 * e_pad * (e_pad + 32 * ((u + 31) // 32)) * T for u in cuts) if E <= 256 else 0
-    peak_ops = 5.0e15
+    # The co-occurrence tables are matrix products over 0/1 indicator tiles in FP4 (E <= 256): per cut C = A^T S (rows x
+    # columns x T) and CG = S^T M (columns x 32 ceil(ng/32) x T), rows and columns of C padded to whole tiles and panels.  Their
+    # dense operation count against the FP4 MFMA peak is what the line reports; the products themselves are a small part of
+    # the call (filling the tiles, barriers and LDS latency, and two short launches, set its time).
+    rows, panel = 32 * ((E + 31) // 32), 64 if E > 128 else 32
+    cols = panel * ((E + panel - 1) // panel)
+    dense_ops = sum(2 * cols * (rows + 32 * ((u + 31) // 32)) * T for u in cuts) if E <= 256 else 0
+    peak_ops = 10.0e15
     result = {"metric": "planner (counts + d* + swap tensor Z + best pair) tokens/s", "value": round(T / (ms_per_step * 1e-3), 1),
               "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 5),
               "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int32", "data": "synthetic",
               "config": {"workload": "%s: T=%d K=%d E=%d G=%d, hierarchy U=%s, gamma=10" % (wl.name, T, K, E, G, U)},
               "roofline": {"bound": "mfma", "kernel": "hm_swap_counts_multi (swap_cooc + swap_pairs)",
                            "achieved": round(dense_ops / (swap_ms * 1e-3) / 1e12, 3), "peak": round(peak_ops / 1e12, 1),
-                           "unit": "int8 TOP/s (dense products of the 0/1 indicator tiles; peak: MI355X int8 MFMA)",
+                           "unit": "FP4 TFLOP/s (dense products of the 0/1 indicator tiles; peak: MI355X FP4 MFMA, dense)",
                            "frac": round(dense_ops / (swap_ms * 1e-3) / peak_ops, 5), "traffic": None,
                            "dense_ops_per_call": dense_ops,
-                           "note": "latency-bound: eight short launches per planner step over a few hundred KiB of input; in the "
+                           "note": "latency-bound: seven or eight short launches per planner step over a few hundred KiB of input; in the "
                                    "matrix kernel the products are a small part of the time, loads, marks and stores of the tables "
                                    "the rest"},
               "cpu_baseline": cpu, "kernels": kern, "monitored_counts": monitored}
