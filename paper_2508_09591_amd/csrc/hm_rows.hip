@@ -1065,10 +1065,10 @@ constexpr int kFlatTokens = 4096;
 // that reads the very rows that dispatch has just written, with nothing between, finds fewer of them on its own die:
 // 65,536 x 72 with one row 11.6 -> 14.1 for both.  The transpose keeps the launch order (16,384 x 2,050 with 7.7 rows
 // and its combine 227.5 -> 229.7), and so do whole lines, of which neighbours share none (8,192 x 7,168 with 3.6 rows
-// 159.8 -> 162.3).
-static inline bool near_pays(const RowForm &f) {
+// 159.8 -> 162.3).  Nor is there anything to group below one whole round of the dies.
+static inline bool near_pays(const RowForm &f, dim3 grid) {
   const int64_t row = (int64_t)f.H * f.elem_bytes, tokens = f.T * row;
-  return !f.lines && row >= 32 && tokens <= (row <= 1400 ? 130000000 : 80000000);
+  return !f.lines && row >= 32 && tokens <= (row <= 1400 ? 130000000 : 80000000) && grid.x >= kDies * kNear;
 }
 
 // Whether the bf16 transpose of ragged rows has the reads of eight rows in flight, which hides its rounding: for up to
@@ -1247,14 +1247,15 @@ extern "C" hm_status hm_dispatch_pack(const void *x_bf16, int32_t T, int32_t K, 
   uint16_t *packed = (uint16_t *)packed_bf16;
   const RowForm form = row_form(T, K, H, 2, x_bf16, packed_bf16);
   const Route route = spread_route(form, plan, false);
-  const bool near = near_pays(form);
   if (route == Route::kFlat) {
     if (!grid_for_flat(p, H, 8, grid)) return HM_ERR_SHAPE;
+    const bool near = near_pays(form, grid);
     hipLaunchKernelGGL((near ? spread_flat_kernel<RowBf16, false, true> : spread_flat_kernel<RowBf16, false, false>), grid,
                        dim3(kFlatThreads), 0, stream, p, x, nullptr, packed_rows, packed);
   } else if (route != Route::kElems) {
     const bool whole = route == Route::kWhole;
     if (!grid_for_units(p, H, 8, whole, packed_bf16, 1, kCopyThreads, grid)) return HM_ERR_SHAPE;
+    const bool near = near_pays(form, grid);
     const unsigned lds = lds_cap_bytes(form.lines ? dispatch_waves_per_cu(plan, T, H) : kCopyWavesPerCu, kCopyThreads);
     if (whole)
       hipLaunchKernelGGL((near ? dispatch_rows_kernel<true> : dispatch_rows_kernel<false>), grid, dim3(kCopyThreads), lds, stream, p, x,

@@ -89,28 +89,30 @@ def plan(T, K, most, rows):
 def kernel(rc):
     assert rc == 0
     one, = launched()
-    return one["name"]
+    return one["name"], one["grid"][0]
 """
 
 
 def test_dispatch_groups_workgroups_by_sizes_alone(recorder):
     """Rows off the line grid: 128 neighbours on one die for rows of 32 bytes or more and up to 80 MB of tokens, 130 MB up to 1,400 bytes a
-    row, for each kernel that has the choice and whatever is known of the rows per token; whole lines keep the launch order."""
+    row, and at least one whole round of 1,024 workgroups, for each kernel that has the choice and whatever is known of the rows per
+    token; whole lines keep the launch order."""
     result = launch_recorder.run(recorder, _ROWS + r"""
 result = []
 for T, H, off in ((4097, 1030, 0), (38834, 1030, 0), (38835, 1030, 0), (8192, 15, 0), (8192, 17, 0), (92857, 700, 0), (92858, 700, 0), (65000, 701, 0),
-                  (65536, 72, 0), (100, 7161, 0), (4096, 1024, 16), (4096, 1024, 0), (65536, 100, 0)):
+                  (65536, 72, 0), (100, 7161, 0), (136, 7161, 0), (137, 7161, 0), (4096, 1024, 16), (4096, 1024, 0), (65536, 100, 0)):
     names = set()
     for most, rows in ((8, None), (0, None), (8, 1.2), (8, 3.0), (8, 5.6), (8, 7.7)):
         x, out = at(1), ctypes.c_void_p(at(2).value + off)
         names.add(kernel(L.hm_dispatch_pack(x, T, 8, H, plan(T, 8, most, rows), out, 8 * T, None)))
-    result.append([T, H, off, sorted(names)])
+    result.append([T, H, off, sorted(names)])   # of kernel and grid
 """)
-    assert len({n.split("<")[0] for r in result for n in r[3]}) >= 3   # spread_ragged, spread_flat, dispatch_rows
+    assert len({n.split("<")[0] for r in result for n, _ in r[3]}) >= 3   # spread_ragged, spread_flat, dispatch_rows
+    assert {g >= 1024 for r in result for _, g in r[3]} == {False, True}
     for T, H, off, names in result:
-        near = (H % 64 != 0 or off != 0) and 2 * H >= 32 and 2 * T * H <= (130e6 if 2 * H <= 1400 else 80e6)
-        for name in names:
-            assert name.startswith("dispatch_elems") or name.endswith("true>") == near, (T, H, off, name)
+        sizes = (H % 64 != 0 or off != 0) and 2 * H >= 32 and 2 * T * H <= (130e6 if 2 * H <= 1400 else 80e6)
+        for name, grid in names:
+            assert name.startswith("dispatch_elems") or name.endswith("true>") == (sizes and grid >= 1024), (T, H, off, name, grid)
 
 
 def test_transpose_reads_eight_rows_for_a_row_count_not_for_a_bound(recorder):
@@ -121,7 +123,7 @@ result = []
 for T, H in ((16384, 1030), (4097, 1030), (3398, 1030), (3399, 1030), (16384, 2050)):
     for K, most, rows in ((8, 8, None), (8, 0, None), (8, 8, 1.2), (8, 8, 6.9), (8, 8, 7.2), (8, 8, 8), (6, 6, None), (6, 6, 5.8), (5, 5, 4.2), (4, 4, 4), (10, 10, 9.9)):
         for fn, bits in (("hm_combine_transpose_bf16", 16), ("hm_combine_transpose", 32)):
-            result.append([T, H, K, rows, bits, kernel(getattr(L, fn)(at(1), T, K, H, plan(T, K, most, rows), at(2), 8 * T, None))])
+            result.append([T, H, K, rows, bits, kernel(getattr(L, fn)(at(1), T, K, H, plan(T, K, most, rows), at(2), 8 * T, None))[0]])
 """)
     for T, H, K, rows, bits, name in result:
         eight = bits == 16 and rows is not None and K <= 8 and rows > max(K - 1, 4.25) and 2 * T * H >= 7e6
