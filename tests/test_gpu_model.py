@@ -81,10 +81,11 @@ def test_counts_at_the_edges(hw, oracle, T, K, E, nodes, rpn):
 
 
 @pytest.mark.parametrize("T,K,E", [(512, 64, 5000), (513, 64, 5000), (1024, 32, 4097), (1100, 4, 1023), (1100, 4, 1024), (1100, 12, 3071),
-                                   (1100, 11, 3072), (300000, 1, 511), (300000, 1, 512), (1025, 7, 300)])
+                                   (1100, 11, 3072), (300000, 1, 511), (300000, 1, 512), (1025, 7, 300), (20000, 24, 3000), (20000, 18, 4096),
+                                   (2000000, 1, 2047), (2000000, 1, 2048), (2000000, 1, 4096)])
 def test_counts_where_the_placement_is_staged(hw, oracle, T, K, E):
-    """Sizes on either side of those at which the placement table goes through LDS, and at which one workgroup
-    counts, with pieces of fewer than eight slots."""
+    """Placement tables too large for the owners, by one workgroup and by several, and by owners up to 4,096 experts; many ids, or so many
+    tokens, that the outputs are added to, with the placement in LDS and, where a lane has few to look up, in memory."""
     import torch
     from paper_2508_09591_amd import binding as B
     rng = np.random.default_rng(T + K)
@@ -116,15 +117,15 @@ def test_counts_of_no_tokens(hw, E):
 
 
 @pytest.mark.parametrize("T,K,E,nodes,rpn", [
-    (1, 1, 1, 1, 1), (256, 3, 16, 2, 2), (512, 2, 300, 2, 4), (513, 2, 300, 2, 4), (257, 8, 2048, 1, 16),   # one workgroup, then owners
-    (1024, 3, 65, 3, 5), (4096, 7, 64, 32, 2), (4097, 7, 64, 32, 2),        # up to four steps of fewer than eight ids
-    (3072, 4, 40, 2, 2), (2049, 6, 40, 2, 8), (1025, 7, 40, 2, 2), (2048, 15, 64, 2, 8), (3072, 12, 128, 4, 8),   # loads by owners, groups added
-    (8192, 8, 4096, 8, 8), (8193, 8, 63, 2, 7), (4096, 9, 128, 1, 64), (1023, 64, 130, 4, 4),   # up to eight steps of eight
-    (7168, 8, 32, 2, 8), (8192, 8, 32, 2, 8), (1024, 33, 64, 2, 2), (1025, 33, 64, 2, 2),       # few experts, long tokens
+    (1, 1, 1, 1, 1), (256, 3, 16, 2, 2), (512, 2, 300, 2, 4), (513, 2, 300, 2, 4), (257, 8, 2048, 1, 16),   # one round: windows of one id, of two, of four
+    (1024, 3, 65, 3, 5), (4096, 7, 64, 32, 2), (4097, 7, 64, 32, 2),        # windows that overlap, up to five rounds
+    (3072, 4, 40, 2, 2), (2049, 6, 40, 2, 8), (1025, 7, 40, 2, 2), (2048, 15, 64, 2, 8), (3072, 12, 128, 4, 8),   # ... and second batches that do
+    (8192, 8, 4096, 8, 8), (8193, 8, 63, 2, 7), (4096, 9, 128, 1, 64), (1023, 64, 130, 4, 4),   # up to nine rounds, eight batches; more groups than owners take whole
+    (7168, 8, 32, 2, 8), (8192, 8, 32, 2, 8), (1024, 33, 64, 2, 2), (1025, 33, 64, 2, 2),       # few experts, long tokens: by owners and, one token more, added
     (2049, 8, 4097, 4, 8), (600, 8, 5000, 4, 8), (1024, 40, 20, 2, 2),      # no room in the owners' table; many ids of few experts
     (16384, 8, 130, 4, 8), (30001, 3, 64, 3, 5), (100001, 1, 256, 8, 8), (70000, 10, 48, 2, 4), (70000, 24, 48, 2, 4)])   # tokens spread over workgroups, and beyond
 def test_counts_by_owners_and_beyond(hw, oracle, T, K, E, nodes, rpn):
-    """Both calls on both sides of the rule that gives each workgroup its own outputs: dropped, repeated and invalid ids, an
+    """Both calls by workgroups that own their outputs, by owners of a part of the tokens each, and beyond: dropped, repeated and invalid ids, an
     invalid placement, outputs that hold rubbish, entries behind a level's groups cleared."""
     import torch
     from paper_2508_09591_amd import binding as B

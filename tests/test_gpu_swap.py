@@ -135,7 +135,8 @@ def test_swap_counts_full_size(hw, oracle, name, placement):
                                           (250, 8, 6, 523001, [8]),           # ... two columns of tiles
                                           (64, 8, 1, 523000, [8]),            # ... and few slots: atomics per slot
                                           (512, 64, 8, 9001, [8, 16, 32, 64]), (320, 32, 5, 12001, [4, 8, 16, 32]), (300, 32, 3, 30000, [32]),   # added, E > 256
-                                          (300, 32, 3, 30000, [4, 32]), (300, 32, 2, 60000, [4, 32]), (600, 32, 3, 5000, [4, 16])])   # ... the last two atomics, several cuts
+                                          (300, 32, 3, 30000, [4, 32]), (300, 32, 2, 60000, [4, 32]), (600, 32, 3, 5000, [4, 16]),   # ... the last one atomics, several cuts
+                                          (288, 8, 2, 46004, [1, 8]), (300, 32, 1, 300000, [4, 32]), (600, 64, 3, 5000, [16, 32, 64])])   # atomics: E <= 512, two rounds of tokens, tables in memory
 def test_swap_counts_long_chunks(hw, oracle, E, G, K, T, cuts):
     """Token counts beyond what the sixteen chunks mark in one tile of up to 1,024 tokens each, so that the matrix kernel's
     loop over the tiles and its ragged end are exercised; the panels of E > 128, added tables and atomics per slot too."""
@@ -233,8 +234,8 @@ def test_swap_counts_where_the_slots_get_a_kernel(hw, oracle, E, K, T):
     (32, 8, 8, 8, 128), (33, 1, 64, 64, 129), (64, 4, 16, 4, 2047), (65, 7, 33, 33, 500), (128, 8, 32, 8, 8193), (129, 5, 6, 3, 700),
     (256, 8, 64, 64, 2049), (96, 9, 12, 12, 1500), (200, 33, 8, 4, 300),        # partial tables, own marks or a byte per slot
     (130, 9, 8, 8, 18500), (64, 17, 8, 4, 9001), (256, 33, 64, 64, 5000), (100, 64, 32, 32, 4500),   # ... several tiles and stages
-    (257, 8, 32, 32, 1100), (362, 3, 8, 8, 900), (363, 6, 64, 64, 900), (512, 8, 64, 16, 2000), (512, 7, 64, 64, 9100),   # added tables; room for CGT or none
-    (300, 9, 8, 8, 400), (513, 4, 8, 8, 300), (362, 3, 8, 4, 900), (512, 2, 8, 8, 24000), (300, 2, 4, 2, 300), (300, 2, 8, 8, 0)])   # atomics per slot but for the third; no tokens
+    (257, 8, 32, 32, 1100), (362, 3, 8, 8, 900), (363, 6, 64, 64, 900), (512, 8, 64, 16, 2000), (512, 7, 64, 64, 9100),   # added tables
+    (300, 9, 8, 8, 400), (513, 4, 8, 8, 300), (362, 3, 8, 4, 900), (512, 2, 8, 8, 24000), (300, 2, 4, 2, 300), (300, 2, 8, 8, 0)])   # atomics per slot (the first two), added tables of few slots and of no tokens
 def test_swap_counts_at_the_lines_between_the_kernels(hw, oracle, E, K, G, ng, T):
     """Repeated, dropped and invalid ids, an invalid placement, a workspace full of rubbish, run twice on it."""
     import torch

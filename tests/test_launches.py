@@ -141,3 +141,54 @@ for E in (16, 128, 256):
 """)
     for rc, names in result:
         assert rc == 0 and len(names) == 2 and names[1] == "swap_pairs_kernel<unsigned short, 16>", names
+
+
+def test_counts_take_the_kernel_their_sizes_ask_for(recorder):
+    """One kernel of each kind for loads and group counts, and one workgroup only where the owners' table has no room."""
+    result = launch_recorder.run(recorder, r"""
+result = []
+for T, K, E in ((0, 8, 64), (256, 2, 16), (8192, 8, 128), (1024, 64, 4096), (1024, 8, 4097), (600, 8, 8193), (16384, 8, 128), (100001, 1, 256), (30001, 3, 64),
+                (70000, 24, 48), (2000000, 1, 4096), (5000, 8, 5000)):
+    names = []
+    L.hm_expert_load(at(1), at(2), T, K, E, B.hm_topology(4, 8), at(3), at(4), at(5), at(6), None)
+    names.append([k["name"] for k in launched()])
+    L.hm_group_counts(at(1), at(2), T, K, E, 32, 2, (ctypes.c_int32 * 2)(32, 4), at(3), at(4), None)
+    result.append([T, K, E, names + [[k["name"] for k in launched()]]])
+""")
+    seen = set()
+    for T, K, E, both in result:
+        for names, what in zip(both, ("load", "group")):
+            seen.update(names)
+            width = 4 if K >= 4 else 2 if K >= 2 else 1
+            alone = T <= 1024 and (E <= 8192 if what == "load" else T * K <= 32768)
+            if E > 4096 and alone:
+                assert names == ["%s_count_kernel<1024, true>" % what], (T, K, E, names)
+            elif E > 4096:
+                assert names == ["%s_clear_kernel" % what, "%s_count_kernel<256, false>" % what], (T, K, E, names)
+            else:
+                assert names in (["%s_owner_kernel<%d, false>" % (what, width)], ["%s_clear_kernel" % what, "%s_owner_kernel<%d, true>" % (what, width)],
+                                 ["%s_clear_kernel" % what, "%s_count_kernel<256, false>" % what]), (T, K, E, names)
+    assert len(seen) == 2 * (1 + 1 + 1 + 3 + 2), sorted(seen)   # clear, one workgroup, added, spread, whole of two widths
+
+
+def test_swap_tables_take_the_kernels_their_sizes_ask_for(recorder):
+    """Matrix products with partial tables, with added ones, and atomics per slot with their tables in LDS and in memory."""
+    result = launch_recorder.run(recorder, r"""
+result = []
+for E, K, G, T, cuts, way in ((128, 8, 32, 8192, [4, 32], "parts"), (256, 9, 32, 8192, [32], "slots"), (256, 8, 32, 522240, [32], "parts"), (256, 8, 32, 522241, [32], "added"),
+                              (257, 8, 32, 8192, [32], "added"), (512, 8, 64, 9001, [8, 64], "added"), (513, 8, 32, 8192, [32], "atomics"), (300, 9, 8, 400, [8], "atomics"),
+                              (288, 2, 8, 46004, [1, 8], "atomics"), (300, 1, 32, 300000, [4, 32], "atomics"), (64, 1, 8, 523000, [8], "atomics"),
+                              (600, 3, 64, 5000, [16, 32, 64], "memory")):
+    Z = (ctypes.c_void_p * len(cuts))(*[at(3 + i).value for i in range(len(cuts))])
+    rc = L.hm_swap_counts_multi(at(1), at(2), T, K, E, G, len(cuts), (ctypes.c_int32 * len(cuts))(*cuts), Z, at(10), at(11), 1 << 40, None)
+    result.append([E, K, T, way, rc, launched()])
+""")
+    for E, K, T, way, rc, launches in result:
+        cols = 2 if 128 < E <= 256 else 1
+        want = {"parts": ["swap_cooc_kernel<%d, true, false>" % cols, "swap_pairs_kernel<unsigned short, 16>"],
+                "slots": ["swap_slots_kernel", "swap_cooc_kernel<%d, false, false>" % cols, "swap_pairs_kernel<unsigned short, 16>"],
+                "added": ["swap_cooc_kernel<%d, true, true>" % cols, "swap_pairs_kernel<int, 1>"]}.get(way, ["swap_factors_kernel", "swap_build_kernel"])
+        assert rc == 0 and [k["name"] for k in launches] == ["swap_clear_kernel"] + want, (E, K, T, way, launches)
+        assert all(k["lds"] <= k["granted"] for k in launches), launches
+        if way in ("atomics", "memory"):
+            assert (launches[1]["lds"] > 0) == (way == "atomics"), launches
