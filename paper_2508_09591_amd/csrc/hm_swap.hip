@@ -614,11 +614,11 @@ __global__ __launch_bounds__(kCoocThreads) void swap_cooc_kernel(CoocParams p) {
 // Z from the tables: a workgroup takes the pairs of two blocks of up to 16 experts, (r, c) and (c, r), as Z[r][c] =
 // Z[c][r]. It sums the chunks of what these pairs need (two blocks of C, the CG rows of 32 experts, every value of C
 // once for the whole chip), puts the two changed counts of every pair together in LDS, and writes both orientations.
-// What bounds it is waiting: by the counters its waves wait for memory, LDS or one another 58 % of their time with 128
-// experts and 47 % with 256, for an instruction to be fetched or issued 17 % and 31 %; their vector instructions (some
+// What bounds it is waiting: by the counters its waves wait for memory, LDS or one another 59 % of their time with 128
+// experts and 48 % with 256, for an instruction to be fetched or issued 16 % and 32 %; their vector instructions (some
 // 250 a wave) take 0.5 us and 2.0 us of the SIMDs' time, and it writes Z and nothing else.  Kernel trace, 128 experts,
 // 16,384 tokens, four cuts: a kernel that summed the chunks and wrote transposes of C and CG, and one that looked them
-// up per value of Z, 4.4 + 5.7 us, now 6.3; 256 experts, 8,192 tokens (15.7 MB of Z) 6.2 + 7.6, now 9.2.
+// up per value of Z, 4.4 + 5.7 us, now 6.2; 256 experts, 8,192 tokens (15.7 MB of Z) 6.2 + 7.6, now 9.0.
 constexpr int kPairThreads = 512;
 struct PairCut {
   const void *tables;
